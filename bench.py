@@ -31,6 +31,7 @@ if ROOT not in sys.path:
 # rate. The 32x32+64 integer multiply-add itself reaches 0.66 - 0.74 of it (bench_peak.py measures that,
 # profiles/peak_microbench.md holds the figures); the nominal figure stays the denominator.
 PEAK_MAD32_PER_S = 256 * 64 * 2.4e9
+PEAK_INT8_OPS_PER_S = 5.0e15  # dense
 
 # HBM bytes of the encryption launch at the profiled shape (2048-bit key, 65536 elements): rocprofv3 --pmc
 # FETCH_SIZE / WRITE_SIZE, each scaled by what the counter reads for a 1 GiB device copy. The figure is
@@ -270,6 +271,9 @@ def main():
     algo_mad = B * mm * montmul_mul32(limbs)
     achieved = algo_mad / (enc_ms * 1e-3)
     executed = B * api.haflo_op_work(pub, _cabi.OP_ENCRYPT) / (enc_ms * 1e-3)
+    # the matrix cores' part: per product four products of a constant matrix (one byte row per stored residue byte of
+    # 69 primes) with the bytes of 71 values of 4 bytes, 2 operations per byte product
+    matrix_ops = B * mm * 4 * 2 * (69 * 4) * (71 * 4) / (enc_ms * 1e-3) if bits == 2048 else None
 
     # outside the timed steps: the key owner's encryption of the same batch (r^n through p^2 and
     # q^2, bit-identical ciphertexts), reported next to the headline, never inside it
@@ -297,7 +301,8 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "u32",
-        "dtype_note": "29-bit limbs in u32 words, 32x32+64-bit integer multiply-add, exact integer arithmetic",
+        "dtype_note": "exact integer arithmetic: 30-bit residues in u32 words (32x32+64-bit multiply-add) and int8 matrix "
+                      "products with int32 sums in the exponentiations, 29-bit limbs elsewhere",
         "data": "synthetic",
         "config": {"workload": "hetero-LR step at a %d-bit key: encode, encrypt, add, scalar_mul, X^T[[d]], "
                                "X[[w]], decrypt, decode" % bits,
@@ -311,22 +316,24 @@ def main():
                                        "algorithmic": "%d Montgomery-product equivalents x (2*%d^2+%d) mul32 per "
                                                       "encryption" % (mm_o, limbs_o, limbs_o)},
         "stage_ms": {k: v / args.steps for k, v in stage_ms.items()},
-        "roofline": {"bound": "alu", "kernel": "k_engine_pairs (encryption program on pairs of residues modulo n)", "achieved": achieved / 1e12,
-                     "peak": PEAK_MAD32_PER_S / 1e12, "unit": "TOP/s", "op": "32x32+64-bit integer multiply-add",
-                     "frac": achieved / PEAK_MAD32_PER_S,
+        "roofline": {"bound": "mfma", "kernel": "k_rns (powers modulo n^2 on pairs of residues modulo n, residue number system)",
+                     "achieved": matrix_ops / 1e12 if matrix_ops else None, "peak": PEAK_INT8_OPS_PER_S / 1e12, "unit": "TOP/s",
+                     "op": "int8 matrix product",
+                     "frac": matrix_ops / PEAK_INT8_OPS_PER_S if matrix_ops else None,
                      "traffic": TRAFFIC_BYTES_PROFILED.get((bits, B)),
                      "traffic_unit": "bytes per launch",
                      "traffic_source": "%s (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE on this launch shape); "
                                        "not measured in this run" % TRAFFIC_PROFILE,
-                     "accounting": "achieved counts every product of the exponentiation schedule as a word-serial "
-                                   "Montgomery product on 32-bit limbs, 2 L^2 + L multiply-adds, squarings included; the "
-                                   "kernel needs fewer: it works modulo n^2 on pairs of half-length residues (5/8 of the "
-                                   "limb products of a product, 0.57 of a squaring's) in 29-bit limbs",
+                     "accounting": "achieved counts the byte products the reductions of the exponentiation schedule need "
+                                   "(no padding); the launch's time includes taking elements into the residue form and out of it",
+                     "conventional": achieved / 1e12,
+                     "conventional_note": "every product of the schedule as a word-serial Montgomery product on 32-bit "
+                                          "limbs (2 L^2 + L multiply-adds), in 10^12 per second; the vector units' peak for that "
+                                          "instruction is %.1f" % (PEAK_MAD32_PER_S / 1e12),
                      "executed": executed / 1e12,
                      "frac_executed": executed / PEAK_MAD32_PER_S,
-                     "executed_note": "v_mad_u64_u32 the kernel really issues per second, in 10^12, and their share of "
-                                      "the same peak; a stream of nothing but this instruction sustains 0.66 of that "
-                                      "peak at the kernel's four wavefronts per SIMD (profiles/peak_microbench.md)",
+                     "executed_note": "32x32+64-bit multiply-adds the vector units really issue per second, in 10^12, and "
+                                      "their share of their peak (profiles/peak_microbench.md)",
                      "algorithmic": "%d Montgomery products x (2*%d^2+%d) mul32 per encryption" % (mm, limbs, limbs)},
     }
     if not args.no_cpu:

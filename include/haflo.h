@@ -26,7 +26,10 @@
  *   staging calls and the store's upload / download copy and may wait.
  * Workspace: operators that need temporary device memory take a caller-supplied
  *   workspace pointer and its size; haflo_workspace_bytes says how much is
- *   needed. The library never allocates device memory inside an operator call.
+ *   needed. Encryption, decryption and what contains them ask for more than they
+ *   need from some batch size on (the window tables of a faster engine) and run
+ *   without that engine when they get less. The library never allocates device
+ *   memory inside an operator call.
  *   Contents of the workspace are undefined afterwards; two calls that share a
  *   workspace must be ordered on one stream.
  *
@@ -142,11 +145,12 @@ int haflo_ctx_set_xtd_bucket_min_rows(haflo_ctx* ctx, size_t min_rows);
  * of p^2). Either output may be NULL. */
 int haflo_op_cost(const haflo_ctx* ctx, int op, uint64_t* montmuls, uint32_t* modulus_limbs);
 
-/* The multiply-adds (32x32+64-bit, on 29-bit limbs) the kernels really execute
- * for one element of an operator on the path a chip-filling batch takes, all
- * lanes together: the squarings leave out the symmetric half of their limb
- * products and the arithmetic modulo n^2 (p^2, q^2) runs on pairs of half-length
- * residues, so this is well below haflo_op_cost's products times (2 L^2 + L).
+/* The 32x32+64-bit multiply-adds the vector units really execute for one element
+ * of an operator on the path a chip-filling batch takes, all lanes together:
+ * the exponentiations run in a residue number system whose reductions are
+ * matrix products of bytes on the matrix cores (public keys of 512 to 2048
+ * bits, private keys of 1024 to 4096), else on pairs of half-length residues in
+ * 29-bit limbs, so this is far below haflo_op_cost's products times (2 L^2 + L).
  * Defined for HAFLO_OP_ENCRYPT on a public context and HAFLO_OP_DECRYPT. */
 int haflo_op_work(const haflo_ctx* ctx, int op, uint64_t* mads_executed);
 
@@ -243,9 +247,9 @@ int haflo_decrypt(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_plain,
  * in a fixed array of HAFLO_STATIC_SCRATCH_BYTES inside the library's device
  * image (one copy per GPU, held until the process ends; its address is
  * resolved when a context is created). No allocation of any kind happens in
- * the call. Limit: haflo_workspace_bytes(ctx, HAFLO_OP_DECRYPT, count, 0) <=
- * HAFLO_STATIC_SCRATCH_BYTES (about 5000 / 1400 / 600 elements at 1024 / 2048 /
- * 4096-bit keys), otherwise HAFLO_ETOOBIG and nothing is launched. All calls on
+ * the call. Limit: the temporaries of a decryption without the engine of large
+ * batches (the least haflo_decrypt accepts) in HAFLO_STATIC_SCRATCH_BYTES (about
+ * 5000 / 1400 / 600 elements at 1024 / 2048 / 4096-bit keys), otherwise HAFLO_ETOOBIG and nothing is launched. All calls on
  * one GPU share the array: calls that overlap (different streams, threads or
  * contexts on the same GPU) race; order them on one stream.
  */

@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhaflo.so")
 PEAK_LIB = os.path.join(HERE, "libhaflo_peak.so")  # the roofline microbenchmarks, a library of their own
-SOURCES = ["ctx.cpp", "staging.cpp", "store.cpp", "kernels_basic.hip", "kernels_modexp.hip", "kernels_matvec.hip", "kernels_buckets.hip", "kernels_loss.hip"]
+SOURCES = ["ctx.cpp", "staging.cpp", "store.cpp", "kernels_basic.hip", "kernels_modexp.hip", "kernels_rns.hip", "kernels_matvec.hip", "kernels_buckets.hip", "kernels_loss.hip"]
 PEAK_SOURCES = ["peak_microbench.hip", "limb_variants.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -6,6 +6,7 @@
 #include <new>
 
 #include "haflo_internal.hpp"
+#include "rns.hpp"
 
 namespace haflo {
 
@@ -374,6 +375,47 @@ static void build_prog_decrypt(DevProg& p, const Big& e, Uploader& up) {
   p.d_ins = up.put(p.host);
 }
 
+// The RNS engine's tables for ms = s and the pair constants that lead into its Montgomery form and out of it
+// (`out` R / M_A is what a result in that form is multiplied with), added to `special`.
+static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
+                      std::vector<std::pair<int, Big>>& special, Uploader& up) {
+  if (!rns::regs_for(ms.nl)) return;
+  ms.d_rns = up.put(rns::build_tables(s, ms.nl, &ms.rns_radix));
+  const Big R = Big::mod(Big::pow2((size_t)kLimbBits * ms.nl), s2);
+  Big c = Big::mod(ms.rns_radix, s2);
+  for (int i = kConstM1; i <= kConstM4; ++i) {
+    c = Big::mod(Big::mul(c, R), s2);
+    special.push_back({i, c});
+  }
+  // out R / M_A modulo s^2, one prime of M_A after the other: 1 / a = (1 + s^2 t) / a with t = -1 / s^2 mod a
+  const MontHost mh(s2);
+  Big inv = mh.to_mont(Big::mod(Big::mul(out, R), s2));
+  for (uint32_t a : rns::primes(rns::primes_for(rns::regs_for(ms.nl)), 3)) {
+    const uint32_t t = a - rns::invmod(s2.mod_small(a), a);
+    const Big num = Big::add(Big::mul(s2, Big((uint64_t)t)), Big(1));
+    std::vector<uint32_t> q(num.w.size());
+    uint64_t rem = 0;
+    for (size_t i = num.w.size(); i-- > 0;) {
+      rem = rem << 32 | num.w[i];
+      q[i] = (uint32_t)(rem / a);
+      rem %= a;
+    }
+    inv = mh.mul(inv, mh.to_mont(Big::from_words(q.data(), q.size())));
+  }
+  special.push_back({kConstMOut, mh.from_mont(inv)});
+}
+static void put_prog(DevProg& p, std::vector<uint32_t> ins, int table_entries, Uploader& up) {
+  p.host = std::move(ins);
+  p.table_entries = table_entries;
+  p.d_ins = up.put(p.host);
+}
+static void build_prog_rns(DevProg& p, const HostSched& sched, Uploader& up) {
+  p.sched = sched;
+  std::vector<uint32_t> ins;
+  append_modexp(ins, sched);
+  put_prog(p, std::move(ins), sched.table_len + 1, up);
+}
+
 static std::vector<uint32_t> to_words(const Big& x, int nw) {
   std::vector<uint32_t> r(nw, 0);
   for (int i = 0; i < nw; ++i) r[i] = x.word(i);
@@ -419,13 +461,23 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
     const Big r2 = Big::mod(Big::mul(R, R), ctx->nsq), r3 = Big::mod(Big::mul(r2, R), ctx->nsq);
     // out of the pair form: times R R_N from a plain pair, times R_N from a pair in Montgomery form; into it
     // from a stored ciphertext W = w_lo + R w_hi (= c R_N): w_lo times R^2 / R_N plus w_hi times R^3 / R_N
-    build_pair_consts(ctx->Nh, n, ctx->nsq,
-                      {{kConstExtra, Big::mod(Big::mul(R, RN), ctx->nsq)},
-                       {kConstR3, RN},
-                       {kConstR4, Big::mod(Big::mul(r2, rn_inv), ctx->nsq)},
-                       {kConstR5, Big::mod(Big::mul(r3, rn_inv), ctx->nsq)}},
-                      up);
+    std::vector<std::pair<int, Big>> special = {{kConstExtra, Big::mod(Big::mul(R, RN), ctx->nsq)},
+                                                {kConstR3, RN},
+                                                {kConstR4, Big::mod(Big::mul(r2, rn_inv), ctx->nsq)},
+                                                {kConstR5, Big::mod(Big::mul(r3, rn_inv), ctx->nsq)}};
     build_prog_encrypt_pairs(ctx->prog_enc_pairs, ctx->prog_enc.sched, up);
+    if (!p) {
+      // r -> r M_A; the power; -> r^n R R_N -> times (1 + m n): the ciphertext in the stored Montgomery form
+      build_rns(ctx->Nh, n, ctx->nsq, Big::mod(Big::mul(R, RN), ctx->nsq), special, up);
+      if (ctx->Nh.d_rns) {
+        build_prog_rns(ctx->prog_rns_enc, ctx->prog_enc.sched, up);
+        put_prog(ctx->prog_rns_enc_in, {eng_ins(ENG_LOAD_W, 1), eng_ins(ENG_MUL_C, kConstM1)}, 1, up);
+        put_prog(ctx->prog_rns_enc_out,
+                 {eng_ins(ENG_LOAD_COL), eng_ins(ENG_MUL_C, kConstMOut), eng_ins(ENG_STORE_T, 0),
+                  eng_ins(ENG_LOAD_W1, 0), eng_ins(ENG_MUL_T, 0)}, 1, up);
+      }
+    }
+    build_pair_consts(ctx->Nh, n, ctx->nsq, special, up);
   }
   ctx->d_n_words = up.put(to_words(n, ctx->lp));
   ctx->d_nb_words = up.put(to_words(Big::sub(n, Big::pow2(64)), ctx->lp));
@@ -442,8 +494,13 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
     if (!up.ok) return HAFLO_ENOMEM;
     build_prog_decrypt(ctx->prog_dec_p, Big::sub(*p, Big(1)), up);
     build_prog_decrypt(ctx->prog_dec_q, Big::sub(*q, Big(1)), up);
-    build_pair_consts(ctx->P, *p, ctx->P2.mod, {}, up);
-    build_pair_consts(ctx->Q, *q, ctx->Q2.mod, {}, up);
+    for (int side = 0; side < 2; ++side) {
+      ModHost& ms = side ? ctx->Q : ctx->P;
+      const ModHost& ms2 = side ? ctx->Q2 : ctx->P2;
+      std::vector<std::pair<int, Big>> special;
+      build_rns(ms, ms.mod, ms2.mod, Big(1), special, up);
+      build_pair_consts(ms, ms.mod, ms2.mod, special, up);
+    }
     build_prog_decrypt_pairs(ctx->prog_dec_pairs_p, ctx->prog_dec_p.sched, up);
     build_prog_decrypt_pairs(ctx->prog_dec_pairs_q, ctx->prog_dec_q.sched, up);
     {
@@ -455,6 +512,22 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
       build_prog_encrypt_lift(ctx->prog_lift_q, *q, up);
       build_prog_lift_pairs(ctx->prog_lift_pairs_p, ctx->prog_lift_p.sched, up);
       build_prog_lift_pairs(ctx->prog_lift_pairs_q, ctx->prog_lift_q.sched, up);
+      if (ctx->P.d_rns) {
+        build_prog_rns(ctx->prog_rns_dec_p, ctx->prog_dec_p.sched, up);
+        build_prog_rns(ctx->prog_rns_dec_q, ctx->prog_dec_q.sched, up);
+        build_prog_rns(ctx->prog_rns_lift_p, ctx->prog_lift_p.sched, up);
+        build_prog_rns(ctx->prog_rns_lift_q, ctx->prog_lift_q.sched, up);
+        std::vector<uint32_t> in;
+        for (uint32_t k = 0; k < 4; ++k) {  // as in build_prog_decrypt_pairs
+          in.push_back(eng_ins(ENG_LOAD_L, k));
+          in.push_back(eng_ins(ENG_MUL_C, kConstM1 + k));
+          if (k) in.push_back(eng_ins(ENG_ADD_T, 0));
+          if (k < 3) in.push_back(eng_ins(ENG_STORE_T, 0));
+        }
+        put_prog(ctx->prog_rns_dec_in, in, 1, up);
+        put_prog(ctx->prog_rns_lift_in, {eng_ins(ENG_LOAD_L, 0), eng_ins(ENG_MUL_C, kConstM1)}, 1, up);
+        put_prog(ctx->prog_rns_priv_out, {eng_ins(ENG_LOAD_COL), eng_ins(ENG_MUL_C, kConstMOut)}, 1, up);
+      }
       // (p^2)^-1 mod q^2 = (p^2)^(q(q-1)-1) mod q^2 (p is a unit there), kept in Montgomery form
       const Big& q2 = ctx->Q2.mod;
       MontHost mq2(q2);
@@ -658,6 +731,12 @@ uint64_t plain_sqr_mads(uint64_t nl, int lpt) { return nl * (nl / lpt) * (sq_pro
 // the pair arithmetic runs with 9 limbs per lane: two windows, three (two for a squaring) products and two reductions
 uint64_t pair_mul_mads(uint64_t nl) { return nl * (nl / 9) * 45 + 2 * nl; }
 uint64_t pair_sqr_mads(uint64_t nl) { return nl * (nl / 9) * (sq_products(9) + 27) + 2 * nl; }
+// the RNS engine's vector multiply-adds per prime of a base: the residue products and their reductions in both bases
+// (5 each, 6 for a product of two elements), the columns and reductions of what the matrix products return (9 + 6)
+uint64_t rns_mads(const haflo::HostSched& s, int nl) {
+  const uint64_t lanes = (uint64_t)haflo::rns::slots(haflo::rns::regs_for(nl));
+  return lanes * (s.nsquare * 25 + s.nmul * 27);
+}
 }  // namespace
 
 int haflo_op_work(const haflo_ctx* ctx, int op, uint64_t* mads_executed) {
@@ -667,7 +746,8 @@ int haflo_op_work(const haflo_ctx* ctx, int op, uint64_t* mads_executed) {
     // pairs modulo n: the power, three more products (into Montgomery form, the (1 + m n) factor, out of the
     // pair form) and the plain product n x1 of the stored integer
     const uint64_t nl = (uint64_t)ctx->Nh.nl;
-    w = ctx->prog_enc.sched.nsquare * pair_sqr_mads(nl) + (ctx->prog_enc.sched.nmul + 3) * pair_mul_mads(nl) + nl * nl;
+    if (ctx->Nh.d_rns) w = rns_mads(ctx->prog_enc.sched, ctx->Nh.nl) + 3 * pair_mul_mads(nl) + nl * nl;
+    else w = ctx->prog_enc.sched.nsquare * pair_sqr_mads(nl) + (ctx->prog_enc.sched.nmul + 3) * pair_mul_mads(nl) + nl * nl;
   } else if (op == HAFLO_OP_DECRYPT) {
     if (!ctx->has_priv) return HAFLO_ENOPRIV;
     // out of Montgomery form modulo n^2; per prime: four products into the pair form, the power, one out;
@@ -675,7 +755,8 @@ int haflo_op_work(const haflo_ctx* ctx, int op, uint64_t* mads_executed) {
     const uint64_t nl = (uint64_t)ctx->P.nl;
     w = plain_mul_mads((uint64_t)ctx->N.nl, ctx->N.lpt);
     for (const haflo::DevProg* dp : {&ctx->prog_dec_p, &ctx->prog_dec_q})
-      w += dp->sched.nsquare * pair_sqr_mads(nl) + (dp->sched.nmul + 5) * pair_mul_mads(nl);
+      if (ctx->P.d_rns) w += rns_mads(dp->sched, ctx->P.nl) + 5 * pair_mul_mads(nl);
+      else w += dp->sched.nsquare * pair_sqr_mads(nl) + (dp->sched.nmul + 5) * pair_mul_mads(nl);
     w += 3 * plain_mul_mads(nl, ctx->P.lpt) + nl * nl;
   } else {
     return HAFLO_EINVAL;

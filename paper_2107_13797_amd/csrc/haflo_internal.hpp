@@ -62,9 +62,15 @@ enum EngOp : uint32_t {
   ENG_LOAD_L = 14,   // acc = limbs [a*NL, (a+1)*NL) of the element's limb input
   ENG_LOAD_TD = 15,  // acc = table[(k >> a) & 15]
   ENG_LOAD_WH = 16,  // acc = limbs [NL, 2 NL) of the element's 32-bit-word input a: the part above ENG_LOAD_W's
-  ENG_LOAD_W1 = 17   // pair engine only: acc = 1 + n w for the element's 32-bit-word input a
+  ENG_LOAD_W1 = 17,  // pair engine only: acc = 1 + n w for the element's 32-bit-word input a
+  ENG_LOAD_COL = 18  // pair engine only: acc = the element's two integers in columns (an RNS engine's result)
 };
-enum { kConstR1 = 0, kConstR2 = 1, kConstR3 = 2, kConstOne = 3, kConstExtra = 4, kConstR4 = 5, kConstR5 = 6, kNumConst = 7 };
+enum {
+  kConstR1 = 0, kConstR2 = 1, kConstR3 = 2, kConstOne = 3, kConstExtra = 4, kConstR4 = 5, kConstR5 = 6,
+  // into the RNS engine's Montgomery form (radix M_A) and out of it: R^k M_A for k = 1 .. 4, and an operator's own
+  kConstM1 = 7, kConstM2 = 8, kConstM3 = 9, kConstM4 = 10, kConstMOut = 11,
+  kNumConst = 12
+};
 inline uint32_t eng_ins(uint32_t op, uint32_t a = 0, uint32_t b = 0) { return op | (a << 8) | (b << 20); }
 
 // acc = acc^e for the plan `h`, using table slots [0, h.table_len] (the last one as scratch)
@@ -90,6 +96,8 @@ struct ModHost {
   // each, [x0 | x1], indexed by kConst*: R, R^2, R^3, 1, an operator-specific one, R^4, R^5, all modulo
   // mod^2 with R = 2^(29 nl). Null where the modulus is not used that way.
   uint32_t* d_pairs = nullptr;
+  uint32_t* d_rns = nullptr;  // device tables of the RNS engine on pairs modulo mod (rns.hpp), null: no such engine
+  Big rns_radix;              // its Montgomery radix
   ModRef ref() const {
     ModRef r;
     r.n = d_tab;
@@ -124,6 +132,10 @@ struct haflo_ctx {
   haflo::DevProg prog_enc_pairs;   // encryption with the public key on pairs modulo n
   haflo::DevProg prog_dec_pairs_p, prog_dec_pairs_q;    // decryption branches on pairs modulo p, q
   haflo::DevProg prog_lift_pairs_p, prog_lift_pairs_q;  // key owner's encryption, second stage, on pairs modulo p, q
+  // the RNS engine's programs: the powers alone, and what takes elements into its form and out of it on the pair engine
+  haflo::DevProg prog_rns_enc, prog_rns_enc_in, prog_rns_enc_out;
+  haflo::DevProg prog_rns_dec_p, prog_rns_dec_q, prog_rns_dec_in;
+  haflo::DevProg prog_rns_lift_p, prog_rns_lift_q, prog_rns_lift_in, prog_rns_priv_out;
   haflo::DevProg prog_enc;     // encryption: r^n modulo n^2 and the (1 + m n) factor
   haflo::DevProg prog_dec_p;   // decryption branch: c^(p-1) modulo p^2
   haflo::DevProg prog_dec_q;   // decryption branch: c^(q-1) modulo q^2
@@ -181,10 +193,12 @@ std::vector<uint32_t> to_limbs29(const Big& x, int nl);
 int static_scratch_init();
 
 // workspace sizes in bytes (kernels_modexp.hip)
-size_t ws_encrypt(const haflo_ctx* ctx, size_t count);
+size_t ws_encrypt(const haflo_ctx* ctx, size_t count);      // what a call asks for
+size_t ws_encrypt_min(const haflo_ctx* ctx, size_t count);  // what it can do with (without the RNS engine)
 size_t ws_scalar_mul(const haflo_ctx* ctx, size_t count);
 size_t ws_encrypt_obf(const haflo_ctx* ctx, size_t count);
 size_t ws_decrypt(const haflo_ctx* ctx, size_t count);
+size_t ws_decrypt_min(const haflo_ctx* ctx, size_t count);
 // workspace of the Taylor-loss sequence in bytes (kernels_loss.hip)
 size_t ws_taylor_loss(const haflo_ctx* ctx, size_t count);
 
@@ -194,6 +208,18 @@ int power_tables(const haflo_ctx* ctx, const uint32_t* d_c, uint32_t* d_tables, 
 
 // out[i] = in[i]^-1 mod n^2 on internal ciphertexts; out may alias in (kernels_matvec.hip)
 int invert_batch(const haflo_ctx* ctx, const uint32_t* in, uint32_t* out, size_t count, hipStream_t st);
+
+// Powers of pairs modulo m[i]^2 by the RNS engine (kernels_rns.hip), one or two moduli of the same size side by
+// side: elements [x0 limbs][x1 limbs] at in[i] to columns at out[i], `count` <= rns_chunk() of them.
+struct RnsBuffers {  // workspace of one chunk, in 32-bit words from its start
+  size_t in[2], out[2], tables, total;
+};
+bool rns_pays(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs);
+size_t rns_chunk(const haflo_ctx* ctx, int jobs);
+int rns_columns(const ModHost& m);
+RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs, int entries);
+int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, const haflo_ctx* ctx, uint32_t* ws,
+              const RnsBuffers& b, size_t count, int entries, hipStream_t st);
 
 // X^T [[d]] by the bucket method (kernels_buckets.hip). Workspace layout in 32-bit words.
 struct XtdBucketPlan {

@@ -356,8 +356,8 @@ int haflo_fore_gradient(const haflo_ctx* ctx, const void* d_c_host, const float*
   // workspace: [guest plaintexts][their encryptions][encryption workspace]
   const size_t plain_bytes = (count * (size_t)ctx->lp * 4 + 255) & ~(size_t)255;
   const size_t cipher_bytes = (count * (size_t)ctx->N.nl * 4 + 255) & ~(size_t)255;
-  const size_t enc_bytes = haflo_workspace_bytes(ctx, HAFLO_OP_ENCRYPT, count, 0);
-  if (!d_workspace || workspace_bytes < plain_bytes + cipher_bytes + enc_bytes) return HAFLO_EINVAL;
+  if (!d_workspace || workspace_bytes < plain_bytes + cipher_bytes + ws_encrypt_min(ctx, count)) return HAFLO_EINVAL;
+  const size_t enc_bytes = workspace_bytes - plain_bytes - cipher_bytes;
   uint32_t* plain = (uint32_t*)d_workspace;
   char* guest = (char*)d_workspace + plain_bytes;
   int z = 2;

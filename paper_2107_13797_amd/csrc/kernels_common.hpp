@@ -97,6 +97,8 @@ struct EngineIO {
   int table_per_item;              // 1: slot = element index (tables are an output), 0: slot = lane group
   size_t first;                    // index of the launch's first element in the per-element arrays
   int out_mode;                    // pair engine: what is stored, see kOut*
+  const long long* in_cols;        // per-element pairs of integers in columns of weight 2^29, in_cols_stride each
+  int in_cols_stride;
 };
 
 // The exponentiation engine: every lane group runs the batch-uniform program
@@ -223,7 +225,24 @@ __device__ __forceinline__ void pair_to_integer(u32 (&lo)[LPT], u32 (&hi)[LPT], 
 // limb input as (l, 0). When the program ends, acc holds the result X as a pair; io.out_mode says what is
 // stored: kOutInteger, the canonical integer x0 + s x1 on 2 NL limbs (low half, high half); kOutSecond, the
 // canonical x1 on NL limbs, for results that are 1 modulo s (x0 = 1), whose (X - 1) / s it is.
-enum { kOutInteger = 0, kOutSecond = 1 };
+// kOutPair: [x0][x1] as they are (lazy limbs).
+enum { kOutInteger = 0, kOutSecond = 1, kOutPair = 2 };
+// Signed columns of weight 2^(29 j), |column| < 2^47, of an integer in [0, 2^(29 NL)): its canonical limbs
+template <int LPT, int T>
+__device__ __forceinline__ void load_columns(u32 (&x)[LPT], const long long* p, const Grp<T>& g) {
+  s32 d[LPT];
+  s64 c = 0;
+#pragma unroll
+  for (int j = 0; j < LPT; ++j) {
+    const s64 v = (g.live() ? p[g.k * LPT + j] : 0) + c;
+    d[j] = (s32)((u32)v & LIMB_MASK);
+    c = v >> LIMB_BITS;
+  }
+  d[0] += (s32)g.from_lower((u32)(s32)c);  // a carry past the top limb is dropped: the value has none
+  resolve<LPT, T>(d, g);
+#pragma unroll
+  for (int j = 0; j < LPT; ++j) x[j] = (u32)d[j];
+}
 template <int LPT, int T, class Prog>
 __device__ __forceinline__ void engine_run_pairs(const ModRef& M, const Prog& P, const EngineIO& io, size_t count,
                                                  unsigned block, unsigned nblocks) {
@@ -304,7 +323,18 @@ __device__ __forceinline__ void engine_run_pairs(const ModRef& M, const Prog& P,
         else if (io.in_limbs_valid) load_limbs_below<LPT, T>(x0, src, io.in_limbs_valid - (int)a * NL, g);
         else load_limbs<LPT, T>(x0, src, g);
         zero_limbs<LPT>(x1);
+      } else if (op == ENG_LOAD_COL) {
+        const long long* src = io.in_cols + (active ? item : 0) * (size_t)(2 * io.in_cols_stride);
+        load_columns<LPT, T>(x0, src, g);
+        load_columns<LPT, T>(x1, src + io.in_cols_stride, g);
       }
+    }
+    if (io.out_mode == kOutPair) {
+      if (active) {
+        store_limbs<LPT, T>(io.out + item * (size_t)(2 * NL), x0, g);
+        store_limbs<LPT, T>(io.out + item * (size_t)(2 * NL) + NL, x1, g);
+      }
+      continue;
     }
     pair_canonical<LPT, T>(x0, x1, mod.n, g);
     if (io.out_mode == kOutSecond) {

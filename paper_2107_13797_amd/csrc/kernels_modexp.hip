@@ -19,7 +19,7 @@ std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};  // device address of `scratch` on each device, once resolved
 
 int decrypt_launches(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_plain, size_t count, void* d_workspace,
-                     hipStream_t st);
+                     size_t workspace_bytes, hipStream_t st);
 
 constexpr int kModexpBlocksPerCu = 4;  // resident blocks assumed when sizing window-table workspace
 
@@ -349,6 +349,67 @@ int launch_power_batch(const haflo_ctx* ctx, hipStream_t st, const ProgInline& p
   return launch_engine(m, b.tail, st, pi, io, count - full);
 }
 
+// Powers of `count` elements by the RNS engine, at most rns_chunk() at a time: the pair engine takes each chunk into
+// the RNS engine's Montgomery form (`in`), that raises it (`power`), and the pair engine takes the result to what the
+// operator stores (`out`). `src` and `dst` describe the whole arrays of each job; `ws` is rns_buffers(...).total words.
+int launch_rns(const haflo_ctx* ctx, int jobs, const ModHost* const* m, const DevProg& in, const DevProg* const* power,
+               const DevProg& out, const EngineIO* src, const EngineIO* dst, size_t out_words, size_t count, u32* ws,
+               hipStream_t st) {
+  int entries = 1;
+  for (int i = 0; i < jobs; ++i) entries = std::max(entries, power[i]->table_entries);
+  const RnsBuffers b = rns_buffers(ctx, *m[0], count, jobs, entries);
+  const size_t chunk = rns_chunk(ctx, jobs);
+  const int t = 2 * m[0]->t;  // lanes per element of the pair engine
+  for (size_t base = 0; base < count; base += chunk) {
+    const size_t n = std::min(chunk, count - base);
+    for (int step = 0; step < 3; ++step) {
+      if (step == 1) {
+        if (int rc = rns_power(m, power, jobs, ctx, ws, b, n, entries, st)) return rc;
+        continue;
+      }
+      LaunchShape sh = launch_shape(ctx, n, t, kModexpBlocksPerCu);
+      EngineJob job[2];
+      for (int i = 0; i < jobs; ++i) {
+        const DevProg& prog = step ? out : in;
+        EngineIO io = pair_io(*m[i], step ? dst[i] : src[i]);
+        for (int k = 0; k < 2; ++k)
+          if (io.in_words[k]) io.in_words[k] += base * (size_t)io.in_nwords;
+        if (io.in_limbs) io.in_limbs += base * (size_t)io.in_limbs_stride;
+        if (step) {
+          io.out_mode = dst[i].out_mode;
+          io.in_cols = (const long long*)(ws + b.out[i]);
+          io.in_cols_stride = rns_columns(*m[i]);
+          io.out += base * out_words;
+        } else {
+          io.out_mode = kOutPair;
+          io.out = ws + b.in[i];
+        }
+        io.tables = ws + b.tables + (size_t)i * sh.slots() * (size_t)(2 * m[i]->nl);
+        io.table_entries = 1;
+        job[i].M = m[i]->ref();
+        job[i].P = ProgPtr{prog.d_ins, (int)prog.host.size()};
+        job[i].io = io;
+      }
+      int rc;
+      if (jobs == 1) {
+        rc = launch_engine_pairs(*m[0], sh, st, job[0].P, job[0].io, n);
+      } else {
+        const unsigned split = (unsigned)sh.blocks;
+        sh.blocks *= 2;
+        rc = launch_engine_pairs2(*m[0], sh, st, job[0], job[1], split, n);
+      }
+      if (rc != HAFLO_OK) return rc;
+    }
+  }
+  return HAFLO_OK;
+}
+// bytes of workspace an RNS launch of `count` elements takes, its start aligned to 256 bytes
+size_t rns_bytes(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs, const DevProg& p0, const DevProg& p1) {
+  if (!rns_pays(ctx, m, count, jobs)) return 0;
+  return rns_buffers(ctx, m, count, jobs, std::max(p0.table_entries, p1.table_entries)).total * 4 + 256;
+}
+u32* align256(u32* p) { return (u32*)(((uintptr_t)p + 255) & ~(uintptr_t)255); }
+
 }  // namespace
 
 namespace haflo {
@@ -366,8 +427,8 @@ int static_scratch_init() {
   return HAFLO_OK;
 }
 
-// table slots: one set per resident lane group
-size_t ws_encrypt(const haflo_ctx* ctx, size_t count) {
+// The least an encryption runs with: table slots, one set per resident lane group
+size_t ws_encrypt_min(const haflo_ctx* ctx, size_t count) {
   if (!ctx->has_priv)
     return modexp_shape(ctx, count, ctx->N).slots() * (size_t)ctx->prog_enc.table_entries * ctx->N.nl * 4;
   // key owner: [y_p, y_q: count*P2.nl each][r^n: count*N.nl; before it is written, the first
@@ -380,6 +441,14 @@ size_t ws_encrypt(const haflo_ctx* ctx, size_t count) {
   size_t last = modexp_shape(ctx, count, ctx->N).slots() * (size_t)ctx->N.nl;
   return (2 * count * (size_t)ctx->P2.nl + count * (size_t)ctx->N.nl + std::max(std::max(low, lift), last)) * 4;
 }
+// what it asks for: with less the RNS engine is not used
+size_t ws_encrypt(const haflo_ctx* ctx, size_t count) {
+  if (!ctx->has_priv)
+    return std::max(ws_encrypt_min(ctx, count), rns_bytes(ctx, ctx->Nh, count, 1, ctx->prog_rns_enc, ctx->prog_rns_enc));
+  const size_t fixed = (2 * count * (size_t)ctx->P2.nl + count * (size_t)ctx->N.nl) * 4;
+  return std::max(ws_encrypt_min(ctx, count),
+                  fixed + rns_bytes(ctx, ctx->P, count, 2, ctx->prog_rns_lift_p, ctx->prog_rns_lift_q));
+}
 // one table slot per resident lane group
 size_t ws_encrypt_obf(const haflo_ctx* ctx, size_t count) {
   return launch_shape(ctx, count, haflo_wide_lanes(ctx->N), 8).slots() * (size_t)ctx->N.nl * 4;
@@ -389,11 +458,18 @@ size_t ws_scalar_mul(const haflo_ctx* ctx, size_t count) {
   return modexp_shape(ctx, count, ctx->N).slots() * (size_t)16 * ctx->N.nl * 4;
 }
 // layout: [canon29: count*N.nl][yp: count*P2.nl][yq: count*Q2.nl][tables]
-size_t ws_decrypt(const haflo_ctx* ctx, size_t count) {
+size_t ws_decrypt_min(const haflo_ctx* ctx, size_t count) {
   if (!ctx->has_priv) return 0;
   size_t tl = (size_t)std::max(ctx->prog_dec_p.table_entries, ctx->prog_dec_q.table_entries);
   return (count * (size_t)ctx->N.nl + 2 * count * (size_t)ctx->P2.nl +
           2 * modexp_shape(ctx, count, ctx->P2, 2).slots() * tl * ctx->P2.nl) * 4;
+}
+
+size_t ws_decrypt(const haflo_ctx* ctx, size_t count) {
+  if (!ctx->has_priv) return 0;
+  const size_t fixed = (count * (size_t)ctx->N.nl + 2 * count * (size_t)ctx->P2.nl) * 4;
+  return std::max(ws_decrypt_min(ctx, count),
+                  fixed + rns_bytes(ctx, ctx->P, count, 2, ctx->prog_rns_dec_p, ctx->prog_rns_dec_q));
 }
 
 // tables[i][d] = c_i^d, d < entries, for `count` internal ciphertexts (used by the matvec)
@@ -424,11 +500,23 @@ int haflo_encrypt(const haflo_ctx* ctx, const uint32_t* d_plain, const uint32_t*
                   void* d_workspace, size_t workspace_bytes, void* stream) {
   if (!ctx || (count && (!d_plain || !d_r || !d_cipher))) return HAFLO_EINVAL;
   if (count == 0) return HAFLO_OK;
-  if (!d_workspace || workspace_bytes < ws_encrypt(ctx, count)) return HAFLO_EINVAL;
+  if (!d_workspace || workspace_bytes < ws_encrypt_min(ctx, count)) return HAFLO_EINVAL;
   const ModHost& m = ctx->N;
   hipStream_t st = (hipStream_t)stream;
   if (!ctx->has_priv) {
     // public key: r^n with the full exponent modulo n^2
+    if (rns_pays(ctx, ctx->Nh, count, 1) && workspace_bytes >= ws_encrypt(ctx, count)) {
+      EngineIO src = engine_io(ctx->Nh), dst = src;
+      src.in_words[1] = d_r;
+      src.in_nwords = ctx->lp;
+      dst.in_words[0] = d_plain;
+      dst.in_nwords = ctx->lp;
+      dst.out = (u32*)d_cipher;
+      const ModHost* mods[1] = {&ctx->Nh};
+      const DevProg* power[1] = {&ctx->prog_rns_enc};
+      return launch_rns(ctx, 1, mods, ctx->prog_rns_enc_in, power, ctx->prog_rns_enc_out, &src, &dst, (size_t)m.nl, count,
+                        align256((u32*)d_workspace), st);
+    }
     EngineIO io = engine_io(m);
     io.constant[kConstExtra] = ctx->d_k1;
     io.in_words[0] = d_plain;
@@ -474,6 +562,23 @@ int haflo_encrypt(const haflo_ctx* ctx, const uint32_t* d_plain, const uint32_t*
   u32* y0q = y0p + count * (size_t)l.nl;
   for (int stage = 0; stage < 2; ++stage) {
     const ModHost& geo = stage ? h : l;
+    if (stage == 1 && rns_pays(ctx, l, count, 2) && workspace_bytes >= ws_encrypt(ctx, count)) {
+      EngineIO src[2], dst[2];
+      for (int side = 0; side < 2; ++side) {
+        src[side] = engine_io(side ? ctx->Q : ctx->P);
+        dst[side] = src[side];
+        src[side].in_limbs = side ? y0q : y0p;
+        src[side].in_limbs_stride = l.nl;
+        dst[side].out = side ? yq : yp;
+        dst[side].out_mode = kOutInteger;
+      }
+      const ModHost* mods[2] = {&ctx->P, &ctx->Q};
+      const DevProg* power[2] = {&ctx->prog_rns_lift_p, &ctx->prog_rns_lift_q};
+      int rc = launch_rns(ctx, 2, mods, ctx->prog_rns_lift_in, power, ctx->prog_rns_priv_out, src, dst, (size_t)h.nl, count,
+                          align256(tables), st);
+      if (rc != HAFLO_OK) return rc;
+      break;
+    }
     const DevProg* progs[2] = {stage ? &ctx->prog_lift_p : &ctx->prog_enc_p, stage ? &ctx->prog_lift_q : &ctx->prog_enc_q};
     const int tl = std::max(progs[0]->table_entries, progs[1]->table_entries);
     // the first stage (plain residues modulo the primes) runs faster on 9 limbs per lane at any batch size up
@@ -654,15 +759,15 @@ int haflo_decrypt(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_plain,
   if (!ctx || (count && (!d_cipher || !d_plain))) return HAFLO_EINVAL;
   if (!ctx->has_priv) return HAFLO_ENOPRIV;
   if (count == 0) return HAFLO_OK;
-  if (!d_workspace || workspace_bytes < ws_decrypt(ctx, count)) return HAFLO_EINVAL;
-  return decrypt_launches(ctx, d_cipher, d_plain, count, d_workspace, (hipStream_t)stream);
+  if (!d_workspace || workspace_bytes < ws_decrypt_min(ctx, count)) return HAFLO_EINVAL;
+  return decrypt_launches(ctx, d_cipher, d_plain, count, d_workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 int haflo_decrypt_static(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_plain, size_t count, void* stream) {
   if (!ctx || (count && (!d_cipher || !d_plain))) return HAFLO_EINVAL;
   if (!ctx->has_priv) return HAFLO_ENOPRIV;
   if (count == 0) return HAFLO_OK;
-  if (ws_decrypt(ctx, count) > (size_t)HAFLO_STATIC_SCRATCH_BYTES) return HAFLO_ETOOBIG;
+  if (ws_decrypt_min(ctx, count) > (size_t)HAFLO_STATIC_SCRATCH_BYTES) return HAFLO_ETOOBIG;
   if (ctx->device < 0 || ctx->device >= kMaxDevices) return HAFLO_EINVAL;
   void* ptr;
   {
@@ -672,14 +777,14 @@ int haflo_decrypt_static(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d
   if (!ptr) return HAFLO_EHIP;  // the context was created on a device whose array could not be resolved
   // every temporary of the decryption (canonical residues, both branch results, window tables) is
   // written before it is read, so nothing of an earlier call's contents has to be cleared
-  return decrypt_launches(ctx, d_cipher, d_plain, count, ptr, (hipStream_t)stream);
+  return decrypt_launches(ctx, d_cipher, d_plain, count, ptr, (size_t)HAFLO_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
 }
 
 }  // extern "C"
 
 namespace {
 int decrypt_launches(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_plain, size_t count, void* d_workspace,
-                     hipStream_t st) {
+                     size_t workspace_bytes, hipStream_t st) {
   int pairs = 0;  // the branch results are the quotients L_s on P.nl limbs, not residues modulo s^2
   u32* canon29 = (u32*)d_workspace;
   u32* yp = canon29 + count * (size_t)ctx->N.nl;
@@ -693,7 +798,23 @@ int decrypt_launches(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_pla
     HAFLO_DISPATCH_GEOMETRY(m, CALL);
 #undef CALL
   }
-  {
+  if (rns_pays(ctx, ctx->P, count, 2) && workspace_bytes >= ws_decrypt(ctx, count)) {
+    EngineIO src[2], dst[2];
+    for (int side = 0; side < 2; ++side) {
+      src[side] = engine_io(side ? ctx->Q : ctx->P);
+      dst[side] = src[side];
+      src[side].in_limbs = canon29;
+      src[side].in_limbs_stride = ctx->N.nl;
+      dst[side].out = side ? yq : yp;
+      dst[side].out_mode = kOutSecond;
+    }
+    const ModHost* mods[2] = {&ctx->P, &ctx->Q};
+    const DevProg* power[2] = {&ctx->prog_rns_dec_p, &ctx->prog_rns_dec_q};
+    int rc = launch_rns(ctx, 2, mods, ctx->prog_rns_dec_in, power, ctx->prog_rns_priv_out, src, dst, (size_t)ctx->P.nl,
+                        count, align256(tables), st);
+    if (rc != HAFLO_OK) return rc;
+    pairs = 1;
+  } else {
     // both prime-power branches in one launch: the first half of the grid works modulo p^2,
     // the second half modulo q^2, each half with its own table slots
     const ModHost& m = ctx->P2;

@@ -1,0 +1,251 @@
+// Geometry and host-built tables of the residue-number-system (RNS) engine: exponentiation modulo s^2 on pairs of
+// residues modulo s (x0 + s x1), where every half is held by its residues modulo two sets of 30-bit primes and
+// the Montgomery reductions are constant integer matrices applied to the residues' bytes on the matrix cores
+// (kernels_rns.hip has the arithmetic). Host code only builds tables here; sizes are shared with the kernels.
+//
+// Base A: k primes a_i, all 3 modulo 4; base B: k primes b_j, all 1 modulo 4; both just below 2^30. M_A, M_B are
+// their products; M_A is the Montgomery radix. A wavefront holds 16 elements, four lanes each; a lane keeps `regs`
+// residues of each base and half of the pair: channel slot 4 i + g in register i of lane group g (lane / 16).
+#pragma once
+#include <stdint.h>
+
+#include <vector>
+
+#include "hostbig.hpp"
+
+namespace haflo {
+namespace rns {
+
+constexpr uint32_t kOmega = 0x80808080u;     // bytes are fed to the signed matrix product as byte - 128
+constexpr uint64_t kBase = 1ull << 47;       // keeps a column of the matrix product non-negative
+constexpr int kOffset = 256;                 // multiple of s added to every reduced value, so that none is negative
+
+// registers per lane, base and half for a modulus of `nl` 29-bit limbs, 0: no such engine
+constexpr int regs_for(int nl) { return nl == 18 ? 6 : nl == 36 ? 10 : nl == 72 ? 18 : 0; }
+// primes per base: 30 k bits exceed the modulus's bits by 28, 26 and 22
+constexpr int primes_for(int nr) { return nr == 6 ? 18 : nr == 10 ? 35 : nr == 18 ? 69 : 0; }
+constexpr int slots(int nr) { return 4 * nr; }
+// tiles of 16 byte rows (4 slots) that hold the primes, and those that hold the limbs of a value
+constexpr int tiles(int nr) { return (primes_for(nr) + 3) / 4; }
+constexpr int limb_tiles(int nr) { return tiles(nr); }
+// the slots of the matrix products' two extra source values: the multiple of M_B to subtract, and the constant 1
+constexpr int alpha_slot(int nr) { return 4 * nr - 2; }
+constexpr int bias_slot(int nr) { return 4 * nr - 1; }
+// A tile's fragments: nr / 4 of 64 source bytes per row and, unless nr is a multiple of 4, one of 32. Of the last tile with 18 registers only the
+// first 4 rows are kept (its other slots have no prime): both matrices of a 2048-bit modulus then fit the 160 KB of LDS.
+constexpr int full_blocks(int nr) { return nr / 4; }
+constexpr int last_rows(int nr) { return nr == 18 ? 4 : 16; }
+constexpr int tile_bytes(int nr, int rows) { return full_blocks(nr) * rows * 64 + (nr % 4 ? rows * 32 : 0); }
+constexpr int lds_matrix_bytes(int nr) { return (tiles(nr) - 1) * tile_bytes(nr, 16) + tile_bytes(nr, last_rows(nr)); }
+constexpr int in_matrix_bytes(int nr) { return tiles(nr) * tile_bytes(nr, 16); }
+constexpr int out_matrix_bytes(int nr) { return limb_tiles(nr) * tile_bytes(nr, 16); }
+// constants of a slot: base A {p, -1/p, e, 0}, base B {p, -1/p, kappa, e}
+constexpr int cst_bytes(int nr) { return 2 * slots(nr) * 16; }
+
+// Device layout: [A -> B][B -> A][constants of A][of B] as the kernel copies them to LDS, then, with all rows,
+// [limbs -> B][B -> limbs]
+constexpr int lds_bytes(int nr) { return 2 * lds_matrix_bytes(nr) + cst_bytes(nr); }
+constexpr int table_bytes(int nr) { return lds_bytes(nr) + in_matrix_bytes(nr) + out_matrix_bytes(nr); }
+
+inline uint32_t mulmod(uint32_t a, uint32_t b, uint32_t p) { return (uint32_t)((uint64_t)a * b % p); }
+inline uint32_t powmod(uint32_t a, uint64_t e, uint32_t p) {
+  uint32_t r = 1 % p;
+  for (a %= p; e; e >>= 1, a = mulmod(a, a, p))
+    if (e & 1) r = mulmod(r, a, p);
+  return r;
+}
+inline uint32_t invmod(uint32_t a, uint32_t p) { return powmod(a, p - 2, p); }
+// Miller-Rabin with bases 2, 3, 5, 7: exact below 3.2 x 10^9
+inline bool is_prime30(uint32_t n) {
+  for (uint32_t d : {2u, 3u, 5u, 7u, 11u, 13u})
+    if (n % d == 0) return n == d;
+  uint32_t d = n - 1;
+  int s = 0;
+  while (!(d & 1)) d >>= 1, ++s;
+  for (uint32_t b : {2u, 3u, 5u, 7u}) {
+    uint32_t x = powmod(b, d, n);
+    bool ok = x == 1 || x == n - 1;
+    for (int i = 1; i < s && !ok; ++i) {
+      x = mulmod(x, x, n);
+      ok = x == n - 1;
+    }
+    if (!ok) return false;
+  }
+  return true;
+}
+// the k largest primes below 2^30 of a residue class, k <= 69; found once per process
+inline std::vector<uint32_t> primes(int k, uint32_t residue_mod_4) {
+  const auto find = [](uint32_t residue) {
+    std::vector<uint32_t> r;
+    for (uint32_t c = (1u << 30) - 4 + residue; (int)r.size() < primes_for(18); c -= 4)
+      if (is_prime30(c)) r.push_back(c);
+    return r;
+  };
+  static const std::vector<uint32_t> one = find(1), three = find(3);
+  const std::vector<uint32_t>& all = residue_mod_4 == 1 ? one : three;
+  return std::vector<uint32_t>(all.begin(), all.begin() + k);
+}
+// the inverses of v modulo p (p not among v's divisors), one inversion for all of them; *prod: the product of v
+inline std::vector<uint32_t> inverses(const std::vector<uint32_t>& v, uint32_t p, uint32_t* prod) {
+  std::vector<uint32_t> r(v.size());
+  uint32_t acc = 1;
+  for (size_t i = 0; i < v.size(); ++i) {
+    r[i] = acc;
+    acc = mulmod(acc, v[i] % p, p);
+  }
+  *prod = acc;
+  uint32_t inv = invmod(acc, p);
+  for (size_t i = v.size(); i-- > 0;) {
+    r[i] = mulmod(r[i], inv, p);
+    inv = mulmod(inv, v[i] % p, p);
+  }
+  return r;
+}
+inline Big product(const std::vector<uint32_t>& v) {
+  Big r(1);
+  for (uint32_t p : v) r = Big::mul(r, Big((uint64_t)p));
+  return r;
+}
+
+// Matrix with byte entries: rows are the four bytes (balanced, -128 .. 127) of a destination slot's constant,
+// columns the four bytes of a source slot. A fragment holds, as one wavefront reads it for v_mfma_i32_16x16x64_i8
+// (of the last block 8 bytes per lane), row 4 g + v of its tile for byte v of slot 4 tile + g, and in bytes 4 c + u of lane
+// group g byte u of slot 4 (4 block + c) + g.
+class Matrix {
+ public:
+  Matrix(int nr, int tiles_, int last_rows_)
+      : nr_(nr), tiles_n_(tiles_), last_(last_rows_),
+        bytes_((size_t)((tiles_ - 1) * tile_bytes(nr, 16) + tile_bytes(nr, last_rows_)), 0) {}
+  // the entry (constant) for byte u of slot `src` towards slot `dst`
+  void set(int src, int u, int dst, int64_t value) {
+    const int tile = dst / 4, g = dst % 4, block = src / 16, c = src / 4 % 4, gs = src % 4;
+    if (tile >= tiles_n_) return;
+    const int rows = tile == tiles_n_ - 1 ? last_ : 16;
+    const int width = block < full_blocks(nr_) ? 16 : 8;  // bytes per lane
+    for (int v = 0; v < 4; ++v) {
+      const int8_t b = (int8_t)(value & 0xFF);
+      value = (value - b) / 256;  // exact
+      const int row = 4 * g + v;
+      if (row >= rows) continue;  // slots without a prime
+      bytes_[(size_t)tile * tile_bytes(nr_, 16) + (size_t)block * rows * 64 + (size_t)(gs * rows + row) * width + 4 * c + u] = (uint8_t)b;
+    }
+  }
+  const std::vector<uint8_t>& bytes() const { return bytes_; }
+
+ private:
+  int nr_, tiles_n_, last_;
+  std::vector<uint8_t> bytes_;
+};
+
+// All tables for the modulus s (odd, prime to the channel primes), as one array of 32-bit words, and M_A.
+inline std::vector<uint32_t> build_tables(const Big& s, int nl, Big* m_a) {
+  const int nr = regs_for(nl), k = primes_for(nr);
+  const std::vector<uint32_t> a = primes(k, 3), b = primes(k, 1);
+  const Big ma = product(a), mb = product(b);
+  *m_a = ma;
+  const int alpha = alpha_slot(nr), bias = bias_slot(nr);
+  std::vector<uint32_t> f(k), h(k), sgn(k), cst((size_t)cst_bytes(nr) / 4, 0);
+  for (int i = 0; i < k; ++i) {
+    // x is kept as f x with f^2 = +-(-1/s) / (M_A / a_i) 2^32: the reduced product of two such residues is the
+    // coefficient of the quotient in base A itself (up to the sign, which the matrix takes)
+    const uint32_t p = a[i], w = (uint32_t)((1ull << 32) % p), sinv = invmod(s.mod_small(p), p);
+    uint32_t rest = 1;
+    for (int t = 0; t < k; ++t)
+      if (t != i) rest = mulmod(rest, a[t] % p, p);
+    const uint32_t c = mulmod(mulmod(p - sinv, invmod(rest, p), p), w, p);
+    sgn[i] = powmod(c, (p - 1) / 2, p) == 1 ? 0 : 1;
+    f[i] = powmod(sgn[i] ? p - c : c, (p + 1) / 4, p);
+    uint32_t* t = &cst[(size_t)i * 4];
+    t[0] = p;
+    t[1] = neg_inv32(p);
+    t[2] = mulmod(sinv, w, p);
+  }
+  for (int j = 0; j < k; ++j) {
+    // x is kept as h x, h = 1 / (M_B / b_j): the coefficient of x in base B itself
+    const uint32_t p = b[j], w = (uint32_t)((1ull << 32) % p), sinv = invmod(s.mod_small(p), p);
+    uint32_t rest = 1;
+    for (int t = 0; t < k; ++t)
+      if (t != j) rest = mulmod(rest, b[t] % p, p);
+    h[j] = invmod(rest, p);
+    uint32_t* t = &cst[(size_t)(slots(nr) + j) * 4];
+    t[0] = p;
+    t[1] = neg_inv32(p);
+    t[2] = mulmod(mulmod(mulmod(rest, invmod(ma.mod_small(p), p), p), w, p), w, p);
+    t[3] = mulmod(sinv, w, p);
+  }
+  Matrix ab(nr, tiles(nr), last_rows(nr)), ba(nr, tiles(nr), last_rows(nr)), in(nr, tiles(nr), 16), out(nr, limb_tiles(nr), 16);
+  const auto channel = [&](Matrix& m, int dst, uint32_t p, const std::vector<std::pair<int, uint32_t>>& src, uint32_t extra) {
+    // sources hold value - kOmega; the bias gives it back, adds `extra` and takes kBase off
+    uint32_t sum = 0;
+    for (const auto& e : src) {
+      uint32_t v = e.second;
+      sum = (uint32_t)(((uint64_t)sum + v) % p);
+      for (int u = 0; u < 4; ++u, v = mulmod(v, 256, p)) m.set(e.first, u, dst, v);
+    }
+    const uint64_t bv = (uint64_t)mulmod(sum, kOmega % p, p) + extra + (p - (uint32_t)(kBase % p));
+    m.set(bias, 0, dst, (int64_t)(bv % p));
+  };
+  for (int j = 0; j < k; ++j) {
+    const uint32_t p = b[j], w = (uint32_t)((1ull << 32) % p);
+    const uint32_t hw = mulmod(h[j], w, p), nhw = mulmod(s.mod_small(p), hw, p);
+    uint32_t ma_p;
+    const std::vector<uint32_t> ainv = inverses(a, p, &ma_p);
+    std::vector<std::pair<int, uint32_t>> src;
+    for (int i = 0; i < k; ++i) {
+      uint32_t c = mulmod(ainv[i], nhw, p);
+      if (sgn[i] && c) c = p - c;
+      src.push_back({i, c});
+    }
+    channel(ab, j, p, src, mulmod((uint32_t)kOffset, nhw, p));
+    src.clear();
+    const uint32_t step = (uint32_t)((1u << 29) % p);
+    uint32_t c = hw;
+    for (int l = 0; l < nl && l < bias; ++l, c = mulmod(c, step, p)) src.push_back({l, c});
+    channel(in, j, p, src, 0);
+  }
+  for (int i = 0; i < k; ++i) {
+    const uint32_t p = a[i], w = (uint32_t)((1ull << 32) % p);
+    uint32_t mb_p;
+    const std::vector<uint32_t> binv = inverses(b, p, &mb_p);
+    const uint32_t fw = mulmod(f[i], w, p), mbfw = mulmod(mb_p, fw, p);
+    std::vector<std::pair<int, uint32_t>> src;
+    for (int j = 0; j < k; ++j) src.push_back({j, mulmod(binv[j], mbfw, p)});
+    const int dst = i;
+    channel(ba, dst, p, src, 0);
+    const uint32_t neg = mbfw ? p - mbfw : 0;
+    ba.set(alpha, 0, dst, neg);
+    ba.set(alpha, 1, dst, mulmod(neg, 128, p));
+  }
+  // out: the integer sum rho_j M_B / b_j - alpha M_B as columns of weight 2^(29 l)
+  {
+    std::vector<Big> pre(k + 1, Big(1)), suf(k + 1, Big(1));
+    for (int j = 0; j < k; ++j) pre[j + 1] = Big::mul(pre[j], Big((uint64_t)b[j]));
+    for (int j = k - 1; j >= 0; --j) suf[j] = Big::mul(suf[j + 1], Big((uint64_t)b[j]));
+    const auto integer = [&](int src, int u, const Big& x, int sign) {
+      for (int l = 0; l < 4 * limb_tiles(nr); ++l) out.set(src, u, l, sign * (int64_t)x.extract((size_t)29 * l, 29));
+    };
+    Big total(0);
+    for (int j = 0; j < k; ++j) {
+      Big x = Big::mul(pre[j], suf[j + 1]);
+      total = Big::add(total, x);
+      for (int u = 0; u < 4; ++u, x = Big::mul(x, Big(256))) integer(j, u, x, 1);
+    }
+    integer(bias, 0, Big::mul(total, Big((uint64_t)kOmega)), 1);
+    integer(alpha, 0, mb, -1);
+    integer(alpha, 1, Big::mul(mb, Big(128)), -1);
+  }
+  std::vector<uint32_t> t;
+  const auto put = [&](const std::vector<uint8_t>& v) {
+    for (size_t o = 0; o < v.size(); o += 4)
+      t.push_back((uint32_t)v[o] | (uint32_t)v[o + 1] << 8 | (uint32_t)v[o + 2] << 16 | (uint32_t)v[o + 3] << 24);
+  };
+  put(ab.bytes());
+  put(ba.bytes());
+  t.insert(t.end(), cst.begin(), cst.end());
+  put(in.bytes());
+  put(out.bytes());
+  return t;
+}
+
+}  // namespace rns
+}  // namespace haflo

@@ -369,7 +369,7 @@ int haflo_h_encrypt(haflo_store* s, haflo_handle plain, haflo_handle r, uint32_t
   int rc = s->create(HAFLO_KIND_CIPHER, count, uses, &hc);
   if (rc != HAFLO_OK) return rc;
   Scratch ws(s);
-  if (!ws.take(haflo_workspace_bytes(s->ctx, HAFLO_OP_ENCRYPT, count, 0))) {
+  if (!ws.take(haflo_workspace_bytes(s->ctx, HAFLO_OP_ENCRYPT, count, 0)) && !ws.take(haflo::ws_encrypt_min(s->ctx, count))) {
     s->drop(hc);
     return HAFLO_ENOMEM;
   }
@@ -396,7 +396,7 @@ int haflo_h_decrypt(haflo_store* s, haflo_handle cipher, uint32_t uses, haflo_ha
   int rc = s->create(HAFLO_KIND_PLAIN, count, uses, &hp);
   if (rc != HAFLO_OK) return rc;
   Scratch ws(s);
-  if (!ws.take(want)) {
+  if (!ws.take(want) && !ws.take(haflo::ws_decrypt_min(s->ctx, count))) {
     s->drop(hp);
     return HAFLO_ENOMEM;
   }

@@ -25,6 +25,7 @@ struct Lane {
   char* stack = nullptr;
 };
 struct WaveSlots {
+  int8_t mat[2][2][kWave][16];  // operands of a matrix product, by lane
   uint32_t val[2][kWave];
   uint64_t op[2][kWave];
 };
@@ -118,6 +119,25 @@ uint64_t ballot(bool p) {
   for (int l = 0; l < kWave; ++l)
     if (t[l]) m |= 1ull << l;
   return m;
+}
+
+// D = A B + C on 16 x 16 by 64 bytes: lane l holds A[l % 16][16 (l / 16) ..], B[16 (l / 16) ..][l % 16] and, in
+// register r, C[4 (l / 16) + r][l % 16]
+void mfma_i32_16x16x64_i8(const uint32_t* a, const uint32_t* b, int32_t* c) {
+  int lane = cur->lane;
+  WaveSlots& w = waves[cur->wave];
+  const int par = (int)(cur->ops & 1);
+  memcpy(w.mat[par][0][lane], a, 16);
+  memcpy(w.mat[par][1][lane], b, 16);
+  exchange(0);
+  for (int r = 0; r < 4; ++r) {
+    int32_t sum = c[r];
+    for (int g = 0; g < 4; ++g) {
+      const int8_t *x = w.mat[par][0][16 * g + 4 * (lane / 16) + r], *y = w.mat[par][1][16 * g + lane % 16];
+      for (int k = 0; k < 16; ++k) sum += (int32_t)x[k] * (int32_t)y[k];
+    }
+    c[r] = sum;
+  }
 }
 
 void barrier() {

@@ -65,6 +65,7 @@ uint32_t dpp(uint32_t old, uint32_t src, int ctrl, int row_mask, int bank_mask, 
 uint64_t ballot(bool p);
 uint32_t readlane(uint32_t v, int src_lane);
 void barrier();
+void mfma_i32_16x16x64_i8(const uint32_t* a, const uint32_t* b, int32_t* c);
 void* dev_alloc(size_t bytes);
 void dev_free(void* p);
 }  // namespace hipemu
@@ -88,6 +89,11 @@ static inline int __builtin_amdgcn_readlane(int v, int lane) { return (int)hipem
 static inline uint64_t __builtin_amdgcn_ballot_w64(bool p) { return hipemu::ballot(p); }
 static inline void __builtin_amdgcn_sched_barrier(int) {}
 static inline void __builtin_amdgcn_sched_group_barrier(int, int, int) {}
+typedef int hipemu_v4i __attribute__((vector_size(16)));
+static inline hipemu_v4i __builtin_amdgcn_mfma_i32_16x16x64_i8(hipemu_v4i a, hipemu_v4i b, hipemu_v4i c, int, int, int) {
+  hipemu::mfma_i32_16x16x64_i8((const uint32_t*)&a, (const uint32_t*)&b, (int32_t*)&c);
+  return c;
+}
 static inline void __syncthreads() { hipemu::barrier(); }
 static inline uint32_t atomicOr(uint32_t* p, uint32_t v) {
   uint32_t o = *p;

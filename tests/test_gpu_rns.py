@@ -1,0 +1,88 @@
+"""The RNS engine (residues modulo two sets of primes, reductions on the matrix cores) against the limb arithmetic that
+serves calls whose workspace has no room for it, which is what the oracle pins: batches on both sides of the size
+from which it is used, with partial tiles of 16 elements and partial passes. Every
+comparison is of all bits of all elements."""
+import ctypes as C
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from conftest import oracle_key  # noqa: E402
+from paper_2107_13797_amd import _cabi  # noqa: E402
+
+from helpers import dev_to_ints, ints_to_dev, random_units_words, to_dev  # noqa: E402
+
+
+
+def encrypt_in(lib, ctx, m, r, nbytes, out):
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    return lib.haflo_encrypt(ctx.handle, C.c_void_p(m.data_ptr()), C.c_void_p(r.data_ptr()), C.c_void_p(out.data_ptr()),
+                             m.shape[0], C.c_void_p(ws.data_ptr()), nbytes,
+                             C.c_void_p(torch.cuda.current_stream().cuda_stream))
+
+
+def decrypt_in(lib, ctx, c, nbytes, out):
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    return lib.haflo_decrypt(ctx.handle, C.c_void_p(c.data_ptr()), C.c_void_p(out.data_ptr()), c.shape[0],
+                             C.c_void_p(ws.data_ptr()), nbytes, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+
+
+def without_engine(call, need, out):
+    """The call in ever smaller workspaces until it is refused; the smallest accepted one has no room for the engine."""
+    best = None
+    nbytes = need - 1
+    while nbytes > 4096 and call(nbytes, out) == 0:
+        best = out.clone()
+        nbytes = nbytes * 3 // 4
+    return best
+
+
+@pytest.mark.parametrize("bits,counts", [
+    (512, (1791, 1792, 4097)),
+    (1024, (1791, 1792, 1809, 65536 + 17)),
+    (2048, (2559, 2561, 65536 + 1)),
+    (4096, (1279, 1297)),  # decryption: the primes' 2048 bits
+])
+def test_rns_engine_matches_limb_arithmetic(bits, counts):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    lib = api.lib()
+    p, q = oracle_key(bits)
+    n = p * q
+    top = max(counts)
+    # edges: the smallest and largest values, and randomness that is no unit or not reduced modulo n
+    edge_m = [0, 1, n - 1, n // 2, 0, n - 1]
+    edge_r = [1, n - 1, 2, 2 ** (bits - 1), 0, min(n + 2, 2 ** bits - 1)]
+    m = to_dev(random_units_words(top, bits, bits + 1))
+    r = to_dev(random_units_words(top, bits, bits + 2))
+    m[:6], r[:6] = ints_to_dev(edge_m, bits // 32)[:top], ints_to_dev(edge_r, bits // 32)[:top]
+    pub = api.haflo_ctx_create_public(n, bits)
+    prv = api.haflo_ctx_create_private(p, q, bits)
+    for count in counts:
+        print("rns", bits, count, flush=True)
+        mc, rc = m[:count].contiguous(), r[:count].contiguous()
+        need = lib.haflo_workspace_bytes(pub.handle, _cabi.OP_ENCRYPT, count, 0)
+        c, out = api.haflo_encrypt(pub, mc, rc), None
+        out = torch.zeros_like(c)
+        want = without_engine(lambda nb, o: encrypt_in(lib, pub, mc, rc, nb, o), need, out)
+        if want is not None:
+            assert torch.equal(c, want)
+        for i in {0, count // 2, count - 1}:
+            mi, ri = dev_to_ints(mc[i:i + 1])[0], dev_to_ints(rc[i:i + 1])[0]
+            assert dev_to_ints(api.haflo_export_cipher(pub, c[i:i + 1].contiguous()))[0] == \
+                (1 + mi * n) * pow(ri, n, n * n) % (n * n)
+        assert torch.equal(api.haflo_encrypt(prv, mc, rc), c)
+        plain = api.haflo_decrypt(prv, c)
+        need = lib.haflo_workspace_bytes(prv.handle, _cabi.OP_DECRYPT, count, 0)
+        want = without_engine(lambda nb, o: decrypt_in(lib, prv, c, nb, o), need, torch.zeros_like(plain))
+        keep = torch.arange(count, device="cuda") != 4  # r = 0 gives no ciphertext: what it decrypts to is not defined
+        if want is not None:
+            assert torch.equal(plain[keep], want[keep])
+        assert torch.equal(plain[keep], mc[keep])
+        del c, plain, want, out
+    pub.close()
+    prv.close()
