@@ -214,7 +214,6 @@ int invert_batch(const haflo_ctx* ctx, const uint32_t* in, uint32_t* out, size_t
 struct RnsBuffers {  // workspace of one chunk, in 32-bit words from its start
   size_t in[2], out[2], tables, total;
 };
-bool rns_pays(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs);
 size_t rns_chunk(const haflo_ctx* ctx, int jobs);
 int rns_columns(const ModHost& m);
 RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs, int entries);

@@ -405,7 +405,7 @@ int launch_rns(const haflo_ctx* ctx, int jobs, const ModHost* const* m, const De
 }
 // bytes of workspace an RNS launch of `count` elements takes, its start aligned to 256 bytes
 size_t rns_bytes(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs, const DevProg& p0, const DevProg& p1) {
-  if (!rns_pays(ctx, m, count, jobs)) return 0;
+  if (!m.d_rns || count == 0) return 0;
   return rns_buffers(ctx, m, count, jobs, std::max(p0.table_entries, p1.table_entries)).total * 4 + 256;
 }
 u32* align256(u32* p) { return (u32*)(((uintptr_t)p + 255) & ~(uintptr_t)255); }
@@ -505,7 +505,7 @@ int haflo_encrypt(const haflo_ctx* ctx, const uint32_t* d_plain, const uint32_t*
   hipStream_t st = (hipStream_t)stream;
   if (!ctx->has_priv) {
     // public key: r^n with the full exponent modulo n^2
-    if (rns_pays(ctx, ctx->Nh, count, 1) && workspace_bytes >= ws_encrypt(ctx, count)) {
+    if (ctx->Nh.d_rns && workspace_bytes >= ws_encrypt(ctx, count)) {
       EngineIO src = engine_io(ctx->Nh), dst = src;
       src.in_words[1] = d_r;
       src.in_nwords = ctx->lp;
@@ -562,7 +562,7 @@ int haflo_encrypt(const haflo_ctx* ctx, const uint32_t* d_plain, const uint32_t*
   u32* y0q = y0p + count * (size_t)l.nl;
   for (int stage = 0; stage < 2; ++stage) {
     const ModHost& geo = stage ? h : l;
-    if (stage == 1 && rns_pays(ctx, l, count, 2) && workspace_bytes >= ws_encrypt(ctx, count)) {
+    if (stage == 1 && l.d_rns && workspace_bytes >= ws_encrypt(ctx, count)) {
       EngineIO src[2], dst[2];
       for (int side = 0; side < 2; ++side) {
         src[side] = engine_io(side ? ctx->Q : ctx->P);
@@ -798,7 +798,7 @@ int decrypt_launches(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_pla
     HAFLO_DISPATCH_GEOMETRY(m, CALL);
 #undef CALL
   }
-  if (rns_pays(ctx, ctx->P, count, 2) && workspace_bytes >= ws_decrypt(ctx, count)) {
+  if (ctx->P.d_rns && workspace_bytes >= ws_decrypt(ctx, count)) {
     EngineIO src[2], dst[2];
     for (int side = 0; side < 2; ++side) {
       src[side] = engine_io(side ? ctx->Q : ctx->P);

@@ -32,6 +32,11 @@ typedef u32 Quad __attribute__((vector_size(16)));
 typedef u32 Twin __attribute__((vector_size(8)));
 typedef int Acc __attribute__((vector_size(16)));  // also a matrix operand of 16 bytes
 
+template <int N>
+struct QuadSet {
+  Acc q[N];
+};
+
 struct RnsJob {
   const u32* tables;  // rns.hpp's device layout
   const u32* prog;    // ENG_SQ, ENG_MUL_T, ENG_MUL_T_ST, ENG_STORE_T, ENG_LOAD_T only
@@ -88,10 +93,10 @@ __device__ __forceinline__ u32 reduce(u64 t, u32 p, u32 pinv) {
 }
 
 struct RnsConsts {
-  s32 k65536, one;  // hidden from the compiler, so that the column sums stay multiply-adds
+  s32 k65536, k256, one;  // hidden from the compiler, so that the column sums stay multiply-adds
   s64 base;
-  __device__ __forceinline__ RnsConsts() : k65536(65536), one(1), base((s64)rns::kBase) {
-    asm volatile("" : "+r"(k65536), "+r"(one), "+r"(base));
+  __device__ __forceinline__ RnsConsts() : k65536(65536), k256(256), one(1), base((s64)rns::kBase) {
+    asm volatile("" : "+r"(k65536), "+r"(k256), "+r"(one), "+r"(base));
   }
 };
 
@@ -103,9 +108,16 @@ __device__ __forceinline__ u32 to_bytes(u32 v) {
   return v;
 }
 
-// the four byte rows of a slot as one number; BASE: 2^47 added
-template <bool BASE>
+// the four byte rows of a slot as one number; BASE: 2^47 added. WIDE: for sums of more than 500 byte products, two of
+// which do not fit 32 bits side by side
+template <bool BASE, bool WIDE = false>
 __device__ __forceinline__ s64 column(const Acc& acc, const RnsConsts& kc) {
+  if constexpr (WIDE) {
+    const s32 top = (s32)((u32)acc[3] << 8) + acc[2];
+    s64 w = (s64)top * (s64)kc.k65536 + (BASE ? kc.base : (s64)0);
+    w = (s64)acc[1] * (s64)kc.k256 + w;
+    return (s64)acc[0] * (s64)kc.one + w;
+  }
   const s32 lo = (s32)((u32)acc[1] << 8) + acc[0];
   const s32 hi = (s32)((u32)acc[3] << 8) + acc[2];
   const s64 t = (s64)hi * (s64)kc.k65536 + (BASE ? kc.base : (s64)0);
@@ -449,6 +461,317 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
   }
 }
 
+// The same arithmetic with the slots of 16 M elements spread over the W wavefronts of a block, TW tiles each, for
+// batches that would leave most of the chip idle with a wavefront per 16 elements, and for moduli whose matrices do not
+// fit the LDS. A wavefront keeps the residues of its own slots and multiplies and reduces them alone; what every
+// wavefront needs of the others, the bytes of all residues, goes through LDS (16 bytes per lane and block of 64, as the
+// matrix product reads its operand), one barrier before each of the two matrix products of a modular product. The
+// matrices stay in registers where they fit (kHeld: 16 to 80 of them), else they stream from L2. What bounds it is the
+// issue of the few wavefronts of a chain and, at 4096 bits, the 630 KB of both matrices per product (64 bytes per clock
+// and compute unit). Measured against the limb arithmetic on one wavefront per integer: 1024 encryptions at a 1024-bit
+// key 2.67 -> 1.04 ms, 256 at 2048 bits 8.5 -> 3.9, 3001 at 4096 bits 74.9 -> 27.2; 3072 decryptions at 1024 bits 1.33
+// -> 0.53 ms, 64 at 4096 bits 8.63 -> 4.01.
+template <int NR, int TW, int W, int M>
+struct RnsGroup {
+  static constexpr int kTiles = rns::tiles(NR);
+  static constexpr int kLimbTiles = rns::limb_tiles(NR);
+  static constexpr int kBlocks = (NR + 3) / 4;  // of 64 bytes, the last one partly empty
+  static constexpr int kFull = rns::full_blocks(NR);
+  static constexpr int kLast = rns::last_rows(NR);
+  static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
+  static constexpr bool kHeld = TW * kBlocks <= 10;
+  static constexpr bool kWide = NR > 32;
+  static_assert(W * TW >= kLimbTiles, "every tile has a wavefront");
+  struct Shared {
+    Quad bytes[2][M][2][kBlocks][WAVE];  // [sigma, rho][elements][x0, x1][block][lane]
+    u32 sum[3][M][2][16];                // alpha's sums, of the last, the present and the next rho
+  };
+  struct State {
+    u32 a0[TW][M], a1[TW][M], b0[TW][M], b1[TW][M];
+  };
+  using Frags = QuadSet<TW * kBlocks>;
+  Shared& sh;
+  const char* tables;
+  int lane, g, wave, turn;
+  RnsConsts kc;
+  Quad ka[TW], kb[TW];  // the constants of this lane's slots
+  Frags held[kHeld ? 2 : 1];
+
+  __device__ __forceinline__ bool mine(int i, int tiles = kTiles) const { return wave * TW + i < tiles; }
+  // a wavefront without a tile of its own repeats the last one and keeps the result to itself
+  __device__ __forceinline__ int tile(int i, int tiles = kTiles) const { return mine(i, tiles) ? wave * TW + i : tiles - 1; }
+  // this lane holds a prime's residue (not one of the extra values) in tile i
+  __device__ __forceinline__ bool owns(int i) const { return mine(i) && (tile(i) < NR - 1 || g < 2); }
+
+  // `l`: the lane
+  __device__ __forceinline__ Acc fragment(const char* matrix, int tiles, int last, int i, int k, unsigned l) const {
+    const int t = tile(i, tiles), rows = t == tiles - 1 ? last : 16;
+    const char* p = matrix + t * kTileBytes + k * rows * 64;
+    const unsigned at = ((l >> 4) * (unsigned)rows + (l & (unsigned)(rows - 1))) * 16;
+    if (k < kFull) return *(const Acc*)(p + at);
+    const Twin h = *(const Twin*)(p + at / 2);
+    return Acc{(int)h[0], (int)h[1], 0, 0};
+  }
+
+  __device__ __forceinline__ RnsGroup(Shared& shared, const u32* tables_)
+      : sh(shared), tables((const char*)tables_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4),
+        wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))), turn(0) {
+    const char* cst = tables + 2 * rns::lds_matrix_bytes(NR);
+#pragma unroll
+    for (int i = 0; i < TW; ++i) {
+      ka[i] = *(const Quad*)(cst + (4 * tile(i) + g) * 16);
+      kb[i] = *(const Quad*)(cst + (rns::slots(NR) + 4 * tile(i) + g) * 16);
+    }
+    if (kHeld)
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int i = 0; i < TW; ++i)
+#pragma unroll
+          for (int k = 0; k < kBlocks; ++k)
+            held[m].q[i * kBlocks + k] = fragment(tables + m * rns::lds_matrix_bytes(NR), kTiles, kLast, i, k, (unsigned)lane);
+    for (int i = (int)threadIdx.x; i < (int)(sizeof(Shared) / 4); i += (int)blockDim.x) ((u32*)&sh)[i] = 0;
+    __syncthreads();
+    set_bias();
+  }
+  // the constant 1 of the bias: lane group 3 of the last register, which no wavefront writes
+  __device__ __forceinline__ void set_bias() {
+    if (threadIdx.x < 16)
+      for (int b = 0; b < 2; ++b)
+        for (int m = 0; m < M; ++m)
+          for (int x = 0; x < 2; ++x) word(b, m, x, NR - 1, 48 + (int)threadIdx.x) = 1;
+  }
+  __device__ __forceinline__ u32& word(int buffer, int m, int x, int i, int l) const {
+    return ((u32*)&sh.bytes[buffer][m][x][i / 4][l])[i % 4];
+  }
+
+  // r = the tiles' products with the bytes in `buffer`, after all wavefronts have written theirs. MATRIX 0, 1: the two
+  // of the modular product; ALPHA: lane group 2 of the last register takes alpha.
+  template <int MATRIX, bool ALPHA>
+  __device__ __forceinline__ void products(Acc (&r)[TW][M][2], int buffer, const char* matrix, int tiles, int last) {
+    unsigned l = (unsigned)lane;
+    asm volatile("" : "+v"(l));  // or the addresses of all fragments are kept in registers from one product to the next
+    u32 alpha[M][2];
+    if (ALPHA) {
+      const int now = (turn + 2) % 3;  // of the last publish()
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const u32 a = (sh.sum[now][m][x][lane & 15] + (1u << 13)) >> 14;
+          alpha[m][x] = (a & 127u) | ((a >> 7) << 8);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) r[i][m][0] = r[i][m][1] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < kBlocks; ++k) {
+      // what streams in is asked for three blocks ahead at most, as far as the registers go
+      if (!(kHeld && MATRIX < 2) && k % 3 == 0) __builtin_amdgcn_sched_barrier(0);
+      Acc f[TW];
+#pragma unroll
+      for (int i = 0; i < TW; ++i)
+        f[i] = kHeld && MATRIX < 2 ? held[MATRIX < 2 ? MATRIX : 0].q[i * kBlocks + k] : fragment(matrix, tiles, last, i, k, l);
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        Quad d0 = sh.bytes[buffer][m][0][k][lane], d1 = sh.bytes[buffer][m][1][k][lane];
+        if (ALPHA && k == (NR - 1) / 4) {
+          d0[(NR - 1) % 4] = g == 2 ? alpha[m][0] : d0[(NR - 1) % 4];
+          d1[(NR - 1) % 4] = g == 2 ? alpha[m][1] : d1[(NR - 1) % 4];
+        }
+#pragma unroll
+        for (int i = 0; i < TW; ++i) {
+          r[i][m][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d0, r[i][m][0], 0, 0, 0);
+          r[i][m][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d1, r[i][m][1], 0, 0, 0);
+        }
+      }
+    }
+  }
+  // base B's bytes and alpha's sums to the other wavefronts
+  __device__ __forceinline__ void publish(const State& x) {
+    u32* s = &sh.sum[turn][0][0][0];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      u32 s0 = 0, s1 = 0;
+#pragma unroll
+      for (int i = 0; i < TW; ++i)
+        if (owns(i)) {
+          word(1, m, 0, tile(i), lane) = x.b0[i][m] ^ rns::kOmega;
+          word(1, m, 1, tile(i), lane) = x.b1[i][m] ^ rns::kOmega;
+          s0 += x.b0[i][m] >> 16;
+          s1 += x.b1[i][m] >> 16;
+        }
+      atomicAdd(s + (m * 2 + 0) * 16 + (lane & 15), s0);
+      atomicAdd(s + (m * 2 + 1) * 16 + (lane & 15), s1);
+    }
+    __syncthreads();
+    // the sums of the publish() before this one were last read before this barrier and are next added to after the
+    // barrier that follows it
+    const int clear = (turn + 2) % 3;
+    if (threadIdx.x < 32)
+      for (int i = (int)threadIdx.x; i < M * 32; i += 32) (&sh.sum[clear][0][0][0])[i] = 0;
+    turn = (turn + 1) % 3;
+  }
+  // base A from what publish() left
+  __device__ __forceinline__ void extend_to_a(State& x) {
+    Acc r[TW][M][2];
+    products<1, true>(r, 1, tables + rns::lds_matrix_bytes(NR), kTiles, kLast);
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        x.a0[i][m] = reduce((u64)column<true, kWide>(r[i][m][0], kc), ka[i][0], ka[i][1]);
+        x.a1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), ka[i][0], ka[i][1]);
+      }
+  }
+  // x times the table entry y, or (null) squared
+  template <bool SQ>
+  __device__ __forceinline__ void multiply(State& x, const u32* y) {
+    u32 z[TW][M], w[TW][M];
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const Quad v = SQ ? Quad{x.a0[i][m], x.a1[i][m], x.b0[i][m], x.b1[i][m]} : *entry_at(y, i, m);
+        const u32 s0 = reduce(mad64(x.a0[i][m], v[0], 0), ka[i][0], ka[i][1]);
+        const u64 ca = SQ ? mad64(x.a0[i][m] << 1, x.a1[i][m], 0) : mad64(x.a0[i][m], v[1], mad64(x.a1[i][m], v[0], 0));
+        const u32 s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
+        if (owns(i)) {
+          word(0, m, 0, tile(i), lane) = s0 ^ rns::kOmega;
+          word(0, m, 1, tile(i), lane) = s1 ^ rns::kOmega;
+        }
+        z[i][m] = reduce(mad64(x.b0[i][m], v[2], 0), kb[i][0], kb[i][1]);
+        const u64 cb = SQ ? mad64(x.b0[i][m] << 1, x.b1[i][m], 0) : mad64(x.b0[i][m], v[3], mad64(x.b1[i][m], v[2], 0));
+        w[i][m] = reduce(mad64(z[i][m], kb[i][3], cb), kb[i][0], kb[i][1]);
+      }
+    __syncthreads();
+    Acc r[TW][M][2];
+    products<0, false>(r, 0, tables, kTiles, kLast);
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const u32 t0 = reduce(mad64(z[i][m], kb[i][2], (u64)column<true, kWide>(r[i][m][0], kc)), kb[i][0], kb[i][1]);
+        const u64 col = mad64(w[i][m], kb[i][2], (u64)column<true, kWide>(r[i][m][1], kc));
+        x.b0[i][m] = t0;
+        x.b1[i][m] = reduce(mad64(t0, kb[i][0] - kb[i][3], col), kb[i][0], kb[i][1]);
+      }
+    publish(x);
+    extend_to_a(x);
+  }
+  // the pairs whose limbs are at `src` (`left` of them, then zeros) into both bases
+  __device__ __forceinline__ void load(State& x, const u32* src, unsigned left, int nl) {
+    const int e = lane & 15;
+    __syncthreads();  // the bytes of the elements before have been read
+    for (int i = wave; i < NR; i += W) {
+      const int l = 4 * i + g;
+      if (l == rns::bias_slot(NR)) continue;
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const bool ok = (unsigned)(16 * m + e) < left && l < nl;
+        const u32* p = src + (size_t)(16 * m + e) * (2 * nl) + l;
+        word(0, m, 0, i, lane) = (ok ? p[0] : 0u) ^ rns::kOmega;
+        word(0, m, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
+      }
+    }
+    __syncthreads();
+    Acc r[TW][M][2];
+    products<2, false>(r, 0, tables + rns::lds_bytes(NR), kTiles, 16);
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        x.b0[i][m] = reduce((u64)column<true, kWide>(r[i][m][0], kc), kb[i][0], kb[i][1]);
+        x.b1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), kb[i][0], kb[i][1]);
+      }
+    publish(x);
+    extend_to_a(x);
+  }
+  // the pairs as two integers each in columns of weight 2^(29 l)
+  __device__ __forceinline__ void store(const State& x, long long* dst, unsigned left) {
+    __syncthreads();  // the bytes of the last product have been read
+    publish(x);
+    Acc r[TW][M][2];
+    products<2, true>(r, 1, tables + rns::lds_bytes(NR) + rns::in_matrix_bytes(NR), kLimbTiles, 16);
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const unsigned e = (unsigned)(16 * m + (lane & 15));
+        if (e < left && mine(i, kLimbTiles)) {
+          long long* d = dst + (size_t)e * (8 * kLimbTiles) + 4 * tile(i, kLimbTiles) + g;
+          d[0] = column<false, kWide>(r[i][m][0], kc);
+          d[4 * kLimbTiles] = column<false, kWide>(r[i][m][1], kc);
+        }
+      }
+  }
+  // Window tables: [wavefront][tile][elements][lane] quads {x0, x1 in base A, in base B}
+  static constexpr int kEntry = W * TW * M * WAVE * 4;  // dwords
+  __device__ __forceinline__ Quad* entry_at(const u32* entry, int i, int m) const {
+    return (Quad*)entry + ((wave * TW + i) * M + m) * WAVE + lane;
+  }
+  __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) *entry_at(entry, i, m) = Quad{x.a0[i][m], x.a1[i][m], x.b0[i][m], x.b1[i][m]};
+  }
+  __device__ __forceinline__ void load_state(State& x, const u32* entry) const {
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const Quad v = *entry_at(entry, i, m);
+        x.a0[i][m] = v[0];
+        x.a1[i][m] = v[1];
+        x.b0[i][m] = v[2];
+        x.b1[i][m] = v[3];
+      }
+  }
+};
+
+// Every block runs the program on 16 M elements at a time. The first `split` blocks run j0, the others j1.
+template <int NR, int TW, int W, int M>
+__global__ __launch_bounds__(W * 64, (W + 3) / 4) void k_rns_group(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
+  using G = RnsGroup<NR, TW, W, M>;
+  __shared__ __align__(16) typename G::Shared shared;
+  const bool second = blockIdx.x >= split;
+  const RnsJob& j = second ? j1 : j0;
+  const unsigned block = second ? blockIdx.x - split : blockIdx.x;
+  const unsigned nblocks = second ? gridDim.x - split : split;
+  G e(shared, j.tables);
+  const u32* prog = j.prog;
+  const int len = __builtin_amdgcn_readfirstlane(j.len);
+  u32* table = j.slots + (size_t)block * (size_t)j.entries * G::kEntry;
+  for (size_t first = (size_t)block * (16 * M); first < count; first += (size_t)nblocks * (16 * M)) {
+    const unsigned left = (unsigned)std::min(count - first, (size_t)(16 * M));
+    typename G::State x;
+    e.load(x, j.in + first * (size_t)(2 * j.nl), left, j.nl);
+    for (int pc = 0; pc < len;) {
+      u32 ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);
+#pragma unroll 1
+      while (ins == ENG_SQ) {
+        e.template multiply<true>(x, nullptr);
+        ins = ++pc < len ? (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]) : ~0u;
+      }
+      if (pc++ >= len) break;
+      const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;
+      u32* entry = table + (size_t)a * G::kEntry;
+      if (op == ENG_STORE_T) {
+        e.store_state(x, entry);
+      } else if (op == ENG_LOAD_T) {
+        e.load_state(x, entry);
+      } else {
+        e.template multiply<false>(x, entry);
+        if (op == ENG_MUL_T_ST) e.store_state(x, table + (size_t)b * G::kEntry);
+      }
+    }
+    e.store(x, j.out + first * (size_t)(8 * G::kLimbTiles), left);
+  }
+}
+
 }  // namespace
 
 namespace haflo {
@@ -456,13 +779,24 @@ namespace haflo {
 // Wavefronts of 16 elements that are resident at once: four per SIMD
 constexpr int kRnsWavesPerCu = 16;
 
-// From how many chains (elements times moduli) on. One wavefront's chain takes the same time however few elements it
-// holds: 3.2 ms for an encryption at a 1024-bit key (2.7 ms with an integer per wavefront up to 1024 chains, 3.7 ms at
-// 2048), 17.1 ms at 2048 bits (8.5 ms up to 1024, 14.7 ms at 2048, 17.5 ms at 3000), 3.2 ms for a decryption at 2048
-// bits (2.7 ms at 512 chains, 3.7 ms at 2048), 17.1 ms at 4096 bits (14.9 ms at 2048 chains, 29 ms at 6000).
-bool rns_pays(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs) {
-  return m.d_rns && count * (size_t)jobs >= (size_t)ctx->num_cu * (m.nl == 72 ? 10 : 7);
+namespace {
+// The blocks of k_rns_group that are resident at once on a compute unit
+int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
+// Where the elements are few, or the matrices too large for the LDS, the slots of 16 elements are spread over a block.
+// Measured on both sides (ms, spread / a wavefront for 16 elements): encryption at a 1024-bit key 1.1 / 3.2 up to 4096
+// elements, 2.1 / 3.4 at 8192, 5.1 / 4.4 at 20000; at 2048 bits 4.1 / 17.1 at 3000, 16.2 / 18.0 at 16384, 32 / 27 at
+// 32768; decryption at a 1024-bit key 0.55 / 0.93 at 4096, 1.02 / 0.93 at 8192.
+bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
+  return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 3);
 }
+size_t table_slots(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
+  const size_t tiles = (count + 15) / 16;
+  if (use_group(ctx, nr, count, jobs))  // one per block
+    return std::min(tiles, std::max((size_t)ctx->num_cu * group_blocks_per_cu(nr) / (size_t)jobs, (size_t)1));
+  return (tiles + kRnsWavesPerCu - 1) / kRnsWavesPerCu * kRnsWavesPerCu;  // whole blocks
+}
+}  // namespace
+
 size_t rns_chunk(const haflo_ctx* ctx, int jobs) {
   return std::max((size_t)ctx->num_cu * kRnsWavesPerCu / (size_t)jobs, (size_t)1) * 16;
 }
@@ -483,8 +817,7 @@ RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int
   }
   b.tables = at;  // 16 bytes aligned
   // the pair engine's slots before and after lie here too: as many as there are elements, 2 nl words each
-  const size_t tiles = ((n + 15) / 16 + kRnsWavesPerCu - 1) / kRnsWavesPerCu * kRnsWavesPerCu;  // whole blocks
-  b.total = at + std::max((size_t)jobs * tiles * (size_t)entries * 4 * (size_t)nr * 64,
+  b.total = at + std::max((size_t)jobs * table_slots(ctx, nr, n, jobs) * (size_t)entries * 4 * (size_t)nr * 64,
                           (size_t)jobs * (n + 128) * 2 * (size_t)m.nl);
   return b;
 }
@@ -493,12 +826,13 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
               const RnsBuffers& b, size_t count, int entries, hipStream_t st) {
   const int nr = rns::regs_for(m[0]->nl);
   const size_t tiles = (count + 15) / 16;
+  const bool group = use_group(ctx, nr, count, jobs);
   // wavefronts of 16 elements: one block per compute unit, with as many in each as it takes to spread the elements
   // over all of them
   size_t waves = (tiles * (size_t)jobs + ctx->num_cu - 1) / ctx->num_cu;
   waves = std::min(std::max(waves, (size_t)1), (size_t)kRnsWavesPerCu);
-  const unsigned blocks = (unsigned)((tiles + waves - 1) / waves);
-  const size_t slots = (size_t)blocks * waves;
+  const size_t slots = group ? table_slots(ctx, nr, count, jobs) : (tiles + waves - 1) / waves * waves;
+  const unsigned blocks = (unsigned)(group ? slots : slots / waves);
   RnsJob job[2];
   for (int i = 0; i < jobs; ++i) {
     job[i].tables = m[i]->d_rns;
@@ -513,12 +847,25 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
   if (jobs == 1) job[1] = job[0];
 #define WAVES(NR) \
   hipLaunchKernelGGL((k_rns<NR>), dim3(blocks * jobs), dim3((unsigned)waves * 64), 0, st, job[0], job[1], blocks, count)
+#define GROUP(NR, TW, W) \
+  hipLaunchKernelGGL((k_rns_group<NR, TW, W, 1>), dim3(blocks * jobs), dim3(W * 64), 0, st, job[0], job[1], blocks, count)
   switch (nr) {
-    case 6: WAVES(6); break;
-    case 10: WAVES(10); break;
-    case 18: WAVES(18); break;
+    case 6:
+      if (group) GROUP(6, 1, 5);
+      else WAVES(6);
+      break;
+    case 10:
+      if (group) GROUP(10, 1, 9);
+      else WAVES(10);
+      break;
+    case 18:
+      if (group) GROUP(18, 2, 9);
+      else WAVES(18);
+      break;
+    case 36: GROUP(36, 3, 12); break;
     default: return HAFLO_EINVAL;
   }
+#undef GROUP
 #undef WAVES
   return hip_status(hipGetLastError());
 }

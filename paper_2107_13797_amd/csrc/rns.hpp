@@ -21,13 +21,13 @@ constexpr uint64_t kBase = 1ull << 47;       // keeps a column of the matrix pro
 constexpr int kOffset = 256;                 // multiple of s added to every reduced value, so that none is negative
 
 // registers per lane, base and half for a modulus of `nl` 29-bit limbs, 0: no such engine
-constexpr int regs_for(int nl) { return nl == 18 ? 6 : nl == 36 ? 10 : nl == 72 ? 18 : 0; }
-// primes per base: 30 k bits exceed the modulus's bits by 28, 26 and 22
-constexpr int primes_for(int nr) { return nr == 6 ? 18 : nr == 10 ? 35 : nr == 18 ? 69 : 0; }
+constexpr int regs_for(int nl) { return nl == 18 ? 6 : nl == 36 ? 10 : nl == 72 ? 18 : nl == 144 ? 36 : 0; }
+// primes per base: 30 k bits exceed the modulus's bits by 28, 26, 22 and 14
+constexpr int primes_for(int nr) { return nr == 6 ? 18 : nr == 10 ? 35 : nr == 18 ? 69 : nr == 36 ? 137 : 0; }
 constexpr int slots(int nr) { return 4 * nr; }
 // tiles of 16 byte rows (4 slots) that hold the primes, and those that hold the limbs of a value
 constexpr int tiles(int nr) { return (primes_for(nr) + 3) / 4; }
-constexpr int limb_tiles(int nr) { return tiles(nr); }
+constexpr int limb_tiles(int nr) { return nr == 36 ? 36 : tiles(nr); }
 // the slots of the matrix products' two extra source values: the multiple of M_B to subtract, and the constant 1
 constexpr int alpha_slot(int nr) { return 4 * nr - 2; }
 constexpr int bias_slot(int nr) { return 4 * nr - 1; }
@@ -73,11 +73,11 @@ inline bool is_prime30(uint32_t n) {
   }
   return true;
 }
-// the k largest primes below 2^30 of a residue class, k <= 69; found once per process
+// the k largest primes below 2^30 of a residue class, k <= 137; found once per process
 inline std::vector<uint32_t> primes(int k, uint32_t residue_mod_4) {
   const auto find = [](uint32_t residue) {
     std::vector<uint32_t> r;
-    for (uint32_t c = (1u << 30) - 4 + residue; (int)r.size() < primes_for(18); c -= 4)
+    for (uint32_t c = (1u << 30) - 4 + residue; (int)r.size() < primes_for(36); c -= 4)
       if (is_prime30(c)) r.push_back(c);
     return r;
   };

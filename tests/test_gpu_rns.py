@@ -1,6 +1,6 @@
 """The RNS engine (residues modulo two sets of primes, reductions on the matrix cores) against the limb arithmetic that
-serves calls whose workspace has no room for it, which is what the oracle pins: batches on both sides of the size
-from which it is used, with partial tiles of 16 elements and partial passes. Every
+serves calls whose workspace has no room for it, which is what the oracle pins: batches on both sides of the rule that
+spreads an element over a block or gives 16 of them to a wavefront, with partial tiles and partial passes. Every
 comparison is of all bits of all elements."""
 import ctypes as C
 
@@ -41,10 +41,10 @@ def without_engine(call, need, out):
 
 
 @pytest.mark.parametrize("bits,counts", [
-    (512, (1791, 1792, 4097)),
-    (1024, (1791, 1792, 1809, 65536 + 17)),
-    (2048, (2559, 2561, 65536 + 1)),
-    (4096, (1279, 1297)),  # decryption: the primes' 2048 bits
+    (512, (1, 17, 4097, 12289)),
+    (1024, (1, 15, 16, 12288, 12289, 65536 + 17)),
+    (2048, (1, 33, 24576, 24577, 65536 + 1)),
+    (4096, (1, 17, 4097)),
 ])
 def test_rns_engine_matches_limb_arithmetic(bits, counts):
     if not torch.cuda.is_available():
