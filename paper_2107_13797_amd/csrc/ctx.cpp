@@ -382,14 +382,15 @@ static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
   if (!rns::regs_for(ms.nl)) return;
   ms.d_rns = up.put(rns::build_tables(s, ms.nl, &ms.rns_radix));
   const Big R = Big::mod(Big::pow2((size_t)kLimbBits * ms.nl), s2);
+  const MontHost mh(s2);
+  const Big rm = mh.to_mont(R);
   Big c = Big::mod(ms.rns_radix, s2);
   for (int i = kConstM1; i <= kConstM4; ++i) {
-    c = Big::mod(Big::mul(c, R), s2);
+    c = mh.mul(c, rm);
     special.push_back({i, c});
   }
   // out R / M_A modulo s^2, one prime of M_A after the other: 1 / a = (1 + s^2 t) / a with t = -1 / s^2 mod a
-  const MontHost mh(s2);
-  Big inv = mh.to_mont(Big::mod(Big::mul(out, R), s2));
+  Big inv = mh.mul(mh.to_mont(out), rm);
   for (uint32_t a : rns::primes(rns::primes_for(rns::regs_for(ms.nl)), 3)) {
     const uint32_t t = a - rns::invmod(s2.mod_small(a), a);
     const Big num = Big::add(Big::mul(s2, Big((uint64_t)t)), Big(1));

@@ -149,6 +149,7 @@ class Big {
   }
   // a mod m by binary shift-and-subtract (only used for per-key constants)
   static Big mod(const Big& a, const Big& m) {
+    if (cmp(a, m) < 0) return a;
     Big r;
     for (size_t i = a.bits(); i-- > 0;) {
       r = r.shl1();
