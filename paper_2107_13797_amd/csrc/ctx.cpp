@@ -516,6 +516,11 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
       if (ctx->P.d_rns) {
         build_prog_rns(ctx->prog_rns_dec_p, ctx->prog_dec_p.sched, up);
         build_prog_rns(ctx->prog_rns_dec_q, ctx->prog_dec_q.sched, up);
+        build_prog_rns(ctx->prog_rns_low_p, ctx->prog_enc_p.sched, up);
+        build_prog_rns(ctx->prog_rns_low_q, ctx->prog_enc_q.sched, up);
+        put_prog(ctx->prog_rns_low_in,  // as in build_prog_encrypt_low
+                 {eng_ins(ENG_LOAD_WH, 1), eng_ins(ENG_MUL_C, kConstM2), eng_ins(ENG_STORE_T, 0), eng_ins(ENG_LOAD_W, 1),
+                  eng_ins(ENG_MUL_C, kConstM1), eng_ins(ENG_ADD_T, 0)}, 1, up);
         build_prog_rns(ctx->prog_rns_lift_p, ctx->prog_lift_p.sched, up);
         build_prog_rns(ctx->prog_rns_lift_q, ctx->prog_lift_q.sched, up);
         std::vector<uint32_t> in;

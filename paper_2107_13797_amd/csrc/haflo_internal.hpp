@@ -135,6 +135,7 @@ struct haflo_ctx {
   // the RNS engine's programs: the powers alone, and what takes elements into its form and out of it on the pair engine
   haflo::DevProg prog_rns_enc, prog_rns_enc_in, prog_rns_enc_out;
   haflo::DevProg prog_rns_dec_p, prog_rns_dec_q, prog_rns_dec_in;
+  haflo::DevProg prog_rns_low_p, prog_rns_low_q, prog_rns_low_in;
   haflo::DevProg prog_rns_lift_p, prog_rns_lift_q, prog_rns_lift_in, prog_rns_priv_out;
   haflo::DevProg prog_enc;     // encryption: r^n modulo n^2 and the (1 + m n) factor
   haflo::DevProg prog_dec_p;   // decryption branch: c^(p-1) modulo p^2
@@ -210,7 +211,8 @@ int power_tables(const haflo_ctx* ctx, const uint32_t* d_c, uint32_t* d_tables, 
 int invert_batch(const haflo_ctx* ctx, const uint32_t* in, uint32_t* out, size_t count, hipStream_t st);
 
 // Powers of pairs modulo m[i]^2 by the RNS engine (kernels_rns.hip), one or two moduli of the same size side by
-// side: elements [x0 limbs][x1 limbs] at in[i] to columns at out[i], `count` <= rns_chunk() of them.
+// side: elements [x0 limbs][x1 limbs] at in[i] to columns at out[i], `count` <= rns_chunk() of them. Without `pair`
+// powers of x0 modulo m[i] alone (x1 = 0 in the result).
 struct RnsBuffers {  // workspace of one chunk, in 32-bit words from its start
   size_t in[2], out[2], tables, total;
 };
@@ -218,7 +220,7 @@ size_t rns_chunk(const haflo_ctx* ctx, int jobs);
 int rns_columns(const ModHost& m);
 RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs, int entries);
 int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, const haflo_ctx* ctx, uint32_t* ws,
-              const RnsBuffers& b, size_t count, int entries, hipStream_t st);
+              const RnsBuffers& b, size_t count, int entries, bool pair, hipStream_t st);
 
 // X^T [[d]] by the bucket method (kernels_buckets.hip). Workspace layout in 32-bit words.
 struct XtdBucketPlan {

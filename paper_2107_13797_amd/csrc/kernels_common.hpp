@@ -220,13 +220,13 @@ __device__ __forceinline__ void pair_to_integer(u32 (&lo)[LPT], u32 (&hi)[LPT], 
 
 // The same engine on residues modulo s^2 held as pairs of residues modulo s (pairmul_core): `M` is the
 // modulus s with half the limbs of s^2; an element of the tables and of the constant arrays is
-// [x0: NL limbs][x1: NL limbs]. Instructions as above, with these readings: ENG_LOAD_W is the pair (w, 0),
+// [x0: NL limbs][x1: NL limbs]. Instructions as above, with these readings: ENG_LOAD_W (ENG_LOAD_WH) is the pair (w, 0),
 // ENG_LOAD_W1 the pair (1, w), i.e. 1 + s w; ENG_LOAD_L a takes limbs [a NL, (a + 1) NL) of the element's
 // limb input as (l, 0). When the program ends, acc holds the result X as a pair; io.out_mode says what is
 // stored: kOutInteger, the canonical integer x0 + s x1 on 2 NL limbs (low half, high half); kOutSecond, the
 // canonical x1 on NL limbs, for results that are 1 modulo s (x0 = 1), whose (X - 1) / s it is.
-// kOutPair: [x0][x1] as they are (lazy limbs).
-enum { kOutInteger = 0, kOutSecond = 1, kOutPair = 2 };
+// kOutPair: [x0][x1] as they are (lazy limbs); kOutFirst: the canonical x0 on NL limbs, the residue modulo s.
+enum { kOutInteger = 0, kOutSecond = 1, kOutPair = 2, kOutFirst = 3 };
 // Signed columns of weight 2^(29 j), |column| < 2^47, of an integer in [0, 2^(29 NL)): its canonical limbs
 template <int LPT, int T>
 __device__ __forceinline__ void load_columns(u32 (&x)[LPT], const long long* p, const Grp<T>& g) {
@@ -308,14 +308,16 @@ __device__ __forceinline__ void engine_run_pairs(const ModRef& M, const Prog& P,
             x1[j] = t1[j];
           }
         }
-      } else if (op == ENG_LOAD_W || op == ENG_LOAD_W1) {
+      } else if (op == ENG_LOAD_W || op == ENG_LOAD_WH || op == ENG_LOAD_W1) {
         u32 w[LPT];
-        if (active) load_words_as_limbs<LPT, T>(w, io.in_words[a] + item * (size_t)io.in_nwords, io.in_nwords, g, 0);
+        if (active)
+          load_words_as_limbs<LPT, T>(w, io.in_words[a] + item * (size_t)io.in_nwords, io.in_nwords, g,
+                                      op == ENG_LOAD_WH ? NL : 0);
         else zero_limbs<LPT>(w);
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
-          x0[j] = op == ENG_LOAD_W ? w[j] : ((g.k == 0 && j == 0) ? 1u : 0u);
-          x1[j] = op == ENG_LOAD_W ? 0u : w[j];
+          x0[j] = op != ENG_LOAD_W1 ? w[j] : ((g.k == 0 && j == 0) ? 1u : 0u);
+          x1[j] = op != ENG_LOAD_W1 ? 0u : w[j];
         }
       } else if (op == ENG_LOAD_L) {
         const u32* src = io.in_limbs + item * (size_t)io.in_limbs_stride + (size_t)a * NL;
@@ -339,6 +341,8 @@ __device__ __forceinline__ void engine_run_pairs(const ModRef& M, const Prog& P,
     pair_canonical<LPT, T>(x0, x1, mod.n, g);
     if (io.out_mode == kOutSecond) {
       if (active) store_limbs<LPT, T>(io.out + item * (size_t)NL, x1, g);
+    } else if (io.out_mode == kOutFirst) {
+      if (active) store_limbs<LPT, T>(io.out + item * (size_t)NL, x0, g);
     } else {
       u32 lo[LPT], hi[LPT];
       pair_to_integer<LPT, T>(lo, hi, x0, x1, mod.n, g);

@@ -48,13 +48,13 @@ struct RnsJob {
   int entries;
 };
 
-// The residues of x0 and x1 of a lane in one base, in the registers that the matrix products take them from: full
-// quads of each, and one quad with the last two of both.
-template <int NR>
+// The residues of x0 and x1 (PAIR; else of one value, x0) of a lane in one base, in the registers that the matrix
+// products take them from: full quads of each, and one quad with the last two of both.
+template <int NR, bool PAIR>
 struct Residues {
   static_assert(NR % 4 == 2, "full blocks and a half one");
   static constexpr int kFull = NR / 4;
-  Quad q[2][kFull];
+  Quad q[PAIR ? 2 : 1][kFull];
   Quad h;
   template <int X>
   __device__ __forceinline__ u32 get(int i) const {
@@ -68,20 +68,23 @@ struct Residues {
   // Gathers quad k of both halves in its registers now: left alone, the compiler keeps the values in the 64-bit results
   // they are the upper words of until all are there.
   __device__ __forceinline__ void gather(int k) {
-    if (k < kFull) asm("" : "+v"(q[0][k]), "+v"(q[1][k]));
-    else asm("" : "+v"(h));
+    if (k < kFull) {
+      asm("" : "+v"(q[0][k]));
+      if constexpr (PAIR) asm("" : "+v"(q[1][k]));
+    } else {
+      asm("" : "+v"(h));
+    }
   }
   // Hides where the values come from: the compiler would widen what is multiplied later to 64 bits where it is made
   // and carry the zero upper words along.
   __device__ __forceinline__ void forget() {
 #pragma unroll
-    for (int k = 0; k < kFull; ++k) asm("" : "+v"(q[0][k]), "+v"(q[1][k]));
-    asm("" : "+v"(h));
+    for (int k = 0; k <= kFull; ++k) gather(k);
   }
 };
-template <int NR>
+template <int NR, bool PAIR>
 struct RnsState {
-  Residues<NR> a, b;
+  Residues<NR, PAIR> a, b;
 };
 
 // T 2^-32 mod p, below (T + 2^32 p) / 2^32
@@ -136,13 +139,14 @@ struct FragmentAt {
 };
 
 // The operand of a matrix product: the half block's words of x0 and of x1 in a quad of their own, zeros behind them.
-template <int NR>
+template <int NR, bool PAIR>
 struct Operand {
-  Residues<NR>& d;
+  Residues<NR, PAIR>& d;
   Quad h0, h1;
-  __device__ __forceinline__ explicit Operand(Residues<NR>& d_)
+  __device__ __forceinline__ explicit Operand(Residues<NR, PAIR>& d_)
       : d(d_), h0(Quad{d_.h[0], d_.h[1], 0, 0}), h1(Quad{d_.h[2], d_.h[3], 0, 0}) {
-    asm("" : "+v"(h0), "+v"(h1));  // made once, not for every tile
+    asm("" : "+v"(h0));  // made once, not for every tile
+    if constexpr (PAIR) asm("" : "+v"(h1));
   }
   // back to the residues' own form
   __device__ __forceinline__ void release() { d.h = Quad{h0[0], h0[1], h1[0], h1[1]}; }
@@ -152,9 +156,9 @@ struct Operand {
 // of a row are stored: what lies in the other registers meets the operand's zeros. (A product of
 // v_mfma_i32_16x16x32_i8 added to one of v_mfma_i32_16x16x64_i8 right after it comes out wrong on this chip, either
 // way round: one shape only.)
-template <int NR>
+template <int NR, bool PAIR>
 __device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile, int rows, const FragmentAt& at,
-                                              const Operand<NR>& d) {
+                                              const Operand<NR, PAIR>& d) {
   constexpr int F = rns::full_blocks(NR);
   const char* p = (const char*)tile;
   Acc m[F + 1];
@@ -171,11 +175,12 @@ __device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile
 #pragma unroll
   for (int k = 0; k <= F; ++k) {
     r0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], (Acc)(k < F ? d.d.q[0][k < F ? k : 0] : d.h0), r0, 0, 0, 0);
-    r1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], (Acc)(k < F ? d.d.q[1][k < F ? k : 0] : d.h1), r1, 0, 0, 0);
+    if constexpr (PAIR)
+      r1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], (Acc)(k < F ? d.d.q[1][k < F ? k : 0] : d.h1), r1, 0, 0, 0);
   }
 }
 
-template <int NR>
+template <int NR, bool PAIR>
 struct RnsEngine {
   static constexpr int kTiles = rns::tiles(NR);  // also the registers that hold primes
   static constexpr int kGroup = 3;               // tiles the compiler may mix
@@ -205,58 +210,60 @@ struct RnsEngine {
     return *(const Quad*)(lds + 2 * rns::lds_matrix_bytes(NR) + (base * rns::slots(NR) + 4 * i) * 16 + cst_at);
   }
   template <int MATRIX>
-  __device__ __forceinline__ void lds_products(Acc& r0, Acc& r1, int t, const Operand<NR>& d) const {
+  __device__ __forceinline__ void lds_products(Acc& r0, Acc& r1, int t, const Operand<NR, PAIR>& d) const {
     const char* p = lds + MATRIX * rns::lds_matrix_bytes(NR) + t * kTileBytes;
-    if (t == kTiles - 1) tile_products<NR>(r0, r1, p, kLast, kLast != 16 ? at_last : at, d);
-    else tile_products<NR>(r0, r1, p, 16, at, d);
+    if (t == kTiles - 1) tile_products<NR, PAIR>(r0, r1, p, kLast, kLast != 16 ? at_last : at, d);
+    else tile_products<NR, PAIR>(r0, r1, p, 16, at, d);
   }
 
   // The residue products of one base of a square (y null) or of a product with the table entry y: bytes of sigma in
   // base A (BASE 0), z and w in base B. The entry's quads are on their way one step ahead.
   template <int BASE, bool SQ>
-  __device__ __forceinline__ void base_products(Residues<NR>& x, const u32* y) {
+  __device__ __forceinline__ void base_products(Residues<NR, PAIR>& x, const u32* y) {
     constexpr int kQuads = NR / 4 + 1;
     const Quad* p = (const Quad*)(y + BASE * kArray) + lane;
     x.forget();
     Quad n0 = {}, n1 = {};
     if (!SQ) {
       n0 = p[0];
-      n1 = p[WAVE];
+      if (PAIR) n1 = p[WAVE];
     }
 #pragma unroll
     for (int q = 0; q < kQuads; ++q) {
       const Quad y0 = n0, y1 = n1;
       forget();
       if (!SQ && q + 1 < kQuads) {
-        n0 = p[2 * (q + 1) * WAVE];
-        if (q + 2 < kQuads) n1 = p[(2 * (q + 1) + 1) * WAVE];
+        n0 = p[(PAIR ? 2 : 1) * (q + 1) * WAVE];
+        if (PAIR && q + 2 < kQuads) n1 = p[(2 * (q + 1) + 1) * WAVE];
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int i = 4 * q + c;
         if (i >= kTiles || i >= NR) continue;
         const Quad k = cst(BASE, i);
-        const u32 u0 = x.template get<0>(i), u1 = x.template get<1>(i);
-        const u32 v0 = SQ ? u0 : y0[c], v1 = SQ ? u1 : (q + 1 < kQuads ? y1[c] : y0[(2 + c) % 4]);
+        const u32 u0 = x.template get<0>(i), v0 = SQ ? u0 : y0[c];
         const u32 s0 = reduce(mad64(u0, v0, 0), k[0], k[1]);
-        const u64 cross = SQ ? mad64(u0 << 1, u1, 0) : mad64(u0, v1, mad64(u1, v0, 0));
-        const u32 s1 = reduce(mad64(s0, BASE ? k[3] : k[2], cross), k[0], k[1]);
         x.template set<0>(i, BASE ? s0 : to_bytes(s0));
-        x.template set<1>(i, BASE ? s1 : to_bytes(s1));
+        if constexpr (PAIR) {
+          const u32 u1 = x.template get<1>(i), v1 = SQ ? u1 : (q + 1 < kQuads ? y1[c] : y0[(2 + c) % 4]);
+          const u64 cross = SQ ? mad64(u0 << 1, u1, 0) : mad64(u0, v1, mad64(u1, v0, 0));
+          const u32 s1 = reduce(mad64(s0, BASE ? k[3] : k[2], cross), k[0], k[1]);
+          x.template set<1>(i, BASE ? s1 : to_bytes(s1));
+        }
       }
       x.gather(q);
     }
   }
   template <bool SQ>
-  __device__ __forceinline__ void products(RnsState<NR>& x, const u32* y) {
+  __device__ __forceinline__ void products(RnsState<NR, PAIR>& x, const u32* y) {
     base_products<0, SQ>(x.a, y);
     base_products<1, SQ>(x.b, y);
   }
 
   // the constant 1 of the bias in its slot, and alpha's bytes in theirs (lane groups 3 and 2 of the last register)
-  __device__ __forceinline__ void set_extra(Residues<NR>& d, u32 alpha0, u32 alpha1) const {
+  __device__ __forceinline__ void set_extra(Residues<NR, PAIR>& d, u32 alpha0, u32 alpha1) const {
     d.h[1] = (d.h[1] & keep) | (alpha0 & mine) | one;
-    d.h[3] = (d.h[3] & keep) | (alpha1 & mine) | one;
+    if (PAIR) d.h[3] = (d.h[3] & keep) | (alpha1 & mine) | one;
   }
   // alpha of a value from the sum of its residues' upper halves over this lane's slots
   __device__ __forceinline__ u32 alpha_bytes(u32 sum) const {
@@ -268,34 +275,38 @@ struct RnsEngine {
 
   // Base B of the reduced pair from sigma (bytes, in base A) and the products z, w (in base B); leaves base B as bytes,
   // alpha among them, for the way back.
-  __device__ __forceinline__ void extend_to_b(RnsState<NR>& x) {
+  __device__ __forceinline__ void extend_to_b(RnsState<NR, PAIR>& x) {
     x.b.forget();
     set_extra(x.a, 0, 0);
-    Operand<NR> d(x.a);
+    Operand<NR, PAIR> d(x.a);
     u32 sum0 = 0, sum1 = 0;
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       if (t % kGroup == 0) {
-        asm volatile("" : "+v"(sum0), "+v"(sum1));  // running sums: summed up at the end they would keep every term alive
+        // running sums: summed up at the end they would keep every term alive
+        asm volatile("" : "+v"(sum0));
+        if (PAIR) asm volatile("" : "+v"(sum1));
         forget();
       }
       Acc r0, r1;
       lds_products<0>(r0, r1, t, d);
       const Quad k = cst(1, t);
       const u32 t0 = reduce(mad64(x.b.template get<0>(t), k[2], (u64)column<true>(r0, kc)), k[0], k[1]);
-      const u64 col = mad64(x.b.template get<1>(t), k[2], (u64)column<true>(r1, kc));
-      const u32 t1 = reduce(mad64(t0, k[0] - k[3], col), k[0], k[1]);
       sum0 += t0 >> 16;
-      sum1 += t1 >> 16;
+      if constexpr (PAIR) {
+        const u64 col = mad64(x.b.template get<1>(t), k[2], (u64)column<true>(r1, kc));
+        const u32 t1 = reduce(mad64(t0, k[0] - k[3], col), k[0], k[1]);
+        sum1 += t1 >> 16;
+        x.b.template set<1>(t, to_bytes(t1));
+      }
       x.b.template set<0>(t, to_bytes(t0));
-      x.b.template set<1>(t, to_bytes(t1));
       if (t % 4 == 3) x.b.gather(t / 4);
     }
-    set_extra(x.b, alpha_bytes(sum0), alpha_bytes(sum1));
+    set_extra(x.b, alpha_bytes(sum0), PAIR ? alpha_bytes(sum1) : 0u);
   }
   // base A from base B's bytes; turns base B back to residues
-  __device__ __forceinline__ void extend_to_a(RnsState<NR>& x) {
-    Operand<NR> d(x.b);
+  __device__ __forceinline__ void extend_to_a(RnsState<NR, PAIR>& x) {
+    Operand<NR, PAIR> d(x.b);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       if (t % kGroup == 0) forget();
@@ -303,101 +314,103 @@ struct RnsEngine {
       lds_products<1>(r0, r1, t, d);
       const Quad k = cst(0, t);
       x.a.template set<0>(t, reduce((u64)column<true>(r0, kc), k[0], k[1]));
-      x.a.template set<1>(t, reduce((u64)column<true>(r1, kc), k[0], k[1]));
+      if constexpr (PAIR) x.a.template set<1>(t, reduce((u64)column<true>(r1, kc), k[0], k[1]));
       if (t % 4 == 3) x.a.gather(t / 4);
     }
     d.release();
     flip(x.b);
   }
   // residues <-> bytes
-  static __device__ __forceinline__ void flip(Residues<NR>& d) {
+  static __device__ __forceinline__ void flip(Residues<NR, PAIR>& d) {
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
       d.q[0][k] ^= rns::kOmega;
-      d.q[1][k] ^= rns::kOmega;
+      if constexpr (PAIR) d.q[1][k] ^= rns::kOmega;
     }
     d.h ^= rns::kOmega;
   }
 
   // the pairs whose limbs are at `src` (`left` of them, then zeros) into both bases
-  __device__ __forceinline__ void load(RnsState<NR>& x, const u32* src, unsigned left, int nl, const char* matrix) {
+  __device__ __forceinline__ void load(RnsState<NR, PAIR>& x, const u32* src, unsigned left, int nl, const char* matrix) {
     const bool active = (unsigned)(lane & 15) < left;
     src += (lane & 15) * 2 * nl;
-    x = RnsState<NR>();
+    x = RnsState<NR, PAIR>();
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const int l = 4 * i + g;
       const bool ok = active && l < nl;
       x.a.template set<0>(i, (ok ? src[l] : 0u) ^ rns::kOmega);
-      x.a.template set<1>(i, (ok ? src[nl + l] : 0u) ^ rns::kOmega);
+      if constexpr (PAIR) x.a.template set<1>(i, (ok ? src[nl + l] : 0u) ^ rns::kOmega);
     }
     if (g == 3) {  // in place of a limb that is zero
       x.a.template set<0>(NR - 1, 1);
-      x.a.template set<1>(NR - 1, 1);
+      if constexpr (PAIR) x.a.template set<1>(NR - 1, 1);
     }
-    Operand<NR> d(x.a);
+    Operand<NR, PAIR> d(x.a);
     u32 sum0 = 0, sum1 = 0;
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       forget();
       Acc r0, r1;
-      tile_products<NR>(r0, r1, matrix + t * kTileBytes, 16, at, d);
+      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d);
       const Quad k = cst(1, t);
       const u32 t0 = reduce((u64)column<true>(r0, kc), k[0], k[1]);
-      const u32 t1 = reduce((u64)column<true>(r1, kc), k[0], k[1]);
       sum0 += t0 >> 16;
-      sum1 += t1 >> 16;
-      asm volatile("" : "+v"(sum0), "+v"(sum1));
       x.b.template set<0>(t, to_bytes(t0));
-      x.b.template set<1>(t, to_bytes(t1));
+      if constexpr (PAIR) {
+        const u32 t1 = reduce((u64)column<true>(r1, kc), k[0], k[1]);
+        sum1 += t1 >> 16;
+        x.b.template set<1>(t, to_bytes(t1));
+      }
+      asm volatile("" : "+v"(sum0), "+v"(sum1));
     }
-    set_extra(x.b, alpha_bytes(sum0), alpha_bytes(sum1));
+    set_extra(x.b, alpha_bytes(sum0), PAIR ? alpha_bytes(sum1) : 0u);
     extend_to_a(x);
   }
   // The pair as two integers in columns of weight 2^(29 l). Base B still holds what the way back left there, alpha and
   // the bias among it.
-  __device__ __forceinline__ void store(RnsState<NR>& x, long long* dst, unsigned left, const char* matrix) {
+  __device__ __forceinline__ void store(RnsState<NR, PAIR>& x, long long* dst, unsigned left, const char* matrix) {
     const bool active = (unsigned)(lane & 15) < left;
     dst += (lane & 15) * 8 * kTiles;
     flip(x.b);
-    Operand<NR> d(x.b);
+    Operand<NR, PAIR> d(x.b);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       forget();
       Acc r0, r1;
-      tile_products<NR>(r0, r1, matrix + t * kTileBytes, 16, at, d);
+      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d);
       if (active) {
         dst[4 * t + g] = column<false>(r0, kc);
-        dst[4 * kTiles + 4 * t + g] = column<false>(r1, kc);
+        dst[4 * kTiles + 4 * t + g] = PAIR ? column<false>(r1, kc) : 0;
       }
     }
   }
 
   // Window tables: an entry holds the registers of base A and of base B one after the other, each as [quad][lane].
-  static constexpr int kArray = (2 * (NR / 4) + 1) * 4 * WAVE;  // dwords
-  __device__ __forceinline__ void load_entry(Residues<NR>& d, const u32* entry, int array) const {
+  static constexpr int kArray = ((PAIR ? 2 : 1) * (NR / 4) + 1) * 4 * WAVE;  // dwords
+  __device__ __forceinline__ void load_entry(Residues<NR, PAIR>& d, const u32* entry, int array) const {
     const Quad* p = (const Quad*)(entry + array * kArray) + lane;
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
-      d.q[0][k] = p[2 * k * WAVE];
-      d.q[1][k] = p[(2 * k + 1) * WAVE];
+      d.q[0][k] = p[(PAIR ? 2 : 1) * k * WAVE];
+      if constexpr (PAIR) d.q[1][k] = p[(2 * k + 1) * WAVE];
     }
-    d.h = p[2 * (NR / 4) * WAVE];
+    d.h = p[(PAIR ? 2 : 1) * (NR / 4) * WAVE];
   }
-  __device__ __forceinline__ void store_entry(const Residues<NR>& d, u32* entry, int array) const {
+  __device__ __forceinline__ void store_entry(const Residues<NR, PAIR>& d, u32* entry, int array) const {
     Quad* p = (Quad*)(entry + array * kArray) + lane;
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
-      p[2 * k * WAVE] = d.q[0][k];
-      p[(2 * k + 1) * WAVE] = d.q[1][k];
+      p[(PAIR ? 2 : 1) * k * WAVE] = d.q[0][k];
+      if constexpr (PAIR) p[(2 * k + 1) * WAVE] = d.q[1][k];
     }
-    p[2 * (NR / 4) * WAVE] = d.h;
+    p[(PAIR ? 2 : 1) * (NR / 4) * WAVE] = d.h;
   }
-  __device__ __forceinline__ void load_state(RnsState<NR>& x, const u32* entry) const {
+  __device__ __forceinline__ void load_state(RnsState<NR, PAIR>& x, const u32* entry) const {
     load_entry(x.a, entry, 0);
     load_entry(x.b, entry, 1);
   }
-  __device__ __forceinline__ void store_state(const RnsState<NR>& x, u32* entry) const {
+  __device__ __forceinline__ void store_state(const RnsState<NR, PAIR>& x, u32* entry) const {
     store_entry(x.a, entry, 0);
     store_entry(x.b, entry, 1);
   }
@@ -409,7 +422,7 @@ struct RnsEngine {
 // 360 matrix instructions per squaring and wavefront), LDS reads take 41 %, at 1.9 GHz. 32 elements per wavefront (half
 // the matrix reads) need 256 registers and more, and spilled.
 // Every wavefront runs the program on 16 elements at a time. The first `split` blocks run j0, the others j1.
-template <int NR>
+template <int NR, bool PAIR>
 __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
   __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
   const bool second = blockIdx.x >= split;
@@ -421,17 +434,17 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
   __syncthreads();
   const char* in_matrix = (const char*)j.tables + rns::lds_bytes(NR);
   const char* out_matrix = in_matrix + rns::in_matrix_bytes(NR);
-  RnsEngine<NR> e(lds);
+  RnsEngine<NR, PAIR> e(lds);
   const unsigned waves = blockDim.x / 64;
   // the same for the whole wavefront, so that what follows from it stays in scalar registers
   const size_t wave = (size_t)block * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-  constexpr size_t kEntry = 4 * NR * WAVE;
+  constexpr size_t kEntry = 2 * RnsEngine<NR, PAIR>::kArray;
   const u32* prog = j.prog;
   const int len = __builtin_amdgcn_readfirstlane(j.len);
   u32* table = j.slots + wave * (size_t)j.entries * kEntry;
   for (size_t tile = wave; tile * 16 < count; tile += (size_t)nblocks * waves) {
     const unsigned left = (unsigned)std::min(count - tile * 16, (size_t)16);
-    RnsState<NR> x;
+    RnsState<NR, PAIR> x;
     e.load(x, j.in + tile * (size_t)(16 * 2 * j.nl), left, j.nl, in_matrix);
     for (int pc = 0; pc < len;) {
       u32 ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);
@@ -471,8 +484,9 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
 // and compute unit). Measured against the limb arithmetic on one wavefront per integer: 1024 encryptions at a 1024-bit
 // key 2.67 -> 1.04 ms, 256 at 2048 bits 8.5 -> 3.9, 3001 at 4096 bits 74.9 -> 27.2; 3072 decryptions at 1024 bits 1.33
 // -> 0.53 ms, 64 at 4096 bits 8.63 -> 4.01.
-template <int NR, int TW, int W, int M>
+template <int NR, int TW, int W, int M, bool PAIR>
 struct RnsGroup {
+  static constexpr int kHalves = PAIR ? 2 : 1;  // x0 and x1, or one value
   static constexpr int kTiles = rns::tiles(NR);
   static constexpr int kLimbTiles = rns::limb_tiles(NR);
   static constexpr int kBlocks = (NR + 3) / 4;  // of 64 bytes, the last one partly empty
@@ -486,8 +500,8 @@ struct RnsGroup {
   static constexpr int kRegBlocks = kHeld ? 0 : 3, kLdsBlocks = kHeld ? 0 : 2;
   static_assert(W * TW >= kLimbTiles, "every tile has a wavefront");
   struct Shared {
-    Quad bytes[2][M][2][kBlocks][WAVE];  // [sigma, rho][elements][x0, x1][block][lane]
-    u32 sum[3][M][2][16];                // alpha's sums, of the last, the present and the next rho
+    Quad bytes[2][M][kHalves][kBlocks][WAVE];  // [sigma, rho][elements][x0, x1][block][lane]
+    u32 sum[3][M][kHalves][16];                // alpha's sums, of the last, the present and the next rho
     Acc resident[kLdsBlocks][kHeld ? 1 : kTiles][WAVE];
   };
   struct State {
@@ -552,7 +566,7 @@ struct RnsGroup {
     if (threadIdx.x < 16)
       for (int b = 0; b < 2; ++b)
         for (int m = 0; m < M; ++m)
-          for (int x = 0; x < 2; ++x) word(b, m, x, NR - 1, 48 + (int)threadIdx.x) = 1;
+          for (int x = 0; x < kHalves; ++x) word(b, m, x, NR - 1, 48 + (int)threadIdx.x) = 1;
   }
   __device__ __forceinline__ u32& word(int buffer, int m, int x, int i, int l) const {
     return ((u32*)&sh.bytes[buffer][m][x][i / 4][l])[i % 4];
@@ -561,16 +575,16 @@ struct RnsGroup {
   // r = the tiles' products with the bytes in `buffer`, after all wavefronts have written theirs. MATRIX 0, 1: the two
   // of the modular product; ALPHA: lane group 2 of the last register takes alpha.
   template <int MATRIX, bool ALPHA>
-  __device__ __forceinline__ void products(Acc (&r)[TW][M][2], int buffer, const char* matrix, int tiles, int last) {
+  __device__ __forceinline__ void products(Acc (&r)[TW][M][kHalves], int buffer, const char* matrix, int tiles, int last) {
     unsigned l = (unsigned)lane;
     asm volatile("" : "+v"(l));  // or the addresses of all fragments are kept in registers from one product to the next
-    u32 alpha[M][2];
+    u32 alpha[M][kHalves];
     if (ALPHA) {
       const int now = (turn + 2) % 3;  // of the last publish()
 #pragma unroll
       for (int m = 0; m < M; ++m)
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {
+        for (int x = 0; x < kHalves; ++x) {
           const u32 a = (sh.sum[now][m][x][lane & 15] + (1u << 13)) >> 14;
           alpha[m][x] = (a & 127u) | ((a >> 7) << 8);
         }
@@ -578,7 +592,9 @@ struct RnsGroup {
 #pragma unroll
     for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int m = 0; m < M; ++m) r[i][m][0] = r[i][m][1] = Acc{0, 0, 0, 0};
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int x = 0; x < kHalves; ++x) r[i][m][x] = Acc{0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < kBlocks; ++k) {
       // what streams in is asked for three blocks ahead at most, as far as the registers go
@@ -592,15 +608,12 @@ struct RnsGroup {
         else f[i] = fragment(matrix, tiles, last, i, k, l);
 #pragma unroll
       for (int m = 0; m < M; ++m) {
-        Quad d0 = sh.bytes[buffer][m][0][k][lane], d1 = sh.bytes[buffer][m][1][k][lane];
-        if (ALPHA && k == (NR - 1) / 4) {
-          d0[(NR - 1) % 4] = g == 2 ? alpha[m][0] : d0[(NR - 1) % 4];
-          d1[(NR - 1) % 4] = g == 2 ? alpha[m][1] : d1[(NR - 1) % 4];
-        }
 #pragma unroll
-        for (int i = 0; i < TW; ++i) {
-          r[i][m][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d0, r[i][m][0], 0, 0, 0);
-          r[i][m][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d1, r[i][m][1], 0, 0, 0);
+        for (int x = 0; x < kHalves; ++x) {
+          Quad d = sh.bytes[buffer][m][x][k][lane];
+          if (ALPHA && k == (NR - 1) / 4) d[(NR - 1) % 4] = g == 2 ? alpha[m][x] : d[(NR - 1) % 4];
+#pragma unroll
+          for (int i = 0; i < TW; ++i) r[i][m][x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d, r[i][m][x], 0, 0, 0);
         }
       }
     }
@@ -615,31 +628,33 @@ struct RnsGroup {
       for (int i = 0; i < TW; ++i)
         if (owns(i)) {
           word(1, m, 0, tile(i), lane) = x.b0[i][m] ^ rns::kOmega;
-          word(1, m, 1, tile(i), lane) = x.b1[i][m] ^ rns::kOmega;
           s0 += x.b0[i][m] >> 16;
-          s1 += x.b1[i][m] >> 16;
+          if constexpr (PAIR) {
+            word(1, m, 1, tile(i), lane) = x.b1[i][m] ^ rns::kOmega;
+            s1 += x.b1[i][m] >> 16;
+          }
         }
-      atomicAdd(s + (m * 2 + 0) * 16 + (lane & 15), s0);
-      atomicAdd(s + (m * 2 + 1) * 16 + (lane & 15), s1);
+      atomicAdd(s + m * kHalves * 16 + (lane & 15), s0);
+      if (PAIR) atomicAdd(s + (m * kHalves + 1) * 16 + (lane & 15), s1);
     }
     __syncthreads();
     // the sums of the publish() before this one were last read before this barrier and are next added to after the
     // barrier that follows it
     const int clear = (turn + 2) % 3;
     if (threadIdx.x < 32)
-      for (int i = (int)threadIdx.x; i < M * 32; i += 32) (&sh.sum[clear][0][0][0])[i] = 0;
+      for (int i = (int)threadIdx.x; i < M * kHalves * 16; i += 32) (&sh.sum[clear][0][0][0])[i] = 0;
     turn = (turn + 1) % 3;
   }
   // base A from what publish() left
   __device__ __forceinline__ void extend_to_a(State& x) {
-    Acc r[TW][M][2];
+    Acc r[TW][M][kHalves];
     products<1, true>(r, 1, tables + rns::lds_matrix_bytes(NR), kTiles, kLast);
 #pragma unroll
     for (int i = 0; i < TW; ++i)
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         x.a0[i][m] = reduce((u64)column<true, kWide>(r[i][m][0], kc), ka[i][0], ka[i][1]);
-        x.a1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), ka[i][0], ka[i][1]);
+        if constexpr (PAIR) x.a1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), ka[i][0], ka[i][1]);
       }
   }
   // x times the table entry y, or (null) squared
@@ -650,29 +665,31 @@ struct RnsGroup {
     for (int i = 0; i < TW; ++i)
 #pragma unroll
       for (int m = 0; m < M; ++m) {
-        const Quad v = SQ ? Quad{x.a0[i][m], x.a1[i][m], x.b0[i][m], x.b1[i][m]} : *entry_at(y, i, m);
+        const Quad v = SQ ? own(x, i, m) : *entry_at(y, i, m);
         const u32 s0 = reduce(mad64(x.a0[i][m], v[0], 0), ka[i][0], ka[i][1]);
-        const u64 ca = SQ ? mad64(x.a0[i][m] << 1, x.a1[i][m], 0) : mad64(x.a0[i][m], v[1], mad64(x.a1[i][m], v[0], 0));
-        const u32 s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
-        if (owns(i)) {
-          word(0, m, 0, tile(i), lane) = s0 ^ rns::kOmega;
-          word(0, m, 1, tile(i), lane) = s1 ^ rns::kOmega;
-        }
         z[i][m] = reduce(mad64(x.b0[i][m], v[2], 0), kb[i][0], kb[i][1]);
-        const u64 cb = SQ ? mad64(x.b0[i][m] << 1, x.b1[i][m], 0) : mad64(x.b0[i][m], v[3], mad64(x.b1[i][m], v[2], 0));
-        w[i][m] = reduce(mad64(z[i][m], kb[i][3], cb), kb[i][0], kb[i][1]);
+        if (owns(i)) word(0, m, 0, tile(i), lane) = s0 ^ rns::kOmega;
+        if constexpr (PAIR) {
+          const u64 ca = SQ ? mad64(x.a0[i][m] << 1, x.a1[i][m], 0) : mad64(x.a0[i][m], v[1], mad64(x.a1[i][m], v[0], 0));
+          const u32 s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
+          if (owns(i)) word(0, m, 1, tile(i), lane) = s1 ^ rns::kOmega;
+          const u64 cb = SQ ? mad64(x.b0[i][m] << 1, x.b1[i][m], 0) : mad64(x.b0[i][m], v[3], mad64(x.b1[i][m], v[2], 0));
+          w[i][m] = reduce(mad64(z[i][m], kb[i][3], cb), kb[i][0], kb[i][1]);
+        }
       }
     __syncthreads();
-    Acc r[TW][M][2];
+    Acc r[TW][M][kHalves];
     products<0, false>(r, 0, tables, kTiles, kLast);
 #pragma unroll
     for (int i = 0; i < TW; ++i)
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         const u32 t0 = reduce(mad64(z[i][m], kb[i][2], (u64)column<true, kWide>(r[i][m][0], kc)), kb[i][0], kb[i][1]);
-        const u64 col = mad64(w[i][m], kb[i][2], (u64)column<true, kWide>(r[i][m][1], kc));
         x.b0[i][m] = t0;
-        x.b1[i][m] = reduce(mad64(t0, kb[i][0] - kb[i][3], col), kb[i][0], kb[i][1]);
+        if constexpr (PAIR) {
+          const u64 col = mad64(w[i][m], kb[i][2], (u64)column<true, kWide>(r[i][m][1], kc));
+          x.b1[i][m] = reduce(mad64(t0, kb[i][0] - kb[i][3], col), kb[i][0], kb[i][1]);
+        }
       }
     publish(x);
     extend_to_a(x);
@@ -689,18 +706,18 @@ struct RnsGroup {
         const bool ok = (unsigned)(16 * m + e) < left && l < nl;
         const u32* p = src + (size_t)(16 * m + e) * (2 * nl) + l;
         word(0, m, 0, i, lane) = (ok ? p[0] : 0u) ^ rns::kOmega;
-        word(0, m, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
+        if constexpr (PAIR) word(0, m, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
       }
     }
     __syncthreads();
-    Acc r[TW][M][2];
+    Acc r[TW][M][kHalves];
     products<2, false>(r, 0, tables + rns::lds_bytes(NR), kTiles, 16);
 #pragma unroll
     for (int i = 0; i < TW; ++i)
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         x.b0[i][m] = reduce((u64)column<true, kWide>(r[i][m][0], kc), kb[i][0], kb[i][1]);
-        x.b1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), kb[i][0], kb[i][1]);
+        if constexpr (PAIR) x.b1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), kb[i][0], kb[i][1]);
       }
     publish(x);
     extend_to_a(x);
@@ -709,7 +726,7 @@ struct RnsGroup {
   __device__ __forceinline__ void store(const State& x, long long* dst, unsigned left) {
     __syncthreads();  // the bytes of the last product have been read
     publish(x);
-    Acc r[TW][M][2];
+    Acc r[TW][M][kHalves];
     products<2, true>(r, 1, tables + rns::lds_bytes(NR) + rns::in_matrix_bytes(NR), kLimbTiles, 16);
 #pragma unroll
     for (int i = 0; i < TW; ++i)
@@ -719,7 +736,7 @@ struct RnsGroup {
         if (e < left && mine(i, kLimbTiles)) {
           long long* d = dst + (size_t)e * (8 * kLimbTiles) + 4 * tile(i, kLimbTiles) + g;
           d[0] = column<false, kWide>(r[i][m][0], kc);
-          d[4 * kLimbTiles] = column<false, kWide>(r[i][m][1], kc);
+          d[4 * kLimbTiles] = PAIR ? column<false, kWide>(r[i][m][kHalves - 1], kc) : 0;
         }
       }
   }
@@ -728,11 +745,14 @@ struct RnsGroup {
   __device__ __forceinline__ Quad* entry_at(const u32* entry, int i, int m) const {
     return (Quad*)entry + ((wave * TW + i) * M + m) * WAVE + lane;
   }
+  static __device__ __forceinline__ Quad own(const State& x, int i, int m) {
+    return Quad{x.a0[i][m], PAIR ? x.a1[i][m] : 0u, x.b0[i][m], PAIR ? x.b1[i][m] : 0u};
+  }
   __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
 #pragma unroll
     for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int m = 0; m < M; ++m) *entry_at(entry, i, m) = Quad{x.a0[i][m], x.a1[i][m], x.b0[i][m], x.b1[i][m]};
+      for (int m = 0; m < M; ++m) *entry_at(entry, i, m) = own(x, i, m);
   }
   __device__ __forceinline__ void load_state(State& x, const u32* entry) const {
 #pragma unroll
@@ -741,17 +761,19 @@ struct RnsGroup {
       for (int m = 0; m < M; ++m) {
         const Quad v = *entry_at(entry, i, m);
         x.a0[i][m] = v[0];
-        x.a1[i][m] = v[1];
         x.b0[i][m] = v[2];
-        x.b1[i][m] = v[3];
+        if constexpr (PAIR) {
+          x.a1[i][m] = v[1];
+          x.b1[i][m] = v[3];
+        }
       }
   }
 };
 
 // Every block runs the program on 16 M elements at a time. The first `split` blocks run j0, the others j1.
-template <int NR, int TW, int W, int M>
+template <int NR, int TW, int W, int M, bool PAIR>
 __global__ __launch_bounds__(W * 64, (W + 3) / 4) void k_rns_group(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
-  using G = RnsGroup<NR, TW, W, M>;
+  using G = RnsGroup<NR, TW, W, M, PAIR>;
   __shared__ __align__(16) typename G::Shared shared;
   const bool second = blockIdx.x >= split;
   const RnsJob& j = second ? j1 : j0;
@@ -839,7 +861,7 @@ RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int
 }
 
 int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, const haflo_ctx* ctx, uint32_t* ws,
-              const RnsBuffers& b, size_t count, int entries, hipStream_t st) {
+              const RnsBuffers& b, size_t count, int entries, bool pair, hipStream_t st) {
   const int nr = rns::regs_for(m[0]->nl);
   const size_t tiles = (count + 15) / 16;
   const bool group = use_group(ctx, nr, count, jobs);
@@ -861,10 +883,18 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
     job[i].entries = entries;
   }
   if (jobs == 1) job[1] = job[0];
-#define WAVES(NR) \
-  hipLaunchKernelGGL((k_rns<NR>), dim3(blocks * jobs), dim3((unsigned)waves * 64), 0, st, job[0], job[1], blocks, count)
-#define GROUP(NR, TW, W) \
-  hipLaunchKernelGGL((k_rns_group<NR, TW, W, 1>), dim3(blocks * jobs), dim3(W * 64), 0, st, job[0], job[1], blocks, count)
+#define LAUNCH(KERNEL, THREADS) \
+  hipLaunchKernelGGL(KERNEL, dim3(blocks * jobs), dim3(THREADS), 0, st, job[0], job[1], blocks, count)
+#define WAVES(NR)                                             \
+  do {                                                        \
+    if (pair) LAUNCH((k_rns<NR, true>), (unsigned)waves * 64); \
+    else LAUNCH((k_rns<NR, false>), (unsigned)waves * 64);     \
+  } while (0)
+#define GROUP(NR, TW, W)                                              \
+  do {                                                                \
+    if (pair) LAUNCH((k_rns_group<NR, TW, W, 1, true>), W * 64);       \
+    else LAUNCH((k_rns_group<NR, TW, W, 1, false>), W * 64);           \
+  } while (0)
   switch (nr) {
     case 6:
       if (group) GROUP(6, 1, 5);
@@ -878,11 +908,15 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
       if (group) GROUP(18, 2, 9);
       else WAVES(18);
       break;
-    case 36: GROUP(36, 3, 12); break;
+    case 36:
+      if (!pair) return HAFLO_EINVAL;
+      LAUNCH((k_rns_group<36, 3, 12, 1, true>), 12 * 64);
+      break;
     default: return HAFLO_EINVAL;
   }
 #undef GROUP
 #undef WAVES
+#undef LAUNCH
   return hip_status(hipGetLastError());
 }
 

@@ -44,7 +44,7 @@ def without_engine(call, need, out):
     (512, (1, 17, 4097, 12289)),
     (1024, (1, 15, 16, 12288, 12289, 65536 + 17)),
     (2048, (1, 33, 24576, 24577, 65536 + 1)),
-    (4096, (1, 17, 4097)),
+    (4096, (1, 17, 12289)),
 ])
 def test_rns_engine_matches_limb_arithmetic(bits, counts):
     if not torch.cuda.is_available():
