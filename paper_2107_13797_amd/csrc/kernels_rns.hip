@@ -827,11 +827,11 @@ int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
 bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
   return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 3);
 }
+// Window tables of one modulus: one set per block, or per wavefront that has elements
 size_t table_slots(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
   const size_t tiles = (count + 15) / 16;
-  if (use_group(ctx, nr, count, jobs))  // one per block
-    return std::min(tiles, std::max((size_t)ctx->num_cu * group_blocks_per_cu(nr) / (size_t)jobs, (size_t)1));
-  return (tiles + kRnsWavesPerCu - 1) / kRnsWavesPerCu * kRnsWavesPerCu;  // whole blocks
+  if (!use_group(ctx, nr, count, jobs)) return tiles;
+  return std::min(tiles, std::max((size_t)ctx->num_cu * group_blocks_per_cu(nr) / (size_t)jobs, (size_t)1));
 }
 }  // namespace
 
@@ -869,8 +869,8 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
   // over all of them
   size_t waves = (tiles * (size_t)jobs + ctx->num_cu - 1) / ctx->num_cu;
   waves = std::min(std::max(waves, (size_t)1), (size_t)kRnsWavesPerCu);
-  const size_t slots = group ? table_slots(ctx, nr, count, jobs) : (tiles + waves - 1) / waves * waves;
-  const unsigned blocks = (unsigned)(group ? slots : slots / waves);
+  const size_t slots = table_slots(ctx, nr, count, jobs);
+  const unsigned blocks = (unsigned)(group ? slots : (tiles + waves - 1) / waves);
   RnsJob job[2];
   for (int i = 0; i < jobs; ++i) {
     job[i].tables = m[i]->d_rns;

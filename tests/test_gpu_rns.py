@@ -86,3 +86,36 @@ def test_rns_engine_matches_limb_arithmetic(bits, counts):
         del c, plain, want, out
     pub.close()
     prv.close()
+
+
+@pytest.mark.parametrize("bits,count", [(1024, 12800), (1024, 12816), (2048, 3001), (2048, 6160)])
+def test_workspace_is_not_exceeded(bits, count):
+    """Window tables of both moduli of a call end inside the workspace asked for, also where the wavefronts of a block
+    do not divide the tiles: a guard area behind it keeps its contents."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    lib = api.lib()
+    p, q = oracle_key(bits)
+    pub, prv = api.haflo_ctx_create_public(p * q, bits), api.haflo_ctx_create_private(p, q, bits)
+    m = to_dev(random_units_words(count, bits, 3))
+    r = to_dev(random_units_words(count, bits, 4))
+    c, plain = api.haflo_encrypt(pub, m, r), torch.zeros_like(m)
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    guard = 64 << 20
+    for ctx, op in ((pub, _cabi.OP_ENCRYPT), (prv, _cabi.OP_ENCRYPT), (prv, _cabi.OP_DECRYPT)):
+        need = lib.haflo_workspace_bytes(ctx.handle, op, count, 0)
+        ws = torch.full((need + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+        out = torch.zeros_like(c)
+        if op == _cabi.OP_DECRYPT:
+            rc = lib.haflo_decrypt(ctx.handle, C.c_void_p(c.data_ptr()), C.c_void_p(plain.data_ptr()), count,
+                                   C.c_void_p(ws.data_ptr()), need, stream)
+            assert rc == 0 and torch.equal(plain, m)
+        else:
+            rc = lib.haflo_encrypt(ctx.handle, C.c_void_p(m.data_ptr()), C.c_void_p(r.data_ptr()),
+                                   C.c_void_p(out.data_ptr()), count, C.c_void_p(ws.data_ptr()), need, stream)
+            assert rc == 0 and torch.equal(out, c)
+        assert int((ws[need:] != 0x5A).sum()) == 0
+        del ws
+    pub.close()
+    prv.close()
