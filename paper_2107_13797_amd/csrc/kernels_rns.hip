@@ -608,13 +608,17 @@ struct RnsGroup {
         else f[i] = fragment(matrix, tiles, last, i, k, l);
 #pragma unroll
       for (int m = 0; m < M; ++m) {
+        Quad d[kHalves];
 #pragma unroll
         for (int x = 0; x < kHalves; ++x) {
-          Quad d = sh.bytes[buffer][m][x][k][lane];
-          if (ALPHA && k == (NR - 1) / 4) d[(NR - 1) % 4] = g == 2 ? alpha[m][x] : d[(NR - 1) % 4];
-#pragma unroll
-          for (int i = 0; i < TW; ++i) r[i][m][x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d, r[i][m][x], 0, 0, 0);
+          d[x] = sh.bytes[buffer][m][x][k][lane];
+          if (ALPHA && k == (NR - 1) / 4) d[x][(NR - 1) % 4] = g == 2 ? alpha[m][x] : d[x][(NR - 1) % 4];
         }
+#pragma unroll
+        for (int i = 0; i < TW; ++i)
+#pragma unroll
+          for (int x = 0; x < kHalves; ++x)
+            r[i][m][x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d[x], r[i][m][x], 0, 0, 0);
       }
     }
   }
@@ -628,11 +632,9 @@ struct RnsGroup {
       for (int i = 0; i < TW; ++i)
         if (owns(i)) {
           word(1, m, 0, tile(i), lane) = x.b0[i][m] ^ rns::kOmega;
+          if constexpr (PAIR) word(1, m, 1, tile(i), lane) = x.b1[i][m] ^ rns::kOmega;
           s0 += x.b0[i][m] >> 16;
-          if constexpr (PAIR) {
-            word(1, m, 1, tile(i), lane) = x.b1[i][m] ^ rns::kOmega;
-            s1 += x.b1[i][m] >> 16;
-          }
+          if constexpr (PAIR) s1 += x.b1[i][m] >> 16;
         }
       atomicAdd(s + m * kHalves * 16 + (lane & 15), s0);
       if (PAIR) atomicAdd(s + (m * kHalves + 1) * 16 + (lane & 15), s1);
@@ -667,12 +669,17 @@ struct RnsGroup {
       for (int m = 0; m < M; ++m) {
         const Quad v = SQ ? own(x, i, m) : *entry_at(y, i, m);
         const u32 s0 = reduce(mad64(x.a0[i][m], v[0], 0), ka[i][0], ka[i][1]);
-        z[i][m] = reduce(mad64(x.b0[i][m], v[2], 0), kb[i][0], kb[i][1]);
-        if (owns(i)) word(0, m, 0, tile(i), lane) = s0 ^ rns::kOmega;
+        u32 s1 = 0;
         if constexpr (PAIR) {
           const u64 ca = SQ ? mad64(x.a0[i][m] << 1, x.a1[i][m], 0) : mad64(x.a0[i][m], v[1], mad64(x.a1[i][m], v[0], 0));
-          const u32 s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
-          if (owns(i)) word(0, m, 1, tile(i), lane) = s1 ^ rns::kOmega;
+          s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
+        }
+        if (owns(i)) {
+          word(0, m, 0, tile(i), lane) = s0 ^ rns::kOmega;
+          if constexpr (PAIR) word(0, m, 1, tile(i), lane) = s1 ^ rns::kOmega;
+        }
+        z[i][m] = reduce(mad64(x.b0[i][m], v[2], 0), kb[i][0], kb[i][1]);
+        if constexpr (PAIR) {
           const u64 cb = SQ ? mad64(x.b0[i][m] << 1, x.b1[i][m], 0) : mad64(x.b0[i][m], v[3], mad64(x.b1[i][m], v[2], 0));
           w[i][m] = reduce(mad64(z[i][m], kb[i][3], cb), kb[i][0], kb[i][1]);
         }
