@@ -26,9 +26,9 @@
  *   staging calls and the store's upload / download copy and may wait.
  * Workspace: operators that need temporary device memory take a caller-supplied
  *   workspace pointer and its size; haflo_workspace_bytes says how much is
- *   needed. Encryption, decryption and what contains them ask for more than they
- *   need from some batch size on (the window tables of a faster engine) and run
- *   without that engine when they get less. The library never allocates device
+ *   needed. Encryption, decryption, scalar multiplication and what contains them ask
+ *   for more than they need (the window tables of a faster engine) and run without
+ *   that engine when they get less. The library never allocates device
  *   memory inside an operator call.
  *   Contents of the workspace are undefined afterwards; two calls that share a
  *   workspace must be ordered on one stream.

@@ -377,8 +377,13 @@ static void build_prog_decrypt(DevProg& p, const Big& e, Uploader& up) {
 
 // The RNS engine's tables for ms = s and the pair constants that lead into its Montgomery form and out of it
 // (`out` R / M_A is what a result in that form is multiplied with), added to `special`.
+static const Big& special_of(const std::vector<std::pair<int, Big>>& special, int which) {
+  for (const std::pair<int, Big>& e : special)
+    if (e.first == which) return e.second;
+  return special.front().second;
+}
 static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
-                      std::vector<std::pair<int, Big>>& special, Uploader& up) {
+                      std::vector<std::pair<int, Big>>& special, Uploader& up, bool stored = false) {
   if (!rns::regs_for(ms.nl)) return;
   ms.d_rns = up.put(rns::build_tables(s, ms.nl, &ms.rns_radix));
   const Big R = Big::mod(Big::pow2((size_t)kLimbBits * ms.nl), s2);
@@ -404,6 +409,17 @@ static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
     inv = mh.mul(inv, mh.to_mont(Big::from_words(q.data(), q.size())));
   }
   special.push_back({kConstMOut, mh.from_mont(inv)});
+  if (stored) {
+    // R_N, the radix of stored ciphertexts: their halves times M_A R / R_N and M_A R^2 / R_N, a power times R R_N / M_A
+    // (`out` is R R_N there, so this is the constant above over R)
+    const Big half = Big::add(s2, Big(1)).shr1();
+    const Big r_inv = mh.powmod(half, Big((uint64_t)kLimbBits * (uint64_t)ms.nl));
+    const Big rn_inv = mh.mul(mh.to_mont(r_inv), r_inv);  // R_N = R^2
+    const Big rn_inv_m = mh.to_mont(rn_inv);
+    special.push_back({kConstMLo, mh.mul(special_of(special, kConstM1), rn_inv_m)});
+    special.push_back({kConstMHi, mh.mul(special_of(special, kConstM2), rn_inv_m)});
+    special.push_back({kConstMStored, mh.mul(mh.from_mont(inv), mh.to_mont(r_inv))});
+  }
 }
 static void put_prog(DevProg& p, std::vector<uint32_t> ins, int table_entries, Uploader& up) {
   p.host = std::move(ins);
@@ -469,8 +485,12 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
     build_prog_encrypt_pairs(ctx->prog_enc_pairs, ctx->prog_enc.sched, up);
     if (!p) {
       // r -> r M_A; the power; -> r^n R R_N -> times (1 + m n): the ciphertext in the stored Montgomery form
-      build_rns(ctx->Nh, n, ctx->nsq, Big::mod(Big::mul(R, RN), ctx->nsq), special, up);
+      build_rns(ctx->Nh, n, ctx->nsq, Big::mod(Big::mul(R, RN), ctx->nsq), special, up, true);
       if (ctx->Nh.d_rns) {
+        put_prog(ctx->prog_rns_power_in,
+                 {eng_ins(ENG_LOAD_L, 1), eng_ins(ENG_MUL_C, kConstMHi), eng_ins(ENG_STORE_T, 0), eng_ins(ENG_LOAD_L, 0),
+                  eng_ins(ENG_MUL_C, kConstMLo), eng_ins(ENG_ADD_T, 0)}, 1, up);
+        put_prog(ctx->prog_rns_power_out, {eng_ins(ENG_LOAD_COL), eng_ins(ENG_MUL_C, kConstMStored)}, 1, up);
         build_prog_rns(ctx->prog_rns_enc, ctx->prog_enc.sched, up);
         put_prog(ctx->prog_rns_enc_in, {eng_ins(ENG_LOAD_W, 1), eng_ins(ENG_MUL_C, kConstM1)}, 1, up);
         put_prog(ctx->prog_rns_enc_out,

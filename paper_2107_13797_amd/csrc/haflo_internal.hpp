@@ -69,7 +69,9 @@ enum {
   kConstR1 = 0, kConstR2 = 1, kConstR3 = 2, kConstOne = 3, kConstExtra = 4, kConstR4 = 5, kConstR5 = 6,
   // into the RNS engine's Montgomery form (radix M_A) and out of it: R^k M_A for k = 1 .. 4, and an operator's own
   kConstM1 = 7, kConstM2 = 8, kConstM3 = 9, kConstM4 = 10, kConstMOut = 11,
-  kNumConst = 12
+  // the same for stored ciphertexts: their lower and upper halves into the form, a power out of it
+  kConstMLo = 12, kConstMHi = 13, kConstMStored = 14,
+  kNumConst = 15
 };
 inline uint32_t eng_ins(uint32_t op, uint32_t a = 0, uint32_t b = 0) { return op | (a << 8) | (b << 20); }
 
@@ -134,6 +136,7 @@ struct haflo_ctx {
   haflo::DevProg prog_lift_pairs_p, prog_lift_pairs_q;  // key owner's encryption, second stage, on pairs modulo p, q
   // the RNS engine's programs: the powers alone, and what takes elements into its form and out of it on the pair engine
   haflo::DevProg prog_rns_enc, prog_rns_enc_in, prog_rns_enc_out;
+  haflo::DevProg prog_rns_power_in, prog_rns_power_out;  // around powers of stored ciphertexts
   haflo::DevProg prog_rns_dec_p, prog_rns_dec_q, prog_rns_dec_in;
   haflo::DevProg prog_rns_low_p, prog_rns_low_q, prog_rns_low_in;
   haflo::DevProg prog_rns_lift_p, prog_rns_lift_q, prog_rns_lift_in, prog_rns_priv_out;
@@ -197,6 +200,7 @@ int static_scratch_init();
 size_t ws_encrypt(const haflo_ctx* ctx, size_t count);      // what a call asks for
 size_t ws_encrypt_min(const haflo_ctx* ctx, size_t count);  // what it can do with (without the RNS engine)
 size_t ws_scalar_mul(const haflo_ctx* ctx, size_t count);
+size_t ws_scalar_mul_min(const haflo_ctx* ctx, size_t count);
 size_t ws_encrypt_obf(const haflo_ctx* ctx, size_t count);
 size_t ws_decrypt(const haflo_ctx* ctx, size_t count);
 size_t ws_decrypt_min(const haflo_ctx* ctx, size_t count);
@@ -211,7 +215,7 @@ int power_tables(const haflo_ctx* ctx, const uint32_t* d_c, uint32_t* d_tables, 
 int invert_batch(const haflo_ctx* ctx, const uint32_t* in, uint32_t* out, size_t count, hipStream_t st);
 
 // Powers of pairs modulo m[i]^2 by the RNS engine (kernels_rns.hip), one or two moduli of the same size side by
-// side: elements [x0 limbs][x1 limbs] at in[i] to columns at out[i], `count` <= rns_chunk() of them. Without `pair`
+// side (a program without device memory travels in the launch): elements [x0 limbs][x1 limbs] at in[i] to columns at out[i], `count` <= rns_chunk() of them. Without `pair`
 // powers of x0 modulo m[i] alone (x1 = 0 in the result).
 struct RnsBuffers {  // workspace of one chunk, in 32-bit words from its start
   size_t in[2], out[2], tables, total;

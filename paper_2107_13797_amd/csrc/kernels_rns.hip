@@ -37,15 +37,17 @@ struct QuadSet {
   Acc q[N];
 };
 
+constexpr int kRnsInline = 96;  // instructions that travel with the launch: 90 at most for a 63-bit scalar
 struct RnsJob {
   const u32* tables;  // rns.hpp's device layout
-  const u32* prog;    // ENG_SQ, ENG_MUL_T, ENG_MUL_T_ST, ENG_STORE_T, ENG_LOAD_T only
+  const u32* prog;    // null: `ins`; ENG_SQ, ENG_MUL_T, ENG_MUL_T_ST, ENG_STORE_T, ENG_LOAD_T only
   int len;
   const u32* in;      // per element [x0: nl limbs][x1: nl limbs], limbs below 2^32
   int nl;
   long long* out;     // per element [x0: columns][x1: columns] of weight 2^(29 l), signed
   u32* slots;         // window tables: 4 NR dwords per lane and entry
   int entries;
+  u32 ins[kRnsInline];
 };
 
 // The residues of x0 and x1 (PAIR; else of one value, x0) of a lane in one base, in the registers that the matrix
@@ -439,7 +441,7 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
   // the same for the whole wavefront, so that what follows from it stays in scalar registers
   const size_t wave = (size_t)block * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
   constexpr size_t kEntry = 2 * RnsEngine<NR, PAIR>::kArray;
-  const u32* prog = j.prog;
+  const u32* prog = j.prog ? j.prog : j.ins;
   const int len = __builtin_amdgcn_readfirstlane(j.len);
   u32* table = j.slots + wave * (size_t)j.entries * kEntry;
   for (size_t tile = wave; tile * 16 < count; tile += (size_t)nblocks * waves) {
@@ -787,7 +789,7 @@ __global__ __launch_bounds__(W * 64, (W + 3) / 4) void k_rns_group(RnsJob j0, Rn
   const unsigned block = second ? blockIdx.x - split : blockIdx.x;
   const unsigned nblocks = second ? gridDim.x - split : split;
   G e(shared, j.tables);
-  const u32* prog = j.prog;
+  const u32* prog = j.prog ? j.prog : j.ins;
   const int len = __builtin_amdgcn_readfirstlane(j.len);
   u32* table = j.slots + (size_t)block * (size_t)j.entries * G::kEntry;
   for (size_t first = (size_t)block * (16 * M); first < count; first += (size_t)nblocks * (16 * M)) {
@@ -883,6 +885,10 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
     job[i].tables = m[i]->d_rns;
     job[i].prog = prog[i]->d_ins;
     job[i].len = (int)prog[i]->host.size();
+    if (!prog[i]->d_ins) {
+      if (prog[i]->host.size() > (size_t)kRnsInline) return HAFLO_EINVAL;
+      std::copy(prog[i]->host.begin(), prog[i]->host.end(), job[i].ins);
+    }
     job[i].in = ws + b.in[i];
     job[i].nl = m[i]->nl;
     job[i].out = (long long*)(ws + b.out[i]);

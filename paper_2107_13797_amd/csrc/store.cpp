@@ -454,7 +454,8 @@ int haflo_h_scalar_mul(haflo_store* s, haflo_handle cipher, int64_t k, uint32_t 
   int rc = HAFLO_ENOMEM;
   {
     Scratch ws(s);
-    if (ws.take(haflo_workspace_bytes(s->ctx, HAFLO_OP_SCALAR_MUL, count, 0)))
+    if (ws.take(haflo_workspace_bytes(s->ctx, HAFLO_OP_SCALAR_MUL, count, 0)) ||
+        ws.take(haflo::ws_scalar_mul_min(s->ctx, count)))
       rc = haflo_scalar_mul_i64_bcast(s->ctx, s->ptr(oc), k, s->base + off, count, ws.ptr(), ws.bytes, s->st);
   }
   if (rc != HAFLO_OK) {
@@ -486,7 +487,7 @@ int haflo_h_scalar_mul_each(haflo_store* s, haflo_handle cipher, haflo_handle sc
   int rc = HAFLO_ENOMEM;
   {
     Scratch ws(s);
-    if (ws.take(haflo_workspace_bytes(s->ctx, HAFLO_OP_SCALAR_MUL, count, 0)))
+    if (ws.take(haflo::ws_scalar_mul_min(s->ctx, count)))
       rc = haflo_scalar_mul_u64(s->ctx, s->ptr(oc), (const uint64_t*)s->ptr(ok), s->base + off, count, ws.ptr(),
                                 ws.bytes, s->st);
   }

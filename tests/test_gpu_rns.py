@@ -119,3 +119,26 @@ def test_workspace_is_not_exceeded(bits, count):
         del ws
     pub.close()
     prv.close()
+
+
+@pytest.mark.parametrize("bits", [512, 1024, 2048])
+def test_powers_by_one_scalar_match_small_batches(bits):
+    """A scalar of 17 bits and more over a large array goes through the residue form: the same bits as in slices that
+    are too small for it, in place as well."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    p, q = oracle_key(bits)
+    n = p * q
+    count = 8192 + 33
+    pub = api.haflo_ctx_create_public(n, bits)
+    c = api.haflo_encrypt(pub, to_dev(random_units_words(count, bits, 5)), to_dev(random_units_words(count, bits, 6)))
+    for k in (2 ** 16, (1 << 21) + 1, 2 ** 63 - 1, -(1 << 40) - 77, 12345):
+        print("scalar", bits, k, flush=True)
+        got = api.haflo_scalar_mul_i64_bcast(pub, c, k)
+        idx = [slice(0, 300), slice(count - 300, count)]
+        for s in idx:
+            assert torch.equal(got[s], api.haflo_scalar_mul_i64_bcast(pub, c[s].contiguous(), k))
+        a, b = (dev_to_ints(api.haflo_export_cipher(pub, t[7:8].contiguous()))[0] for t in (c, got))
+        assert b == pow(a, k, n * n)
+    pub.close()
