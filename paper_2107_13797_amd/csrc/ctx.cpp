@@ -384,7 +384,6 @@ static const Big& special_of(const std::vector<std::pair<int, Big>>& special, in
 }
 static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
                       std::vector<std::pair<int, Big>>& special, Uploader& up, bool stored = false) {
-  if (!rns::regs_for(ms.nl)) return;
   ms.d_rns = up.put(rns::build_tables(s, ms.nl, &ms.rns_radix));
   const Big R = Big::mod(Big::pow2((size_t)kLimbBits * ms.nl), s2);
   const MontHost mh(s2);
@@ -483,20 +482,18 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
                                                 {kConstR4, Big::mod(Big::mul(r2, rn_inv), ctx->nsq)},
                                                 {kConstR5, Big::mod(Big::mul(r3, rn_inv), ctx->nsq)}};
     build_prog_encrypt_pairs(ctx->prog_enc_pairs, ctx->prog_enc.sched, up);
-    if (!p) {
+    if (!p && rns::usable(n, nl_h)) {
       // r -> r M_A; the power; -> r^n R R_N -> times (1 + m n): the ciphertext in the stored Montgomery form
       build_rns(ctx->Nh, n, ctx->nsq, Big::mod(Big::mul(R, RN), ctx->nsq), special, up, true);
-      if (ctx->Nh.d_rns) {
-        put_prog(ctx->prog_rns_power_in,
-                 {eng_ins(ENG_LOAD_L, 1), eng_ins(ENG_MUL_C, kConstMHi), eng_ins(ENG_STORE_T, 0), eng_ins(ENG_LOAD_L, 0),
-                  eng_ins(ENG_MUL_C, kConstMLo), eng_ins(ENG_ADD_T, 0)}, 1, up);
-        put_prog(ctx->prog_rns_power_out, {eng_ins(ENG_LOAD_COL), eng_ins(ENG_MUL_C, kConstMStored)}, 1, up);
-        build_prog_rns(ctx->prog_rns_enc, ctx->prog_enc.sched, up);
-        put_prog(ctx->prog_rns_enc_in, {eng_ins(ENG_LOAD_W, 1), eng_ins(ENG_MUL_C, kConstM1)}, 1, up);
-        put_prog(ctx->prog_rns_enc_out,
-                 {eng_ins(ENG_LOAD_COL), eng_ins(ENG_MUL_C, kConstMOut), eng_ins(ENG_STORE_T, 0),
-                  eng_ins(ENG_LOAD_W1, 0), eng_ins(ENG_MUL_T, 0)}, 1, up);
-      }
+      put_prog(ctx->prog_rns_power_in,
+               {eng_ins(ENG_LOAD_L, 1), eng_ins(ENG_MUL_C, kConstMHi), eng_ins(ENG_STORE_T, 0), eng_ins(ENG_LOAD_L, 0),
+                eng_ins(ENG_MUL_C, kConstMLo), eng_ins(ENG_ADD_T, 0)}, 1, up);
+      put_prog(ctx->prog_rns_power_out, {eng_ins(ENG_LOAD_COL), eng_ins(ENG_MUL_C, kConstMStored)}, 1, up);
+      build_prog_rns(ctx->prog_rns_enc, ctx->prog_enc.sched, up);
+      put_prog(ctx->prog_rns_enc_in, {eng_ins(ENG_LOAD_W, 1), eng_ins(ENG_MUL_C, kConstM1)}, 1, up);
+      put_prog(ctx->prog_rns_enc_out,
+               {eng_ins(ENG_LOAD_COL), eng_ins(ENG_MUL_C, kConstMOut), eng_ins(ENG_STORE_T, 0),
+                eng_ins(ENG_LOAD_W1, 0), eng_ins(ENG_MUL_T, 0)}, 1, up);
     }
     build_pair_consts(ctx->Nh, n, ctx->nsq, special, up);
   }
@@ -515,11 +512,13 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
     if (!up.ok) return HAFLO_ENOMEM;
     build_prog_decrypt(ctx->prog_dec_p, Big::sub(*p, Big(1)), up);
     build_prog_decrypt(ctx->prog_dec_q, Big::sub(*q, Big(1)), up);
+    // both sides or neither: a launch serves the two moduli with one engine
+    const bool residues = rns::usable(*p, nl_q) && rns::usable(*q, nl_q);
     for (int side = 0; side < 2; ++side) {
       ModHost& ms = side ? ctx->Q : ctx->P;
       const ModHost& ms2 = side ? ctx->Q2 : ctx->P2;
       std::vector<std::pair<int, Big>> special;
-      build_rns(ms, ms.mod, ms2.mod, Big(1), special, up);
+      if (residues) build_rns(ms, ms.mod, ms2.mod, Big(1), special, up);
       build_pair_consts(ms, ms.mod, ms2.mod, special, up);
     }
     build_prog_decrypt_pairs(ctx->prog_dec_pairs_p, ctx->prog_dec_p.sched, up);
@@ -533,7 +532,7 @@ static int ctx_build(haflo_ctx* ctx, const Big& n, const Big* p, const Big* q, u
       build_prog_encrypt_lift(ctx->prog_lift_q, *q, up);
       build_prog_lift_pairs(ctx->prog_lift_pairs_p, ctx->prog_lift_p.sched, up);
       build_prog_lift_pairs(ctx->prog_lift_pairs_q, ctx->prog_lift_q.sched, up);
-      if (ctx->P.d_rns) {
+      if (residues) {
         build_prog_rns(ctx->prog_rns_dec_p, ctx->prog_dec_p.sched, up);
         build_prog_rns(ctx->prog_rns_dec_q, ctx->prog_dec_q.sched, up);
         build_prog_rns(ctx->prog_rns_low_p, ctx->prog_enc_p.sched, up);

@@ -137,7 +137,18 @@ class Matrix {
   std::vector<uint8_t> bytes_;
 };
 
-// All tables for the modulus s (odd, prime to the channel primes), as one array of 32-bit words, and M_A.
+// Whether the engine can work modulo s on nl 29-bit limbs: there is one for this size, and no prime of either base divides
+// s (1 / s is a constant of every channel). Keys have no factor of 30 bits; a public modulus may be any odd number.
+inline bool usable(const Big& s, int nl) {
+  const int nr = regs_for(nl);
+  if (!nr) return false;
+  for (uint32_t residue : {1u, 3u})
+    for (uint32_t p : primes(primes_for(nr), residue))
+      if (s.mod_small(p) == 0) return false;
+  return true;
+}
+
+// All tables for the modulus s (odd, usable()), as one array of 32-bit words, and M_A.
 inline std::vector<uint32_t> build_tables(const Big& s, int nl, Big* m_a) {
   const int nr = regs_for(nl), k = primes_for(nr);
   const std::vector<uint32_t> a = primes(k, 3), b = primes(k, 1);

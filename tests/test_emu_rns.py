@@ -1,0 +1,78 @@
+"""The residue number system engine's host side and routes on the CPU build of the library's sources (see
+test_emu_kernels.py): moduli it must leave alone, workspaces without room for it, the cost of its tables."""
+import ctypes as C
+import random
+
+import pytest
+
+from paper_2107_13797_amd import _cabi, synth
+
+from test_emu_kernels import emu, words, ws, zeros  # noqa: F401
+
+
+def public_ctx(lib, n, bits):
+    ctx = C.c_void_p()
+    buf = (C.c_uint8 * (bits // 8)).from_buffer_copy(n.to_bytes(bits // 8, "little"))
+    assert lib.haflo_ctx_create_public(buf, bits, C.byref(ctx)) == 0
+    return ctx
+
+
+def export_n(lib, ctx, bits, d_cipher, count):
+    out = zeros(lib, (count, bits // 16))
+    assert lib.haflo_export_cipher(ctx, d_cipher.p, out.p, count, None) == 0
+    return synth.words_to_ints(out.get())
+
+
+def channel_prime(residue, index):
+    """The index-th largest prime below 2^30 of the class residue modulo 4 (3: base A, 1: base B)."""
+    c = (1 << 30) - 4 + residue
+    while True:
+        if all(c % d for d in range(3, 32768, 2)):
+            if index == 0:
+                return c
+            index -= 1
+        c -= 4
+
+
+def odd_multiple(prime, bits, seed):
+    rng = random.Random(seed)
+    while True:
+        n = prime * (rng.getrandbits(bits) // prime | 1)
+        if n.bit_length() == bits:
+            return n
+
+
+# the first and the last prime of both bases of a 512-bit modulus (18 each), and one prime of the bases of larger moduli
+@pytest.mark.parametrize("residue,index", [(3, 0), (3, 17), (1, 0), (1, 17), (3, 18)])
+def test_moduli_that_share_a_factor_with_the_channel_primes(emu, residue, index):  # noqa: F811
+    """Any odd n of the right length makes a public context; one that a channel prime divides has no residues modulo
+    that prime to work with and is served by the limb arithmetic."""
+    lib, bits = emu, 512
+    n = odd_multiple(channel_prime(residue, index), bits, 100 * residue + index)
+    nsq, rng = n * n, random.Random(7)
+    ctx = public_ctx(lib, n, bits)
+    ms, rs = [rng.randrange(n) for _ in range(3)], [rng.randrange(1, n) for _ in range(3)]
+    d_c = zeros(lib, (3, bits * 9 // 128))
+    w, nb = ws(lib, ctx, _cabi.OP_ENCRYPT, 3)
+    assert lib.haflo_encrypt(ctx, words(lib, ms, bits // 32).p, words(lib, rs, bits // 32).p, d_c.p, 3, w.p, nb, None) == 0
+    got = export_n(lib, ctx, bits, d_c, 3)
+    lib.haflo_ctx_destroy(ctx)
+    assert got == [(1 + m * n) * pow(r, n, nsq) % nsq for m, r in zip(ms, rs)]
+
+
+@pytest.mark.parametrize("residue,index", [(3, 20), (1, 34)])
+def test_scalar_powers_modulo_multiples_of_channel_primes(emu, residue, index):  # noqa: F811
+    """The same for powers of large arrays by one scalar, at 1024 bits (35 primes a base); 32 elements are a large array
+    on the one-unit emulated chip."""
+    lib, bits, count = emu, 1024, 33
+    n = odd_multiple(channel_prime(residue, index), bits, residue)
+    nsq, rng = n * n, random.Random(8)
+    ctx = public_ctx(lib, n, bits)
+    cs = [rng.randrange(nsq) for _ in range(count)]
+    d_c, d_o = zeros(lib, (count, bits * 9 // 128)), zeros(lib, (count, bits * 9 // 128))
+    assert lib.haflo_import_cipher(ctx, words(lib, cs, bits // 16).p, d_c.p, None, count, None) == 0
+    w, nb = ws(lib, ctx, _cabi.OP_SCALAR_MUL, count)
+    assert lib.haflo_scalar_mul_i64_bcast(ctx, d_c.p, (1 << 16) + 5, d_o.p, count, w.p, nb, None) == 0
+    got = export_n(lib, ctx, bits, d_o, count)
+    lib.haflo_ctx_destroy(ctx)
+    assert got == [pow(c, (1 << 16) + 5, nsq) for c in cs]
