@@ -25,11 +25,11 @@
  *   a HIP graph and replayed on new contents of the same buffers; the
  *   staging calls and the store's upload / download copy and may wait.
  * Workspace: operators that need temporary device memory take a caller-supplied
- *   workspace pointer and its size; haflo_workspace_bytes says how much is
- *   needed. Encryption, decryption, scalar multiplication and what contains them ask
+ *   workspace pointer and its size; haflo_workspace_bytes says how much they ask
+ *   for. Encryption, decryption, scalar multiplication and what contains them ask
  *   for more than they need (the window tables of a faster engine) and run without
- *   that engine when they get less. The library never allocates device
- *   memory inside an operator call.
+ *   that engine when they get less, down to haflo_workspace_bytes_least. The library
+ *   never allocates device memory inside an operator call.
  *   Contents of the workspace are undefined afterwards; two calls that share a
  *   workspace must be ordered on one stream.
  *
@@ -154,11 +154,17 @@ int haflo_op_cost(const haflo_ctx* ctx, int op, uint64_t* montmuls, uint32_t* mo
  * Defined for HAFLO_OP_ENCRYPT on a public context and HAFLO_OP_DECRYPT. */
 int haflo_op_work(const haflo_ctx* ctx, int op, uint64_t* mads_executed);
 
-/* Workspace needed by an operator call of the given shape. For element-wise
+/* Workspace an operator call of the given shape asks for. For element-wise
  * operators `rows` is the element count and `cols` is ignored; for the matvecs
  * they are the matrix shape. Returns 0 for operators that need none and
  * (size_t)-1 on bad arguments. */
 size_t haflo_workspace_bytes(const haflo_ctx* ctx, int op, size_t rows, size_t cols);
+
+/* The least workspace the same call accepts. Smaller than haflo_workspace_bytes
+ * where the call asks for room for a faster engine's window tables (encryption,
+ * decryption, scalar multiplication, haflo_fore_gradient, haflo_taylor_loss): with
+ * anything in between it runs without that engine, with the same results. */
+size_t haflo_workspace_bytes_least(const haflo_ctx* ctx, int op, size_t rows, size_t cols);
 
 /*
  * Serialisation boundary (paper Section 3.2, "Data Preprocessing" /

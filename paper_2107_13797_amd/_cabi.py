@@ -25,6 +25,7 @@ PROTOTYPES = {
     "haflo_op_cost": (c_int, [c_void_p, c_int, C.POINTER(c_u64), C.POINTER(c_u32)]),
     "haflo_op_work": (c_int, [c_void_p, c_int, C.POINTER(c_u64)]),
     "haflo_workspace_bytes": (c_size_t, [c_void_p, c_int, c_size_t, c_size_t]),
+    "haflo_workspace_bytes_least": (c_size_t, [c_void_p, c_int, c_size_t, c_size_t]),
     "haflo_import_cipher": (c_int, [c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]),
     "haflo_export_cipher": (c_int, [c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]),
     "haflo_encode_f32": (c_int, [c_void_p, c_void_p, c_u32, c_void_p, c_void_p, c_size_t, c_void_p]),

@@ -206,6 +206,7 @@ size_t ws_decrypt(const haflo_ctx* ctx, size_t count);
 size_t ws_decrypt_min(const haflo_ctx* ctx, size_t count);
 // workspace of the Taylor-loss sequence in bytes (kernels_loss.hip)
 size_t ws_taylor_loss(const haflo_ctx* ctx, size_t count);
+size_t ws_taylor_loss_min(const haflo_ctx* ctx, size_t count);
 
 // tables[i][d] = c_i^d for d < entries (kernels_modexp.hip)
 int power_tables(const haflo_ctx* ctx, const uint32_t* d_c, uint32_t* d_tables, int entries, size_t count,

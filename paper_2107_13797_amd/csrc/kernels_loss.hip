@@ -105,9 +105,10 @@ __global__ __launch_bounds__(WAVE) void k_loss_plain(const Wide* __restrict__ pa
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct LossPlan {
-  size_t off_k, off_partial, off_plain, off_t1, off_t2, off_t3, off_ws, ws_bytes, total;
+  size_t off_k, off_partial, off_plain, off_t1, off_t2, off_t3, off_ws, total;
 };
-LossPlan loss_plan(const haflo_ctx* ctx, size_t count) {
+// `encrypt`: the workspace of the one encryption, what it asks for or what it can do with
+LossPlan loss_plan(const haflo_ctx* ctx, size_t count, size_t encrypt) {
   LossPlan p;
   const size_t cipher = align256((size_t)ctx->N.nl * 4);
   size_t b = 0;
@@ -119,11 +120,9 @@ LossPlan loss_plan(const haflo_ctx* ctx, size_t count) {
   p.off_t3 = b;       b += cipher;
   p.off_ws = b;
   size_t w = haflo_workspace_bytes(ctx, HAFLO_OP_MATVEC_XT_D, count, 1);
-  size_t e = haflo_workspace_bytes(ctx, HAFLO_OP_ENCRYPT, 1, 0);
+  if (encrypt > w) w = encrypt;
+  const size_t e = haflo_workspace_bytes(ctx, HAFLO_OP_ENCRYPT_OBFUSCATOR, 1, 0);
   if (e > w) w = e;
-  e = haflo_workspace_bytes(ctx, HAFLO_OP_ENCRYPT_OBFUSCATOR, 1, 0);
-  if (e > w) w = e;
-  p.ws_bytes = w;
   p.total = b + w;
   return p;
 }
@@ -131,7 +130,8 @@ LossPlan loss_plan(const haflo_ctx* ctx, size_t count) {
 }  // namespace
 
 namespace haflo {
-size_t ws_taylor_loss(const haflo_ctx* ctx, size_t count) { return loss_plan(ctx, count).total; }
+size_t ws_taylor_loss(const haflo_ctx* ctx, size_t count) { return loss_plan(ctx, count, ws_encrypt(ctx, 1)).total; }
+size_t ws_taylor_loss_min(const haflo_ctx* ctx, size_t count) { return loss_plan(ctx, count, ws_encrypt_min(ctx, 1)).total; }
 }  // namespace haflo
 
 extern "C" {
@@ -142,8 +142,9 @@ int haflo_taylor_loss(const haflo_ctx* ctx, const void* d_c_u, const void* d_c_u
   if (!ctx || scale_bits > 27 || !d_out || (count && (!d_c_u || !d_c_u2 || !d_u_guest || !d_label)))
     return HAFLO_EINVAL;
   if (count > 0xFFFFFFFFull) return HAFLO_EINVAL;
-  const LossPlan p = loss_plan(ctx, count);
+  const LossPlan p = loss_plan(ctx, count, ws_encrypt_min(ctx, 1));
   if (!d_workspace || workspace_bytes < p.total) return HAFLO_EINVAL;
+  const size_t ws_bytes = workspace_bytes - p.off_ws;
   hipStream_t st = (hipStream_t)stream;
   char* base = (char*)d_workspace;
   int* k = (int*)(base + p.off_k);
@@ -164,14 +165,14 @@ int haflo_taylor_loss(const haflo_ctx* ctx, const void* d_c_u, const void* d_c_u
   one.threads = WAVE;
   one.gpb = WAVE;
   HAFLO_LAUNCH(k_loss_plain, one, st, (const Wide*)partial, sh.blocks, (const u32*)ctx->d_n_words, ctx->lp, plain);
-  int rc = haflo_cipher_matvec(ctx, 0, d_c_u, k, count, 1, t1, ws, p.ws_bytes, stream);
+  int rc = haflo_cipher_matvec(ctx, 0, d_c_u, k, count, 1, t1, ws, ws_bytes, stream);
   if (rc != HAFLO_OK) return rc;
-  rc = haflo_cipher_sum(ctx, d_c_u2, count, t2, ws, p.ws_bytes, stream);
+  rc = haflo_cipher_sum(ctx, d_c_u2, count, t2, ws, ws_bytes, stream);
   if (rc != HAFLO_OK) return rc;
   // without an r the plaintext part enters as g^P = 1 + P n (obfuscator 1): two products instead of a
   // full exponentiation; the result is still randomised by the host's ciphertexts
-  rc = d_r ? haflo_encrypt(ctx, plain, d_r, t3, 1, ws, p.ws_bytes, stream)
-           : haflo_encrypt_with_obfuscator(ctx, plain, ctx->N.ref().r1, t3, 1, ws, p.ws_bytes, stream);
+  rc = d_r ? haflo_encrypt(ctx, plain, d_r, t3, 1, ws, ws_bytes, stream)
+           : haflo_encrypt_with_obfuscator(ctx, plain, ctx->N.ref().r1, t3, 1, ws, ws_bytes, stream);
   if (rc != HAFLO_OK) return rc;
   rc = haflo_add(ctx, t1, t2, t1, 1, stream);
   if (rc != HAFLO_OK) return rc;

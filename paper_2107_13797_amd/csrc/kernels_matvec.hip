@@ -904,6 +904,19 @@ size_t haflo_workspace_bytes(const haflo_ctx* ctx, int op, size_t rows, size_t c
   }
 }
 
+size_t haflo_workspace_bytes_least(const haflo_ctx* ctx, int op, size_t rows, size_t cols) {
+  const size_t asked = haflo_workspace_bytes(ctx, op, rows, cols);
+  if (asked == (size_t)-1) return asked;
+  switch (op) {
+    case HAFLO_OP_ENCRYPT: return ws_encrypt_min(ctx, rows);
+    case HAFLO_OP_DECRYPT: return ws_decrypt_min(ctx, rows);
+    case HAFLO_OP_SCALAR_MUL: return ws_scalar_mul_min(ctx, rows);
+    case HAFLO_OP_FORE_GRADIENT: return asked - ws_encrypt(ctx, rows) + ws_encrypt_min(ctx, rows);
+    case HAFLO_OP_TAYLOR_LOSS: return ws_taylor_loss_min(ctx, rows);
+    default: return asked;
+  }
+}
+
 int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, const int32_t* d_X, size_t rows,
                         size_t cols, void* d_out, void* d_workspace, size_t workspace_bytes, void* stream) {
   if (!ctx || (orientation != 0 && orientation != 1)) return HAFLO_EINVAL;

@@ -3,11 +3,14 @@ test_emu_kernels.py): moduli it must leave alone, workspaces without room for it
 import ctypes as C
 import random
 
+import numpy as np
 import pytest
 
+from conftest import oracle_key
+from oracle import paillier_oracle as O
 from paper_2107_13797_amd import _cabi, synth
 
-from test_emu_kernels import emu, words, ws, zeros  # noqa: F401
+from test_emu_kernels import Dev, emu, words, ws, zeros  # noqa: F401
 
 
 def public_ctx(lib, n, bits):
@@ -76,3 +79,35 @@ def test_scalar_powers_modulo_multiples_of_channel_primes(emu, residue, index): 
     got = export_n(lib, ctx, bits, d_o, count)
     lib.haflo_ctx_destroy(ctx)
     assert got == [pow(c, (1 << 16) + 5, nsq) for c in cs]
+
+
+def test_taylor_loss_in_the_least_workspace(emu):  # noqa: F811
+    """The loss sequence contains one encryption and runs, like encryption itself, in a workspace without room for the
+    engine's tables, with and without randomness of its own; one byte less is refused."""
+    lib, bits, count, s = emu, 512, 5, 20
+    p, q = oracle_key(bits)
+    pk = O.PrivateKey(p, q).public
+    rng = random.Random(9)
+    ctx = public_ctx(lib, pk.n, bits)
+    ug = synth.normal_f32(count, 1.5, 42)
+    y = np.where(np.arange(count) % 2 == 0, 1.0, -1.0).astype(np.float32)
+    c_u, c_u2 = ([rng.randrange(2, pk.nsq) for _ in range(count)] for _ in range(2))
+    r = rng.randrange(1, pk.n)
+    nlw = bits * 9 // 128
+    d_u, d_u2, d_o = zeros(lib, (count, nlw)), zeros(lib, (count, nlw)), zeros(lib, (1, nlw))
+    for src, dst in ((c_u, d_u), (c_u2, d_u2)):
+        assert lib.haflo_import_cipher(ctx, words(lib, src, bits // 16).p, dst.p, None, count, None) == 0
+    asked = lib.haflo_workspace_bytes(ctx, _cabi.OP_TAYLOR_LOSS, count, 0)
+    least = lib.haflo_workspace_bytes_least(ctx, _cabi.OP_TAYLOR_LOSS, count, 0)
+    assert least < asked
+    d_ug, d_y, d_r = Dev(lib, ug), Dev(lib, y), words(lib, [r], bits // 32)
+    for nb in (least, asked):
+        w = Dev(lib, np.zeros(nb, np.uint8))  # ends at a guard page
+        for with_r in (True, False):
+            assert lib.haflo_taylor_loss(ctx, d_u.p, d_u2.p, d_ug.p, d_y.p, d_r.p if with_r else None, s, d_o.p, None,
+                                         count, w.p, nb, None) == 0, (nb, with_r)
+            want, _ = O.taylor_loss(pk, c_u, c_u2, [float(v) for v in ug], [float(v) for v in y], r if with_r else 1, s)
+            assert export_n(lib, ctx, bits, d_o, 1) == [want], (nb, with_r)
+    assert lib.haflo_taylor_loss(ctx, d_u.p, d_u2.p, d_ug.p, d_y.p, d_r.p, s, d_o.p, None, count, w.p, least - 1,
+                                 None) == -1
+    lib.haflo_ctx_destroy(ctx)
