@@ -71,14 +71,31 @@ class Context:
         self.n_bits, self.cipher_limbs, self.plain_limbs = nb.value, lc.value, lp.value
         self.cipher_words = cb.value // 4  # int32 words of one internal ciphertext
         self._ws = None
+        self._refused = float("inf")  # bytes that the device had no room for
 
-    def workspace(self, nbytes):
+    def workspace(self, nbytes, least=None):
+        """A buffer of `nbytes` or, where the device has no room for that, of the bytes that `least()` names."""
         if nbytes == 2 ** 64 - 1:
             raise HafloError("bad workspace query")
         need = max(nbytes, 256)
-        if self._ws is None or self._ws.numel() < need:
-            self._ws = None
+        held = 0 if self._ws is None else self._ws.numel()
+        if held >= need:
+            return self._ws
+        small = need if least is None else max(least(), 256)
+        if small < need and need >= self._refused:
+            # a refused size is asked for again only once there is room: a failed allocation empties torch's cache
+            if torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved() - torch.cuda.memory_allocated() + held < need:
+                need = small
+                if held >= need:
+                    return self._ws
+        self._ws = None
+        try:
             self._ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError:
+            if small >= need:
+                raise
+            self._refused = need
+            self._ws = torch.empty(small, dtype=torch.uint8, device="cuda")
         return self._ws
 
     def close(self):
@@ -124,6 +141,16 @@ def haflo_ctx_set_xtd_bucket_min_rows(ctx, min_rows):
 
 def haflo_workspace_bytes(ctx, op, rows, cols=0):
     return lib().haflo_workspace_bytes(ctx.handle, op, rows, cols)
+
+
+def haflo_workspace_bytes_least(ctx, op, rows, cols=0):
+    """The least workspace the call accepts (haflo_workspace_bytes asks for room for a faster engine's tables)."""
+    return lib().haflo_workspace_bytes_least(ctx.handle, op, rows, cols)
+
+
+def _workspace(ctx, op, rows, cols=0):
+    return ctx.workspace(haflo_workspace_bytes(ctx, op, rows, cols),
+                         lambda: haflo_workspace_bytes_least(ctx, op, rows, cols))
 
 
 def haflo_op_work(ctx, op):
@@ -183,8 +210,7 @@ def haflo_encrypt(ctx, plain, r, out=None):
     count = plain.shape[0]
     if out is None:
         out = _new_cipher(ctx, count)
-    nb = haflo_workspace_bytes(ctx, _cabi.OP_ENCRYPT, count)
-    ws = ctx.workspace(nb)
+    ws = _workspace(ctx, _cabi.OP_ENCRYPT, count)
     _check(lib().haflo_encrypt(ctx.handle, _ptr(plain), _ptr(r), _ptr(out), count, _ptr(ws), ws.numel(), _stream()))
     return out
 
@@ -193,7 +219,7 @@ def haflo_fore_gradient(ctx, c_host, logits_guest, label, r, scale_bits, out=Non
     count = c_host.shape[0]
     if out is None:
         out = _new_cipher(ctx, count)
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, _cabi.OP_FORE_GRADIENT, count))
+    ws = _workspace(ctx, _cabi.OP_FORE_GRADIENT, count)
     _check(lib().haflo_fore_gradient(ctx.handle, _ptr(c_host), _ptr(logits_guest), _ptr(label), _ptr(r), scale_bits,
                                      _ptr(out), _ptr(status) if status is not None else None, count, _ptr(ws),
                                      ws.numel(), _stream()))
@@ -204,7 +230,7 @@ def haflo_encrypt_with_obfuscator(ctx, plain, obfuscator, out=None):
     count = plain.shape[0]
     if out is None:
         out = _new_cipher(ctx, count)
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, _cabi.OP_ENCRYPT_OBFUSCATOR, count))
+    ws = _workspace(ctx, _cabi.OP_ENCRYPT_OBFUSCATOR, count)
     _check(lib().haflo_encrypt_with_obfuscator(ctx.handle, _ptr(plain), _ptr(obfuscator), _ptr(out), count, _ptr(ws),
                                                ws.numel(), _stream()))
     return out
@@ -213,7 +239,7 @@ def haflo_encrypt_with_obfuscator(ctx, plain, obfuscator, out=None):
 def haflo_taylor_loss(ctx, c_u, c_u2, u_guest, label, r, scale_bits, status=None):
     count = c_u.shape[0]
     out = _new_cipher(ctx, 1)
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, _cabi.OP_TAYLOR_LOSS, count))
+    ws = _workspace(ctx, _cabi.OP_TAYLOR_LOSS, count)
     _check(lib().haflo_taylor_loss(ctx.handle, _ptr(c_u), _ptr(c_u2), _ptr(u_guest), _ptr(label),
                                    _ptr(r) if r is not None else None, scale_bits,
                                    _ptr(out), _ptr(status) if status is not None else None, count, _ptr(ws),
@@ -225,8 +251,7 @@ def haflo_decrypt(ctx, cipher, out=None):
     count = cipher.shape[0]
     if out is None:
         out = torch.empty((count, ctx.plain_limbs), dtype=torch.int32, device="cuda")
-    nb = haflo_workspace_bytes(ctx, _cabi.OP_DECRYPT, count)
-    ws = ctx.workspace(nb)
+    ws = _workspace(ctx, _cabi.OP_DECRYPT, count)
     _check(lib().haflo_decrypt(ctx.handle, _ptr(cipher), _ptr(out), count, _ptr(ws), ws.numel(), _stream()))
     return out
 
@@ -252,7 +277,7 @@ def haflo_scalar_mul_u64(ctx, c, k, out=None):
     count = c.shape[0]
     if out is None:
         out = _new_cipher(ctx, count)
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, _cabi.OP_SCALAR_MUL, count))
+    ws = ctx.workspace(haflo_workspace_bytes_least(ctx, _cabi.OP_SCALAR_MUL, count))
     _check(lib().haflo_scalar_mul_u64(ctx.handle, _ptr(c), _ptr(k), _ptr(out), count, _ptr(ws), ws.numel(), _stream()))
     return out
 
@@ -261,7 +286,7 @@ def haflo_scalar_mul_i64_bcast(ctx, c, k, out=None):
     count = c.shape[0]
     if out is None:
         out = _new_cipher(ctx, count)
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, _cabi.OP_SCALAR_MUL, count))
+    ws = _workspace(ctx, _cabi.OP_SCALAR_MUL, count)
     _check(lib().haflo_scalar_mul_i64_bcast(ctx.handle, _ptr(c), int(k), _ptr(out), count, _ptr(ws), ws.numel(),
                                             _stream()))
     return out
@@ -273,7 +298,7 @@ def haflo_cipher_matvec(ctx, orientation, c, X, out=None):
     if out is None:
         out = _new_cipher(ctx, nout)
     op = _cabi.OP_MATVEC_XT_D if orientation == 0 else _cabi.OP_MATVEC_X_W
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, op, rows, cols))
+    ws = _workspace(ctx, op, rows, cols)
     _check(lib().haflo_cipher_matvec(ctx.handle, orientation, _ptr(c), _ptr(X), rows, cols, _ptr(out), _ptr(ws),
                                      ws.numel(), _stream()))
     return out
@@ -282,7 +307,7 @@ def haflo_cipher_matvec(ctx, orientation, c, X, out=None):
 def haflo_cipher_sum(ctx, c):
     count = c.shape[0]
     out = _new_cipher(ctx, 1)
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_XT_D, count, 1))
+    ws = _workspace(ctx, _cabi.OP_MATVEC_XT_D, count, 1)
     _check(lib().haflo_cipher_sum(ctx.handle, _ptr(c), count, _ptr(out), _ptr(ws), ws.numel(), _stream()))
     return out
 
@@ -293,7 +318,7 @@ def haflo_cipher_sum_segments(ctx, c, offsets, status=None):
     if offsets.dtype != torch.int32 or nseg < 0:
         raise HafloError("offsets: int32 tensor of nseg + 1 entries")
     out = _new_cipher(ctx, nseg)
-    ws = ctx.workspace(haflo_workspace_bytes(ctx, _cabi.OP_SUM_SEGMENTS, count, nseg))
+    ws = _workspace(ctx, _cabi.OP_SUM_SEGMENTS, count, nseg)
     _check(lib().haflo_cipher_sum_segments(ctx.handle, _ptr(c) if count else None, count, _ptr(offsets), nseg,
                                            _ptr(out) if nseg else None, _ptr(status), _ptr(ws), ws.numel(), _stream()))
     return out
