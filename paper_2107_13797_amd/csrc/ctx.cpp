@@ -262,8 +262,8 @@ static void build_prog_encrypt_pairs(DevProg& p, const HostSched& sched, Uploade
 
 // x < s^2 as the pair (x mod s, x div s), nl limbs each
 static std::vector<uint32_t> pair_limbs(const Big& x, const Big& n, int nl) {
-  const Big lo = Big::mod(x, n);
-  const Big hi = Big::div(x, n);
+  Big lo, hi;
+  Big::divmod(x, n, &hi, &lo);
   std::vector<uint32_t> v = to_limbs29(lo, nl), h = to_limbs29(hi, nl);
   v.insert(v.end(), h.begin(), h.end());
   return v;
@@ -393,20 +393,16 @@ static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
     c = mh.mul(c, rm);
     special.push_back({i, c});
   }
-  // out R / M_A modulo s^2, one prime of M_A after the other: 1 / a = (1 + s^2 t) / a with t = -1 / s^2 mod a
-  Big inv = mh.mul(mh.to_mont(out), rm);
+  // out R / M_A modulo s^2: 1 / M_A = (1 + s^2 t) / M_A with t = -1 / s^2 mod M_A from its residues
+  Big t;
   for (uint32_t a : rns::primes(rns::primes_for(rns::regs_for(ms.nl)), 3)) {
-    const uint32_t t = a - rns::invmod(s2.mod_small(a), a);
-    const Big num = Big::add(Big::mul(s2, Big((uint64_t)t)), Big(1));
-    std::vector<uint32_t> q(num.w.size());
-    uint64_t rem = 0;
-    for (size_t i = num.w.size(); i-- > 0;) {
-      rem = rem << 32 | num.w[i];
-      q[i] = (uint32_t)(rem / a);
-      rem %= a;
-    }
-    inv = mh.mul(inv, mh.to_mont(Big::from_words(q.data(), q.size())));
+    const Big rest = Big::div(ms.rns_radix, Big((uint64_t)a));
+    const uint32_t v = a - rns::invmod(s2.mod_small(a), a);
+    t = Big::add(t, Big::mul(rest, Big((uint64_t)rns::mulmod(v, rns::invmod(rest.mod_small(a), a), a))));
   }
+  t = Big::mod(t, ms.rns_radix);
+  const Big radix_inv = Big::div(Big::add(Big::mul(s2, t), Big(1)), ms.rns_radix);
+  const Big inv = mh.mul(mh.mul(mh.to_mont(out), rm), mh.to_mont(radix_inv));
   special.push_back({kConstMOut, mh.from_mont(inv)});
   if (stored) {
     // R_N, the radix of stored ciphertexts: their halves times M_A R / R_N and M_A R^2 / R_N, a power times R R_N / M_A

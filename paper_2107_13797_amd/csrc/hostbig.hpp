@@ -147,36 +147,87 @@ class Big {
     for (size_t i = w.size(); i-- > 0;) r = ((r << 32) | w[i]) % d;
     return (uint32_t)r;
   }
-  // a mod m by binary shift-and-subtract (only used for per-key constants)
-  static Big mod(const Big& a, const Big& m) {
-    if (cmp(a, m) < 0) return a;
-    Big r;
-    for (size_t i = a.bits(); i-- > 0;) {
-      r = r.shl1();
-      if (a.bit(i)) {
-        if (r.w.empty()) r.w.push_back(1);
-        else r.w[0] |= 1;
-      }
-      if (r >= m) r = sub(r, m);
+  // a = q m + r, 0 <= r < m, for m > 0: the schoolbook division on 32-bit words (Knuth, The Art of Computer
+  // Programming, vol. 2, 4.3.1, algorithm D). Either result may be null.
+  static void divmod(const Big& a, const Big& m, Big* quot, Big* rem) {
+    const size_t n = m.w.size();
+    if (cmp(a, m) < 0) {
+      if (rem) *rem = a;
+      if (quot) *quot = Big();
+      return;
     }
+    Big q;
+    q.w.assign(a.w.size() - n + 1, 0);
+    if (n == 1) {
+      uint64_t r = 0;
+      for (size_t i = a.w.size(); i-- > 0;) {
+        r = (r << 32) | a.w[i];
+        q.w[i] = (uint32_t)(r / m.w[0]);
+        r %= m.w[0];
+      }
+      if (rem) *rem = Big(r);
+    } else {
+      // both shifted left until the divisor's top bit is set: a digit estimated from the top words is at most 2 too large
+      const int sh = __builtin_clz(m.w.back());
+      const auto shifted = [sh](const Big& x, size_t i) {  // word i of x 2^sh
+        const uint64_t v = ((uint64_t)x.word(i) << 32) | (i ? x.word(i - 1) : 0u);
+        return (uint32_t)((v << sh) >> 32);
+      };
+      std::vector<uint32_t> u(a.w.size() + 1), v(n);
+      for (size_t i = 0; i < u.size(); ++i) u[i] = shifted(a, i);
+      for (size_t i = 0; i < n; ++i) v[i] = shifted(m, i);
+      for (size_t j = q.w.size(); j-- > 0;) {
+        const uint64_t top = ((uint64_t)u[j + n] << 32) | u[j + n - 1];
+        uint64_t d = top / v[n - 1], r = top % v[n - 1];
+        while (d >> 32 || d * v[n - 2] > ((r << 32) | u[j + n - 2])) {
+          --d;
+          r += v[n - 1];
+          if (r >> 32) break;
+        }
+        uint64_t carry = 0;
+        int64_t borrow = 0;
+        for (size_t i = 0; i < n; ++i) {
+          carry += d * v[i];
+          borrow += (int64_t)u[i + j] - (int64_t)(uint32_t)carry;
+          u[i + j] = (uint32_t)borrow;
+          borrow >>= 32;
+          carry >>= 32;
+        }
+        borrow += (int64_t)u[j + n] - (int64_t)carry;
+        u[j + n] = (uint32_t)borrow;
+        if (borrow < 0) {  // one too large after all
+          --d;
+          uint64_t c = 0;
+          for (size_t i = 0; i < n; ++i) {
+            c += (uint64_t)u[i + j] + v[i];
+            u[i + j] = (uint32_t)c;
+            c >>= 32;
+          }
+          u[j + n] += (uint32_t)c;
+        }
+        q.w[j] = (uint32_t)d;
+      }
+      if (rem) {
+        Big r;
+        r.w.resize(n);
+        for (size_t i = 0; i < n; ++i) r.w[i] = (uint32_t)((((uint64_t)u[i + 1] << 32) | u[i]) >> sh);
+        r.trim();
+        *rem = r;
+      }
+    }
+    if (quot) {
+      q.trim();
+      *quot = q;
+    }
+  }
+  static Big mod(const Big& a, const Big& m) {
+    Big r;
+    divmod(a, m, nullptr, &r);
     return r;
   }
-  // floor(a / m) by the same shift-and-subtract
   static Big div(const Big& a, const Big& m) {
-    Big r, q;
-    q.w.assign((a.bits() + 31) / 32, 0);
-    for (size_t i = a.bits(); i-- > 0;) {
-      r = r.shl1();
-      if (a.bit(i)) {
-        if (r.w.empty()) r.w.push_back(1);
-        else r.w[0] |= 1;
-      }
-      if (r >= m) {
-        r = sub(r, m);
-        q.w[i / 32] |= 1u << (i % 32);
-      }
-    }
-    q.trim();
+    Big q;
+    divmod(a, m, &q, nullptr);
     return q;
   }
   static Big gcd(Big a, Big b) {

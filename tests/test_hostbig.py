@@ -110,3 +110,20 @@ def test_inverse_modulo_a_power_of_two(shim):
         x = rng.getrandbits(rng.choice((8, 64, 1024))) | 1
         inv = call(shim, "inv_pow2", x, k=k)
         assert inv < (1 << k) and (inv * x) % (1 << k) == 1
+
+
+def test_division_by_words(shim):
+    """Estimated quotient digits that are one or two too large, and those that must be corrected by adding the divisor
+    back: operands of words next to 0, 2^31 and 2^32, beside two that are known to need it."""
+    cases = [(0x7FFFFFFF_80000000_00000000_00000000, 0x80000000_00000000_00000001),
+             (0x80000000_FFFFFFFE_00000000, 0x80000000_FFFFFFFF), ((1 << 96) - 1, 1 << 32), ((1 << 96) - 1, (1 << 64) - 1)]
+    rng = random.Random(3)
+    words = [0, 1, 2, 2 ** 31 - 1, 2 ** 31, 2 ** 31 + 1, 2 ** 32 - 2, 2 ** 32 - 1]
+
+    def number(n):
+        return sum(rng.choice(words) << (32 * i) for i in range(n))
+
+    cases += [(number(rng.randrange(1, 9)), number(rng.randrange(1, 6)) or 1) for _ in range(3000)]
+    for a, b in cases:
+        assert call(shim, "div", a, b) == a // b, (hex(a), hex(b))
+        assert call(shim, "mod", a, b) == a % b, (hex(a), hex(b))
