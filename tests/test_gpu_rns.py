@@ -142,3 +142,35 @@ def test_powers_by_one_scalar_match_small_batches(bits):
         a, b = (dev_to_ints(api.haflo_export_cipher(pub, t[7:8].contiguous()))[0] for t in (c, got))
         assert b == pow(a, k, n * n)
     pub.close()
+
+
+@pytest.mark.parametrize("bits,count", [(1024, 24576), (1024, 24577), (1024, 45000), (1024, 80000)])
+def test_key_owner_is_not_slower_with_the_workspace_asked_for(bits, count):
+    """Both sides of the rule that leaves the first stage on limbs: the same bits as in the least workspace, which is
+    the limb arithmetic throughout, and no slower. (45000 and 80000 elements took 1.07 and 1.09 of its time with both
+    stages in residues, 0.98 now; the bound leaves 6 % for what runs of one side differ.)"""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    lib = api.lib()
+    p, q = oracle_key(bits)
+    prv = api.haflo_ctx_create_private(p, q, bits)
+    m, r = to_dev(random_units_words(count, bits, 8)), to_dev(random_units_words(count, bits, 9))
+    sizes = [f(prv.handle, _cabi.OP_ENCRYPT, count, 0) for f in (lib.haflo_workspace_bytes, lib.haflo_workspace_bytes_least)]
+    ws = torch.empty(max(sizes), dtype=torch.uint8, device="cuda")
+    out = [torch.zeros((count, prv.cipher_words), dtype=torch.int32, device="cuda") for _ in sizes]
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    best = [1e9, 1e9]
+    for _ in range(9):
+        for i, nbytes in enumerate(sizes):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            assert lib.haflo_encrypt(prv.handle, C.c_void_p(m.data_ptr()), C.c_void_p(r.data_ptr()),
+                                     C.c_void_p(out[i].data_ptr()), count, C.c_void_p(ws.data_ptr()), nbytes, stream) == 0
+            b.record()
+            b.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b))
+    print("owner", bits, count, best, flush=True)
+    prv.close()
+    assert torch.equal(out[0], out[1])
+    assert best[0] < 1.04 * best[1]
