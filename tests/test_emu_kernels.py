@@ -78,8 +78,10 @@ def export(lib, ctx, d_cipher, count):
     return synth.words_to_ints(out.get())
 
 
-def ws(lib, ctx, op, rows, cols=0):
-    nb = lib.haflo_workspace_bytes(ctx, op, rows, cols)
+def ws(lib, ctx, op, rows, cols=0, room="asked"):
+    """The workspace a call asks for, or the least it accepts: without room for the residue number system's tables, so
+    that the powers run on limbs."""
+    nb = (lib.haflo_workspace_bytes if room == "asked" else lib.haflo_workspace_bytes_least)(ctx, op, rows, cols)
     assert nb != 2 ** 64 - 1
     return zeros(lib, (nb // 4 + 1,)), nb
 
@@ -415,17 +417,19 @@ def test_wider_lane_groups(emu, bits):
     lib.haflo_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("room", ["least", "asked"])
 @pytest.mark.parametrize("bits,count", [
     (1024, 1),
     # the pair engine with one pair per wavefront (36 lanes, 2 limbs of each half): a minute and a half emulated
     pytest.param(2048, 1, marks=pytest.mark.skipif(not os.environ.get("HAFLO_SLOW_TESTS"),
                                                    reason="slow: set HAFLO_SLOW_TESTS=1")),
 ])
-def test_whole_wavefront_groups_encrypt_decrypt(emu, bits, count):
+def test_whole_wavefront_groups_encrypt_decrypt(emu, bits, count, room):
     """Batches of at most one element per SIMD give every big integer a wavefront to itself (18 to 48
     lanes with 2 or 3 limbs each, neighbour exchange across DPP rows, the quotient digit through a
     scalar register): the full encryption program with the public key, the key owner's two-stage
-    route and the decryption through p^2 and q^2, against the oracle."""
+    route and the decryption through p^2 and q^2, against the oracle. With the workspace asked for, the
+    powers go to the residue number system's blocks instead and the conversions keep this geometry."""
     lib = emu
     p, q = oracle_key(bits)
     sk = O.PrivateKey(p, q)
@@ -450,12 +454,12 @@ def test_whole_wavefront_groups_encrypt_decrypt(emu, bits, count):
     lc_out = zeros(lib, (count, lc))
     for ctx in (pub, own):
         d_c = zeros(lib, (count, nlw))
-        w, nb = ws(lib, ctx, _cabi.OP_ENCRYPT, count)
+        w, nb = ws(lib, ctx, _cabi.OP_ENCRYPT, count, room=room)
         assert lib.haflo_encrypt(ctx, words(lib, ms, lp).p, words(lib, rs, lp).p, d_c.p, count, w.p, nb, None) == 0
         assert lib.haflo_export_cipher(ctx, d_c.p, lc_out.p, count, None) == 0
         assert synth.words_to_ints(lc_out.get()) == want
     d_pl = zeros(lib, (count, lp))
-    w, nb = ws(lib, own, _cabi.OP_DECRYPT, count)
+    w, nb = ws(lib, own, _cabi.OP_DECRYPT, count, room=room)
     assert lib.haflo_decrypt(own, d_c.p, d_pl.p, count, w.p, nb, None) == 0
     assert synth.words_to_ints(d_pl.get()) == ms
     lib.haflo_ctx_destroy(own)
@@ -466,7 +470,8 @@ def test_pair_arithmetic_on_batches_that_fill_the_chip(env):
     """Batches beyond what the wide geometries take (more than 128 integers of two lanes, or 256 of one
     lane, on the one-unit emulated chip) run the exponentiations on pairs of half-length residues: the
     public-key encryption, the key owner's second stage, both decryption branches and the ciphertext
-    powers (with their conversion into and out of the pair form), all against the oracle."""
+    powers (with their conversion into and out of the pair form), all against the oracle. The public
+    route in both workspaces: on limbs, and with room for the residue number system."""
     lib, ctx, sk, nlw = env
     pk = sk.public
     n, nsq = pk.n, pk.nsq
@@ -487,10 +492,11 @@ def test_pair_arithmetic_on_batches_that_fill_the_chip(env):
     assert lib.haflo_encrypt(ctx, d_m.p, d_r.p, d_c.p, count, w.p, nb, None) == 0
     assert export(lib, ctx, d_c, count) == want
     sub = 140
-    d_cp = zeros(lib, (sub, nlw))
-    w, nb = ws(lib, pub, _cabi.OP_ENCRYPT, sub)
-    assert lib.haflo_encrypt(pub, d_m.p, d_r.p, d_cp.p, sub, w.p, nb, None) == 0
-    assert export(lib, pub, d_cp, sub) == want[:sub]
+    for room in ("least", "asked"):
+        d_cp = zeros(lib, (sub, nlw))
+        w, nb = ws(lib, pub, _cabi.OP_ENCRYPT, sub, room=room)
+        assert lib.haflo_encrypt(pub, d_m.p, d_r.p, d_cp.p, sub, w.p, nb, None) == 0
+        assert export(lib, pub, d_cp, sub) == want[:sub], room
     d_pl = zeros(lib, (count, lp))
     w, nb = ws(lib, ctx, _cabi.OP_DECRYPT, count)
     assert lib.haflo_decrypt(ctx, d_c.p, d_pl.p, count, w.p, nb, None) == 0

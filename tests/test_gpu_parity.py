@@ -53,6 +53,18 @@ def context(api, bits):
 
 from helpers import dev_to_ints, ints_to_dev, random_units_words, to_dev  # noqa: E402
 
+@pytest.fixture(params=["asked", "least"])
+def room(request, api, monkeypatch):
+    """Calls in the workspace they ask for, and in the least they accept: without room for the residue number system's
+    tables, so that the exponentiations run on limbs in the geometry of their batch."""
+    if request.param == "least":
+        def least_workspace(ctx, nbytes, least=None):
+            assert nbytes != 2 ** 64 - 1
+            return torch.empty(max(least() if least else nbytes, 256), dtype=torch.uint8, device="cuda")
+        monkeypatch.setattr(api.Context, "workspace", least_workspace)
+    return request.param
+
+
 # X^T [[d]] has two implementations chosen by the row count (power tables below the threshold,
 # buckets above); the threshold is a setting of the context, so either can be forced.
 XTD_METHODS = {"tables": 2 ** 64 - 1, "buckets": 1}
@@ -739,7 +751,7 @@ def test_random_operator_mixes(api):
 
 @pytest.mark.parametrize("bits,counts", [(1024, (512, 513, 1024, 1025, 1500, 2048, 2049)), (2048, (512, 513, 1500, 2049)),
                                          (4096, (1024, 1025))])
-def test_batch_sizes_around_the_geometry_switches(api, bits, counts):
+def test_batch_sizes_around_the_geometry_switches(api, bits, counts, room):
     """Batch sizes on both sides of the points where a launch changes the lanes it gives a big integer
     (a wavefront each up to one or two elements per SIMD, then twice the lanes of the modulus, then its own
     geometry): both encryption routes agree, sampled ciphertexts match the oracle, decryption returns
@@ -751,7 +763,7 @@ def test_batch_sizes_around_the_geometry_switches(api, bits, counts):
     pub = api.haflo_ctx_create_public(n, bits)
     rng = random.Random(bits)
     for count in counts:
-        say("geometry switch", bits, count)
+        say("geometry switch", bits, count, room)
         ms = [rng.randrange(n) for _ in range(count)]
         rs = [rng.randrange(1, n) for _ in range(count)]
         c = api.haflo_encrypt(pub, ints_to_dev(ms, lp), ints_to_dev(rs, lp))
@@ -958,7 +970,7 @@ def test_encrypt_with_obfuscator_matches_encrypt(api):
 
 
 @pytest.mark.parametrize("extra", ["few", "half_a_pass"])
-def test_batch_with_partial_last_pass(api, extra):
+def test_batch_with_partial_last_pass(api, extra, room):
     """A batch larger than the resident lane groups is run as full passes plus a remainder launch (a
     small remainder in the geometry of a small batch, a large one on pairs like the full passes);
     elements on both sides of the cut and at the very end must be right."""

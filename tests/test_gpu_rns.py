@@ -16,28 +16,29 @@ from paper_2107_13797_amd import _cabi  # noqa: E402
 from helpers import dev_to_ints, ints_to_dev, random_units_words, to_dev  # noqa: E402
 
 
-
-def encrypt_in(lib, ctx, m, r, nbytes, out):
-    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-    return lib.haflo_encrypt(ctx.handle, C.c_void_p(m.data_ptr()), C.c_void_p(r.data_ptr()), C.c_void_p(out.data_ptr()),
-                             m.shape[0], C.c_void_p(ws.data_ptr()), nbytes,
-                             C.c_void_p(torch.cuda.current_stream().cuda_stream))
-
-
-def decrypt_in(lib, ctx, c, nbytes, out):
-    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-    return lib.haflo_decrypt(ctx.handle, C.c_void_p(c.data_ptr()), C.c_void_p(out.data_ptr()), c.shape[0],
-                             C.c_void_p(ws.data_ptr()), nbytes, C.c_void_p(torch.cuda.current_stream().cuda_stream))
-
-
-def without_engine(call, need, out):
-    """The call in ever smaller workspaces until it is refused; the smallest accepted one has no room for the engine."""
-    best = None
-    nbytes = need - 1
-    while nbytes > 4096 and call(nbytes, out) == 0:
-        best = out.clone()
-        nbytes = nbytes * 3 // 4
-    return best
+def on_limbs(api, ctx, op, args, out):
+    """The call on slices of its arrays, each in the least workspace it accepts, which has no room for the engine."""
+    lib, count = api.lib(), args[0].shape[0]
+    sizes = lib.haflo_workspace_bytes, lib.haflo_workspace_bytes_least
+    step = count
+    while True:
+        asked, least = (f(ctx.handle, op, step, 0) for f in sizes)
+        if least < asked:
+            break
+        assert step > 1
+        step = (step + 1) // 2
+    for at in range(0, count, step):
+        part = [t[at:at + step].contiguous() for t in args]
+        n = part[0].shape[0]
+        asked, least = (f(ctx.handle, op, n, 0) for f in sizes)
+        assert least < asked
+        ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+        fn = lib.haflo_encrypt if op == _cabi.OP_ENCRYPT else lib.haflo_decrypt
+        res = torch.empty_like(out[:n])
+        assert fn(ctx.handle, *[C.c_void_p(t.data_ptr()) for t in part], C.c_void_p(res.data_ptr()), n,
+                  C.c_void_p(ws.data_ptr()), least, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        out[at:at + n] = res
+    return out
 
 
 @pytest.mark.parametrize("bits,counts", [
@@ -50,7 +51,6 @@ def test_rns_engine_matches_limb_arithmetic(bits, counts):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2107_13797_amd import api
-    lib = api.lib()
     p, q = oracle_key(bits)
     n = p * q
     top = max(counts)
@@ -65,33 +65,30 @@ def test_rns_engine_matches_limb_arithmetic(bits, counts):
     for count in counts:
         print("rns", bits, count, flush=True)
         mc, rc = m[:count].contiguous(), r[:count].contiguous()
-        need = lib.haflo_workspace_bytes(pub.handle, _cabi.OP_ENCRYPT, count, 0)
-        c, out = api.haflo_encrypt(pub, mc, rc), None
-        out = torch.zeros_like(c)
-        want = without_engine(lambda nb, o: encrypt_in(lib, pub, mc, rc, nb, o), need, out)
-        if want is not None:
-            assert torch.equal(c, want)
+        c = api.haflo_encrypt(pub, mc, rc)
+        assert torch.equal(c, on_limbs(api, pub, _cabi.OP_ENCRYPT, (mc, rc), torch.zeros_like(c)))
         for i in {0, count // 2, count - 1}:
             mi, ri = dev_to_ints(mc[i:i + 1])[0], dev_to_ints(rc[i:i + 1])[0]
             assert dev_to_ints(api.haflo_export_cipher(pub, c[i:i + 1].contiguous()))[0] == \
                 (1 + mi * n) * pow(ri, n, n * n) % (n * n)
         assert torch.equal(api.haflo_encrypt(prv, mc, rc), c)
         plain = api.haflo_decrypt(prv, c)
-        need = lib.haflo_workspace_bytes(prv.handle, _cabi.OP_DECRYPT, count, 0)
-        want = without_engine(lambda nb, o: decrypt_in(lib, prv, c, nb, o), need, torch.zeros_like(plain))
         keep = torch.arange(count, device="cuda") != 4  # r = 0 gives no ciphertext: what it decrypts to is not defined
-        if want is not None:
+        if bits > 512:  # the primes of a 512-bit key are too small for the engine
+            want = on_limbs(api, prv, _cabi.OP_DECRYPT, (c,), torch.zeros_like(plain))
             assert torch.equal(plain[keep], want[keep])
         assert torch.equal(plain[keep], mc[keep])
-        del c, plain, want, out
+        del c, plain
     pub.close()
     prv.close()
 
 
-@pytest.mark.parametrize("bits,count", [(1024, 12800), (1024, 12816), (2048, 3001), (2048, 6160)])
+@pytest.mark.parametrize("bits,count", [(512, 6160), (1024, 12800), (1024, 12816), (2048, 3001), (2048, 6160),
+                                        (2048, 8209), (4096, 17), (4096, 2064)])
 def test_workspace_is_not_exceeded(bits, count):
     """Window tables of both moduli of a call end inside the workspace asked for, also where the wavefronts of a block
-    do not divide the tiles: a guard area behind it keeps its contents."""
+    do not divide the tiles: a guard area behind it keeps its contents. From 8192 elements on (1024 and 2048 bits) the
+    powers by one scalar have such tables too."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2107_13797_amd import api
@@ -117,14 +114,22 @@ def test_workspace_is_not_exceeded(bits, count):
             assert rc == 0 and torch.equal(out, c)
         assert int((ws[need:] != 0x5A).sum()) == 0
         del ws
+    need = lib.haflo_workspace_bytes(pub.handle, _cabi.OP_SCALAR_MUL, count, 0)
+    ws, out = torch.full((need + guard,), 0x5A, dtype=torch.uint8, device="cuda"), torch.zeros_like(c)
+    k = 2 ** 63 - 1  # the largest plan
+    assert lib.haflo_scalar_mul_i64_bcast(pub.handle, C.c_void_p(c.data_ptr()), k, C.c_void_p(out.data_ptr()), count,
+                                          C.c_void_p(ws.data_ptr()), need, stream) == 0
+    assert int((ws[need:] != 0x5A).sum()) == 0
+    a, b = (dev_to_ints(api.haflo_export_cipher(pub, t[count - 1:].contiguous()))[0] for t in (c, out))
+    assert b == pow(a, k, (p * q) ** 2)
     pub.close()
     prv.close()
 
 
 @pytest.mark.parametrize("bits", [512, 1024, 2048])
 def test_powers_by_one_scalar_match_small_batches(bits):
-    """A scalar of 17 bits and more over a large array goes through the residue form: the same bits as in slices that
-    are too small for it, in place as well."""
+    """A scalar of 17 bits and more over a large array goes through the residue form at 1024 and 2048 bits (at 512 it
+    stays on limbs): the same bits as in slices that are too small for it, in place as well."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2107_13797_amd import api
@@ -141,6 +146,8 @@ def test_powers_by_one_scalar_match_small_batches(bits):
             assert torch.equal(got[s], api.haflo_scalar_mul_i64_bcast(pub, c[s].contiguous(), k))
         a, b = (dev_to_ints(api.haflo_export_cipher(pub, t[7:8].contiguous()))[0] for t in (c, got))
         assert b == pow(a, k, n * n)
+        own = c.clone()
+        assert torch.equal(api.haflo_scalar_mul_i64_bcast(pub, own, k, out=own), got)
     pub.close()
 
 
