@@ -476,7 +476,7 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
   }
 }
 
-// The same arithmetic with the slots of 16 M elements spread over the W wavefronts of a block, TW tiles each, for
+// The same arithmetic with the slots of 16 elements spread over the W wavefronts of a block, TW tiles each, for
 // batches that would leave most of the chip idle with a wavefront per 16 elements, and for moduli whose matrices do not
 // fit the LDS. A wavefront keeps the residues of its own slots and multiplies and reduces them alone; what every
 // wavefront needs of the others, the bytes of all residues, goes through LDS (16 bytes per lane and block of 64, as the
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
 // and compute unit). Measured against the limb arithmetic on one wavefront per integer: 1024 encryptions at a 1024-bit
 // key 2.67 -> 1.04 ms, 256 at 2048 bits 8.5 -> 3.9, 3001 at 4096 bits 74.9 -> 27.2; 3072 decryptions at 1024 bits 1.33
 // -> 0.53 ms, 64 at 4096 bits 8.63 -> 4.01.
-template <int NR, int TW, int W, int M, bool PAIR>
+template <int NR, int TW, int W, bool PAIR>
 struct RnsGroup {
   static constexpr int kHalves = PAIR ? 2 : 1;  // x0 and x1, or one value
   static constexpr int kTiles = rns::tiles(NR);
@@ -502,12 +502,12 @@ struct RnsGroup {
   static constexpr int kRegBlocks = kHeld ? 0 : 3, kLdsBlocks = kHeld ? 0 : 2;
   static_assert(W * TW >= kLimbTiles, "every tile has a wavefront");
   struct Shared {
-    Quad bytes[2][M][kHalves][kBlocks][WAVE];  // [sigma, rho][elements][x0, x1][block][lane]
-    u32 sum[3][M][kHalves][16];                // alpha's sums, of the last, the present and the next rho
+    Quad bytes[2][kHalves][kBlocks][WAVE];  // [sigma, rho][x0, x1][block][lane]
+    u32 sum[3][kHalves][16];                // alpha's sums, of the last, the present and the next rho
     Acc resident[kLdsBlocks][kHeld ? 1 : kTiles][WAVE];
   };
   struct State {
-    u32 a0[TW][M], a1[TW][M], b0[TW][M], b1[TW][M];
+    u32 a0[TW], a1[TW], b0[TW], b1[TW];
   };
   using Frags = QuadSet<TW * kBlocks>;
   Shared& sh;
@@ -545,12 +545,12 @@ struct RnsGroup {
     }
     if (kHeld)
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int mat = 0; mat < 2; ++mat)
 #pragma unroll
         for (int i = 0; i < TW; ++i)
 #pragma unroll
           for (int k = 0; k < kBlocks; ++k)
-            held[m].q[i * kBlocks + k] = fragment(tables + m * rns::lds_matrix_bytes(NR), kTiles, kLast, i, k, (unsigned)lane);
+            held[mat].q[i * kBlocks + k] = fragment(tables + mat * rns::lds_matrix_bytes(NR), kTiles, kLast, i, k, (unsigned)lane);
     for (int i = (int)threadIdx.x; i < (int)(sizeof(Shared) / 4); i += (int)blockDim.x) ((u32*)&sh)[i] = 0;
     __syncthreads();
     set_bias();
@@ -567,36 +567,31 @@ struct RnsGroup {
   __device__ __forceinline__ void set_bias() {
     if (threadIdx.x < 16)
       for (int b = 0; b < 2; ++b)
-        for (int m = 0; m < M; ++m)
-          for (int x = 0; x < kHalves; ++x) word(b, m, x, NR - 1, 48 + (int)threadIdx.x) = 1;
+        for (int x = 0; x < kHalves; ++x) word(b, x, NR - 1, 48 + (int)threadIdx.x) = 1;
   }
-  __device__ __forceinline__ u32& word(int buffer, int m, int x, int i, int l) const {
-    return ((u32*)&sh.bytes[buffer][m][x][i / 4][l])[i % 4];
+  __device__ __forceinline__ u32& word(int buffer, int x, int i, int l) const {
+    return ((u32*)&sh.bytes[buffer][x][i / 4][l])[i % 4];
   }
 
   // r = the tiles' products with the bytes in `buffer`, after all wavefronts have written theirs. MATRIX 0, 1: the two
   // of the modular product; ALPHA: lane group 2 of the last register takes alpha.
   template <int MATRIX, bool ALPHA>
-  __device__ __forceinline__ void products(Acc (&r)[TW][M][kHalves], int buffer, const char* matrix, int tiles, int last) {
+  __device__ __forceinline__ void products(Acc (&r)[TW][kHalves], int buffer, const char* matrix, int tiles, int last) {
     unsigned l = (unsigned)lane;
     asm volatile("" : "+v"(l));  // or the addresses of all fragments are kept in registers from one product to the next
-    u32 alpha[M][kHalves];
+    u32 alpha[kHalves];
     if (ALPHA) {
       const int now = (turn + 2) % 3;  // of the last publish()
 #pragma unroll
-      for (int m = 0; m < M; ++m)
-#pragma unroll
-        for (int x = 0; x < kHalves; ++x) {
-          const u32 a = (sh.sum[now][m][x][lane & 15] + (1u << 13)) >> 14;
-          alpha[m][x] = (a & 127u) | ((a >> 7) << 8);
-        }
+      for (int x = 0; x < kHalves; ++x) {
+        const u32 a = (sh.sum[now][x][lane & 15] + (1u << 13)) >> 14;
+        alpha[x] = (a & 127u) | ((a >> 7) << 8);
+      }
     }
 #pragma unroll
     for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int m = 0; m < M; ++m)
-#pragma unroll
-        for (int x = 0; x < kHalves; ++x) r[i][m][x] = Acc{0, 0, 0, 0};
+      for (int x = 0; x < kHalves; ++x) r[i][x] = Acc{0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < kBlocks; ++k) {
       // what streams in is asked for three blocks ahead at most, as far as the registers go
@@ -608,98 +603,86 @@ struct RnsGroup {
         else if (MATRIX == 0 && k < kRegBlocks) f[i] = part.q[i * kRegBlocks + k];
         else if (MATRIX == 1 && k < kLdsBlocks) f[i] = sh.resident[kLdsBlocks ? k : 0][tile(i)][lane];
         else f[i] = fragment(matrix, tiles, last, i, k, l);
+      Quad d[kHalves];
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        Quad d[kHalves];
-#pragma unroll
-        for (int x = 0; x < kHalves; ++x) {
-          d[x] = sh.bytes[buffer][m][x][k][lane];
-          if (ALPHA && k == (NR - 1) / 4) d[x][(NR - 1) % 4] = g == 2 ? alpha[m][x] : d[x][(NR - 1) % 4];
-        }
-#pragma unroll
-        for (int i = 0; i < TW; ++i)
-#pragma unroll
-          for (int x = 0; x < kHalves; ++x)
-            r[i][m][x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d[x], r[i][m][x], 0, 0, 0);
+      for (int x = 0; x < kHalves; ++x) {
+        d[x] = sh.bytes[buffer][x][k][lane];
+        if (ALPHA && k == (NR - 1) / 4) d[x][(NR - 1) % 4] = g == 2 ? alpha[x] : d[x][(NR - 1) % 4];
       }
+#pragma unroll
+      for (int i = 0; i < TW; ++i)
+#pragma unroll
+        for (int x = 0; x < kHalves; ++x)
+          r[i][x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d[x], r[i][x], 0, 0, 0);
     }
   }
   // base B's bytes and alpha's sums to the other wavefronts
   __device__ __forceinline__ void publish(const State& x) {
-    u32* s = &sh.sum[turn][0][0][0];
+    u32* s = &sh.sum[turn][0][0];
+    u32 s0 = 0, s1 = 0;
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-      u32 s0 = 0, s1 = 0;
-#pragma unroll
-      for (int i = 0; i < TW; ++i)
-        if (owns(i)) {
-          word(1, m, 0, tile(i), lane) = x.b0[i][m] ^ rns::kOmega;
-          if constexpr (PAIR) word(1, m, 1, tile(i), lane) = x.b1[i][m] ^ rns::kOmega;
-          s0 += x.b0[i][m] >> 16;
-          if constexpr (PAIR) s1 += x.b1[i][m] >> 16;
-        }
-      atomicAdd(s + m * kHalves * 16 + (lane & 15), s0);
-      if (PAIR) atomicAdd(s + (m * kHalves + 1) * 16 + (lane & 15), s1);
-    }
+    for (int i = 0; i < TW; ++i)
+      if (owns(i)) {
+        word(1, 0, tile(i), lane) = x.b0[i] ^ rns::kOmega;
+        if constexpr (PAIR) word(1, 1, tile(i), lane) = x.b1[i] ^ rns::kOmega;
+        s0 += x.b0[i] >> 16;
+        if constexpr (PAIR) s1 += x.b1[i] >> 16;
+      }
+    atomicAdd(s + (lane & 15), s0);
+    if (PAIR) atomicAdd(s + 16 + (lane & 15), s1);
     __syncthreads();
     // the sums of the publish() before this one were last read before this barrier and are next added to after the
     // barrier that follows it
     const int clear = (turn + 2) % 3;
     if (threadIdx.x < 32)
-      for (int i = (int)threadIdx.x; i < M * kHalves * 16; i += 32) (&sh.sum[clear][0][0][0])[i] = 0;
+      for (int i = (int)threadIdx.x; i < kHalves * 16; i += 32) (&sh.sum[clear][0][0])[i] = 0;
     turn = (turn + 1) % 3;
   }
   // base A from what publish() left
   __device__ __forceinline__ void extend_to_a(State& x) {
-    Acc r[TW][M][kHalves];
+    Acc r[TW][kHalves];
     products<1, true>(r, 1, tables + rns::lds_matrix_bytes(NR), kTiles, kLast);
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        x.a0[i][m] = reduce((u64)column<true, kWide>(r[i][m][0], kc), ka[i][0], ka[i][1]);
-        if constexpr (PAIR) x.a1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), ka[i][0], ka[i][1]);
-      }
+    for (int i = 0; i < TW; ++i) {
+      x.a0[i] = reduce((u64)column<true, kWide>(r[i][0], kc), ka[i][0], ka[i][1]);
+      if constexpr (PAIR) x.a1[i] = reduce((u64)column<true, kWide>(r[i][1], kc), ka[i][0], ka[i][1]);
+    }
   }
   // x times the table entry y, or (null) squared
   template <bool SQ>
   __device__ __forceinline__ void multiply(State& x, const u32* y) {
-    u32 z[TW][M], w[TW][M];
+    u32 z[TW], w[TW];
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const Quad v = SQ ? own(x, i, m) : *entry_at(y, i, m);
-        const u32 s0 = reduce(mad64(x.a0[i][m], v[0], 0), ka[i][0], ka[i][1]);
-        u32 s1 = 0;
-        if constexpr (PAIR) {
-          const u64 ca = SQ ? mad64(x.a0[i][m] << 1, x.a1[i][m], 0) : mad64(x.a0[i][m], v[1], mad64(x.a1[i][m], v[0], 0));
-          s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
-        }
-        if (owns(i)) {
-          word(0, m, 0, tile(i), lane) = s0 ^ rns::kOmega;
-          if constexpr (PAIR) word(0, m, 1, tile(i), lane) = s1 ^ rns::kOmega;
-        }
-        z[i][m] = reduce(mad64(x.b0[i][m], v[2], 0), kb[i][0], kb[i][1]);
-        if constexpr (PAIR) {
-          const u64 cb = SQ ? mad64(x.b0[i][m] << 1, x.b1[i][m], 0) : mad64(x.b0[i][m], v[3], mad64(x.b1[i][m], v[2], 0));
-          w[i][m] = reduce(mad64(z[i][m], kb[i][3], cb), kb[i][0], kb[i][1]);
-        }
+    for (int i = 0; i < TW; ++i) {
+      const Quad v = SQ ? own(x, i) : *entry_at(y, i);
+      const u32 s0 = reduce(mad64(x.a0[i], v[0], 0), ka[i][0], ka[i][1]);
+      u32 s1 = 0;
+      if constexpr (PAIR) {
+        const u64 ca = SQ ? mad64(x.a0[i] << 1, x.a1[i], 0) : mad64(x.a0[i], v[1], mad64(x.a1[i], v[0], 0));
+        s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
       }
+      if (owns(i)) {
+        word(0, 0, tile(i), lane) = s0 ^ rns::kOmega;
+        if constexpr (PAIR) word(0, 1, tile(i), lane) = s1 ^ rns::kOmega;
+      }
+      z[i] = reduce(mad64(x.b0[i], v[2], 0), kb[i][0], kb[i][1]);
+      if constexpr (PAIR) {
+        const u64 cb = SQ ? mad64(x.b0[i] << 1, x.b1[i], 0) : mad64(x.b0[i], v[3], mad64(x.b1[i], v[2], 0));
+        w[i] = reduce(mad64(z[i], kb[i][3], cb), kb[i][0], kb[i][1]);
+      }
+    }
     __syncthreads();
-    Acc r[TW][M][kHalves];
+    Acc r[TW][kHalves];
     products<0, false>(r, 0, tables, kTiles, kLast);
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const u32 t0 = reduce(mad64(z[i][m], kb[i][2], (u64)column<true, kWide>(r[i][m][0], kc)), kb[i][0], kb[i][1]);
-        x.b0[i][m] = t0;
-        if constexpr (PAIR) {
-          const u64 col = mad64(w[i][m], kb[i][2], (u64)column<true, kWide>(r[i][m][1], kc));
-          x.b1[i][m] = reduce(mad64(t0, kb[i][0] - kb[i][3], col), kb[i][0], kb[i][1]);
-        }
+    for (int i = 0; i < TW; ++i) {
+      const u32 t0 = reduce(mad64(z[i], kb[i][2], (u64)column<true, kWide>(r[i][0], kc)), kb[i][0], kb[i][1]);
+      x.b0[i] = t0;
+      if constexpr (PAIR) {
+        const u64 col = mad64(w[i], kb[i][2], (u64)column<true, kWide>(r[i][1], kc));
+        x.b1[i] = reduce(mad64(t0, kb[i][0] - kb[i][3], col), kb[i][0], kb[i][1]);
       }
+    }
     publish(x);
     extend_to_a(x);
   }
@@ -710,24 +693,19 @@ struct RnsGroup {
     for (int i = wave; i < NR; i += W) {
       const int l = 4 * i + g;
       if (l == rns::bias_slot(NR)) continue;
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const bool ok = (unsigned)(16 * m + e) < left && l < nl;
-        const u32* p = src + (size_t)(16 * m + e) * (2 * nl) + l;
-        word(0, m, 0, i, lane) = (ok ? p[0] : 0u) ^ rns::kOmega;
-        if constexpr (PAIR) word(0, m, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
-      }
+      const bool ok = (unsigned)e < left && l < nl;
+      const u32* p = src + (size_t)e * (2 * nl) + l;
+      word(0, 0, i, lane) = (ok ? p[0] : 0u) ^ rns::kOmega;
+      if constexpr (PAIR) word(0, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
     }
     __syncthreads();
-    Acc r[TW][M][kHalves];
+    Acc r[TW][kHalves];
     products<2, false>(r, 0, tables + rns::lds_bytes(NR), kTiles, 16);
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        x.b0[i][m] = reduce((u64)column<true, kWide>(r[i][m][0], kc), kb[i][0], kb[i][1]);
-        if constexpr (PAIR) x.b1[i][m] = reduce((u64)column<true, kWide>(r[i][m][1], kc), kb[i][0], kb[i][1]);
-      }
+    for (int i = 0; i < TW; ++i) {
+      x.b0[i] = reduce((u64)column<true, kWide>(r[i][0], kc), kb[i][0], kb[i][1]);
+      if constexpr (PAIR) x.b1[i] = reduce((u64)column<true, kWide>(r[i][1], kc), kb[i][0], kb[i][1]);
+    }
     publish(x);
     extend_to_a(x);
   }
@@ -735,54 +713,48 @@ struct RnsGroup {
   __device__ __forceinline__ void store(const State& x, long long* dst, unsigned left) {
     __syncthreads();  // the bytes of the last product have been read
     publish(x);
-    Acc r[TW][M][kHalves];
+    Acc r[TW][kHalves];
     products<2, true>(r, 1, tables + rns::lds_bytes(NR) + rns::in_matrix_bytes(NR), kLimbTiles, 16);
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const unsigned e = (unsigned)(16 * m + (lane & 15));
-        if (e < left && mine(i, kLimbTiles)) {
-          long long* d = dst + (size_t)e * (8 * kLimbTiles) + 4 * tile(i, kLimbTiles) + g;
-          d[0] = column<false, kWide>(r[i][m][0], kc);
-          d[4 * kLimbTiles] = PAIR ? column<false, kWide>(r[i][m][kHalves - 1], kc) : 0;
-        }
+    for (int i = 0; i < TW; ++i) {
+      const unsigned e = (unsigned)(lane & 15);
+      if (e < left && mine(i, kLimbTiles)) {
+        long long* d = dst + (size_t)e * (8 * kLimbTiles) + 4 * tile(i, kLimbTiles) + g;
+        d[0] = column<false, kWide>(r[i][0], kc);
+        d[4 * kLimbTiles] = PAIR ? column<false, kWide>(r[i][kHalves - 1], kc) : 0;
       }
+    }
   }
-  // Window tables: [wavefront][tile][elements][lane] quads {x0, x1 in base A, in base B}
-  static constexpr int kEntry = W * TW * M * WAVE * 4;  // dwords
-  __device__ __forceinline__ Quad* entry_at(const u32* entry, int i, int m) const {
-    return (Quad*)entry + ((wave * TW + i) * M + m) * WAVE + lane;
+  // Window tables: [wavefront][tile][lane] quads {x0, x1 in base A, in base B}
+  static constexpr int kEntry = W * TW * WAVE * 4;  // dwords
+  __device__ __forceinline__ Quad* entry_at(const u32* entry, int i) const {
+    return (Quad*)entry + (wave * TW + i) * WAVE + lane;
   }
-  static __device__ __forceinline__ Quad own(const State& x, int i, int m) {
-    return Quad{x.a0[i][m], PAIR ? x.a1[i][m] : 0u, x.b0[i][m], PAIR ? x.b1[i][m] : 0u};
+  static __device__ __forceinline__ Quad own(const State& x, int i) {
+    return Quad{x.a0[i], PAIR ? x.a1[i] : 0u, x.b0[i], PAIR ? x.b1[i] : 0u};
   }
   __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-      for (int m = 0; m < M; ++m) *entry_at(entry, i, m) = own(x, i, m);
+    for (int i = 0; i < TW; ++i) *entry_at(entry, i) = own(x, i);
   }
   __device__ __forceinline__ void load_state(State& x, const u32* entry) const {
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const Quad v = *entry_at(entry, i, m);
-        x.a0[i][m] = v[0];
-        x.b0[i][m] = v[2];
-        if constexpr (PAIR) {
-          x.a1[i][m] = v[1];
-          x.b1[i][m] = v[3];
-        }
+    for (int i = 0; i < TW; ++i) {
+      const Quad v = *entry_at(entry, i);
+      x.a0[i] = v[0];
+      x.b0[i] = v[2];
+      if constexpr (PAIR) {
+        x.a1[i] = v[1];
+        x.b1[i] = v[3];
       }
+    }
   }
 };
 
-// Every block runs the program on 16 M elements at a time. The first `split` blocks run j0, the others j1.
-template <int NR, int TW, int W, int M, bool PAIR>
+// Every block runs the program on 16 elements at a time. The first `split` blocks run j0, the others j1.
+template <int NR, int TW, int W, bool PAIR>
 __global__ __launch_bounds__(W * 64, (W + 3) / 4) void k_rns_group(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
-  using G = RnsGroup<NR, TW, W, M, PAIR>;
+  using G = RnsGroup<NR, TW, W, PAIR>;
   __shared__ __align__(16) typename G::Shared shared;
   const bool second = blockIdx.x >= split;
   const RnsJob& j = second ? j1 : j0;
@@ -792,8 +764,8 @@ __global__ __launch_bounds__(W * 64, (W + 3) / 4) void k_rns_group(RnsJob j0, Rn
   const u32* prog = j.prog ? j.prog : j.ins;
   const int len = __builtin_amdgcn_readfirstlane(j.len);
   u32* table = j.slots + (size_t)block * (size_t)j.entries * G::kEntry;
-  for (size_t first = (size_t)block * (16 * M); first < count; first += (size_t)nblocks * (16 * M)) {
-    const unsigned left = (unsigned)std::min(count - first, (size_t)(16 * M));
+  for (size_t first = (size_t)block * 16; first < count; first += (size_t)nblocks * 16) {
+    const unsigned left = (unsigned)std::min(count - first, (size_t)16);
     typename G::State x;
     e.load(x, j.in + first * (size_t)(2 * j.nl), left, j.nl);
     for (int pc = 0; pc < len;) {
@@ -905,8 +877,8 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
   } while (0)
 #define GROUP(NR, TW, W)                                              \
   do {                                                                \
-    if (pair) LAUNCH((k_rns_group<NR, TW, W, 1, true>), W * 64);       \
-    else LAUNCH((k_rns_group<NR, TW, W, 1, false>), W * 64);           \
+    if (pair) LAUNCH((k_rns_group<NR, TW, W, true>), W * 64);       \
+    else LAUNCH((k_rns_group<NR, TW, W, false>), W * 64);           \
   } while (0)
   switch (nr) {
     case 6:
@@ -923,7 +895,7 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
       break;
     case 36:
       if (!pair) return HAFLO_EINVAL;
-      LAUNCH((k_rns_group<36, 3, 12, 1, true>), 12 * 64);
+      LAUNCH((k_rns_group<36, 3, 12, true>), 12 * 64);
       break;
     default: return HAFLO_EINVAL;
   }
