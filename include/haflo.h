@@ -148,7 +148,7 @@ int haflo_op_cost(const haflo_ctx* ctx, int op, uint64_t* montmuls, uint32_t* mo
 /* The 32x32+64-bit multiply-adds the vector units really execute for one element
  * of an operator on the path a chip-filling batch takes, all lanes together:
  * the exponentiations run in a residue number system whose reductions are
- * matrix products of bytes on the matrix cores (public keys of 512 to 2048
+ * matrix products of bytes on the matrix cores (public keys of 512 to 4096
  * bits, private keys of 1024 to 4096), else on pairs of half-length residues in
  * 29-bit limbs, so this is far below haflo_op_cost's products times (2 L^2 + L).
  * Defined for HAFLO_OP_ENCRYPT on a public context and HAFLO_OP_DECRYPT. */
@@ -211,8 +211,9 @@ int haflo_decode(const haflo_ctx* ctx, const uint32_t* d_plain, uint32_t scale_b
  * uint32, the caller's random units in [1, n) (the library draws no random
  * numbers). d_cipher: device, count internal elements (may not alias inputs).
  * Workspace: haflo_workspace_bytes(ctx, HAFLO_OP_ENCRYPT, count, 0).
- * A private context computes r^n through p^2 and q^2 (about three times the
- * rate of a public one); the ciphertexts are the same bit for bit.
+ * A private context computes r^n through p^2 and q^2 (1.4, 1.6 and 2.2 times
+ * the rate of a public one on 65536 elements at 1024-, 2048- and 4096-bit
+ * keys); the ciphertexts are the same bit for bit.
  */
 int haflo_encrypt(const haflo_ctx* ctx, const uint32_t* d_plain, const uint32_t* d_r, void* d_cipher, size_t count,
                   void* d_workspace, size_t workspace_bytes, void* stream);
@@ -253,9 +254,9 @@ int haflo_decrypt(const haflo_ctx* ctx, const void* d_cipher, uint32_t* d_plain,
  * in a fixed array of HAFLO_STATIC_SCRATCH_BYTES inside the library's device
  * image (one copy per GPU, held until the process ends; its address is
  * resolved when a context is created). No allocation of any kind happens in
- * the call. Limit: the temporaries of a decryption without the engine of large
- * batches (the least haflo_decrypt accepts) in HAFLO_STATIC_SCRATCH_BYTES (about
- * 5000 / 1400 / 600 elements at 1024 / 2048 / 4096-bit keys), otherwise HAFLO_ETOOBIG and nothing is launched. All calls on
+ * the call. Limit: haflo_workspace_bytes_least(ctx, HAFLO_OP_DECRYPT, count, 0) <=
+ * HAFLO_STATIC_SCRATCH_BYTES (about 3000 / 800 / 200 elements at 1024 / 2048 /
+ * 4096-bit keys), otherwise HAFLO_ETOOBIG and nothing is launched. All calls on
  * one GPU share the array: calls that overlap (different streams, threads or
  * contexts on the same GPU) race; order them on one stream.
  */

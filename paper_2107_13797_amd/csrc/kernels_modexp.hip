@@ -411,7 +411,9 @@ size_t rns_bytes(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs,
 // Powers of stored ciphertexts by one scalar of 17 bits and more (16 squarings), large arrays: a way into the residue
 // form and back costs about four products on limbs. ms on limbs / in residues: 8192 elements at a 2048-bit key 0.234 /
 // 0.146 for 17 bits, 0.76 / 0.30 for 63; 65536 elements 1.11 / 0.72 and 3.42 / 1.59; at 1024 bits 65536 elements 0.305 /
-// 0.245 and 0.88 / 0.58; at 512 bits 0.101 / 0.120 and 0.271 / 0.273, where it stays on limbs.
+// 0.245 and 0.88 / 0.58; at 512 bits 0.101 / 0.120 and 0.271 / 0.273, where it stays on limbs. 4096-bit keys stay on
+// limbs as well, although residues would be faster there: 8192 elements 0.57 / 0.39 and 2.26 / 1.11, 64 elements 0.19 /
+// 0.18 and 0.85 / 0.47.
 constexpr uint64_t kResiduePowerSquarings = 16;
 bool power_in_residues(const haflo_ctx* ctx, size_t count) {
   return ctx->Nh.d_rns && (ctx->Nh.nl == 36 || ctx->Nh.nl == 72) && count >= (size_t)ctx->num_cu * 32;

@@ -8,8 +8,8 @@
 //     t_i = sum_j rho_j M_B / b_j - alpha M_B mod a_i, rho_j = t_j / (M_B / b_j) mod b_j, alpha = round(sum rho_j / 2^30)
 //                                                                             a constant matrix times rho
 // (sum sigma_i M_A / a_i may exceed the quotient by a multiple of M_A: t then exceeds the reduced value by a small
-// multiple of s, which M_A's 22 to 28 spare bits absorb. The second extension is exact: t is far below M_B and the
-// b_j are within 2^-17 of 2^30, so the sum lies within 2^-7 of an integer.)
+// multiple of s, which M_A's 14 to 28 spare bits absorb. The second extension is exact: t is below 600 s, M_B above
+// 2^14 s and the b_j within 2^-17 of 2^30, so the sum lies less than 2^-4.6 above an integer.)
 // The word-serial pair product takes 3.6 (5 for a product of two elements) NL^2 multiply-adds per element; here the
 // NL^2 part are four products with constant matrices over a whole batch, which the matrix cores do on the residues'
 // bytes, and the vector unit is left with about 50 instructions per prime.
@@ -155,9 +155,9 @@ struct Operand {
 };
 
 // One tile (4 destination slots, one per lane) of a matrix times both halves of a pair. Of the half block only 8 bytes
-// of a row are stored: what lies in the other registers meets the operand's zeros. (A product of
-// v_mfma_i32_16x16x32_i8 added to one of v_mfma_i32_16x16x64_i8 right after it comes out wrong on this chip, either
-// way round: one shape only.)
+// of a row are stored: what lies in the other registers meets the operand's zeros. (A version with
+// v_mfma_i32_16x16x32_i8 for the half block, accumulated onto the 16x16x64 products, gave wrong sums. Why is not
+// understood: neither a wrong idea of its operands' layout nor a missing wait was excluded.)
 template <int NR, bool PAIR>
 __device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile, int rows, const FragmentAt& at,
                                               const Operand<NR, PAIR>& d) {
@@ -422,7 +422,10 @@ struct RnsEngine {
 // elements and a 2048-bit modulus: 49 ms per 2363 products where the word-serial pair products took 128 (1024 bits: 10
 // against 25 ms); the matrix cores are busy 61 % of the cycles, the vector units issue in 64 % of them (1119 vector and
 // 360 matrix instructions per squaring and wavefront), LDS reads take 41 %, at 1.9 GHz. 32 elements per wavefront (half
-// the matrix reads) need 256 registers and more, and spilled.
+// the matrix reads) need 256 registers and more, and spilled. What spills at 128, as compiled: the pair form of 2048-bit
+// moduli 54 registers (76 bytes of scratch a lane), the single form 290 there (1148 bytes: 32768 powers in 45.5 ms, a pair
+// takes 48.7) and 26 at 1024 bits (92 bytes), although it holds half the state; the others none. The bound is also
+// that of launches with two or three wavefronts per SIMD, which could have more.
 // Every wavefront runs the program on 16 elements at a time. The first `split` blocks run j0, the others j1.
 template <int NR, bool PAIR>
 __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
@@ -481,11 +484,12 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
 // fit the LDS. A wavefront keeps the residues of its own slots and multiplies and reduces them alone; what every
 // wavefront needs of the others, the bytes of all residues, goes through LDS (16 bytes per lane and block of 64, as the
 // matrix product reads its operand), one barrier before each of the two matrix products of a modular product. The
-// matrices stay in registers where they fit (kHeld: 16 to 80 of them), else they stream from L2. What bounds it is the
-// issue of the few wavefronts of a chain and, at 4096 bits, the 630 KB of both matrices per product (64 bytes per clock
-// and compute unit). Measured against the limb arithmetic on one wavefront per integer: 1024 encryptions at a 1024-bit
-// key 2.67 -> 1.04 ms, 256 at 2048 bits 8.5 -> 3.9, 3001 at 4096 bits 74.9 -> 27.2; 3072 decryptions at 1024 bits 1.33
-// -> 0.53 ms, 64 at 4096 bits 8.63 -> 4.01.
+// matrices stay in registers where they fit (kHeld: 16 to 80 of them), else they stream from L2. What bounds it is
+// waiting: half of a wavefront's cycles (1024 and 2048 bits) go to barriers, LDS and matrix results, with vector issue
+// and LDS each at about 40 %, the matrix cores at 21 and 37 % of the compute unit's cycles; at 4096 bits two thirds, with
+// 455 KB of the 630 KB of both matrices read from L2 per product. Measured against the limb arithmetic on one
+// wavefront per integer: 1024 encryptions at a 1024-bit key 2.67 -> 1.05 ms, 256 at 2048 bits 8.5 -> 3.9, 3001 at 4096
+// bits 74.9 -> 23.4; 3072 decryptions at 1024 bits 1.33 -> 0.55 ms, 64 at 4096 bits 8.63 -> 3.97.
 template <int NR, int TW, int W, bool PAIR>
 struct RnsGroup {
   static constexpr int kHalves = PAIR ? 2 : 1;  // x0 and x1, or one value
@@ -497,8 +501,10 @@ struct RnsGroup {
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
   static constexpr bool kHeld = TW * kBlocks <= 10;
   static constexpr bool kWide = NR > 32;
-  // Of matrices that stream from L2: blocks of the first one kept in registers and of the second one in LDS, as many
-  // as fit (165 of 168 registers, 126 of 160 KB): 3001 encryptions at a 4096-bit key 27.4 -> 23.8 ms.
+  // Of matrices that stream from L2: blocks of the first one kept in registers (167 of 168 are in use) and of the
+  // second one in LDS: 3001 encryptions at a 4096-bit key 27.4 -> 23.8 ms. Shared takes 108,928 bytes; the compiler puts
+  // 24 bytes a lane of the state beside it (an array that the paths of the program loop join on), 127,360 together. A
+  // third block in LDS would just fit (163,200 of 163,840); not measured.
   static constexpr int kRegBlocks = kHeld ? 0 : 3, kLdsBlocks = kHeld ? 0 : 2;
   static_assert(W * TW >= kLimbTiles, "every tile has a wavefront");
   struct Shared {
@@ -804,7 +810,11 @@ int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
 // Where the elements are few, or the matrices too large for the LDS, the slots of 16 elements are spread over a block.
 // Measured on both sides (ms, spread / a wavefront for 16 elements): encryption at a 1024-bit key 1.1 / 3.2 up to 4096
 // elements, 2.1 / 3.4 at 8192, 5.1 / 4.4 at 20000; at 2048 bits 4.1 / 17.1 at 3000, 16.2 / 18.0 at 16384, 32 / 27 at
-// 32768; decryption at a 1024-bit key 0.55 / 0.93 at 4096, 1.02 / 0.93 at 8192.
+// 32768; decryption at a 1024-bit key 0.55 / 0.93 at 4096, 1.02 / 0.93 at 8192. The single form (the key owner's first
+// stage, in its encryption with the second stage on limbs): at a 1024-bit key 1.70 / 2.02 at 4096, 2.04 / 2.05 at 6200, 3.09
+// / 2.86 at 10000; at 2048 bits 5.86 / 7.26 at 4096, 9.70 / 10.5 at 8192, 12.9 / 12.1 at 16384; at 4096 bits spread over a
+// block is faster at every size measured, 64.6 / 71.7 at 12288 and 104 / 113 at 20000 (the other form spills), but
+// follows the pairs' rule.
 bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
   return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 3);
 }
