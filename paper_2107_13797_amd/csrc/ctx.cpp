@@ -753,10 +753,10 @@ uint64_t plain_sqr_mads(uint64_t nl, int lpt) { return nl * (nl / lpt) * (sq_pro
 uint64_t pair_mul_mads(uint64_t nl) { return nl * (nl / 9) * 45 + 2 * nl; }
 uint64_t pair_sqr_mads(uint64_t nl) { return nl * (nl / 9) * (sq_products(9) + 27) + 2 * nl; }
 // the RNS engine's vector multiply-adds per prime of a base: the residue products and their reductions in both bases
-// (5 each, 6 for a product of two elements), the columns and reductions of what the matrix products return (9 + 6)
+// (6 each), the reductions of what the matrix products return (5 + 2)
 uint64_t rns_mads(const haflo::HostSched& s, int nl) {
   const uint64_t lanes = (uint64_t)haflo::rns::slots(haflo::rns::regs_for(nl));
-  return lanes * (s.nsquare * 25 + s.nmul * 27);
+  return lanes * ((s.nsquare + s.nmul) * 19);
 }
 }  // namespace
 

@@ -9,17 +9,17 @@
 //                                                                             a constant matrix times rho
 // (sum sigma_i M_A / a_i may exceed the quotient by a multiple of M_A: t then exceeds the reduced value by a small
 // multiple of s, which M_A's 14 to 28 spare bits absorb. The second extension is exact: t is below 600 s, M_B above
-// 2^14 s and the b_j within 2^-17 of 2^30, so the sum lies less than 2^-4.6 above an integer.)
+// 2^14 s and the b_j within 2^-16 of 2^30, so the sum lies less than 2^-4.6 above an integer.)
 // The word-serial pair product takes 3.6 (5 for a product of two elements) NL^2 multiply-adds per element; here the
 // NL^2 part are four products with constant matrices over a whole batch, which the matrix cores do on the residues'
-// bytes, and the vector unit is left with about 50 instructions per prime.
+// bytes, and the vector unit is left with about 42 instructions per prime and pair squared. It issues one of them per four
+// cycles, whatever it is, and loses two such slots to every matrix instruction: their number is what the kernels are built
+// around. Residues are signed and reduced only as far as one Montgomery reduction goes, and the byte rows of a matrix are
+// weighted so that a product's sums are the two words of what is to be reduced (rns::Matrix).
 //
-// Layout. A wavefront owns 16 elements; lane l holds a quarter (g = l / 16) of the residues of element l % 16: channel
-// slot 4 i + g in register i. With the constant matrix as the first operand of v_mfma_i32_16x16x64_i8 and the residues'
-// bytes as the second, four consecutive rows of a result belong to one lane: the four byte rows of one destination slot.
-// So a lane gets whole residues from the product, works on them alone and feeds them to the next product as they are: no
-// lane exchange, no LDS traffic but the matrices', no barrier. Both reductions of a product share every matrix fragment
-// they read.
+// Layout. Lane l of a wavefront holds a quarter (g = l / 16) of the residues of element l % 16: channel slot 4 i + g in
+// register i. With the constant matrix as the first operand of v_mfma_i32_16x16x64_i8 and the residues' bytes as the
+// second, four consecutive rows of a result belong to one lane: the four byte rows of one destination slot.
 #include "kernels_common.hpp"
 #include "rns.hpp"
 
@@ -49,6 +49,45 @@ struct RnsJob {
   int entries;
   u32 ins[kRnsInline];
 };
+
+__device__ __forceinline__ s64 smad(u32 a, u32 b, s64 c) { return (s64)(s32)a * (s64)(s32)b + c; }
+// 2 a b, which may take 33 bits of a factor: two multiply-adds, hidden from the compiler, which would shift a wider one
+__device__ __forceinline__ s64 twice(u32 a, u32 b) {
+  s64 t = smad(a, b, 0);
+  asm("" : "+v"(t));
+  return smad(a, b, t);
+}
+// T 2^-32 mod p, signed: (T + m p) / 2^32 for an m between -2^31 and 2^31
+__device__ __forceinline__ u32 reduce(s64 t, u32 p, u32 pinv) {
+  const u32 m = (u32)t * pinv;
+  u32 r = (u32)((u64)smad(m, p, t) >> 32);
+  asm("" : "+v"(r));  // a register of its own: the compiler would carry the dead low word along with it
+  return r;
+}
+
+// What the sums of a tile's products start from: 2^31 in every column's lower word, which then is not negative
+__device__ __forceinline__ Acc start_sums(bool kept = true) {
+  Acc a = {0, rns::kStart, 0, 0};
+  if (kept) asm volatile("" : "+v"(a));
+  return a;
+}
+// the four byte rows of a slot as one number, see rns::Matrix
+__device__ __forceinline__ s64 column(const Acc& acc) {
+  const u32 lo = ((u32)acc[1] << 8) + (u32)acc[0];
+  const u32 hi = ((u32)acc[3] << 8) + (u32)acc[2];
+  s64 v = (s64)((u64)hi << 32 | lo);
+  asm("" : "+v"(v));  // a pair of registers as it is: the compiler would add its halves one by one to what it is added to
+  return v;
+}
+// the same for rows of radix 256 and sums from zero
+__device__ __forceinline__ s64 integer(const Acc& acc) {
+  return (((s64)acc[3] * 256 + acc[2]) * 256 + acc[1]) * 256 + acc[0];
+}
+// alpha, the multiple of M_B, from what it is the rounded quotient of (by 2^14), as two bytes: modulo 128 and the rest
+__device__ __forceinline__ u32 alpha_bytes(u32 sum) {
+  const s32 a = (s32)sum >> 14;
+  return ((u32)a & 127u) | ((u32)(a >> 7) & 255u) << 8;
+}
 
 // The residues of x0 and x1 (PAIR; else of one value, x0) of a lane in one base, in the registers that the matrix
 // products take them from: full quads of each, and one quad with the last two of both.
@@ -89,44 +128,12 @@ struct RnsState {
   Residues<NR, PAIR> a, b;
 };
 
-// T 2^-32 mod p, below (T + 2^32 p) / 2^32
-__device__ __forceinline__ u32 reduce(u64 t, u32 p, u32 pinv) {
-  const u32 m = (u32)t * pinv;
-  u32 r = (u32)(mad64(m, p, t) >> 32);
-  asm("" : "+v"(r));  // a register of its own: the compiler would carry the dead low word along with it
-  return r;
-}
-
-struct RnsConsts {
-  s32 k65536, k256, one;  // hidden from the compiler, so that the column sums stay multiply-adds
-  s64 base;
-  __device__ __forceinline__ RnsConsts() : k65536(65536), k256(256), one(1), base((s64)rns::kBase) {
-    asm volatile("" : "+r"(k65536), "+r"(k256), "+r"(one), "+r"(base));
-  }
-};
-
 // A residue as the bytes the matrix products take (each 128 less), and back. Hidden from the compiler, which would
 // otherwise keep the residue beside its bytes instead of taking it back from them.
 __device__ __forceinline__ u32 to_bytes(u32 v) {
   v ^= rns::kOmega;
   asm("" : "+v"(v));
   return v;
-}
-
-// the four byte rows of a slot as one number; BASE: 2^47 added. WIDE: for sums of more than 500 byte products, two of
-// which do not fit 32 bits side by side
-template <bool BASE, bool WIDE = false>
-__device__ __forceinline__ s64 column(const Acc& acc, const RnsConsts& kc) {
-  if constexpr (WIDE) {
-    const s32 top = (s32)((u32)acc[3] << 8) + acc[2];
-    s64 w = (s64)top * (s64)kc.k65536 + (BASE ? kc.base : (s64)0);
-    w = (s64)acc[1] * (s64)kc.k256 + w;
-    return (s64)acc[0] * (s64)kc.one + w;
-  }
-  const s32 lo = (s32)((u32)acc[1] << 8) + acc[0];
-  const s32 hi = (s32)((u32)acc[3] << 8) + acc[2];
-  const s64 t = (s64)hi * (s64)kc.k65536 + (BASE ? kc.base : (s64)0);
-  return (s64)lo * (s64)kc.one + t;
 }
 
 // Where this lane's part of a fragment lies in a tile of 16 (kept) rows: of a full one, and of the half one
@@ -160,7 +167,7 @@ struct Operand {
 // understood: neither a wrong idea of its operands' layout nor a missing wait was excluded.)
 template <int NR, bool PAIR>
 __device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile, int rows, const FragmentAt& at,
-                                              const Operand<NR, PAIR>& d) {
+                                              const Operand<NR, PAIR>& d, const Acc& start, Acc* half = nullptr) {
   constexpr int F = rns::full_blocks(NR);
   const char* p = (const char*)tile;
   Acc m[F + 1];
@@ -172,8 +179,8 @@ __device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile
   asm("" : "=v"(any0), "=v"(any1));
 #endif
   m[F] = Acc{(int)h[0], (int)h[1], any0, any1};
-  r0 = Acc{0, 0, 0, 0};
-  r1 = Acc{0, 0, 0, 0};
+  if (half) *half = m[F];
+  r0 = r1 = start;
 #pragma unroll
   for (int k = 0; k <= F; ++k) {
     r0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], (Acc)(k < F ? d.d.q[0][k < F ? k : 0] : d.h0), r0, 0, 0, 0);
@@ -187,17 +194,18 @@ struct RnsEngine {
   static constexpr int kTiles = rns::tiles(NR);  // also the registers that hold primes
   static constexpr int kGroup = 3;               // tiles the compiler may mix
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
-  static constexpr int kLast = rns::last_rows(NR);
   const char* lds;
   int lane, g;
-  RnsConsts kc;
-  FragmentAt at, at_last;  // of a tile, and of the last one
-  int cst_at;              // of this lane group's constants in a row of four slots
-  u32 keep, mine, one;     // masks of set_extra
+  Acc start;
+  FragmentAt at, at_last0, at_last1;  // of a tile, and of the last one of either matrix
+  int cst_at;                         // of this lane group's constants in a row of four slots
+  u32 keep, mine, one;                // masks of set_extra and set_alpha
 
   __device__ __forceinline__ RnsEngine(const void* lds_)
-      : lds((const char*)lds_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4), at(lane, 16), at_last(lane, kLast),
-        cst_at(16 * g), keep(g < 2 ? ~0u : 0u), mine(g == 2 ? ~0u : 0u), one(g == 3 ? 1u : 0u) {
+      : lds((const char*)lds_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4), start(start_sums()), at(lane, 16),
+        at_last0(lane, rns::last_rows(NR, 0)), at_last1(lane, rns::last_rows(NR, 1)), cst_at(16 * g),
+        keep(g == rns::alpha_group(NR) || g == rns::bias_group(NR) ? 0u : ~0u), mine(g == rns::alpha_group(NR) ? ~0u : 0u),
+        one(g == rns::bias_group(NR) ? 1u : 0u) {
     asm volatile("" : "+v"(keep), "+v"(mine), "+v"(one));  // no branches
   }
   // Everything a wavefront reads from LDS is constant over the launch: without these the compiler would read it once
@@ -205,17 +213,22 @@ struct RnsEngine {
   __device__ __forceinline__ void forget() {
     __builtin_amdgcn_sched_barrier(0);
     at.forget();
-    if (kLast != 16) at_last.forget();
+    if (rns::last_rows(NR, 0) != 16) {
+      at_last0.forget();
+      at_last1.forget();
+    }
     asm volatile("" : "+v"(cst_at));
   }
+  // of base A (0), base B's products (1) and its sums (2)
   __device__ __forceinline__ Quad cst(int base, int i) const {
-    return *(const Quad*)(lds + 2 * rns::lds_matrix_bytes(NR) + (base * rns::slots(NR) + 4 * i) * 16 + cst_at);
+    return *(const Quad*)(lds + rns::lds_matrices_bytes(NR) + (base * rns::slots(NR) + 4 * i) * 16 + cst_at);
   }
   template <int MATRIX>
-  __device__ __forceinline__ void lds_products(Acc& r0, Acc& r1, int t, const Operand<NR, PAIR>& d) const {
-    const char* p = lds + MATRIX * rns::lds_matrix_bytes(NR) + t * kTileBytes;
-    if (t == kTiles - 1) tile_products<NR, PAIR>(r0, r1, p, kLast, kLast != 16 ? at_last : at, d);
-    else tile_products<NR, PAIR>(r0, r1, p, 16, at, d);
+  __device__ __forceinline__ void lds_products(Acc& r0, Acc& r1, int t, const Operand<NR, PAIR>& d, Acc* half = nullptr) const {
+    constexpr int kLast = rns::last_rows(NR, MATRIX);
+    const char* p = lds + MATRIX * rns::lds_matrix_bytes(NR, 0) + t * kTileBytes;
+    if (t == kTiles - 1) tile_products<NR, PAIR>(r0, r1, p, kLast, kLast == 16 ? at : MATRIX ? at_last1 : at_last0, d, start, half);
+    else tile_products<NR, PAIR>(r0, r1, p, 16, at, d, start);
   }
 
   // The residue products of one base of a square (y null) or of a product with the table entry y: bytes of sigma in
@@ -244,12 +257,12 @@ struct RnsEngine {
         if (i >= kTiles || i >= NR) continue;
         const Quad k = cst(BASE, i);
         const u32 u0 = x.template get<0>(i), v0 = SQ ? u0 : y0[c];
-        const u32 s0 = reduce(mad64(u0, v0, 0), k[0], k[1]);
+        const u32 s0 = reduce(smad(u0, v0, 0), k[0], k[1]);
         x.template set<0>(i, BASE ? s0 : to_bytes(s0));
         if constexpr (PAIR) {
           const u32 u1 = x.template get<1>(i), v1 = SQ ? u1 : (q + 1 < kQuads ? y1[c] : y0[(2 + c) % 4]);
-          const u64 cross = SQ ? mad64(u0 << 1, u1, 0) : mad64(u0, v1, mad64(u1, v0, 0));
-          const u32 s1 = reduce(mad64(s0, BASE ? k[3] : k[2], cross), k[0], k[1]);
+          const s64 cross = SQ ? twice(u0, u1) : smad(u0, v1, smad(u1, v0, 0));
+          const u32 s1 = reduce(smad(s0, k[2], cross), k[0], k[1]);
           x.template set<1>(i, BASE ? s1 : to_bytes(s1));
         }
       }
@@ -262,61 +275,59 @@ struct RnsEngine {
     base_products<1, SQ>(x.b, y);
   }
 
-  // the constant 1 of the bias in its slot, and alpha's bytes in theirs (lane groups 3 and 2 of the last register)
-  __device__ __forceinline__ void set_extra(Residues<NR, PAIR>& d, u32 alpha0, u32 alpha1) const {
-    d.h[1] = (d.h[1] & keep) | (alpha0 & mine) | one;
-    if (PAIR) d.h[3] = (d.h[3] & keep) | (alpha1 & mine) | one;
-  }
-  // alpha of a value from the sum of its residues' upper halves over this lane's slots
-  __device__ __forceinline__ u32 alpha_bytes(u32 sum) const {
-    sum += (u32)__builtin_amdgcn_ds_bpermute((lane ^ 16) << 2, (int)sum);
-    sum += (u32)__builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, (int)sum);
-    const u32 a = (sum + (1u << 13)) >> 14;
-    return (a & 127u) | ((a >> 7) << 8);
+  // the constant 1 of the bias in its slot, and nothing in alpha's yet
+  __device__ __forceinline__ void set_extra(Residues<NR, PAIR>& d) const {
+    d.h[1] = (d.h[1] & keep) | one;
+    if (PAIR) d.h[3] = (d.h[3] & keep) | one;
   }
 
-  // Base B of the reduced pair from sigma (bytes, in base A) and the products z, w (in base B); leaves base B as bytes,
-  // alpha among them, for the way back.
+  // Base B of the reduced pair from sigma (bytes, in base A) and the products z, w (in base B); leaves base B as bytes
+  // for the way back.
   __device__ __forceinline__ void extend_to_b(RnsState<NR, PAIR>& x) {
     x.b.forget();
-    set_extra(x.a, 0, 0);
+    set_extra(x.a);
     Operand<NR, PAIR> d(x.a);
-    u32 sum0 = 0, sum1 = 0;
-#pragma unroll
-    for (int t = 0; t < kTiles; ++t) {
-      if (t % kGroup == 0) {
-        // running sums: summed up at the end they would keep every term alive
-        asm volatile("" : "+v"(sum0));
-        if (PAIR) asm volatile("" : "+v"(sum1));
-        forget();
-      }
-      Acc r0, r1;
-      lds_products<0>(r0, r1, t, d);
-      const Quad k = cst(1, t);
-      const u32 t0 = reduce(mad64(x.b.template get<0>(t), k[2], (u64)column<true>(r0, kc)), k[0], k[1]);
-      sum0 += t0 >> 16;
-      if constexpr (PAIR) {
-        const u64 col = mad64(x.b.template get<1>(t), k[2], (u64)column<true>(r1, kc));
-        const u32 t1 = reduce(mad64(t0, k[0] - k[3], col), k[0], k[1]);
-        sum1 += t1 >> 16;
-        x.b.template set<1>(t, to_bytes(t1));
-      }
-      x.b.template set<0>(t, to_bytes(t0));
-      if (t % 4 == 3) x.b.gather(t / 4);
-    }
-    set_extra(x.b, alpha_bytes(sum0), PAIR ? alpha_bytes(sum1) : 0u);
-  }
-  // base A from base B's bytes; turns base B back to residues
-  __device__ __forceinline__ void extend_to_a(RnsState<NR, PAIR>& x) {
-    Operand<NR, PAIR> d(x.b);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       if (t % kGroup == 0) forget();
       Acc r0, r1;
-      lds_products<1>(r0, r1, t, d);
+      lds_products<0>(r0, r1, t, d);
+      const Quad k = cst(2, t);
+      const u32 t0 = reduce(smad(x.b.template get<0>(t), k[2], column(r0)), k[0], k[1]);
+      if constexpr (PAIR) {
+        const s64 col = smad(x.b.template get<1>(t), k[2], column(r1));
+        x.b.template set<1>(t, to_bytes(reduce(smad(t0, k[3], col), k[0], k[1])));
+      }
+      x.b.template set<0>(t, to_bytes(t0));
+      if (t % 4 == 3) x.b.gather(t / 4);
+    }
+    set_extra(x.b);
+  }
+  // base A from base B's bytes; turns base B back to residues, with alpha in its slot
+  __device__ __forceinline__ void extend_to_a(RnsState<NR, PAIR>& x) {
+    Operand<NR, PAIR> d(x.b);
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) {
+      const int t = i == 0 ? kTiles - 1 : i - 1;
+      if (i % kGroup == 0) forget();
+      Acc r0, r1;
+      if (i == 0) {  // the tile that has alpha's row: its own primes take alpha afterwards
+        Acc half;
+        lds_products<1>(r0, r1, t, d, &half);
+        const Quad a0 = {0, alpha_bytes((u32)column(r0) + rns::alpha_round(NR)) & mine, 0, 0};
+        r0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(half, (Acc)a0, r0, 0, 0, 0);
+        d.h0[1] |= a0[1];
+        if constexpr (PAIR) {
+          const Quad a1 = {0, alpha_bytes((u32)column(r1) + rns::alpha_round(NR)) & mine, 0, 0};
+          r1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(half, (Acc)a1, r1, 0, 0, 0);
+          d.h1[1] |= a1[1];
+        }
+      } else {
+        lds_products<1>(r0, r1, t, d);
+      }
       const Quad k = cst(0, t);
-      x.a.template set<0>(t, reduce((u64)column<true>(r0, kc), k[0], k[1]));
-      if constexpr (PAIR) x.a.template set<1>(t, reduce((u64)column<true>(r1, kc), k[0], k[1]));
+      x.a.template set<0>(t, reduce(column(r0), k[0], k[1]));
+      if constexpr (PAIR) x.a.template set<1>(t, reduce(column(r1), k[0], k[1]));
       if (t % 4 == 3) x.a.gather(t / 4);
     }
     d.release();
@@ -344,29 +355,21 @@ struct RnsEngine {
       x.a.template set<0>(i, (ok ? src[l] : 0u) ^ rns::kOmega);
       if constexpr (PAIR) x.a.template set<1>(i, (ok ? src[nl + l] : 0u) ^ rns::kOmega);
     }
-    if (g == 3) {  // in place of a limb that is zero
+    if (one) {  // in place of a limb that is zero
       x.a.template set<0>(NR - 1, 1);
       if constexpr (PAIR) x.a.template set<1>(NR - 1, 1);
     }
     Operand<NR, PAIR> d(x.a);
-    u32 sum0 = 0, sum1 = 0;
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       forget();
       Acc r0, r1;
-      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d);
+      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d, start);
       const Quad k = cst(1, t);
-      const u32 t0 = reduce((u64)column<true>(r0, kc), k[0], k[1]);
-      sum0 += t0 >> 16;
-      x.b.template set<0>(t, to_bytes(t0));
-      if constexpr (PAIR) {
-        const u32 t1 = reduce((u64)column<true>(r1, kc), k[0], k[1]);
-        sum1 += t1 >> 16;
-        x.b.template set<1>(t, to_bytes(t1));
-      }
-      asm volatile("" : "+v"(sum0), "+v"(sum1));
+      x.b.template set<0>(t, to_bytes(reduce(column(r0), k[0], k[1])));
+      if constexpr (PAIR) x.b.template set<1>(t, to_bytes(reduce(column(r1), k[0], k[1])));
     }
-    set_extra(x.b, alpha_bytes(sum0), PAIR ? alpha_bytes(sum1) : 0u);
+    set_extra(x.b);
     extend_to_a(x);
   }
   // The pair as two integers in columns of weight 2^(29 l). Base B still holds what the way back left there, alpha and
@@ -380,10 +383,10 @@ struct RnsEngine {
     for (int t = 0; t < kTiles; ++t) {
       forget();
       Acc r0, r1;
-      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d);
+      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d, Acc{0, 0, 0, 0});
       if (active) {
-        dst[4 * t + g] = column<false>(r0, kc);
-        dst[4 * kTiles + 4 * t + g] = PAIR ? column<false>(r1, kc) : 0;
+        dst[4 * t + g] = integer(r0);
+        dst[4 * kTiles + 4 * t + g] = PAIR ? integer(r1) : 0;
       }
     }
   }
@@ -490,27 +493,33 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
 // 455 KB of the 630 KB of both matrices read from L2 per product. Measured against the limb arithmetic on one
 // wavefront per integer: 1024 encryptions at a 1024-bit key 2.67 -> 1.05 ms, 256 at 2048 bits 8.5 -> 3.9, 3001 at 4096
 // bits 74.9 -> 23.4; 3072 decryptions at 1024 bits 1.33 -> 0.55 ms, 64 at 4096 bits 8.63 -> 3.97.
-template <int NR, int TW, int W, bool PAIR>
+//
+// FOLD: 8 elements to a block, x0 in columns 0 to 7 of the matrix products and x1 in columns 8 to 15, for batches that do
+// not fill the chip with blocks of 16: half the matrix instructions and operand reads per product. A lane then has one half
+// of a pair; x1's lanes take the first half's values by DPP, x0's run through the same instructions with zeros in place.
+// W wavefronts, TILES tiles in all.
+template <int NR, int TW, int W, int TILES, bool PAIR, bool FOLD>
 struct RnsGroup {
-  static constexpr int kHalves = PAIR ? 2 : 1;  // x0 and x1, or one value
+  static constexpr bool kBoth = PAIR && !FOLD;  // x0 and x1 in one lane
+  static constexpr int kHalves = kBoth ? 2 : 1;
+  static constexpr int kElements = FOLD ? 8 : 16;
   static constexpr int kTiles = rns::tiles(NR);
   static constexpr int kLimbTiles = rns::limb_tiles(NR);
   static constexpr int kBlocks = (NR + 3) / 4;  // of 64 bytes, the last one partly empty
   static constexpr int kFull = rns::full_blocks(NR);
-  static constexpr int kLast = rns::last_rows(NR);
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
-  static constexpr bool kHeld = TW * kBlocks <= 10;
-  static constexpr bool kWide = NR > 32;
-  // Of matrices that stream from L2: blocks of the first one kept in registers (167 of 168 are in use) and of the
-  // second one in LDS: 3001 encryptions at a 4096-bit key 27.4 -> 23.8 ms. Shared takes 108,928 bytes; the compiler puts
-  // 24 bytes a lane of the state beside it (an array that the paths of the program loop join on), 127,360 together. A
-  // third block in LDS would just fit (163,200 of 163,840); not measured.
-  static constexpr int kRegBlocks = kHeld ? 0 : 3, kLdsBlocks = kHeld ? 0 : 2;
-  static_assert(W * TW >= kLimbTiles, "every tile has a wavefront");
+  // Matrices stay in registers; those of 4096-bit moduli stream from L2, but for three of nine blocks: of the first one in
+  // registers, of the second one in LDS, where the constants are as well. kAhead of the others are on their way at any
+  // time, also across the barriers that the operands wait for; the resident ones are multiplied in between.
+  static constexpr bool kHeld = NR != 36;
+  static constexpr int kStay = kHeld ? 0 : 3, kAhead = 2, kStream = kBlocks - kStay;
+  static_assert(kHeld || kStream % kAhead == 0, "a matrix begins where the other one ends");
+  static_assert(TILES >= kLimbTiles, "every tile has a wavefront");
   struct Shared {
     Quad bytes[2][kHalves][kBlocks][WAVE];  // [sigma, rho][x0, x1][block][lane]
-    u32 sum[3][kHalves][16];                // alpha's sums, of the last, the present and the next rho
-    Acc resident[kLdsBlocks][kHeld ? 1 : kTiles][WAVE];
+    Quad sum[3][kHalves][16];               // alpha's sums over lane group 0 .. 3's slots, of the last, the present and the next rho
+    Acc resident[kStay][kHeld ? 1 : kTiles][WAVE];
+    Quad cst[kHeld ? 0 : 2][rns::slots(NR)];
   };
   struct State {
     u32 a0[TW], a1[TW], b0[TW], b1[TW];
@@ -518,17 +527,29 @@ struct RnsGroup {
   using Frags = QuadSet<TW * kBlocks>;
   Shared& sh;
   const char* tables;
-  int lane, g, wave, turn;
-  RnsConsts kc;
-  Quad ka[TW], kb[TW];  // the constants of this lane's slots
+  int lane, g, wave, own_tile, turn;  // own_tile: the first of TW
+  Acc start;
+  Quad held_cst[2][kHeld ? TW : 1];  // the constants of this lane's slots in base A and base B
+  u32 second;           // FOLD: all ones in x1's lanes
   Frags held[kHeld ? 2 : 1];
-  QuadSet<(kRegBlocks ? kRegBlocks : 1) * TW> part;
+  QuadSet<kHeld ? 1 : kStay * TW> part;
+  QuadSet<kHeld ? 1 : kAhead * TW> coming;
 
-  __device__ __forceinline__ bool mine(int i, int tiles = kTiles) const { return wave * TW + i < tiles; }
+  __device__ __forceinline__ bool mine(int i, int tiles = kTiles) const { return own_tile + i < tiles; }
   // a wavefront without a tile of its own repeats the last one and keeps the result to itself
-  __device__ __forceinline__ int tile(int i, int tiles = kTiles) const { return mine(i, tiles) ? wave * TW + i : tiles - 1; }
+  __device__ __forceinline__ int tile(int i, int tiles = kTiles) const { return mine(i, tiles) ? own_tile + i : tiles - 1; }
   // this lane holds a prime's residue (not one of the extra values) in tile i
-  __device__ __forceinline__ bool owns(int i) const { return mine(i) && (tile(i) < NR - 1 || g < 2); }
+  __device__ __forceinline__ bool owns(int i) const { return mine(i) && 4 * tile(i) + g < rns::primes_for(NR); }
+
+  __device__ __forceinline__ Quad cst(int base, int i) const { return kHeld ? held_cst[base][kHeld ? i : 0] : sh.cst[kHeld ? 0 : base][4 * tile(i) + g]; }
+
+  // FOLD: x0's value for both halves; and for x1's lanes only, zero in x0's
+  static __device__ __forceinline__ u32 of_first(u32 v) {
+    return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118 /* row_shr:8 */, 0xf, 0xc, false);
+  }
+  static __device__ __forceinline__ u32 from_first(u32 v) {
+    return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x118 /* row_shr:8 */, 0xf, 0xf, true);
+  }
 
   // `l`: the lane
   __device__ __forceinline__ Acc fragment(const char* matrix, int tiles, int last, int i, int k, unsigned l) const {
@@ -540,15 +561,16 @@ struct RnsGroup {
     return Acc{(int)h[0], (int)h[1], 0, 0};
   }
 
-  __device__ __forceinline__ RnsGroup(Shared& shared, const u32* tables_)
+  __device__ __forceinline__ RnsGroup(Shared& shared, const u32* tables_, int own_tile_)
       : sh(shared), tables((const char*)tables_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4),
-        wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))), turn(0) {
-    const char* cst = tables + 2 * rns::lds_matrix_bytes(NR);
+        wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))), own_tile(own_tile_), turn(0), start(start_sums(kHeld)),
+        second(FOLD && (threadIdx.x & 8) ? ~0u : 0u) {
+    const char* from = tables + rns::lds_matrices_bytes(NR);
+    if (kHeld)
 #pragma unroll
-    for (int i = 0; i < TW; ++i) {
-      ka[i] = *(const Quad*)(cst + (4 * tile(i) + g) * 16);
-      kb[i] = *(const Quad*)(cst + (rns::slots(NR) + 4 * tile(i) + g) * 16);
-    }
+      for (int i = 0; i < TW; ++i)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) held_cst[b][kHeld ? i : 0] = *(const Quad*)(from + (2 * b * rns::slots(NR) + 4 * tile(i) + g) * 16);
     if (kHeld)
 #pragma unroll
       for (int mat = 0; mat < 2; ++mat)
@@ -556,33 +578,53 @@ struct RnsGroup {
         for (int i = 0; i < TW; ++i)
 #pragma unroll
           for (int k = 0; k < kBlocks; ++k)
-            held[mat].q[i * kBlocks + k] = fragment(tables + mat * rns::lds_matrix_bytes(NR), kTiles, kLast, i, k, (unsigned)lane);
+            held[mat].q[i * kBlocks + k] = fragment(tables + mat * rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, mat), i, k, (unsigned)lane);
     for (int i = (int)threadIdx.x; i < (int)(sizeof(Shared) / 4); i += (int)blockDim.x) ((u32*)&sh)[i] = 0;
     __syncthreads();
+    if (!kHeld)
+      for (int i = (int)threadIdx.x; i < 2 * rns::slots(NR); i += (int)blockDim.x)
+        sh.cst[kHeld ? 0 : i / rns::slots(NR)][i % rns::slots(NR)] = *(const Quad*)(from + (i + i / rns::slots(NR) * rns::slots(NR)) * 16);
     set_bias();
     if (!kHeld)
 #pragma unroll
-      for (int i = 0; i < TW; ++i) {
+      for (int i = 0; i < TW; ++i)
 #pragma unroll
-        for (int k = 0; k < kRegBlocks; ++k) part.q[i * kRegBlocks + k] = fragment(tables, kTiles, kLast, i, k, (unsigned)lane);
-        for (int k = 0; k < kLdsBlocks; ++k)  // this wavefront's own tiles (the last ones may write the same tile twice)
-          sh.resident[k][tile(i)][lane] = fragment(tables + rns::lds_matrix_bytes(NR), kTiles, kLast, i, k, (unsigned)lane);
-      }
+        for (int k = 0; k < kStay; ++k) {
+          part.q[i * kStay + k] = fragment(tables, kTiles, rns::last_rows(NR, 0), i, k, (unsigned)lane);
+          // this wavefront's own tiles (the last ones may write the same tile twice)
+          sh.resident[k][tile(i)][lane] = fragment(tables + rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, 1), i, k, (unsigned)lane);
+        }
   }
-  // the constant 1 of the bias: lane group 3 of the last register, which no wavefront writes
+  // A residue's bytes to where the other wavefronts read them. All lanes write: what has no prime meets zeros in the matrix,
+  // a wavefront that repeats a tile writes what its owner does, and the bias stays 1 where it shares a register with primes.
+  __device__ __forceinline__ void put(int buffer, int x, int i, u32 v) const {
+    v ^= rns::kOmega;
+    if (rns::tiles(NR) == NR && tile(i) == NR - 1) v = g == rns::bias_group(NR) ? 1u : v;
+    word(buffer, x, tile(i), lane) = v;
+  }
+  // asks for a block of one of the two matrices
+  template <int MATRIX>
+  __device__ __forceinline__ void ask(int stream) {
+    unsigned l = (unsigned)lane;
+    asm volatile("" : "+v"(l));  // or the addresses of all fragments are kept in registers from one product to the next
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+      coming.q[stream % kAhead * TW + i] = fragment(tables + MATRIX * rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, MATRIX), i, kStay + stream, l);
+  }
+  // the constant 1 of the bias: a lane group of the last register, which no wavefront writes
   __device__ __forceinline__ void set_bias() {
     if (threadIdx.x < 16)
       for (int b = 0; b < 2; ++b)
-        for (int x = 0; x < kHalves; ++x) word(b, x, NR - 1, 48 + (int)threadIdx.x) = 1;
+        for (int x = 0; x < kHalves; ++x) word(b, x, NR - 1, 16 * rns::bias_group(NR) + (int)threadIdx.x) = 1;
   }
   __device__ __forceinline__ u32& word(int buffer, int x, int i, int l) const {
     return ((u32*)&sh.bytes[buffer][x][i / 4][l])[i % 4];
   }
 
   // r = the tiles' products with the bytes in `buffer`, after all wavefronts have written theirs. MATRIX 0, 1: the two
-  // of the modular product; ALPHA: lane group 2 of the last register takes alpha.
+  // of the modular product; ALPHA: its lane group of the last register takes alpha.
   template <int MATRIX, bool ALPHA>
-  __device__ __forceinline__ void products(Acc (&r)[TW][kHalves], int buffer, const char* matrix, int tiles, int last) {
+  __device__ __forceinline__ void products(Acc (&r)[TW][kHalves], int buffer, const char* matrix, int tiles, int last, const Acc& from) {
     unsigned l = (unsigned)lane;
     asm volatile("" : "+v"(l));  // or the addresses of all fragments are kept in registers from one product to the next
     u32 alpha[kHalves];
@@ -590,103 +632,132 @@ struct RnsGroup {
       const int now = (turn + 2) % 3;  // of the last publish()
 #pragma unroll
       for (int x = 0; x < kHalves; ++x) {
-        const u32 a = (sh.sum[now][x][lane & 15] + (1u << 13)) >> 14;
-        alpha[x] = (a & 127u) | ((a >> 7) << 8);
+        const Quad q = sh.sum[now][x][lane & 15];
+        alpha[x] = alpha_bytes(q[0] + q[1] + q[2] + q[3] + (1u << 13) + (u32)rns::primes_for(NR) / 2);
       }
     }
 #pragma unroll
     for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int x = 0; x < kHalves; ++x) r[i][x] = Acc{0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < kBlocks; ++k) {
-      // what streams in is asked for three blocks ahead at most, as far as the registers go
-      if (!(kHeld && MATRIX < 2) && k % 3 == 0) __builtin_amdgcn_sched_barrier(0);
-      Acc f[TW];
-#pragma unroll
-      for (int i = 0; i < TW; ++i)
-        if (kHeld && MATRIX < 2) f[i] = held[MATRIX < 2 ? MATRIX : 0].q[i * kBlocks + k];
-        else if (MATRIX == 0 && k < kRegBlocks) f[i] = part.q[i * kRegBlocks + k];
-        else if (MATRIX == 1 && k < kLdsBlocks) f[i] = sh.resident[kLdsBlocks ? k : 0][tile(i)][lane];
-        else f[i] = fragment(matrix, tiles, last, i, k, l);
+      for (int x = 0; x < kHalves; ++x) r[i][x] = from;
+    const auto block = [&](int k, const Acc* f) {
       Quad d[kHalves];
 #pragma unroll
       for (int x = 0; x < kHalves; ++x) {
         d[x] = sh.bytes[buffer][x][k][lane];
-        if (ALPHA && k == (NR - 1) / 4) d[x][(NR - 1) % 4] = g == 2 ? alpha[x] : d[x][(NR - 1) % 4];
+        if (ALPHA && k == (NR - 1) / 4) d[x][(NR - 1) % 4] = g == rns::alpha_group(NR) ? alpha[x] : d[x][(NR - 1) % 4];
       }
 #pragma unroll
       for (int i = 0; i < TW; ++i)
 #pragma unroll
         for (int x = 0; x < kHalves; ++x)
           r[i][x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d[x], r[i][x], 0, 0, 0);
+    };
+    if constexpr (kHeld || MATRIX == 2) {
+#pragma unroll
+      for (int k = 0; k < kBlocks; ++k) {
+        if (MATRIX == 2 && k % 3 == 0) __builtin_amdgcn_sched_barrier(0);
+        Acc f[TW];
+#pragma unroll
+        for (int i = 0; i < TW; ++i)
+          f[i] = MATRIX < 2 ? held[MATRIX < 2 ? MATRIX : 0].q[i * kBlocks + k] : fragment(matrix, tiles, last, i, k, l);
+        block(k, f);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kStream; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
+        block(kStay + k, &coming.q[k % kAhead * TW]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k + kAhead < kStream) ask<MATRIX>(k + kAhead);
+        else ask<1 - MATRIX>(k + kAhead - kStream);
+        if (k < kStay) {
+          Acc f[TW];
+#pragma unroll
+          for (int i = 0; i < TW; ++i) f[i] = MATRIX == 0 ? part.q[i * kStay + k] : sh.resident[k][tile(i)][lane];
+          block(k, f);
+        }
+      }
     }
   }
   // base B's bytes and alpha's sums to the other wavefronts
   __device__ __forceinline__ void publish(const State& x) {
-    u32* s = &sh.sum[turn][0][0];
     u32 s0 = 0, s1 = 0;
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-      if (owns(i)) {
-        word(1, 0, tile(i), lane) = x.b0[i] ^ rns::kOmega;
-        if constexpr (PAIR) word(1, 1, tile(i), lane) = x.b1[i] ^ rns::kOmega;
-        s0 += x.b0[i] >> 16;
-        if constexpr (PAIR) s1 += x.b1[i] >> 16;
-      }
-    atomicAdd(s + (lane & 15), s0);
-    if (PAIR) atomicAdd(s + 16 + (lane & 15), s1);
+    for (int i = 0; i < TW; ++i) {
+      put(1, 0, i, x.b0[i]);
+      if constexpr (kBoth) put(1, 1, i, x.b1[i]);
+      s0 += owns(i) ? (u32)((s32)x.b0[i] >> 16) : 0u;
+      if constexpr (kBoth) s1 += owns(i) ? (u32)((s32)x.b1[i] >> 16) : 0u;
+    }
+    u32* s = (u32*)&sh.sum[turn][0][lane & 15] + g;
+    atomicAdd(s, s0);
+    if (kBoth) atomicAdd(s + 64, s1);
     __syncthreads();
     // the sums of the publish() before this one were last read before this barrier and are next added to after the
     // barrier that follows it
     const int clear = (turn + 2) % 3;
-    if (threadIdx.x < 32)
-      for (int i = (int)threadIdx.x; i < kHalves * 16; i += 32) (&sh.sum[clear][0][0])[i] = 0;
+    if (threadIdx.x < 64)
+      for (int i = (int)threadIdx.x; i < kHalves * 64; i += 64) ((u32*)&sh.sum[clear][0][0])[i] = 0;
     turn = (turn + 1) % 3;
   }
   // base A from what publish() left
   __device__ __forceinline__ void extend_to_a(State& x) {
     Acc r[TW][kHalves];
-    products<1, true>(r, 1, tables + rns::lds_matrix_bytes(NR), kTiles, kLast);
+    products<1, true>(r, 1, tables + rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, 1), start);
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
-      x.a0[i] = reduce((u64)column<true, kWide>(r[i][0], kc), ka[i][0], ka[i][1]);
-      if constexpr (PAIR) x.a1[i] = reduce((u64)column<true, kWide>(r[i][1], kc), ka[i][0], ka[i][1]);
+      const Quad k = cst(0, i);
+      x.a0[i] = reduce(column(r[i][0]), k[0], k[1]);
+      if constexpr (kBoth) x.a1[i] = reduce(column(r[i][kHalves - 1]), k[0], k[1]);
+    }
+  }
+  // the residue products of one base of slot i: x0 y0 and x0 y1 + x1 y0 + e x0 y0 (e: of the reduced first one)
+  template <bool SQ>
+  __device__ __forceinline__ void residues(u32& r0, u32& r1, u32 u0, u32 u1, u32 v0, u32 v1, u32 p, u32 pinv, u32 e) const {
+    if constexpr (FOLD) {
+      const s64 t = smad(of_first(u0), v0, smad(u0 & second, of_first(v0), 0));
+      r0 = reduce(smad(from_first(reduce(t, p, pinv)), e, t), p, pinv);
+      r1 = 0;
+    } else {
+      r0 = reduce(smad(u0, v0, 0), p, pinv);
+      r1 = 0;
+      if constexpr (kBoth) r1 = reduce(smad(r0, e, SQ ? twice(u0, u1) : smad(u0, v1, smad(u1, v0, 0))), p, pinv);
     }
   }
   // x times the table entry y, or (null) squared
   template <bool SQ>
   __device__ __forceinline__ void multiply(State& x, const u32* y) {
     u32 z[TW], w[TW];
+    Quad v[TW];
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
-      const Quad v = SQ ? own(x, i) : *entry_at(y, i);
-      const u32 s0 = reduce(mad64(x.a0[i], v[0], 0), ka[i][0], ka[i][1]);
-      u32 s1 = 0;
-      if constexpr (PAIR) {
-        const u64 ca = SQ ? mad64(x.a0[i] << 1, x.a1[i], 0) : mad64(x.a0[i], v[1], mad64(x.a1[i], v[0], 0));
-        s1 = reduce(mad64(s0, ka[i][2], ca), ka[i][0], ka[i][1]);
-      }
-      if (owns(i)) {
-        word(0, 0, tile(i), lane) = s0 ^ rns::kOmega;
-        if constexpr (PAIR) word(0, 1, tile(i), lane) = s1 ^ rns::kOmega;
-      }
-      z[i] = reduce(mad64(x.b0[i], v[2], 0), kb[i][0], kb[i][1]);
-      if constexpr (PAIR) {
-        const u64 cb = SQ ? mad64(x.b0[i] << 1, x.b1[i], 0) : mad64(x.b0[i], v[3], mad64(x.b1[i], v[2], 0));
-        w[i] = reduce(mad64(z[i], kb[i][3], cb), kb[i][0], kb[i][1]);
-      }
+      v[i] = SQ ? own(x, i) : entry(y, i);
+      const Quad k = cst(0, i);
+      u32 s0, s1;
+      residues<SQ>(s0, s1, x.a0[i], kBoth ? x.a1[i] : 0u, v[i][0], v[i][1], k[0], k[1], k[2]);
+      put(0, 0, i, s0);
+      if constexpr (kBoth) put(0, 1, i, s1);
     }
     __syncthreads();
-    Acc r[TW][kHalves];
-    products<0, false>(r, 0, tables, kTiles, kLast);
+    // base B's share is not needed before the matrix product's result
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
-      const u32 t0 = reduce(mad64(z[i], kb[i][2], (u64)column<true, kWide>(r[i][0], kc)), kb[i][0], kb[i][1]);
+      const Quad k = cst(1, i);
+      residues<SQ>(z[i], w[i], x.b0[i], kBoth ? x.b1[i] : 0u, v[i][2], v[i][3], k[0], k[1], 0u - k[3]);
+    }
+    Acc r[TW][kHalves];
+    products<0, false>(r, 0, tables, kTiles, rns::last_rows(NR, 0), start);
+#pragma unroll
+    for (int i = 0; i < TW; ++i) {
+      const Quad k = cst(1, i);
+      s64 col = smad(z[i], k[2], column(r[i][0]));
+      u32 t0 = reduce(col, k[0], k[1]);
+      if constexpr (FOLD) t0 = reduce(smad(from_first(t0), k[3], col), k[0], k[1]);
       x.b0[i] = t0;
-      if constexpr (PAIR) {
-        const u64 col = mad64(w[i], kb[i][2], (u64)column<true, kWide>(r[i][1], kc));
-        x.b1[i] = reduce(mad64(t0, kb[i][0] - kb[i][3], col), kb[i][0], kb[i][1]);
+      if constexpr (kBoth) {
+        col = smad(w[i], k[2], column(r[i][kHalves - 1]));
+        x.b1[i] = reduce(smad(t0, k[3], col), k[0], k[1]);
       }
     }
     publish(x);
@@ -694,24 +765,28 @@ struct RnsGroup {
   }
   // the pairs whose limbs are at `src` (`left` of them, then zeros) into both bases
   __device__ __forceinline__ void load(State& x, const u32* src, unsigned left, int nl) {
-    const int e = lane & 15;
+    const int e = lane & (kElements - 1), half = FOLD ? lane >> 3 & 1 : 0;
     __syncthreads();  // the bytes of the elements before have been read
     for (int i = wave; i < NR; i += W) {
       const int l = 4 * i + g;
       if (l == rns::bias_slot(NR)) continue;
       const bool ok = (unsigned)e < left && l < nl;
-      const u32* p = src + (size_t)e * (2 * nl) + l;
+      const u32* p = src + (size_t)e * (2 * nl) + half * nl + l;
       word(0, 0, i, lane) = (ok ? p[0] : 0u) ^ rns::kOmega;
-      if constexpr (PAIR) word(0, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
+      if constexpr (kBoth) word(0, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
     }
     __syncthreads();
     Acc r[TW][kHalves];
-    products<2, false>(r, 0, tables + rns::lds_bytes(NR), kTiles, 16);
+    products<2, false>(r, 0, tables + rns::lds_bytes(NR), kTiles, 16, start);
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
-      x.b0[i] = reduce((u64)column<true, kWide>(r[i][0], kc), kb[i][0], kb[i][1]);
-      if constexpr (PAIR) x.b1[i] = reduce((u64)column<true, kWide>(r[i][1], kc), kb[i][0], kb[i][1]);
+      const Quad k = cst(1, i);
+      x.b0[i] = reduce(column(r[i][0]), k[0], k[1]);
+      if constexpr (kBoth) x.b1[i] = reduce(column(r[i][kHalves - 1]), k[0], k[1]);
     }
+    if constexpr (!kHeld)
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) ask<1>(k);
     publish(x);
     extend_to_a(x);
   }
@@ -720,36 +795,44 @@ struct RnsGroup {
     __syncthreads();  // the bytes of the last product have been read
     publish(x);
     Acc r[TW][kHalves];
-    products<2, true>(r, 1, tables + rns::lds_bytes(NR) + rns::in_matrix_bytes(NR), kLimbTiles, 16);
+    products<2, true>(r, 1, tables + rns::lds_bytes(NR) + rns::in_matrix_bytes(NR), kLimbTiles, 16, Acc{0, 0, 0, 0});
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
-      const unsigned e = (unsigned)(lane & 15);
+      const unsigned e = (unsigned)(lane & (kElements - 1)), half = FOLD ? (unsigned)lane >> 3 & 1 : 0;
       if (e < left && mine(i, kLimbTiles)) {
-        long long* d = dst + (size_t)e * (8 * kLimbTiles) + 4 * tile(i, kLimbTiles) + g;
-        d[0] = column<false, kWide>(r[i][0], kc);
-        d[4 * kLimbTiles] = PAIR ? column<false, kWide>(r[i][kHalves - 1], kc) : 0;
+        long long* d = dst + (size_t)e * (8 * kLimbTiles) + half * (4 * kLimbTiles) + 4 * tile(i, kLimbTiles) + g;
+        d[0] = integer(r[i][0]);
+        if (!FOLD) d[4 * kLimbTiles] = kBoth ? integer(r[i][kHalves - 1]) : 0;
       }
     }
   }
-  // Window tables: [wavefront][tile][lane] quads {x0, x1 in base A, in base B}
-  static constexpr int kEntry = W * TW * WAVE * 4;  // dwords
-  __device__ __forceinline__ Quad* entry_at(const u32* entry, int i) const {
-    return (Quad*)entry + (wave * TW + i) * WAVE + lane;
+  // Window tables: [tile][lane] quads {x0, x1 in base A, in base B}, of one half alone {base A, base B}
+  static constexpr int kWords = kBoth ? 4 : 2;
+  static constexpr int kEntry = TILES * WAVE * kWords;  // dwords
+  __device__ __forceinline__ u32* entry_at(const u32* entry, int i) const {
+    return (u32*)entry + ((own_tile + i) * WAVE + lane) * kWords;
   }
   static __device__ __forceinline__ Quad own(const State& x, int i) {
-    return Quad{x.a0[i], PAIR ? x.a1[i] : 0u, x.b0[i], PAIR ? x.b1[i] : 0u};
+    return Quad{x.a0[i], kBoth ? x.a1[i] : 0u, x.b0[i], kBoth ? x.b1[i] : 0u};
+  }
+  __device__ __forceinline__ Quad entry(const u32* entry, int i) const {
+    if constexpr (kBoth) return *(const Quad*)entry_at(entry, i);
+    const Twin v = *(const Twin*)entry_at(entry, i);
+    return Quad{v[0], 0, v[1], 0};
   }
   __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
 #pragma unroll
-    for (int i = 0; i < TW; ++i) *entry_at(entry, i) = own(x, i);
+    for (int i = 0; i < TW; ++i)
+      if constexpr (kBoth) *(Quad*)entry_at(entry, i) = own(x, i);
+      else *(Twin*)entry_at(entry, i) = Twin{x.a0[i], x.b0[i]};
   }
-  __device__ __forceinline__ void load_state(State& x, const u32* entry) const {
+  __device__ __forceinline__ void load_state(State& x, const u32* y) const {
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
-      const Quad v = *entry_at(entry, i);
+      const Quad v = entry(y, i);
       x.a0[i] = v[0];
       x.b0[i] = v[2];
-      if constexpr (PAIR) {
+      if constexpr (kBoth) {
         x.a1[i] = v[1];
         x.b1[i] = v[3];
       }
@@ -757,56 +840,76 @@ struct RnsGroup {
   }
 };
 
-// Every block runs the program on 16 elements at a time. The first `split` blocks run j0, the others j1.
-template <int NR, int TW, int W, bool PAIR>
-__global__ __launch_bounds__(W * 64, (W + 3) / 4) void k_rns_group(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
-  using G = RnsGroup<NR, TW, W, PAIR>;
-  __shared__ __align__(16) typename G::Shared shared;
+// Every block runs the program on 16 (FOLD: 8) elements at a time. The first `split` blocks run j0, the others j1.
+// W wavefronts with TW tiles each, then W1 with TW1: the tiles over the four SIMDs as evenly as they go.
+template <int NR, int TW, int W, int TW1, int W1, bool PAIR, bool FOLD>
+__global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
+  using Main = RnsGroup<NR, TW, W + W1, W * TW + W1 * TW1, PAIR, FOLD>;
+  using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, PAIR, FOLD>;
+  __shared__ __align__(16) typename Main::Shared shared;
   const bool second = blockIdx.x >= split;
   const RnsJob& j = second ? j1 : j0;
   const unsigned block = second ? blockIdx.x - split : blockIdx.x;
   const unsigned nblocks = second ? gridDim.x - split : split;
-  G e(shared, j.tables);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const u32* prog = j.prog ? j.prog : j.ins;
   const int len = __builtin_amdgcn_readfirstlane(j.len);
-  u32* table = j.slots + (size_t)block * (size_t)j.entries * G::kEntry;
-  for (size_t first = (size_t)block * 16; first < count; first += (size_t)nblocks * 16) {
-    const unsigned left = (unsigned)std::min(count - first, (size_t)16);
-    typename G::State x;
-    e.load(x, j.in + first * (size_t)(2 * j.nl), left, j.nl);
-    for (int pc = 0; pc < len;) {
-      u32 ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);
-#pragma unroll 1
-      while (ins == ENG_SQ) {
-        e.template multiply<true>(x, nullptr);
-        ins = ++pc < len ? (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]) : ~0u;
-      }
-      if (pc++ >= len) break;
-      const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;
-      u32* entry = table + (size_t)a * G::kEntry;
-      if (op == ENG_STORE_T) {
-        e.store_state(x, entry);
-      } else if (op == ENG_LOAD_T) {
-        e.load_state(x, entry);
-      } else {
-        e.template multiply<false>(x, entry);
-        if (op == ENG_MUL_T_ST) e.store_state(x, table + (size_t)b * G::kEntry);
-      }
-    }
-    e.store(x, j.out + first * (size_t)(8 * G::kLimbTiles), left);
+  u32* table = j.slots + (size_t)block * (size_t)j.entries * Main::kEntry;
+// in the kernel itself: as a function's argument the program's place in the launch's arguments would cost a copy of them
+#define RUN(G, FIRST_TILE)                                                                                          \
+  do {                                                                                                              \
+    G e((typename G::Shared&)shared, j.tables, FIRST_TILE);                                                         \
+    for (size_t first = (size_t)block * G::kElements; first < count; first += (size_t)nblocks * G::kElements) {    \
+      const unsigned left = (unsigned)std::min(count - first, (size_t)G::kElements);                               \
+      typename G::State x;                                                                                          \
+      e.load(x, j.in + first * (size_t)(2 * j.nl), left, j.nl);                                                     \
+      for (int pc = 0; pc < len;) {                                                                                 \
+        u32 ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);                                               \
+        _Pragma("unroll 1") while (ins == ENG_SQ) {                                                                 \
+          e.template multiply<true>(x, nullptr);                                                                    \
+          ins = ++pc < len ? (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]) : ~0u;                              \
+        }                                                                                                           \
+        if (pc++ >= len) break;                                                                                     \
+        const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;                                         \
+        u32* entry = table + (size_t)a * G::kEntry;                                                                 \
+        if (op == ENG_STORE_T) {                                                                                    \
+          e.store_state(x, entry);                                                                                  \
+        } else if (op == ENG_LOAD_T) {                                                                              \
+          e.load_state(x, entry);                                                                                   \
+        } else {                                                                                                    \
+          e.template multiply<false>(x, entry);                                                                     \
+          if (op == ENG_MUL_T_ST) e.store_state(x, table + (size_t)b * G::kEntry);                                  \
+        }                                                                                                           \
+      }                                                                                                             \
+      e.store(x, j.out + first * (size_t)(8 * G::kLimbTiles), left);                                                \
+    }                                                                                                               \
+  } while (0)
+  if (W1 == 0 || wave < W) {
+    RUN(Main, wave * TW);
+  } else if constexpr (W1 > 0) {  // the same barriers
+    static_assert(sizeof(typename Main::Shared) == sizeof(typename Rest::Shared), "one layout");
+    RUN(Rest, W * TW + (wave - W) * TW1);
   }
+#undef RUN
 }
 
 }  // namespace
 
 namespace haflo {
 
-// Wavefronts of 16 elements that are resident at once: four per SIMD
-constexpr int kRnsWavesPerCu = 16;
+constexpr int kRnsElementsPerCu = 256;  // in flight at once
 
 namespace {
 // The blocks of k_rns_group that are resident at once on a compute unit
 int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
+// Blocks of 8 elements, while each has a compute unit to itself
+bool group_folds(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool pair) {
+  return pair && (count + 7) / 8 * (size_t)jobs <= (size_t)ctx->num_cu;
+}
+size_t group_blocks(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool fold) {
+  const size_t all = fold ? (count + 7) / 8 : (count + 15) / 16;
+  return std::min(all, std::max((size_t)ctx->num_cu * group_blocks_per_cu(nr) / (size_t)jobs, (size_t)1));
+}
 // Where the elements are few, or the matrices too large for the LDS, the slots of 16 elements are spread over a block.
 // Measured on both sides (ms, spread / a wavefront for 16 elements): encryption at a 1024-bit key 1.1 / 3.2 up to 4096
 // elements, 2.1 / 3.4 at 8192, 5.1 / 4.4 at 20000; at 2048 bits 4.1 / 17.1 at 3000, 16.2 / 18.0 at 16384, 32 / 27 at
@@ -818,16 +921,16 @@ int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
 bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
   return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 3);
 }
-// Window tables of one modulus: one set per block, or per wavefront that has elements
+// Window tables of one modulus, each of 16 elements: one per block, or as many as the wavefronts that have elements hold
 size_t table_slots(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
-  const size_t tiles = (count + 15) / 16;
-  if (!use_group(ctx, nr, count, jobs)) return tiles;
-  return std::min(tiles, std::max((size_t)ctx->num_cu * group_blocks_per_cu(nr) / (size_t)jobs, (size_t)1));
+  if (!use_group(ctx, nr, count, jobs)) return (count + 15) / 16;
+  if (group_folds(ctx, nr, count, jobs, true)) return (count + 15) / 16;  // two blocks of 8 each
+  return group_blocks(ctx, nr, count, jobs, false);
 }
 }  // namespace
 
 size_t rns_chunk(const haflo_ctx* ctx, int jobs) {
-  return std::max((size_t)ctx->num_cu * kRnsWavesPerCu / (size_t)jobs, (size_t)1) * 16;
+  return std::max((size_t)ctx->num_cu * kRnsElementsPerCu / 32 / (size_t)jobs, (size_t)1) * 32;
 }
 int rns_columns(const ModHost& m) { return 4 * rns::limb_tiles(rns::regs_for(m.nl)); }
 
@@ -859,9 +962,10 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
   // wavefronts of 16 elements: one block per compute unit, with as many in each as it takes to spread the elements
   // over all of them
   size_t waves = (tiles * (size_t)jobs + ctx->num_cu - 1) / ctx->num_cu;
-  waves = std::min(std::max(waves, (size_t)1), (size_t)kRnsWavesPerCu);
+  waves = std::min(std::max(waves, (size_t)1), (size_t)kRnsElementsPerCu / 16);
   const size_t slots = table_slots(ctx, nr, count, jobs);
-  const unsigned blocks = (unsigned)(group ? slots : (tiles + waves - 1) / waves);
+  const bool fold = group && group_folds(ctx, nr, count, jobs, pair);
+  const unsigned blocks = (unsigned)(group ? group_blocks(ctx, nr, count, jobs, fold) : (tiles + waves - 1) / waves);
   RnsJob job[2];
   for (int i = 0; i < jobs; ++i) {
     job[i].tables = m[i]->d_rns;
@@ -885,27 +989,29 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
     if (pair) LAUNCH((k_rns<NR, true>), (unsigned)waves * 64); \
     else LAUNCH((k_rns<NR, false>), (unsigned)waves * 64);     \
   } while (0)
-#define GROUP(NR, TW, W)                                              \
-  do {                                                                \
-    if (pair) LAUNCH((k_rns_group<NR, TW, W, true>), W * 64);       \
-    else LAUNCH((k_rns_group<NR, TW, W, false>), W * 64);           \
+#define GROUP(NR, TW, W, TW1, W1)                                                      \
+  do {                                                                                 \
+    if (fold) LAUNCH((k_rns_group<NR, TW, W, TW1, W1, true, true>), (W + W1) * 64);       \
+    else if (pair) LAUNCH((k_rns_group<NR, TW, W, TW1, W1, true, false>), (W + W1) * 64); \
+    else LAUNCH((k_rns_group<NR, TW, W, TW1, W1, false, false>), (W + W1) * 64);          \
   } while (0)
   switch (nr) {
     case 6:
-      if (group) GROUP(6, 1, 5);
+      if (group) GROUP(6, 1, 5, 1, 0);
       else WAVES(6);
       break;
     case 10:
-      if (group) GROUP(10, 1, 9);
+      if (group) GROUP(10, 1, 9, 1, 0);
       else WAVES(10);
       break;
     case 18:
-      if (group) GROUP(18, 2, 9);
+      if (group) GROUP(18, 2, 8, 1, 2);
       else WAVES(18);
       break;
     case 36:
       if (!pair) return HAFLO_EINVAL;
-      LAUNCH((k_rns_group<36, 3, 12, true>), 12 * 64);
+      if (fold) LAUNCH((k_rns_group<36, 3, 12, 1, 0, true, true>), 12 * 64);
+      else LAUNCH((k_rns_group<36, 3, 12, 1, 0, true, false>), 12 * 64);
       break;
     default: return HAFLO_EINVAL;
   }
