@@ -89,13 +89,580 @@ __device__ __forceinline__ u32 alpha_bytes(u32 sum) {
   return ((u32)a & 127u) | ((u32)(a >> 7) & 255u) << 8;
 }
 
-// The residues of x0 and x1 (PAIR; else of one value, x0) of a lane in one base, in the registers that the matrix
-// products take them from: full quads of each, and one quad with the last two of both.
-template <int NR, bool PAIR>
+// One or two sets of 16 elements, which a wavefront works on side by side, so that a fragment of a matrix read from LDS serves
+// both: the residues of x0 and x1 (PAIR; else of one value, x0) in one base, in the registers that the matrix products take
+// them from: full quads of each, and one quad per set with the last two of both.
+template <int NR, bool PAIR, int kSets>
 struct Residues {
   static_assert(NR % 4 == 2, "full blocks and a half one");
+  static constexpr int kFull = NR / 4, kHalves = PAIR ? 2 : 1;
+  Quad q[kSets][kHalves][kFull];
+  Quad h[kSets];
+  __device__ __forceinline__ u32 get(int s, int x, int i) const {
+    return i < 4 * kFull ? q[s][x][i / 4][i % 4] : h[s][2 * x + i % 4];
+  }
+  __device__ __forceinline__ void set(int s, int x, int i, u32 v) {
+    if (i < 4 * kFull) q[s][x][i / 4][i % 4] = v;
+    else h[s][2 * x + i % 4] = v;
+  }
+  // Gathers quad k in its registers now: left alone, the compiler keeps the values in the 64-bit results they are the
+  // upper words of until all are there.
+  __device__ __forceinline__ void gather(int k) {
+#pragma unroll
+    for (int s = 0; s < kSets; ++s) {
+      if (k < kFull) {
+        asm("" : "+v"(q[s][0][k]));
+        if constexpr (PAIR) asm("" : "+v"(q[s][1][k]));
+      } else {
+        asm("" : "+v"(h[s]));
+      }
+    }
+  }
+};
+template <int NR, bool PAIR, int kSets>
+struct RnsState {
+  Residues<NR, PAIR, kSets> a, b;
+};
+
+// The operand of a matrix product: the half block's words of x0 and of x1 in quads of their own, zeros behind them.
+template <int NR, bool PAIR, int kSets>
+struct Operand {
+  static constexpr int kFull = NR / 4, kHalves = PAIR ? 2 : 1;
+  Residues<NR, PAIR, kSets>& d;
+  Quad o[kSets][kHalves];
+  __device__ __forceinline__ explicit Operand(Residues<NR, PAIR, kSets>& d_) : d(d_) {
+#pragma unroll
+    for (int s = 0; s < kSets; ++s)
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x) {
+        o[s][x] = Quad{d.h[s][2 * x], d.h[s][2 * x + 1], 0, 0};
+        asm("" : "+v"(o[s][x]));  // made once, not for every tile
+      }
+  }
+  __device__ __forceinline__ Acc get(int s, int x, int k) const { return (Acc)(k < kFull ? d.q[s][x][k < kFull ? k : 0] : o[s][x]); }
+  // back to the residues' own form
+  __device__ __forceinline__ void release() {
+#pragma unroll
+    for (int s = 0; s < kSets; ++s)
+      d.h[s] = Quad{o[s][0][0], o[s][0][1], PAIR ? o[s][kHalves - 1][0] : 0u, PAIR ? o[s][kHalves - 1][1] : 0u};
+  }
+};
+
+// A modular product is two matrix products, sigma to base B and rho to base A, tile by tile (four slots, one per lane
+// group). A lane gets whole residues from one, works on them alone and feeds them to the next as they are: no lane
+// exchange, no LDS traffic but the matrices' and the constants', no barrier. While the matrix unit works on one tile, the
+// vector unit finishes the one before.
+// Between operations base A is held as residues (in a run of squarings as the next one's sigma), base B as bytes, with
+// the extra sources of the last way back in their slots.
+template <int NR, bool PAIR, int kSets>
+struct RnsEngine {
+  static constexpr int kHalves = PAIR ? 2 : 1;
+  static constexpr int kFull = rns::full_blocks(NR);
+  static constexpr int kTiles = rns::tiles(NR);  // also the registers that hold primes
+  static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
+  using Res = Residues<NR, PAIR, kSets>;
+  using State = RnsState<NR, PAIR, kSets>;
+  using Op = Operand<NR, PAIR, kSets>;
+  struct Frags {  // of a tile; of the half block only 8 bytes of a row are stored, the rest meets the operand's zeros
+    Acc q[kFull + 1];
+  };
+  struct Sums {  // of one set
+    Acc r[kHalves];
+  };
+  const char* lds;
+  int lane, g;
+  Acc start;
+  // An LDS read adds at most 64 KB to an address, a matrix of 2048-bit moduli is 78 KB: two windows.
+  static constexpr int kWindow = 1 << 16, kWindows = rns::lds_matrix_bytes(NR, 1) > kWindow ? 2 : 1;
+  int at[kWindows], at_half[kWindows];  // this lane's part of a matrix's fragments; of half blocks
+  int at_cst;                           // of this lane group's constants in a row of four slots
+
+  __device__ __forceinline__ RnsEngine(const void* lds_)
+      : lds((const char*)lds_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4), start(start_sums()) {
+    use_matrix<0>();
+  }
+  // What a wavefront reads from LDS is constant over the launch: with addresses that are made anew for each matrix
+  // product the compiler does not read it once and run out of registers for it.
+  template <int MATRIX>
+  __device__ __forceinline__ void use_matrix() {
+    int l = lane;
+    asm volatile("" : "+v"(l));
+#pragma unroll
+    for (int w = 0; w < kWindows; ++w) {
+      at[w] = MATRIX * rns::lds_matrix_bytes(NR, 0) + w * kWindow + 16 * l;
+      at_half[w] = MATRIX * rns::lds_matrix_bytes(NR, 0) + w * kWindow + 8 * l;
+      asm volatile("" : "+v"(at[w]), "+v"(at_half[w]));
+    }
+    at_cst = rns::lds_matrices_bytes(NR) + (l & 48);
+    asm volatile("" : "+v"(at_cst));
+  }
+  // the constants of base A (0), base B's products (1) and its sums (2)
+  __device__ __forceinline__ Quad cst(int base, int i) const {
+    return *(const Quad*)(lds + at_cst + (base * rns::slots(NR) + 4 * i) * 16);
+  }
+  static __device__ __forceinline__ Acc half_fragment(const void* p) {
+    const Twin h = *(const Twin*)p;
+    int any0 = 0, any1 = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "=v"(any0), "=v"(any1));
+#endif
+    return Acc{(int)h[0], (int)h[1], any0, any1};
+  }
+  template <int MATRIX>
+  __device__ __forceinline__ void fragments(Frags& m, int t) const {
+    constexpr int kRows = rns::last_rows(NR, MATRIX);
+    if (t == kTiles - 1 && kRows != 16) {
+      const char* p = lds + MATRIX * rns::lds_matrix_bytes(NR, 0) + t * kTileBytes;
+      int row = (lane >> 4) * kRows + (lane & (kRows - 1));
+      asm volatile("" : "+v"(row));
+#pragma unroll
+      for (int k = 0; k < kFull; ++k) m.q[k] = *(const Acc*)(p + k * kRows * 64 + 16 * row);
+      m.q[kFull] = half_fragment(p + kFull * kRows * 64 + 8 * row);
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < kFull; ++k) {
+      const int o = t * kTileBytes + k * 1024;
+      m.q[k] = *(const Acc*)(lds + at[o / kWindow] + o % kWindow);
+    }
+    const int o = t * kTileBytes + kFull * 1024;
+    m.q[kFull] = half_fragment(lds + at_half[o / kWindow] + o % kWindow);
+  }
+  static __device__ __forceinline__ Sums sums(const Frags& m, const Op& d, int s, const Acc& from) {
+    Sums v;
+#pragma unroll
+    for (int x = 0; x < kHalves; ++x) v.r[x] = from;
+#pragma unroll
+    for (int k = 0; k <= kFull; ++k)
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x)
+        v.r[x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(m.q[k], d.get(s, x, k), v.r[x], 0, 0, 0);
+    return v;
+  }
+  // The order that one set's products of a tile are issued in: a matrix instruction keeps its unit busy for 16 cycles and
+  // the issue slot for 8; the vector unit's work on the set before goes between, as do the next fragments' reads.
+  template <int VALU, bool READ>
+  static __device__ __forceinline__ void interleave() {
+#pragma unroll
+    for (int k = 0; k <= kFull; ++k)
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        if (READ && x == kHalves - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, VALU, 0);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // the residue products of register i with v0, v1: of base A (sigma) or base B (z, w)
+  static __device__ __forceinline__ void product(u32& r0, u32& r1, u32 u0, u32 u1, u32 v0, u32 v1, u32 p, u32 pinv, u32 e) {
+    r0 = reduce(smad(u0, v0, 0), p, pinv);
+    if constexpr (PAIR) r1 = reduce(smad(r0, e, smad(u0, v1, smad(u1, v0, 0))), p, pinv);
+  }
+  static __device__ __forceinline__ void square(u32& r0, u32& r1, u32 u0, u32 u1, u32 p, u32 pinv, u32 e) {
+    r0 = reduce(smad(u0, u0, 0), p, pinv);
+    if constexpr (PAIR) r1 = reduce(smad(r0, e, twice(u0, u1)), p, pinv);
+  }
+  // sigma, as bytes, of the square of base A's residues
+  __device__ __forceinline__ void square_a(Res& a) {
+    use_matrix<0>();
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) {
+      if (i % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+      const Quad k = cst(0, i);
+#pragma unroll
+      for (int s = 0; s < kSets; ++s) {
+        u32 r0, r1 = 0;
+        square(r0, r1, a.get(s, 0, i), PAIR ? a.get(s, 1, i) : 0u, k[0], k[1], k[2]);
+        a.set(s, 0, i, r0 ^ rns::kOmega);
+        if constexpr (PAIR) a.set(s, 1, i, r1 ^ rns::kOmega);
+      }
+      if (i % 4 == 3 || i == kTiles - 1) a.gather(i / 4);
+    }
+  }
+  // Sigma, and z and w, of the product with a table entry, which comes from memory: the next kAhead quads of four
+  // registers are on their way.
+  struct EntryQuad {
+    Quad q[kSets][kHalves];
+  };
+  static constexpr int kAhead = kSets == 1 ? 1 : 3;
+  __device__ __forceinline__ EntryQuad load_quad(const u32* entry, int j) const {
+    const int base = j / (kFull + 1), k = j % (kFull + 1);
+    const Quad* p = (const Quad*)(entry + base * kArray) + lane;
+    EntryQuad r;
+#pragma unroll
+    for (int s = 0; s < kSets; ++s) {
+      if (k == kFull) {
+        const Quad h = p[(kSets * kHalves * kFull + s) * WAVE];
+        r.q[s][0] = h;
+        r.q[s][kHalves - 1] = PAIR ? Quad{h[2], h[3], 0, 0} : h;
+      } else {
+#pragma unroll
+        for (int x = 0; x < kHalves; ++x) r.q[s][x] = p[((kSets * k + s) * kHalves + x) * WAVE];
+      }
+    }
+    return r;
+  }
+  __device__ __forceinline__ void multiply_residues(State& x, const u32* entry) {
+    use_matrix<0>();
+    constexpr int kSteps = 2 * (kFull + 1);
+    EntryQuad y[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) y[j] = load_quad(entry, j);
+#pragma unroll
+    for (int j = 0; j < kSteps; ++j) {
+      const int base = j / (kFull + 1), k4 = j % (kFull + 1);
+      Res& d = base ? x.b : x.a;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 4 * k4; i < 4 * k4 + 4 && i < kTiles; ++i) {
+        const Quad k = cst(base, i);
+#pragma unroll
+        for (int s = 0; s < kSets; ++s) {
+          const u32 flip = base ? rns::kOmega : 0u;
+          u32 r0, r1 = 0;
+          product(r0, r1, d.get(s, 0, i) ^ flip, PAIR ? d.get(s, 1, i) ^ flip : 0u, y[j % kAhead].q[s][0][i % 4],
+                  PAIR ? y[j % kAhead].q[s][kHalves - 1][i % 4] : 0u, k[0], k[1], k[2]);
+          d.set(s, 0, i, base ? r0 : r0 ^ rns::kOmega);
+          if constexpr (PAIR) d.set(s, 1, i, base ? r1 : r1 ^ rns::kOmega);
+        }
+      }
+      d.gather(k4);
+      __builtin_amdgcn_sched_barrier(0);
+      if (j + kAhead < kSteps) y[j % kAhead] = load_quad(entry, j + kAhead);
+    }
+  }
+
+  // the constant 1 of the bias in its slot, and nothing in alpha's yet
+  __device__ __forceinline__ void set_extra(Res& d) const {
+    const bool alpha = g == rns::alpha_group(NR), bias = g == rns::bias_group(NR);
+#pragma unroll
+    for (int s = 0; s < kSets; ++s)
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x) d.h[s][2 * x + 1] = alpha ? 0u : bias ? 1u : d.h[s][2 * x + 1];
+  }
+  // Base B of a register's reduced value, as bytes, from a tile's sums and z, w
+  static __device__ __forceinline__ void finish_b(Res& b, int i, int s, const Sums& v, const Quad& k) {
+    const u32 t0 = reduce(smad(b.get(s, 0, i), k[2], column(v.r[0])), k[0], k[1]);
+    b.set(s, 0, i, t0 ^ rns::kOmega);
+    if constexpr (PAIR) {
+      s64 col = smad(b.get(s, 1, i), k[2], column(v.r[1]));
+      asm("" : "+v"(col));  // multiply-adds one after the other
+      b.set(s, 1, i, reduce(smad(t0, k[3], col), k[0], k[1]) ^ rns::kOmega);
+    }
+    if (s == kSets - 1 && (i % 4 == 3 || i == kTiles - 1)) b.gather(i / 4);
+  }
+  // z and w of the square of a register, in place of its bytes
+  static __device__ __forceinline__ void square_b(Res& b, int i, int s, const Quad& k) {
+    u32 r0, r1 = 0;
+    square(r0, r1, b.get(s, 0, i) ^ rns::kOmega, PAIR ? b.get(s, 1, i) ^ rns::kOmega : 0u, k[0], k[1], 0u - k[3]);
+    b.set(s, 0, i, r0);
+    if constexpr (PAIR) b.set(s, 1, i, r1);
+  }
+  // Base B of the reduced pair, as bytes, from sigma in base A; SQ: of a square, whose z and w are made on the way from
+  // base B's bytes, else from those.
+  template <bool SQ>
+  __device__ __forceinline__ void extend_to_b(State& x) {
+    use_matrix<0>();
+    set_extra(x.a);
+    Op d(x.a);
+    Frags m;
+    Sums v0, v1;
+    Quad k = {}, k_before = {}, k_next = cst(2, 0);
+    fragments<0>(m, 0);
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      k = k_next;
+      v0 = sums(m, d, 0, start);
+      if (kSets == 1 && t + 1 < kTiles) {
+        fragments<0>(m, t + 1);
+        k_next = cst(2, t + 1);
+      }
+      if (t > 0) finish_b(x.b, t - 1, kSets - 1, v1, k_before);
+      if (SQ) square_b(x.b, t, 0, k);
+      interleave<2, kSets == 1>();
+      if constexpr (kSets == 2) {
+        v1 = sums(m, d, 1, start);
+        if (t + 1 < kTiles) {
+          fragments<0>(m, t + 1);
+          k_next = cst(2, t + 1);
+        }
+        finish_b(x.b, t, 0, v0, k);
+        if (SQ) square_b(x.b, t, 1, k);
+        interleave<2, true>();
+      } else {
+        v1 = v0;
+      }
+      k_before = k;
+    }
+    finish_b(x.b, kTiles - 1, kSets - 1, v1, k_before);
+    set_extra(x.b);
+  }
+
+  // base A of a register from a tile's sums; NEXT: and sigma of its square, as bytes
+  template <bool NEXT>
+  static __device__ __forceinline__ void finish_a(Res& a, int i, int s, const Sums& v, const Quad& k) {
+    u32 u0 = reduce(column(v.r[0]), k[0], k[1]), u1 = 0;
+    if constexpr (PAIR) u1 = reduce(column(v.r[kHalves - 1]), k[0], k[1]);
+    if (NEXT) {
+      u32 r0, r1 = 0;
+      square(r0, r1, u0, u1, k[0], k[1], k[2]);
+      u0 = r0 ^ rns::kOmega;
+      u1 = r1 ^ rns::kOmega;
+    }
+    a.set(s, 0, i, u0);
+    if constexpr (PAIR) a.set(s, 1, i, u1);
+    if (s == kSets - 1 && i % 4 == 3) a.gather(i / 4);
+  }
+  // base A from base B's bytes, NEXT: as sigma of the square; alpha stays in its slot of base B
+  template <bool NEXT>
+  __device__ __forceinline__ void extend_to_a(State& x) {
+    use_matrix<1>();
+    Op d(x.b);
+    Frags m;
+    fragments<1>(m, kTiles - 1);
+    Quad k_before = cst(0, kTiles - 1), k_next = cst(0, 0);
+    // the tile that has alpha's row: its own primes take alpha afterwards
+    Sums v0 = sums(m, d, 0, start), v1;
+    if constexpr (kSets == 2) v1 = sums(m, d, 1, start);
+    const Acc half = m.q[kFull];
+    fragments<1>(m, 0);
+#pragma unroll
+    for (int s = 0; s < kSets; ++s)
+#pragma unroll
+      for (int i = 0; i < kHalves; ++i) {
+        Acc& r = s == 1 ? v1.r[i] : v0.r[i];
+        const u32 a = g == rns::alpha_group(NR) ? alpha_bytes((u32)column(r) + rns::alpha_round(NR)) : 0u;
+        const Quad only = {0, a, 0, 0};
+        r = __builtin_amdgcn_mfma_i32_16x16x64_i8(half, (Acc)only, r, 0, 0, 0);
+        d.o[s][i][1] |= a;
+      }
+    if constexpr (kSets == 2) finish_a<NEXT>(x.a, kTiles - 1, 0, v0, k_before);
+    else v1 = v0;
+#pragma unroll
+    for (int t = 0; t < kTiles - 1; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      const Quad k = k_next;
+      v0 = sums(m, d, 0, start);
+      if (kSets == 1 && t + 2 < kTiles) {
+        fragments<1>(m, t + 1);
+        k_next = cst(0, t + 1);
+      }
+      finish_a<NEXT>(x.a, t == 0 ? kTiles - 1 : t - 1, kSets - 1, v1, k_before);
+      interleave<2, kSets == 1>();
+      if constexpr (kSets == 2) {
+        v1 = sums(m, d, 1, start);
+        if (t + 2 < kTiles) {
+          fragments<1>(m, t + 1);
+          k_next = cst(0, t + 1);
+        }
+        finish_a<NEXT>(x.a, t, 0, v0, k);
+        interleave<2, true>();
+      } else {
+        v1 = v0;
+      }
+      k_before = k;
+    }
+    finish_a<NEXT>(x.a, kTiles - 2, kSets - 1, v1, k_before);
+    if ((kTiles - 2) / 4 < kFull) x.a.gather((kTiles - 2) / 4);
+    x.a.gather(kFull);
+    d.release();
+  }
+
+  // one tile of a matrix in global memory, with all rows
+  __device__ __forceinline__ Frags global_fragments(const char* matrix, int t) const {
+    Frags m;
+    const char* p = matrix + t * kTileBytes;
+#pragma unroll
+    for (int k = 0; k < kFull; ++k) m.q[k] = *(const Acc*)(p + k * 1024 + lane * 16);
+    m.q[kFull] = half_fragment(p + kFull * 1024 + lane * 8);
+    return m;
+  }
+  // the pairs whose limbs are at `src` (`left` of them, then zeros) into both bases
+  __device__ __forceinline__ void load(State& x, const u32* src, unsigned left, int nl, const char* matrix) {
+    x = State();
+#pragma unroll
+    for (int s = 0; s < kSets; ++s) {
+      const bool active = (unsigned)((lane & 15) + 16 * s) < left;
+      const u32* p = src + ((lane & 15) + 16 * s) * 2 * nl;
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const int l = 4 * i + g;
+        const bool ok = active && l < nl;
+        x.a.set(s, 0, i, (ok ? p[l] : 0u) ^ rns::kOmega);
+        if constexpr (PAIR) x.a.set(s, 1, i, (ok ? p[nl + l] : 0u) ^ rns::kOmega);
+      }
+    }
+    if (g == rns::bias_group(NR)) {  // in place of a limb that is zero
+#pragma unroll
+      for (int s = 0; s < kSets; ++s)
+#pragma unroll
+        for (int i = 0; i < kHalves; ++i) x.a.set(s, i, NR - 1, 1);
+    }
+    use_matrix<0>();
+    Op d(x.a);
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      const Frags m = global_fragments(matrix, t);
+      const Quad k = cst(1, t);
+#pragma unroll
+      for (int s = 0; s < kSets; ++s) {
+        const Sums v = sums(m, d, s, start);
+#pragma unroll
+        for (int i = 0; i < kHalves; ++i) x.b.set(s, i, t, reduce(column(v.r[i]), k[0], k[1]) ^ rns::kOmega);
+      }
+      if (t % 4 == 3 || t == kTiles - 1) x.b.gather(t / 4);
+    }
+    set_extra(x.b);
+    extend_to_a<false>(x);
+  }
+  // the pairs as two integers each in columns of weight 2^(29 l), from base B
+  __device__ __forceinline__ void store(State& x, long long* dst, unsigned left, const char* matrix) {
+    Op d(x.b);
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      const Frags m = global_fragments(matrix, t);
+#pragma unroll
+      for (int s = 0; s < kSets; ++s) {
+        const Sums v = sums(m, d, s, Acc{0, 0, 0, 0});
+        const unsigned e = (unsigned)((lane & 15) + 16 * s);
+        if (e < left) {
+          long long* p = dst + e * (8 * kTiles) + 4 * t + g;
+          p[0] = integer(v.r[0]);
+          p[4 * kTiles] = PAIR ? integer(v.r[kHalves - 1]) : 0;
+        }
+      }
+    }
+  }
+
+  // Window tables: an entry holds the residues of base A and of base B one after the other, each as
+  // [quad][set][x0, x1][lane], the last quad for both halves.
+  static constexpr int kArray = kSets * (kHalves * kFull + 1) * 4 * WAVE;  // dwords
+  // quads `from` to `to` of one base
+  __device__ __forceinline__ void load_entry(Res& d, const u32* entry, int base, int from, int to) const {
+    const Quad* p = (const Quad*)(entry + base * kArray) + lane;
+#pragma unroll
+    for (int k = from; k < to; ++k)
+#pragma unroll
+      for (int s = 0; s < kSets; ++s) {
+        if (k == kFull) {
+          d.h[s] = p[(kSets * kHalves * kFull + s) * WAVE];
+          continue;
+        }
+#pragma unroll
+        for (int x = 0; x < kHalves; ++x) d.q[s][x][k < kFull ? k : 0] = p[((kSets * k + s) * kHalves + x) * WAVE];
+      }
+  }
+  __device__ __forceinline__ void store_entry(const Res& d, u32* entry, int base, u32 flip) const {
+    Quad* p = (Quad*)(entry + base * kArray) + lane;
+#pragma unroll
+    for (int s = 0; s < kSets; ++s) {
+#pragma unroll
+      for (int k = 0; k < kFull; ++k)
+#pragma unroll
+        for (int x = 0; x < kHalves; ++x) p[((kSets * k + s) * kHalves + x) * WAVE] = d.q[s][x][k] ^ flip;
+      p[(kSets * kHalves * kFull + s) * WAVE] = d.h[s] ^ flip;
+    }
+  }
+  __device__ __forceinline__ void load_state(State& x, const u32* entry) const {
+    load_entry(x.a, entry, 0, 0, kFull + 1);
+    load_entry(x.b, entry, 1, 0, kFull + 1);
+#pragma unroll
+    for (int s = 0; s < kSets; ++s) {
+#pragma unroll
+      for (int k = 0; k < kFull; ++k)
+#pragma unroll
+        for (int i = 0; i < kHalves; ++i) x.b.q[s][i][k] ^= rns::kOmega;
+      x.b.h[s] ^= rns::kOmega;
+    }
+  }
+  __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
+    store_entry(x.a, entry, 0, 0u);
+    store_entry(x.b, entry, 1, rns::kOmega);
+  }
+};
+
+// Wavefronts per SIMD: two with 256 registers each for two sets, three with 168 for one. Measured against wavefronts of one
+// set, four to a SIMD, whose phases did not overlap within a wavefront and which spent 54 instructions per prime: 65536
+// encryptions at a 1024-bit key 9.8 -> 8.4 ms, 32768 decryptions at a 2048-bit key 10.0 -> 8.7, 8192 of them 3.47 -> 2.58,
+// 20001 key-owner encryptions 11.2 -> 9.8. Per squaring of 32 elements at 1024 bits: 790 vector and 218 matrix instructions,
+// 7.0 k cycles for a SIMD's only wavefront and 9 - 10 k for two together. The clock gives way under it (2.0 GHz with one
+// wavefront per SIMD, 1.5 - 1.65 with two, and up to 6 % apart between the dies): more instructions in flight no longer help.
+// What spills (99 registers in the pair form of 1024 bits) does so outside the run of squarings.
+constexpr int rns_waves_per_simd(int sets) { return sets == 1 ? 3 : 2; }
+// Every wavefront runs the program on its sets at a time. The first `split` blocks run j0, the others j1.
+template <int NR, bool PAIR, int kSets>
+__global__ __launch_bounds__(rns_waves_per_simd(kSets) * 256, rns_waves_per_simd(kSets)) void k_rns(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
+  constexpr int kElements = 16 * kSets;
+  __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
+  const bool second = blockIdx.x >= split;
+  const RnsJob& j = second ? j1 : j0;
+  const unsigned block = second ? blockIdx.x - split : blockIdx.x;
+  const unsigned nblocks = second ? gridDim.x - split : split;
+  for (int i = (int)threadIdx.x; i < rns::lds_bytes(NR) / 16; i += (int)blockDim.x)
+    ((Quad*)lds)[i] = ((const Quad*)j.tables)[i];
+  __syncthreads();
+  const char* in_matrix = (const char*)j.tables + rns::lds_bytes(NR);
+  const char* out_matrix = in_matrix + rns::in_matrix_bytes(NR);
+  RnsEngine<NR, PAIR, kSets> e(lds);
+  const unsigned waves = blockDim.x / 64;
+  // the same for the whole wavefront, so that what follows from it stays in scalar registers
+  const size_t wave = (size_t)block * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+  constexpr size_t kEntry = 2 * RnsEngine<NR, PAIR, kSets>::kArray;
+  const u32* prog = j.prog ? j.prog : j.ins;
+  const int len = __builtin_amdgcn_readfirstlane(j.len);
+  u32* table = j.slots + wave * (size_t)j.entries * kEntry;
+  for (size_t tile = wave; tile * kElements < count; tile += (size_t)nblocks * waves) {
+    const unsigned left = (unsigned)std::min(count - tile * kElements, (size_t)kElements);
+    RnsState<NR, PAIR, kSets> x;
+    e.load(x, j.in + tile * (size_t)(kElements * 2 * j.nl), left, j.nl, in_matrix);
+    for (int pc = 0; pc < len;) {
+      const u32 ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc++]);
+      const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;
+      u32* entry = table + (size_t)a * kEntry;
+      if (op == ENG_STORE_T) {
+        e.store_state(x, entry);
+        continue;
+      }
+      if (op == ENG_LOAD_T) {
+        e.load_state(x, entry);
+        continue;
+      }
+      if (op == ENG_SQ) {  // a run of them, nine tenths of a program, each but the last with the next one's sigma
+        e.square_a(x.a);
+        e.template extend_to_b<true>(x);
+#pragma unroll 1
+        while (pc < len && (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]) == ENG_SQ) {
+          ++pc;
+
+          e.template extend_to_a<true>(x);
+          e.template extend_to_b<true>(x);
+        }
+      } else {
+        e.multiply_residues(x, entry);
+        e.template extend_to_b<false>(x);
+      }
+      e.template extend_to_a<false>(x);
+      if (op == ENG_MUL_T_ST) e.store_state(x, table + (size_t)b * kEntry);
+    }
+    e.store(x, j.out + tile * (size_t)(kElements * 8 * rns::tiles(NR)), left, out_matrix);
+  }
+}
+
+// The same for pairs of 2048-bit halves: 16 elements per wavefront and four wavefronts per SIMD, whose 128 registers hold
+// the 72 of an element set's state, and each phase of a product after the other, without the next one's work in between.
+// 65536 encryptions at a 2048-bit key take 48.5 ms with it (49.2 with the residues of before, kept below 2^31 by 54
+// instructions per prime instead of 47), 52.4 with k_rns's two sets of which every wavefront's 256 registers are full:
+// tables and spilled registers then wait for memory, two wavefronts per SIMD are too few to hide it.
+// The residues of x0 and x1 of a lane in one base: full quads of each, and one quad with the last two of both.
+template <int NR>
+struct OneResidues {
+  static_assert(NR % 4 == 2, "full blocks and a half one");
   static constexpr int kFull = NR / 4;
-  Quad q[PAIR ? 2 : 1][kFull];
+  Quad q[2][kFull];
   Quad h;
   template <int X>
   __device__ __forceinline__ u32 get(int i) const {
@@ -111,7 +678,7 @@ struct Residues {
   __device__ __forceinline__ void gather(int k) {
     if (k < kFull) {
       asm("" : "+v"(q[0][k]));
-      if constexpr (PAIR) asm("" : "+v"(q[1][k]));
+      asm("" : "+v"(q[1][k]));
     } else {
       asm("" : "+v"(h));
     }
@@ -123,9 +690,9 @@ struct Residues {
     for (int k = 0; k <= kFull; ++k) gather(k);
   }
 };
-template <int NR, bool PAIR>
-struct RnsState {
-  Residues<NR, PAIR> a, b;
+template <int NR>
+struct OneState {
+  OneResidues<NR> a, b;
 };
 
 // A residue as the bytes the matrix products take (each 128 less), and back. Hidden from the compiler, which would
@@ -137,9 +704,9 @@ __device__ __forceinline__ u32 to_bytes(u32 v) {
 }
 
 // Where this lane's part of a fragment lies in a tile of 16 (kept) rows: of a full one, and of the half one
-struct FragmentAt {
+struct OneFragmentAt {
   int full, half;  // bytes
-  __device__ __forceinline__ FragmentAt(int lane, int rows) {
+  __device__ __forceinline__ OneFragmentAt(int lane, int rows) {
     full = ((lane >> 4) * rows + (lane & (rows - 1))) * 16;
     half = full / 2;
   }
@@ -148,14 +715,14 @@ struct FragmentAt {
 };
 
 // The operand of a matrix product: the half block's words of x0 and of x1 in a quad of their own, zeros behind them.
-template <int NR, bool PAIR>
-struct Operand {
-  Residues<NR, PAIR>& d;
+template <int NR>
+struct OneOperand {
+  OneResidues<NR>& d;
   Quad h0, h1;
-  __device__ __forceinline__ explicit Operand(Residues<NR, PAIR>& d_)
+  __device__ __forceinline__ explicit OneOperand(OneResidues<NR>& d_)
       : d(d_), h0(Quad{d_.h[0], d_.h[1], 0, 0}), h1(Quad{d_.h[2], d_.h[3], 0, 0}) {
     asm("" : "+v"(h0));  // made once, not for every tile
-    if constexpr (PAIR) asm("" : "+v"(h1));
+    asm("" : "+v"(h1));
   }
   // back to the residues' own form
   __device__ __forceinline__ void release() { d.h = Quad{h0[0], h0[1], h1[0], h1[1]}; }
@@ -165,9 +732,9 @@ struct Operand {
 // of a row are stored: what lies in the other registers meets the operand's zeros. (A version with
 // v_mfma_i32_16x16x32_i8 for the half block, accumulated onto the 16x16x64 products, gave wrong sums. Why is not
 // understood: neither a wrong idea of its operands' layout nor a missing wait was excluded.)
-template <int NR, bool PAIR>
-__device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile, int rows, const FragmentAt& at,
-                                              const Operand<NR, PAIR>& d, const Acc& start, Acc* half = nullptr) {
+template <int NR>
+__device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile, int rows, const OneFragmentAt& at,
+                                              const OneOperand<NR>& d, const Acc& start, Acc* half = nullptr) {
   constexpr int F = rns::full_blocks(NR);
   const char* p = (const char*)tile;
   Acc m[F + 1];
@@ -184,24 +751,23 @@ __device__ __forceinline__ void tile_products(Acc& r0, Acc& r1, const void* tile
 #pragma unroll
   for (int k = 0; k <= F; ++k) {
     r0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], (Acc)(k < F ? d.d.q[0][k < F ? k : 0] : d.h0), r0, 0, 0, 0);
-    if constexpr (PAIR)
-      r1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], (Acc)(k < F ? d.d.q[1][k < F ? k : 0] : d.h1), r1, 0, 0, 0);
+    r1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[k], (Acc)(k < F ? d.d.q[1][k < F ? k : 0] : d.h1), r1, 0, 0, 0);
   }
 }
 
-template <int NR, bool PAIR>
-struct RnsEngine {
+template <int NR>
+struct OneEngine {
   static constexpr int kTiles = rns::tiles(NR);  // also the registers that hold primes
   static constexpr int kGroup = 3;               // tiles the compiler may mix
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
   const char* lds;
   int lane, g;
   Acc start;
-  FragmentAt at, at_last0, at_last1;  // of a tile, and of the last one of either matrix
+  OneFragmentAt at, at_last0, at_last1;  // of a tile, and of the last one of either matrix
   int cst_at;                         // of this lane group's constants in a row of four slots
   u32 keep, mine, one;                // masks of set_extra and set_alpha
 
-  __device__ __forceinline__ RnsEngine(const void* lds_)
+  __device__ __forceinline__ OneEngine(const void* lds_)
       : lds((const char*)lds_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4), start(start_sums()), at(lane, 16),
         at_last0(lane, rns::last_rows(NR, 0)), at_last1(lane, rns::last_rows(NR, 1)), cst_at(16 * g),
         keep(g == rns::alpha_group(NR) || g == rns::bias_group(NR) ? 0u : ~0u), mine(g == rns::alpha_group(NR) ? ~0u : 0u),
@@ -224,32 +790,32 @@ struct RnsEngine {
     return *(const Quad*)(lds + rns::lds_matrices_bytes(NR) + (base * rns::slots(NR) + 4 * i) * 16 + cst_at);
   }
   template <int MATRIX>
-  __device__ __forceinline__ void lds_products(Acc& r0, Acc& r1, int t, const Operand<NR, PAIR>& d, Acc* half = nullptr) const {
+  __device__ __forceinline__ void lds_products(Acc& r0, Acc& r1, int t, const OneOperand<NR>& d, Acc* half = nullptr) const {
     constexpr int kLast = rns::last_rows(NR, MATRIX);
     const char* p = lds + MATRIX * rns::lds_matrix_bytes(NR, 0) + t * kTileBytes;
-    if (t == kTiles - 1) tile_products<NR, PAIR>(r0, r1, p, kLast, kLast == 16 ? at : MATRIX ? at_last1 : at_last0, d, start, half);
-    else tile_products<NR, PAIR>(r0, r1, p, 16, at, d, start);
+    if (t == kTiles - 1) tile_products<NR>(r0, r1, p, kLast, kLast == 16 ? at : MATRIX ? at_last1 : at_last0, d, start, half);
+    else tile_products<NR>(r0, r1, p, 16, at, d, start);
   }
 
   // The residue products of one base of a square (y null) or of a product with the table entry y: bytes of sigma in
   // base A (BASE 0), z and w in base B. The entry's quads are on their way one step ahead.
   template <int BASE, bool SQ>
-  __device__ __forceinline__ void base_products(Residues<NR, PAIR>& x, const u32* y) {
+  __device__ __forceinline__ void base_products(OneResidues<NR>& x, const u32* y) {
     constexpr int kQuads = NR / 4 + 1;
     const Quad* p = (const Quad*)(y + BASE * kArray) + lane;
     x.forget();
     Quad n0 = {}, n1 = {};
     if (!SQ) {
       n0 = p[0];
-      if (PAIR) n1 = p[WAVE];
+      n1 = p[WAVE];
     }
 #pragma unroll
     for (int q = 0; q < kQuads; ++q) {
       const Quad y0 = n0, y1 = n1;
       forget();
       if (!SQ && q + 1 < kQuads) {
-        n0 = p[(PAIR ? 2 : 1) * (q + 1) * WAVE];
-        if (PAIR && q + 2 < kQuads) n1 = p[(2 * (q + 1) + 1) * WAVE];
+        n0 = p[2 * (q + 1) * WAVE];
+        if (q + 2 < kQuads) n1 = p[(2 * (q + 1) + 1) * WAVE];
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -259,7 +825,7 @@ struct RnsEngine {
         const u32 u0 = x.template get<0>(i), v0 = SQ ? u0 : y0[c];
         const u32 s0 = reduce(smad(u0, v0, 0), k[0], k[1]);
         x.template set<0>(i, BASE ? s0 : to_bytes(s0));
-        if constexpr (PAIR) {
+        {
           const u32 u1 = x.template get<1>(i), v1 = SQ ? u1 : (q + 1 < kQuads ? y1[c] : y0[(2 + c) % 4]);
           const s64 cross = SQ ? twice(u0, u1) : smad(u0, v1, smad(u1, v0, 0));
           const u32 s1 = reduce(smad(s0, k[2], cross), k[0], k[1]);
@@ -270,23 +836,23 @@ struct RnsEngine {
     }
   }
   template <bool SQ>
-  __device__ __forceinline__ void products(RnsState<NR, PAIR>& x, const u32* y) {
+  __device__ __forceinline__ void products(OneState<NR>& x, const u32* y) {
     base_products<0, SQ>(x.a, y);
     base_products<1, SQ>(x.b, y);
   }
 
   // the constant 1 of the bias in its slot, and nothing in alpha's yet
-  __device__ __forceinline__ void set_extra(Residues<NR, PAIR>& d) const {
+  __device__ __forceinline__ void set_extra(OneResidues<NR>& d) const {
     d.h[1] = (d.h[1] & keep) | one;
-    if (PAIR) d.h[3] = (d.h[3] & keep) | one;
+    d.h[3] = (d.h[3] & keep) | one;
   }
 
   // Base B of the reduced pair from sigma (bytes, in base A) and the products z, w (in base B); leaves base B as bytes
   // for the way back.
-  __device__ __forceinline__ void extend_to_b(RnsState<NR, PAIR>& x) {
+  __device__ __forceinline__ void extend_to_b(OneState<NR>& x) {
     x.b.forget();
     set_extra(x.a);
-    Operand<NR, PAIR> d(x.a);
+    OneOperand<NR> d(x.a);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       if (t % kGroup == 0) forget();
@@ -294,7 +860,7 @@ struct RnsEngine {
       lds_products<0>(r0, r1, t, d);
       const Quad k = cst(2, t);
       const u32 t0 = reduce(smad(x.b.template get<0>(t), k[2], column(r0)), k[0], k[1]);
-      if constexpr (PAIR) {
+      {
         const s64 col = smad(x.b.template get<1>(t), k[2], column(r1));
         x.b.template set<1>(t, to_bytes(reduce(smad(t0, k[3], col), k[0], k[1])));
       }
@@ -304,8 +870,8 @@ struct RnsEngine {
     set_extra(x.b);
   }
   // base A from base B's bytes; turns base B back to residues, with alpha in its slot
-  __device__ __forceinline__ void extend_to_a(RnsState<NR, PAIR>& x) {
-    Operand<NR, PAIR> d(x.b);
+  __device__ __forceinline__ void extend_to_a(OneState<NR>& x) {
+    OneOperand<NR> d(x.b);
 #pragma unroll
     for (int i = 0; i < kTiles; ++i) {
       const int t = i == 0 ? kTiles - 1 : i - 1;
@@ -317,7 +883,7 @@ struct RnsEngine {
         const Quad a0 = {0, alpha_bytes((u32)column(r0) + rns::alpha_round(NR)) & mine, 0, 0};
         r0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(half, (Acc)a0, r0, 0, 0, 0);
         d.h0[1] |= a0[1];
-        if constexpr (PAIR) {
+        {
           const Quad a1 = {0, alpha_bytes((u32)column(r1) + rns::alpha_round(NR)) & mine, 0, 0};
           r1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(half, (Acc)a1, r1, 0, 0, 0);
           d.h1[1] |= a1[1];
@@ -327,111 +893,103 @@ struct RnsEngine {
       }
       const Quad k = cst(0, t);
       x.a.template set<0>(t, reduce(column(r0), k[0], k[1]));
-      if constexpr (PAIR) x.a.template set<1>(t, reduce(column(r1), k[0], k[1]));
+      x.a.template set<1>(t, reduce(column(r1), k[0], k[1]));
       if (t % 4 == 3) x.a.gather(t / 4);
     }
     d.release();
     flip(x.b);
   }
   // residues <-> bytes
-  static __device__ __forceinline__ void flip(Residues<NR, PAIR>& d) {
+  static __device__ __forceinline__ void flip(OneResidues<NR>& d) {
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
       d.q[0][k] ^= rns::kOmega;
-      if constexpr (PAIR) d.q[1][k] ^= rns::kOmega;
+      d.q[1][k] ^= rns::kOmega;
     }
     d.h ^= rns::kOmega;
   }
 
   // the pairs whose limbs are at `src` (`left` of them, then zeros) into both bases
-  __device__ __forceinline__ void load(RnsState<NR, PAIR>& x, const u32* src, unsigned left, int nl, const char* matrix) {
+  __device__ __forceinline__ void load(OneState<NR>& x, const u32* src, unsigned left, int nl, const char* matrix) {
     const bool active = (unsigned)(lane & 15) < left;
     src += (lane & 15) * 2 * nl;
-    x = RnsState<NR, PAIR>();
+    x = OneState<NR>();
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const int l = 4 * i + g;
       const bool ok = active && l < nl;
       x.a.template set<0>(i, (ok ? src[l] : 0u) ^ rns::kOmega);
-      if constexpr (PAIR) x.a.template set<1>(i, (ok ? src[nl + l] : 0u) ^ rns::kOmega);
+      x.a.template set<1>(i, (ok ? src[nl + l] : 0u) ^ rns::kOmega);
     }
     if (one) {  // in place of a limb that is zero
       x.a.template set<0>(NR - 1, 1);
-      if constexpr (PAIR) x.a.template set<1>(NR - 1, 1);
+      x.a.template set<1>(NR - 1, 1);
     }
-    Operand<NR, PAIR> d(x.a);
+    OneOperand<NR> d(x.a);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       forget();
       Acc r0, r1;
-      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d, start);
+      tile_products<NR>(r0, r1, matrix + t * kTileBytes, 16, at, d, start);
       const Quad k = cst(1, t);
       x.b.template set<0>(t, to_bytes(reduce(column(r0), k[0], k[1])));
-      if constexpr (PAIR) x.b.template set<1>(t, to_bytes(reduce(column(r1), k[0], k[1])));
+      x.b.template set<1>(t, to_bytes(reduce(column(r1), k[0], k[1])));
     }
     set_extra(x.b);
     extend_to_a(x);
   }
   // The pair as two integers in columns of weight 2^(29 l). Base B still holds what the way back left there, alpha and
   // the bias among it.
-  __device__ __forceinline__ void store(RnsState<NR, PAIR>& x, long long* dst, unsigned left, const char* matrix) {
+  __device__ __forceinline__ void store(OneState<NR>& x, long long* dst, unsigned left, const char* matrix) {
     const bool active = (unsigned)(lane & 15) < left;
     dst += (lane & 15) * 8 * kTiles;
     flip(x.b);
-    Operand<NR, PAIR> d(x.b);
+    OneOperand<NR> d(x.b);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
       forget();
       Acc r0, r1;
-      tile_products<NR, PAIR>(r0, r1, matrix + t * kTileBytes, 16, at, d, Acc{0, 0, 0, 0});
+      tile_products<NR>(r0, r1, matrix + t * kTileBytes, 16, at, d, Acc{0, 0, 0, 0});
       if (active) {
         dst[4 * t + g] = integer(r0);
-        dst[4 * kTiles + 4 * t + g] = PAIR ? integer(r1) : 0;
+        dst[4 * kTiles + 4 * t + g] = integer(r1);
       }
     }
   }
 
   // Window tables: an entry holds the registers of base A and of base B one after the other, each as [quad][lane].
-  static constexpr int kArray = ((PAIR ? 2 : 1) * (NR / 4) + 1) * 4 * WAVE;  // dwords
-  __device__ __forceinline__ void load_entry(Residues<NR, PAIR>& d, const u32* entry, int array) const {
+  static constexpr int kArray = (2 * (NR / 4) + 1) * 4 * WAVE;  // dwords
+  __device__ __forceinline__ void load_entry(OneResidues<NR>& d, const u32* entry, int array) const {
     const Quad* p = (const Quad*)(entry + array * kArray) + lane;
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
-      d.q[0][k] = p[(PAIR ? 2 : 1) * k * WAVE];
-      if constexpr (PAIR) d.q[1][k] = p[(2 * k + 1) * WAVE];
+      d.q[0][k] = p[2 * k * WAVE];
+      d.q[1][k] = p[(2 * k + 1) * WAVE];
     }
-    d.h = p[(PAIR ? 2 : 1) * (NR / 4) * WAVE];
+    d.h = p[2 * (NR / 4) * WAVE];
   }
-  __device__ __forceinline__ void store_entry(const Residues<NR, PAIR>& d, u32* entry, int array) const {
+  __device__ __forceinline__ void store_entry(const OneResidues<NR>& d, u32* entry, int array) const {
     Quad* p = (Quad*)(entry + array * kArray) + lane;
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
-      p[(PAIR ? 2 : 1) * k * WAVE] = d.q[0][k];
-      if constexpr (PAIR) p[(2 * k + 1) * WAVE] = d.q[1][k];
+      p[2 * k * WAVE] = d.q[0][k];
+      p[(2 * k + 1) * WAVE] = d.q[1][k];
     }
-    p[(PAIR ? 2 : 1) * (NR / 4) * WAVE] = d.h;
+    p[2 * (NR / 4) * WAVE] = d.h;
   }
-  __device__ __forceinline__ void load_state(RnsState<NR, PAIR>& x, const u32* entry) const {
+  __device__ __forceinline__ void load_state(OneState<NR>& x, const u32* entry) const {
     load_entry(x.a, entry, 0);
     load_entry(x.b, entry, 1);
   }
-  __device__ __forceinline__ void store_state(const RnsState<NR, PAIR>& x, u32* entry) const {
+  __device__ __forceinline__ void store_state(const OneState<NR>& x, u32* entry) const {
     store_entry(x.a, entry, 0);
     store_entry(x.b, entry, 1);
   }
 };
 
-// Four wavefronts per SIMD, 128 registers: 72 of state, 20 for a tile's fragments, 8 for its sums. Measured at 65536
-// elements and a 2048-bit modulus: 49 ms per 2363 products where the word-serial pair products took 128 (1024 bits: 10
-// against 25 ms); the matrix cores are busy 61 % of the cycles, the vector units issue in 64 % of them (1119 vector and
-// 360 matrix instructions per squaring and wavefront), LDS reads take 41 %, at 1.9 GHz. 32 elements per wavefront (half
-// the matrix reads) need 256 registers and more, and spilled. What spills at 128, as compiled: the pair form of 2048-bit
-// moduli 54 registers (76 bytes of scratch a lane), the single form 290 there (1148 bytes: 32768 powers in 45.5 ms, a pair
-// takes 48.7) and 26 at 1024 bits (92 bytes), although it holds half the state; the others none. The bound is also
-// that of launches with two or three wavefronts per SIMD, which could have more.
 // Every wavefront runs the program on 16 elements at a time. The first `split` blocks run j0, the others j1.
-template <int NR, bool PAIR>
-__global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
+template <int NR>
+__global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsigned split, size_t count) {
   __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
   const bool second = blockIdx.x >= split;
   const RnsJob& j = second ? j1 : j0;
@@ -442,17 +1000,17 @@ __global__ __launch_bounds__(1024, 4) void k_rns(RnsJob j0, RnsJob j1, unsigned 
   __syncthreads();
   const char* in_matrix = (const char*)j.tables + rns::lds_bytes(NR);
   const char* out_matrix = in_matrix + rns::in_matrix_bytes(NR);
-  RnsEngine<NR, PAIR> e(lds);
+  OneEngine<NR> e(lds);
   const unsigned waves = blockDim.x / 64;
   // the same for the whole wavefront, so that what follows from it stays in scalar registers
   const size_t wave = (size_t)block * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-  constexpr size_t kEntry = 2 * RnsEngine<NR, PAIR>::kArray;
+  constexpr size_t kEntry = 2 * OneEngine<NR>::kArray;
   const u32* prog = j.prog ? j.prog : j.ins;
   const int len = __builtin_amdgcn_readfirstlane(j.len);
   u32* table = j.slots + wave * (size_t)j.entries * kEntry;
   for (size_t tile = wave; tile * 16 < count; tile += (size_t)nblocks * waves) {
     const unsigned left = (unsigned)std::min(count - tile * 16, (size_t)16);
-    RnsState<NR, PAIR> x;
+    OneState<NR> x;
     e.load(x, j.in + tile * (size_t)(16 * 2 * j.nl), left, j.nl, in_matrix);
     for (int pc = 0; pc < len;) {
       u32 ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);
@@ -919,11 +1477,21 @@ size_t group_blocks(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool f
 // block is faster at every size measured, 64.6 / 71.7 at 12288 and 104 / 113 at 20000 (the other form spills), but
 // follows the pairs' rule.
 bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
-  return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 3);
+  return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 2);
+}
+// Sets of 16 elements per wavefront of k_rns. A SIMD's time follows from its wavefronts: with one set each 2.5, 4.0 and
+// 6.1 ms for one, two and three of them (encryption at a 1024-bit key, 16384, 30000 and 40000 elements), with two sets 3.75
+// and 7.5 - 8.4. So one set where its wavefronts are one or three to a SIMD (40000 elements 6.1 / 7.5 ms; 30000, two to a
+// SIMD, 4.18 / 4.08; 65536, four, 9.3 / 8.4); the short products of 256-bit primes' pairs with two to a SIMD as well
+// (12288 decryptions at a 1024-bit key 1.05 / 1.13).
+int rns_sets(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool pair) {
+  if (nr == 18) return pair ? 1 : 2;
+  const size_t per_simd = ((count + 15) / 16 * (size_t)jobs + 4 * ctx->num_cu - 1) / (4 * (size_t)ctx->num_cu);
+  return per_simd == 1 || per_simd == 3 || (nr == 6 && per_simd == 2) ? 1 : 2;
 }
 // Window tables of one modulus, each of 16 elements: one per block, or as many as the wavefronts that have elements hold
 size_t table_slots(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
-  if (!use_group(ctx, nr, count, jobs)) return (count + 15) / 16;
+  if (!use_group(ctx, nr, count, jobs)) return (count + 31) / 32 * 2;
   if (group_folds(ctx, nr, count, jobs, true)) return (count + 15) / 16;  // two blocks of 8 each
   return group_blocks(ctx, nr, count, jobs, false);
 }
@@ -957,12 +1525,13 @@ RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int
 int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, const haflo_ctx* ctx, uint32_t* ws,
               const RnsBuffers& b, size_t count, int entries, bool pair, hipStream_t st) {
   const int nr = rns::regs_for(m[0]->nl);
-  const size_t tiles = (count + 15) / 16;
+  const int sets = rns_sets(ctx, nr, count, jobs, pair);
+  const size_t elements = 16 * (size_t)sets, tiles = (count + elements - 1) / elements;
   const bool group = use_group(ctx, nr, count, jobs);
-  // wavefronts of 16 elements: one block per compute unit, with as many in each as it takes to spread the elements
+  // wavefronts of 16 or 32 elements: one block per compute unit, with as many in each as it takes to spread the elements
   // over all of them
   size_t waves = (tiles * (size_t)jobs + ctx->num_cu - 1) / ctx->num_cu;
-  waves = std::min(std::max(waves, (size_t)1), (size_t)kRnsElementsPerCu / 16);
+  waves = std::min(std::max(waves, (size_t)1), (size_t)(nr == 18 && pair ? 16 : 4 * rns_waves_per_simd(sets)));
   const size_t slots = table_slots(ctx, nr, count, jobs);
   const bool fold = group && group_folds(ctx, nr, count, jobs, pair);
   const unsigned blocks = (unsigned)(group ? group_blocks(ctx, nr, count, jobs, fold) : (tiles + waves - 1) / waves);
@@ -984,10 +1553,12 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
   if (jobs == 1) job[1] = job[0];
 #define LAUNCH(KERNEL, THREADS) \
   hipLaunchKernelGGL(KERNEL, dim3(blocks * jobs), dim3(THREADS), 0, st, job[0], job[1], blocks, count)
-#define WAVES(NR)                                             \
-  do {                                                        \
-    if (pair) LAUNCH((k_rns<NR, true>), (unsigned)waves * 64); \
-    else LAUNCH((k_rns<NR, false>), (unsigned)waves * 64);     \
+#define WAVES(NR)                                                                          \
+  do {                                                                                     \
+    if (pair && sets == 1) LAUNCH((k_rns<NR, true, 1>), (unsigned)waves * 64);             \
+    else if (pair) LAUNCH((k_rns<NR, true, 2>), (unsigned)waves * 64);                     \
+    else if (sets == 1) LAUNCH((k_rns<NR, false, 1>), (unsigned)waves * 64);               \
+    else LAUNCH((k_rns<NR, false, 2>), (unsigned)waves * 64);                              \
   } while (0)
 #define GROUP(NR, TW, W, TW1, W1)                                                      \
   do {                                                                                 \
@@ -1006,7 +1577,8 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
       break;
     case 18:
       if (group) GROUP(18, 2, 8, 1, 2);
-      else WAVES(18);
+      else if (pair) LAUNCH((k_rns_one<18>), (unsigned)waves * 64);
+      else LAUNCH((k_rns<18, false, 2>), (unsigned)waves * 64);
       break;
     case 36:
       if (!pair) return HAFLO_EINVAL;
