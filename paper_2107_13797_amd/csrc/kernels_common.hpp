@@ -517,6 +517,15 @@ __global__ __launch_bounds__(kBlockThreads, 4) void k_to_pairs(ModRef M, const u
     else if ((mh).lpt == 18 && (mh).t == 8) { CALL(9, 16); }      \
     else return HAFLO_EINVAL;                                     \
   } while (0)
+// The same for few pairs, whose chains of products are all that counts: one pair per wavefront, 2 or 3 limbs of each half
+// per lane (36-limb halves on 18 lanes, 72 on 36, 144 on 48). The limb arrays in memory are the same.
+#define HAFLO_DISPATCH_PAIRS_WAVE(mh, CALL)                       \
+  do {                                                            \
+    if ((mh).nl == 36) { CALL(2, 18); }                           \
+    else if ((mh).nl == 72) { CALL(2, 36); }                      \
+    else if ((mh).nl == 144) { CALL(3, 48); }                     \
+    else return HAFLO_EINVAL;                                     \
+  } while (0)
 inline bool haflo_has_pair_geometry(const haflo::ModHost& mh) { return mh.d_pairs && mh.lpt == 18 && mh.t <= 8; }
 // The same dispatch for batches of at most one big integer per SIMD, where the latency of one product is all
 // that counts: one integer per wavefront on 18 to 48 lanes with 2 to 6 limbs each (steps of a dozen
