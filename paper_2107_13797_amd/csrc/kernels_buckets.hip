@@ -829,42 +829,29 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
   // What is left are chains of 14, 14 and up to 45 products on few pairs, bound by the latency of one product: a
   // wavefront for each pair while there are at most two to a SIMD. The three launches of 600 rows by 11 columns take 110 us
   // less so at 1024 bits (0.53 -> 0.42 ms for the whole call), 200 at 2048 (0.93 -> 0.73) and 290 at 4096 bits (1.85 ->
-  // 1.56, one column); 4096 by 32 at 1024 bits 681 -> 587 us, 65536 by 32 at 2048 bits 5.71 -> 5.49 ms. Beyond two to a
-  // SIMD the groups of a few lanes fill the chip better; at the line (42 | 43 columns in the first fold, 128 | 129 in the
-  // second) both sides gain over groups throughout: 0.73 -> 0.65 | 0.75 -> 0.68 ms and 0.82 -> 0.77 | 0.75 -> 0.70.
-  // 512-bit keys have no geometry with a pair on so many lanes.
-  const auto chains = [&](size_t count, bool& wave) {
-    wave = mh.nl != 18 && count <= (size_t)ctx->num_cu * 8;
-    LaunchShape sh = launch_shape(ctx, count, lanes, 8);
-    if (wave) sh.blocks = (int)std::max(count, (size_t)1), sh.threads = WAVE, sh.gpb = 1;
-    return sh;
-  };
+  // 1.56, one column); 4096 by 32 at 1024 bits 681 -> 587 us, 65536 by 32 at 2048 bits 5.71 -> 5.49 ms. At the
+  // line (42 | 43 columns in the first fold, 128 | 129 in the second) both sides gain over groups throughout: 0.73 -> 0.65 |
+  // 0.75 -> 0.68 ms and 0.82 -> 0.77 | 0.75 -> 0.70.
   bool wave;
-#define DISPATCH(CALL)                              \
-  do {                                              \
-    if (wave) HAFLO_DISPATCH_PAIRS_WAVE(mh, CALL);  \
-    else HAFLO_DISPATCH_PAIRS(mh, CALL);            \
-  } while (0)
   {
-    const LaunchShape sh = chains(combos * kSegs, wave);
+    const LaunchShape sh = launch_pairs(ctx, mh, combos * kSegs, lanes, wave);
 #define CALL(LPT, T) HAFLO_LAUNCH((k_bk_fold1<LPT, T, true>), sh, st, M, one, (const u32*)G, combos, AT)
-    DISPATCH(CALL);
+    HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
   }
   {
-    const LaunchShape sh = chains(combos * 2, wave);
+    const LaunchShape sh = launch_pairs(ctx, mh, combos * 2, lanes, wave);
 #define CALL(LPT, T) HAFLO_LAUNCH((k_bk_fold2<LPT, T, true>), sh, st, M, one, (const u32*)AT, combos, R)
-    DISPATCH(CALL);
+    HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
   }
   {
-    const LaunchShape sh = chains(cols * 2, wave);
+    const LaunchShape sh = launch_pairs(ctx, mh, cols * 2, lanes, wave);
 #define CALL(LPT, T) \
   HAFLO_LAUNCH((k_bk_horner<LPT, T, true>), sh, st, M, one, leave, (const u32*)R, cols, d_P, (const u32*)stats)
-    DISPATCH(CALL);
+    HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
   }
-#undef DISPATCH
   return hip_status(hipGetLastError());
 }
 

@@ -526,6 +526,21 @@ __global__ __launch_bounds__(kBlockThreads, 4) void k_to_pairs(ModRef M, const u
     else if ((mh).nl == 144) { CALL(3, 48); }                     \
     else return HAFLO_EINVAL;                                     \
   } while (0)
+// Whether `count` pairs take that geometry (while there are at most two wavefronts to a SIMD: beyond that groups of a few
+// lanes fill the chip better; 512-bit keys have no geometry with a pair on so many lanes), and the launch: `lanes` to a
+// group otherwise.
+inline haflo::LaunchShape launch_pairs(const haflo_ctx* ctx, const haflo::ModHost& mh, size_t count, int lanes,
+                                       bool& wave) {
+  wave = mh.nl != 18 && count <= (size_t)ctx->num_cu * 8;
+  haflo::LaunchShape sh = haflo::launch_shape(ctx, count, lanes, 8);
+  if (wave) sh.blocks = (int)std::max(count, (size_t)1), sh.threads = 64, sh.gpb = 1;
+  return sh;
+}
+#define HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL)      \
+  do {                                                \
+    if (wave) HAFLO_DISPATCH_PAIRS_WAVE(mh, CALL);    \
+    else HAFLO_DISPATCH_PAIRS(mh, CALL);              \
+  } while (0)
 inline bool haflo_has_pair_geometry(const haflo::ModHost& mh) { return mh.d_pairs && mh.lpt == 18 && mh.t <= 8; }
 // The same dispatch for batches of at most one big integer per SIMD, where the latency of one product is all
 // that counts: one integer per wavefront on 18 to 48 lanes with 2 to 6 limbs each (steps of a dozen

@@ -991,20 +991,25 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
     if (cols) {
       rc = invert_batch(ctx, (const u32*)d_c, inv, cols, st);
       if (rc != HAFLO_OK) return rc;
+      // The squarings and the first levels are as many products as there are launches and positions, on few pairs: the
+      // latency of a product bounds them, so a wavefront for each pair while launch_pairs allows. 1000 rows by 32 columns
+      // 0.40 -> 0.35 ms at 1024 bits and 0.74 -> 0.65 at 2048, 300 by 32 at 4096 bits 1.57 -> 1.42, 16384 by 256 at 2048
+      // 3.51 -> 3.46 (256 columns are the last whose squarings fit: 64 rows by 256 | 300 at 1024 bits 0.78 -> 0.74 | 0.86).
+      bool wave;
       {
-        const LaunchShape sh = launch_shape(ctx, cols * 2 * kMaxPos, lanes, 8);
+        const LaunchShape sh = launch_pairs(ctx, mh, cols * 2 * kMaxPos, lanes, wave);
 #define CALL(LPT, T)                                                                                                \
   HAFLO_LAUNCH((k_xw_positions<LPT, T, true>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstR4 * 2 * mh.nl), \
                (const u32*)(mh.d_pairs + (size_t)kConstR5 * 2 * mh.nl), (const u32*)d_c, (const u32*)inv, cols,     \
                tables, (const u32*)ws)
-        HAFLO_DISPATCH_PAIRS(mh, CALL);
+        HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
       }
       for (int B = 1; B < kWinEntries; B *= 2) {
         const size_t groups = cols * 2 * kMaxPos * (size_t)std::min(B, kWinEntries - 1 - B);
-        const LaunchShape sh = launch_shape(ctx, groups, lanes, 8);
+        const LaunchShape sh = launch_pairs(ctx, mh, groups, lanes, wave);
 #define CALL(LPT, T) HAFLO_LAUNCH((k_xw_level<LPT, T, true>), sh, st, M, one, cols, B, tables, (const u32*)ws)
-        HAFLO_DISPATCH_PAIRS(mh, CALL);
+        HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
       }
     }
