@@ -418,13 +418,6 @@ constexpr uint64_t kResiduePowerSquarings = 16;
 bool power_in_residues(const haflo_ctx* ctx, size_t count) {
   return ctx->Nh.d_rns && (ctx->Nh.nl == 36 || ctx->Nh.nl == 72) && count >= (size_t)ctx->num_cu * 32;
 }
-// The key owner's first stage modulo 512-bit primes, where a product on limbs is short: on limbs for large batches. ms
-// in residues / on limbs, both stages together: 16385 elements 2.58 / 2.74, 20001 2.71 / 2.89, 24577 3.33 / 3.37, 28000
-// 3.55 / 3.52, 32768 3.73 / 3.59, 45000 5.81 / 5.27, 65536 7.47 / 6.98, 80000 9.66 / 8.69. (Around 10000 the two are
-// within 3 %. For larger primes residues win at every size: 65536 at a 2048-bit key 31.5 / 34.9.)
-bool first_stage_on_limbs(const haflo_ctx* ctx, size_t count) {
-  return ctx->P.nl == 18 && count > (size_t)ctx->num_cu * 96;
-}
 u32* align256(u32* p) { return (u32*)(((uintptr_t)p + 255) & ~(uintptr_t)255); }
 
 }  // namespace
@@ -587,9 +580,10 @@ int haflo_encrypt(const haflo_ctx* ctx, const uint32_t* d_plain, const uint32_t*
   for (int stage = 0; stage < 2; ++stage) {
     const ModHost& geo = stage ? h : l;
     // both stages in the residue number system, the first one on single residues modulo the primes (half the work of a
-    // pair): 20001 encryptions at a 2048-bit key 13.3 -> 11.1 ms against limb arithmetic in the first stage, 1024 at a
-    // 1024-bit key 1.18 -> 0.78, 16384 at 4096 bits 57.7 -> 56.0
-    if (l.d_rns && workspace_bytes >= ws_encrypt(ctx, count) && !(stage == 0 && first_stage_on_limbs(ctx, count))) {
+    // pair). The closest are the 512-bit primes, where a product on limbs is short: ms at a 1024-bit key with the first
+    // stage in residues / on limbs, 16384 encryptions 2.02 / 2.04, 20001 2.43 / 2.69, 32768 2.99 / 3.22, 45000 4.72 / 4.69,
+    // 65536 5.96 / 6.03, 80000 7.74 / 7.70; so at every size.
+    if (l.d_rns && workspace_bytes >= ws_encrypt(ctx, count)) {
       EngineIO src[2], dst[2];
       for (int side = 0; side < 2; ++side) {
         src[side] = engine_io(side ? ctx->Q : ctx->P);

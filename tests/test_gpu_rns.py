@@ -153,9 +153,9 @@ def test_powers_by_one_scalar_match_small_batches(bits):
 
 @pytest.mark.parametrize("bits,count", [(1024, 24576), (1024, 24577), (1024, 45000), (1024, 80000)])
 def test_key_owner_is_not_slower_with_the_workspace_asked_for(bits, count):
-    """Both sides of the rule that leaves the first stage on limbs: the same bits as in the least workspace, which is
-    the limb arithmetic throughout, and no slower. (45000 and 80000 elements took 1.07 and 1.09 of its time with both
-    stages in residues, 0.98 now; the bound leaves 6 % for what runs of one side differ.)"""
+    """The sizes around which single products modulo 512-bit primes are as quick on limbs as in residues: the same bits as
+    in the least workspace, which is the limb arithmetic throughout, and no slower. (45000 and 80000 elements take about
+    0.88 of its time; the bound leaves what runs of one side differ.)"""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2107_13797_amd import api
