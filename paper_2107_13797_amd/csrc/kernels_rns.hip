@@ -1046,11 +1046,12 @@ __global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsig
 // wavefront needs of the others, the bytes of all residues, goes through LDS (16 bytes per lane and block of 64, as the
 // matrix product reads its operand), one barrier before each of the two matrix products of a modular product. The
 // matrices stay in registers where they fit (kHeld: 16 to 80 of them), else they stream from L2. What bounds it is
-// waiting: half of a wavefront's cycles (1024 and 2048 bits) go to barriers, LDS and matrix results, with vector issue
-// and LDS each at about 40 %, the matrix cores at 21 and 37 % of the compute unit's cycles; at 4096 bits two thirds, with
-// 455 KB of the 630 KB of both matrices read from L2 per product. Measured against the limb arithmetic on one
-// wavefront per integer: 1024 encryptions at a 1024-bit key 2.67 -> 1.05 ms, 256 at 2048 bits 8.5 -> 3.9, 3001 at 4096
-// bits 74.9 -> 23.4; 3072 decryptions at 1024 bits 1.33 -> 0.55 ms, 64 at 4096 bits 8.63 -> 3.97.
+// waiting: 52, 40 and 46 % of a wavefront's cycles (1024, 2048 and 4096 bits) go to barriers, LDS, memory and matrix results,
+// with vector issue at 38, 54 and 32 % and the matrix cores at 13, 31 and 46 % of the SIMDs' cycles, 1670, 2310 and 11200 a
+// product; at 4096 bits 420 KB of the 630 KB of both matrices come from L2 per product. Measured against the limb arithmetic on one
+// wavefront per integer, and against the version before blocks of 8 elements and weighted rows: 1024 encryptions at a
+// 1024-bit key 2.67, 1.06 -> 0.86 ms, 256 at 2048 bits 8.5, 3.9 -> 2.3, 3001 at 4096 bits 74.9, 23.5 -> 22.5; 3072 decryptions
+// at 1024 bits 1.33, 0.55 -> 0.51 ms, 64 at 4096 bits 8.63, 4.01 -> 2.41.
 //
 // FOLD: 8 elements to a block, x0 in columns 0 to 7 of the matrix products and x1 in columns 8 to 15, for batches that do
 // not fill the chip with blocks of 16: half the matrix instructions and operand reads per product. A lane then has one half
@@ -1460,7 +1461,9 @@ constexpr int kRnsElementsPerCu = 256;  // in flight at once
 namespace {
 // The blocks of k_rns_group that are resident at once on a compute unit
 int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
-// Blocks of 8 elements, while each has a compute unit to itself
+// Blocks of 8 elements, while each has a compute unit to itself. ms with 16 / 8 to a block: 2048 encryptions at a 1024-bit
+// key 1.06 / 0.87, at 2048 bits 3.58 / 2.42, at 4096 bits 21.8 / 20.6 (100 of them 20.8 / 18.2); 1024 decryptions at 1024 bits
+// 0.465 / 0.425, at 2048 bits 1.12 / 0.94, at 4096 bits 3.64 / 2.53.
 bool group_folds(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool pair) {
   return pair && (count + 7) / 8 * (size_t)jobs <= (size_t)ctx->num_cu;
 }
@@ -1469,13 +1472,12 @@ size_t group_blocks(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool f
   return std::min(all, std::max((size_t)ctx->num_cu * group_blocks_per_cu(nr) / (size_t)jobs, (size_t)1));
 }
 // Where the elements are few, or the matrices too large for the LDS, the slots of 16 elements are spread over a block.
-// Measured on both sides (ms, spread / a wavefront for 16 elements): encryption at a 1024-bit key 1.1 / 3.2 up to 4096
-// elements, 2.1 / 3.4 at 8192, 5.1 / 4.4 at 20000; at 2048 bits 4.1 / 17.1 at 3000, 16.2 / 18.0 at 16384, 32 / 27 at
-// 32768; decryption at a 1024-bit key 0.55 / 0.93 at 4096, 1.02 / 0.93 at 8192. The single form (the key owner's first
-// stage, in its encryption with the second stage on limbs): at a 1024-bit key 1.70 / 2.02 at 4096, 2.04 / 2.05 at 6200, 3.09
-// / 2.86 at 10000; at 2048 bits 5.86 / 7.26 at 4096, 9.70 / 10.5 at 8192, 12.9 / 12.1 at 16384; at 4096 bits spread over a
-// block is faster at every size measured, 64.6 / 71.7 at 12288 and 104 / 113 at 20000 (the other form spills), but
-// follows the pairs' rule.
+// Measured on both sides (ms, spread / not): encryption at a 1024-bit key 1.17 / 2.32 at 4096 elements, 2.11 / 2.37 at 8192,
+// 3.09 / 2.39 at 9216; at 2048 bits 7.3 / 17.1 at 8192, 21.4 / 23.7 at 24576, 25.0 / 25.2 at 28672, 28.5 / 26.7 at 32768;
+// decryption at a 1024-bit key 0.54 / 0.76 at 4096, 0.96 / 0.76 at 5120, at 2048 bits 2.14 / 2.42 and (6144) 3.17 / 2.48, at 4096
+// bits 21.6 / 24.0 at 12288, 28.8 / 26.9 at 16384. The key owner's encryption, whose first stage is of the single form: at a
+// 1024-bit key 0.88 / 1.26 at 4096, 1.63 / 1.28 at 6144, at 2048 bits 3.03 / 4.01 and 4.90 / 4.13, at 4096 bits 33.3 / 35.4 at
+// 12288, 44.3 / 39.9 at 16384.
 bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
   return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 2);
 }
