@@ -11,6 +11,7 @@
 #pragma once
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "hostbig.hpp"
@@ -63,6 +64,8 @@ constexpr int lds_bytes(int nr) { return lds_matrices_bytes(nr) + cst_bytes(nr);
 constexpr int table_bytes(int nr) { return lds_bytes(nr) + in_matrix_bytes(nr) + out_matrix_bytes(nr); }
 
 inline uint32_t mulmod(uint32_t a, uint32_t b, uint32_t p) { return (uint32_t)((uint64_t)a * b % p); }
+// v mod p for two channel primes, which differ by less than either
+inline uint32_t prime_mod(uint32_t v, uint32_t p) { return v < p ? v : v - p; }
 // 256 v mod p for the channel primes, all just below 2^30
 inline uint32_t times256(uint32_t v, uint32_t p) {
   const uint64_t t = (uint64_t)v << 8;
@@ -108,19 +111,19 @@ inline std::vector<uint32_t> primes(int k, uint32_t residue_mod_4) {
   const std::vector<uint32_t>& all = residue_mod_4 == 1 ? one : three;
   return std::vector<uint32_t>(all.begin(), all.begin() + k);
 }
-// the inverses of v modulo p (p not among v's divisors), one inversion for all of them; *prod: the product of v
+// the inverses of the channel primes v modulo p (not among them), one inversion for all of them; *prod: the product of v
 inline std::vector<uint32_t> inverses(const std::vector<uint32_t>& v, uint32_t p, uint32_t* prod) {
   std::vector<uint32_t> r(v.size());
   uint32_t acc = 1;
   for (size_t i = 0; i < v.size(); ++i) {
     r[i] = acc;
-    acc = mulmod(acc, v[i] % p, p);
+    acc = mulmod(acc, prime_mod(v[i], p), p);
   }
   *prod = acc;
   uint32_t inv = invmod(acc, p);
   for (size_t i = v.size(); i-- > 0;) {
     r[i] = mulmod(r[i], inv, p);
-    inv = mulmod(inv, v[i] % p, p);
+    inv = mulmod(inv, prime_mod(v[i], p), p);
   }
   return r;
 }
@@ -217,7 +220,7 @@ inline std::vector<uint32_t> build_tables(const Big& s, int nl, Big* m_a) {
     const uint32_t p = a[i], w = (uint32_t)((1ull << 32) % p), sinv = invmod(s.mod_small(p), p);
     uint32_t rest = 1;
     for (int t = 0; t < k; ++t)
-      if (t != i) rest = mulmod(rest, a[t] % p, p);
+      if (t != i) rest = mulmod(rest, prime_mod(a[t], p), p);
     const uint32_t c = mulmod(mulmod(p - sinv, invmod(rest, p), p), w, p);
     sgn[i] = powmod(c, (p - 1) / 2, p) == 1 ? 0 : 1;
     f[i] = powmod(sgn[i] ? p - c : c, (p + 1) / 4, p);
@@ -231,7 +234,7 @@ inline std::vector<uint32_t> build_tables(const Big& s, int nl, Big* m_a) {
     const uint32_t p = b[j], w = (uint32_t)((1ull << 32) % p), sinv = invmod(s.mod_small(p), p);
     uint32_t rest = 1;
     for (int t = 0; t < k; ++t)
-      if (t != j) rest = mulmod(rest, b[t] % p, p);
+      if (t != j) rest = mulmod(rest, prime_mod(b[t], p), p);
     h[j] = invmod(rest, p);
     uint32_t* t = &cst[(size_t)(slots(nr) + j) * 4];
     t[0] = p;
@@ -309,14 +312,15 @@ inline std::vector<uint32_t> build_tables(const Big& s, int nl, Big* m_a) {
     integer(alpha, 0, mb, -1);
     integer(alpha, 1, Big::mul(mb, Big(128)), -1);
   }
-  std::vector<uint32_t> t;
+  std::vector<uint32_t> t((size_t)table_bytes(nr) / 4);
+  auto to = t.begin();
   const auto put = [&](const std::vector<uint8_t>& v) {
     for (size_t o = 0; o < v.size(); o += 4)
-      t.push_back((uint32_t)v[o] | (uint32_t)v[o + 1] << 8 | (uint32_t)v[o + 2] << 16 | (uint32_t)v[o + 3] << 24);
+      *to++ = (uint32_t)v[o] | (uint32_t)v[o + 1] << 8 | (uint32_t)v[o + 2] << 16 | (uint32_t)v[o + 3] << 24;
   };
   put(ab.bytes());
   put(ba.bytes());
-  t.insert(t.end(), cst.begin(), cst.end());
+  to = std::copy(cst.begin(), cst.end(), to);
   put(in.bytes());
   put(out.bytes());
   return t;
