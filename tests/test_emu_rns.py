@@ -3,6 +3,7 @@ test_emu_kernels.py): moduli it must leave alone, workspaces without room for it
 import ctypes as C
 import os
 import random
+import subprocess
 import time
 
 import numpy as np
@@ -13,6 +14,8 @@ from oracle import paillier_oracle as O
 from paper_2107_13797_amd import _cabi, synth
 
 from test_emu_kernels import Dev, emu, words, ws, zeros  # noqa: F401
+
+HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 def public_ctx(lib, n, bits):
@@ -28,15 +31,23 @@ def export_n(lib, ctx, bits, d_cipher, count):
     return synth.words_to_ints(out.get())
 
 
-def channel_prime(residue, index):
-    """The index-th largest prime below 2^30 of the class residue modulo 4 (3: base A, 1: base B)."""
-    c = (1 << 30) - 4 + residue
-    while True:
-        if all(c % d for d in range(3, 32768, 2)):
-            if index == 0:
-                return c
-            index -= 1
-        c -= 4
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("rns") / "librns_shim.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "rns_shim.cpp")], check=True)
+    return C.CDLL(out)
+
+
+def channel_primes(shim, k, residue):
+    """The engine's own: the k largest it takes of the class residue modulo 4 (3: base A, 1: base B)."""
+    buf = (C.c_uint32 * k)()
+    assert shim.rns_primes(k, residue, buf) == k
+    return list(buf)
+
+
+def uses_residues(lib, ctx, op, count):
+    """Whether a call in the workspace asked for goes through the engine: the limb arithmetic needs no more than the least."""
+    return lib.haflo_workspace_bytes(ctx, op, count, 0) > lib.haflo_workspace_bytes_least(ctx, op, count, 0)
 
 
 def odd_multiple(prime, bits, seed):
@@ -49,13 +60,17 @@ def odd_multiple(prime, bits, seed):
 
 # the first and the last prime of both bases of a 512-bit modulus (18 each), and one prime of the bases of larger moduli
 @pytest.mark.parametrize("residue,index", [(3, 0), (3, 17), (1, 0), (1, 17), (3, 18)])
-def test_moduli_that_share_a_factor_with_the_channel_primes(emu, residue, index):  # noqa: F811
+def test_moduli_that_share_a_factor_with_the_channel_primes(emu, shim, residue, index):  # noqa: F811
     """Any odd n of the right length makes a public context; one that a channel prime divides has no residues modulo
     that prime to work with and is served by the limb arithmetic."""
-    lib, bits = emu, 512
-    n = odd_multiple(channel_prime(residue, index), bits, 100 * residue + index)
+    lib, bits, k = emu, 512, shim.rns_primes_for(6)
+    prime = channel_primes(shim, index + 1, residue)[index]
+    assert k == 18 and (prime in channel_primes(shim, k, residue)) == (index < k)
+    n = odd_multiple(prime, bits, 100 * residue + index)
+    assert n % prime == 0
     nsq, rng = n * n, random.Random(7)
     ctx = public_ctx(lib, n, bits)
+    assert uses_residues(lib, ctx, _cabi.OP_ENCRYPT, 3) == (index >= k)
     ms, rs = [rng.randrange(n) for _ in range(3)], [rng.randrange(1, n) for _ in range(3)]
     d_c = zeros(lib, (3, bits * 9 // 128))
     w, nb = ws(lib, ctx, _cabi.OP_ENCRYPT, 3)
@@ -66,13 +81,19 @@ def test_moduli_that_share_a_factor_with_the_channel_primes(emu, residue, index)
 
 
 @pytest.mark.parametrize("residue,index", [(3, 20), (1, 34)])
-def test_scalar_powers_modulo_multiples_of_channel_primes(emu, residue, index):  # noqa: F811
+def test_scalar_powers_modulo_multiples_of_channel_primes(emu, shim, residue, index):  # noqa: F811
     """The same for powers of large arrays by one scalar, at 1024 bits (35 primes a base); 32 elements are a large array
     on the one-unit emulated chip."""
     lib, bits, count = emu, 1024, 33
-    n = odd_multiple(channel_prime(residue, index), bits, residue)
+    prime = channel_primes(shim, shim.rns_primes_for(10), residue)[index]
+    n = odd_multiple(prime, bits, residue)
+    assert n % prime == 0
     nsq, rng = n * n, random.Random(8)
+    ctx = public_ctx(lib, n + 2, bits)
+    assert uses_residues(lib, ctx, _cabi.OP_SCALAR_MUL, count)  # the next odd modulus does
+    lib.haflo_ctx_destroy(ctx)
     ctx = public_ctx(lib, n, bits)
+    assert not uses_residues(lib, ctx, _cabi.OP_SCALAR_MUL, count)
     cs = [rng.randrange(nsq) for _ in range(count)]
     d_c, d_o = zeros(lib, (count, bits * 9 // 128)), zeros(lib, (count, bits * 9 // 128))
     assert lib.haflo_import_cipher(ctx, words(lib, cs, bits // 16).p, d_c.p, None, count, None) == 0
