@@ -42,7 +42,9 @@ struct RnsJob {
   const u32* tables;  // rns.hpp's device layout
   const u32* prog;    // null: `ins`; ENG_SQ, ENG_MUL_T, ENG_MUL_T_ST, ENG_STORE_T, ENG_LOAD_T only
   int len;
-  const u32* in;      // per element [x0: nl limbs][x1: nl limbs], limbs below 2^32
+  // Per element [x0: nl limbs][x1: nl limbs], lazy: limbs below 2^29 + 2^8. They go into the matrix product as they are, the top
+  // byte as a signed one, and the bounds of its sums (tests/test_rns_tables.py) take limbs of that size.
+  const u32* in;
   int nl;
   long long* out;     // per element [x0: columns][x1: columns] of weight 2^(29 l), signed
   u32* slots;         // window tables: 4 NR dwords per lane and entry

@@ -17,5 +17,11 @@ void rns_rows(int nr, int dst, uint32_t value, uint32_t p, int8_t* out) {
   for (int v = 0; v < 4; ++v) out[v] = (int8_t)m.bytes()[(size_t)tile * rns::tile_bytes(nr, 16) + (size_t)(4 * g + v) * (rns::full_blocks(nr) ? 16 : 8)];
 }
 uint32_t rns_times256(uint32_t v, uint32_t p) { return rns::times256(v, p); }
+// the limbs that go into the bases, of the modulus size that has `nr` registers
+int rns_limb_sources(int nr) {
+  for (int nl : {18, 36, 72, 144})
+    if (rns::regs_for(nl) == nr) return nl < rns::bias_slot(nr) ? nl : rns::bias_slot(nr);
+  return 0;
+}
 uint32_t rns_primes_for(int nr) { return (uint32_t)rns::primes_for(nr); }
 }

@@ -63,3 +63,15 @@ def test_sums_stay_exact(shim, nr):  # noqa: F811
     assert k * max(b0, b1) / min(both) < 128 * 127
     # the multiple of s added to every value outweighs what signed coefficients can take off
     assert k * max(s0, s1) / min(both) < 256
+    # The way in: the sources are limbs below 2^29 + 2^8, all that are stored but the one in the bias's slot. What it leaves
+    # in base B is no larger than what the products leave there.
+    limbs = {6: 18, 10: 36, 18: 71, 36: 143}[nr]
+    assert limbs == shim.rns_limb_sources(nr)
+    fed = limbs * (384 + (2 ** 29 + 2 ** 8) / 2 ** 24 + 1) + 1
+    assert fed * x_max < 2 ** 31
+    assert fed * y_max * 2 ** 32 + reduction < 2 ** 63
+    assert fed * y_max + half < min(b0, b1)
+    # the way out: rows of radix 256 and sums from zero, base B's bytes, alpha's two and the bias
+    fed = k * (384 + max(b0, b1) / 2 ** 24 + 1) + 256
+    assert fed * 128 < 2 ** 31
+    assert fed * 2 ** 29 < 2 ** 47  # what the pair engine reads as columns
