@@ -1042,6 +1042,20 @@ __global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsig
   }
 }
 
+// What the wavefronts of a block of k_rns_group share, whichever tiles they have.
+template <int NR, int HALVES>
+struct GroupShared {
+  static constexpr int kBlocks = (NR + 3) / 4;  // of 64 bytes, the last one partly empty
+  // Matrices stay in registers; those of 4096-bit moduli stream from L2, but for three of nine blocks: of the first one in
+  // registers, of the second one in LDS, where the constants are as well.
+  static constexpr bool kHeld = NR != 36;
+  static constexpr int kStay = kHeld ? 0 : 3;
+  Quad bytes[2][HALVES][kBlocks][WAVE];  // [sigma, rho][x0, x1][block][lane]
+  Quad sum[3][HALVES][16];               // alpha's sums over lane group 0 .. 3's slots, of the last, the present and the next rho
+  Acc resident[kStay][kHeld ? 1 : rns::tiles(NR)][WAVE];
+  Quad cst[kHeld ? 0 : 2][rns::slots(NR)];
+};
+
 // The same arithmetic with the slots of 16 elements spread over the W wavefronts of a block, TW tiles each, for
 // batches that would leave most of the chip idle with a wavefront per 16 elements, and for moduli whose matrices do not
 // fit the LDS. A wavefront keeps the residues of its own slots and multiplies and reduces them alone; what every
@@ -1066,22 +1080,16 @@ struct RnsGroup {
   static constexpr int kElements = FOLD ? 8 : 16;
   static constexpr int kTiles = rns::tiles(NR);
   static constexpr int kLimbTiles = rns::limb_tiles(NR);
-  static constexpr int kBlocks = (NR + 3) / 4;  // of 64 bytes, the last one partly empty
+  using Shared = GroupShared<NR, kHalves>;
+  static constexpr int kBlocks = Shared::kBlocks;
   static constexpr int kFull = rns::full_blocks(NR);
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
-  // Matrices stay in registers; those of 4096-bit moduli stream from L2, but for three of nine blocks: of the first one in
-  // registers, of the second one in LDS, where the constants are as well. kAhead of the others are on their way at any
-  // time, also across the barriers that the operands wait for; the resident ones are multiplied in between.
-  static constexpr bool kHeld = NR != 36;
-  static constexpr int kStay = kHeld ? 0 : 3, kAhead = 2, kStream = kBlocks - kStay;
+  // kAhead of the blocks that stream are on their way at any time, also across the barriers that the operands wait for; the
+  // resident ones are multiplied in between.
+  static constexpr bool kHeld = Shared::kHeld;
+  static constexpr int kStay = Shared::kStay, kAhead = 2, kStream = kBlocks - kStay;
   static_assert(kHeld || kStream % kAhead == 0, "a matrix begins where the other one ends");
   static_assert(TILES >= kLimbTiles, "every tile has a wavefront");
-  struct Shared {
-    Quad bytes[2][kHalves][kBlocks][WAVE];  // [sigma, rho][x0, x1][block][lane]
-    Quad sum[3][kHalves][16];               // alpha's sums over lane group 0 .. 3's slots, of the last, the present and the next rho
-    Acc resident[kStay][kHeld ? 1 : kTiles][WAVE];
-    Quad cst[kHeld ? 0 : 2][rns::slots(NR)];
-  };
   struct State {
     u32 a0[TW], a1[TW], b0[TW], b1[TW];
   };
@@ -1419,7 +1427,7 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group(R
 // in the kernel itself: as a function's argument the program's place in the launch's arguments would cost a copy of them
 #define RUN(G, FIRST_TILE)                                                                                          \
   do {                                                                                                              \
-    G e((typename G::Shared&)shared, j.tables, FIRST_TILE);                                                         \
+    G e(shared, j.tables, FIRST_TILE);                                                                              \
     for (size_t first = (size_t)block * G::kElements; first < count; first += (size_t)nblocks * G::kElements) {    \
       const unsigned left = (unsigned)std::min(count - first, (size_t)G::kElements);                               \
       typename G::State x;                                                                                          \
@@ -1447,8 +1455,9 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group(R
   } while (0)
   if (W1 == 0 || wave < W) {
     RUN(Main, wave * TW);
-  } else if constexpr (W1 > 0) {  // the same barriers
-    static_assert(sizeof(typename Main::Shared) == sizeof(typename Rest::Shared), "one layout");
+  } else if constexpr (W1 > 0) {
+    // As many barriers as above, though elsewhere in the code: their number follows from the program and the count of
+    // elements, which all wavefronts share, and a barrier counts wavefronts wherever they wait for it.
     RUN(Rest, W * TW + (wave - W) * TW1);
   }
 #undef RUN
