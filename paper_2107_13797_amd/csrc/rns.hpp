@@ -161,15 +161,14 @@ class Matrix {
   };
   // row v of slot `dst` for byte u of slot `src`
   void set_byte(int src, int u, int dst, int v, int8_t value) {
-    const int8_t b[4] = {value, value, value, value};
-    set_rows(src, u, dst, v, v + 1, b);
+    const Rows r = rows(src, dst);
+    if (r.first) r.first[v * r.width + u] = (uint8_t)value;
   }
   // the constant for byte u of slot `src` towards slot `dst`: modulo p, and (radix 256) as the integer it is
   void set(int src, int u, int dst, uint32_t value, const Weight& k) {
-    const int32_t e = (int32_t)centred(value, (uint32_t)k.p);
-    const int32_t y = (int32_t)(e * k.inverse + (e < 0 ? -0.5 : 0.5)), x = e - y * k.w;
-    const int8_t b[4] = {(int8_t)x, (int8_t)((x - (int8_t)x) / 256), (int8_t)y, (int8_t)((y - (int8_t)y) / 256)};
-    set_rows(src, u, dst, 0, 4, b);
+    int8_t b[4];
+    split(value, k, b);
+    store(rows(src, dst), u, b);
   }
   void set_integer(int src, int u, int dst, int64_t value) {
     int8_t b[4];
@@ -177,19 +176,42 @@ class Matrix {
       b[v] = (int8_t)(value & 0xFF);
       value = (value - b[v]) / 256;  // exact
     }
-    set_rows(src, u, dst, 0, 4, b);
+    store(rows(src, dst), u, b);
+  }
+  // the constants for all bytes of slot `src` modulo p: `value`, 256 times it and so on
+  void set_word(int src, int dst, uint32_t value, const Weight& k) {
+    const Rows r = rows(src, dst);
+    if (!r.first) return;
+    int8_t b[4];
+    for (int u = 0; u < 4; ++u, value = times256(value, (uint32_t)k.p)) {
+      split(value, k, b);
+      store(r, u, b);
+    }
   }
   const std::vector<uint8_t>& bytes() const { return bytes_; }
 
  private:
-  void set_rows(int src, int u, int dst, int from, int to, const int8_t* b) {
+  // the first of the rows of slot `dst`, where the bytes of slot `src` are, and the bytes from one to the next; null for a
+  // slot without a prime
+  struct Rows {
+    uint8_t* first;
+    int width;
+  };
+  Rows rows(int src, int dst) {
     const int tile = dst / 4, g = dst % 4, block = src / 16, c = src / 4 % 4, gs = src % 4;
-    if (tile >= tiles_n_) return;
-    const int rows = tile == tiles_n_ - 1 ? last_ : 16;
+    const int n = tile == tiles_n_ - 1 ? last_ : 16;
+    if (tile >= tiles_n_ || 4 * g >= n) return {nullptr, 0};
     const int width = block < full_blocks(nr_) ? 16 : 8;  // bytes per lane
-    uint8_t* p = &bytes_[(size_t)tile * tile_bytes(nr_, 16) + (size_t)block * rows * 64 + (size_t)gs * rows * width + 4 * c + u];
-    for (int v = from; v < to; ++v)
-      if (4 * g + v < rows) p[(size_t)(4 * g + v) * width] = (uint8_t)b[v];  // not for slots without a prime
+    return {&bytes_[(size_t)tile * tile_bytes(nr_, 16) + (size_t)block * n * 64 + (size_t)(gs * n + 4 * g) * width + 4 * c], width};
+  }
+  static void split(uint32_t value, const Weight& k, int8_t (&b)[4]) {
+    const int32_t e = (int32_t)centred(value, (uint32_t)k.p);
+    const int32_t y = (int32_t)(e * k.inverse + (e < 0 ? -0.5 : 0.5)), x = e - y * k.w;
+    b[0] = (int8_t)x, b[1] = (int8_t)((x - (int8_t)x) / 256), b[2] = (int8_t)y, b[3] = (int8_t)((y - (int8_t)y) / 256);
+  }
+  static void store(const Rows& r, int u, const int8_t (&b)[4]) {
+    if (r.first)
+      for (int v = 0; v < 4; ++v) r.first[v * r.width + u] = (uint8_t)b[v];
   }
   int nr_, tiles_n_, last_;
   std::vector<uint8_t> bytes_;
@@ -252,9 +274,8 @@ inline std::vector<uint32_t> build_tables(const Big& s, int nl, Big* m_a) {
     // sources hold value - kOmega; the bias gives it back, adds `extra` and takes off what the sums start from
     uint32_t sum = 0;
     for (const auto& e : src) {
-      uint32_t v = e.second;
-      sum = (uint32_t)(((uint64_t)sum + v) % p);
-      for (int u = 0; u < 4; ++u, v = times256(v, p)) m.set(e.first, u, dst, v, weight);
+      sum = (uint32_t)(((uint64_t)sum + e.second) % p);
+      m.set_word(e.first, dst, e.second, weight);
     }
     const uint64_t bv = (uint64_t)mulmod(sum, kOmega, p) + extra + (3ull * p - (uint32_t)kStart * 256u);
     m.set(bias, 0, dst, (uint32_t)(bv % p), weight);
