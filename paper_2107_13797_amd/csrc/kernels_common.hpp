@@ -528,7 +528,9 @@ __global__ __launch_bounds__(kBlockThreads, 4) void k_to_pairs(ModRef M, const u
   } while (0)
 // Whether `count` pairs take that geometry (while there are at most two wavefronts to a SIMD: beyond that groups of a few
 // lanes fill the chip better; 512-bit keys have no geometry with a pair on so many lanes), and the launch: `lanes` to a
-// group otherwise.
+// group otherwise. Two wavefronts to a SIMD by `count`: the forward pass counts four digit positions, as only the device knows
+// how many its exponents reach, and has three quarters of the wavefronts with 17-bit ones. The lines measured beside the
+// launches are lines of the count.
 inline haflo::LaunchShape launch_pairs(const haflo_ctx* ctx, const haflo::ModHost& mh, size_t count, int lanes,
                                        bool& wave) {
   wave = mh.nl != 18 && count <= (size_t)ctx->num_cu * 8;

@@ -994,7 +994,7 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
       // The squarings and the first levels are as many products as there are launches and positions, on few pairs: the
       // latency of a product bounds them, so a wavefront for each pair while launch_pairs allows. 1000 rows by 32 columns
       // 0.40 -> 0.35 ms at 1024 bits and 0.74 -> 0.65 at 2048, 300 by 32 at 4096 bits 1.57 -> 1.42, 16384 by 256 at 2048
-      // 3.51 -> 3.46 (256 columns are the last whose squarings fit: 64 rows by 256 | 300 at 1024 bits 0.78 -> 0.74 | 0.86).
+      // 3.60 -> 3.48 (256 columns are the last whose squarings fit: 64 rows by 256 | 300 at 1024 bits 0.78 -> 0.74 | 0.86).
       bool wave;
       {
         const LaunchShape sh = launch_pairs(ctx, mh, cols * 2 * kMaxPos, lanes, wave);

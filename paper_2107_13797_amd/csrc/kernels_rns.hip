@@ -658,7 +658,8 @@ __global__ __launch_bounds__(rns_waves_per_simd(kSets) * 256, rns_waves_per_simd
 // the 72 of an element set's state, and each phase of a product after the other, without the next one's work in between.
 // 65536 encryptions at a 2048-bit key take 48.5 ms with it (49.2 with the residues of before, kept below 2^31 by 54
 // instructions per prime instead of 47), 52.4 with k_rns's two sets of which every wavefront's 256 registers are full:
-// tables and spilled registers then wait for memory, two wavefronts per SIMD are too few to hide it.
+// tables and spilled registers then wait for memory, two wavefronts per SIMD are too few to hide it. k_rns's one set with three
+// wavefronts of 168 registers, which lies between, was not measured.
 // The residues of x0 and x1 of a lane in one base: full quads of each, and one quad with the last two of both.
 template <int NR>
 struct OneResidues {
@@ -1472,10 +1473,14 @@ constexpr int kRnsElementsPerCu = 256;  // in flight at once
 namespace {
 // The blocks of k_rns_group that are resident at once on a compute unit
 int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
-// Blocks of 8 elements, while each has a compute unit to itself. ms with 16 / 8 to a block: 2048 encryptions at a 1024-bit
-// key 1.06 / 0.87, at 2048 bits 3.58 / 2.42, at 4096 bits 21.8 / 20.6 (100 of them 20.8 / 18.2); 1024 decryptions at 1024 bits
-// 0.465 / 0.425, at 2048 bits 1.12 / 0.94, at 4096 bits 3.64 / 2.53.
-bool group_folds(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool pair) {
+// Blocks of 8 elements, while each has a compute unit to itself. ms with 16 / 8 to a block, up to the line: 2048 encryptions at
+// a 1024-bit key 1.06 / 0.87, at 2048 bits 3.58 / 2.42, at 4096 bits 21.8 / 20.6 (100 of them 20.8 / 18.2); 1024 decryptions at
+// 1024 bits 0.465 / 0.425, at 2048 bits 1.12 / 0.94, at 4096 bits 3.64 / 2.53. Beyond it, with two blocks of 8 and more to a
+// compute unit: encryptions at 1024 bits 1.06 / 1.67 (2049), 1.08 / 1.69 (4096), 2.10 / 2.51 (6144), at 2048 bits 3.57 / 4.80
+// (2049), 3.62 / 4.68 (4096), at 4096 bits 21.8 / 40.5 (2049); decryptions at 2048 bits 1.12 / 1.73 (1025), at 4096 bits 3.65 /
+// 4.95. The short products of 256-bit primes are no slower there while at most four blocks share a compute unit, and little
+// faster: 0.457 / 0.439 (1025 decryptions at a 1024-bit key), 0.460 / 0.457 (2048), 0.519 / 0.518 (3072), 0.52 / 0.58 (4096).
+bool group_folds(const haflo_ctx* ctx, size_t count, int jobs, bool pair) {
   return pair && (count + 7) / 8 * (size_t)jobs <= (size_t)ctx->num_cu;
 }
 size_t group_blocks(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool fold) {
@@ -1496,7 +1501,8 @@ bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
 // 6.1 ms for one, two and three of them (encryption at a 1024-bit key, 16384, 30000 and 40000 elements), with two sets 3.75
 // and 7.5 - 8.4. So one set where its wavefronts are one or three to a SIMD (40000 elements 6.1 / 7.5 ms; 30000, two to a
 // SIMD, 4.18 / 4.08; 65536, four, 9.3 / 8.4); the short products of 256-bit primes' pairs with two to a SIMD as well
-// (12288 decryptions at a 1024-bit key 1.05 / 1.13).
+// (12288 decryptions at a 1024-bit key 1.05 / 1.13). For pairs of 2048-bit halves one, which k_rns_one has; for single residues
+// of 2048 bits two, one was not measured.
 int rns_sets(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool pair) {
   if (nr == 18) return pair ? 1 : 2;
   const size_t per_simd = ((count + 15) / 16 * (size_t)jobs + 4 * ctx->num_cu - 1) / (4 * (size_t)ctx->num_cu);
@@ -1505,7 +1511,9 @@ int rns_sets(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool pair) {
 // Window tables of one modulus, each of 16 elements: one per block, or as many as the wavefronts that have elements hold
 size_t table_slots(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
   if (!use_group(ctx, nr, count, jobs)) return (count + 31) / 32 * 2;
-  if (group_folds(ctx, nr, count, jobs, true)) return (count + 15) / 16;  // two blocks of 8 each
+  // Few enough for blocks of 8: one for two such blocks, and for a block of 16 of the single form, which none of the limits of
+  // group_blocks cuts short at these counts. So the number does not depend on the form.
+  if (group_folds(ctx, count, jobs, true)) return (count + 15) / 16;
   return group_blocks(ctx, nr, count, jobs, false);
 }
 }  // namespace
@@ -1546,7 +1554,7 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
   size_t waves = (tiles * (size_t)jobs + ctx->num_cu - 1) / ctx->num_cu;
   waves = std::min(std::max(waves, (size_t)1), (size_t)(nr == 18 && pair ? 16 : 4 * rns_waves_per_simd(sets)));
   const size_t slots = table_slots(ctx, nr, count, jobs);
-  const bool fold = group && group_folds(ctx, nr, count, jobs, pair);
+  const bool fold = group && group_folds(ctx, count, jobs, pair);
   const unsigned blocks = (unsigned)(group ? group_blocks(ctx, nr, count, jobs, fold) : (tiles + waves - 1) / waves);
   RnsJob job[2];
   for (int i = 0; i < jobs; ++i) {
