@@ -37,7 +37,9 @@ PEAK_INT8_OPS_PER_S = 5.0e15  # dense
 # FETCH_SIZE / WRITE_SIZE, each scaled by what the counter reads for a 1 GiB device copy. The figure is
 # transcribed from the profile named here, not measured by this run, and is reported for that shape only.
 TRAFFIC_PROFILE = "profiles/k_rns_encrypt_2048bit_b65536_pmc.md"
-TRAFFIC_BYTES_PROFILED = {(2048, 65536): (26082571 + 5536988) * 1024}
+TRAFFIC_BYTES_PROFILED = {(2048, 65536): (26846852 + 8591674) * 1024}
+# the kernel of the powers in a batch that fills the chip, by key size
+POWER_KERNEL = {1024: "k_rns", 2048: "k_rns_one", 4096: "k_rns_group"}
 
 
 def montmul_mul32(limbs):
@@ -318,7 +320,8 @@ def main():
                                        "algorithmic": "%d Montgomery-product equivalents x (2*%d^2+%d) mul32 per "
                                                       "encryption" % (mm_o, limbs_o, limbs_o)},
         "stage_ms": {k: v / args.steps for k, v in stage_ms.items()},
-        "roofline": {"bound": "mfma", "kernel": "k_rns (powers modulo n^2 on pairs of residues modulo n, residue number system)",
+        "roofline": {"bound": "mfma", "kernel": "%s (powers modulo n^2 on pairs of residues modulo n, residue number system)" %
+                                                 POWER_KERNEL.get(bits, "k_rns"),
                      "achieved": matrix_ops / 1e12 if matrix_ops else None, "peak": PEAK_INT8_OPS_PER_S / 1e12, "unit": "TOP/s",
                      "op": "int8 matrix product",
                      "frac": matrix_ops / PEAK_INT8_OPS_PER_S if matrix_ops else None,
