@@ -1062,13 +1062,15 @@ struct GroupShared {
 // fit the LDS. A wavefront keeps the residues of its own slots and multiplies and reduces them alone; what every
 // wavefront needs of the others, the bytes of all residues, goes through LDS (16 bytes per lane and block of 64, as the
 // matrix product reads its operand), one barrier before each of the two matrix products of a modular product. The
-// matrices stay in registers where they fit (kHeld: 16 to 80 of them), else they stream from L2. What bounds it is
-// waiting: 52, 40 and 46 % of a wavefront's cycles (1024, 2048 and 4096 bits) go to barriers, LDS, memory and matrix results,
-// with vector issue at 38, 54 and 32 % and the matrix cores at 13, 31 and 46 % of the SIMDs' cycles, 1670, 2310 and 11200 a
-// product; at 4096 bits 420 KB of the 630 KB of both matrices come from L2 per product. Measured against the limb arithmetic on one
-// wavefront per integer, and against the version before blocks of 8 elements and weighted rows: 1024 encryptions at a
-// 1024-bit key 2.67, 1.06 -> 0.86 ms, 256 at 2048 bits 8.5, 3.9 -> 2.3, 3001 at 4096 bits 74.9, 23.5 -> 22.5; 3072 decryptions
-// at 1024 bits 1.33, 0.55 -> 0.51 ms, 64 at 4096 bits 8.63, 4.01 -> 2.41.
+// matrices stay in registers where they fit (kHeld: 16 to 80 of them), else they stream from L2. What bounds it is one
+// wavefront's chain from barrier to barrier and the SIMD with the most tiles (three of a 1024-bit modulus's nine): on blocks of 8
+// elements a product takes some 1450, 2100 and 9200 cycles of 2.4 GHz (1024, 2048 and 4096 bits); at 4096 bits 420 KB of
+// the 630 KB of both matrices come from L2 per product. Measured against the limb arithmetic on one wavefront per integer, the
+// version before blocks of 8 elements and weighted rows, and the one before the program's words were kept in registers, a
+// square's lanes of x1 took a second multiply-add instead of a 64-bit factor, and alpha's sums were cleared off the first SIMD:
+// 1024 encryptions at a 1024-bit key 2.67, 1.06, 0.85 -> 0.73 ms, 256 at 2048 bits 8.5, 3.9, 2.30 -> 2.08, 16 at 4096 bits (the
+// last two) 18.2 -> 17.9; 3072 decryptions at 1024 bits 1.33, 0.55, 0.51 -> 0.47 ms, 100 at 2048 bits (the last two) 0.89 ->
+// 0.77, 64 at 4096 bits 8.63, 4.01, 2.38 -> 2.14.
 //
 // FOLD: 8 elements to a block, x0 in columns 0 to 7 of the matrix products and x1 in columns 8 to 15, for batches that do
 // not fill the chip with blocks of 16: half the matrix instructions and operand reads per product. A lane then has one half
@@ -1081,6 +1083,7 @@ struct RnsGroup {
   static constexpr int kElements = FOLD ? 8 : 16;
   static constexpr int kTiles = rns::tiles(NR);
   static constexpr int kLimbTiles = rns::limb_tiles(NR);
+  static constexpr bool kClearLate = NR <= 10;  // where alpha's old sums are cleared, see publish()
   using Shared = GroupShared<NR, kHalves>;
   static constexpr int kBlocks = Shared::kBlocks;
   static constexpr int kFull = rns::full_blocks(NR);
@@ -1199,10 +1202,9 @@ struct RnsGroup {
     asm volatile("" : "+v"(l));  // or the addresses of all fragments are kept in registers from one product to the next
     u32 alpha[kHalves];
     if (ALPHA) {
-      const int now = (turn + 2) % 3;  // of the last publish()
 #pragma unroll
       for (int x = 0; x < kHalves; ++x) {
-        const Quad q = sh.sum[now][x][lane & 15];
+        const Quad q = sh.sum[turn == 0 ? 2 : turn - 1][x][lane & 15];
         alpha[x] = alpha_bytes(q[0] + q[1] + q[2] + q[3] + (1u << 13) + (u32)rns::primes_for(NR) / 2);
       }
     }
@@ -1264,17 +1266,22 @@ struct RnsGroup {
     atomicAdd(s, s0);
     if (kBoth) atomicAdd(s + 64, s1);
     __syncthreads();
-    // the sums of the publish() before this one were last read before this barrier and are next added to after the
-    // barrier that follows it
-    const int clear = (turn + 2) % 3;
-    if (threadIdx.x < 64)
-      for (int i = (int)threadIdx.x; i < kHalves * 64; i += 64) ((u32*)&sh.sum[clear][0][0])[i] = 0;
-    turn = (turn + 1) % 3;
+    turn = turn == 2 ? 0 : turn + 1;
+    // At once, or after the matrix product: 1024 encryptions at a 1024-bit key 785 / 771 us, 256 at 2048 bits 2142 / 2198
+    if (!kClearLate) clear_sums();
+  }
+  // The sums of the publish() before the last one, which were last read before its barrier, are next added to after the
+  // barrier of the one that follows: called between the two.
+  __device__ __forceinline__ void clear_sums() const {
+    if (wave == 3)  // of a SIMD that has fewer tiles than the first one
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x) ((u32*)&sh.sum[turn == 2 ? 0 : turn + 1][x][0])[lane] = 0;
   }
   // base A from what publish() left
   __device__ __forceinline__ void extend_to_a(State& x) {
     Acc r[TW][kHalves];
     products<1, true>(r, 1, tables + rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, 1), start);
+    if (kClearLate) clear_sums();
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
       const Quad k = cst(0, i);
@@ -1286,7 +1293,15 @@ struct RnsGroup {
   template <bool SQ>
   __device__ __forceinline__ void residues(u32& r0, u32& r1, u32 u0, u32 u1, u32 v0, u32 v1, u32 p, u32 pinv, u32 e) const {
     if constexpr (FOLD) {
-      const s64 t = smad(of_first(u0), v0, smad(u0 & second, of_first(v0), 0));
+      s64 t;
+      if constexpr (SQ) {  // x1's lanes twice, hidden from the compiler, which would multiply a wider sum of factors
+        const u32 first = of_first(u0);
+        t = smad(first, u0, 0);
+        asm("" : "+v"(t));
+        t = smad(first, u0 & second, t);
+      } else {
+        t = smad(of_first(u0), v0, smad(u0 & second, of_first(v0), 0));
+      }
       r0 = reduce(smad(from_first(reduce(t, p, pinv)), e, t), p, pinv);
       r1 = 0;
     } else {
@@ -1366,6 +1381,7 @@ struct RnsGroup {
     publish(x);
     Acc r[TW][kHalves];
     products<2, true>(r, 1, tables + rns::lds_bytes(NR) + rns::in_matrix_bytes(NR), kLimbTiles, 16, Acc{0, 0, 0, 0});
+    if (kClearLate) clear_sums();
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
       const unsigned e = (unsigned)(lane & (kElements - 1)), half = FOLD ? (unsigned)lane >> 3 & 1 : 0;
@@ -1410,6 +1426,23 @@ struct RnsGroup {
   }
 };
 
+// Instruction pc of the program `prog` of `len`, asked for one after the other. A wavefront keeps 64 of them at a time in the
+// lanes of `words`: read from memory between two products, one costs a wavefront that waits for little else 2 to 5 % of a
+// product. (4096-bit moduli, whose products are long and whose wavefronts have no register left, read them so.) A macro: as a
+// function's argument the program's place in the launch's arguments would cost a copy of them.
+#define INSTRUCTION(ins, prog, len, pc, words)                                  \
+  do {                                                                          \
+    if constexpr (NR == 36) {                                                   \
+      ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);                 \
+    } else {                                                                    \
+      if ((pc & (WAVE - 1)) == 0) {                                             \
+        const int at = pc + (int)(threadIdx.x & (WAVE - 1));                    \
+        words = prog[at < len ? at : len - 1];                                  \
+      }                                                                         \
+      ins = (u32)__builtin_amdgcn_readlane((int)words, pc & (WAVE - 1));        \
+    }                                                                           \
+  } while (0)
+
 // Every block runs the program on 16 (FOLD: 8) elements at a time. The first `split` blocks run j0, the others j1.
 // W wavefronts with TW tiles each, then W1 with TW1: the tiles over the four SIMDs as evenly as they go.
 template <int NR, int TW, int W, int TW1, int W1, bool PAIR, bool FOLD>
@@ -1433,11 +1466,14 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group(R
       const unsigned left = (unsigned)std::min(count - first, (size_t)G::kElements);                               \
       typename G::State x;                                                                                          \
       e.load(x, j.in + first * (size_t)(2 * j.nl), left, j.nl);                                                     \
+      [[maybe_unused]] u32 words = 0;                                                                               \
       for (int pc = 0; pc < len;) {                                                                                 \
-        u32 ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);                                               \
+        u32 ins;                                                                                                    \
+        INSTRUCTION(ins, prog, len, pc, words);                                                                     \
         _Pragma("unroll 1") while (ins == ENG_SQ) {                                                                 \
           e.template multiply<true>(x, nullptr);                                                                    \
-          ins = ++pc < len ? (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]) : ~0u;                              \
+          ins = ~0u;                                                                                                \
+          if (++pc < len) INSTRUCTION(ins, prog, len, pc, words);                                                   \
         }                                                                                                           \
         if (pc++ >= len) break;                                                                                     \
         const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;                                         \
