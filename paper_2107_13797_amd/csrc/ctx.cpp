@@ -389,6 +389,7 @@ static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
   const MontHost mh(s2);
   const Big rm = mh.to_mont(R);
   Big c = Big::mod(ms.rns_radix, s2);
+  if (stored) special.push_back({kConstMOne, c});
   for (int i = kConstM1; i <= kConstM4; ++i) {
     c = mh.mul(c, rm);
     special.push_back({i, c});
@@ -413,7 +414,9 @@ static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
     const Big rn_inv_m = mh.to_mont(rn_inv);
     special.push_back({kConstMLo, mh.mul(special_of(special, kConstM1), rn_inv_m)});
     special.push_back({kConstMHi, mh.mul(special_of(special, kConstM2), rn_inv_m)});
-    special.push_back({kConstMStored, mh.mul(mh.from_mont(inv), mh.to_mont(r_inv))});
+    const Big r_inv_m = mh.to_mont(r_inv), to_stored = mh.mul(mh.from_mont(inv), r_inv_m);
+    special.push_back({kConstMStored, to_stored});
+    special.push_back({kConstMPair, mh.mul(to_stored, r_inv_m)});  // as R_N = R^2
   }
 }
 static void put_prog(DevProg& p, std::vector<uint32_t> ins, int table_entries, Uploader& up) {

@@ -71,7 +71,8 @@ enum {
   kConstM1 = 7, kConstM2 = 8, kConstM3 = 9, kConstM4 = 10, kConstMOut = 11,
   // the same for stored ciphertexts: their lower and upper halves into the form, a power out of it
   kConstMLo = 12, kConstMHi = 13, kConstMStored = 14,
-  kNumConst = 15
+  kConstMOne = 15, kConstMPair = 16,  // one in that form; out of it to the pair engine's own, R^2 / M_A
+  kNumConst = 17
 };
 inline uint32_t eng_ins(uint32_t op, uint32_t a = 0, uint32_t b = 0) { return op | (a << 8) | (b << 20); }
 
@@ -227,6 +228,29 @@ RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int
 int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, const haflo_ctx* ctx, uint32_t* ws,
               const RnsBuffers& b, size_t count, int entries, bool pair, hipStream_t st);
 
+// Products of lists of pairs modulo m^2 in the residue form (kernels_rns.hip; halves of 2048 bits). An element is
+// rns_item_words() words. Chain i is {place of its product, first item, items, unused}; item k of it is element
+// first + k, or index[first + k].
+size_t rns_item_words(const ModHost& m);
+// Pairs of lazy limbs (times M_A) at `in` into the form, element i to place[i] (null: i), and one as the element after the
+// last. There are `count` of them, or *total (a device word, at most `count`) unless that is null.
+int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, const uint32_t* total, size_t count,
+              const uint32_t* place, uint32_t* items, hipStream_t st);
+enum { kChainsTotal = 0, kChainsColumns = 1, kChainsControl = 2 };  // device words: number of chains; whether products leave the form
+struct RnsChains {
+  const uint32_t* tables;   // set by rns_chains()
+  const uint32_t* items;
+  const uint32_t* one;      // the element that is one in the form
+  const uint32_t* chains;   // in the order in which they are handed out; of similar length side by side
+  const uint32_t* index;    // or null
+  const uint32_t* control;
+  uint32_t* next;           // a counter, zero at launch
+  uint32_t* out;            // elements, or
+  long long* columns;       // 2 rns_columns() signed columns of weight 2^(29 l)
+};
+// `bound`: no fewer than the chains that the device may find
+int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound, hipStream_t st);
+
 // X^T [[d]] by the bucket method (kernels_buckets.hip). Workspace layout in 32-bit words.
 struct XtdBucketPlan {
   int rounds;
@@ -234,13 +258,16 @@ struct XtdBucketPlan {
   size_t keys, scan_blocks;
   size_t off_cnt, off_totals, off_offs, off_sorted, off_arena[2], off_G, off_AT, off_R, off_pairs, off_order, total;
   bool pairs;  // the products run on pairs of residues modulo n
+  bool residues;  // the rounds' in the residue form
+  size_t off_items, off_columns, off_chains, off_control, off_last;
 };
 bool xtd_buckets_fit(size_t rows, size_t cols);
-XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols);
+bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols);  // if the workspace has room for it
+XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols, bool residues);
 // d_P[j][sign] = product of c_i^|x_ij| over the entries of column j with that sign (lazy Montgomery form).
 // ws: xtd_bucket_plan(...).total words.
 int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, size_t rows, size_t cols,
-                uint32_t* ws, uint32_t* d_P, hipStream_t st);
+                bool residues, uint32_t* ws, uint32_t* d_P, hipStream_t st);
 
 // Segmented summation through the bucket reduction rounds (kernels_buckets.hip). Workspace layout in 32-bit words.
 struct SegSumPlan {

@@ -286,6 +286,53 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_order(const u32* __restric
   }
 }
 
+// The chunks of a round as lists for the residue engine's chains (rns_chains), in the order of `order` where there is one:
+// chunk q's product goes to place q. The last round's products leave the residue form.
+__global__ __launch_bounds__(kBlockThreads) void k_bk_chains(const u32* __restrict__ cnt, const u32* __restrict__ off,
+                                                             const u32* __restrict__ choff, size_t K, int round, int cb,
+                                                             const u32* __restrict__ stats,
+                                                             const u32* __restrict__ order, uint4* __restrict__ chains,
+                                                             u32* __restrict__ control) {
+  const int run = rounds_run(stats[kStatMaxCount], cb);
+  const u32 total = round < run ? choff[K] : 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    control[kChainsTotal] = total;
+    control[kChainsColumns] = round == run - 1;
+  }
+  for (u32 at = blockIdx.x * blockDim.x + threadIdx.x; at < total; at += gridDim.x * blockDim.x) {
+    const u32 q = order ? order[at] : at;
+    const ChunkAt ch = chunk_at(q, true, cnt, choff, K, round, cb);
+    chains[at] = make_uint4(q, off[ch.key] + ch.begin, ch.len, 0u);
+  }
+}
+
+// The items that the last round left, from the residue engine's columns into the pair form: times `leave` = R^2 / M_A
+template <int LPT, int T>
+__global__ __launch_bounds__(kBlockThreads, 4) void k_bk_leave(ModRef M, const u32* __restrict__ leave,
+                                                               const long long* __restrict__ columns, int stride,
+                                                               const u32* __restrict__ offs, size_t K, int cb,
+                                                               const u32* __restrict__ stats, u32* __restrict__ out) {
+  constexpr int NLH = LPT * T;
+  Grp<T> g;
+  Batch<T> bt;
+  ModRegs<LPT> mod;
+  load_mod<LPT, T>(mod, M, g);
+  const size_t count = offs[(size_t)rounds_run(stats[kStatMaxCount], cb) * (K + 1) + K];
+  for (size_t base = bt.first(); base < count; base += bt.stride()) {
+    const size_t it = base + bt.gib;
+    const bool active = it < count;
+    const long long* src = columns + (active ? it : 0) * (size_t)(2 * stride);
+    u32 x0[LPT], x1[LPT];
+    load_columns<LPT, T>(x0, src, g);
+    load_columns<LPT, T>(x1, src + stride, g);
+    pairmul_mem<LPT, T>(x0, x1, x0, x1, leave, mod.n, mod.n0inv, g);
+    if (active) {
+      store_limbs<LPT, T>(out + it * (size_t)(2 * NLH), x0, g);
+      store_limbs<LPT, T>(out + it * (size_t)(2 * NLH) + NLH, x1, g);
+    }
+  }
+}
+
 // Reduction round `round`. Key k owns items [off[k], off[k] + items_at(cnt[k], round, cb)) and is cut into
 // choff[k+1] - choff[k] chunks of near-equal size; chunk q's product goes to out[q]. FIRST: item t is the
 // ciphertext of row sorted[t]; otherwise item t is in[t]. PAIR: the items are pairs modulo M (see Elem);
@@ -704,11 +751,21 @@ bool xtd_buckets_fit(size_t rows, size_t cols) {
   return rows < (1ull << 32) && cols != 0 && cols <= 1024 && rows * kMaxPos <= 0xFFFFFFFFull / cols;
 }
 
-XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
+// The rounds in the residue form, whose products on full compute units take a third of the time (the first round of 65536 by
+// 32 entries 4.2 -> 1.35 ms) but whose chains are slow on few, against a way in and out of some 0.2 ms. Whole calls on limbs /
+// in residues, ms: 5000 by 7 0.88 / 0.91, 4096 by 16 0.97 / 0.98, 4096 by 32 1.15 / 1.13, 16384 by 9 1.13 / 1.00, 65536 by 4
+// 1.54 / 1.25, 65536 by 32 5.33 / 2.77.
+bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  return ctx->Nh.d_rns && ctx->Nh.nl == 72 && rows * cols >= (size_t)ctx->num_cu * 512;
+}
+
+XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols, bool residues) {
   XtdBucketPlan p;
   const size_t nl = (size_t)ctx->N.nl;
   p.pairs = haflo_has_pair_geometry(ctx->Nh);
+  p.residues = residues;
   p.chunk_bits = chunk_bits(ctx, rows * cols * 2, p.pairs ? 2 * ctx->Nh.t : ctx->N.t);  // two digits per entry as a rule
+  const size_t item = residues ? rns_item_words(ctx->Nh) : nl;  // words of what the rounds multiply
   p.rounds = rounds_for(rows, p.chunk_bits);
   p.keys = cols * kMaxPos * 2 * kMags;
   p.scan_blocks = (p.keys + kScanKeys - 1) / kScanKeys;
@@ -724,8 +781,13 @@ XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.off_offs = w;    w += (size_t)(p.rounds + 1) * (p.keys + 1);
   p.off_sorted = w;  w += terms;
   w = (w + 63) & ~(size_t)63;
-  p.off_arena[0] = w; w += p1 * nl;
-  p.off_arena[1] = w; w += p2 * nl;
+  p.off_arena[0] = w; w += p1 * item;
+  p.off_arena[1] = w; w += p2 * item;
+  p.off_items = w;    w += residues ? (rows + 1) * item : 0;  // the ciphertexts and one
+  p.off_columns = w;  w += residues ? p.keys * 4 * (size_t)rns_columns(ctx->Nh) : 0;
+  p.off_chains = w;   w += residues ? p1 * 4 : 0;
+  p.off_control = w;  w += residues ? 64 : 0;
+  p.off_last = w;     w += residues ? p.keys * nl : 0;  // what the rounds leave, in the pair form
   p.off_G = w;       w += combos * kSubProducts * nl;
   p.off_AT = w;      w += combos * kSegs * 2 * nl;
   p.off_R = w;       w += combos * 2 * nl;
@@ -736,8 +798,8 @@ XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
 }
 
 int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, size_t rows, size_t cols,
-                uint32_t* ws, uint32_t* d_P, hipStream_t st) {
-  const XtdBucketPlan p = xtd_bucket_plan(ctx, rows, cols);
+                bool residues, uint32_t* ws, uint32_t* d_P, hipStream_t st) {
+  const XtdBucketPlan p = xtd_bucket_plan(ctx, rows, cols, residues);
   const int cb = p.chunk_bits;
   if (p.rounds + 1 > kMaxComp || kStatNextChunk + p.rounds > kStatWords) return HAFLO_EINVAL;
   const size_t K = p.keys;
@@ -775,13 +837,20 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
   u32* cp = ws + p.off_pairs;
   {
     const LaunchShape sh = launch_shape(ctx, rows, lanes, 8);
-#define CALL(LPT, T)                                                                                         \
-  HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstR4 * 2 * mh.nl),    \
-               (const u32*)(mh.d_pairs + (size_t)kConstR5 * 2 * mh.nl), d_c, rows, cp)
+    const u32* lo = mh.d_pairs + (size_t)(residues ? kConstMLo : kConstR4) * 2 * mh.nl;
+    const u32* hi = mh.d_pairs + (size_t)(residues ? kConstMHi : kConstR5) * 2 * mh.nl;
+#define CALL(LPT, T) HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, lo, hi, d_c, rows, cp)
     HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL
   }
   const u32* items = cp;
+  const u32 *last0 = ws + p.off_arena[0], *last1 = ws + p.off_arena[1];  // what the rounds leave, after an odd and an even number
+  if (residues) {
+    int rc = rns_enter(ctx, mh, cp, nullptr, rows, nullptr, ws + p.off_items, st);
+    if (rc != HAFLO_OK) return rc;
+    items = ws + p.off_items;
+    last0 = last1 = ws + p.off_last;
+  }
   for (int r = 0; r < p.rounds; ++r) {
     // upper bound of the chunks of this round: one lane group each, capped by the grid-stride loop
     size_t bound = rows * cols * kMaxPos;
@@ -800,6 +869,24 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
       HAFLO_LAUNCH((k_bk_order<true>), osh, st, (const u32*)cnt, (const u32*)offs(r + 1), K, r, cb, stats, order);
       ord = order;
     }
+    if (residues) {
+      u32* control = ws + p.off_control + r * kChainsControl;
+      const LaunchShape csh = launch_shape(ctx, bound, 1, 8);
+      HAFLO_LAUNCH(k_bk_chains, csh, st, (const u32*)cnt, (const u32*)offs(r), (const u32*)offs(r + 1), K, r, cb,
+                   (const u32*)stats, ord, (uint4*)(ws + p.off_chains), control);
+      RnsChains j = {};
+      j.items = items;
+      j.one = ws + p.off_items + rows * rns_item_words(mh);
+      j.chains = ws + p.off_chains;
+      j.index = srt;
+      j.control = control;
+      j.next = stats + kStatNextChunk + r;
+      j.out = out;
+      j.columns = (long long*)(ws + p.off_columns);
+      if (int rc = rns_chains(ctx, mh, j, bound, st)) return rc;
+      items = out;
+      continue;
+    }
 #define CALL_ROUND(LPT, T, FIRST)                                                                        \
   HAFLO_LAUNCH((k_bk_round<LPT, T, FIRST, true>), sh, st, M, one, items, srt, (const u32*)cnt,          \
                (const u32*)offs(r), (const u32*)offs(r + 1), K, r, cb, stats, ord, out)
@@ -808,6 +895,15 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
 #undef CALL
 #undef CALL_ROUND
     items = out;
+  }
+  if (residues) {
+    const LaunchShape sh = launch_shape(ctx, K, lanes, 8);
+#define CALL(LPT, T)                                                                                               \
+  HAFLO_LAUNCH((k_bk_leave<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstMPair * 2 * mh.nl),       \
+               (const long long*)(ws + p.off_columns), rns_columns(mh), (const u32*)offs(0), K, cb, (const u32*)stats, \
+               ws + p.off_last)
+    HAFLO_DISPATCH_PAIRS(mh, CALL);
+#undef CALL
   }
   const size_t combos = cols * kMaxPos * 2;
   u32* G = ws + p.off_G;
@@ -819,8 +915,7 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
     const bool split = combos * kSubProducts * (size_t)lanes < (size_t)ctx->num_cu * 16 * WAVE;
     const LaunchShape sh = launch_shape(ctx, combos * kSubProducts * (split ? 4 : 1), lanes, 8);
 #define CALL_SUB(LPT, T, SPLIT)                                                                         \
-  HAFLO_LAUNCH((k_bk_sub<LPT, T, true, SPLIT>), sh, st, M, one, (const u32*)(ws + p.off_arena[0]),     \
-               (const u32*)(ws + p.off_arena[1]), (const u32*)cnt, (const u32*)offs(0), K, cb, (const u32*)stats, combos, G)
+  HAFLO_LAUNCH((k_bk_sub<LPT, T, true, SPLIT>), sh, st, M, one, last0, last1, (const u32*)cnt, (const u32*)offs(0), K, cb, (const u32*)stats, combos, G)
 #define CALL(LPT, T) do { if (split) CALL_SUB(LPT, T, 4); else CALL_SUB(LPT, T, 1); } while (0)
     HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL

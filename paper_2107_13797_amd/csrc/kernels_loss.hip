@@ -107,8 +107,8 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 struct LossPlan {
   size_t off_k, off_partial, off_plain, off_t1, off_t2, off_t3, off_ws, total;
 };
-// `encrypt`: the workspace of the one encryption, what it asks for or what it can do with
-LossPlan loss_plan(const haflo_ctx* ctx, size_t count, size_t encrypt) {
+// `matvec`, `encrypt`: the workspace of the matvec and of the one encryption, what they ask for or what they can do with
+LossPlan loss_plan(const haflo_ctx* ctx, size_t count, size_t matvec, size_t encrypt) {
   LossPlan p;
   const size_t cipher = align256((size_t)ctx->N.nl * 4);
   size_t b = 0;
@@ -119,7 +119,7 @@ LossPlan loss_plan(const haflo_ctx* ctx, size_t count, size_t encrypt) {
   p.off_t2 = b;       b += cipher;
   p.off_t3 = b;       b += cipher;
   p.off_ws = b;
-  size_t w = haflo_workspace_bytes(ctx, HAFLO_OP_MATVEC_XT_D, count, 1);
+  size_t w = matvec;
   if (encrypt > w) w = encrypt;
   const size_t e = haflo_workspace_bytes(ctx, HAFLO_OP_ENCRYPT_OBFUSCATOR, 1, 0);
   if (e > w) w = e;
@@ -130,8 +130,12 @@ LossPlan loss_plan(const haflo_ctx* ctx, size_t count, size_t encrypt) {
 }  // namespace
 
 namespace haflo {
-size_t ws_taylor_loss(const haflo_ctx* ctx, size_t count) { return loss_plan(ctx, count, ws_encrypt(ctx, 1)).total; }
-size_t ws_taylor_loss_min(const haflo_ctx* ctx, size_t count) { return loss_plan(ctx, count, ws_encrypt_min(ctx, 1)).total; }
+size_t ws_taylor_loss(const haflo_ctx* ctx, size_t count) {
+  return loss_plan(ctx, count, haflo_workspace_bytes(ctx, HAFLO_OP_MATVEC_XT_D, count, 1), ws_encrypt(ctx, 1)).total;
+}
+size_t ws_taylor_loss_min(const haflo_ctx* ctx, size_t count) {
+  return loss_plan(ctx, count, haflo_workspace_bytes_least(ctx, HAFLO_OP_MATVEC_XT_D, count, 1), ws_encrypt_min(ctx, 1)).total;
+}
 }  // namespace haflo
 
 extern "C" {
@@ -142,7 +146,7 @@ int haflo_taylor_loss(const haflo_ctx* ctx, const void* d_c_u, const void* d_c_u
   if (!ctx || scale_bits > 27 || !d_out || (count && (!d_c_u || !d_c_u2 || !d_u_guest || !d_label)))
     return HAFLO_EINVAL;
   if (count > 0xFFFFFFFFull) return HAFLO_EINVAL;
-  const LossPlan p = loss_plan(ctx, count, ws_encrypt_min(ctx, 1));
+  const LossPlan p = loss_plan(ctx, count, haflo_workspace_bytes_least(ctx, HAFLO_OP_MATVEC_XT_D, count, 1), ws_encrypt_min(ctx, 1));
   if (!d_workspace || workspace_bytes < p.total) return HAFLO_EINVAL;
   const size_t ws_bytes = workspace_bytes - p.off_ws;
   hipStream_t st = (hipStream_t)stream;

@@ -782,11 +782,11 @@ bool use_buckets(const haflo_ctx* ctx, size_t rows, size_t cols) {
 struct XtdBucketLayout {
   size_t off_P, off_ws, total;  // in u32 words; word 0 holds the largest |x|
 };
-XtdBucketLayout xtd_bucket_layout(const haflo_ctx* ctx, size_t rows, size_t cols) {
+XtdBucketLayout xtd_bucket_layout(const haflo_ctx* ctx, size_t rows, size_t cols, bool residues) {
   XtdBucketLayout l;
   l.off_P = 64;
   l.off_ws = (l.off_P + cols * 2 * (size_t)ctx->N.nl + 63) & ~(size_t)63;
-  l.total = l.off_ws + xtd_bucket_plan(ctx, rows, cols).total;
+  l.total = l.off_ws + xtd_bucket_plan(ctx, rows, cols, residues).total;
   return l;
 }
 
@@ -817,6 +817,16 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.seg_shift = xw_seg_shift(ctx, rows, cols);
   p.total = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * nl : 0);
   return p;
+}
+
+// X^T [[d]]: what a call can do with, and what it asks for where the residue engine serves it (else 0)
+size_t ws_xtd_min(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  if (!cols) return 0;
+  return (use_buckets(ctx, rows, cols) ? xtd_bucket_layout(ctx, rows, cols, false).total : xtd_plan(ctx, rows, cols).total) * 4;
+}
+size_t ws_xtd_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  if (!cols || !use_buckets(ctx, rows, cols) || !xtd_buckets_in_residues(ctx, rows, cols)) return 0;
+  return xtd_bucket_layout(ctx, rows, cols, true).total * 4 + 256;  // its start is aligned to 256 bytes
 }
 
 int sum_blocks(const haflo_ctx* ctx, size_t count) {
@@ -894,8 +904,7 @@ size_t haflo_workspace_bytes(const haflo_ctx* ctx, int op, size_t rows, size_t c
       return ((rows * (size_t)ctx->lp * 4 + 255) & ~(size_t)255) + ((rows * (size_t)ctx->N.nl * 4 + 255) & ~(size_t)255) +
              ws_encrypt(ctx, rows);
     case HAFLO_OP_MATVEC_XT_D:
-      if (!cols) return 0;
-      return (use_buckets(ctx, rows, cols) ? xtd_bucket_layout(ctx, rows, cols).total : xtd_plan(ctx, rows, cols).total) * 4;
+      return std::max(ws_xtd_min(ctx, rows, cols), ws_xtd_residues(ctx, rows, cols));
     case HAFLO_OP_MATVEC_X_W: return xw_plan(ctx, rows, cols).total * 4;
     case HAFLO_OP_SUM_SEGMENTS:
       if (rows >= (1ull << 32) || cols >= (1ull << 24)) return (size_t)-1;
@@ -911,6 +920,7 @@ size_t haflo_workspace_bytes_least(const haflo_ctx* ctx, int op, size_t rows, si
     case HAFLO_OP_ENCRYPT: return ws_encrypt_min(ctx, rows);
     case HAFLO_OP_DECRYPT: return ws_decrypt_min(ctx, rows);
     case HAFLO_OP_SCALAR_MUL: return ws_scalar_mul_min(ctx, rows);
+    case HAFLO_OP_MATVEC_XT_D: return ws_xtd_min(ctx, rows, cols);
     case HAFLO_OP_FORE_GRADIENT: return asked - ws_encrypt(ctx, rows) + ws_encrypt_min(ctx, rows);
     case HAFLO_OP_TAYLOR_LOSS: return ws_taylor_loss_min(ctx, rows);
     default: return asked;
@@ -926,7 +936,7 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
   if (!d_out || (nin && (!d_c || !d_X))) return HAFLO_EINVAL;
   const ModHost& m = ctx->N;
   hipStream_t st = (hipStream_t)stream;
-  const size_t need = haflo_workspace_bytes(ctx, orientation == 0 ? HAFLO_OP_MATVEC_XT_D : HAFLO_OP_MATVEC_X_W, rows, cols);
+  const size_t need = haflo_workspace_bytes_least(ctx, orientation == 0 ? HAFLO_OP_MATVEC_XT_D : HAFLO_OP_MATVEC_X_W, rows, cols);
   if (!d_workspace || workspace_bytes < need) return HAFLO_EINVAL;
   u32* ws = (u32*)d_workspace;
   const bool buckets = orientation == 0 && use_buckets(ctx, rows, cols);
@@ -935,9 +945,12 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
   if (rc != HAFLO_OK) return rc;
   const int nbatch = inverse_batches(ctx);
   if (buckets) {
-    const XtdBucketLayout l = xtd_bucket_layout(ctx, rows, cols);
+    const size_t asked = ws_xtd_residues(ctx, rows, cols);
+    const bool residues = asked != 0 && workspace_bytes >= asked;
+    const XtdBucketLayout l = xtd_bucket_layout(ctx, rows, cols, residues);
+    if (residues) ws = (u32*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     u32* P = ws + l.off_P;
-    rc = xtd_buckets(ctx, (const u32*)d_c, d_X, rows, cols, ws + l.off_ws, P, st);
+    rc = xtd_buckets(ctx, (const u32*)d_c, d_X, rows, cols, residues, ws + l.off_ws, P, st);
     if (rc != HAFLO_OK) return rc;
     const LaunchShape sh = latency_shape(ctx, cols, m);
 #define CALL(LPT, T) HAFLO_LAUNCH((k_xtd_finish<LPT, T>), sh, st, m.ref(), ctx->Nw.ref(), cols, (const u32*)P, (u32*)d_out, nbatch)

@@ -802,23 +802,23 @@ struct OneEngine {
 
   // The residue products of one base of a square (y null) or of a product with the table entry y: bytes of sigma in
   // base A (BASE 0), z and w in base B. The entry's quads are on their way one step ahead.
-  template <int BASE, bool SQ>
+  template <int BASE, bool SQ, int STEP>
   __device__ __forceinline__ void base_products(OneResidues<NR>& x, const u32* y) {
     constexpr int kQuads = NR / 4 + 1;
-    const Quad* p = (const Quad*)(y + BASE * kArray) + lane;
+    const Quad* p = quads<STEP>(y, BASE);
     x.forget();
     Quad n0 = {}, n1 = {};
     if (!SQ) {
       n0 = p[0];
-      n1 = p[WAVE];
+      n1 = p[STEP];
     }
 #pragma unroll
     for (int q = 0; q < kQuads; ++q) {
       const Quad y0 = n0, y1 = n1;
       forget();
       if (!SQ && q + 1 < kQuads) {
-        n0 = p[2 * (q + 1) * WAVE];
-        if (q + 2 < kQuads) n1 = p[(2 * (q + 1) + 1) * WAVE];
+        n0 = p[2 * (q + 1) * STEP];
+        if (q + 2 < kQuads) n1 = p[(2 * (q + 1) + 1) * STEP];
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -838,10 +838,10 @@ struct OneEngine {
       x.gather(q);
     }
   }
-  template <bool SQ>
+  template <bool SQ, int STEP>
   __device__ __forceinline__ void products(OneState<NR>& x, const u32* y) {
-    base_products<0, SQ>(x.a, y);
-    base_products<1, SQ>(x.b, y);
+    base_products<0, SQ, STEP>(x.a, y);
+    base_products<1, SQ, STEP>(x.b, y);
   }
 
   // the constant 1 of the bias in its slot, and nothing in alpha's yet
@@ -916,6 +916,10 @@ struct OneEngine {
   __device__ __forceinline__ void load(OneState<NR>& x, const u32* src, unsigned left, int nl, const char* matrix) {
     const bool active = (unsigned)(lane & 15) < left;
     src += (lane & 15) * 2 * nl;
+    load_own(x, src, active, nl, matrix);
+  }
+  // the same, each from this lane's own `src`
+  __device__ __forceinline__ void load_own(OneState<NR>& x, const u32* src, bool active, int nl, const char* matrix) {
     x = OneState<NR>();
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
@@ -941,11 +945,10 @@ struct OneEngine {
     set_extra(x.b);
     extend_to_a(x);
   }
-  // The pair as two integers in columns of weight 2^(29 l). Base B still holds what the way back left there, alpha and
-  // the bias among it.
-  __device__ __forceinline__ void store(OneState<NR>& x, long long* dst, unsigned left, const char* matrix) {
-    const bool active = (unsigned)(lane & 15) < left;
-    dst += (lane & 15) * 8 * kTiles;
+  // The pairs as two integers each in columns of weight 2^(29 l), this lane's to element `own` behind `dst`. Base B still
+  // holds what the way back left there, alpha and the bias among it.
+  __device__ __forceinline__ void store(OneState<NR>& x, long long* dst, unsigned own, bool active, const char* matrix) {
+    dst += own * (8 * kTiles);
     flip(x.b);
     OneOperand<NR> d(x.b);
 #pragma unroll
@@ -960,33 +963,44 @@ struct OneEngine {
     }
   }
 
-  // Window tables: an entry holds the registers of base A and of base B one after the other, each as [quad][lane].
-  static constexpr int kArray = (2 * (NR / 4) + 1) * 4 * WAVE;  // dwords
-  __device__ __forceinline__ void load_entry(OneResidues<NR>& d, const u32* entry, int array) const {
-    const Quad* p = (const Quad*)(entry + array * kArray) + lane;
+  // In memory the registers of base A and of base B lie one after the other, a lane's quads STEP apart: WAVE in a window
+  // table's entry of 16 elements, where a lane's first is quad `lane`, and 4 in an element by itself (quad `g`), whose
+  // place each lane knows.
+  template <int STEP>
+  static constexpr int kArray = (2 * (NR / 4) + 1) * 4 * STEP;  // dwords of one base
+  template <int STEP>
+  __device__ __forceinline__ const Quad* quads(const u32* y, int base) const {
+    return (const Quad*)(y + base * kArray<STEP>) + (STEP == WAVE ? lane : g);
+  }
+  template <int STEP>
+  __device__ __forceinline__ void load_array(OneResidues<NR>& d, const u32* y, int base) const {
+    const Quad* p = quads<STEP>(y, base);
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
-      d.q[0][k] = p[2 * k * WAVE];
-      d.q[1][k] = p[(2 * k + 1) * WAVE];
+      d.q[0][k] = p[2 * k * STEP];
+      d.q[1][k] = p[(2 * k + 1) * STEP];
     }
-    d.h = p[2 * (NR / 4) * WAVE];
+    d.h = p[2 * (NR / 4) * STEP];
   }
-  __device__ __forceinline__ void store_entry(const OneResidues<NR>& d, u32* entry, int array) const {
-    Quad* p = (Quad*)(entry + array * kArray) + lane;
+  template <int STEP>
+  __device__ __forceinline__ void store_array(const OneResidues<NR>& d, u32* y, int base) const {
+    Quad* p = (Quad*)quads<STEP>(y, base);
 #pragma unroll
     for (int k = 0; k < NR / 4; ++k) {
-      p[2 * k * WAVE] = d.q[0][k];
-      p[(2 * k + 1) * WAVE] = d.q[1][k];
+      p[2 * k * STEP] = d.q[0][k];
+      p[(2 * k + 1) * STEP] = d.q[1][k];
     }
-    p[2 * (NR / 4) * WAVE] = d.h;
+    p[2 * (NR / 4) * STEP] = d.h;
   }
-  __device__ __forceinline__ void load_state(OneState<NR>& x, const u32* entry) const {
-    load_entry(x.a, entry, 0);
-    load_entry(x.b, entry, 1);
+  template <int STEP>
+  __device__ __forceinline__ void load_state(OneState<NR>& x, const u32* y) const {
+    load_array<STEP>(x.a, y, 0);
+    load_array<STEP>(x.b, y, 1);
   }
-  __device__ __forceinline__ void store_state(const OneState<NR>& x, u32* entry) const {
-    store_entry(x.a, entry, 0);
-    store_entry(x.b, entry, 1);
+  template <int STEP>
+  __device__ __forceinline__ void store_state(const OneState<NR>& x, u32* y) const {
+    store_array<STEP>(x.a, y, 0);
+    store_array<STEP>(x.b, y, 1);
   }
 };
 
@@ -1007,7 +1021,7 @@ __global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsig
   const unsigned waves = blockDim.x / 64;
   // the same for the whole wavefront, so that what follows from it stays in scalar registers
   const size_t wave = (size_t)block * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-  constexpr size_t kEntry = 2 * OneEngine<NR>::kArray;
+  constexpr size_t kEntry = 2 * OneEngine<NR>::template kArray<WAVE>;
   const u32* prog = j.prog ? j.prog : j.ins;
   const int len = __builtin_amdgcn_readfirstlane(j.len);
   u32* table = j.slots + wave * (size_t)j.entries * kEntry;
@@ -1020,7 +1034,7 @@ __global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsig
       // a run of squarings (nine tenths of a program) in a loop of its own, where the state stays in registers
 #pragma unroll 1
       while (ins == ENG_SQ) {
-        e.template products<true>(x, nullptr);
+        e.template products<true, WAVE>(x, nullptr);
         e.extend_to_b(x);
         e.extend_to_a(x);
         ins = ++pc < len ? (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]) : ~0u;
@@ -1029,17 +1043,94 @@ __global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsig
       const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;
       u32* entry = table + (size_t)a * kEntry;
       if (op == ENG_STORE_T) {
-        e.store_state(x, entry);
+        e.template store_state<WAVE>(x, entry);
       } else if (op == ENG_LOAD_T) {
-        e.load_state(x, entry);
+        e.template load_state<WAVE>(x, entry);
       } else {
-        e.template products<false>(x, entry);
+        e.template products<false, WAVE>(x, entry);
         e.extend_to_b(x);
         e.extend_to_a(x);
-        if (op == ENG_MUL_T_ST) e.store_state(x, table + (size_t)b * kEntry);
+        if (op == ENG_MUL_T_ST) e.template store_state<WAVE>(x, table + (size_t)b * kEntry);
       }
     }
-    e.store(x, j.out + tile * (size_t)(16 * 8 * rns::tiles(NR)), left, out_matrix);
+    e.store(x, j.out + tile * (size_t)(16 * 8 * rns::tiles(NR)), e.lane & 15, (unsigned)(e.lane & 15) < left, out_matrix);
+  }
+}
+
+// Products of lists of elements, each in memory by itself as [base A, base B][quad][lane group] (rns_item_words()): a lane
+// group's four lanes read 64 consecutive bytes, 18 times, from wherever the element lies.
+// Into that form: lazy limb pairs as in RnsJob::in, element i to place[i] (null: i); `last` is the element after them. `total`:
+// where the device finds their number, null: `count`.
+template <int NR>
+__global__ __launch_bounds__(1024, 4) void k_rns_enter(const u32* __restrict__ tables, const u32* __restrict__ in,
+                                                       const u32* __restrict__ last, const u32* __restrict__ total,
+                                                       size_t count, int nl, const u32* __restrict__ place,
+                                                       u32* __restrict__ items) {
+  __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
+  for (int i = (int)threadIdx.x; i < rns::lds_bytes(NR) / 16; i += (int)blockDim.x)
+    ((Quad*)lds)[i] = ((const Quad*)tables)[i];
+  __syncthreads();
+  OneEngine<NR> e(lds);
+  const unsigned waves = blockDim.x / WAVE;
+  const size_t wave = (size_t)blockIdx.x * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  if (total) count = *total;
+  const size_t all = count + 1;
+  for (size_t tile = wave; tile * 16 < all; tile += (size_t)gridDim.x * waves) {
+    const size_t own = tile * 16 + (threadIdx.x & 15);
+    OneState<NR> x;
+    e.load_own(x, own < count ? in + own * (size_t)(2 * nl) : last, own < all, nl, (const char*)tables + rns::lds_bytes(NR));
+    if (own < all) e.template store_state<4>(x, items + (place ? place[own] : own) * (size_t)rns::item_words(NR));
+  }
+}
+
+// Every wavefront multiplies 16 lists side by side, up to the longest of them. A factor's quads are on their way one step
+// ahead, its place two products ahead. What bounds it are the matrix products and the vector unit's work between them, one
+// after the other within a wavefront: 2.75 x 10^6 products a ms, with three wavefronts of 168 registers per SIMD; with four of
+// 128, which spill 88 of them, 2.55 x 10^6 (65536 by 32 entries' gradient 2.81 / 3.19 ms). The limb arithmetic forms 1.0 x 10^6.
+template <int NR>
+__global__ __launch_bounds__(768, 3) void k_rns_chains(RnsChains j) {
+  __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
+  const u32 total = j.control[kChainsTotal];
+  if (total == 0) return;
+  for (int i = (int)threadIdx.x; i < rns::lds_bytes(NR) / 16; i += (int)blockDim.x)
+    ((Quad*)lds)[i] = ((const Quad*)j.tables)[i];
+  __syncthreads();
+  const bool columns = j.control[kChainsColumns] != 0;
+  OneEngine<NR> e(lds);
+  const unsigned waves = blockDim.x / WAVE;
+  // The first runs, the longest, are spread over all compute units; the wavefronts draw the ones behind them from a counter.
+  u32 at = ((unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)) * gridDim.x + blockIdx.x) * 16;
+  const u32 drawn_from = gridDim.x * waves * 16;
+  while (at < total) {
+    const u32 own = at + (threadIdx.x & 15);
+    const bool active = own < total;
+    const Quad c = active ? ((const Quad*)j.chains)[own] : Quad{0, 0, 0, 0};
+    const u32 first = c[1], len = c[2];
+    // an element whose list has ended is multiplied by one
+    const auto item = [&](u32 i) -> u32 { return i < len ? j.index ? j.index[first + i] : first + i : 0u; };
+    const auto element = [&](u32 i, u32 at) {
+      return i < len ? j.items + (size_t)at * rns::item_words(NR) : j.one;
+    };
+    const u32 longest = (u32)__builtin_amdgcn_readfirstlane((int)wave_max(len));
+    OneState<NR> x;
+    e.template load_state<4>(x, element(0, item(0)));
+    u32 next = item(1);
+#pragma unroll 1
+    for (u32 i = 1; i < longest; ++i) {
+      const u32* y = element(i, next);
+      next = item(i + 1);
+      e.template products<false, 4>(x, y);
+      e.extend_to_b(x);
+      e.extend_to_a(x);
+    }
+    if (columns) {
+      e.store(x, j.columns + (size_t)c[0] * (8 * rns::tiles(NR)), 0, active, (const char*)j.tables + rns::lds_bytes(NR) + rns::in_matrix_bytes(NR));
+    } else if (active) {
+      e.template store_state<4>(x, j.out + (size_t)c[0] * rns::item_words(NR));
+    }
+    u32 drawn = 0;
+    if (e.lane == 0) drawn = atomicAdd(j.next, 16u);
+    at = drawn_from + (u32)__builtin_amdgcn_readfirstlane((int)drawn);
   }
 }
 
@@ -1577,6 +1668,36 @@ RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int
   b.total = at + std::max((size_t)jobs * table_slots(ctx, nr, n, jobs) * (size_t)entries * 4 * (size_t)nr * 64,
                           (size_t)jobs * (n + 128) * 2 * (size_t)m.nl);
   return b;
+}
+
+size_t rns_item_words(const ModHost& m) { return (size_t)rns::item_words(rns::regs_for(m.nl)); }
+
+namespace {
+// One block per compute unit, with as many wavefronts, `most` of them, as spread `count` elements over all of them
+LaunchShape rns_shape(const haflo_ctx* ctx, size_t count, size_t most) {
+  const size_t tiles = std::max((count + 15) / 16, (size_t)1);
+  const size_t waves = std::min((tiles + ctx->num_cu - 1) / ctx->num_cu, most);
+  LaunchShape sh;
+  sh.threads = (int)waves * WAVE;
+  sh.gpb = (int)waves * 16;
+  sh.blocks = (int)std::min((tiles + waves - 1) / waves, (size_t)ctx->num_cu);
+  return sh;
+}
+}  // namespace
+
+int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, const uint32_t* total, size_t count,
+              const uint32_t* place, uint32_t* items, hipStream_t st) {
+  if (rns::regs_for(m.nl) != 18) return HAFLO_EINVAL;
+  const u32* one = m.d_pairs + (size_t)kConstMOne * 2 * m.nl;
+  HAFLO_LAUNCH((k_rns_enter<18>), rns_shape(ctx, count + 1, 16), st, (const u32*)m.d_rns, in, one, total, count, m.nl, place, items);
+  return hip_status(hipGetLastError());
+}
+
+int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound, hipStream_t st) {
+  if (rns::regs_for(m.nl) != 18) return HAFLO_EINVAL;
+  j.tables = m.d_rns;
+  HAFLO_LAUNCH((k_rns_chains<18>), rns_shape(ctx, bound, 12), st, j);
+  return hip_status(hipGetLastError());
 }
 
 int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, const haflo_ctx* ctx, uint32_t* ws,

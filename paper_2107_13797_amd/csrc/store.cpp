@@ -515,8 +515,8 @@ int haflo_h_matvec(haflo_store* s, int orientation, haflo_handle cipher, haflo_h
   int rc = s->create(HAFLO_KIND_CIPHER, n_out, uses, &ho);
   if (rc != HAFLO_OK) return rc;
   Scratch ws(s);
-  if (!ws.take(haflo_workspace_bytes(s->ctx, orientation == 0 ? HAFLO_OP_MATVEC_XT_D : HAFLO_OP_MATVEC_X_W, rows,
-                                     cols))) {
+  const int op = orientation == 0 ? HAFLO_OP_MATVEC_XT_D : HAFLO_OP_MATVEC_X_W;
+  if (!ws.take(haflo_workspace_bytes(s->ctx, op, rows, cols)) && !ws.take(haflo_workspace_bytes_least(s->ctx, op, rows, cols))) {
     s->drop(ho);
     return HAFLO_ENOMEM;
   }
@@ -541,7 +541,7 @@ int haflo_h_sum(haflo_store* s, haflo_handle cipher, uint32_t uses, haflo_handle
   int rc = s->create(HAFLO_KIND_CIPHER, 1, uses, &ho);
   if (rc != HAFLO_OK) return rc;
   Scratch ws(s);
-  if (!ws.take(haflo_workspace_bytes(s->ctx, HAFLO_OP_MATVEC_XT_D, count, 1))) {
+  if (!ws.take(haflo_workspace_bytes_least(s->ctx, HAFLO_OP_MATVEC_XT_D, count, 1))) {
     s->drop(ho);
     return HAFLO_ENOMEM;
   }

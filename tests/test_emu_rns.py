@@ -153,3 +153,44 @@ def test_creating_a_public_context_is_quick(emu):  # noqa: F811
         return min(times)
 
     assert best(lambda: emu.haflo_ctx_destroy(public_ctx(emu, n, 2048))) < 0.2 * best(lambda: pow(3, n, n * n))
+
+
+def matvec(lib, ctx, bits, orientation, cs, x, room):
+    rows, cols = x.shape
+    op = _cabi.OP_MATVEC_XT_D if orientation == 0 else _cabi.OP_MATVEC_X_W
+    nlw, nout = bits * 9 // 128, cols if orientation == 0 else rows
+    d_c, d_o = zeros(lib, (len(cs), nlw)), zeros(lib, (nout, nlw))
+    assert lib.haflo_import_cipher(ctx, words(lib, cs, bits // 16).p, d_c.p, None, len(cs), None) == 0
+    w, nb = ws(lib, ctx, op, rows, cols, room)
+    assert lib.haflo_cipher_matvec(ctx, orientation, d_c.p, Dev(lib, x).p, rows, cols, d_o.p, w.p, nb, None) == 0
+    return export_n(lib, ctx, bits, d_o, nout)
+
+
+def matvec_case(kind, rows, cols, seed):
+    """Exponent matrices: random with zeros and the extremes; one bucket that holds a whole column, and a zero column."""
+    npr = np.random.default_rng(seed)
+    x = npr.integers(-(1 << 18), 1 << 18, size=(rows, cols)).astype(np.int32)
+    x[npr.random(x.shape) < 0.2] = 0
+    x[1, 0], x[2, 0] = -2 ** 31, 2 ** 31 - 1
+    if kind == "heavy":
+        x[:, 0] = npr.choice(np.array([1025, -1025, 3 * 1024 + 7], dtype=np.int32), size=rows)
+        x[:, 1:] = 0
+    return x
+
+
+@pytest.mark.parametrize("kind,rows,cols", [("random", 257, 2), ("heavy", 300, 2)])
+def test_gradient_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
+    """The bucket rounds in the residue form (the workspace asked for) and on limbs (the least): one to three rounds."""
+    lib, bits = emu, 2048
+    p, q = oracle_key(bits)
+    n, rng = p * q, random.Random(rows)
+    ctx = public_ctx(lib, n, bits)
+    assert lib.haflo_ctx_set_xtd_bucket_min_rows(ctx, 1) == 0
+    assert lib.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_XT_D, rows, cols) > lib.haflo_workspace_bytes_least(
+        ctx, _cabi.OP_MATVEC_XT_D, rows, cols)
+    cs = [rng.randrange(2, n * n) for _ in range(rows)]
+    x = matvec_case(kind, rows, cols, rows)
+    want = O.matvec(O.PrivateKey(p, q).public, 0, cs, x.tolist())
+    for room in ("asked", "least"):
+        assert matvec(lib, ctx, bits, 0, cs, x, room) == want, room
+    lib.haflo_ctx_destroy(ctx)

@@ -181,3 +181,48 @@ def test_key_owner_is_not_slower_with_the_workspace_asked_for(bits, count):
     prv.close()
     assert torch.equal(out[0], out[1])
     assert best[0] < 1.04 * best[1]
+
+
+def matvec_on_limbs(api, ctx, orientation, c, x):
+    """The call in the least workspace it accepts, which has no room for the engine."""
+    lib, (rows, cols) = api.lib(), x.shape
+    op = _cabi.OP_MATVEC_XT_D if orientation == 0 else _cabi.OP_MATVEC_X_W
+    least = lib.haflo_workspace_bytes_least(ctx.handle, op, rows, cols)
+    assert least < lib.haflo_workspace_bytes(ctx.handle, op, rows, cols)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    out = torch.empty((cols if orientation == 0 else rows, c.shape[1]), dtype=c.dtype, device="cuda")
+    assert lib.haflo_cipher_matvec(ctx.handle, orientation, C.c_void_p(c.data_ptr()), C.c_void_p(x.data_ptr()), rows, cols,
+                                   C.c_void_p(out.data_ptr()), C.c_void_p(ws.data_ptr()), least,
+                                   C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    return out
+
+
+def exponents(rows, cols, top, seed):
+    """Random exponents below `top` with zeros, a column of equal entries (one bucket holds all rows), and the extremes."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    x = torch.randint(-top, top, (rows, cols), dtype=torch.int32, device="cuda", generator=gen)
+    x[torch.rand(x.shape, device="cuda", generator=gen) < 0.3] = 0
+    x[:, cols // 2] = 1024 * 3 + 5
+    x[0, 0], x[1, 0] = -2 ** 31, 2 ** 31 - 1
+    return x
+
+
+def random_ciphertexts(api, ctx, n, bits, count):
+    plain = to_dev(random_units_words(count, bits, bits + 3))
+    return api.haflo_encrypt_with_obfuscator(ctx, plain, api.haflo_import_cipher(
+        ctx, to_dev(random_units_words(count, 2 * bits, bits + 4))))
+
+
+# the first shapes are next to the rule (131072 entries on 256 compute units); chunks of 16 and of 32 items, one to four rounds
+@pytest.mark.parametrize("rows,cols,top", [(4096, 32, 1 << 18), (5043, 26, 600), (65537, 2, 40), (140001, 1, 3), (32768, 33, 1 << 17)])
+def test_gradient_matvec_in_residues_matches_limb_arithmetic(rows, cols, top):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    bits = 2048
+    p, q = oracle_key(bits)
+    ctx = api.haflo_ctx_create_public(p * q, bits)
+    c = random_ciphertexts(api, ctx, p * q, bits, rows)
+    x = exponents(rows, cols, top, rows)
+    assert torch.equal(api.haflo_cipher_matvec(ctx, 0, c, x), matvec_on_limbs(api, ctx, 0, c, x))
