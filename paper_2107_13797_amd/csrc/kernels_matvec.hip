@@ -451,13 +451,15 @@ __global__ __launch_bounds__(kBlockThreads) void k_xtd_finish(ModRef M, ModRef M
 // k_xw_positions, one group per (j, sign, s): T[1] = b^(256^s) by 8 s squarings. Then eight launches of
 // k_xw_level with B = 1, 2, 4, .., 128, one group per entry d in (B, 2 B]: T[d] = T[d - B] * T[B]. Every entry
 // costs one product and the chain is 8 s + 8 products long.
+// A table takes `entries` places. In the residue form two factors make an entry, T[16 h + l] = T[16 h] T[l], and the levels
+// stop at 16; four more then fill the places 17 to 30, from place 15 on, with T[32], T[48], ..., T[240].
 // PAIR: the tables are in the pair form modulo M (see Elem); the bases, stored ciphertexts, are taken into it
 // as they are loaded (k_lo, k_hi: see to_pair).
 template <int LPT, int T, bool PAIR>
 __global__ __launch_bounds__(kBlockThreads) void k_xw_positions(ModRef M, const u32* __restrict__ k_lo,
                                                                 const u32* __restrict__ k_hi,
                                                                 const u32* __restrict__ bases,
-                                                                const u32* __restrict__ invbases, size_t cols,
+                                                                const u32* __restrict__ invbases, size_t cols, int entries,
                                                                 u32* __restrict__ tables,
                                                                 const u32* __restrict__ maxmag) {
   using Ops = ElemOps<LPT, T, PAIR>;
@@ -484,14 +486,14 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_positions(ModRef M, const 
       Ops::sqr(t, mod, g);
       if (i < kWin * s) Ops::copy(x, t);
     }
-    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)kWinEntries) * EL;
+    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)entries) * EL;
     if (active) Ops::store(tb + EL, x, g);
   }
 }
 
 template <int LPT, int T, bool PAIR>
 __global__ __launch_bounds__(kBlockThreads) void k_xw_level(ModRef M, const u32* __restrict__ one, size_t cols, int B,
-                                                            u32* __restrict__ tables,
+                                                            int last, int entries, u32* __restrict__ tables,
                                                             const u32* __restrict__ maxmag) {
   using Ops = ElemOps<LPT, T, PAIR>;
   constexpr int EL = Ops::kLimbs;
@@ -500,7 +502,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_level(ModRef M, const u32*
   ModRegs<LPT> mod;
   load_mod<LPT, T>(mod, M, g);
   const int npos = (bit_length(*maxmag) + kWin - 1) / kWin;
-  const int per = B < kWinEntries - 1 - B ? B : kWinEntries - 1 - B;  // entries B + 1 .. min(2 B, 255)
+  const int per = B < last - B ? B : last - B;  // entries B + 1 .. min(2 B, last)
   const size_t count = cols * 2 * (size_t)npos * (size_t)per;
   for (size_t base = bt.first(); base < count; base += bt.stride()) {
     const size_t it = base + bt.gib;
@@ -509,11 +511,87 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_level(ModRef M, const u32*
     const int d = B + 1 + (active ? (int)(it - tab * (size_t)per) : 0);
     const size_t item = tab / (size_t)(npos ? npos : 1);
     const int s = (int)(tab - item * (size_t)(npos ? npos : 1));
-    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)kWinEntries) * EL;
+    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)entries) * EL;
     typename Ops::E a;
     Ops::load(a, active ? tb + (size_t)(d - B) * EL : one, g);
     Ops::mul_mem(a, active ? tb + (size_t)B * EL : one, mod, g);
     if (active) Ops::store(tb + (size_t)d * EL, a, g);
+  }
+}
+
+// The 30 entries of a table that k_xw_level leaves, all tables' of one position after the other, into the residue engine's
+// Montgomery form (times M_A = `enter`), and where in the whole tables of 256 entries they belong; after them the place of one.
+constexpr int kHalfEntries = 32, kHalfUsed = 30, kMixed = 225;  // places, entries, and entries that two of them make
+template <int LPT, int T>
+__global__ __launch_bounds__(kBlockThreads) void k_xw_scale(ModRef M, const u32* __restrict__ enter, size_t cols,
+                                                            const u32* __restrict__ tables, u32* __restrict__ scaled,
+                                                            u32* __restrict__ place, u32* __restrict__ total,
+                                                            const u32* __restrict__ maxmag) {
+  constexpr int EL = 2 * LPT * T;
+  using Ops = ElemOps<LPT, T, true>;
+  Grp<T> g;
+  Batch<T> bt;
+  ModRegs<LPT> mod;
+  load_mod<LPT, T>(mod, M, g);
+  const size_t count = cols * 2 * kHalfUsed * (size_t)((bit_length(*maxmag) + kWin - 1) / kWin);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *total = (u32)count;
+    place[count] = 0;  // of the first table, which has no entry there
+  }
+  for (size_t base = bt.first(); base < count; base += bt.stride()) {
+    const size_t it = base + bt.gib;
+    const bool active = it < count;
+    const size_t tab = active ? it / kHalfUsed : 0;  // s * 2 cols + j * 2 + sign
+    const int t = active ? (int)(it - tab * kHalfUsed) + 1 : 1;
+    const size_t at = tab % (cols * 2) * kMaxPos + tab / (cols * 2);
+    typename Ops::E a;
+    Ops::load(a, tables + (at * kHalfEntries + (size_t)t) * EL, g);
+    Ops::mul_mem(a, enter, mod, g);
+    if (active) {
+      Ops::store(scaled + it * EL, a, g);
+      if (g.k == 0) place[it] = (u32)(at * kWinEntries) + (u32)(t < 16 ? t : 16 * (t - 15));
+    }
+  }
+}
+
+// The other entries of the tables as chains (see rns_chains) of the two they are made of
+__global__ __launch_bounds__(kBlockThreads) void k_xw_mixed(size_t cols, uint4* __restrict__ chains,
+                                                            u32* __restrict__ index, u32* __restrict__ control,
+                                                            const u32* __restrict__ maxmag) {
+  const size_t count = cols * 2 * kMixed * (size_t)((bit_length(*maxmag) + kWin - 1) / kWin);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    control[kChainsTotal] = (u32)count;
+    control[kChainsColumns] = 0;
+  }
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x) {
+    const size_t tab = i / kMixed;
+    const u32 r = (u32)(i - tab * kMixed), high = 16 * (r / 15 + 1), low = r % 15 + 1;
+    const u32 at = (u32)((tab % (cols * 2) * kMaxPos + tab / (cols * 2)) * kWinEntries);
+    index[2 * i] = at + high;
+    index[2 * i + 1] = at + low;
+    chains[i] = make_uint4(at + high + low, (u32)(2 * i), 2u, 0u);
+  }
+}
+
+// Rows' products as chains: 2^seg_shift of near-equal length for a row, in the order `order`, and behind them (unless a row
+// is one chain) those that combine a row's.
+__global__ __launch_bounds__(kBlockThreads) void k_xw_chains(size_t rows, size_t list_stride, int seg_shift,
+                                                             const u32* __restrict__ counts, const u32* __restrict__ order,
+                                                             uint4* __restrict__ chains, u32* __restrict__ control,
+                                                             u32* __restrict__ control2) {
+  const size_t items = rows << seg_shift;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    control[kChainsTotal] = (u32)items;
+    control[kChainsColumns] = seg_shift == 0;
+    control2[kChainsTotal] = (u32)rows;
+    control2[kChainsColumns] = 1;
+  }
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < items; i += (size_t)gridDim.x * blockDim.x) {
+    const u32 row = order[i >> seg_shift], seg = (u32)i & ((1u << seg_shift) - 1u);
+    const u64 len = counts[row];
+    const u32 e0 = (u32)((len * seg) >> seg_shift), e1 = (u32)((len * (seg + 1u)) >> seg_shift);
+    chains[i] = make_uint4((row << seg_shift) + seg, (u32)(row * list_stride) + e0, e1 - e0, 0u);
+    if (seg == 0 && seg_shift) chains[items + row] = make_uint4(row, row << seg_shift, 1u << seg_shift, 0u);
   }
 }
 
@@ -643,6 +721,27 @@ __device__ __forceinline__ void xw_store_result(u32* dst, Elem<LPT, PAIR>& acc, 
   } else {
     canonicalise<LPT, T>(acc.x0, mod.n, g);
     if (active) store_limbs<LPT, T>(dst, acc.x0, g);
+  }
+}
+
+// The same from the residue engine's columns
+template <int LPT, int T>
+__global__ __launch_bounds__(kBlockThreads, 4) void k_xw_leave(ModRef M, const u32* __restrict__ leave,
+                                                               const long long* __restrict__ columns, int stride,
+                                                               size_t rows, u32* __restrict__ out) {
+  constexpr int EL = 2 * LPT * T;
+  Grp<T> g;
+  Batch<T> bt;
+  ModRegs<LPT> mod;
+  load_mod<LPT, T>(mod, M, g);
+  for (size_t base = bt.first(); base < rows; base += bt.stride()) {
+    const size_t row = base + bt.gib;
+    const bool active = row < rows;
+    const long long* src = columns + (active ? row : 0) * (size_t)(2 * stride);
+    Elem<LPT, true> acc;
+    load_columns<LPT, T>(acc.x0, src, g);
+    load_columns<LPT, T>(acc.x1, src + stride, g);
+    xw_store_result<LPT, T, true>(out + (active ? row : 0) * (size_t)EL, acc, active, leave, mod, g);
   }
 }
 
@@ -795,7 +894,10 @@ struct XwPlan {
   // [kXwBinsAt, kXwBinsAt + kLenBins) the length classes
   size_t off_inv, off_tables, off_nz, off_cnt, off_order, off_partial, total;
   int seg_shift;  // every row's list is multiplied in 2^seg_shift segments
+  // in the residue form the limb tables are halves, and words 2 and 3 are counters too, 8 to 15 what the chains' lengths are
+  size_t off_scaled, off_place, off_index, off_chains, off_items, off_columns;
 };
+constexpr size_t kXwControlAt = 8;
 constexpr size_t kXwBinsAt = 64;
 // Segments per row: doubled while the chip would hold fewer than four wavefronts per SIMD, up to 8
 // and while a full row still gives every segment a few entries.
@@ -817,6 +919,45 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.seg_shift = xw_seg_shift(ctx, rows, cols);
   p.total = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * nl : 0);
   return p;
+}
+// Tables and rows in the residue form. Besides the products themselves (see xtd_buckets_in_residues) the tables take less:
+// 30 of their 255 entries on limbs, the rest one product in residues each. Whole calls on limbs / in residues, ms, 70 % zeros:
+// 1000 by 256 1.17 / 1.27, 4096 by 64 0.77 / 0.80, 16384 by 16 0.69 / 0.73, 60000 by 7 0.83 / 0.77, 65536 by 32 1.77 / 1.10, 16384
+// by 256 3.55 / 1.93. List places and table entries are 32-bit.
+bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  return ctx->Nh.d_rns && ctx->Nh.nl == 72 && cols && rows < (1u << 28) && cols < (1u << 20) &&
+         rows * cols * kMaxPos <= 0xFFFFFFFFull && rows * cols >= (size_t)ctx->num_cu * 1280;
+}
+// Segments per row: doubled while the engine has no more than its fill of chains, and a list of 30 % a few factors a chain
+int xw_residue_shift(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  int sh = 0;
+  while (sh < 5 && (rows << sh) < (size_t)ctx->num_cu * 256 && cols >= ((size_t)16 << sh)) ++sh;
+  return sh;
+}
+XwPlan xw_residue_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  XwPlan p;
+  const size_t nl = (size_t)ctx->N.nl, item = rns_item_words(ctx->Nh), tabs = cols * 2 * kMaxPos;
+  const auto aligned = [](size_t w) { return (w + 63) & ~(size_t)63; };
+  p.seg_shift = xw_residue_shift(ctx, rows, cols);
+  const size_t chains = (rows << p.seg_shift) + (p.seg_shift ? rows : 0);
+  p.off_inv = kXwBinsAt + kLenBins;
+  p.off_tables = p.off_inv + cols * nl;
+  p.off_scaled = p.off_tables + tabs * kHalfEntries * nl;
+  p.off_place = p.off_scaled + tabs * kHalfUsed * nl;
+  p.off_index = p.off_place + tabs * kHalfUsed + 1;
+  p.off_nz = p.off_index + tabs * kMixed * 2;
+  p.off_cnt = p.off_nz + rows * cols * kMaxPos;
+  p.off_order = p.off_cnt + rows;
+  p.off_chains = aligned(p.off_order + rows);
+  p.off_items = aligned(p.off_chains + std::max(tabs * kMixed, chains) * 4);
+  p.off_partial = p.off_items + tabs * kWinEntries * item;
+  p.off_columns = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * item : 0);
+  p.total = p.off_columns + rows * 4 * (size_t)rns_columns(ctx->Nh);
+  return p;
+}
+// what a call asks for where the residue engine serves it (its start is aligned to 256 bytes), else 0
+size_t ws_xw_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  return xw_in_residues(ctx, rows, cols) ? xw_residue_plan(ctx, rows, cols).total * 4 + 256 : 0;
 }
 
 // X^T [[d]]: what a call can do with, and what it asks for where the residue engine serves it (else 0)
@@ -905,7 +1046,7 @@ size_t haflo_workspace_bytes(const haflo_ctx* ctx, int op, size_t rows, size_t c
              ws_encrypt(ctx, rows);
     case HAFLO_OP_MATVEC_XT_D:
       return std::max(ws_xtd_min(ctx, rows, cols), ws_xtd_residues(ctx, rows, cols));
-    case HAFLO_OP_MATVEC_X_W: return xw_plan(ctx, rows, cols).total * 4;
+    case HAFLO_OP_MATVEC_X_W: return std::max(xw_plan(ctx, rows, cols).total * 4, ws_xw_residues(ctx, rows, cols));
     case HAFLO_OP_SUM_SEGMENTS:
       if (rows >= (1ull << 32) || cols >= (1ull << 24)) return (size_t)-1;
       return cols ? seg_sum_plan(ctx, rows, cols).total * 4 : 0;
@@ -921,6 +1062,7 @@ size_t haflo_workspace_bytes_least(const haflo_ctx* ctx, int op, size_t rows, si
     case HAFLO_OP_DECRYPT: return ws_decrypt_min(ctx, rows);
     case HAFLO_OP_SCALAR_MUL: return ws_scalar_mul_min(ctx, rows);
     case HAFLO_OP_MATVEC_XT_D: return ws_xtd_min(ctx, rows, cols);
+    case HAFLO_OP_MATVEC_X_W: return xw_plan(ctx, rows, cols).total * 4;
     case HAFLO_OP_FORE_GRADIENT: return asked - ws_encrypt(ctx, rows) + ws_encrypt_min(ctx, rows);
     case HAFLO_OP_TAYLOR_LOSS: return ws_taylor_loss_min(ctx, rows);
     default: return asked;
@@ -939,16 +1081,16 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
   const size_t need = haflo_workspace_bytes_least(ctx, orientation == 0 ? HAFLO_OP_MATVEC_XT_D : HAFLO_OP_MATVEC_X_W, rows, cols);
   if (!d_workspace || workspace_bytes < need) return HAFLO_EINVAL;
   u32* ws = (u32*)d_workspace;
+  const size_t asked = orientation == 0 ? ws_xtd_residues(ctx, rows, cols) : ws_xw_residues(ctx, rows, cols);
+  const bool residues = asked != 0 && workspace_bytes >= asked;
+  if (residues) ws = (u32*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
   const bool buckets = orientation == 0 && use_buckets(ctx, rows, cols);
   int rc = buckets ? HAFLO_OK
                    : launch_maxmag(ctx, d_X, rows * cols, ws, orientation == 0 ? 2 : (int)(kXwBinsAt + kLenBins), st);
   if (rc != HAFLO_OK) return rc;
   const int nbatch = inverse_batches(ctx);
   if (buckets) {
-    const size_t asked = ws_xtd_residues(ctx, rows, cols);
-    const bool residues = asked != 0 && workspace_bytes >= asked;
     const XtdBucketLayout l = xtd_bucket_layout(ctx, rows, cols, residues);
-    if (residues) ws = (u32*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     u32* P = ws + l.off_P;
     rc = xtd_buckets(ctx, (const u32*)d_c, d_X, rows, cols, residues, ws + l.off_ws, P, st);
     if (rc != HAFLO_OK) return rc;
@@ -988,7 +1130,7 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
 #undef CALL
     }
   } else {
-    const XwPlan p = xw_plan(ctx, rows, cols);
+    const XwPlan p = residues ? xw_residue_plan(ctx, rows, cols) : xw_plan(ctx, rows, cols);
     u32* inv = ws + p.off_inv;
     u32* tables = ws + p.off_tables;
     u32* lists = ws + p.off_nz;
@@ -1014,17 +1156,45 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
 #define CALL(LPT, T)                                                                                                \
   HAFLO_LAUNCH((k_xw_positions<LPT, T, true>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstR4 * 2 * mh.nl), \
                (const u32*)(mh.d_pairs + (size_t)kConstR5 * 2 * mh.nl), (const u32*)d_c, (const u32*)inv, cols,     \
-               tables, (const u32*)ws)
+               residues ? kHalfEntries : kWinEntries, tables, (const u32*)ws)
         HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
       }
-      for (int B = 1; B < kWinEntries; B *= 2) {
-        const size_t groups = cols * 2 * kMaxPos * (size_t)std::min(B, kWinEntries - 1 - B);
-        const LaunchShape sh = launch_pairs(ctx, mh, groups, lanes, wave);
-#define CALL(LPT, T) HAFLO_LAUNCH((k_xw_level<LPT, T, true>), sh, st, M, one, cols, B, tables, (const u32*)ws)
-        HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
+      for (int part = 0; part < (residues ? 2 : 1); ++part) {
+        const int entries = residues ? kHalfEntries : kWinEntries, last = !residues ? kWinEntries - 1 : part ? 15 : 16;
+        u32* from = tables + (size_t)(part * 15) * 2 * mh.nl;
+        for (int B = 1; B < last; B *= 2) {
+          const size_t groups = cols * 2 * kMaxPos * (size_t)std::min(B, last - B);
+          const LaunchShape sh = launch_pairs(ctx, mh, groups, lanes, wave);
+#define CALL(LPT, T) HAFLO_LAUNCH((k_xw_level<LPT, T, true>), sh, st, M, one, cols, B, last, entries, from, (const u32*)ws)
+          HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
+        }
       }
+    }
+    RnsChains chains = {};
+    if (residues) {
+      const size_t tabs = cols * 2 * kMaxPos;
+      u32* place = ws + p.off_place;
+      u32* total = ws + kXwControlAt;
+      const LaunchShape sh = launch_shape(ctx, tabs * kHalfUsed, lanes, 8);
+#define CALL(LPT, T)                                                                                          \
+  HAFLO_LAUNCH((k_xw_scale<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstMOne * 2 * mh.nl), cols, \
+               (const u32*)tables, ws + p.off_scaled, place, total, (const u32*)ws)
+      HAFLO_DISPATCH_PAIRS(mh, CALL);
+#undef CALL
+      rc = rns_enter(ctx, mh, ws + p.off_scaled, total, tabs * kHalfUsed, place, ws + p.off_items, st);
+      if (rc != HAFLO_OK) return rc;
+      chains.items = chains.one = ws + p.off_items;
+      chains.chains = ws + p.off_chains;
+      chains.index = ws + p.off_index;
+      chains.control = ws + kXwControlAt + kChainsControl;
+      chains.next = ws + 2;
+      chains.out = ws + p.off_items;
+      HAFLO_LAUNCH(k_xw_mixed, launch_shape(ctx, tabs * kMixed, 1, 8), st, cols, (uint4*)(ws + p.off_chains),
+                   ws + p.off_index, ws + kXwControlAt + kChainsControl, (const u32*)ws);
+      rc = rns_chains(ctx, mh, chains, tabs * kMixed, st);
+      if (rc != HAFLO_OK) return rc;
     }
     u32* bins = ws + kXwBinsAt;
     u32* order = ws + p.off_order;
@@ -1041,6 +1211,33 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
       HAFLO_LAUNCH(k_xw_order<true>, per_row, st, (const u32*)cnt, rows, cols, bins, order, (const u32*)ws);
     }
     u32* partial = ws + p.off_partial;
+    if (residues) {
+      u32* control = ws + kXwControlAt + 2 * kChainsControl;
+      HAFLO_LAUNCH(k_xw_chains, launch_shape(ctx, rows << p.seg_shift, 1, 8), st, rows, cols * (size_t)kMaxPos, p.seg_shift,
+                   (const u32*)cnt, (const u32*)order, (uint4*)(ws + p.off_chains), control, control + kChainsControl);
+      chains.index = lists;
+      chains.control = control;
+      chains.next = ws + 1;
+      chains.out = partial;
+      chains.columns = (long long*)(ws + p.off_columns);
+      rc = rns_chains(ctx, mh, chains, rows << p.seg_shift, st);
+      if (rc == HAFLO_OK && p.seg_shift) {
+        chains.items = partial;
+        chains.chains += (rows << p.seg_shift) * 4;
+        chains.index = nullptr;
+        chains.control += kChainsControl;
+        chains.next = ws + 3;
+        rc = rns_chains(ctx, mh, chains, rows, st);
+      }
+      if (rc != HAFLO_OK) return rc;
+      const LaunchShape sh = launch_shape(ctx, rows, lanes, 8);
+#define CALL(LPT, T)                                                                                            \
+  HAFLO_LAUNCH((k_xw_leave<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstMStored * 2 * mh.nl),  \
+               (const long long*)(ws + p.off_columns), rns_columns(mh), rows, (u32*)d_out)
+      HAFLO_DISPATCH_PAIRS(mh, CALL);
+#undef CALL
+      return hip_status(hipGetLastError());
+    }
     {
       const LaunchShape sh = launch_shape(ctx, rows << p.seg_shift, lanes, 3);
 #define CALL(LPT, T)                                                                                            \

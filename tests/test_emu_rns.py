@@ -194,3 +194,26 @@ def test_gradient_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
     for room in ("asked", "least"):
         assert matvec(lib, ctx, bits, 0, cs, x, room) == want, room
     lib.haflo_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("kind,rows,cols", [("random", 641, 2), ("sparse", 81, 16), ("zero", 1280, 1)])
+def test_forward_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
+    """Tables and row products in the residue form (the workspace asked for) and on limbs (the least): rows in several
+    chains and in one, empty rows, exponents of all digit positions and none."""
+    lib, bits = emu, 2048
+    p, q = oracle_key(bits)
+    n, rng = p * q, random.Random(rows)
+    ctx = public_ctx(lib, n, bits)
+    assert lib.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_X_W, rows, cols) > lib.haflo_workspace_bytes_least(
+        ctx, _cabi.OP_MATVEC_X_W, rows, cols)
+    cs = [rng.randrange(2, n * n) for _ in range(cols)]
+    x = matvec_case(kind, rows, cols, rows)
+    if kind == "sparse":
+        x = (np.sign(x) * (np.abs(x.astype(np.int64)) % 256)).astype(np.int32)
+        x[np.random.default_rng(3).random(x.shape) < 0.6] = 0
+    if kind == "zero":
+        x[:] = 0
+    want = O.matvec(O.PrivateKey(p, q).public, 1, cs, x.tolist())
+    for room in ("asked", "least"):
+        assert matvec(lib, ctx, bits, 1, cs, x, room) == want, room
+    lib.haflo_ctx_destroy(ctx)

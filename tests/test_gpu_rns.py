@@ -226,3 +226,20 @@ def test_gradient_matvec_in_residues_matches_limb_arithmetic(rows, cols, top):
     c = random_ciphertexts(api, ctx, p * q, bits, rows)
     x = exponents(rows, cols, top, rows)
     assert torch.equal(api.haflo_cipher_matvec(ctx, 0, c, x), matvec_on_limbs(api, ctx, 0, c, x))
+
+
+# the first shapes are next to the rule (327680 entries on 256 compute units); rows in 1, 2 and 16 chains, one to four digits
+@pytest.mark.parametrize("rows,cols,top", [(81920, 4, 1 << 16), (10241, 32, 1 << 9), (641, 512, 200), (40001, 17, 1 << 28)])
+def test_forward_matvec_in_residues_matches_limb_arithmetic(rows, cols, top):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    bits = 2048
+    p, q = oracle_key(bits)
+    ctx = api.haflo_ctx_create_public(p * q, bits)
+    c = random_ciphertexts(api, ctx, p * q, bits, cols)
+    x = exponents(rows, cols, top, rows)
+    x[5] = 0  # an empty list
+    if top < 256:
+        x[x.abs() > 4 * 1024] = 7  # one digit throughout
+    assert torch.equal(api.haflo_cipher_matvec(ctx, 1, c, x), matvec_on_limbs(api, ctx, 1, c, x))
