@@ -414,9 +414,7 @@ static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
     const Big rn_inv_m = mh.to_mont(rn_inv);
     special.push_back({kConstMLo, mh.mul(special_of(special, kConstM1), rn_inv_m)});
     special.push_back({kConstMHi, mh.mul(special_of(special, kConstM2), rn_inv_m)});
-    const Big r_inv_m = mh.to_mont(r_inv), to_stored = mh.mul(mh.from_mont(inv), r_inv_m);
-    special.push_back({kConstMStored, to_stored});
-    special.push_back({kConstMPair, mh.mul(to_stored, r_inv_m)});  // as R_N = R^2
+    special.push_back({kConstMStored, mh.mul(mh.from_mont(inv), mh.to_mont(r_inv))});
   }
 }
 static void put_prog(DevProg& p, std::vector<uint32_t> ins, int table_entries, Uploader& up) {

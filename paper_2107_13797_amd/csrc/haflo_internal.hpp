@@ -71,8 +71,8 @@ enum {
   kConstM1 = 7, kConstM2 = 8, kConstM3 = 9, kConstM4 = 10, kConstMOut = 11,
   // the same for stored ciphertexts: their lower and upper halves into the form, a power out of it
   kConstMLo = 12, kConstMHi = 13, kConstMStored = 14,
-  kConstMOne = 15, kConstMPair = 16,  // one in that form; out of it to the pair engine's own, R^2 / M_A
-  kNumConst = 17
+  kConstMOne = 15,  // one in that form
+  kNumConst = 16
 };
 inline uint32_t eng_ins(uint32_t op, uint32_t a = 0, uint32_t b = 0) { return op | (a << 8) | (b << 20); }
 
@@ -232,10 +232,8 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
 // rns_item_words() words. Chain i is {place of its product, first item, items, unused}; item k of it is element
 // first + k, or index[first + k].
 size_t rns_item_words(const ModHost& m);
-// Pairs of lazy limbs (times M_A) at `in` into the form, element i to place[i] (null: i), and one as the element after the
-// last. There are `count` of them, or *total (a device word, at most `count`) unless that is null.
-int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, const uint32_t* total, size_t count,
-              const uint32_t* place, uint32_t* items, hipStream_t st);
+// `count` pairs of lazy limbs (times M_A) at `in` into the form, and one as the element after the last
+int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, size_t count, uint32_t* items, hipStream_t st);
 enum { kChainsTotal = 0, kChainsColumns = 1, kChainsControl = 2 };  // device words: number of chains; whether products leave the form
 struct RnsChains {
   const uint32_t* tables;   // set by rns_chains()
@@ -248,6 +246,41 @@ struct RnsChains {
   uint32_t* out;            // elements, or
   long long* columns;       // 2 rns_columns() signed columns of weight 2^(29 l)
 };
+// A program that every element of a launch runs on operands of its own. It has two values, both one at first. An operand is
+// the next row of `operands` (for element e word e of it), an element's place or kNoOperand, which is one.
+enum RnsListOp : uint8_t {
+  LIST_RUN_ITEM,   // run *= operand
+  LIST_ACC_ITEM,   // acc *= operand
+  LIST_ACC_RUN,    // acc *= run
+  LIST_ACC_SQ,     // acc *= acc
+  LIST_STORE_ACC,  // acc to the place that the next row of `places` has
+  LIST_STORE_RUN,
+  LIST_COLUMNS,    // acc leaves the form: to the element's columns
+  LIST_ACC_LIMBS   // acc = the element's pair of lazy limbs, taken into the form
+};
+constexpr uint32_t kNoOperand = ~0u;
+constexpr int kListOps = 96, kListRows = 32;  // at most; an instruction is four bits
+struct RnsLists {
+  const uint32_t* tables;    // set by rns_lists()
+  const uint32_t* items;
+  const uint32_t* one;
+  const uint32_t* operands;  // `rows` of them, of `stride` words
+  const uint32_t* places;    // null: an element's is its own number
+  size_t stride;
+  int rows;
+  const uint32_t* live;      // device word: elements there are
+  const uint32_t* limit;     // device word: instructions to run, or null
+  uint32_t* out;
+  long long* columns;
+  const uint32_t* limbs;     // an element's are 2 nl words
+  int nl, len;
+  uint32_t ops[kListOps / 8];
+  void add(RnsListOp op, int times = 1) {
+    for (; times > 0; --times, ++len) ops[len / 8] |= (uint32_t)op << len % 8 * 4;
+  }
+};
+// `bound`: no fewer than the elements that the device may find
+int rns_lists(const haflo_ctx* ctx, const ModHost& m, RnsLists j, size_t bound, hipStream_t st);
 // `bound`: no fewer than the chains that the device may find
 int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound, hipStream_t st);
 
@@ -259,7 +292,7 @@ struct XtdBucketPlan {
   size_t off_cnt, off_totals, off_offs, off_sorted, off_arena[2], off_G, off_AT, off_R, off_pairs, off_order, total;
   bool pairs;  // the products run on pairs of residues modulo n
   bool residues;  // the rounds' in the residue form
-  size_t off_items, off_columns, off_chains, off_control, off_last;
+  size_t off_items, off_one, off_chains, off_control, off_tail, arena1_items;  // what the first arena holds
 };
 bool xtd_buckets_fit(size_t rows, size_t cols);
 bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols);  // if the workspace has room for it

@@ -287,7 +287,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_order(const u32* __restric
 }
 
 // The chunks of a round as lists for the residue engine's chains (rns_chains), in the order of `order` where there is one:
-// chunk q's product goes to place q. The last round's products leave the residue form.
+// chunk q's product goes to place q.
 __global__ __launch_bounds__(kBlockThreads) void k_bk_chains(const u32* __restrict__ cnt, const u32* __restrict__ off,
                                                              const u32* __restrict__ choff, size_t K, int round, int cb,
                                                              const u32* __restrict__ stats,
@@ -297,39 +297,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_chains(const u32* __restri
   const u32 total = round < run ? choff[K] : 0u;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     control[kChainsTotal] = total;
-    control[kChainsColumns] = round == run - 1;
+    control[kChainsColumns] = 0;
   }
   for (u32 at = blockIdx.x * blockDim.x + threadIdx.x; at < total; at += gridDim.x * blockDim.x) {
     const u32 q = order ? order[at] : at;
     const ChunkAt ch = chunk_at(q, true, cnt, choff, K, round, cb);
     chains[at] = make_uint4(q, off[ch.key] + ch.begin, ch.len, 0u);
-  }
-}
-
-// The items that the last round left, from the residue engine's columns into the pair form: times `leave` = R^2 / M_A
-template <int LPT, int T>
-__global__ __launch_bounds__(kBlockThreads, 4) void k_bk_leave(ModRef M, const u32* __restrict__ leave,
-                                                               const long long* __restrict__ columns, int stride,
-                                                               const u32* __restrict__ offs, size_t K, int cb,
-                                                               const u32* __restrict__ stats, u32* __restrict__ out) {
-  constexpr int NLH = LPT * T;
-  Grp<T> g;
-  Batch<T> bt;
-  ModRegs<LPT> mod;
-  load_mod<LPT, T>(mod, M, g);
-  const size_t count = offs[(size_t)rounds_run(stats[kStatMaxCount], cb) * (K + 1) + K];
-  for (size_t base = bt.first(); base < count; base += bt.stride()) {
-    const size_t it = base + bt.gib;
-    const bool active = it < count;
-    const long long* src = columns + (active ? it : 0) * (size_t)(2 * stride);
-    u32 x0[LPT], x1[LPT];
-    load_columns<LPT, T>(x0, src, g);
-    load_columns<LPT, T>(x1, src + stride, g);
-    pairmul_mem<LPT, T>(x0, x1, x0, x1, leave, mod.n, mod.n0inv, g);
-    if (active) {
-      store_limbs<LPT, T>(out + it * (size_t)(2 * NLH), x0, g);
-      store_limbs<LPT, T>(out + it * (size_t)(2 * NLH) + NLH, x1, g);
-    }
   }
 }
 
@@ -615,6 +588,90 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_horner(ModRef M, const u32
   }
 }
 
+// In the residue form the same steps are four programs (RnsLists), one value or two for each
+//   1. share of a sub-product, kShare factors of it: 4 of a high one, then 2 of a low one
+//   2. segment of kSegLen sub-products: run and acc as in k_bk_fold1, with a sub-product's shares one after the other
+//   3. part, low and high, as in k_bk_fold2
+//   4. column and sign, as in k_bk_horner
+// Steps 2 and 3 are ordered by segment and by part, so that what only some have is passed over by whole blocks.
+constexpr int kShare = 8, kHiShares = kLoCount / kShare, kLoShares = kHiCount / kShare;
+constexpr int kShares = kHiCount * kHiShares + kLoCount * kLoShares;
+struct TailPlan {  // words from the start of the workspace
+  size_t operands[4], places, live, items[3], columns;
+};
+__global__ __launch_bounds__(kBlockThreads) void k_bk_tail(const u32* __restrict__ cnt, const u32* __restrict__ offs, size_t K,
+                                                           size_t cols, u32 second_arena, int cb,
+                                                           const u32* __restrict__ stats, u32* __restrict__ ws, TailPlan p) {
+  const int ran = rounds_run(stats[kStatMaxCount], cb), npos = digit_positions(stats[kStatMaxMag]);
+  const u32* off = offs + (size_t)ran * (K + 1);
+  const u32 arena = (ran - 1) & 1 ? second_arena : 0u;
+  const u32 most = (u32)(cols * 2 * kMaxPos), combos = (u32)(cols * 2) * (u32)npos;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    u32* live = ws + p.live;
+    live[0] = combos * kShares;
+    live[1] = combos * kSegs;
+    live[2] = combos * 2;
+    live[3] = (u32)(cols * 2);
+  }
+  const u32 at = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (u32 i = at; i < combos * kShares * kShare; i += step) {
+    const u32 e = i % (combos * kShares), u = i / (combos * kShares), combo = e / kShares, t = e % kShares;
+    const bool high = t < kHiCount * kHiShares;
+    const u32 v = high ? t : t - kHiCount * kHiShares;
+    const size_t key = (size_t)combo * kMags + (high ? v / kHiShares * kLoCount + v % kHiShares * kShare + u
+                                                     : v / kLoShares + (v % kLoShares * kShare + u) * kLoCount);
+    ws[p.operands[0] + (size_t)u * most * kShares + e] = cnt[key] ? arena + off[key] : kNoOperand;
+  }
+  for (u32 i = at; i < combos * kSegs * kSegLen * kHiShares; i += step) {
+    const u32 e = i % (combos * kSegs), r = i / (combos * kSegs), combo = e % combos, seg = e / combos;
+    const u32 u = kSegLen - 1 - r / kHiShares, part = r % kHiShares;
+    const bool high = seg >= kLoSegs;
+    const u32 sub = (high ? seg - kLoSegs : seg) * kSegLen + u + (high ? 1 : 0);
+    const bool there = high ? sub < kHiCount : part < kLoShares;
+    ws[p.operands[1] + (size_t)r * most * kSegs + e] =
+        there ? combo * kShares + (high ? sub * kHiShares : kHiCount * kHiShares + sub * kLoShares) + part : kNoOperand;
+    if (r < 2) ws[p.places + (size_t)r * most * kSegs + e] = 2 * e + r;  // A, T
+  }
+  for (u32 i = at; i < combos * 2 * (2 * kLoSegs - 1); i += step) {
+    const u32 e = i % (combos * 2), r = i / (combos * 2), combo = e % combos;
+    const bool high = e >= combos;
+    const u32 q = r < kLoSegs - 1 ? kLoSegs - 1 - r : r - (kLoSegs - 1);  // T of 3, 2, 1, then A of 0 to 3
+    const u32 seg = high ? kLoSegs + q : q;
+    ws[p.operands[2] + (size_t)r * most * 2 + e] = q < (u32)(high ? kHiSegs : kLoSegs) ? 2 * (seg * combos + combo) + (r < kLoSegs - 1 ? 1 : 0) : kNoOperand;
+  }
+  for (u32 i = at; i < (u32)cols * 2 * kMaxPos * 2; i += step) {
+    const u32 e = i % ((u32)cols * 2), r = i / ((u32)cols * 2), s = kMaxPos - 1 - r / 2;
+    ws[p.operands[3] + (size_t)r * cols * 2 + e] = s < (u32)npos ? (r % 2 ? 0 : combos) + s * (u32)(cols * 2) + e : kNoOperand;
+  }
+}
+
+// What the last program left, from the residue engine's columns to the form of a stored ciphertext: times `leave`
+template <int LPT, int T>
+__global__ __launch_bounds__(kBlockThreads, 4) void k_bk_leave(ModRef M, const u32* __restrict__ leave,
+                                                               const long long* __restrict__ columns, int stride,
+                                                               size_t count, u32* __restrict__ out) {
+  constexpr int NLH = LPT * T;
+  Grp<T> g;
+  Batch<T> bt;
+  ModRegs<LPT> mod;
+  load_mod<LPT, T>(mod, M, g);
+  for (size_t base = bt.first(); base < count; base += bt.stride()) {
+    const size_t it = base + bt.gib;
+    const bool active = it < count;
+    const long long* src = columns + (active ? it : 0) * (size_t)(2 * stride);
+    u32 x0[LPT], x1[LPT], lo[LPT], hi[LPT];
+    load_columns<LPT, T>(x0, src, g);
+    load_columns<LPT, T>(x1, src + stride, g);
+    pairmul_mem<LPT, T>(x0, x1, x0, x1, leave, mod.n, mod.n0inv, g);
+    pair_canonical<LPT, T>(x0, x1, mod.n, g);
+    pair_to_integer<LPT, T>(lo, hi, x0, x1, mod.n, g);
+    if (active) {
+      store_limbs<LPT, T>(out + it * (size_t)(2 * NLH), lo, g);
+      store_limbs<LPT, T>(out + it * (size_t)(2 * NLH) + NLH, hi, g);
+    }
+  }
+}
+
 // Segmented summation: segment k = elements [o[k], o[k+1]) of one array is a "bucket" whose rows are
 // already in place. cnt[k] = its length; offsets that run backwards or past the end of the array are
 // the caller's error and give an empty or clipped segment (and a status bit), never an access outside.
@@ -745,6 +802,86 @@ int seg_sum(const haflo_ctx* ctx, const uint32_t* d_c, const uint32_t* d_offsets
   return hip_status(hipGetLastError());
 }
 
+namespace {
+TailPlan tail_plan(const haflo_ctx* ctx, size_t cols, size_t at) {
+  TailPlan p;
+  const size_t most = cols * 2 * kMaxPos, item = rns_item_words(ctx->Nh);
+  const size_t rows[4] = {most * kShares * kShare, most * kSegs * kSegLen * kHiShares, most * 2 * (2 * kLoSegs - 1), cols * 4 * kMaxPos};
+  for (int i = 0; i < 4; ++i) {
+    p.operands[i] = at;
+    at += rows[i];
+  }
+  p.places = at;  at += most * kSegs * 2;
+  p.live = at;    at += 4;
+  at = (at + 63) & ~(size_t)63;
+  const size_t out[3] = {most * kShares, most * kSegs * 2, most * 2};
+  for (int i = 0; i < 3; ++i) {
+    p.items[i] = at;
+    at += out[i] * item;
+  }
+  p.columns = at;
+  return p;
+}
+// The four programs, from the items that the last round left to the columns' results in d_P
+int tail(const haflo_ctx* ctx, const XtdBucketPlan& p, size_t cols, const u32* cnt, const u32* offs, const u32* stats, u32* ws,
+         u32* d_P, hipStream_t st) {
+  const ModHost& mh = ctx->Nh;
+  const TailPlan t = tail_plan(ctx, cols, p.off_tail);
+  const size_t most = cols * 2 * kMaxPos;
+  HAFLO_LAUNCH(k_bk_tail, launch_shape(ctx, most * kShares * kShare, 1, 8), st, cnt, offs, p.keys, cols, (u32)p.arena1_items,
+               p.chunk_bits, stats, ws, t);
+  const size_t bound[4] = {most * kShares, most * kSegs, most * 2, cols * 2};
+  for (int i = 0; i < 4; ++i) {
+    RnsLists j = {};
+    j.items = ws + (i ? t.items[i - 1] : p.off_arena[0]);
+    j.one = ws + p.off_one;
+    j.operands = ws + t.operands[i];
+    j.places = i == 1 ? ws + t.places : nullptr;
+    j.stride = bound[i];
+    j.live = ws + t.live + i;
+    if (i < 3) j.out = ws + t.items[i];
+    j.columns = (long long*)(ws + t.columns);
+    if (i == 0) {
+      j.rows = kShare;
+      j.add(LIST_ACC_ITEM, kShare);
+      j.add(LIST_STORE_ACC);
+    } else if (i == 1) {
+      j.rows = kSegLen * kHiShares;
+      for (int u = 0; u < kSegLen; ++u) {
+        j.add(LIST_RUN_ITEM, kHiShares);
+        j.add(LIST_ACC_RUN);
+      }
+      j.add(LIST_STORE_ACC);
+      j.add(LIST_STORE_RUN);
+    } else if (i == 2) {
+      j.rows = 2 * kLoSegs - 1;
+      for (int q = 1; q < kLoSegs; ++q) {
+        j.add(LIST_RUN_ITEM);
+        j.add(LIST_ACC_RUN);
+      }
+      j.add(LIST_ACC_SQ, 3);  // ^8 = ^kSegLen
+      j.add(LIST_ACC_ITEM, kLoSegs);
+      j.add(LIST_STORE_ACC);
+    } else {
+      j.rows = 2 * kMaxPos;
+      for (int half = 0; half < 2 * kMaxPos; ++half) {
+        j.add(LIST_ACC_SQ, 5);
+        j.add(LIST_ACC_ITEM);
+      }
+      j.add(LIST_COLUMNS);
+    }
+    if (int rc = rns_lists(ctx, mh, j, bound[i], st)) return rc;
+  }
+  const LaunchShape sh = launch_shape(ctx, cols * 2, 2 * mh.t, 8);
+#define CALL(LPT, T)                                                                                                       \
+  HAFLO_LAUNCH((k_bk_leave<LPT, T>), sh, st, mh.ref(), (const u32*)(mh.d_pairs + (size_t)kConstMStored * 2 * mh.nl),      \
+               (const long long*)(ws + t.columns), rns_columns(mh), cols * 2, d_P)
+  HAFLO_DISPATCH_PAIRS(mh, CALL);
+#undef CALL
+  return hip_status(hipGetLastError());
+}
+}  // namespace
+
 bool xtd_buckets_fit(size_t rows, size_t cols) {
   // row indices, chunk counts and item offsets are 32-bit; the prefix sum over the 4096 keys per column
   // adds up the totals of all earlier blocks in every block, which is meant for at most a few thousand blocks
@@ -784,10 +921,12 @@ XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols, bo
   p.off_arena[0] = w; w += p1 * item;
   p.off_arena[1] = w; w += p2 * item;
   p.off_items = w;    w += residues ? (rows + 1) * item : 0;  // the ciphertexts and one
-  p.off_columns = w;  w += residues ? p.keys * 4 * (size_t)rns_columns(ctx->Nh) : 0;
   p.off_chains = w;   w += residues ? p1 * 4 : 0;
   p.off_control = w;  w += residues ? 64 : 0;
-  p.off_last = w;     w += residues ? p.keys * nl : 0;  // what the rounds leave, in the pair form
+  if (residues) w = (w + 63) & ~(size_t)63;
+  p.off_tail = w;     w += residues ? tail_plan(ctx, cols, 0).columns + cols * 8 * (size_t)rns_columns(ctx->Nh) : 0;
+  p.off_one = p.off_items + rows * item;
+  p.arena1_items = p1;
   p.off_G = w;       w += combos * kSubProducts * nl;
   p.off_AT = w;      w += combos * kSegs * 2 * nl;
   p.off_R = w;       w += combos * 2 * nl;
@@ -839,17 +978,15 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
     const LaunchShape sh = launch_shape(ctx, rows, lanes, 8);
     const u32* lo = mh.d_pairs + (size_t)(residues ? kConstMLo : kConstR4) * 2 * mh.nl;
     const u32* hi = mh.d_pairs + (size_t)(residues ? kConstMHi : kConstR5) * 2 * mh.nl;
-#define CALL(LPT, T) HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, lo, hi, d_c, rows, cp)
+#define CALL(LPT, T) HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, lo, hi, d_c, d_c, rows, rows, cp)
     HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL
   }
   const u32* items = cp;
-  const u32 *last0 = ws + p.off_arena[0], *last1 = ws + p.off_arena[1];  // what the rounds leave, after an odd and an even number
   if (residues) {
-    int rc = rns_enter(ctx, mh, cp, nullptr, rows, nullptr, ws + p.off_items, st);
+    int rc = rns_enter(ctx, mh, cp, rows, ws + p.off_items, st);
     if (rc != HAFLO_OK) return rc;
     items = ws + p.off_items;
-    last0 = last1 = ws + p.off_last;
   }
   for (int r = 0; r < p.rounds; ++r) {
     // upper bound of the chunks of this round: one lane group each, capped by the grid-stride loop
@@ -876,13 +1013,12 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
                    (const u32*)stats, ord, (uint4*)(ws + p.off_chains), control);
       RnsChains j = {};
       j.items = items;
-      j.one = ws + p.off_items + rows * rns_item_words(mh);
+      j.one = ws + p.off_one;
       j.chains = ws + p.off_chains;
       j.index = srt;
       j.control = control;
       j.next = stats + kStatNextChunk + r;
       j.out = out;
-      j.columns = (long long*)(ws + p.off_columns);
       if (int rc = rns_chains(ctx, mh, j, bound, st)) return rc;
       items = out;
       continue;
@@ -896,15 +1032,7 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
 #undef CALL_ROUND
     items = out;
   }
-  if (residues) {
-    const LaunchShape sh = launch_shape(ctx, K, lanes, 8);
-#define CALL(LPT, T)                                                                                               \
-  HAFLO_LAUNCH((k_bk_leave<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstMPair * 2 * mh.nl),       \
-               (const long long*)(ws + p.off_columns), rns_columns(mh), (const u32*)offs(0), K, cb, (const u32*)stats, \
-               ws + p.off_last)
-    HAFLO_DISPATCH_PAIRS(mh, CALL);
-#undef CALL
-  }
+  if (residues) return tail(ctx, p, cols, cnt, offs(0), stats, ws, d_P, st);
   const size_t combos = cols * kMaxPos * 2;
   u32* G = ws + p.off_G;
   u32* AT = ws + p.off_AT;
@@ -915,7 +1043,8 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
     const bool split = combos * kSubProducts * (size_t)lanes < (size_t)ctx->num_cu * 16 * WAVE;
     const LaunchShape sh = launch_shape(ctx, combos * kSubProducts * (split ? 4 : 1), lanes, 8);
 #define CALL_SUB(LPT, T, SPLIT)                                                                         \
-  HAFLO_LAUNCH((k_bk_sub<LPT, T, true, SPLIT>), sh, st, M, one, last0, last1, (const u32*)cnt, (const u32*)offs(0), K, cb, (const u32*)stats, combos, G)
+  HAFLO_LAUNCH((k_bk_sub<LPT, T, true, SPLIT>), sh, st, M, one, (const u32*)(ws + p.off_arena[0]),     \
+               (const u32*)(ws + p.off_arena[1]), (const u32*)cnt, (const u32*)offs(0), K, cb, (const u32*)stats, combos, G)
 #define CALL(LPT, T) do { if (split) CALL_SUB(LPT, T, 4); else CALL_SUB(LPT, T, 1); } while (0)
     HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL

@@ -453,11 +453,12 @@ __device__ __forceinline__ void to_pair(u32 (&x0)[LPT], u32 (&x1)[LPT], const u3
   partial_norm<LPT, T>(x0, g);
   partial_norm<LPT, T>(x1, g);
 }
+// The first `split` elements are at `in`, the others at `in2`.
 template <int LPT, int T>
 __global__ __launch_bounds__(kBlockThreads, 4) void k_to_pairs(ModRef M, const u32* __restrict__ k_lo,
                                                                const u32* __restrict__ k_hi,
-                                                               const u32* __restrict__ in, size_t count,
-                                                               u32* __restrict__ out) {
+                                                               const u32* __restrict__ in, const u32* __restrict__ in2,
+                                                               size_t split, size_t count, u32* __restrict__ out) {
   constexpr int NLH = LPT * T;
   Grp<T> g;
   Batch<T> bt;
@@ -467,7 +468,8 @@ __global__ __launch_bounds__(kBlockThreads, 4) void k_to_pairs(ModRef M, const u
     const size_t it = base + bt.gib;
     const bool active = it < count;
     u32 a0[LPT], a1[LPT];
-    to_pair<LPT, T>(a0, a1, in + (active ? it : 0) * (size_t)(2 * NLH), k_lo, k_hi, mod, g);
+    const u32* src = !active ? in : it < split ? in + it * (size_t)(2 * NLH) : in2 + (it - split) * (size_t)(2 * NLH);
+    to_pair<LPT, T>(a0, a1, src, k_lo, k_hi, mod, g);
     if (active) {
       store_limbs<LPT, T>(out + it * (size_t)(2 * NLH), a0, g);
       store_limbs<LPT, T>(out + it * (size_t)(2 * NLH) + NLH, a1, g);

@@ -451,15 +451,13 @@ __global__ __launch_bounds__(kBlockThreads) void k_xtd_finish(ModRef M, ModRef M
 // k_xw_positions, one group per (j, sign, s): T[1] = b^(256^s) by 8 s squarings. Then eight launches of
 // k_xw_level with B = 1, 2, 4, .., 128, one group per entry d in (B, 2 B]: T[d] = T[d - B] * T[B]. Every entry
 // costs one product and the chain is 8 s + 8 products long.
-// A table takes `entries` places. In the residue form two factors make an entry, T[16 h + l] = T[16 h] T[l], and the levels
-// stop at 16; four more then fill the places 17 to 30, from place 15 on, with T[32], T[48], ..., T[240].
 // PAIR: the tables are in the pair form modulo M (see Elem); the bases, stored ciphertexts, are taken into it
 // as they are loaded (k_lo, k_hi: see to_pair).
 template <int LPT, int T, bool PAIR>
 __global__ __launch_bounds__(kBlockThreads) void k_xw_positions(ModRef M, const u32* __restrict__ k_lo,
                                                                 const u32* __restrict__ k_hi,
                                                                 const u32* __restrict__ bases,
-                                                                const u32* __restrict__ invbases, size_t cols, int entries,
+                                                                const u32* __restrict__ invbases, size_t cols,
                                                                 u32* __restrict__ tables,
                                                                 const u32* __restrict__ maxmag) {
   using Ops = ElemOps<LPT, T, PAIR>;
@@ -486,14 +484,14 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_positions(ModRef M, const 
       Ops::sqr(t, mod, g);
       if (i < kWin * s) Ops::copy(x, t);
     }
-    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)entries) * EL;
+    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)kWinEntries) * EL;
     if (active) Ops::store(tb + EL, x, g);
   }
 }
 
 template <int LPT, int T, bool PAIR>
 __global__ __launch_bounds__(kBlockThreads) void k_xw_level(ModRef M, const u32* __restrict__ one, size_t cols, int B,
-                                                            int last, int entries, u32* __restrict__ tables,
+                                                            u32* __restrict__ tables,
                                                             const u32* __restrict__ maxmag) {
   using Ops = ElemOps<LPT, T, PAIR>;
   constexpr int EL = Ops::kLimbs;
@@ -502,7 +500,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_level(ModRef M, const u32*
   ModRegs<LPT> mod;
   load_mod<LPT, T>(mod, M, g);
   const int npos = (bit_length(*maxmag) + kWin - 1) / kWin;
-  const int per = B < last - B ? B : last - B;  // entries B + 1 .. min(2 B, last)
+  const int per = B < kWinEntries - 1 - B ? B : kWinEntries - 1 - B;  // entries B + 1 .. min(2 B, 255)
   const size_t count = cols * 2 * (size_t)npos * (size_t)per;
   for (size_t base = bt.first(); base < count; base += bt.stride()) {
     const size_t it = base + bt.gib;
@@ -511,7 +509,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_level(ModRef M, const u32*
     const int d = B + 1 + (active ? (int)(it - tab * (size_t)per) : 0);
     const size_t item = tab / (size_t)(npos ? npos : 1);
     const int s = (int)(tab - item * (size_t)(npos ? npos : 1));
-    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)entries) * EL;
+    u32* tb = tables + ((item * (size_t)kMaxPos + (size_t)s) * (size_t)kWinEntries) * EL;
     typename Ops::E a;
     Ops::load(a, active ? tb + (size_t)(d - B) * EL : one, g);
     Ops::mul_mem(a, active ? tb + (size_t)B * EL : one, mod, g);
@@ -519,57 +517,46 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_level(ModRef M, const u32*
   }
 }
 
-// The 30 entries of a table that k_xw_level leaves, all tables' of one position after the other, into the residue engine's
-// Montgomery form (times M_A = `enter`), and where in the whole tables of 256 entries they belong; after them the place of one.
-constexpr int kHalfEntries = 32, kHalfUsed = 30, kMixed = 225;  // places, entries, and entries that two of them make
-template <int LPT, int T>
-__global__ __launch_bounds__(kBlockThreads) void k_xw_scale(ModRef M, const u32* __restrict__ enter, size_t cols,
-                                                            const u32* __restrict__ tables, u32* __restrict__ scaled,
-                                                            u32* __restrict__ place, u32* __restrict__ total,
-                                                            const u32* __restrict__ maxmag) {
-  constexpr int EL = 2 * LPT * T;
-  using Ops = ElemOps<LPT, T, true>;
-  Grp<T> g;
-  Batch<T> bt;
-  ModRegs<LPT> mod;
-  load_mod<LPT, T>(mod, M, g);
-  const size_t count = cols * 2 * kHalfUsed * (size_t)((bit_length(*maxmag) + kWin - 1) / kWin);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *total = (u32)count;
-    place[count] = 0;  // of the first table, which has no entry there
+// The tables in the residue form are two programs (RnsLists) and one set of chains:
+//   1. c_j or its inverse (and, behind them, one): its powers to 16^q, q = 0 to 7, as far as the exponents go
+//   2. base and q: the powers to 1, .., 15 of that, T[d] (q even) or T[16 d] of position q / 2
+//   3. T[16 h + l] = T[16 h] T[l], of the last position up to the largest digit
+constexpr int kNibbles = 2 * kMaxPos, kMixed = 225;
+struct XwTablePlan {  // words from the start of the workspace
+  size_t operands, places[2], live, index, chains, control;
+};
+__global__ __launch_bounds__(kBlockThreads) void k_xw_places(u32 cols, u32* __restrict__ ws, XwTablePlan p,
+                                                             const u32* __restrict__ one, u32 limbs, u32* __restrict__ pair,
+                                                             const u32* __restrict__ maxmag) {
+  const u32 npos = (u32)((bit_length(*maxmag) + kWin - 1) / kWin), bases = cols * 2;
+  const u32 top = npos ? *maxmag >> (npos - 1) * kWin : 0;  // the largest digit of the last position
+  const u32 top_mixed = top < 17 ? 0 : (top / 16 - 1) * 15 + top % 16, mixed = npos ? bases * ((npos - 1) * kMixed + top_mixed) : 0;
+  const u32 at = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  if (at == 0) {
+    u32* live = ws + p.live;
+    live[0] = bases + 1;
+    live[1] = bases * 2 * npos;
+    live[2] = npos ? 2 + 5 * (2 * npos - 1) : 2;  // of the first program's instructions
+    ws[p.control + kChainsTotal] = mixed;
+    ws[p.control + kChainsColumns] = 0;
   }
-  for (size_t base = bt.first(); base < count; base += bt.stride()) {
-    const size_t it = base + bt.gib;
-    const bool active = it < count;
-    const size_t tab = active ? it / kHalfUsed : 0;  // s * 2 cols + j * 2 + sign
-    const int t = active ? (int)(it - tab * kHalfUsed) + 1 : 1;
-    const size_t at = tab % (cols * 2) * kMaxPos + tab / (cols * 2);
-    typename Ops::E a;
-    Ops::load(a, tables + (at * kHalfEntries + (size_t)t) * EL, g);
-    Ops::mul_mem(a, enter, mod, g);
-    if (active) {
-      Ops::store(scaled + it * EL, a, g);
-      if (g.k == 0) place[it] = (u32)(at * kWinEntries) + (u32)(t < 16 ? t : 16 * (t - 15));
-    }
+  for (u32 i = at; i < limbs; i += step) pair[i] = one[i];
+  // the powers: of the bases, of the inverses, of one
+  for (u32 i = at; i < (bases + 1) * kNibbles; i += step) ws[p.places[0] + i] = i % (bases + 1) * kNibbles + i / (bases + 1);
+  for (u32 i = at; i < bases * kNibbles; i += step) {
+    const u32 e = i % bases, q = i / bases;  // e: 2 j + sign
+    ws[p.operands + i] = (e / 2 + e % 2 * cols) * kNibbles + q;
+    for (u32 d = 1; d < 16; ++d)
+      ws[p.places[1] + (size_t)(d - 1) * bases * kNibbles + i] = (e * kMaxPos + q / 2) * kWinEntries + (q % 2 ? 16 * d : d);
   }
-}
-
-// The other entries of the tables as chains (see rns_chains) of the two they are made of
-__global__ __launch_bounds__(kBlockThreads) void k_xw_mixed(size_t cols, uint4* __restrict__ chains,
-                                                            u32* __restrict__ index, u32* __restrict__ control,
-                                                            const u32* __restrict__ maxmag) {
-  const size_t count = cols * 2 * kMixed * (size_t)((bit_length(*maxmag) + kWin - 1) / kWin);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    control[kChainsTotal] = (u32)count;
-    control[kChainsColumns] = 0;
-  }
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t tab = i / kMixed;
-    const u32 r = (u32)(i - tab * kMixed), high = 16 * (r / 15 + 1), low = r % 15 + 1;
-    const u32 at = (u32)((tab % (cols * 2) * kMaxPos + tab / (cols * 2)) * kWinEntries);
-    index[2 * i] = at + high;
-    index[2 * i + 1] = at + low;
-    chains[i] = make_uint4(at + high + low, (u32)(2 * i), 2u, 0u);
+  for (u32 i = at; i < mixed; i += step) {
+    const u32 full = bases * (npos - 1) * kMixed;
+    const u32 tab = i < full ? i / kMixed : bases * (npos - 1) + (i - full) / top_mixed;
+    const u32 r = i < full ? i % kMixed : (i - full) % top_mixed, high = 16 * (r / 15 + 1), low = r % 15 + 1;
+    const u32 t = (tab % bases * kMaxPos + tab / bases) * kWinEntries;
+    ws[p.index + 2 * (size_t)i] = t + high;
+    ws[p.index + 2 * (size_t)i + 1] = t + low;
+    ((uint4*)(ws + p.chains))[i] = make_uint4(t + high + low, 2 * i, 2u, 0u);
   }
 }
 
@@ -894,8 +881,9 @@ struct XwPlan {
   // [kXwBinsAt, kXwBinsAt + kLenBins) the length classes
   size_t off_inv, off_tables, off_nz, off_cnt, off_order, off_partial, total;
   int seg_shift;  // every row's list is multiplied in 2^seg_shift segments
-  // in the residue form the limb tables are halves, and words 2 and 3 are counters too, 8 to 15 what the chains' lengths are
-  size_t off_scaled, off_place, off_index, off_chains, off_items, off_columns;
+  // in the residue form words 2 and 3 are counters too, from 8 on what the device finds about programs and chains
+  size_t off_pairs, off_powers, off_chains, off_items, off_columns;
+  XwTablePlan tables;
 };
 constexpr size_t kXwControlAt = 8;
 constexpr size_t kXwBinsAt = 64;
@@ -920,8 +908,7 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.total = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * nl : 0);
   return p;
 }
-// Tables and rows in the residue form. Besides the products themselves (see xtd_buckets_in_residues) the tables take less:
-// 30 of their 255 entries on limbs, the rest one product in residues each. Whole calls on limbs / in residues, ms, 70 % zeros:
+// Tables and rows in the residue form. Whole calls on limbs / in residues, ms, 70 % zeros:
 // 1000 by 256 1.17 / 1.27, 4096 by 64 0.77 / 0.80, 16384 by 16 0.69 / 0.73, 60000 by 7 0.83 / 0.77, 65536 by 32 1.77 / 1.10, 16384
 // by 256 3.55 / 1.93. List places and table entries are 32-bit.
 bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
@@ -941,15 +928,22 @@ XwPlan xw_residue_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.seg_shift = xw_residue_shift(ctx, rows, cols);
   const size_t chains = (rows << p.seg_shift) + (p.seg_shift ? rows : 0);
   p.off_inv = kXwBinsAt + kLenBins;
-  p.off_tables = p.off_inv + cols * nl;
-  p.off_scaled = p.off_tables + tabs * kHalfEntries * nl;
-  p.off_place = p.off_scaled + tabs * kHalfUsed * nl;
-  p.off_index = p.off_place + tabs * kHalfUsed + 1;
-  p.off_nz = p.off_index + tabs * kMixed * 2;
+  p.off_pairs = p.off_inv + cols * nl;
+  size_t at = p.off_pairs + (cols * 2 + 1) * nl;
+  const size_t words[4] = {cols * 2 * kNibbles, (cols * 2 + 1) * kNibbles, cols * 2 * kNibbles * 15, tabs * kMixed * 2};
+  size_t* const parts[4] = {&p.tables.operands, &p.tables.places[0], &p.tables.places[1], &p.tables.index};
+  for (int i = 0; i < 4; ++i) {
+    *parts[i] = at;
+    at += words[i];
+  }
+  p.tables.control = kXwControlAt;
+  p.tables.live = kXwControlAt + 3 * kChainsControl;
+  p.off_nz = at;
   p.off_cnt = p.off_nz + rows * cols * kMaxPos;
   p.off_order = p.off_cnt + rows;
-  p.off_chains = aligned(p.off_order + rows);
-  p.off_items = aligned(p.off_chains + std::max(tabs * kMixed, chains) * 4);
+  p.off_chains = p.tables.chains = aligned(p.off_order + rows);
+  p.off_powers = aligned(p.off_chains + std::max(tabs * kMixed, chains) * 4);
+  p.off_items = p.off_powers + (cols * 2 + 1) * kNibbles * item;
   p.off_partial = p.off_items + tabs * kWinEntries * item;
   p.off_columns = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * item : 0);
   p.total = p.off_columns + rows * 4 * (size_t)rns_columns(ctx->Nh);
@@ -968,6 +962,61 @@ size_t ws_xtd_min(const haflo_ctx* ctx, size_t rows, size_t cols) {
 size_t ws_xtd_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
   if (!cols || !use_buckets(ctx, rows, cols) || !xtd_buckets_in_residues(ctx, rows, cols)) return 0;
   return xtd_bucket_layout(ctx, rows, cols, true).total * 4 + 256;  // its start is aligned to 256 bytes
+}
+
+// The tables of 256 entries per base and position, and `chains` as the rows' products need it
+int xw_residue_tables(const haflo_ctx* ctx, const XwPlan& p, const u32* d_c, size_t cols, u32* ws, RnsChains& chains,
+                      hipStream_t st) {
+  const ModHost& mh = ctx->Nh;
+  const size_t tabs = cols * 2 * kMaxPos;
+  const XwTablePlan& t = p.tables;
+  const LaunchShape sh = launch_shape(ctx, cols * 2, 2 * mh.t, 8);
+  const u32* lo = mh.d_pairs + (size_t)kConstMLo * 2 * mh.nl;
+  const u32* hi = mh.d_pairs + (size_t)kConstMHi * 2 * mh.nl;
+  u32* pairs = ws + p.off_pairs;
+#define CALL(LPT, T) \
+  HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, mh.ref(), lo, hi, d_c, (const u32*)(ws + p.off_inv), cols, cols * 2, pairs)
+  HAFLO_DISPATCH_PAIRS(mh, CALL);
+#undef CALL
+  HAFLO_LAUNCH(k_xw_places, launch_shape(ctx, tabs * kMixed, 1, 8), st, (u32)cols, ws, t,
+               (const u32*)(mh.d_pairs + (size_t)kConstMOne * 2 * mh.nl), (u32)(2 * mh.nl), pairs + cols * 4 * mh.nl, (const u32*)ws);
+  const u32* one = ws + p.off_powers + cols * 2 * kNibbles * rns_item_words(mh);
+  for (int i = 0; i < 2; ++i) {
+    RnsLists j = {};
+    j.items = ws + p.off_powers;
+    j.one = one;
+    j.operands = ws + t.operands;
+    j.places = ws + t.places[i];
+    j.stride = i ? cols * 2 * kNibbles : cols * 2 + 1;
+    j.rows = i;
+    j.live = ws + t.live + i;
+    j.out = ws + (i ? p.off_items : p.off_powers);
+    if (i == 0) {
+      j.limit = ws + t.live + 2;
+      j.limbs = pairs;
+      j.add(LIST_ACC_LIMBS);
+      j.add(LIST_STORE_ACC);
+      for (int q = 1; q < kNibbles; ++q) {
+        j.add(LIST_ACC_SQ, 4);
+        j.add(LIST_STORE_ACC);
+      }
+    } else {
+      j.add(LIST_RUN_ITEM);
+      for (int d = 1; d < 16; ++d) {
+        j.add(LIST_ACC_RUN);
+        j.add(LIST_STORE_ACC);
+      }
+    }
+    if (int rc = rns_lists(ctx, mh, j, j.stride, st)) return rc;
+  }
+  chains.items = ws + p.off_items;
+  chains.one = one;
+  chains.chains = ws + t.chains;
+  chains.index = ws + t.index;
+  chains.control = ws + t.control;
+  chains.next = ws + 2;
+  chains.out = ws + p.off_items;
+  return rns_chains(ctx, mh, chains, tabs * kMixed, st);
 }
 
 int sum_blocks(const haflo_ctx* ctx, size_t count) {
@@ -1146,6 +1195,12 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
     if (cols) {
       rc = invert_batch(ctx, (const u32*)d_c, inv, cols, st);
       if (rc != HAFLO_OK) return rc;
+    }
+    RnsChains chains = {};
+    if (residues) {
+      rc = xw_residue_tables(ctx, p, (const u32*)d_c, cols, ws, chains, st);
+      if (rc != HAFLO_OK) return rc;
+    } else if (cols) {
       // The squarings and the first levels are as many products as there are launches and positions, on few pairs: the
       // latency of a product bounds them, so a wavefront for each pair while launch_pairs allows. 1000 rows by 32 columns
       // 0.40 -> 0.35 ms at 1024 bits and 0.74 -> 0.65 at 2048, 300 by 32 at 4096 bits 1.57 -> 1.42, 16384 by 256 at 2048
@@ -1156,45 +1211,17 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
 #define CALL(LPT, T)                                                                                                \
   HAFLO_LAUNCH((k_xw_positions<LPT, T, true>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstR4 * 2 * mh.nl), \
                (const u32*)(mh.d_pairs + (size_t)kConstR5 * 2 * mh.nl), (const u32*)d_c, (const u32*)inv, cols,     \
-               residues ? kHalfEntries : kWinEntries, tables, (const u32*)ws)
+               tables, (const u32*)ws)
         HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
       }
-      for (int part = 0; part < (residues ? 2 : 1); ++part) {
-        const int entries = residues ? kHalfEntries : kWinEntries, last = !residues ? kWinEntries - 1 : part ? 15 : 16;
-        u32* from = tables + (size_t)(part * 15) * 2 * mh.nl;
-        for (int B = 1; B < last; B *= 2) {
-          const size_t groups = cols * 2 * kMaxPos * (size_t)std::min(B, last - B);
-          const LaunchShape sh = launch_pairs(ctx, mh, groups, lanes, wave);
-#define CALL(LPT, T) HAFLO_LAUNCH((k_xw_level<LPT, T, true>), sh, st, M, one, cols, B, last, entries, from, (const u32*)ws)
-          HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
+      for (int B = 1; B < kWinEntries; B *= 2) {
+        const size_t groups = cols * 2 * kMaxPos * (size_t)std::min(B, kWinEntries - 1 - B);
+        const LaunchShape sh = launch_pairs(ctx, mh, groups, lanes, wave);
+#define CALL(LPT, T) HAFLO_LAUNCH((k_xw_level<LPT, T, true>), sh, st, M, one, cols, B, tables, (const u32*)ws)
+        HAFLO_DISPATCH_PAIRS_FEW(mh, wave, CALL);
 #undef CALL
-        }
       }
-    }
-    RnsChains chains = {};
-    if (residues) {
-      const size_t tabs = cols * 2 * kMaxPos;
-      u32* place = ws + p.off_place;
-      u32* total = ws + kXwControlAt;
-      const LaunchShape sh = launch_shape(ctx, tabs * kHalfUsed, lanes, 8);
-#define CALL(LPT, T)                                                                                          \
-  HAFLO_LAUNCH((k_xw_scale<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstMOne * 2 * mh.nl), cols, \
-               (const u32*)tables, ws + p.off_scaled, place, total, (const u32*)ws)
-      HAFLO_DISPATCH_PAIRS(mh, CALL);
-#undef CALL
-      rc = rns_enter(ctx, mh, ws + p.off_scaled, total, tabs * kHalfUsed, place, ws + p.off_items, st);
-      if (rc != HAFLO_OK) return rc;
-      chains.items = chains.one = ws + p.off_items;
-      chains.chains = ws + p.off_chains;
-      chains.index = ws + p.off_index;
-      chains.control = ws + kXwControlAt + kChainsControl;
-      chains.next = ws + 2;
-      chains.out = ws + p.off_items;
-      HAFLO_LAUNCH(k_xw_mixed, launch_shape(ctx, tabs * kMixed, 1, 8), st, cols, (uint4*)(ws + p.off_chains),
-                   ws + p.off_index, ws + kXwControlAt + kChainsControl, (const u32*)ws);
-      rc = rns_chains(ctx, mh, chains, tabs * kMixed, st);
-      if (rc != HAFLO_OK) return rc;
     }
     u32* bins = ws + kXwBinsAt;
     u32* order = ws + p.off_order;
@@ -1212,7 +1239,7 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
     }
     u32* partial = ws + p.off_partial;
     if (residues) {
-      u32* control = ws + kXwControlAt + 2 * kChainsControl;
+      u32* control = ws + kXwControlAt + kChainsControl;
       HAFLO_LAUNCH(k_xw_chains, launch_shape(ctx, rows << p.seg_shift, 1, 8), st, rows, cols * (size_t)kMaxPos, p.seg_shift,
                    (const u32*)cnt, (const u32*)order, (uint4*)(ws + p.off_chains), control, control + kChainsControl);
       chains.index = lists;

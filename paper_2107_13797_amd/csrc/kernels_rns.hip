@@ -1059,12 +1059,10 @@ __global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsig
 
 // Products of lists of elements, each in memory by itself as [base A, base B][quad][lane group] (rns_item_words()): a lane
 // group's four lanes read 64 consecutive bytes, 18 times, from wherever the element lies.
-// Into that form: lazy limb pairs as in RnsJob::in, element i to place[i] (null: i); `last` is the element after them. `total`:
-// where the device finds their number, null: `count`.
+// Into that form: lazy limb pairs as in RnsJob::in; `last` is the element after them.
 template <int NR>
 __global__ __launch_bounds__(1024, 4) void k_rns_enter(const u32* __restrict__ tables, const u32* __restrict__ in,
-                                                       const u32* __restrict__ last, const u32* __restrict__ total,
-                                                       size_t count, int nl, const u32* __restrict__ place,
+                                                       const u32* __restrict__ last, size_t count, int nl,
                                                        u32* __restrict__ items) {
   __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
   for (int i = (int)threadIdx.x; i < rns::lds_bytes(NR) / 16; i += (int)blockDim.x)
@@ -1073,13 +1071,12 @@ __global__ __launch_bounds__(1024, 4) void k_rns_enter(const u32* __restrict__ t
   OneEngine<NR> e(lds);
   const unsigned waves = blockDim.x / WAVE;
   const size_t wave = (size_t)blockIdx.x * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-  if (total) count = *total;
   const size_t all = count + 1;
   for (size_t tile = wave; tile * 16 < all; tile += (size_t)gridDim.x * waves) {
     const size_t own = tile * 16 + (threadIdx.x & 15);
     OneState<NR> x;
     e.load_own(x, own < count ? in + own * (size_t)(2 * nl) : last, own < all, nl, (const char*)tables + rns::lds_bytes(NR));
-    if (own < all) e.template store_state<4>(x, items + (place ? place[own] : own) * (size_t)rns::item_words(NR));
+    if (own < all) e.template store_state<4>(x, items + own * (size_t)rns::item_words(NR));
   }
 }
 
@@ -1111,7 +1108,9 @@ __global__ __launch_bounds__(768, 3) void k_rns_chains(RnsChains j) {
     const auto element = [&](u32 i, u32 at) {
       return i < len ? j.items + (size_t)at * rns::item_words(NR) : j.one;
     };
-    const u32 longest = (u32)__builtin_amdgcn_readfirstlane((int)wave_max(len));
+    u32 longest = (u32)__builtin_amdgcn_readfirstlane((int)wave_max(len));
+    // An element as it lies in memory need not have alpha in its slot, which the way out takes: what leaves has been a product.
+    if (columns && longest < 2) longest = 2;
     OneState<NR> x;
     e.template load_state<4>(x, element(0, item(0)));
     u32 next = item(1);
@@ -1135,17 +1134,19 @@ __global__ __launch_bounds__(768, 3) void k_rns_chains(RnsChains j) {
 }
 
 // What the wavefronts of a block of k_rns_group share, whichever tiles they have.
-template <int NR, int HALVES>
+// LISTS: of k_rns_lists, whose registers go to two values and an operand on its way: its constants lie in LDS.
+template <int NR, int HALVES, bool LISTS>
 struct GroupShared {
   static constexpr int kBlocks = (NR + 3) / 4;  // of 64 bytes, the last one partly empty
   // Matrices stay in registers; those of 4096-bit moduli stream from L2, but for three of nine blocks: of the first one in
   // registers, of the second one in LDS, where the constants are as well.
   static constexpr bool kHeld = NR != 36;
   static constexpr int kStay = kHeld ? 0 : 3;
+  static constexpr bool kHeldCst = kHeld && !LISTS;
   Quad bytes[2][HALVES][kBlocks][WAVE];  // [sigma, rho][x0, x1][block][lane]
   Quad sum[3][HALVES][16];               // alpha's sums over lane group 0 .. 3's slots, of the last, the present and the next rho
   Acc resident[kStay][kHeld ? 1 : rns::tiles(NR)][WAVE];
-  Quad cst[kHeld ? 0 : 2][rns::slots(NR)];
+  Quad cst[kHeldCst ? 0 : 2][rns::slots(NR)];
 };
 
 // The same arithmetic with the slots of 16 elements spread over the W wavefronts of a block, TW tiles each, for
@@ -1167,21 +1168,22 @@ struct GroupShared {
 // not fill the chip with blocks of 16: half the matrix instructions and operand reads per product. A lane then has one half
 // of a pair; x1's lanes take the first half's values by DPP, x0's run through the same instructions with zeros in place.
 // W wavefronts, TILES tiles in all.
-template <int NR, int TW, int W, int TILES, bool PAIR, bool FOLD>
+template <int NR, int TW, int W, int TILES, bool PAIR, bool FOLD, bool LISTS = false>
 struct RnsGroup {
   static constexpr bool kBoth = PAIR && !FOLD;  // x0 and x1 in one lane
   static constexpr int kHalves = kBoth ? 2 : 1;
   static constexpr int kElements = FOLD ? 8 : 16;
+  static constexpr int kRegs = NR, kOwn = TW;
   static constexpr int kTiles = rns::tiles(NR);
   static constexpr int kLimbTiles = rns::limb_tiles(NR);
   static constexpr bool kClearLate = NR <= 10;  // where alpha's old sums are cleared, see publish()
-  using Shared = GroupShared<NR, kHalves>;
+  using Shared = GroupShared<NR, kHalves, LISTS>;
   static constexpr int kBlocks = Shared::kBlocks;
   static constexpr int kFull = rns::full_blocks(NR);
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
   // kAhead of the blocks that stream are on their way at any time, also across the barriers that the operands wait for; the
   // resident ones are multiplied in between.
-  static constexpr bool kHeld = Shared::kHeld;
+  static constexpr bool kHeld = Shared::kHeld, kHeldCst = Shared::kHeldCst;
   static constexpr int kStay = Shared::kStay, kAhead = 2, kStream = kBlocks - kStay;
   static_assert(kHeld || kStream % kAhead == 0, "a matrix begins where the other one ends");
   static_assert(TILES >= kLimbTiles, "every tile has a wavefront");
@@ -1193,7 +1195,7 @@ struct RnsGroup {
   const char* tables;
   int lane, g, wave, own_tile, turn;  // own_tile: the first of TW
   Acc start;
-  Quad held_cst[2][kHeld ? TW : 1];  // the constants of this lane's slots in base A and base B
+  Quad held_cst[2][kHeldCst ? TW : 1];  // the constants of this lane's slots in base A and base B
   u32 second;           // FOLD: all ones in x1's lanes
   Frags held[kHeld ? 2 : 1];
   QuadSet<kHeld ? 1 : kStay * TW> part;
@@ -1205,7 +1207,7 @@ struct RnsGroup {
   // this lane holds a prime's residue (not one of the extra values) in tile i
   __device__ __forceinline__ bool owns(int i) const { return mine(i) && 4 * tile(i) + g < rns::primes_for(NR); }
 
-  __device__ __forceinline__ Quad cst(int base, int i) const { return kHeld ? held_cst[base][kHeld ? i : 0] : sh.cst[kHeld ? 0 : base][4 * tile(i) + g]; }
+  __device__ __forceinline__ Quad cst(int base, int i) const { return kHeldCst ? held_cst[base][kHeldCst ? i : 0] : sh.cst[kHeldCst ? 0 : base][4 * tile(i) + g]; }
 
   // FOLD: x0's value for both halves; and for x1's lanes only, zero in x0's
   static __device__ __forceinline__ u32 of_first(u32 v) {
@@ -1230,11 +1232,11 @@ struct RnsGroup {
         wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))), own_tile(own_tile_), turn(0), start(start_sums(kHeld)),
         second(FOLD && (threadIdx.x & 8) ? ~0u : 0u) {
     const char* from = tables + rns::lds_matrices_bytes(NR);
-    if (kHeld)
+    if (kHeldCst)
 #pragma unroll
       for (int i = 0; i < TW; ++i)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) held_cst[b][kHeld ? i : 0] = *(const Quad*)(from + (2 * b * rns::slots(NR) + 4 * tile(i) + g) * 16);
+        for (int b = 0; b < 2; ++b) held_cst[b][kHeldCst ? i : 0] = *(const Quad*)(from + (2 * b * rns::slots(NR) + 4 * tile(i) + g) * 16);
     if (kHeld)
 #pragma unroll
       for (int mat = 0; mat < 2; ++mat)
@@ -1245,9 +1247,9 @@ struct RnsGroup {
             held[mat].q[i * kBlocks + k] = fragment(tables + mat * rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, mat), i, k, (unsigned)lane);
     for (int i = (int)threadIdx.x; i < (int)(sizeof(Shared) / 4); i += (int)blockDim.x) ((u32*)&sh)[i] = 0;
     __syncthreads();
-    if (!kHeld)
+    if (!kHeldCst)
       for (int i = (int)threadIdx.x; i < 2 * rns::slots(NR); i += (int)blockDim.x)
-        sh.cst[kHeld ? 0 : i / rns::slots(NR)][i % rns::slots(NR)] = *(const Quad*)(from + (i + i / rns::slots(NR) * rns::slots(NR)) * 16);
+        sh.cst[kHeldCst ? 0 : i / rns::slots(NR)][i % rns::slots(NR)] = *(const Quad*)(from + (i + i / rns::slots(NR) * rns::slots(NR)) * 16);
     set_bias();
     if (!kHeld)
 #pragma unroll
@@ -1404,11 +1406,17 @@ struct RnsGroup {
   // x times the table entry y, or (null) squared
   template <bool SQ>
   __device__ __forceinline__ void multiply(State& x, const u32* y) {
-    u32 z[TW], w[TW];
     Quad v[TW];
 #pragma unroll
+    for (int i = 0; i < TW; ++i) v[i] = SQ ? own(x, i) : entry(y, i);
+    multiply<SQ>(x, v, [] {});
+  }
+  // `meanwhile` asks for what the next product takes, behind this one's first barrier
+  template <bool SQ, class F>
+  __device__ __forceinline__ void multiply(State& x, const Quad (&v)[TW], const F& meanwhile) {
+    u32 z[TW], w[TW];
+#pragma unroll
     for (int i = 0; i < TW; ++i) {
-      v[i] = SQ ? own(x, i) : entry(y, i);
       const Quad k = cst(0, i);
       u32 s0, s1;
       residues<SQ>(s0, s1, x.a0[i], kBoth ? x.a1[i] : 0u, v[i][0], v[i][1], k[0], k[1], k[2]);
@@ -1416,6 +1424,7 @@ struct RnsGroup {
       if constexpr (kBoth) put(0, 1, i, s1);
     }
     __syncthreads();
+    meanwhile();
     // base B's share is not needed before the matrix product's result
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
@@ -1496,6 +1505,40 @@ struct RnsGroup {
     if constexpr (kBoth) return *(const Quad*)entry_at(entry, i);
     const Twin v = *(const Twin*)entry_at(entry, i);
     return Quad{v[0], 0, v[1], 0};
+  }
+  // The same of an element in memory by itself (see item_words): where the word of this lane's half (kBoth: of half x) is
+  __device__ __forceinline__ int item_at(int base, int x, int i) const {
+    const int t = tile(i), half = kBoth ? x : lane >> 3 & 1;
+    const int quad = t < 4 * kFull ? 2 * (t / 4) + half : 2 * kFull, word = t < 4 * kFull ? t % 4 : 2 * half + t % 4;
+    return base * (rns::item_words(NR) / 2) + (quad * 4 + g) * 4 + word;
+  }
+  __device__ __forceinline__ void load_item(Quad (&v)[TW], const u32* item) const {
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+      v[i] = Quad{item[item_at(0, 0, i)], kBoth ? item[item_at(0, 1, i)] : 0u, item[item_at(1, 0, i)], kBoth ? item[item_at(1, 1, i)] : 0u};
+  }
+  __device__ __forceinline__ void store_item(const State& x, u32* item) const {
+#pragma unroll
+    for (int i = 0; i < TW; ++i) {
+      if (!mine(i)) continue;
+      item[item_at(0, 0, i)] = x.a0[i];
+      item[item_at(1, 0, i)] = x.b0[i];
+      if constexpr (kBoth) {
+        item[item_at(0, 1, i)] = x.a1[i];
+        item[item_at(1, 1, i)] = x.b1[i];
+      }
+    }
+  }
+  static __device__ __forceinline__ void set(State& x, const Quad (&v)[TW]) {
+#pragma unroll
+    for (int i = 0; i < TW; ++i) {
+      x.a0[i] = v[i][0];
+      x.b0[i] = v[i][2];
+      if constexpr (kBoth) {
+        x.a1[i] = v[i][1];
+        x.b1[i] = v[i][3];
+      }
+    }
   }
   __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
 #pragma unroll
@@ -1589,6 +1632,111 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group(R
     RUN(Rest, W * TW + (wave - W) * TW1);
   }
 #undef RUN
+}
+
+// RnsLists' program on 8 elements at a time, for what is few and has long chains. All wavefronts take the same way through
+// it: each knows every element's operands, whose places lie in LDS. An operand is on its way one product ahead. What bounds
+// it is a product's chain from barrier to barrier, 1 to 1.5 us at 2048 bits; a wavefront to a pair on limbs takes 8.
+struct ListShared {
+  u32 place[kListRows][16];
+};
+template <class G>
+__device__ __forceinline__ void run_lists(G& e, const RnsLists& j, ListShared& sh, u32 ops) {
+  // scalars, all of them: the way through the program is the same for all lanes
+  const unsigned count = (unsigned)__builtin_amdgcn_readfirstlane((int)*j.live);
+  const int limit = j.limit ? __builtin_amdgcn_readfirstlane((int)*j.limit) : kListOps;
+  const int len = j.len < limit ? j.len : limit;
+  for (unsigned first = blockIdx.x * G::kElements; first < count; first += gridDim.x * G::kElements) {
+    const unsigned left = std::min(count - first, (unsigned)G::kElements);
+    const unsigned own = (unsigned)(e.lane & (G::kElements - 1));
+    __syncthreads();  // the places before have been read
+    for (int i = (int)threadIdx.x; i < j.rows * G::kElements; i += (int)blockDim.x) {
+      const unsigned r = (unsigned)i / G::kElements, l = (unsigned)i % G::kElements;
+      sh.place[r][l] = l < left ? j.operands[r * j.stride + first + l] : kNoOperand;
+    }
+    __syncthreads();
+    int row = 0;
+    const auto next_place = [&]() { return sh.place[row < j.rows ? row : j.rows - 1][own]; };
+    const auto item = [&](u32 p) { return p == kNoOperand ? j.one : j.items + (size_t)p * rns::item_words(G::kRegs); };
+    const u32* place = j.places + first;
+    typename G::State run = {}, acc = {};
+    bool run_one = true, acc_one = true;  // known to be one in all elements
+    Quad next[G::kOwn];
+    u32 p = j.rows ? next_place() : kNoOperand;
+    e.load_item(next, item(p));
+#pragma unroll 1
+    for (int pc = 0; pc < len; ++pc) {
+      const u32 op = (u32)__builtin_amdgcn_readlane((int)ops, pc / 8) >> pc % 8 * 4 & 15u;
+      const bool on_run = op == LIST_RUN_ITEM || op == LIST_STORE_RUN;
+      typename G::State x = on_run ? run : acc;
+      const bool x_one = on_run ? run_one : acc_one;
+      if (op <= LIST_ACC_SQ) {
+        const bool from_item = op <= LIST_ACC_ITEM;
+        Quad y[G::kOwn];
+        bool y_one = op == LIST_ACC_RUN ? run_one : acc_one;
+        if (from_item) {
+          y_one = __builtin_amdgcn_ballot_w64(p != kNoOperand) == 0;
+          ++row;
+          p = next_place();
+        }
+#pragma unroll
+        for (int i = 0; i < G::kOwn; ++i) {
+          const Quad o = e.own(op == LIST_ACC_RUN ? run : acc, i);
+          y[i] = from_item ? next[i] : o;
+        }
+        if (y_one || x_one) {
+          e.load_item(next, item(p));
+          if (y_one) continue;
+          e.set(x, y);
+        } else {
+          e.template multiply<false>(x, y, [&] { e.load_item(next, item(p)); });
+        }
+        if (on_run) {
+          run = x;
+          run_one = false;
+        } else {
+          acc = x;
+          acc_one = false;
+        }
+        continue;
+      }
+      if (op == LIST_ACC_LIMBS) {
+        e.load(acc, j.limbs + (size_t)first * (2 * j.nl), left, j.nl);
+        acc_one = false;
+        continue;
+      }
+      if (x_one) {
+        Quad one[G::kOwn];
+        e.load_item(one, j.one);
+        e.set(x, one);
+      }
+      if (op == LIST_COLUMNS) {
+        e.store(x, j.columns + first * (size_t)(8 * G::kLimbTiles), left);
+      } else {
+        if (own < left) e.store_item(x, j.out + (size_t)(j.places ? place[own] : first + own) * rns::item_words(G::kRegs));
+        place += j.stride;
+      }
+    }
+  }
+}
+template <int NR, int TW, int W, int TW1, int W1, bool FOLD>
+__global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_lists(RnsLists j) {
+  using Main = RnsGroup<NR, TW, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
+  using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
+  __shared__ __align__(16) typename Main::Shared shared;
+  __shared__ ListShared lists;
+  if ((size_t)blockIdx.x * Main::kElements >= *j.live) return;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  u32 ops = 0;  // in the lanes of a register, as an index that varies would cost a copy of the arguments
+#pragma unroll
+  for (int i = 0; i < kListOps / 8; ++i) ops = (threadIdx.x & (WAVE - 1)) == i ? j.ops[i] : ops;
+  if (W1 == 0 || wave < W) {
+    Main e(shared, j.tables, wave * TW);
+    run_lists(e, j, lists, ops);
+  } else if constexpr (W1 > 0) {  // as many barriers, see k_rns_group
+    Rest e(shared, j.tables, W * TW + (wave - W) * TW1);
+    run_lists(e, j, lists, ops);
+  }
 }
 
 }  // namespace
@@ -1685,11 +1833,27 @@ LaunchShape rns_shape(const haflo_ctx* ctx, size_t count, size_t most) {
 }
 }  // namespace
 
-int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, const uint32_t* total, size_t count,
-              const uint32_t* place, uint32_t* items, hipStream_t st) {
+int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, size_t count, uint32_t* items, hipStream_t st) {
   if (rns::regs_for(m.nl) != 18) return HAFLO_EINVAL;
   const u32* one = m.d_pairs + (size_t)kConstMOne * 2 * m.nl;
-  HAFLO_LAUNCH((k_rns_enter<18>), rns_shape(ctx, count + 1, 16), st, (const u32*)m.d_rns, in, one, total, count, m.nl, place, items);
+  HAFLO_LAUNCH((k_rns_enter<18>), rns_shape(ctx, count + 1, 16), st, (const u32*)m.d_rns, in, one, count, m.nl, items);
+  return hip_status(hipGetLastError());
+}
+
+int rns_lists(const haflo_ctx* ctx, const ModHost& m, RnsLists j, size_t bound, hipStream_t st) {
+  const int nr = rns::regs_for(m.nl);
+  // always 8 elements to a block: with 16 the matrices, two values and an operand on its way do not fit the registers (26
+  // spilled; 12288 sub-products' shares of 8 factors 160 us, 120 so)
+  const unsigned blocks = (unsigned)std::max(group_blocks(ctx, nr, bound, 1, true), (size_t)1);
+  j.tables = m.d_rns;
+  j.nl = m.nl;
+#define GROUP(NR, TW, W, TW1, W1) \
+  hipLaunchKernelGGL((k_rns_lists<NR, TW, W, TW1, W1, true>), dim3(blocks), dim3((W + W1) * 64), 0, st, j)
+  switch (nr) {
+    case 18: GROUP(18, 2, 8, 1, 2); break;
+    default: return HAFLO_EINVAL;
+  }
+#undef GROUP
   return hip_status(hipGetLastError());
 }
 

@@ -56,7 +56,7 @@ constexpr int lds_matrices_bytes(int nr) { return lds_matrix_bytes(nr, 0) + lds_
 constexpr int in_matrix_bytes(int nr) { return tiles(nr) * tile_bytes(nr, 16); }
 constexpr int out_matrix_bytes(int nr) { return limb_tiles(nr) * tile_bytes(nr, 16); }
 // an element in memory by itself: the quads of x0's and x1's registers, of both bases, for four lanes
-constexpr int item_words(int nr) { return 2 * (2 * (nr / 4) + 1) * 4 * 4; }
+constexpr int item_words(int nr) { return 2 * (2 * (nr / 4) + (nr % 4 ? 1 : 0)) * 4 * 4; }
 // constants of a slot: base A {p, -1/p, e, 0}, base B {p, -1/p, e, 0} for products and {p, -1/p, kappa, -e} for sums
 constexpr int cst_bytes(int nr) { return 3 * slots(nr) * 16; }
 

@@ -213,6 +213,7 @@ def test_forward_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
         x[np.random.default_rng(3).random(x.shape) < 0.6] = 0
     if kind == "zero":
         x[:] = 0
+        x[5, 0], x[40, 0] = 255, -16  # lists of one entry
     want = O.matvec(O.PrivateKey(p, q).public, 1, cs, x.tolist())
     for room in ("asked", "least"):
         assert matvec(lib, ctx, bits, 1, cs, x, room) == want, room

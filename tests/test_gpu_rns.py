@@ -239,7 +239,9 @@ def test_forward_matvec_in_residues_matches_limb_arithmetic(rows, cols, top):
     ctx = api.haflo_ctx_create_public(p * q, bits)
     c = random_ciphertexts(api, ctx, p * q, bits, cols)
     x = exponents(rows, cols, top, rows)
-    x[5] = 0  # an empty list
+    x[5] = 0  # an empty list, and lists of one entry
+    x[64:128] = 0
+    x[64:128, 0] = torch.arange(-32, 32, dtype=torch.int32, device="cuda")
     if top < 256:
         x[x.abs() > 4 * 1024] = 7  # one digit throughout
     assert torch.equal(api.haflo_cipher_matvec(ctx, 1, c, x), matvec_on_limbs(api, ctx, 1, c, x))
