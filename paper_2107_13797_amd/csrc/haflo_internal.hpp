@@ -228,11 +228,11 @@ RnsBuffers rns_buffers(const haflo_ctx* ctx, const ModHost& m, size_t count, int
 int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, const haflo_ctx* ctx, uint32_t* ws,
               const RnsBuffers& b, size_t count, int entries, bool pair, hipStream_t st);
 
-// Products of lists of pairs modulo m^2 in the residue form (kernels_rns.hip; halves of 2048 bits). An element is
+// Products of lists of pairs modulo m^2 in the residue form (kernels_rns.hip; halves of 2048 and 4096 bits). An element is
 // rns_item_words() words. Chain i is {place of its product, first item, items, unused}; item k of it is element
 // first + k, or index[first + k].
 size_t rns_item_words(const ModHost& m);
-// `count` pairs of lazy limbs (times M_A) at `in` into the form, and one as the element after the last
+// `count` pairs of lazy limbs (times M_A) at `in` into the form
 int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, size_t count, uint32_t* items, hipStream_t st);
 enum { kChainsTotal = 0, kChainsColumns = 1, kChainsControl = 2 };  // device words: number of chains; whether products leave the form
 struct RnsChains {
@@ -268,7 +268,7 @@ struct RnsLists {
   const uint32_t* places;    // null: an element's is its own number
   size_t stride;
   int rows;
-  const uint32_t* live;      // device word: elements there are
+  const uint32_t* live;      // device word: elements there are; null: `stride`
   const uint32_t* limit;     // device word: instructions to run, or null
   uint32_t* out;
   long long* columns;
@@ -281,8 +281,8 @@ struct RnsLists {
 };
 // `bound`: no fewer than the elements that the device may find
 int rns_lists(const haflo_ctx* ctx, const ModHost& m, RnsLists j, size_t bound, hipStream_t st);
-// `bound`: no fewer than the chains that the device may find
-int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound, hipStream_t st);
+// `bound`: no fewer than the chains that the device may find, `expected`: as many as it finds as a rule
+int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound, size_t expected, hipStream_t st);
 
 // X^T [[d]] by the bucket method (kernels_buckets.hip). Workspace layout in 32-bit words.
 struct XtdBucketPlan {

@@ -888,12 +888,16 @@ bool xtd_buckets_fit(size_t rows, size_t cols) {
   return rows < (1ull << 32) && cols != 0 && cols <= 1024 && rows * kMaxPos <= 0xFFFFFFFFull / cols;
 }
 
-// The rounds in the residue form, whose products on full compute units take a third of the time (the first round of 65536 by
-// 32 entries 4.2 -> 1.35 ms) but whose chains are slow on few, against a way in and out of some 0.2 ms. Whole calls on limbs /
-// in residues, ms: 5000 by 7 0.88 / 0.91, 4096 by 16 0.97 / 0.98, 4096 by 32 1.15 / 1.13, 16384 by 9 1.13 / 1.00, 65536 by 4
-// 1.54 / 1.25, 65536 by 32 5.33 / 2.77.
+// All products in the residue form. Those of the first round take a third of the time on a full chip (65536 by 32 entries at
+// 2048 bits 4.2 -> 1.35 ms), and the chains behind the rounds less than a quarter (0.55 -> 0.17), against a way in. Whole calls on
+// limbs / in residues, ms. 2048 bits: 4096 by 1 0.84 / 0.61, 30000 by 1 1.00 / 0.71, 4096 by 16 0.97 / 0.80, 4096 by 32 1.15 /
+// 0.84, 65536 by 4 1.53 / 1.08, 65536 by 32 5.40 / 2.49; so at every size. 4096 bits, where the matrices stream and the way in of
+// a row costs as much as some ten products: 4096 by 16 2.34 / 2.38, 16384 by 4 2.31 / 2.35, 65536 by 2 3.38 / 3.48; 4096 by 32
+// 3.28 / 3.10, 16384 by 16 4.14 / 3.57, 16384 by 32 6.58 / 5.18. At 1024 bits limbs are the quicker: 65536 by 32 1.78 / 2.59
+// on blocks of 16 elements, 4096 by 32 0.59 / 0.65.
 bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  return ctx->Nh.d_rns && ctx->Nh.nl == 72 && rows * cols >= (size_t)ctx->num_cu * 512;
+  if (!ctx->Nh.d_rns) return false;
+  return ctx->Nh.nl == 72 || (ctx->Nh.nl == 144 && cols >= 16 && rows * cols >= (size_t)ctx->num_cu * 512);
 }
 
 XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols, bool residues) {
@@ -930,7 +934,7 @@ XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols, bo
   p.off_G = w;       w += combos * kSubProducts * nl;
   p.off_AT = w;      w += combos * kSegs * 2 * nl;
   p.off_R = w;       w += combos * 2 * nl;
-  p.off_pairs = w;   w += p.pairs ? rows * nl : 0;  // the ciphertexts in the pair form
+  p.off_pairs = w;   w += p.pairs ? (residues ? rows + 1 : rows) * nl : 0;  // the ciphertexts in the pair form, and one
   p.off_order = w;   w += p1;                       // the chunks of a round in the order of their lengths
   p.total = w;
   return p;
@@ -978,13 +982,13 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
     const LaunchShape sh = launch_shape(ctx, rows, lanes, 8);
     const u32* lo = mh.d_pairs + (size_t)(residues ? kConstMLo : kConstR4) * 2 * mh.nl;
     const u32* hi = mh.d_pairs + (size_t)(residues ? kConstMHi : kConstR5) * 2 * mh.nl;
-#define CALL(LPT, T) HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, lo, hi, d_c, d_c, rows, rows, cp)
+#define CALL(LPT, T) HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, lo, hi, d_c, (const u32*)ctx->N.ref().r1, rows, residues ? rows + 1 : rows, cp)
     HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL
   }
   const u32* items = cp;
   if (residues) {
-    int rc = rns_enter(ctx, mh, cp, rows, ws + p.off_items, st);
+    int rc = rns_enter(ctx, mh, cp, rows + 1, ws + p.off_items, st);
     if (rc != HAFLO_OK) return rc;
     items = ws + p.off_items;
   }
@@ -1019,7 +1023,7 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
       j.control = control;
       j.next = stats + kStatNextChunk + r;
       j.out = out;
-      if (int rc = rns_chains(ctx, mh, j, bound, st)) return rc;
+      if (int rc = rns_chains(ctx, mh, j, bound, (rows * cols * 2) >> (cb * (r + 1)), st)) return rc;
       items = out;
       continue;
     }

@@ -908,12 +908,14 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.total = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * nl : 0);
   return p;
 }
-// Tables and rows in the residue form. Whole calls on limbs / in residues, ms, 70 % zeros:
-// 1000 by 256 1.17 / 1.27, 4096 by 64 0.77 / 0.80, 16384 by 16 0.69 / 0.73, 60000 by 7 0.83 / 0.77, 65536 by 32 1.77 / 1.10, 16384
-// by 256 3.55 / 1.93. List places and table entries are 32-bit.
+// Tables and rows in the residue form. Whole calls on limbs / in residues, ms, 70 % zeros. 2048 bits: 65536 by 1 0.56 / 0.57, 16384
+// by 2 0.462 / 0.466; 40000 by 4 0.66 / 0.54, 4096 by 8 0.52 / 0.47, 1000 by 64 0.68 / 0.53, 64 by 256 1.14 / 0.70, 65536 by 32
+// 1.77 / 1.07, 16384 by 256 3.51 / 1.65. 4096 bits: 4096 by 8 1.17 / 1.31, 2000 by 32 1.44 / 1.46; 4096 by 32 1.65 / 1.55, 1000 by
+// 64 1.67 / 1.57, 64 by 256 3.25 / 2.57, 16384 by 64 4.00 / 3.12. At 1024 bits limbs are the quicker: 16384 by 64 0.54 / 0.69.
+// List places and table entries are 32-bit.
 bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  return ctx->Nh.d_rns && ctx->Nh.nl == 72 && cols && rows < (1u << 28) && cols < (1u << 20) &&
-         rows * cols * kMaxPos <= 0xFFFFFFFFull && rows * cols >= (size_t)ctx->num_cu * 1280;
+  if (!ctx->Nh.d_rns || rows >= (1u << 28) || cols >= (1u << 20) || rows > 0xFFFFFFFFull / kMaxPos / (cols ? cols : 1)) return false;
+  return (ctx->Nh.nl == 72 && cols >= 4) || (ctx->Nh.nl == 144 && (cols >= 64 || (cols >= 32 && rows >= 4096)));
 }
 // Segments per row: doubled while the engine has no more than its fill of chains, and a list of 30 % a few factors a chain
 int xw_residue_shift(const haflo_ctx* ctx, size_t rows, size_t cols) {
@@ -1016,7 +1018,7 @@ int xw_residue_tables(const haflo_ctx* ctx, const XwPlan& p, const u32* d_c, siz
   chains.control = ws + t.control;
   chains.next = ws + 2;
   chains.out = ws + p.off_items;
-  return rns_chains(ctx, mh, chains, tabs * kMixed, st);
+  return rns_chains(ctx, mh, chains, tabs * kMixed, tabs / 2 * kMixed, st);
 }
 
 int sum_blocks(const haflo_ctx* ctx, size_t count) {
@@ -1247,14 +1249,14 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
       chains.next = ws + 1;
       chains.out = partial;
       chains.columns = (long long*)(ws + p.off_columns);
-      rc = rns_chains(ctx, mh, chains, rows << p.seg_shift, st);
+      rc = rns_chains(ctx, mh, chains, rows << p.seg_shift, rows << p.seg_shift, st);
       if (rc == HAFLO_OK && p.seg_shift) {
         chains.items = partial;
         chains.chains += (rows << p.seg_shift) * 4;
         chains.index = nullptr;
         chains.control += kChainsControl;
         chains.next = ws + 3;
-        rc = rns_chains(ctx, mh, chains, rows, st);
+        rc = rns_chains(ctx, mh, chains, rows, rows, st);
       }
       if (rc != HAFLO_OK) return rc;
       const LaunchShape sh = launch_shape(ctx, rows, lanes, 8);

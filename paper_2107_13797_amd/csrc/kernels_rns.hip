@@ -916,10 +916,6 @@ struct OneEngine {
   __device__ __forceinline__ void load(OneState<NR>& x, const u32* src, unsigned left, int nl, const char* matrix) {
     const bool active = (unsigned)(lane & 15) < left;
     src += (lane & 15) * 2 * nl;
-    load_own(x, src, active, nl, matrix);
-  }
-  // the same, each from this lane's own `src`
-  __device__ __forceinline__ void load_own(OneState<NR>& x, const u32* src, bool active, int nl, const char* matrix) {
     x = OneState<NR>();
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
@@ -1059,11 +1055,10 @@ __global__ __launch_bounds__(1024, 4) void k_rns_one(RnsJob j0, RnsJob j1, unsig
 
 // Products of lists of elements, each in memory by itself as [base A, base B][quad][lane group] (rns_item_words()): a lane
 // group's four lanes read 64 consecutive bytes, 18 times, from wherever the element lies.
-// Into that form: lazy limb pairs as in RnsJob::in; `last` is the element after them.
+// Into that form: lazy limb pairs as in RnsJob::in.
 template <int NR>
 __global__ __launch_bounds__(1024, 4) void k_rns_enter(const u32* __restrict__ tables, const u32* __restrict__ in,
-                                                       const u32* __restrict__ last, size_t count, int nl,
-                                                       u32* __restrict__ items) {
+                                                       size_t count, int nl, u32* __restrict__ items) {
   __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
   for (int i = (int)threadIdx.x; i < rns::lds_bytes(NR) / 16; i += (int)blockDim.x)
     ((Quad*)lds)[i] = ((const Quad*)tables)[i];
@@ -1071,12 +1066,11 @@ __global__ __launch_bounds__(1024, 4) void k_rns_enter(const u32* __restrict__ t
   OneEngine<NR> e(lds);
   const unsigned waves = blockDim.x / WAVE;
   const size_t wave = (size_t)blockIdx.x * waves + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-  const size_t all = count + 1;
-  for (size_t tile = wave; tile * 16 < all; tile += (size_t)gridDim.x * waves) {
+  for (size_t tile = wave; tile * 16 < count; tile += (size_t)gridDim.x * waves) {
     const size_t own = tile * 16 + (threadIdx.x & 15);
     OneState<NR> x;
-    e.load_own(x, own < count ? in + own * (size_t)(2 * nl) : last, own < all, nl, (const char*)tables + rns::lds_bytes(NR));
-    if (own < all) e.template store_state<4>(x, items + own * (size_t)rns::item_words(NR));
+    e.load(x, in + tile * (size_t)(16 * 2 * nl), (unsigned)std::min(count - tile * 16, (size_t)16), nl, (const char*)tables + rns::lds_bytes(NR));
+    if (own < count) e.template store_state<4>(x, items + own * (size_t)rns::item_words(NR));
   }
 }
 
@@ -1411,6 +1405,12 @@ struct RnsGroup {
     for (int i = 0; i < TW; ++i) v[i] = SQ ? own(x, i) : entry(y, i);
     multiply<SQ>(x, v, [] {});
   }
+  // before the first product of elements that load() did not bring in
+  __device__ __forceinline__ void begin() {
+    if constexpr (!kHeld)
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) ask<0>(k);
+  }
   // `meanwhile` asks for what the next product takes, behind this one's first barrier
   template <bool SQ, class F>
   __device__ __forceinline__ void multiply(State& x, const Quad (&v)[TW], const F& meanwhile) {
@@ -1477,6 +1477,12 @@ struct RnsGroup {
   }
   // the pairs as two integers each in columns of weight 2^(29 l)
   __device__ __forceinline__ void store(const State& x, long long* dst, unsigned left) {
+    const unsigned e = (unsigned)(lane & (kElements - 1));
+    store(x, dst, e, e < left);
+  }
+  // the same, this lane's to element `e` behind `dst`
+  template <class I>
+  __device__ __forceinline__ void store(const State& x, long long* dst, I e, bool active) {
     __syncthreads();  // the bytes of the last product have been read
     publish(x);
     Acc r[TW][kHalves];
@@ -1484,8 +1490,8 @@ struct RnsGroup {
     if (kClearLate) clear_sums();
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
-      const unsigned e = (unsigned)(lane & (kElements - 1)), half = FOLD ? (unsigned)lane >> 3 & 1 : 0;
-      if (e < left && mine(i, kLimbTiles)) {
+      const unsigned half = FOLD ? (unsigned)lane >> 3 & 1 : 0;
+      if (active && mine(i, kLimbTiles)) {
         long long* d = dst + (size_t)e * (8 * kLimbTiles) + half * (4 * kLimbTiles) + 4 * tile(i, kLimbTiles) + g;
         d[0] = integer(r[i][0]);
         if (!FOLD) d[4 * kLimbTiles] = kBoth ? integer(r[i][kHalves - 1]) : 0;
@@ -1643,9 +1649,10 @@ struct ListShared {
 template <class G>
 __device__ __forceinline__ void run_lists(G& e, const RnsLists& j, ListShared& sh, u32 ops) {
   // scalars, all of them: the way through the program is the same for all lanes
-  const unsigned count = (unsigned)__builtin_amdgcn_readfirstlane((int)*j.live);
+  const unsigned count = j.live ? (unsigned)__builtin_amdgcn_readfirstlane((int)*j.live) : (unsigned)j.stride;
   const int limit = j.limit ? __builtin_amdgcn_readfirstlane((int)*j.limit) : kListOps;
   const int len = j.len < limit ? j.len : limit;
+  e.begin();
   for (unsigned first = blockIdx.x * G::kElements; first < count; first += gridDim.x * G::kElements) {
     const unsigned left = std::min(count - first, (unsigned)G::kElements);
     const unsigned own = (unsigned)(e.lane & (G::kElements - 1));
@@ -1725,7 +1732,7 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_lists(R
   using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
   __shared__ __align__(16) typename Main::Shared shared;
   __shared__ ListShared lists;
-  if ((size_t)blockIdx.x * Main::kElements >= *j.live) return;
+  if (j.live && (size_t)blockIdx.x * Main::kElements >= *j.live) return;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   u32 ops = 0;  // in the lanes of a register, as an index that varies would cost a copy of the arguments
 #pragma unroll
@@ -1736,6 +1743,56 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_lists(R
   } else if constexpr (W1 > 0) {  // as many barriers, see k_rns_group
     Rest e(shared, j.tables, W * TW + (wave - W) * TW1);
     run_lists(e, j, lists, ops);
+  }
+}
+
+// RnsChains on blocks of 8 or 16 elements, as k_rns_chains does on wavefronts of 16
+template <class G>
+__device__ __forceinline__ void run_chains(G& e, const RnsChains& j, unsigned total) {
+  const bool columns = __builtin_amdgcn_readfirstlane((int)j.control[kChainsColumns]) != 0;
+  e.begin();
+  for (unsigned first = blockIdx.x * G::kElements; first < total; first += gridDim.x * G::kElements) {
+    const unsigned own = first + (unsigned)(e.lane & (G::kElements - 1));
+    const bool active = own < total;
+    const Quad c = active ? ((const Quad*)j.chains)[own] : Quad{0, 0, 0, 0};
+    const u32 start = c[1], len = c[2];
+    const u32 longest = (u32)__builtin_amdgcn_readfirstlane((int)wave_max(len));  // each wavefront has all elements
+    const auto place = [&](u32 i) -> u32 { return i < len ? j.index ? j.index[start + i] : start + i : kNoOperand; };
+    const auto item = [&](u32 p) { return p == kNoOperand ? j.one : j.items + (size_t)p * rns::item_words(G::kRegs); };
+    Quad next[G::kOwn];
+    typename G::State x;
+    e.load_item(next, item(place(0)));
+    e.set(x, next);
+    e.load_item(next, item(place(1)));
+    u32 p = place(2);
+#pragma unroll 1
+    for (u32 i = 1; i < longest; ++i) {
+      Quad y[G::kOwn];
+#pragma unroll
+      for (int t = 0; t < G::kOwn; ++t) y[t] = next[t];
+      e.template multiply<false>(x, y, [&] {
+        e.load_item(next, item(p));
+        p = place(i + 2);
+      });
+    }
+    if (columns) e.store(x, j.columns, (size_t)c[0], active);
+    else if (active) e.store_item(x, j.out + (size_t)c[0] * rns::item_words(G::kRegs));
+  }
+}
+template <int NR, int TW, int W, int TW1, int W1, bool FOLD>
+__global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group_chains(RnsChains j) {
+  using Main = RnsGroup<NR, TW, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
+  using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
+  __shared__ __align__(16) typename Main::Shared shared;
+  const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane((int)j.control[kChainsTotal]);
+  if (blockIdx.x * Main::kElements >= total) return;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  if (W1 == 0 || wave < W) {
+    Main e(shared, j.tables, wave * TW);
+    run_chains(e, j, total);
+  } else if constexpr (W1 > 0) {  // as many barriers, see k_rns_group
+    Rest e(shared, j.tables, W * TW + (wave - W) * TW1);
+    run_chains(e, j, total);
   }
 }
 
@@ -1834,10 +1891,18 @@ LaunchShape rns_shape(const haflo_ctx* ctx, size_t count, size_t most) {
 }  // namespace
 
 int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, size_t count, uint32_t* items, hipStream_t st) {
-  if (rns::regs_for(m.nl) != 18) return HAFLO_EINVAL;
-  const u32* one = m.d_pairs + (size_t)kConstMOne * 2 * m.nl;
-  HAFLO_LAUNCH((k_rns_enter<18>), rns_shape(ctx, count + 1, 16), st, (const u32*)m.d_rns, in, one, count, m.nl, items);
-  return hip_status(hipGetLastError());
+  if (rns::regs_for(m.nl) == 18) {
+    HAFLO_LAUNCH((k_rns_enter<18>), rns_shape(ctx, count, 16), st, (const u32*)m.d_rns, in, count, m.nl, items);
+    return hip_status(hipGetLastError());
+  }
+  RnsLists j = {};
+  j.limbs = in;
+  j.one = items;
+  j.items = j.out = items;
+  j.stride = count;
+  j.add(LIST_ACC_LIMBS);
+  j.add(LIST_STORE_ACC);
+  return rns_lists(ctx, m, j, count, st);
 }
 
 int rns_lists(const haflo_ctx* ctx, const ModHost& m, RnsLists j, size_t bound, hipStream_t st) {
@@ -1851,16 +1916,36 @@ int rns_lists(const haflo_ctx* ctx, const ModHost& m, RnsLists j, size_t bound, 
   hipLaunchKernelGGL((k_rns_lists<NR, TW, W, TW1, W1, true>), dim3(blocks), dim3((W + W1) * 64), 0, st, j)
   switch (nr) {
     case 18: GROUP(18, 2, 8, 1, 2); break;
+    case 36: GROUP(36, 3, 12, 1, 0); break;
     default: return HAFLO_EINVAL;
   }
 #undef GROUP
   return hip_status(hipGetLastError());
 }
 
-int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound, hipStream_t st) {
-  if (rns::regs_for(m.nl) != 18) return HAFLO_EINVAL;
+int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound, size_t expected, hipStream_t st) {
+  const int nr = rns::regs_for(m.nl);
   j.tables = m.d_rns;
-  HAFLO_LAUNCH((k_rns_chains<18>), rns_shape(ctx, bound, 12), st, j);
+  // Wavefronts of 16 elements once there are 32 to a compute unit, else blocks of 8 elements, whose products take less time on
+  // their own. ms with wavefronts / blocks: forward 1000 by 64 (8000 chains) 0.57 / 0.53, 16384 by 8 (16384 of some five factors)
+  // 0.57 / 0.53; gradient 4096 by 16 (8192) 0.795 / 0.798, 16384 by 8 (16384 of 16 factors) 0.82 / 0.87.
+  if (nr == 18 && expected > (size_t)ctx->num_cu * 32) {
+    HAFLO_LAUNCH((k_rns_chains<18>), rns_shape(ctx, bound, 12), st, j);
+    return hip_status(hipGetLastError());
+  }
+  const bool fold = nr == 18 || expected <= (size_t)ctx->num_cu * 8 * group_blocks_per_cu(nr);
+  const unsigned blocks = (unsigned)std::max(group_blocks(ctx, nr, bound, 1, fold), (size_t)1);
+#define GROUP(NR, TW, W, TW1, W1, FOLD) \
+  hipLaunchKernelGGL((k_rns_group_chains<NR, TW, W, TW1, W1, FOLD>), dim3(blocks), dim3((W + W1) * 64), 0, st, j)
+  switch (nr) {
+    case 18: GROUP(18, 2, 8, 1, 2, true); break;
+    case 36:
+      if (fold) GROUP(36, 3, 12, 1, 0, true);
+      else GROUP(36, 3, 12, 1, 0, false);
+      break;
+    default: return HAFLO_EINVAL;
+  }
+#undef GROUP
   return hip_status(hipGetLastError());
 }
 

@@ -178,10 +178,11 @@ def matvec_case(kind, rows, cols, seed):
     return x
 
 
-@pytest.mark.parametrize("kind,rows,cols", [("random", 257, 2), ("heavy", 300, 2)])
-def test_gradient_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
+@pytest.mark.parametrize("bits,kind,rows,cols", [(2048, "random", 131, 2), (2048, "heavy", 300, 2),
+                                                 (4096, "random", 32, 16)])
+def test_gradient_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     """The bucket rounds in the residue form (the workspace asked for) and on limbs (the least): one to three rounds."""
-    lib, bits = emu, 2048
+    lib = emu
     p, q = oracle_key(bits)
     n, rng = p * q, random.Random(rows)
     ctx = public_ctx(lib, n, bits)
@@ -196,11 +197,12 @@ def test_gradient_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
     lib.haflo_ctx_destroy(ctx)
 
 
-@pytest.mark.parametrize("kind,rows,cols", [("random", 641, 2), ("sparse", 81, 16), ("zero", 1280, 1)])
-def test_forward_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
+@pytest.mark.parametrize("bits,kind,rows,cols", [(2048, "random", 70, 4), (2048, "sparse", 41, 16), (2048, "zero", 600, 4),
+                                                 (4096, "sparse", 3, 64)])
+def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     """Tables and row products in the residue form (the workspace asked for) and on limbs (the least): rows in several
     chains and in one, empty rows, exponents of all digit positions and none."""
-    lib, bits = emu, 2048
+    lib = emu
     p, q = oracle_key(bits)
     n, rng = p * q, random.Random(rows)
     ctx = public_ctx(lib, n, bits)
@@ -213,7 +215,7 @@ def test_forward_matvec_in_residues(emu, kind, rows, cols):  # noqa: F811
         x[np.random.default_rng(3).random(x.shape) < 0.6] = 0
     if kind == "zero":
         x[:] = 0
-        x[5, 0], x[40, 0] = 255, -16  # lists of one entry
+        x[5, 0], x[40, 3] = 255, -16  # lists of one entry
     want = O.matvec(O.PrivateKey(p, q).public, 1, cs, x.tolist())
     for room in ("asked", "least"):
         assert matvec(lib, ctx, bits, 1, cs, x, room) == want, room

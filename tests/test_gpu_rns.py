@@ -214,13 +214,14 @@ def random_ciphertexts(api, ctx, n, bits, count):
         ctx, to_dev(random_units_words(count, 2 * bits, bits + 4))))
 
 
-# the first shapes are next to the rule (131072 entries on 256 compute units); chunks of 16 and of 32 items, one to four rounds
-@pytest.mark.parametrize("rows,cols,top", [(4096, 32, 1 << 18), (5043, 26, 600), (65537, 2, 40), (140001, 1, 3), (32768, 33, 1 << 17)])
-def test_gradient_matvec_in_residues_matches_limb_arithmetic(rows, cols, top):
+# chunks of 16 and of 32 items, one to four rounds, chains on wavefronts and on blocks; at 4096 bits shapes next to the rule
+@pytest.mark.parametrize("bits,rows,cols,top", [
+    (2048, 4096, 1, 1 << 18), (2048, 4099, 32, 1 << 18), (2048, 5043, 26, 600), (2048, 65537, 2, 40), (2048, 140001, 1, 3),
+    (2048, 32768, 33, 1 << 17), (4096, 4096, 32, 1 << 18), (4096, 8201, 16, 40), (4096, 9001, 41, 1 << 17)])
+def test_gradient_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, top):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2107_13797_amd import api
-    bits = 2048
     p, q = oracle_key(bits)
     ctx = api.haflo_ctx_create_public(p * q, bits)
     c = random_ciphertexts(api, ctx, p * q, bits, rows)
@@ -228,13 +229,14 @@ def test_gradient_matvec_in_residues_matches_limb_arithmetic(rows, cols, top):
     assert torch.equal(api.haflo_cipher_matvec(ctx, 0, c, x), matvec_on_limbs(api, ctx, 0, c, x))
 
 
-# the first shapes are next to the rule (327680 entries on 256 compute units); rows in 1, 2 and 16 chains, one to four digits
-@pytest.mark.parametrize("rows,cols,top", [(81920, 4, 1 << 16), (10241, 32, 1 << 9), (641, 512, 200), (40001, 17, 1 << 28)])
-def test_forward_matvec_in_residues_matches_limb_arithmetic(rows, cols, top):
+# rows in 1, 2 and up to 16 chains, one to four digits; at 4096 bits shapes next to the rule
+@pytest.mark.parametrize("bits,rows,cols,top", [
+    (2048, 81920, 4, 1 << 16), (2048, 10241, 32, 1 << 9), (2048, 641, 512, 200), (2048, 40001, 17, 1 << 28), (2048, 129, 5, 1 << 16),
+    (4096, 4096, 32, 1 << 16), (4096, 131, 64, 200), (4096, 6001, 65, 1 << 28)])
+def test_forward_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, top):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2107_13797_amd import api
-    bits = 2048
     p, q = oracle_key(bits)
     ctx = api.haflo_ctx_create_public(p * q, bits)
     c = random_ciphertexts(api, ctx, p * q, bits, cols)
