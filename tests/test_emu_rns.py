@@ -178,7 +178,7 @@ def matvec_case(kind, rows, cols, seed):
     return x
 
 
-@pytest.mark.parametrize("bits,kind,rows,cols", [(2048, "random", 131, 2), (2048, "heavy", 300, 2),
+@pytest.mark.parametrize("bits,kind,rows,cols", [(2048, "random", 67, 2), (2048, "heavy", 300, 2),
                                                  (4096, "random", 32, 16)])
 def test_gradient_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     """The bucket rounds in the residue form (the workspace asked for) and on limbs (the least): one to three rounds."""
@@ -197,7 +197,7 @@ def test_gradient_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     lib.haflo_ctx_destroy(ctx)
 
 
-@pytest.mark.parametrize("bits,kind,rows,cols", [(2048, "random", 70, 4), (2048, "sparse", 41, 16), (2048, "zero", 600, 4),
+@pytest.mark.parametrize("bits,kind,rows,cols", [(2048, "random", 37, 4), (2048, "sparse", 41, 16), (2048, "zero", 300, 4),
                                                  (4096, "sparse", 3, 64)])
 def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     """Tables and row products in the residue form (the workspace asked for) and on limbs (the least): rows in several
