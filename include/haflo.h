@@ -26,9 +26,9 @@
  *   staging calls and the store's upload / download copy and may wait.
  * Workspace: operators that need temporary device memory take a caller-supplied
  *   workspace pointer and its size; haflo_workspace_bytes says how much they ask
- *   for. Encryption, decryption, scalar multiplication and what contains them ask
- *   for more than they need (the window tables of a faster engine) and run without
- *   that engine when they get less, down to haflo_workspace_bytes_least. The library
+ *   for. Encryption, decryption, scalar multiplication, the matvecs and what contains
+ *   them ask for more than they need (the tables and operands of a faster engine) and run
+ *   without that engine when they get less, down to haflo_workspace_bytes_least. The library
  *   never allocates device memory inside an operator call.
  *   Contents of the workspace are undefined afterwards; two calls that share a
  *   workspace must be ordered on one stream.
@@ -161,9 +161,10 @@ int haflo_op_work(const haflo_ctx* ctx, int op, uint64_t* mads_executed);
 size_t haflo_workspace_bytes(const haflo_ctx* ctx, int op, size_t rows, size_t cols);
 
 /* The least workspace the same call accepts. Smaller than haflo_workspace_bytes
- * where the call asks for room for a faster engine's window tables (encryption,
- * decryption, scalar multiplication, haflo_fore_gradient, haflo_taylor_loss): with
- * anything in between it runs without that engine, with the same results. */
+ * where the call asks for room for a faster engine's tables and operands (encryption,
+ * decryption, scalar multiplication, haflo_cipher_matvec, haflo_fore_gradient,
+ * haflo_taylor_loss): with anything in between it runs without that engine, with the
+ * same results. */
 size_t haflo_workspace_bytes_least(const haflo_ctx* ctx, int op, size_t rows, size_t cols);
 
 /*
@@ -344,7 +345,7 @@ int haflo_taylor_loss(const haflo_ctx* ctx, const void* d_c_u, const void* d_c_u
 
 /* "Homomorphic Summation" (paper Table 1): out[0] = prod_i c[i] mod n^2 over
  * count internal elements (1 for count = 0). Workspace: the same as
- * HAFLO_OP_MATVEC_XT_D with rows = count, cols = 1. */
+ * HAFLO_OP_MATVEC_XT_D with rows = count, cols = 1 (the least of it will do). */
 int haflo_cipher_sum(const haflo_ctx* ctx, const void* d_c, size_t count, void* d_out, void* d_workspace,
                      size_t workspace_bytes, void* stream);
 

@@ -309,7 +309,7 @@ def haflo_cipher_matvec(ctx, orientation, c, X, out=None):
 def haflo_cipher_sum(ctx, c):
     count = c.shape[0]
     out = _new_cipher(ctx, 1)
-    ws = _workspace(ctx, _cabi.OP_MATVEC_XT_D, count, 1)
+    ws = ctx.workspace(haflo_workspace_bytes_least(ctx, _cabi.OP_MATVEC_XT_D, count, 1))
     _check(lib().haflo_cipher_sum(ctx.handle, _ptr(c), count, _ptr(out), _ptr(ws), ws.numel(), _stream()))
     return out
 

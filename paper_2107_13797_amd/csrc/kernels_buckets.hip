@@ -894,9 +894,9 @@ bool xtd_buckets_fit(size_t rows, size_t cols) {
 // 0.84, 65536 by 4 1.53 / 1.08, 65536 by 32 5.40 / 2.49; so at every size. 4096 bits, where the matrices stream and the way in of
 // a row costs as much as some ten products: 4096 by 16 2.34 / 2.38, 16384 by 4 2.31 / 2.35, 65536 by 2 3.38 / 3.48; 4096 by 32
 // 3.28 / 3.10, 16384 by 16 4.14 / 3.57, 16384 by 32 6.58 / 5.18. At 1024 bits limbs are the quicker: 65536 by 32 1.78 / 2.59
-// on blocks of 16 elements, 4096 by 32 0.59 / 0.65.
+// on blocks of 16 elements, 4096 by 32 0.59 / 0.65. An element takes twice the memory: beyond 2^27 entries (20 GB) limbs.
 bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  if (!ctx->Nh.d_rns) return false;
+  if (!ctx->Nh.d_rns || rows * cols > (1u << 27)) return false;
   return ctx->Nh.nl == 72 || (ctx->Nh.nl == 144 && cols >= 16 && rows * cols >= (size_t)ctx->num_cu * 512);
 }
 

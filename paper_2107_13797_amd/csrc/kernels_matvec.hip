@@ -910,9 +910,9 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
 // by 2 0.462 / 0.466; 40000 by 4 0.66 / 0.54, 4096 by 8 0.52 / 0.47, 1000 by 64 0.68 / 0.53, 64 by 256 1.14 / 0.70, 65536 by 32
 // 1.77 / 1.07, 16384 by 256 3.51 / 1.65. 4096 bits: 4096 by 8 1.17 / 1.31, 2000 by 32 1.44 / 1.46; 4096 by 32 1.65 / 1.55, 1000 by
 // 64 1.67 / 1.57, 64 by 256 3.25 / 2.57, 16384 by 64 4.00 / 3.12. At 1024 bits limbs are the quicker: 16384 by 64 0.54 / 0.69.
-// List places and table entries are 32-bit.
+// List places and table entries are 32-bit, and an entry takes twice the memory: beyond 2048 columns (5 GB at 2048 bits) limbs.
 bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  if (!ctx->Nh.d_rns || rows >= (1u << 28) || cols >= (1u << 20) || rows > 0xFFFFFFFFull / kMaxPos / (cols ? cols : 1)) return false;
+  if (!ctx->Nh.d_rns || rows >= (1u << 28) || cols > 2048 || rows > 0xFFFFFFFFull / kMaxPos / (cols ? cols : 1)) return false;
   return (ctx->Nh.nl == 72 && cols >= 4) || (ctx->Nh.nl == 144 && (cols >= 64 || (cols >= 32 && rows >= 4096)));
 }
 // Segments per row: doubled while the engine has no more than its fill of chains, and a list of 30 % a few factors a chain
