@@ -390,7 +390,7 @@ static void build_rns(ModHost& ms, const Big& s, const Big& s2, const Big& out,
   const Big rm = mh.to_mont(R);
   Big c = Big::mod(ms.rns_radix, s2);
   if (stored) special.push_back({kConstMOne, c});
-  for (int i = kConstM1; i <= kConstM4; ++i) {
+  for (int i = kConstM1; i <= (stored ? kConstM3 : kConstM4); ++i) {
     c = mh.mul(c, rm);
     special.push_back({i, c});
   }

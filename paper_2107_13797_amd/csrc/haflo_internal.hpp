@@ -71,8 +71,8 @@ enum {
   kConstM1 = 7, kConstM2 = 8, kConstM3 = 9, kConstM4 = 10, kConstMOut = 11,
   // the same for stored ciphertexts: their lower and upper halves into the form, a power out of it
   kConstMLo = 12, kConstMHi = 13, kConstMStored = 14,
-  kConstMOne = 15,  // one in that form
-  kNumConst = 16
+  kConstMOne = kConstM4,  // and one in that form, where M4 has no use
+  kNumConst = 15
 };
 inline uint32_t eng_ins(uint32_t op, uint32_t a = 0, uint32_t b = 0) { return op | (a << 8) | (b << 20); }
 
