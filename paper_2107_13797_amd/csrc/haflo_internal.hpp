@@ -292,7 +292,9 @@ struct XtdBucketPlan {
   size_t off_cnt, off_totals, off_offs, off_sorted, off_arena[2], off_G, off_AT, off_R, off_pairs, off_order, total;
   bool pairs;  // the products run on pairs of residues modulo n
   bool residues;  // the rounds' in the residue form
-  size_t off_items, off_one, off_chains, off_control, off_tail, arena1_items;  // what the first arena holds
+  size_t off_items, off_one, off_chains, off_control, off_tail;  // the element at off_one is followed by the first of off_items
+  size_t enter;         // elements on their way into it at a time
+  size_t arena1_items;  // the first of the second arena, counted from the first arena
 };
 bool xtd_buckets_fit(size_t rows, size_t cols);
 bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols);  // if the workspace has room for it

@@ -888,20 +888,24 @@ bool xtd_buckets_fit(size_t rows, size_t cols) {
   return rows < (1ull << 32) && cols != 0 && cols <= 1024 && rows * kMaxPos <= 0xFFFFFFFFull / cols;
 }
 
+constexpr size_t kResidueWords = (size_t)8 << 30;  // of 32 bits
+constexpr size_t kEnterRows = 1 << 17;  // 75 MB of pairs at 2048 bits; way in of so many 0.4 ms, against two launches
 // All products in the residue form. Those of the first round take a third of the time on a full chip (65536 by 32 entries at
 // 2048 bits 4.2 -> 1.35 ms), and the chains behind the rounds less than a quarter (0.55 -> 0.17), against a way in. Whole calls on
 // limbs / in residues, ms. 2048 bits: 4096 by 1 0.84 / 0.61, 30000 by 1 1.00 / 0.71, 4096 by 16 0.97 / 0.80, 4096 by 32 1.15 /
 // 0.84, 65536 by 4 1.53 / 1.08, 65536 by 32 5.40 / 2.49; so at every size. 4096 bits, where the matrices stream and the way in of
 // a row costs as much as some ten products: 4096 by 16 2.34 / 2.38, 16384 by 4 2.31 / 2.35, 65536 by 2 3.38 / 3.48; 4096 by 32
 // 3.28 / 3.10, 16384 by 16 4.14 / 3.57, 16384 by 32 6.58 / 5.18. At 1024 bits limbs are the quicker: 65536 by 32 1.78 / 2.59
-// on blocks of 16 elements, 4096 by 32 0.59 / 0.65. An element takes twice the memory: beyond 2^27 entries (20 GB) limbs.
+// on blocks of 16 elements, 4096 by 32 0.59 / 0.65. An element takes twice the memory: where the plan would take more than 32 GiB
+// (2048 bits: 131072 by 1024 is still below it, 2^24 by 8 and 2^25 by 1 are not) limbs.
 bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  if (!ctx->Nh.d_rns || rows * cols > (1u << 27)) return false;
-  return ctx->Nh.nl == 72 || (ctx->Nh.nl == 144 && cols >= 16 && rows * cols >= (size_t)ctx->num_cu * 512);
+  if (!ctx->Nh.d_rns) return false;
+  if (ctx->Nh.nl != 72 && !(ctx->Nh.nl == 144 && cols >= 16 && rows * cols >= (size_t)ctx->num_cu * 512)) return false;
+  return xtd_bucket_plan(ctx, rows, cols, true).total <= kResidueWords;
 }
 
 XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols, bool residues) {
-  XtdBucketPlan p;
+  XtdBucketPlan p = {};
   const size_t nl = (size_t)ctx->N.nl;
   p.pairs = haflo_has_pair_geometry(ctx->Nh);
   p.residues = residues;
@@ -922,19 +926,29 @@ XtdBucketPlan xtd_bucket_plan(const haflo_ctx* ctx, size_t rows, size_t cols, bo
   p.off_offs = w;    w += (size_t)(p.rounds + 1) * (p.keys + 1);
   p.off_sorted = w;  w += terms;
   w = (w + 63) & ~(size_t)63;
-  p.off_arena[0] = w; w += p1 * item;
-  p.off_arena[1] = w; w += p2 * item;
-  p.off_items = w;    w += residues ? (rows + 1) * item : 0;  // the ciphertexts and one
-  p.off_chains = w;   w += residues ? p1 * 4 : 0;
-  p.off_control = w;  w += residues ? 64 : 0;
-  if (residues) w = (w + 63) & ~(size_t)63;
-  p.off_tail = w;     w += residues ? tail_plan(ctx, cols, 0).columns + cols * 8 * (size_t)rns_columns(ctx->Nh) : 0;
-  p.off_one = p.off_items + rows * item;
-  p.arena1_items = p1;
-  p.off_G = w;       w += combos * kSubProducts * nl;
-  p.off_AT = w;      w += combos * kSegs * 2 * nl;
-  p.off_R = w;       w += combos * 2 * nl;
-  p.off_pairs = w;   w += p.pairs ? (residues ? rows + 1 : rows) * nl : 0;  // the ciphertexts in the pair form, and one
+  p.off_arena[0] = w;
+  if (residues) {
+    // The pairs on their way in lie in the first arena, as many at a time as it holds (kEnterRows if it is smaller). The
+    // elements, one and then the ciphertexts, have been read when the second round writes the second arena over them.
+    p.off_pairs = w;
+    p.enter = std::max(p1 * item / nl, std::min(rows + 1, kEnterRows));
+    p.arena1_items = (p.enter * nl + item - 1) / item + 1;
+    if (p.arena1_items < p1 + 1) p.arena1_items = p1 + 1;
+    w += (p.arena1_items - 1) * item;
+    p.off_one = w;      w += item;
+    p.off_arena[1] = p.off_items = w; w += std::max(rows, p2) * item;
+    p.off_chains = w;   w += p1 * 4;
+    p.off_control = w;  w += 64;
+    w = (w + 63) & ~(size_t)63;
+    p.off_tail = w;     w += tail_plan(ctx, cols, 0).columns + cols * 8 * (size_t)rns_columns(ctx->Nh);
+  } else {
+    w += p1 * nl;
+    p.off_arena[1] = w; w += p2 * nl;
+    p.off_G = w;        w += combos * kSubProducts * nl;
+    p.off_AT = w;       w += combos * kSegs * 2 * nl;
+    p.off_R = w;        w += combos * 2 * nl;
+    p.off_pairs = w;    w += p.pairs ? rows * nl : 0;  // the ciphertexts in the pair form
+  }
   p.off_order = w;   w += p1;                       // the chunks of a round in the order of their lengths
   p.total = w;
   return p;
@@ -978,20 +992,21 @@ int xtd_buckets(const haflo_ctx* ctx, const uint32_t* d_c, const int32_t* d_X, s
   const u32* one = mh.d_pairs + (size_t)kConstR1 * 2 * mh.nl;
   const u32* leave = mh.d_pairs + (size_t)kConstR3 * 2 * mh.nl;
   u32* cp = ws + p.off_pairs;
-  {
-    const LaunchShape sh = launch_shape(ctx, rows, lanes, 8);
-    const u32* lo = mh.d_pairs + (size_t)(residues ? kConstMLo : kConstR4) * 2 * mh.nl;
-    const u32* hi = mh.d_pairs + (size_t)(residues ? kConstMHi : kConstR5) * 2 * mh.nl;
-#define CALL(LPT, T) HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, lo, hi, d_c, (const u32*)ctx->N.ref().r1, rows, residues ? rows + 1 : rows, cp)
+  const u32* lo = mh.d_pairs + (size_t)(residues ? kConstMLo : kConstR4) * 2 * mh.nl;
+  const u32* hi = mh.d_pairs + (size_t)(residues ? kConstMHi : kConstR5) * 2 * mh.nl;
+  const u32* r1 = ctx->N.ref().r1;
+  const size_t all = residues ? rows + 1 : rows, portion = residues ? p.enter : rows;
+  for (size_t at = 0; at < all; at += portion) {
+    const size_t count = std::min(all - at, portion), ones = residues && at == 0 ? 1 : 0;
+    const u32* src = d_c + (at ? at - 1 : 0) * (size_t)ctx->N.nl;
+    const LaunchShape sh = launch_shape(ctx, count, lanes, 8);
+#define CALL(LPT, T) HAFLO_LAUNCH((k_to_pairs<LPT, T>), sh, st, M, lo, hi, r1, src, ones, count, cp)
     HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL
+    if (!residues) continue;
+    if (int rc = rns_enter(ctx, mh, cp, count, ws + p.off_one + at * rns_item_words(mh), st)) return rc;
   }
-  const u32* items = cp;
-  if (residues) {
-    int rc = rns_enter(ctx, mh, cp, rows + 1, ws + p.off_items, st);
-    if (rc != HAFLO_OK) return rc;
-    items = ws + p.off_items;
-  }
+  const u32* items = residues ? ws + p.off_items : cp;
   for (int r = 0; r < p.rounds; ++r) {
     // upper bound of the chunks of this round: one lane group each, capped by the grid-stride loop
     size_t bound = rows * cols * kMaxPos;

@@ -220,3 +220,20 @@ def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     for room in ("asked", "least"):
         assert matvec(lib, ctx, bits, 1, cs, x, room) == want, room
     lib.haflo_ctx_destroy(ctx)
+
+
+# Shapes of the residue form next to what bounds its memory (rows alone, columns alone, both), and some beyond it.
+@pytest.mark.parametrize("bits,rows,cols", [
+    (2048, 4096, 1), (2048, 65536, 32), (2048, 4096, 1024), (2048, 1 << 20, 1), (2048, 1 << 22, 32), (2048, 1 << 24, 8),
+    (2048, 1 << 26, 2), (2048, 1 << 27, 1), (2048, 131072, 1024), (4096, 65536, 64), (4096, 1 << 22, 16), (4096, 131072, 1024)])
+def test_gradient_workspace_is_bounded(emu, bits, rows, cols):  # noqa: F811
+    """What the call asks for is at most 2.2 times what it can do with (an element takes twice the memory, and there are
+    some more for a column's last products), and more than the least only up to 32 GiB: the binding takes what is asked for
+    whenever the device has it."""
+    p, q = oracle_key(bits)
+    ctx = public_ctx(emu, p * q, bits)
+    asked = emu.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_XT_D, rows, cols)
+    least = emu.haflo_workspace_bytes_least(ctx, _cabi.OP_MATVEC_XT_D, rows, cols)
+    emu.haflo_ctx_destroy(ctx)
+    assert least <= asked <= 2.2 * least
+    assert asked == least or asked <= 32 << 30
