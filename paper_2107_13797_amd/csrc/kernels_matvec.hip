@@ -559,23 +559,30 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_places(u32 cols, u32* __re
 }
 
 // Rows' products as chains: 2^seg_shift of near-equal length for a row, in the order `order`, and behind them (unless a row
-// is one chain) those that combine a row's.
-__global__ __launch_bounds__(kBlockThreads) void k_xw_chains(size_t rows, size_t list_stride, int seg_shift,
+// is one chain) those that combine a row's. The chains that end in a row's product are launched `portion` at a time, each time
+// with kPortionWords of control words and counter of their own, and into places of their own where there are several.
+enum { kPortionNext = kChainsControl, kPortionWords = 4 };
+__global__ __launch_bounds__(kBlockThreads) void k_xw_chains(size_t rows, size_t list_stride, int seg_shift, size_t portion,
                                                              const u32* __restrict__ counts, const u32* __restrict__ order,
                                                              uint4* __restrict__ chains, u32* __restrict__ control,
-                                                             u32* __restrict__ control2) {
-  const size_t items = rows << seg_shift;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+                                                             u32* __restrict__ portions) {
+  const size_t items = rows << seg_shift, at = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  if (at == 0) {
     control[kChainsTotal] = (u32)items;
-    control[kChainsColumns] = seg_shift == 0;
-    control2[kChainsTotal] = (u32)rows;
-    control2[kChainsColumns] = 1;
+    control[kChainsColumns] = 0;
   }
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < items; i += (size_t)gridDim.x * blockDim.x) {
+  for (size_t i = at; i * portion < rows; i += step) {
+    u32* c = portions + i * kPortionWords;
+    c[kChainsTotal] = (u32)std::min(rows - i * portion, portion);
+    c[kChainsColumns] = 1;
+    c[kPortionNext] = 0;
+  }
+  for (size_t i = at; i < items; i += step) {
     const u32 row = order[i >> seg_shift], seg = (u32)i & ((1u << seg_shift) - 1u);
     const u64 len = counts[row];
     const u32 e0 = (u32)((len * seg) >> seg_shift), e1 = (u32)((len * (seg + 1u)) >> seg_shift);
-    chains[i] = make_uint4((row << seg_shift) + seg, (u32)(row * list_stride) + e0, e1 - e0, 0u);
+    const u32 place = rows > portion ? (u32)(i % portion) : (row << seg_shift) + seg;
+    chains[i] = make_uint4(place, (u32)(row * list_stride) + e0, e1 - e0, 0u);
     if (seg == 0 && seg_shift) chains[items + row] = make_uint4(row, row << seg_shift, 1u << seg_shift, 0u);
   }
 }
@@ -709,11 +716,12 @@ __device__ __forceinline__ void xw_store_result(u32* dst, Elem<LPT, PAIR>& acc, 
   }
 }
 
-// The same from the residue engine's columns
+// The same from the residue engine's columns, those of row order[i], if there is an order, at place i
 template <int LPT, int T>
 __global__ __launch_bounds__(kBlockThreads, 4) void k_xw_leave(ModRef M, const u32* __restrict__ leave,
                                                                const long long* __restrict__ columns, int stride,
-                                                               size_t rows, u32* __restrict__ out) {
+                                                               size_t rows, const u32* __restrict__ order,
+                                                               u32* __restrict__ out) {
   constexpr int EL = 2 * LPT * T;
   Grp<T> g;
   Batch<T> bt;
@@ -726,7 +734,8 @@ __global__ __launch_bounds__(kBlockThreads, 4) void k_xw_leave(ModRef M, const u
     Elem<LPT, true> acc;
     load_columns<LPT, T>(acc.x0, src, g);
     load_columns<LPT, T>(acc.x1, src + stride, g);
-    xw_store_result<LPT, T, true>(out + (active ? row : 0) * (size_t)EL, acc, active, leave, mod, g);
+    const size_t to = !active ? 0 : order ? order[row] : row;
+    xw_store_result<LPT, T, true>(out + to * (size_t)EL, acc, active, leave, mod, g);
   }
 }
 
@@ -879,8 +888,9 @@ struct XwPlan {
   // [kXwBinsAt, kXwBinsAt + kLenBins) the length classes
   size_t off_inv, off_tables, off_nz, off_cnt, off_order, off_partial, total;
   int seg_shift;  // every row's list is multiplied in 2^seg_shift segments
-  // in the residue form words 2 and 3 are counters too, from 8 on what the device finds about programs and chains
-  size_t off_pairs, off_powers, off_chains, off_items, off_columns;
+  // in the residue form word 2 is a counter too, from 8 on there is what the device finds about programs and chains
+  size_t off_pairs, off_portions, off_powers, off_chains, off_items, off_columns;
+  size_t portion;  // rows whose products lie in columns at a time
   XwTablePlan tables;
 };
 constexpr size_t kXwControlAt = 8;
@@ -894,7 +904,7 @@ int xw_seg_shift(const haflo_ctx* ctx, size_t rows, size_t cols) {
   return sh;
 }
 XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  XwPlan p;
+  XwPlan p = {};
   const size_t nl = (size_t)ctx->N.nl;
   p.off_inv = kXwBinsAt + kLenBins;
   p.off_tables = p.off_inv + cols * nl;
@@ -910,7 +920,8 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
 // by 2 0.462 / 0.466; 40000 by 4 0.66 / 0.54, 4096 by 8 0.52 / 0.47, 1000 by 64 0.68 / 0.53, 64 by 256 1.14 / 0.70, 65536 by 32
 // 1.77 / 1.07, 16384 by 256 3.51 / 1.65. 4096 bits: 4096 by 8 1.17 / 1.31, 2000 by 32 1.44 / 1.46; 4096 by 32 1.65 / 1.55, 1000 by
 // 64 1.67 / 1.57, 64 by 256 3.25 / 2.57, 16384 by 64 4.00 / 3.12. At 1024 bits limbs are the quicker: 16384 by 64 0.54 / 0.69.
-// List places and table entries are 32-bit, and an entry takes twice the memory: beyond 2048 columns (5 GB at 2048 bits) limbs.
+// List places and table entries are 32-bit. An entry takes twice the memory of limbs: beyond 2048 columns (tables of 5 GB at 2048
+// bits, 10 at 4096) limbs. Rows take no more than on limbs but for one portion's columns (xw_portion) and 16 bytes each.
 bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
   if (!ctx->Nh.d_rns || rows >= (1u << 28) || cols > 2048 || rows > 0xFFFFFFFFull / kMaxPos / (cols ? cols : 1)) return false;
   return (ctx->Nh.nl == 72 && cols >= 4) || (ctx->Nh.nl == 144 && (cols >= 64 || (cols >= 32 && rows >= 4096)));
@@ -921,12 +932,20 @@ int xw_residue_shift(const haflo_ctx* ctx, size_t rows, size_t cols) {
   while (sh < 5 && (rows << sh) < (size_t)ctx->num_cu * 256 && cols >= ((size_t)16 << sh)) ++sh;
   return sh;
 }
+// Rows that leave the residue form at a time: at most 524288 on 256 compute units, 0.6 GB of columns at 2048 bits and 1.2 at 4096, in
+// portions of one size. A further portion costs some 45 us (1000000 rows by 4 at 2048 bits 2.78 ms in one, 2.82 in two, 2.95 in
+// four, 3.41 in sixteen). Far more than what is cut into segments.
+size_t xw_portion(const haflo_ctx* ctx, size_t rows) {
+  const size_t most = (size_t)ctx->num_cu * 2048, portions = (rows + most - 1) / most;
+  return portions > 1 ? ((rows + portions - 1) / portions + 15) & ~(size_t)15 : most;
+}
 XwPlan xw_residue_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  XwPlan p;
+  XwPlan p = {};
   const size_t nl = (size_t)ctx->N.nl, item = rns_item_words(ctx->Nh), tabs = cols * 2 * kMaxPos;
   const auto aligned = [](size_t w) { return (w + 63) & ~(size_t)63; };
   p.seg_shift = xw_residue_shift(ctx, rows, cols);
   const size_t chains = (rows << p.seg_shift) + (p.seg_shift ? rows : 0);
+  p.portion = xw_portion(ctx, rows);
   p.off_inv = kXwBinsAt + kLenBins;
   p.off_pairs = p.off_inv + cols * nl;
   size_t at = p.off_pairs + (cols * 2 + 1) * nl;
@@ -937,8 +956,9 @@ XwPlan xw_residue_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
     at += words[i];
   }
   p.tables.control = kXwControlAt;
-  p.tables.live = kXwControlAt + 3 * kChainsControl;
-  p.off_nz = at;
+  p.tables.live = kXwControlAt + 2 * kChainsControl;
+  p.off_portions = at;
+  p.off_nz = at + (rows + p.portion - 1) / p.portion * kPortionWords;
   p.off_cnt = p.off_nz + rows * cols * kMaxPos;
   p.off_order = p.off_cnt + rows;
   p.off_chains = p.tables.chains = aligned(p.off_order + rows);
@@ -946,7 +966,7 @@ XwPlan xw_residue_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.off_items = p.off_powers + (cols * 2 + 1) * kNibbles * item;
   p.off_partial = p.off_items + tabs * kWinEntries * item;
   p.off_columns = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * item : 0);
-  p.total = p.off_columns + rows * 4 * (size_t)rns_columns(ctx->Nh);
+  p.total = p.off_columns + std::min(rows, p.portion) * 4 * (size_t)rns_columns(ctx->Nh);
   return p;
 }
 // what a call asks for where the residue engine serves it (its start is aligned to 256 bytes), else 0
@@ -1240,29 +1260,37 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
     u32* partial = ws + p.off_partial;
     if (residues) {
       u32* control = ws + kXwControlAt + kChainsControl;
+      u32* portions = ws + p.off_portions;
       HAFLO_LAUNCH(k_xw_chains, launch_shape(ctx, rows << p.seg_shift, 1, 8), st, rows, cols * (size_t)kMaxPos, p.seg_shift,
-                   (const u32*)cnt, (const u32*)order, (uint4*)(ws + p.off_chains), control, control + kChainsControl);
+                   p.portion, (const u32*)cnt, (const u32*)order, (uint4*)(ws + p.off_chains), control, portions);
+      chains.chains = ws + p.off_chains;
       chains.index = lists;
-      chains.control = control;
-      chains.next = ws + 1;
       chains.out = partial;
       chains.columns = (long long*)(ws + p.off_columns);
-      rc = rns_chains(ctx, mh, chains, rows << p.seg_shift, rows << p.seg_shift, st);
-      if (rc == HAFLO_OK && p.seg_shift) {
+      if (p.seg_shift) {
+        chains.control = control;
+        chains.next = ws + 1;
+        rc = rns_chains(ctx, mh, chains, rows << p.seg_shift, rows << p.seg_shift, st);
+        if (rc != HAFLO_OK) return rc;
         chains.items = partial;
         chains.chains += (rows << p.seg_shift) * 4;
         chains.index = nullptr;
-        chains.control += kChainsControl;
-        chains.next = ws + 3;
-        rc = rns_chains(ctx, mh, chains, rows, rows, st);
       }
-      if (rc != HAFLO_OK) return rc;
-      const LaunchShape sh = launch_shape(ctx, rows, lanes, 8);
+      for (size_t at = 0; at < rows; at += p.portion) {
+        const size_t count = std::min(rows - at, p.portion);
+        chains.control = portions + at / p.portion * kPortionWords;
+        chains.next = portions + at / p.portion * kPortionWords + kPortionNext;
+        rc = rns_chains(ctx, mh, chains, count, count, st);
+        if (rc != HAFLO_OK) return rc;
+        chains.chains += count * 4;
+        const u32* places = rows > p.portion ? order + at : nullptr;
+        const LaunchShape sh = launch_shape(ctx, count, lanes, 8);
 #define CALL(LPT, T)                                                                                            \
   HAFLO_LAUNCH((k_xw_leave<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstMStored * 2 * mh.nl),  \
-               (const long long*)(ws + p.off_columns), rns_columns(mh), rows, (u32*)d_out)
-      HAFLO_DISPATCH_PAIRS(mh, CALL);
+               (const long long*)(ws + p.off_columns), rns_columns(mh), count, places, (u32*)d_out)
+        HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL
+      }
       return hip_status(hipGetLastError());
     }
     {

@@ -198,10 +198,11 @@ def test_gradient_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
 
 
 @pytest.mark.parametrize("bits,kind,rows,cols", [(2048, "random", 37, 4), (2048, "sparse", 41, 16), (2048, "zero", 300, 4),
-                                                 (4096, "sparse", 3, 64)])
+                                                 (2048, "tall", 2065, 4), (4096, "sparse", 3, 64)])
 def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     """Tables and row products in the residue form (the workspace asked for) and on limbs (the least): rows in several
-    chains and in one, empty rows, exponents of all digit positions and none."""
+    chains and in one, empty rows, exponents of all digit positions and none; more rows than leave the form at a time (2048 on
+    the one-unit emulated chip)."""
     lib = emu
     p, q = oracle_key(bits)
     n, rng = p * q, random.Random(rows)
@@ -216,6 +217,10 @@ def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     if kind == "zero":
         x[:] = 0
         x[5, 0], x[40, 3] = 255, -16  # lists of one entry
+    if kind == "tall":
+        x[:] = 0
+        x[:, 0] = np.arange(rows) % 7 - 3
+        x[:, 3] = np.arange(rows) % 5 // 4
     want = O.matvec(O.PrivateKey(p, q).public, 1, cs, x.tolist())
     for room in ("asked", "least"):
         assert matvec(lib, ctx, bits, 1, cs, x, room) == want, room
@@ -237,3 +242,17 @@ def test_gradient_workspace_is_bounded(emu, bits, rows, cols):  # noqa: F811
     emu.haflo_ctx_destroy(ctx)
     assert least <= asked <= 2.2 * least
     assert asked == least or asked <= 32 << 30
+
+
+@pytest.mark.parametrize("bits,rows,cols", [
+    (2048, 64, 4), (2048, 65536, 32), (2048, 16384, 256), (2048, 100, 2048), (2048, 1 << 24, 4), (2048, 1 << 24, 8),
+    (2048, 40000000, 4), (4096, 1 << 20, 32), (4096, 300, 2048)])
+def test_forward_workspace_is_bounded(emu, bits, rows, cols):  # noqa: F811
+    """The same for the forward product: its rows' lists are as long as on limbs, their products leave the form in portions
+    of bounded size (0.6 GB at 2048 bits on 256 compute units; here there is one), and a row's place among them is 16 bytes."""
+    p, q = oracle_key(bits)
+    ctx = public_ctx(emu, p * q, bits)
+    asked = emu.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_X_W, rows, cols)
+    least = emu.haflo_workspace_bytes_least(ctx, _cabi.OP_MATVEC_X_W, rows, cols)
+    emu.haflo_ctx_destroy(ctx)
+    assert least < asked <= 2.2 * least + (bits // 2048 << 22)

@@ -229,10 +229,11 @@ def test_gradient_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, t
     assert torch.equal(api.haflo_cipher_matvec(ctx, 0, c, x), matvec_on_limbs(api, ctx, 0, c, x))
 
 
-# rows in 1, 2 and up to 16 chains, one to four digits; at 4096 bits shapes next to the rule
+# rows in 1, 2 and up to 16 chains, one to four digits, more rows than leave the form at a time; at 4096 bits shapes next to
+# the rule
 @pytest.mark.parametrize("bits,rows,cols,top", [
     (2048, 81920, 4, 1 << 16), (2048, 10241, 32, 1 << 9), (2048, 641, 512, 200), (2048, 40001, 17, 1 << 28), (2048, 129, 5, 1 << 16),
-    (4096, 4096, 32, 1 << 16), (4096, 131, 64, 200), (4096, 6001, 65, 1 << 28)])
+    (2048, 530001, 4, 1 << 16), (4096, 4096, 32, 1 << 16), (4096, 131, 64, 200), (4096, 6001, 65, 1 << 28)])
 def test_forward_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, top):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
