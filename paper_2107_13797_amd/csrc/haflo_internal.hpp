@@ -264,7 +264,7 @@ struct RnsLists {
   const uint32_t* tables;    // set by rns_lists()
   const uint32_t* items;
   const uint32_t* one;
-  const uint32_t* operands;  // `rows` of them, of `stride` words
+  const uint32_t* operands;  // `rows` of them, of `stride` words; without any `items` and `one` are not read
   const uint32_t* places;    // null: an element's is its own number
   size_t stride;
   int rows;

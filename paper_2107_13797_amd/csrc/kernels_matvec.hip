@@ -1003,12 +1003,8 @@ int xw_residue_tables(const haflo_ctx* ctx, const XwPlan& p, const u32* d_c, siz
   const u32* one = ws + p.off_powers + cols * 2 * kNibbles * rns_item_words(mh);
   for (int i = 0; i < 2; ++i) {
     RnsLists j = {};
-    j.items = ws + p.off_powers;
-    j.one = one;
-    j.operands = ws + t.operands;
     j.places = ws + t.places[i];
     j.stride = i ? cols * 2 * kNibbles : cols * 2 + 1;
-    j.rows = i;
     j.live = ws + t.live + i;
     j.out = ws + (i ? p.off_items : p.off_powers);
     if (i == 0) {
@@ -1021,6 +1017,10 @@ int xw_residue_tables(const haflo_ctx* ctx, const XwPlan& p, const u32* d_c, siz
         j.add(LIST_STORE_ACC);
       }
     } else {
+      j.items = ws + p.off_powers;
+      j.one = one;
+      j.operands = ws + t.operands;
+      j.rows = 1;
       j.add(LIST_RUN_ITEM);
       for (int d = 1; d < 16; ++d) {
         j.add(LIST_ACC_RUN);

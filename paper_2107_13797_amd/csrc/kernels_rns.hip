@@ -1664,7 +1664,9 @@ __device__ __forceinline__ void run_lists(G& e, const RnsLists& j, ListShared& s
     __syncthreads();
     int row = 0;
     const auto next_place = [&]() { return sh.place[row < j.rows ? row : j.rows - 1][own]; };
-    const auto item = [&](u32 p) { return p == kNoOperand ? j.one : j.items + (size_t)p * rns::item_words(G::kRegs); };
+    // A program without operands, as those that make the element `one`, asks for constants in their place, and uses none.
+    const u32* none = j.rows ? j.one : j.tables;
+    const auto item = [&](u32 p) { return p == kNoOperand ? none : j.items + (size_t)p * rns::item_words(G::kRegs); };
     const u32* place = j.places + first;
     typename G::State run = {}, acc = {};
     bool run_one = true, acc_one = true;  // known to be one in all elements
@@ -1897,8 +1899,7 @@ int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, size_t
   }
   RnsLists j = {};
   j.limbs = in;
-  j.one = items;
-  j.items = j.out = items;
+  j.out = items;
   j.stride = count;
   j.add(LIST_ACC_LIMBS);
   j.add(LIST_STORE_ACC);

@@ -256,3 +256,28 @@ def test_forward_workspace_is_bounded(emu, bits, rows, cols):  # noqa: F811
     least = emu.haflo_workspace_bytes_least(ctx, _cabi.OP_MATVEC_X_W, rows, cols)
     emu.haflo_ctx_destroy(ctx)
     assert least < asked <= 2.2 * least + (bits // 2048 << 22)
+
+
+@pytest.mark.skipif(os.environ.get("HAFLO_EMU_SANITIZE", "") == "1", reason="links the plain build")
+def test_programs_without_operands_read_none(emu, tmp_path):  # noqa: F811
+    """A program that takes its elements from limbs runs while the launch that it is part of writes the element `one`: it
+    must not load that, nor any operand. In a process of its own, where a read through a null pointer ends it."""
+    import build_emu
+    out = str(tmp_path / "liblists_shim.so")
+    root, lib_dir = os.path.dirname(HERE), os.path.dirname(build_emu.OUT)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wno-unknown-pragmas", "-o", out,
+                    "-I", os.path.join(HERE, "emu", "include"), "-I", os.path.join(root, "include"),
+                    "-I", os.path.join(root, "paper_2107_13797_amd", "csrc"), os.path.join(HERE, "rns_lists_shim.cpp"),
+                    "-L", lib_dir, "-l:" + os.path.basename(build_emu.OUT), "-Wl,-rpath," + lib_dir], check=True)
+    shim = C.CDLL(out)
+    shim.lists_item_words.restype = C.c_size_t
+    bits, count = 2048, 3
+    p, q = oracle_key(bits)
+    ctx = public_ctx(emu, p * q, bits)
+    limbs = Dev(emu, np.random.default_rng(1).integers(0, 1 << 29, (count, bits * 9 // 128), dtype=np.uint32))
+    items = zeros(emu, (count, shim.lists_item_words(ctx)))
+    child = os.fork()
+    if child == 0:
+        os._exit(0 if shim.lists_without_operands(ctx, C.c_void_p(limbs.p), C.c_size_t(count), C.c_void_p(items.p)) == 0 else 1)
+    assert os.waitpid(child, 0)[1] == 0
+    emu.haflo_ctx_destroy(ctx)
