@@ -6,6 +6,7 @@ import random
 
 import numpy as np
 
+from conftest import oracle_key
 from oracle import paillier_oracle as O
 from paper_2107_13797_amd import _cabi, synth
 from test_emu_kernels import BITS, Dev, emu, env, words, zeros  # noqa: F401  (fixtures)
@@ -234,6 +235,41 @@ def test_store_matvec_sum_and_scalars_match_oracle(env):
     # temporaries are gone: what is live is hc, hx, f, t, e
     assert st.stats()["live_objects"] == 5 and st.stats()["peak_bytes"] > st.stats()["live_bytes"]
     st.close()
+
+
+def test_store_matvec_in_the_workspace_there_is(emu):  # noqa: F811
+    """A matvec takes the workspace that it asks for from the arena, and the least where there is no room for more; without
+    room for that it consumes nothing."""
+    lib, bits, rows, cols = emu, 2048, 3, 4
+    p, q = oracle_key(bits)
+    n, rng = p * q, random.Random(5)
+    ctx = C.c_void_p()
+    buf = (C.c_uint8 * (bits // 8)).from_buffer_copy(n.to_bytes(bits // 8, "little"))
+    assert lib.haflo_ctx_create_public(buf, bits, C.byref(ctx)) == 0
+    asked = lib.haflo_workspace_bytes(ctx, K.OP_MATVEC_X_W, rows, cols)
+    least = lib.haflo_workspace_bytes_least(ctx, K.OP_MATVEC_X_W, rows, cols)
+    assert least + (1 << 16) < asked
+    cs = [rng.randrange(2, n * n) for _ in range(cols)]
+    x = np.array([[1, 0, -3, 300], [0, 0, 0, 0], [7, -255, 0, 1]], dtype=np.int32)
+    want = O.matvec(O.PrivateKey(p, q).public, 1, cs, x.tolist())
+    granules = 1 << 14  # the operands and the result
+    for room in (asked, least, least - (1 << 16)):
+        st = EmuStore(lib, ctx, (room + granules + 255) // 256 * 256)
+        rc, hc = st.new(K.KIND_CIPHER, cols, 0)
+        assert rc == 0
+        assert lib.haflo_import_cipher(ctx, words(lib, cs, bits // 16).p, st.info(hc)[2], None, cols, None) == 0
+        hx = st.up(K.KIND_I32, x, rows * cols)
+        live = st.stats()
+        rc, f = st.op("haflo_h_matvec", 1, hc, hx, rows, cols, 1)
+        if room < least:
+            assert rc == ENOMEM and st.info(hx)[3] == 1 and st.stats()["live_objects"] == live["live_objects"]
+        else:
+            assert rc == 0 and (st.stats()["peak_bytes"] > asked) == (room == asked)
+            out = zeros(lib, (rows, bits // 16))
+            assert lib.haflo_export_cipher(ctx, st.info(f)[2], out.p, rows, None) == 0
+            assert synth.words_to_ints(out.get()) == want
+        st.close()
+    lib.haflo_ctx_destroy(ctx)
 
 
 def test_store_allocator_random_sequences(env):

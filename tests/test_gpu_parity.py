@@ -396,6 +396,17 @@ def test_edges_matvec(api, bits, method):
         _edges_matvec(api, bits, method, ctx, sk)
 
 
+@pytest.mark.parametrize("bits,method", [(2048, "tables"), (2048, "buckets"), (4096, "tables")])
+def test_edges_matvec_public(api, bits, method):
+    """The same with a public context, whose products at these sizes run in residues: at 2048 bits those of both orientations,
+    the gradient's by buckets, at 4096 bits the forward ones of 70 columns."""
+    _, sk = context(api, bits)
+    ctx = api.haflo_ctx_create_public(sk.public.n, bits)
+    with xtd_method(api, ctx, method):
+        _edges_matvec(api, bits, method, ctx, sk)
+    ctx.close()
+
+
 def _edges_matvec(api, bits, method, ctx, sk):
     pk = sk.public
     n = pk.n

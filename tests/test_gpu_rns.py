@@ -214,7 +214,8 @@ def random_ciphertexts(api, ctx, n, bits, count):
         ctx, to_dev(random_units_words(count, 2 * bits, bits + 4))))
 
 
-# chunks of 16 and of 32 items, one to four rounds, chains on wavefronts and on blocks; at 4096 bits shapes next to the rule
+# chunks of 16 and of 32 items, one to four rounds, chains on wavefronts and on blocks, all digit positions (the extremes have
+# them); at 4096 bits shapes next to the rule
 @pytest.mark.parametrize("bits,rows,cols,top", [
     (2048, 4096, 1, 1 << 18), (2048, 4099, 32, 1 << 18), (2048, 5043, 26, 600), (2048, 65537, 2, 40), (2048, 140001, 1, 3),
     (2048, 32768, 33, 1 << 17), (4096, 4096, 32, 1 << 18), (4096, 8201, 16, 40), (4096, 9001, 41, 1 << 17)])
@@ -229,8 +230,8 @@ def test_gradient_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, t
     assert torch.equal(api.haflo_cipher_matvec(ctx, 0, c, x), matvec_on_limbs(api, ctx, 0, c, x))
 
 
-# rows in 1, 2 and up to 16 chains, one to four digits, more rows than leave the form at a time; at 4096 bits shapes next to
-# the rule
+# rows in 1, 2 and up to 16 chains, lists of no to four digits an entry, all digit positions, more rows than leave the form at a
+# time; at 4096 bits shapes next to the rule
 @pytest.mark.parametrize("bits,rows,cols,top", [
     (2048, 81920, 4, 1 << 16), (2048, 10241, 32, 1 << 9), (2048, 641, 512, 200), (2048, 40001, 17, 1 << 28), (2048, 129, 5, 1 << 16),
     (2048, 530001, 4, 1 << 16), (4096, 4096, 32, 1 << 16), (4096, 131, 64, 200), (4096, 6001, 65, 1 << 28)])
@@ -246,5 +247,88 @@ def test_forward_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, to
     x[64:128] = 0
     x[64:128, 0] = torch.arange(-32, 32, dtype=torch.int32, device="cuda")
     if top < 256:
-        x[x.abs() > 4 * 1024] = 7  # one digit throughout
+        x[x.abs() > 4 * 1024] = 7
     assert torch.equal(api.haflo_cipher_matvec(ctx, 1, c, x), matvec_on_limbs(api, ctx, 1, c, x))
+
+
+@pytest.fixture(scope="module")
+def public_and_ciphertexts():
+    """A public context and 4100 ciphertexts, once per key size."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    made = {}
+
+    def get(bits):
+        if bits not in made:
+            p, q = oracle_key(bits)
+            ctx = api.haflo_ctx_create_public(p * q, bits)
+            made[bits] = api, ctx, random_ciphertexts(api, ctx, p * q, bits, 4100)
+        return made[bits]
+    return get
+
+
+# The programs' length, the elements that are live and, in the forward tables, the last position's products depend on the largest
+# magnitude: at and next to the points where a digit position is added (gradient: 511, 512 | 523775, 523776 | 535821823; forward:
+# 255, 256 | 65535, 65536) and where the last digit has no or one product of two nibbles (1, 15, 16, 17).
+@pytest.mark.parametrize("largest", [1, 15, 16, 17, 31, 33, 200, 255, 256, 511, 512, 0x1105, 65535, 0x12345, 523775, 523776,
+                                     0xABCDEF, 535821823, 0x10000000, 2 ** 31 - 1])
+@pytest.mark.parametrize("bits,rows,cols", [(2048, 4099, 5), (4096, 4100, 33)])
+def test_matvecs_in_residues_by_largest_magnitude(public_and_ciphertexts, bits, rows, cols, largest):
+    api, ctx, c = public_and_ciphertexts(bits)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(largest)
+    x = (torch.rand((rows, cols), device="cuda", generator=gen, dtype=torch.float64) * (2.0 * largest + 1)).floor() - largest
+    x = x.to(torch.int64).clamp(-largest, largest).to(torch.int32)
+    x[torch.rand(x.shape, device="cuda", generator=gen) < 0.3] = 0
+    x[rows // 2, cols - 1] = -largest
+    assert int(x.to(torch.int64).abs().max()) == largest
+    for orientation, n in ((0, rows), (1, cols)):
+        used = c[:n].contiguous()
+        assert torch.equal(api.haflo_cipher_matvec(ctx, orientation, used, x), matvec_on_limbs(api, ctx, orientation, used, x))
+
+
+@pytest.mark.parametrize("bits,cols", [(2048, 3), (4096, 32)])
+def test_gradient_in_residues_against_the_oracle(public_and_ciphertexts, bits, cols):
+    """4096 rows, where public contexts multiply in residues: two columns as plain products of powers."""
+    api, ctx, c = public_and_ciphertexts(bits)
+    rows = 4096
+    p, q = oracle_key(bits)
+    nsq = (p * q) ** 2
+    x = exponents(rows, cols, 1 << 18, bits)
+    assert api.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_XT_D, rows, cols) > api.haflo_workspace_bytes_least(
+        ctx, _cabi.OP_MATVEC_XT_D, rows, cols)
+    used = c[:rows].contiguous()
+    got = dev_to_ints(api.haflo_export_cipher(ctx, api.haflo_cipher_matvec(ctx, 0, used, x)))
+    cs, xs = dev_to_ints(api.haflo_export_cipher(ctx, used)), x.cpu().tolist()
+    for j in (0, cols // 2):
+        parts = [1, 1]  # factors with exponents above and below zero
+        for ci, row in zip(cs, xs):
+            if row[j]:
+                parts[row[j] < 0] = parts[row[j] < 0] * pow(ci, abs(row[j]), nsq) % nsq
+        assert got[j] * parts[1] % nsq == parts[0]
+
+
+def test_taylor_loss_with_its_matvec_in_residues(public_and_ciphertexts):
+    """4096 rows at a 2048-bit key: the loss's one column goes through the residue form in the workspace asked for, and not in
+    the least."""
+    api, ctx, c = public_and_ciphertexts(2048)
+    lib, count, s = api.lib(), 4097, 20
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    u = torch.randn(count, device="cuda", generator=gen)
+    y = torch.where(torch.rand(count, device="cuda", generator=gen) < 0.5, -1.0, 1.0)
+    r = to_dev(random_units_words(1, 2048, 8))
+    c_u, c_u2 = c[:count].contiguous(), c[3:3 + count].contiguous()
+    asked, least = (f(ctx, _cabi.OP_TAYLOR_LOSS, count, 0) for f in (api.haflo_workspace_bytes, api.haflo_workspace_bytes_least))
+    matvec = api.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_XT_D, count, 1)
+    assert least < matvec < asked
+    outs = []
+    for nbytes in (asked, least):
+        ws, out = torch.empty(nbytes, dtype=torch.uint8, device="cuda"), torch.empty_like(c[:1])
+        assert lib.haflo_taylor_loss(ctx.handle, *[C.c_void_p(t.data_ptr()) for t in (c_u, c_u2, u, y, r)], s,
+                                     C.c_void_p(out.data_ptr()), None, count, C.c_void_p(ws.data_ptr()), nbytes,
+                                     C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        outs.append(out)
+    assert torch.equal(*outs)
+    assert torch.equal(outs[0], api.haflo_taylor_loss(ctx, c_u, c_u2, u, y, r, s))
