@@ -926,10 +926,14 @@ bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
   if (!ctx->Nh.d_rns || rows >= (1u << 28) || cols > 2048 || rows > 0xFFFFFFFFull / kMaxPos / (cols ? cols : 1)) return false;
   return (ctx->Nh.nl == 72 && cols >= 4) || (ctx->Nh.nl == 144 && (cols >= 64 || (cols >= 32 && rows >= 4096)));
 }
-// Segments per row: doubled while the engine has no more than its fill of chains, and a list of 30 % a few factors a chain
+// Segments per row: doubled while the engine has no more than its fill of chains, and a list of 30 % a few factors a chain. A
+// compute unit has 192 chains in flight at 2048 bits and 16 at 4096, where a further segment's product weighs more: 20000 by 64 with
+// 30 % of four digits 3.55 ms at up to 256 chains to a compute unit, 3.47 at 64, 3.48 at 16; with 5 % of one digit 1.52, 1.28, 1.27;
+// 5000 by 64 with 30 % 1.94, 1.91, 2.23.
 int xw_residue_shift(const haflo_ctx* ctx, size_t rows, size_t cols) {
   int sh = 0;
-  while (sh < 5 && (rows << sh) < (size_t)ctx->num_cu * 256 && cols >= ((size_t)16 << sh)) ++sh;
+  const size_t fill = (size_t)ctx->num_cu * (ctx->Nh.nl == 144 ? 64 : 256);
+  while (sh < 5 && (rows << sh) < fill && cols >= ((size_t)16 << sh)) ++sh;
   return sh;
 }
 // Rows that leave the residue form at a time: at most 524288 on 256 compute units, 0.6 GB of columns at 2048 bits and 1.2 at 4096, in
