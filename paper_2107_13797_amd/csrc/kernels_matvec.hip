@@ -67,7 +67,8 @@ __host__ __device__ inline int signed_digit_positions(unsigned maxmag) {
 // where f0 and g0 are wave-uniform) as well as on the vector unit; a row of the matrix is one 64-bit integer, u + 2^32 v,
 // on which shifts, sums and differences are those of its entries. About half as many loop rounds as steps, of 23 scalar
 // instructions each. They bound the inversion, whose wavefront issues one at a time: with masks on four entries, 36 of them,
-// 32 inversions took 142, 280 us at 1024 and 2048 bits, now 104 and 205.
+// 32 inversions took 142, 280 us at 1024 and 2048 bits, now 104 and 205. Several integers to a wavefront, on the vector unit, gain
+// too: 20000 powers by -5 at 1024, 2048 and 4096 bits 466, 1297 and 4134 us, now 426, 1169 and 3766.
 __device__ __forceinline__ void divsteps29(int& delta, u32 f0, u32 g0, s32& u, s32& v, s32& q, s32& r) {
   s32 eta = -delta;  // the swap condition is eta < 0
   u64 row_f = 1, row_g = 1ull << 32;
@@ -916,10 +917,12 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   p.total = p.off_partial + (p.seg_shift ? (rows << p.seg_shift) * nl : 0);
   return p;
 }
-// Tables and rows in the residue form. Whole calls on limbs / in residues, ms, 70 % zeros. 2048 bits: 65536 by 1 0.56 / 0.57, 16384
-// by 2 0.462 / 0.466; 40000 by 4 0.66 / 0.54, 4096 by 8 0.52 / 0.47, 1000 by 64 0.68 / 0.53, 64 by 256 1.14 / 0.70, 65536 by 32
-// 1.77 / 1.07, 16384 by 256 3.51 / 1.65. 4096 bits: 4096 by 8 1.17 / 1.31, 2000 by 32 1.44 / 1.46; 4096 by 32 1.65 / 1.55, 1000 by
-// 64 1.67 / 1.57, 64 by 256 3.25 / 2.57, 16384 by 64 4.00 / 3.12. At 1024 bits limbs are the quicker: 16384 by 64 0.54 / 0.69.
+// Tables and rows in the residue form. Whole calls on limbs / in residues, ms, 70 % zeros. 2048 bits: 65536 by 1 0.482 / 0.492, 16384
+// by 2 0.408 / 0.406; 40000 by 4 0.62 / 0.50, 4096 by 8 0.46 / 0.40, 1000 by 64 0.62 / 0.46, 64 by 256 1.11 / 0.62, 65536 by 32
+// 1.89 / 0.99, 16384 by 256 3.78 / 1.69. 4096 bits: 4096 by 8 0.99 / 1.16, 2000 by 32 1.26 / 1.28; 4096 by 32 1.51 / 1.40, 1000 by
+// 64 1.49 / 1.40, 64 by 256 3.05 / 2.39, 16384 by 64 4.15 / 3.13. At 1024 bits limbs are the quicker: 16384 by 64 0.54 / 0.69.
+// The shape does not say how many entries are zero: with less than one factor a row at 2048 bits, some five at 4096, limbs are
+// (300000 by 4 with 10 % of one digit 0.84 / 1.05 at 2048, 20000 by 64 with 5 % 1.13 / 1.28 at 4096).
 // List places and table entries are 32-bit. An entry takes twice the memory of limbs: beyond 2048 columns (tables of 5 GB at 2048
 // bits, 10 at 4096) limbs. Rows take no more than on limbs but for one portion's columns (xw_portion) and 16 bytes each.
 bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {

@@ -659,7 +659,8 @@ __global__ __launch_bounds__(rns_waves_per_simd(kSets) * 256, rns_waves_per_simd
 // 65536 encryptions at a 2048-bit key take 48.5 ms with it (49.2 with the residues of before, kept below 2^31 by 54
 // instructions per prime instead of 47), 52.4 with k_rns's two sets of which every wavefront's 256 registers are full:
 // tables and spilled registers then wait for memory, two wavefronts per SIMD are too few to hide it. k_rns's one set with three
-// wavefronts of 168 registers, which lies between, was not measured.
+// wavefronts of 168 registers, which lies between, spills 348 of them: 49152 elements 39.4 ms against 37.8. This kernel with three
+// wavefronts of 154, without a spill, takes 36.8 for those, but for 65536, 1.33 passes then, 64.8.
 // The residues of x0 and x1 of a lane in one base: full quads of each, and one quad with the last two of both.
 template <int NR>
 struct OneResidues {
@@ -1076,8 +1077,9 @@ __global__ __launch_bounds__(1024, 4) void k_rns_enter(const u32* __restrict__ t
 
 // Every wavefront multiplies 16 lists side by side, up to the longest of them. A factor's quads are on their way one step
 // ahead, its place two products ahead. What bounds it are the matrix products and the vector unit's work between them, one
-// after the other within a wavefront: 2.75 x 10^6 products a ms, with three wavefronts of 168 registers per SIMD; with four of
-// 128, which spill 88 of them, 2.55 x 10^6 (65536 by 32 entries' gradient 2.81 / 3.19 ms). The limb arithmetic forms 1.0 x 10^6.
+// after the other within a wavefront: 2.9 x 10^6 products a ms, matrix cores 59 % and vector issue 54 % of the cycles, with three
+// wavefronts of 168 registers per SIMD; with four of 128, which spill 88 of them, 8 % less (65536 by 32 entries' gradient 2.81 /
+// 3.19 ms). The limb arithmetic forms 1.0 x 10^6.
 template <int NR>
 __global__ __launch_bounds__(768, 3) void k_rns_chains(RnsChains j) {
   __shared__ __align__(16) u32 lds[rns::lds_bytes(NR) / 4];
@@ -1827,12 +1829,12 @@ namespace {
 // The blocks of k_rns_group that are resident at once on a compute unit
 int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
 // Blocks of 8 elements, while each has a compute unit to itself. ms with 16 / 8 to a block, up to the line: 2048 encryptions at
-// a 1024-bit key 1.06 / 0.87, at 2048 bits 3.58 / 2.42, at 4096 bits 21.8 / 20.6 (100 of them 20.8 / 18.2); 1024 decryptions at
-// 1024 bits 0.465 / 0.425, at 2048 bits 1.12 / 0.94, at 4096 bits 3.64 / 2.53. Beyond it, with two blocks of 8 and more to a
-// compute unit: encryptions at 1024 bits 1.06 / 1.67 (2049), 1.08 / 1.69 (4096), 2.10 / 2.51 (6144), at 2048 bits 3.57 / 4.80
-// (2049), 3.62 / 4.68 (4096), at 4096 bits 21.8 / 40.5 (2049); decryptions at 2048 bits 1.12 / 1.73 (1025), at 4096 bits 3.65 /
-// 4.95. The short products of 256-bit primes are no slower there while at most four blocks share a compute unit, and little
-// faster: 0.457 / 0.439 (1025 decryptions at a 1024-bit key), 0.460 / 0.457 (2048), 0.519 / 0.518 (3072), 0.52 / 0.58 (4096).
+// a 1024-bit key 0.97 / 0.74, at 2048 bits 3.40 / 2.21, at 4096 bits 21.3 / 20.7 (100 of them 20.7 / 17.9); 1024 decryptions at
+// 1024 bits 0.399 / 0.354, at 2048 bits 1.03 / 0.79, at 4096 bits 3.47 / 2.30. Beyond it, with two blocks of 8 and more to a
+// compute unit: encryptions at 1024 bits 0.97 / 1.40 (2049), 0.99 / 1.43 (4096), 1.92 / 2.12 (6144), at 2048 bits 3.40 / 4.32
+// (2049), 3.49 / 4.23 (4096), at 4096 bits 21.9 / 39.2 (2049); decryptions at 2048 bits 1.03 / 1.46 (1025), at 4096 bits 3.50 /
+// 4.44. The short products of 256-bit primes are 2 to 3 % faster there with two blocks to a compute unit, but not with three:
+// 0.400 / 0.388 (1025 decryptions at a 1024-bit key), 0.402 / 0.395 (2048), 0.473 / 0.723 (2500), 0.475 / 0.726 (3072).
 bool group_folds(const haflo_ctx* ctx, size_t count, int jobs, bool pair) {
   return pair && (count + 7) / 8 * (size_t)jobs <= (size_t)ctx->num_cu;
 }
@@ -1841,12 +1843,12 @@ size_t group_blocks(const haflo_ctx* ctx, int nr, size_t count, int jobs, bool f
   return std::min(all, std::max((size_t)ctx->num_cu * group_blocks_per_cu(nr) / (size_t)jobs, (size_t)1));
 }
 // Where the elements are few, or the matrices too large for the LDS, the slots of 16 elements are spread over a block.
-// Measured on both sides (ms, spread / not): encryption at a 1024-bit key 1.17 / 2.32 at 4096 elements, 2.11 / 2.37 at 8192,
-// 3.09 / 2.39 at 9216; at 2048 bits 7.3 / 17.1 at 8192, 21.4 / 23.7 at 24576, 25.0 / 25.2 at 28672, 28.5 / 26.7 at 32768;
-// decryption at a 1024-bit key 0.54 / 0.76 at 4096, 0.96 / 0.76 at 5120, at 2048 bits 2.14 / 2.42 and (6144) 3.17 / 2.48, at 4096
-// bits 21.6 / 24.0 at 12288, 28.8 / 26.9 at 16384. The key owner's encryption, whose first stage is of the single form: at a
-// 1024-bit key 0.88 / 1.26 at 4096, 1.63 / 1.28 at 6144, at 2048 bits 3.03 / 4.01 and 4.90 / 4.13, at 4096 bits 33.3 / 35.4 at
-// 12288, 44.3 / 39.9 at 16384.
+// Measured on both sides (ms, spread / not): encryption at a 512-bit key 0.45 / 0.71 at 8192 elements, 0.73 / 0.72 at 9216; at
+// 1024 bits 1.00 / 2.31 at 4096, 1.95 / 2.37 at 8192, 2.84 / 2.40 at 8193; at 2048 bits 7.4 / 17.1 at 8192, 21.5 / 24.0 at 24576,
+// 24.6 / 23.9 at 24577, 24.8 / 25.4 at 28672 (seven full passes), 28.1 / 27.1 at 32768; decryption at a 1024-bit key 0.48 / 0.74 at
+// 4096, 0.88 / 0.75 at 4097, at 2048 bits 2.00 / 2.42 and 2.91 / 2.44, at 4096 bits 21.4 / 24.2 at 12288, 24.9 / 24.3 at 12289, 28.3 /
+// 27.5 at 16384. The key owner's encryption, whose first stage is of the single form: at a 1024-bit key 0.79 / 1.23 at 4096, 1.47 /
+// 1.25 at 4097, at 2048 bits 2.80 / 4.00 and 4.45 / 4.06, at 4096 bits 32.6 / 35.7 at 12288, 38.0 / 35.5 at 12289.
 bool use_group(const haflo_ctx* ctx, int nr, size_t count, int jobs) {
   return nr == 36 || (count + 15) / 16 * (size_t)jobs <= (size_t)ctx->num_cu * (nr == 18 ? 6 : 2);
 }

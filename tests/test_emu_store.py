@@ -2,9 +2,11 @@
 runtime: allocator bookkeeping, release on last use, and chains of operators over handles
 compared with the oracle running the same chain."""
 import ctypes as C
+import os
 import random
 
 import numpy as np
+import pytest
 
 from conftest import oracle_key
 from oracle import paillier_oracle as O
@@ -237,6 +239,7 @@ def test_store_matvec_sum_and_scalars_match_oracle(env):
     st.close()
 
 
+@pytest.mark.skipif(os.environ.get("HAFLO_EMU_SANITIZE", "") == "1", reason="minutes in the sanitized build")
 def test_store_matvec_in_the_workspace_there_is(emu):  # noqa: F811
     """A matvec takes the workspace that it asks for from the arena, and the least where there is no room for more; without
     room for that it consumes nothing."""
