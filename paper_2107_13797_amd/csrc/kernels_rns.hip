@@ -1134,31 +1134,24 @@ __global__ __launch_bounds__(768, 3) void k_rns_chains(RnsChains j) {
 template <int NR, int HALVES, bool LISTS>
 struct GroupShared {
   static constexpr int kBlocks = (NR + 3) / 4;  // of 64 bytes, the last one partly empty
-  // Matrices stay in registers; those of 4096-bit moduli stream from L2, but for three of nine blocks: of the first one in
-  // registers, of the second one in LDS, where the constants are as well.
-  static constexpr bool kHeld = NR != 36;
-  static constexpr int kStay = kHeld ? 0 : 3;
-  static constexpr bool kHeldCst = kHeld && !LISTS;
+  static constexpr bool kHeldCst = !LISTS;
   Quad bytes[2][HALVES][kBlocks][WAVE];  // [sigma, rho][x0, x1][block][lane]
   Quad sum[3][HALVES][16];               // alpha's sums over lane group 0 .. 3's slots, of the last, the present and the next rho
-  Acc resident[kStay][kHeld ? 1 : rns::tiles(NR)][WAVE];
   Quad cst[kHeldCst ? 0 : 2][rns::slots(NR)];
 };
 
-// The same arithmetic with the slots of 16 elements spread over the W wavefronts of a block, TW tiles each, for
-// batches that would leave most of the chip idle with a wavefront per 16 elements, and for moduli whose matrices do not
-// fit the LDS. A wavefront keeps the residues of its own slots and multiplies and reduces them alone; what every
-// wavefront needs of the others, the bytes of all residues, goes through LDS (16 bytes per lane and block of 64, as the
-// matrix product reads its operand), one barrier before each of the two matrix products of a modular product. The
-// matrices stay in registers where they fit (kHeld: 16 to 80 of them), else they stream from L2. What bounds it is one
-// wavefront's chain from barrier to barrier and the SIMD with the most tiles (three of a 1024-bit modulus's nine): on blocks of 8
-// elements a product takes some 1450, 2100 and 9200 cycles of 2.4 GHz (1024, 2048 and 4096 bits); at 4096 bits 420 KB of
-// the 630 KB of both matrices come from L2 per product. Measured against the limb arithmetic on one wavefront per integer, the
-// version before blocks of 8 elements and weighted rows, and the one before the program's words were kept in registers, a
+// The same arithmetic with the slots of 16 elements spread over the W wavefronts of a block, TW tiles each, for batches that
+// would leave most of the chip idle with a wavefront per 16 elements. A wavefront keeps the residues of its own slots and
+// multiplies and reduces them alone; what every wavefront needs of the others, the bytes of all residues, goes through LDS (16
+// bytes per lane and block of 64, as the matrix product reads its operand), one barrier before each of the two matrix products
+// of a modular product. The matrices stay in registers, 16 to 80 of them. What bounds it is one wavefront's chain from barrier
+// to barrier and the SIMD with the most tiles (three of a 1024-bit modulus's nine): on blocks of 8 elements a product takes
+// some 1450 and 2100 cycles of 2.4 GHz (1024 and 2048 bits). Measured against the limb arithmetic on one wavefront per integer,
+// the version before blocks of 8 elements and weighted rows, and the one before the program's words were kept in registers, a
 // square's lanes of x1 took a second multiply-add instead of a 64-bit factor, and alpha's sums were cleared off the first SIMD:
-// 1024 encryptions at a 1024-bit key 2.67, 1.06, 0.85 -> 0.73 ms, 256 at 2048 bits 8.5, 3.9, 2.30 -> 2.08, 16 at 4096 bits (the
-// last two) 18.2 -> 17.9; 3072 decryptions at 1024 bits 1.33, 0.55, 0.51 -> 0.47 ms, 100 at 2048 bits (the last two) 0.89 ->
-// 0.77, 64 at 4096 bits 8.63, 4.01, 2.38 -> 2.14.
+// 1024 encryptions at a 1024-bit key 2.67, 1.06, 0.85 -> 0.73 ms, 256 at 2048 bits 8.5, 3.9, 2.30 -> 2.08; 3072 decryptions at
+// 1024 bits 1.33, 0.55, 0.51 -> 0.47 ms, 100 at 2048 bits (the last two) 0.89 -> 0.77, 64 at 4096 bits 8.63, 4.01, 2.38 ->
+// 2.14.
 //
 // FOLD: 8 elements to a block, x0 in columns 0 to 7 of the matrix products and x1 in columns 8 to 15, for batches that do
 // not fill the chip with blocks of 16: half the matrix instructions and operand reads per product. A lane then has one half
@@ -1177,11 +1170,7 @@ struct RnsGroup {
   static constexpr int kBlocks = Shared::kBlocks;
   static constexpr int kFull = rns::full_blocks(NR);
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
-  // kAhead of the blocks that stream are on their way at any time, also across the barriers that the operands wait for; the
-  // resident ones are multiplied in between.
-  static constexpr bool kHeld = Shared::kHeld, kHeldCst = Shared::kHeldCst;
-  static constexpr int kStay = Shared::kStay, kAhead = 2, kStream = kBlocks - kStay;
-  static_assert(kHeld || kStream % kAhead == 0, "a matrix begins where the other one ends");
+  static constexpr bool kHeldCst = Shared::kHeldCst;
   static_assert(TILES >= kLimbTiles, "every tile has a wavefront");
   struct State {
     u32 a0[TW], a1[TW], b0[TW], b1[TW];
@@ -1193,9 +1182,7 @@ struct RnsGroup {
   Acc start;
   Quad held_cst[2][kHeldCst ? TW : 1];  // the constants of this lane's slots in base A and base B
   u32 second;           // FOLD: all ones in x1's lanes
-  Frags held[kHeld ? 2 : 1];
-  QuadSet<kHeld ? 1 : kStay * TW> part;
-  QuadSet<kHeld ? 1 : kAhead * TW> coming;
+  Frags held[2];
 
   __device__ __forceinline__ bool mine(int i, int tiles = kTiles) const { return own_tile + i < tiles; }
   // a wavefront without a tile of its own repeats the last one and keeps the result to itself
@@ -1225,7 +1212,7 @@ struct RnsGroup {
 
   __device__ __forceinline__ RnsGroup(Shared& shared, const u32* tables_, int own_tile_)
       : sh(shared), tables((const char*)tables_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4),
-        wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))), own_tile(own_tile_), turn(0), start(start_sums(kHeld)),
+        wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))), own_tile(own_tile_), turn(0), start(start_sums()),
         second(FOLD && (threadIdx.x & 8) ? ~0u : 0u) {
     const char* from = tables + rns::lds_matrices_bytes(NR);
     if (kHeldCst)
@@ -1233,29 +1220,19 @@ struct RnsGroup {
       for (int i = 0; i < TW; ++i)
 #pragma unroll
         for (int b = 0; b < 2; ++b) held_cst[b][kHeldCst ? i : 0] = *(const Quad*)(from + (2 * b * rns::slots(NR) + 4 * tile(i) + g) * 16);
-    if (kHeld)
 #pragma unroll
-      for (int mat = 0; mat < 2; ++mat)
+    for (int mat = 0; mat < 2; ++mat)
 #pragma unroll
-        for (int i = 0; i < TW; ++i)
+      for (int i = 0; i < TW; ++i)
 #pragma unroll
-          for (int k = 0; k < kBlocks; ++k)
-            held[mat].q[i * kBlocks + k] = fragment(tables + mat * rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, mat), i, k, (unsigned)lane);
+        for (int k = 0; k < kBlocks; ++k)
+          held[mat].q[i * kBlocks + k] = fragment(tables + mat * rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, mat), i, k, (unsigned)lane);
     for (int i = (int)threadIdx.x; i < (int)(sizeof(Shared) / 4); i += (int)blockDim.x) ((u32*)&sh)[i] = 0;
     __syncthreads();
     if (!kHeldCst)
       for (int i = (int)threadIdx.x; i < 2 * rns::slots(NR); i += (int)blockDim.x)
         sh.cst[kHeldCst ? 0 : i / rns::slots(NR)][i % rns::slots(NR)] = *(const Quad*)(from + (i + i / rns::slots(NR) * rns::slots(NR)) * 16);
     set_bias();
-    if (!kHeld)
-#pragma unroll
-      for (int i = 0; i < TW; ++i)
-#pragma unroll
-        for (int k = 0; k < kStay; ++k) {
-          part.q[i * kStay + k] = fragment(tables, kTiles, rns::last_rows(NR, 0), i, k, (unsigned)lane);
-          // this wavefront's own tiles (the last ones may write the same tile twice)
-          sh.resident[k][tile(i)][lane] = fragment(tables + rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, 1), i, k, (unsigned)lane);
-        }
   }
   // A residue's bytes to where the other wavefronts read them. All lanes write: what has no prime meets zeros in the matrix,
   // a wavefront that repeats a tile writes what its owner does, and the bias stays 1 where it shares a register with primes.
@@ -1263,15 +1240,6 @@ struct RnsGroup {
     v ^= rns::kOmega;
     if (rns::tiles(NR) == NR && tile(i) == NR - 1) v = g == rns::bias_group(NR) ? 1u : v;
     word(buffer, x, tile(i), lane) = v;
-  }
-  // asks for a block of one of the two matrices
-  template <int MATRIX>
-  __device__ __forceinline__ void ask(int stream) {
-    unsigned l = (unsigned)lane;
-    asm volatile("" : "+v"(l));  // or the addresses of all fragments are kept in registers from one product to the next
-#pragma unroll
-    for (int i = 0; i < TW; ++i)
-      coming.q[stream % kAhead * TW + i] = fragment(tables + MATRIX * rns::lds_matrix_bytes(NR, 0), kTiles, rns::last_rows(NR, MATRIX), i, kStay + stream, l);
   }
   // the constant 1 of the bias: a lane group of the last register, which no wavefront writes
   __device__ __forceinline__ void set_bias() {
@@ -1314,31 +1282,14 @@ struct RnsGroup {
         for (int x = 0; x < kHalves; ++x)
           r[i][x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], (Acc)d[x], r[i][x], 0, 0, 0);
     };
-    if constexpr (kHeld || MATRIX == 2) {
 #pragma unroll
-      for (int k = 0; k < kBlocks; ++k) {
-        if (MATRIX == 2 && k % 3 == 0) __builtin_amdgcn_sched_barrier(0);
-        Acc f[TW];
+    for (int k = 0; k < kBlocks; ++k) {
+      if (MATRIX == 2 && k % 3 == 0) __builtin_amdgcn_sched_barrier(0);
+      Acc f[TW];
 #pragma unroll
-        for (int i = 0; i < TW; ++i)
-          f[i] = MATRIX < 2 ? held[MATRIX < 2 ? MATRIX : 0].q[i * kBlocks + k] : fragment(matrix, tiles, last, i, k, l);
-        block(k, f);
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < kStream; ++k) {
-        __builtin_amdgcn_sched_barrier(0);
-        block(kStay + k, &coming.q[k % kAhead * TW]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (k + kAhead < kStream) ask<MATRIX>(k + kAhead);
-        else ask<1 - MATRIX>(k + kAhead - kStream);
-        if (k < kStay) {
-          Acc f[TW];
-#pragma unroll
-          for (int i = 0; i < TW; ++i) f[i] = MATRIX == 0 ? part.q[i * kStay + k] : sh.resident[k][tile(i)][lane];
-          block(k, f);
-        }
-      }
+      for (int i = 0; i < TW; ++i)
+        f[i] = MATRIX < 2 ? held[MATRIX < 2 ? MATRIX : 0].q[i * kBlocks + k] : fragment(matrix, tiles, last, i, k, l);
+      block(k, f);
     }
   }
   // base B's bytes and alpha's sums to the other wavefronts
@@ -1407,12 +1358,7 @@ struct RnsGroup {
     for (int i = 0; i < TW; ++i) v[i] = SQ ? own(x, i) : entry(y, i);
     multiply<SQ>(x, v, [] {});
   }
-  // before the first product of elements that load() did not bring in
-  __device__ __forceinline__ void begin() {
-    if constexpr (!kHeld)
-#pragma unroll
-      for (int k = 0; k < kAhead; ++k) ask<0>(k);
-  }
+  __device__ __forceinline__ void begin() {}
   // `meanwhile` asks for what the next product takes, behind this one's first barrier
   template <bool SQ, class F>
   __device__ __forceinline__ void multiply(State& x, const Quad (&v)[TW], const F& meanwhile) {
@@ -1471,9 +1417,6 @@ struct RnsGroup {
       x.b0[i] = reduce(column(r[i][0]), k[0], k[1]);
       if constexpr (kBoth) x.b1[i] = reduce(column(r[i][kHalves - 1]), k[0], k[1]);
     }
-    if constexpr (!kHeld)
-#pragma unroll
-      for (int k = 0; k < kAhead; ++k) ask<1>(k);
     publish(x);
     extend_to_a(x);
   }
@@ -1568,21 +1511,707 @@ struct RnsGroup {
   }
 };
 
+// The engine of 4096-bit moduli, whose matrices, 630 KB, fit neither a wavefront's registers nor the LDS: the slots of 16 (FOLD: 8)
+// elements spread over a block of four wavefronts, one to a SIMD, each with all 512 of its registers and nine tiles. Against twelve
+// wavefronts of three tiles, the form before:
+// - the operand of a matrix product is read from LDS once by each of four wavefronts, and not of twelve: 72 KB instead of 216;
+// - of the 18 blocks of both matrices a tile has, 10 stay on the compute unit instead of 6: 7 in registers, in the half that only
+//   loads and the matrix unit reach, and three in LDS. 288 KB instead of 420 come from L2 for a product;
+// - a matrix product goes tile by tile, with the vector unit's work on one tile between the matrix instructions of the next: the
+//   phases of the twelve wavefronts lay one after the other between their barriers.
+// ms before and now: encryption of 64 elements 17.8 / 12.6, 3001 21.7 / 18.8, 4096 25.5 / 21.4, 20000 125.6 / 105.1; gradient 20000 by
+// 64 8.76 / 5.9, forward 4096 by 64 1.72 / 1.30. What bounds it is the issue of a SIMD's only wavefront (without the blocks that
+// stream 64 and 3001 elements take 9.7 and 14.3) and the 64 bytes a clock that they come with; the entries of a window table are
+// waited for.
+template <bool FOLD>
+struct WideShared {
+  static constexpr int kNr = 36, kHalves = FOLD ? 1 : 2;
+  Quad bytes[2][kHalves][rns::full_blocks(kNr)][WAVE];  // [sigma, rho][x0, x1][block][lane]
+  Quad sum[3][kHalves][16];                             // see GroupShared
+  Quad cst[2][rns::slots(kNr)];
+  Acc resident[4][9][3][WAVE];                          // [wavefront][tile][block]: one address and constants reach all of a lane's
+};
+template <bool FOLD, int STREAM0, int STREAM1, int RING, bool HELD>
+struct RnsWide {
+  static constexpr int kRegs = 36, kOwn = 9, kWaves = 4;
+  static constexpr bool kBoth = !FOLD;  // x0 and x1 in one lane
+  static constexpr int kHalves = kBoth ? 2 : 1;
+  static constexpr int kElements = FOLD ? 8 : 16;
+  static constexpr int kTiles = rns::tiles(kRegs), kLimbTiles = rns::limb_tiles(kRegs);
+  static constexpr int kBlocks = rns::full_blocks(kRegs), kTileBytes = rns::tile_bytes(kRegs, 16);
+  static_assert(kRegs % 4 == 0 && kLimbTiles == kOwn * kWaves && kTiles == kLimbTiles - 1, "whole blocks, and a tile without primes");
+  using Shared = WideShared<FOLD>;
+  // A tile's blocks, in the order in which they are multiplied: every other one streams, so that the requests come evenly, up to
+  // STREAM0 of the first matrix and STREAM1 of the second one. Of the rest, the first ones stay in registers, the last three of the
+  // second matrix in LDS.
+  static constexpr int kLds = 3;
+  static constexpr int kStay0 = kBlocks - STREAM0, kStay1 = kBlocks - kLds - STREAM1;
+  static __host__ __device__ constexpr int count(int m) { return m == 0 ? STREAM0 : STREAM1; }
+  static __host__ __device__ constexpr bool streams(int m, int n) { return n % 2 == 0 && n / 2 < count(m); }
+  static __host__ __device__ constexpr int rest(int m, int n) { return n - (n + 1 < 2 * count(m) ? (n + 1) / 2 : count(m)); }  // its number
+  static __host__ __device__ constexpr int rest_block(int m, int r) { return r < count(m) ? 2 * r + 1 : r + count(m); }
+  static_assert(2 * STREAM0 <= kBlocks && 2 * STREAM1 <= kBlocks && rest_block(0, rest(0, 8)) == 8 && rest_block(1, rest(1, 1)) == 1, "");
+  // Tiles whose matrix products are issued in turn, with the vector unit's work on as many others between them: a step
+  static constexpr int kStep = FOLD ? 2 : 1;
+  static __host__ __device__ constexpr int stream_begin(int m) { return m == 0 ? 0 : kOwn * STREAM0; }  // in a product's
+  static_assert(kOwn * (STREAM0 + STREAM1) % RING == 0 && RING <= kOwn * STREAM0 && RING <= kOwn * STREAM1, "a product begins where the last one ended");
+  // The n-th block of tile i that streams, in the order in which they are multiplied: by steps, by blocks, by tiles
+  static __host__ __device__ constexpr int step_tiles(int t) { return t + kStep <= kOwn ? kStep : kOwn - t; }
+  static __host__ __device__ constexpr int stream_at(int m, int i, int n) { return i / kStep * kStep * count(m) + n * step_tiles(i / kStep * kStep) + i % kStep; }
+  static __host__ __device__ constexpr int stream_step(int m, int s) { return s / (kStep * count(m)) * kStep; }
+  static __host__ __device__ constexpr int stream_block(int m, int s) { return s % (kStep * count(m)) / step_tiles(stream_step(m, s)); }
+  static __host__ __device__ constexpr int stream_tile(int m, int s) { return stream_step(m, s) + s % (kStep * count(m)) % step_tiles(stream_step(m, s)); }
+  // HELD: a value's residues in base B are registers of its state. Else they are only where the other wavefronts read them, but
+  // for the last tile's, which two wavefronts have: a lane reads its own back from there, and there are registers for more
+  // blocks on their way.
+  static constexpr int kHeldB = HELD ? kOwn : 1;
+  struct State {
+    u32 a0[kOwn], a1[kOwn], b0[kHeldB], b1[kHeldB];
+  };
+  struct Sums {
+    Acc r[kHalves];
+  };
+  struct Words {  // x0's and x1's in one base
+    Twin w[kOwn];
+  };
+  Shared& sh;
+  const char* tables;
+#if defined(__HIP_DEVICE_COMPILE__)
+  __amdgpu_buffer_rsrc_t rows;  // of both matrices
+#endif
+  int lane, g, wave, turn;
+  unsigned place;
+  Acc start;
+  u32 second;  // FOLD: all ones in x1's lanes
+  u32 last;    // all ones where the ninth tile has a prime
+  QuadSet<kOwn * kStay0> stay0;
+  QuadSet<kOwn * kStay1> stay1;
+  QuadSet<RING> ring;
+
+  // Tile i of this wavefront: two blocks of four and one of the last block
+  __device__ __forceinline__ int limb_tile(int i) const { return i < 8 ? 8 * wave + i : 32 + wave; }
+  // of those with primes: the last wavefront repeats the last one and keeps the result to itself
+  __device__ __forceinline__ bool mine(int i) const { return i < 8 || limb_tile(i) < kTiles; }
+  __device__ __forceinline__ int tile(int i) const { return mine(i) ? limb_tile(i) : kTiles - 1; }
+  __device__ __forceinline__ Quad cst(int base, int i) const { return sh.cst[base][4 * tile(i) + g]; }
+  // FOLD: x0's value for both halves; and for x1's lanes only, zero in x0's
+  static __device__ __forceinline__ u32 of_first(u32 v) {
+    return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118 /* row_shr:8 */, 0xf, 0xc, false);
+  }
+  static __device__ __forceinline__ u32 from_first(u32 v) {
+    return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x118 /* row_shr:8 */, 0xf, 0xf, true);
+  }
+  static __device__ __forceinline__ Acc fragment(const char* matrix, int tile, int k, unsigned at) {
+    return *(const Acc*)(matrix + tile * kTileBytes + k * 1024 + at);
+  }
+  // Fragment n of those that stay, the first 63 in the half of the registers that only loads and the matrix unit reach: left alone,
+  // the compiler copies what it keeps there to the other half for each use.
+  static __device__ __forceinline__ Acc stays([[maybe_unused]] int n, Acc f) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (n < 63) asm("" : "+a"(f));
+#endif
+    return f;
+  }
+  __device__ __forceinline__ const char* matrix(int m) const { return tables + m * rns::lds_matrix_bytes(kRegs, 0); }
+  // this lane's place in a fragment, made anew: or the addresses of all fragments are kept in registers from one product to the next
+  __device__ __forceinline__ unsigned fresh_place() const {
+    unsigned l = place;
+    asm volatile("" : "+v"(l));
+    return l;
+  }
+
+  __device__ __forceinline__ RnsWide(Shared& shared, const u32* tables_)
+      : sh(shared), tables((const char*)tables_), lane((int)(threadIdx.x & (WAVE - 1))), g(lane >> 4),
+        wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))), turn(0), place(16 * (threadIdx.x & (WAVE - 1))),
+        start(start_sums()), second(FOLD && (threadIdx.x & 8) ? ~0u : 0u), last(mine(8) && 4 * tile(8) + g < rns::primes_for(kRegs) ? ~0u : 0u) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    rows = __builtin_amdgcn_make_buffer_rsrc((void*)tables, 0, rns::lds_matrices_bytes(kRegs), 0x00020000 /* untyped words */);
+#endif
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+#pragma unroll
+      for (int k = 0; k < kStay0; ++k) stay0.q[i * kStay0 + k] = stays(i * kStay0 + k, fragment(matrix(0), tile(i), rest_block(0, k), place));
+#pragma unroll
+      for (int k = 0; k < kStay1; ++k)
+        stay1.q[i * kStay1 + k] = stays(kOwn * kStay0 + i * kStay1 + k, fragment(matrix(1), tile(i), rest_block(1, k), place));
+#pragma unroll
+      for (int k = 0; k < kLds; ++k) sh.resident[wave][i][k][lane] = fragment(matrix(1), tile(i), rest_block(1, kStay1 + k), place);
+    }
+    constexpr int kClear = (int)(sizeof(sh.bytes) + sizeof(sh.sum)) / 4;
+    for (int i = (int)threadIdx.x; i < kClear; i += (int)blockDim.x) ((u32*)&sh)[i] = 0;
+    const char* from = tables + rns::lds_matrices_bytes(kRegs);
+    for (int i = (int)threadIdx.x; i < 2 * rns::slots(kRegs); i += (int)blockDim.x)
+      sh.cst[i / rns::slots(kRegs)][i % rns::slots(kRegs)] = *(const Quad*)(from + (i + i / rns::slots(kRegs) * rns::slots(kRegs)) * 16);
+    __syncthreads();
+    // the constant 1 of the bias: a lane group of the last register, which no wavefront writes
+    if (threadIdx.x < 16)
+      for (int b = 0; b < 2; ++b)
+        for (int x = 0; x < kHalves; ++x) word(b, x, kRegs - 1, 16 * rns::bias_group(kRegs) + (int)threadIdx.x) = 1;
+  }
+  __device__ __forceinline__ u32& word(int buffer, int x, int i, int l) const {
+    return ((u32*)&sh.bytes[buffer][x][i / 4][l])[i % 4];
+  }
+  // Residues' bytes to where the other wavefronts read them, once the value of tile i is there: four at a time. All lanes write,
+  // what has no prime meets zeros in the matrix.
+  __device__ __forceinline__ void put(int buffer, int x, int i, const u32 (&v)[kOwn]) const {
+    if (i == 8) word(buffer, x, tile(8), lane) = v[8] ^ rns::kOmega;
+    else if (i % 4 == 3) sh.bytes[buffer][x][2 * wave + i / 4][lane] = Quad{v[i - 3], v[i - 2], v[i - 1], v[i]} ^ rns::kOmega;
+  }
+  // Asks for block s of those of a matrix that stream. A lane's place in a fragment never changes and a tile's lies in a scalar
+  // register, so that it takes one instruction.
+  template <int MATRIX>
+  __device__ __forceinline__ void ask(int s) {
+    const int i = stream_tile(MATRIX, s), k = stream_block(MATRIX, s);
+    const int tile_at = MATRIX * rns::lds_matrix_bytes(kRegs, 0) + (i < 8 ? 8 * wave + i : tile(8)) * kTileBytes;
+    const unsigned at = place + (unsigned)k * 2048;
+    Acc f;
+#if defined(__HIP_DEVICE_COMPILE__)
+    f = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)at, tile_at, 0);
+#else
+    f = *(const Acc*)(tables + tile_at + at);
+#endif
+    ring.q[(s + stream_begin(MATRIX)) % RING] = f;
+  }
+  // before the first product of elements that load() did not bring in
+  __device__ __forceinline__ void begin() {
+#pragma unroll
+    for (int s = 0; s < RING; ++s) ask<0>(s);
+  }
+  struct Operand {
+    Acc q[kHalves][kBlocks];
+  };
+  // the bytes in `buffer`, after all wavefronts have written theirs; ALPHA: with alpha in its slot
+  template <bool ALPHA>
+  __device__ __forceinline__ void read(Operand& d, int buffer) const {
+    u32 alpha[kHalves] = {};
+    if (ALPHA) {
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x) {
+        const Quad q = sh.sum[turn == 0 ? 2 : turn - 1][x][lane & 15];
+        alpha[x] = alpha_bytes(q[0] + q[1] + q[2] + q[3] + (1u << 13) + (u32)rns::primes_for(kRegs) / 2);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kBlocks; ++k)
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x) {
+        Quad q = sh.bytes[buffer][x][k][lane];
+        if (ALPHA && k == kBlocks - 1) q[3] = g == rns::alpha_group(kRegs) ? alpha[x] : q[3];
+        d.q[x][k] = (Acc)q;
+      }
+  }
+  // The matrix product of this wavefront's tiles, a step at a time. Between the matrix instructions of block n, work(i, n, k) is
+  // piece n of what the vector unit can do for the step's tile i without its sums, and finish(i, n, k, sums) of what it does with
+  // the sums of the step before; k: the constants of base 1 - MATRIX. ready(i) asks LDS for what work() takes of tile i, a step
+  // ahead. The order is as it stands here, and the compiler's only within a block: left to itself it asks for blocks so late that
+  // the next one waits for them, and leaves the vector unit's work to the end.
+  template <int MATRIX, class R, class B, class F>
+  __device__ __forceinline__ void sweep(const Operand& d, const R& ready, const B& work, const F& finish) {
+    Sums v[2][kStep];
+    Quad c[3][kStep];
+#pragma unroll
+    for (int j = 0; j < kStep; ++j) {
+      c[0][j] = cst(1 - MATRIX, j);
+      ready(j);
+    }
+#pragma unroll
+    for (int t = 0; t < kOwn; t += kStep) {
+      const int step = t / kStep, now = step % 2;
+      Acc lds[kStep][kLds];
+#pragma unroll
+      for (int n = 0; n < kBlocks; ++n) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < kStep; ++j) {
+          const int i = t + j;
+          if (i >= kOwn) continue;
+          const int r = streams(MATRIX, n) ? 0 : rest(MATRIX, n);
+          Acc f;
+          if (streams(MATRIX, n)) f = ring.q[(stream_at(MATRIX, i, n / 2) + stream_begin(MATRIX)) % RING];
+          else if (MATRIX == 0) f = stay0.q[i * kStay0 + r];
+          else if (r < kStay1) f = stay1.q[i * kStay1 + (r < kStay1 ? r : 0)];
+          else f = lds[j][r < kStay1 ? 0 : r - kStay1];
+#pragma unroll
+          for (int x = 0; x < kHalves; ++x)
+            v[now][j].r[x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f, d.q[x][n], n == 0 ? start : v[now][j].r[x], 0, 0, 0);
+          if (streams(MATRIX, n)) {
+            const int s = stream_at(MATRIX, i, n / 2) + RING;
+            if (s < kOwn * count(MATRIX)) ask<MATRIX>(s);
+            else ask<1 - MATRIX>(s - kOwn * count(MATRIX));
+          }
+          if (MATRIX == 1 && n == 1)
+#pragma unroll
+            for (int k = 0; k < kLds; ++k) lds[j][k] = sh.resident[wave][i][k][lane];
+          if (n == 2 && i + kStep < kOwn) {
+            c[(step + 1) % 3][j] = cst(1 - MATRIX, i + kStep);
+            ready(i + kStep);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < kStep; ++j)
+          if (t + j < kOwn) work(t + j, n, c[step % 3][j]);
+#pragma unroll
+        for (int j = 0; j < kStep; ++j)
+          if (t > 0) finish(t - kStep + j, n, c[(step + 2) % 3][j], v[1 - now][j]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int kFrom = (kOwn - 1) / kStep * kStep;
+#pragma unroll
+    for (int i = kFrom; i < kOwn; ++i)
+#pragma unroll
+      for (int n = 0; n < kBlocks; ++n) finish(i, n, c[kFrom / kStep % 3][i - kFrom], v[kFrom / kStep % 2][i - kFrom]);
+  }
+  // the same with a matrix in global memory, for the ways in and out
+  template <class F>
+  __device__ __forceinline__ void sweep_global(const Operand& d, const char* m, bool limbs, const Acc& from, const F& finish) {
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      const unsigned l = fresh_place();
+      Sums v;
+#pragma unroll
+      for (int x = 0; x < kHalves; ++x) v.r[x] = from;
+#pragma unroll
+      for (int k = 0; k < kBlocks; ++k) {
+        const Acc f = fragment(m, limbs ? limb_tile(i) : tile(i), k, l);
+#pragma unroll
+        for (int x = 0; x < kHalves; ++x) v.r[x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f, d.q[x][k], v.r[x], 0, 0, 0);
+      }
+      finish(i, v);
+    }
+  }
+
+  // The residue products of one base of a slot, u v or (SQ) u u: r0 = x0 y0 and r1 = x0 y1 + x1 y0 + e r0, in eight pieces.
+  // FOLD: r0 has either one, by its lane.
+  template <bool SQ>
+  struct Product {
+    u32 u0, u1, v0, v1, r0, r1;
+    u32 m, f0, f1;
+    s64 t, t1;
+    __device__ __forceinline__ void step(int n, u32 second, u32 p, u32 pinv, u32 e) {
+      if constexpr (FOLD) {
+        if (n == 0) {
+          f0 = of_first(u0);
+          f1 = SQ ? 0u : of_first(v0);
+        } else if (n == 1) {
+          t = SQ ? smad(f0, u0, 0) : smad(u0 & second, f1, 0);
+          if (SQ) asm("" : "+v"(t));  // x1's lanes twice, hidden from the compiler, which would multiply a wider sum of factors
+        } else if (n == 2) {
+          t = SQ ? smad(f0, u0 & second, t) : smad(f0, v0, t);
+        } else if (n == 3) {
+          m = (u32)t * pinv;
+        } else if (n == 4) {
+          f0 = from_first(upper(smad(m, p, t)));
+        } else if (n == 5) {
+          t = smad(f0, e, t);
+        } else if (n == 6) {
+          m = (u32)t * pinv;
+        } else if (n == 7) {
+          r0 = upper(smad(m, p, t));
+          r1 = 0;
+        }
+      } else {
+        if (n == 0) {
+          t = smad(u0, SQ ? u0 : v0, 0);
+        } else if (n == 1) {
+          m = (u32)t * pinv;
+          t1 = smad(u1, SQ ? u0 : v0, 0);
+          if (SQ) asm("" : "+v"(t1));
+        } else if (n == 2) {
+          r0 = upper(smad(m, p, t));
+        } else if (n == 3) {
+          t1 = SQ ? smad(u1, u0, t1) : smad(u0, v1, t1);
+        } else if (n == 4) {
+          t1 = smad(r0, e, t1);
+        } else if (n == 5) {
+          m = (u32)t1 * pinv;
+        } else if (n == 6) {
+          r1 = upper(smad(m, p, t1));
+        }
+      }
+    }
+    __device__ __forceinline__ void all(u32 second, u32 p, u32 pinv, u32 e) {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) step(n, second, p, pinv, e);
+    }
+    static __device__ __forceinline__ u32 upper(s64 v) {
+      u32 r = (u32)((u64)v >> 32);
+      asm("" : "+v"(r));  // see reduce()
+      return r;
+    }
+  };
+  // sigma of the product with y, whose words in base A these are, (SQ: of the square) to the other wavefronts
+  template <bool SQ>
+  __device__ __forceinline__ void sigma(const State& x, const Words& y) const {
+    sigma<SQ>(x, y, [] {});
+  }
+  // `meanwhile` asks for y's words in base B, in place of those
+  template <bool SQ, class F>
+  __device__ __forceinline__ void sigma(const State& x, const Words& y_, const F& meanwhile) const {
+    const Words y = y_;
+    u32 s0[kOwn], s1[kOwn];
+    meanwhile();
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      const Quad k = cst(0, i);
+      Product<SQ> r = {x.a0[i], kBoth ? x.a1[i] : 0u, y.w[i][0], y.w[i][1]};
+      r.all(second, k[0], k[1], k[2]);
+      s0[i] = r.r0;
+      s1[i] = r.r1;
+      put(0, 0, i, s0);
+      if constexpr (kBoth) put(0, 1, i, s1);
+    }
+  }
+  // quad j of this lane's own residues in base B, where the other wavefronts read them
+  __device__ __forceinline__ Quad own_b(int x, int j) const { return sh.bytes[1][x][2 * wave + j][lane] ^ rns::kOmega; }
+  // all of a value's residues in base B
+  __device__ __forceinline__ void get_b(Words& y, const State& x) const {
+#pragma unroll
+    for (int j = 0; j < (HELD ? 0 : 2); ++j) {
+      const Quad q0 = own_b(0, j), q1 = kBoth ? own_b(kHalves - 1, j) : Quad{0, 0, 0, 0};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y.w[4 * j + k] = Twin{q0[k], q1[k]};
+    }
+#pragma unroll
+    for (int i = HELD ? 0 : 8; i < kOwn; ++i) y.w[i] = Twin{x.b0[i % kHeldB], kBoth ? x.b1[i % kHeldB] : 0u};
+  }
+  // what get_b() gives
+  __device__ __forceinline__ void set_b(State& x, const Words& y) const {
+    if constexpr (!HELD) {
+      __syncthreads();  // those of the value before have been read
+      put_b(y);
+    }
+#pragma unroll
+    for (int i = HELD ? 0 : 8; i < kOwn; ++i) {
+      x.b0[i % kHeldB] = y.w[i][0];
+      x.b1[i % kHeldB] = y.w[i][1];
+    }
+  }
+  __device__ __forceinline__ void put_b(const Words& y) const {
+#pragma unroll
+    for (int h = 0; h < kHalves; ++h) {
+      u32 v[kOwn];
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i) {
+        v[i] = y.w[i][h];
+        put(1, h, i, v);
+      }
+    }
+  }
+  // Base B of the reduced pair from sigma, and to the other wavefronts with alpha's sums. Its products z, w with y, whose words
+  // in base B these are, (SQ: with itself) are made on the way.
+  template <bool SQ>
+  __device__ __forceinline__ void extend_to_b(State& x, const Words& y) {
+    __syncthreads();
+    Operand d;
+    read<false>(d, 0);
+    Product<SQ> r[2][kStep];
+    Quad own[2][2] = {};  // of tiles 0 to 3 or 4 to 7, and the next ones'
+    u32 sum[2] = {}, m, b0[kOwn], b1[kOwn];
+    s64 t[2][kStep];
+    sweep<0>(
+        d,
+        [&](int i) {
+          if (HELD || i == 8 || i % 4 != 0) return;
+          own[i / 4][0] = own_b(0, i / 4);
+          if constexpr (kBoth) own[i / 4][1] = own_b(1, i / 4);
+        },
+        [&](int i, int n, const Quad& k) {
+          Product<SQ>& q = r[i / kStep % 2][i % kStep];
+          if (n == 0)
+            q = Product<SQ>{HELD || i == 8 ? x.b0[i % kHeldB] : own[i / 4 % 2][0][i % 4],
+                            !kBoth ? 0u : HELD || i == 8 ? x.b1[i % kHeldB] : own[i / 4 % 2][1][i % 4],
+                            y.w[i][0], y.w[i][1]};
+          q.step(n, second, k[0], k[1], 0u - k[3]);
+        },
+        [&](int i, int n, const Quad& k, const Sums& sums) {
+          const Product<SQ>& q = r[i / kStep % 2][i % kStep];
+          s64 &t0 = t[0][i % kStep], &t1 = t[1][i % kStep];
+          const u32 mask = i < 8 ? ~0u : last;
+          if (n == 0) {
+            t0 = column(sums.r[0]);
+          } else if (n == 1) {
+            t0 = smad(q.r0, k[2], t0);
+          } else if (n == 2) {
+            m = (u32)t0 * k[1];
+            if constexpr (kBoth) t1 = column(sums.r[kHalves - 1]);
+            else t0 = smad(from_first(Product<SQ>::upper(smad(m, k[0], t0))), k[3], t0);
+          } else if (n == 3) {
+            if constexpr (kBoth) {
+              b0[i] = Product<SQ>::upper(smad(m, k[0], t0));
+              t1 = smad(q.r1, k[2], t1);
+            } else {
+              m = (u32)t0 * k[1];
+              b0[i] = Product<SQ>::upper(smad(m, k[0], t0));
+            }
+          } else if (n == 4) {
+            if constexpr (kBoth) t1 = smad(b0[i], k[3], t1);
+          } else if (n == 5) {
+            if constexpr (kBoth) m = (u32)t1 * k[1];
+            sum[0] += (u32)((s32)b0[i] >> 16) & mask;
+          } else if (n == 6) {
+            if constexpr (kBoth) b1[i] = Product<SQ>::upper(smad(m, k[0], t1));
+          } else if (n == 7) {
+            if constexpr (kBoth) sum[1] += (u32)((s32)b1[i] >> 16) & mask;
+            put(1, 0, i, b0);
+          } else if (n == 8) {
+            if constexpr (kBoth) put(1, 1, i, b1);
+            if (HELD || i == 8) {
+              x.b0[i % kHeldB] = b0[i];
+              if constexpr (kBoth) x.b1[i % kHeldB] = b1[i];
+            }
+          }
+        });
+    publish_sums(sum[0], sum[1]);
+  }
+  __device__ __forceinline__ void publish_sums(u32 s0, u32 s1) {
+    u32* s = (u32*)&sh.sum[turn][0][lane & 15] + g;
+    atomicAdd(s, s0);
+    if (kBoth) atomicAdd(s + 64, s1);
+    __syncthreads();
+    turn = turn == 2 ? 0 : turn + 1;
+    // The sums of the publish_sums() before the last one, which were last read before its barrier, are next added to after the
+    // barrier of the one that follows. Every wavefront clears them: a branch would part the loads that are on their way.
+#pragma unroll
+    for (int x = 0; x < kHalves; ++x) ((u32*)&sh.sum[turn == 2 ? 0 : turn + 1][x][0])[lane] = 0;
+  }
+  // base B's bytes and alpha's sums to the other wavefronts
+  __device__ __forceinline__ void publish(const Words& y) {
+    u32 sum[2] = {};
+    put_b(y);
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i)
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) sum[h] += (u32)((s32)y.w[i][h] >> 16) & (i < 8 ? ~0u : last);
+    publish_sums(sum[0], sum[1]);
+  }
+  // Base A from what publish() left, NEXT: as sigma of the square, to the other wavefronts
+  template <bool NEXT>
+  __device__ __forceinline__ void extend_to_a(State& x) {
+    Operand d;
+    read<true>(d, 1);
+    Product<true> r[kStep];
+    u32 s0[kOwn], s1[kOwn], m, m1, u0[kStep], u1[kStep];
+    s64 t[2][kStep];
+    sweep<1>(
+        d, [](int) {}, [](int, int, const Quad&) {},
+        [&](int i, int n, const Quad& k, const Sums& sums) {
+          s64 &t0 = t[0][i % kStep], &t1 = t[1][i % kStep];
+          Product<true>& q = r[i % kStep];
+          u32 &v0 = u0[i % kStep], &v1 = u1[i % kStep];
+          if (n == 0) {
+            t0 = column(sums.r[0]);
+          } else if (n == 1) {
+            m = (u32)t0 * k[1];
+            if constexpr (kBoth) t1 = column(sums.r[kHalves - 1]);
+            else v0 = Product<true>::upper(smad(m, k[0], t0));
+          } else if (n == 2) {
+            if constexpr (kBoth) {
+              v0 = Product<true>::upper(smad(m, k[0], t0));
+              m1 = (u32)t1 * k[1];
+              v1 = Product<true>::upper(smad(m1, k[0], t1));
+            }
+          }
+          if constexpr (NEXT) {
+            if (n == 2) q = Product<true>{v0, kBoth ? v1 : 0u, 0u, 0u};
+            const auto step = [&](int piece) { q.step(piece, second, k[0], k[1], k[2]); };
+            if (n == 2) step(0);
+            if (n == 3) step(1);
+            if (n == 4) step(2);
+            if (n == 5) {
+              step(3);
+              step(4);
+            }
+            if (n == 6) step(5);
+            if (n == 7) {
+              step(6);
+              step(7);
+              s0[i] = q.r0;
+              s1[i] = q.r1;
+            }
+            if (n == 8) {
+              put(0, 0, i, s0);
+              if constexpr (kBoth) put(0, 1, i, s1);
+            }
+          } else if (n == 3) {
+            x.a0[i] = v0;
+            if constexpr (kBoth) x.a1[i] = v1;
+          }
+        });
+  }
+  // x times v. `meanwhile` asks for what the next product takes.
+  template <bool SQ, class F>
+  __device__ __forceinline__ void multiply(State& x, const Quad (&v)[kOwn], const F& meanwhile) {
+    Words y;
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) y.w[i] = Twin{v[i][0], v[i][1]};
+    sigma<SQ>(x, y);
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) y.w[i] = Twin{v[i][2], v[i][3]};
+    extend_to_b<SQ>(x, y);
+    meanwhile();
+    extend_to_a<false>(x);
+  }
+  // the pairs whose limbs are at `src` (`left` of them, then zeros) into both bases
+  __device__ __forceinline__ void load(State& x, const u32* src, unsigned left, int nl) {
+    const int e = lane & (kElements - 1), half = FOLD ? lane >> 3 & 1 : 0;
+    __syncthreads();  // the bytes of the elements before have been read
+    for (int i = wave; i < kRegs; i += kWaves) {
+      const int l = 4 * i + g;
+      if (l == rns::bias_slot(kRegs)) continue;
+      const bool ok = (unsigned)e < left && l < nl;
+      const u32* p = src + (size_t)e * (2 * nl) + half * nl + l;
+      word(0, 0, i, lane) = (ok ? p[0] : 0u) ^ rns::kOmega;
+      if constexpr (kBoth) word(0, 1, i, lane) = (ok ? p[nl] : 0u) ^ rns::kOmega;
+    }
+    __syncthreads();
+    Operand d;
+    read<false>(d, 0);
+    Words y;
+    sweep_global(d, tables + rns::lds_bytes(kRegs), false, start, [&](int i, const Sums& v) {
+      const Quad k = cst(1, i);
+      y.w[i] = Twin{reduce(column(v.r[0]), k[0], k[1]), kBoth ? reduce(column(v.r[kHalves - 1]), k[0], k[1]) : 0u};
+      if (HELD || i == 8) {
+        x.b0[i % kHeldB] = y.w[i][0];
+        x.b1[i % kHeldB] = y.w[i][1];
+      }
+    });
+#pragma unroll
+    for (int s = 0; s < RING; ++s) ask<1>(s);
+    publish(y);
+    extend_to_a<false>(x);
+  }
+  // the pairs as two integers each in columns of weight 2^(29 l)
+  __device__ __forceinline__ void store(const State& x, long long* dst, unsigned left) {
+    const unsigned e = (unsigned)(lane & (kElements - 1));
+    store(x, dst, e, e < left);
+  }
+  // the same, this lane's to element `e` behind `dst`
+  template <class I>
+  __device__ __forceinline__ void store(const State& x, long long* dst, I e, bool active) {
+    Words y;
+    get_b(y, x);
+    __syncthreads();  // the bytes of the last product have been read
+    publish(y);
+    Operand d;
+    read<true>(d, 1);
+    const unsigned half = FOLD ? (unsigned)lane >> 3 & 1 : 0;
+    long long* to = dst + (size_t)e * (8 * kLimbTiles) + half * (4 * kLimbTiles) + g;
+    sweep_global(d, tables + rns::lds_bytes(kRegs) + rns::in_matrix_bytes(kRegs), true, Acc{0, 0, 0, 0}, [&](int i, const Sums& v) {
+      if (active) {
+        to[4 * limb_tile(i)] = integer(v.r[0]);
+        if constexpr (kBoth) to[4 * kLimbTiles + 4 * limb_tile(i)] = integer(v.r[kHalves - 1]);
+      }
+    });
+  }
+  // Window tables: [base][wavefront, tile][lane] words of x0 and x1
+  static constexpr int kEntry = 2 * kLimbTiles * WAVE * kHalves;  // dwords
+  __device__ __forceinline__ u32* entry_at(const u32* entry, int base, int i) const {
+    return (u32*)entry + (base * kLimbTiles * WAVE + (kOwn * wave + i) * WAVE + lane) * kHalves;
+  }
+  static __device__ __forceinline__ Quad own(const State& x, int i) {
+    return Quad{x.a0[i], kBoth ? x.a1[i] : 0u, x.b0[i % kHeldB], kBoth ? x.b1[i % kHeldB] : 0u};
+  }
+  __device__ __forceinline__ void load_entry(Words& y, const u32* entry, int base) const {
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i)
+      if constexpr (kBoth) y.w[i] = *(const Twin*)entry_at(entry, base, i);
+      else y.w[i] = Twin{*entry_at(entry, base, i), 0};
+  }
+  // The same of an element in memory by itself (see item_words): quad j of this lane's half (kBoth: of half x) in a base
+  __device__ __forceinline__ int item_quad(int base, int x, int j) const {
+    const int half = kBoth ? x : lane >> 3 & 1;
+    return base * (rns::item_words(kRegs) / 2) + ((2 * (j < 2 ? 2 * wave + j : 8) + half) * 4 + g) * 4;
+  }
+  __device__ __forceinline__ void load_item(Words& y, const u32* item, int base) const {
+#pragma unroll
+    for (int x = 0; x < kHalves; ++x) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const Quad q = *(const Quad*)(item + item_quad(base, x, j));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y.w[4 * j + c][x] = q[c];
+      }
+      y.w[8][x] = item[item_quad(base, x, 2) + tile(8) % 4];
+    }
+    if (!kBoth)
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i) y.w[i][1] = 0;
+  }
+  __device__ __forceinline__ void load_item(Quad (&v)[kOwn], const u32* item) const {
+    Words a, b;
+    load_item(a, item, 0);
+    load_item(b, item, 1);
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) v[i] = Quad{a.w[i][0], a.w[i][1], b.w[i][0], b.w[i][1]};
+  }
+  __device__ __forceinline__ void store_item(const State& x, u32* item) const {
+    Words y[2];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) y[0].w[i] = Twin{x.a0[i], kBoth ? x.a1[i] : 0u};
+    get_b(y[1], x);
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          *(Quad*)(item + item_quad(b, h, j)) = Quad{y[b].w[4 * j][h], y[b].w[4 * j + 1][h], y[b].w[4 * j + 2][h], y[b].w[4 * j + 3][h]};
+        if (mine(8)) item[item_quad(b, h, 2) + wave] = y[b].w[8][h];
+      }
+  }
+  __device__ __forceinline__ void set(State& x, const Quad (&v)[kOwn]) const {
+    Words y[2];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      y[0].w[i] = Twin{v[i][0], v[i][1]};
+      y[1].w[i] = Twin{v[i][2], v[i][3]};
+    }
+    set_a(x, y[0]);
+    set_b(x, y[1]);
+  }
+  static __device__ __forceinline__ void set_a(State& x, const Words& y) {
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      x.a0[i] = y.w[i][0];
+      x.a1[i] = y.w[i][1];
+    }
+  }
+  __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
+    Words y;
+    get_b(y, x);
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i)
+      if constexpr (kBoth) {
+        *(Twin*)entry_at(entry, 0, i) = Twin{x.a0[i], x.a1[i]};
+        *(Twin*)entry_at(entry, 1, i) = y.w[i];
+      } else {
+        *entry_at(entry, 0, i) = x.a0[i];
+        *entry_at(entry, 1, i) = y.w[i][0];
+      }
+  }
+  __device__ __forceinline__ void load_state(State& x, const u32* entry) const {
+    Words y;
+    load_entry(y, entry, 0);
+    set_a(x, y);
+    load_entry(y, entry, 1);
+    set_b(x, y);
+  }
+};
+
 // Instruction pc of the program `prog` of `len`, asked for one after the other. A wavefront keeps 64 of them at a time in the
 // lanes of `words`: read from memory between two products, one costs a wavefront that waits for little else 2 to 5 % of a
-// product. (4096-bit moduli, whose products are long and whose wavefronts have no register left, read them so.) A macro: as a
-// function's argument the program's place in the launch's arguments would cost a copy of them.
-#define INSTRUCTION(ins, prog, len, pc, words)                                  \
-  do {                                                                          \
-    if constexpr (NR == 36) {                                                   \
-      ins = (u32)__builtin_amdgcn_readfirstlane((int)prog[pc]);                 \
-    } else {                                                                    \
-      if ((pc & (WAVE - 1)) == 0) {                                             \
-        const int at = pc + (int)(threadIdx.x & (WAVE - 1));                    \
-        words = prog[at < len ? at : len - 1];                                  \
-      }                                                                         \
-      ins = (u32)__builtin_amdgcn_readlane((int)words, pc & (WAVE - 1));        \
-    }                                                                           \
+// product. They are waited for where they are read, not where the ways join, which would wait for all loads at each instruction.
+// A macro: as a function's argument the program's place in the launch's arguments would cost a copy of them.
+#define INSTRUCTION(ins, prog, len, pc, words)                                \
+  do {                                                                        \
+    if ((pc & (WAVE - 1)) == 0) {                                             \
+      const int at = pc + (int)(threadIdx.x & (WAVE - 1));                    \
+      words = prog[at < len ? at : len - 1];                                  \
+      asm volatile("" : "+v"(words));                                         \
+    }                                                                         \
+    ins = (u32)__builtin_amdgcn_readlane((int)words, pc & (WAVE - 1));        \
   } while (0)
 
 // Every block runs the program on 16 (FOLD: 8) elements at a time. The first `split` blocks run j0, the others j1.
@@ -1610,7 +2239,7 @@ __global__ __launch_bounds__((W + W1) * 64, NR == 10 && !PAIR ? 6 : (W + W1 + 3)
       const unsigned left = (unsigned)std::min(count - first, (size_t)G::kElements);                               \
       typename G::State x;                                                                                          \
       e.load(x, j.in + first * (size_t)(2 * j.nl), left, j.nl);                                                     \
-      [[maybe_unused]] u32 words = 0;                                                                               \
+      u32 words = 0;                                                                                                \
       for (int pc = 0; pc < len;) {                                                                                 \
         u32 ins;                                                                                                    \
         INSTRUCTION(ins, prog, len, pc, words);                                                                     \
@@ -1642,6 +2271,74 @@ __global__ __launch_bounds__((W + W1) * 64, NR == 10 && !PAIR ? 6 : (W + W1 + 3)
     RUN(Rest, W * TW + (wave - W) * TW1);
   }
 #undef RUN
+}
+
+// The same for 4096-bit moduli. How many blocks stream, and how many of them are on their way, by what fits the registers: with one
+// block less, or more on their way, the paths around the run of squarings spill (3001 encryptions 18.8 ms with three on their way, 19.9
+// with six, 22.4 with nine; 64 of them 12.6 with six and 13.7 with nine). The ways through the lists' two values and an operand leave
+// room for the residues of base B as registers.
+template <bool FOLD>
+struct Wide;
+template <>
+struct Wide<true> {
+  using Power = RnsWide<true, 4, 4, 6, false>;
+  using Chains = RnsWide<true, 4, 4, 6, false>;
+  using Lists = RnsWide<true, 4, 4, 6, true>;
+};
+template <>
+struct Wide<false> {
+  using Power = RnsWide<false, 4, 4, 3, false>;
+  using Chains = RnsWide<false, 4, 4, 6, false>;
+};
+template <bool FOLD>
+__global__ __launch_bounds__(256, 1) void k_rns_wide(RnsJob j, size_t count) {
+  using G = typename Wide<FOLD>::Power;
+  __shared__ __align__(16) typename G::Shared shared;
+  const u32* prog = j.prog ? j.prog : j.ins;
+  const int len = __builtin_amdgcn_readfirstlane(j.len);
+  u32* table = j.slots + (size_t)blockIdx.x * (size_t)j.entries * G::kEntry;
+  G e(shared, j.tables);
+  for (size_t first = (size_t)blockIdx.x * G::kElements; first < count; first += (size_t)gridDim.x * G::kElements) {
+    const unsigned left = (unsigned)std::min(count - first, (size_t)G::kElements);
+    typename G::State x;
+    e.load(x, j.in + first * (size_t)(2 * j.nl), left, j.nl);
+    u32 words = 0;
+    for (int pc = 0; pc < len;) {
+      u32 ins;
+      INSTRUCTION(ins, prog, len, pc, words);
+      ++pc;
+      const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;
+      u32* entry = table + (size_t)a * G::kEntry;
+      if (op == ENG_STORE_T) {
+        e.store_state(x, entry);
+        continue;
+      }
+      if (op == ENG_LOAD_T) {
+        e.load_state(x, entry);
+        continue;
+      }
+      typename G::Words y = {};
+      if (op == ENG_SQ) {  // a run of them, each but the last with the next one's sigma
+        e.template sigma<true>(x, y);
+        for (;;) {
+          e.template extend_to_b<true>(x, y);
+          if (pc >= len) break;
+          INSTRUCTION(ins, prog, len, pc, words);
+          if (ins != ENG_SQ) break;
+          ++pc;
+          e.template extend_to_a<true>(x);
+        }
+      } else {
+        e.load_entry(y, entry, 0);
+        e.template sigma<false>(x, y);
+        e.load_entry(y, entry, 1);
+        e.template extend_to_b<false>(x, y);
+      }
+      e.template extend_to_a<false>(x);
+      if (op == ENG_MUL_T_ST) e.store_state(x, table + (size_t)b * G::kEntry);
+    }
+    e.store(x, j.out + first * (size_t)(8 * G::kLimbTiles), left);
+  }
 }
 
 // RnsLists' program on 8 elements at a time, for what is few and has long chains. All wavefronts take the same way through
@@ -1752,20 +2449,30 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_lists(R
   }
 }
 
-// k_rns_enter on blocks of 16 elements. What bounds it are the matrices of the way in and of the way back, which stream from L2
-// for 16 elements at a time: 65536 elements of 4096-bit moduli 217 us, 641 as a program of k_rns_lists on blocks of 8.
-template <int NR, int TW, int W>
-__global__ __launch_bounds__(W * 64, (W + 3) / 4) void k_rns_group_enter(const u32* __restrict__ tables,
-                                                                         const u32* __restrict__ in, size_t count, int nl,
-                                                                         u32* __restrict__ items) {
-  using G = RnsGroup<NR, TW, W, W * TW, true, false, true>;
+__global__ __launch_bounds__(256, 1) void k_rns_wide_lists(RnsLists j) {
+  using G = Wide<true>::Lists;
   __shared__ __align__(16) typename G::Shared shared;
-  G e(shared, tables, __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)) * TW);
+  __shared__ ListShared lists;
+  if (j.live && (size_t)blockIdx.x * G::kElements >= *j.live) return;
+  u32 ops = 0;
+#pragma unroll
+  for (int i = 0; i < kListOps / 8; ++i) ops = (threadIdx.x & (WAVE - 1)) == i ? j.ops[i] : ops;
+  G e(shared, j.tables);
+  run_lists(e, j, lists, ops);
+}
+
+// k_rns_enter for 4096-bit moduli, on blocks of 16 elements. What bounds it are the matrices of the way in and of the way back, which
+// stream from L2 for 16 elements at a time: 20000 elements 86 us.
+__global__ __launch_bounds__(256, 1) void k_rns_wide_enter(const u32* __restrict__ tables, const u32* __restrict__ in,
+                                                           size_t count, int nl, u32* __restrict__ items) {
+  using G = Wide<false>::Chains;
+  __shared__ __align__(16) typename G::Shared shared;
+  G e(shared, tables);
   for (size_t first = (size_t)blockIdx.x * G::kElements; first < count; first += (size_t)gridDim.x * G::kElements) {
     const unsigned left = (unsigned)std::min(count - first, (size_t)G::kElements), own = (unsigned)(e.lane & (G::kElements - 1));
     typename G::State x;
     e.load(x, in + first * (size_t)(2 * nl), left, nl);
-    if (own < left) e.store_item(x, items + (first + own) * (size_t)rns::item_words(NR));
+    if (own < left) e.store_item(x, items + (first + own) * (size_t)rns::item_words(G::kRegs));
   }
 }
 
@@ -1819,6 +2526,48 @@ __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group_c
   }
 }
 
+template <bool FOLD>
+__global__ __launch_bounds__(256, 1) void k_rns_wide_chains(RnsChains j) {
+  using G = typename Wide<FOLD>::Chains;
+  __shared__ __align__(16) typename G::Shared shared;
+  const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane((int)j.control[kChainsTotal]);
+  if (blockIdx.x * G::kElements >= total) return;
+  G e(shared, j.tables);
+  const bool columns = __builtin_amdgcn_readfirstlane((int)j.control[kChainsColumns]) != 0;
+  e.begin();
+  // as run_chains(), with a factor's words of one base after those of the other
+  for (unsigned first = blockIdx.x * G::kElements; first < total; first += gridDim.x * G::kElements) {
+    const unsigned own = first + (unsigned)(e.lane & (G::kElements - 1));
+    const bool active = own < total;
+    const Quad c = active ? ((const Quad*)j.chains)[own] : Quad{0, 0, 0, 0};
+    const u32 start = c[1], len = c[2];
+    const u32 longest = (u32)__builtin_amdgcn_readfirstlane((int)wave_max(len));  // each wavefront has all elements
+    const auto place = [&](u32 i) -> u32 { return i < len ? j.index ? j.index[start + i] : start + i : kNoOperand; };
+    const auto item = [&](u32 p) { return p == kNoOperand ? j.one : j.items + (size_t)p * rns::item_words(G::kRegs); };
+    typename G::State x;
+    typename G::Words y;
+    const u32* from = item(place(0));
+    e.load_item(y, from, 0);
+    e.set_a(x, y);
+    e.load_item(y, from, 1);
+    e.set_b(x, y);
+    from = item(place(1));
+    e.load_item(y, from, 0);
+    u32 p = place(2);
+#pragma unroll 1
+    for (u32 i = 1; i < longest; ++i) {
+      e.template sigma<false>(x, y, [&] { e.load_item(y, from, 1); });
+      e.template extend_to_b<false>(x, y);
+      from = item(p);
+      e.load_item(y, from, 0);
+      p = place(i + 2);
+      e.template extend_to_a<false>(x);
+    }
+    if (columns) e.store(x, j.columns, (size_t)c[0], active);
+    else if (active) e.store_item(x, j.out + (size_t)c[0] * rns::item_words(G::kRegs));
+  }
+}
+
 }  // namespace
 
 namespace haflo {
@@ -1829,10 +2578,10 @@ namespace {
 // The blocks of k_rns_group that are resident at once on a compute unit
 int group_blocks_per_cu(int nr) { return nr <= 10 ? 2 : 1; }
 // Blocks of 8 elements, while each has a compute unit to itself. ms with 16 / 8 to a block, up to the line: 2048 encryptions at
-// a 1024-bit key 0.97 / 0.74, at 2048 bits 3.40 / 2.21, at 4096 bits 21.3 / 20.7 (100 of them 20.7 / 17.9); 1024 decryptions at
+// a 1024-bit key 0.97 / 0.74, at 2048 bits 3.40 / 2.21, at 4096 bits 18.6 / 14.6 (100 of them 18.3 / 12.6); 1024 decryptions at
 // 1024 bits 0.399 / 0.354, at 2048 bits 1.03 / 0.79, at 4096 bits 3.47 / 2.30. Beyond it, with two blocks of 8 and more to a
 // compute unit: encryptions at 1024 bits 0.97 / 1.40 (2049), 0.99 / 1.43 (4096), 1.92 / 2.12 (6144), at 2048 bits 3.40 / 4.32
-// (2049), 3.49 / 4.23 (4096), at 4096 bits 21.9 / 39.2 (2049); decryptions at 2048 bits 1.03 / 1.46 (1025), at 4096 bits 3.50 /
+// (2049), 3.49 / 4.23 (4096), at 4096 bits 18.6 / 28.4 (2049); decryptions at 2048 bits 1.03 / 1.46 (1025), at 4096 bits 3.50 /
 // 4.44. The short products of 256-bit primes are 2 to 3 % faster there with two blocks to a compute unit, but not with three:
 // 0.400 / 0.388 (1025 decryptions at a 1024-bit key), 0.402 / 0.395 (2048), 0.473 / 0.723 (2500), 0.475 / 0.726 (3072).
 bool group_folds(const haflo_ctx* ctx, size_t count, int jobs, bool pair) {
@@ -1920,7 +2669,7 @@ int rns_enter(const haflo_ctx* ctx, const ModHost& m, const uint32_t* in, size_t
   }
   if (rns::regs_for(m.nl) != 36) return HAFLO_EINVAL;
   const unsigned blocks = (unsigned)std::max(group_blocks(ctx, 36, count, 1, false), (size_t)1);
-  hipLaunchKernelGGL((k_rns_group_enter<36, 3, 12>), dim3(blocks), dim3(12 * 64), 0, st, (const u32*)m.d_rns, in, count, m.nl, items);
+  hipLaunchKernelGGL(k_rns_wide_enter, dim3(blocks), dim3(256), 0, st, (const u32*)m.d_rns, in, count, m.nl, items);
   return hip_status(hipGetLastError());
 }
 
@@ -1935,7 +2684,7 @@ int rns_lists(const haflo_ctx* ctx, const ModHost& m, RnsLists j, size_t bound, 
   hipLaunchKernelGGL((k_rns_lists<NR, TW, W, TW1, W1, true>), dim3(blocks), dim3((W + W1) * 64), 0, st, j)
   switch (nr) {
     case 18: GROUP(18, 2, 8, 1, 2); break;
-    case 36: GROUP(36, 3, 12, 1, 0); break;
+    case 36: hipLaunchKernelGGL(k_rns_wide_lists, dim3(blocks), dim3(256), 0, st, j); break;
     default: return HAFLO_EINVAL;
   }
 #undef GROUP
@@ -1959,8 +2708,8 @@ int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound
   switch (nr) {
     case 18: GROUP(18, 2, 8, 1, 2, true); break;
     case 36:
-      if (fold) GROUP(36, 3, 12, 1, 0, true);
-      else GROUP(36, 3, 12, 1, 0, false);
+      if (fold) hipLaunchKernelGGL((k_rns_wide_chains<true>), dim3(blocks), dim3(256), 0, st, j);
+      else hipLaunchKernelGGL((k_rns_wide_chains<false>), dim3(blocks), dim3(256), 0, st, j);
       break;
     default: return HAFLO_EINVAL;
   }
@@ -2027,9 +2776,9 @@ int rns_power(const ModHost* const* m, const DevProg* const* prog, int jobs, con
       else LAUNCH((k_rns<18, false, 2>), (unsigned)waves * 64);
       break;
     case 36:
-      if (!pair) return HAFLO_EINVAL;
-      if (fold) LAUNCH((k_rns_group<36, 3, 12, 1, 0, true, true>), 12 * 64);
-      else LAUNCH((k_rns_group<36, 3, 12, 1, 0, true, false>), 12 * 64);
+      if (!pair || jobs != 1) return HAFLO_EINVAL;
+      if (fold) hipLaunchKernelGGL((k_rns_wide<true>), dim3(blocks), dim3(256), 0, st, job[0], count);
+      else hipLaunchKernelGGL((k_rns_wide<false>), dim3(blocks), dim3(256), 0, st, job[0], count);
       break;
     default: return HAFLO_EINVAL;
   }

@@ -281,3 +281,64 @@ def test_programs_without_operands_read_none(emu, tmp_path):  # noqa: F811
         os._exit(0 if shim.lists_without_operands(ctx, C.c_void_p(limbs.p), C.c_size_t(count), C.c_void_p(items.p)) == 0 else 1)
     assert os.waitpid(child, 0)[1] == 0
     emu.haflo_ctx_destroy(ctx)
+
+
+@pytest.fixture(scope="module")
+def power_shim(emu, tmp_path_factory):  # noqa: F811
+    import build_emu
+    out = str(tmp_path_factory.mktemp("power") / "libpower_shim.so")
+    root, lib_dir = os.path.dirname(HERE), os.path.dirname(build_emu.OUT)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wno-unknown-pragmas", "-o", out,
+                    "-I", os.path.join(HERE, "emu", "include"), "-I", os.path.join(root, "include"),
+                    "-I", os.path.join(root, "paper_2107_13797_amd", "csrc"), os.path.join(HERE, "rns_power_shim.cpp"),
+                    "-L", lib_dir, "-l:" + os.path.basename(build_emu.OUT), "-Wl,-rpath," + lib_dir], check=True)
+    lib = C.CDLL(out)
+    lib.power_workspace_words.restype = C.c_size_t
+    return lib
+
+
+# blocks of 8 elements and of 16, with full and partial ones, on the one-unit emulated chip
+@pytest.mark.skipif(os.environ.get("HAFLO_EMU_SANITIZE", "") == "1", reason="links the plain build")
+@pytest.mark.parametrize("count", [1, 8, 9, 19])
+def test_short_power_program_at_4096_bits(emu, shim, power_shim, count):  # noqa: F811
+    """The engine of 4096-bit moduli through every kind of its programs' instructions, squarings alone and in a run, against
+    the interpreter's integers: products are those of pairs x0 + n x1 modulo n^2 with the Montgomery radix M_A. A power of a
+    whole exponent would take the emulation hours."""
+    bits, nl, entries = 4096, 144, 3
+    p, q = oracle_key(bits)
+    n, rng = p * q, random.Random(count)
+    nsq = n * n
+    ctx = public_ctx(emu, n, bits)
+    radix = 1
+    for a in channel_primes(shim, shim.rns_primes_for(36), 3):
+        radix *= a
+    rinv = pow(radix, -1, nsq)
+    SQ, MUL, MUL_ST, LOAD, STORE = 0, 1, 2, 8, 9
+    program = [(STORE, 0, 0), (SQ, 0, 0), (MUL_ST, 0, 1), (SQ, 0, 0), (SQ, 0, 0), (SQ, 0, 0), (MUL, 1, 0), (STORE, 2, 0), (LOAD, 1, 0),
+               (MUL, 2, 0), (SQ, 0, 0)]
+    halves = [[0, 0], [n - 1, n - 1], [1, 0]] + [[rng.randrange(n) for _ in range(2)] for _ in range(count)]
+    halves = halves[-count:] if count < 4 else halves[:count]
+    limbs = np.array([[(v >> 29 * i) & (1 << 29) - 1 for v in pair for i in range(nl)] for pair in halves], dtype=np.uint32)
+    columns = power_shim.power_columns(ctx)
+    got = np.zeros((count, 2, columns), dtype=np.int64)
+    ws_words = power_shim.power_workspace_words(ctx, C.c_size_t(count), entries)
+    w, d_limbs = Dev(emu, np.zeros(ws_words, np.uint32)), Dev(emu, limbs)
+    ins = np.array([op | a << 8 | b << 20 for op, a, b in program], dtype=np.uint32)
+    assert power_shim.power_program(ctx, C.c_void_p(w.p), C.c_void_p(d_limbs.p), C.c_size_t(count), entries,
+                                    ins.ctypes.data_as(C.c_void_p), len(program), got.ctypes.data_as(C.c_void_p)) == 0
+    emu.haflo_ctx_destroy(ctx)
+    for pair, cols in zip(halves, got.tolist()):
+        acc, table = pair[0] + n * pair[1], {}
+        for op, a, b in program:
+            if op == SQ:
+                acc = acc * acc * rinv % nsq
+            elif op in (MUL, MUL_ST):
+                acc = acc * table[a] * rinv % nsq
+            elif op == LOAD:
+                acc = table[a]
+            if op == STORE:
+                table[a] = acc
+            elif op == MUL_ST:
+                table[b] = acc
+        x0, x1 = (sum(v << 29 * i for i, v in enumerate(c)) for c in cols)
+        assert (x0 + n * x1) % nsq == acc
