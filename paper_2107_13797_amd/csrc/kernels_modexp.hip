@@ -408,15 +408,16 @@ size_t rns_bytes(const haflo_ctx* ctx, const ModHost& m, size_t count, int jobs,
   if (!m.d_rns || count == 0) return 0;
   return rns_buffers(ctx, m, count, jobs, std::max(p0.table_entries, p1.table_entries)).total * 4 + 256;
 }
-// Powers of stored ciphertexts by one scalar of 17 bits and more (16 squarings), large arrays: a way into the residue
-// form and back costs about four products on limbs. ms on limbs / in residues: 8192 elements at a 2048-bit key 0.234 /
-// 0.146 for 17 bits, 0.76 / 0.30 for 63; 65536 elements 1.11 / 0.72 and 3.42 / 1.59; at 1024 bits 65536 elements 0.305 /
-// 0.245 and 0.88 / 0.58; at 512 bits 0.101 / 0.120 and 0.271 / 0.273, where it stays on limbs. 4096-bit keys stay on
-// limbs as well, although residues would be faster there: 8192 elements 0.57 / 0.39 and 2.26 / 1.11, 64 elements 0.19 /
-// 0.18 and 0.85 / 0.47.
-constexpr uint64_t kResiduePowerSquarings = 16;
-bool power_in_residues(const haflo_ctx* ctx, size_t count) {
-  return ctx->Nh.d_rns && (ctx->Nh.nl == 36 || ctx->Nh.nl == 72) && count >= (size_t)ctx->num_cu * 32;
+// Powers of stored ciphertexts by one scalar: a way into the residue form and back costs about four products on limbs. Squarings from
+// which they go through it, 0: never. us on limbs / in residues: at 1024 and 2048 bits large arrays, 8192 elements at a 2048-bit key
+// 234 / 146 for 17 bits, 760 / 300 for 63; 65536 elements 1110 / 720 and 3420 / 1590; at 1024 bits 65536 elements 305 / 245 and 880 /
+// 580. At 512 bits 101 / 120 and 271 / 273, where it stays on limbs. At 4096 bits, where an array of any size is spread over blocks:
+// 16 elements 9 bits 102 / 118, 13 bits 149 / 132, 22 bits 243 / 155; 2048 elements 6 bits 138 / 138, 9 bits 200 / 148, 63 bits
+// 1622 / 390; 65536 elements 6 bits 2055 / 1852, 22 bits 5379 / 2936.
+int residue_power_squarings(const haflo_ctx* ctx, size_t count) {
+  if (!ctx->Nh.d_rns) return 0;
+  if (ctx->Nh.nl == 144) return count >= (size_t)ctx->num_cu * 8 ? 8 : 12;
+  return (ctx->Nh.nl == 36 || ctx->Nh.nl == 72) && count >= (size_t)ctx->num_cu * 32 ? 16 : 0;
 }
 u32* align256(u32* p) { return (u32*)(((uintptr_t)p + 255) & ~(uintptr_t)255); }
 
@@ -471,7 +472,7 @@ size_t ws_scalar_mul_min(const haflo_ctx* ctx, size_t count) {
 // the residue form's tables hold at most 9 entries of a 63-bit scalar's plan
 size_t ws_scalar_mul(const haflo_ctx* ctx, size_t count) {
   size_t w = ws_scalar_mul_min(ctx, count);
-  if (power_in_residues(ctx, count)) w = std::max(w, rns_buffers(ctx, ctx->Nh, count, 1, 9).total * 4 + 256);
+  if (residue_power_squarings(ctx, count)) w = std::max(w, rns_buffers(ctx, ctx->Nh, count, 1, 9).total * 4 + 256);
   return w;
 }
 // layout: [canon29: count*N.nl][yp: count*P2.nl][yq: count*Q2.nl][tables]
@@ -769,7 +770,8 @@ int haflo_scalar_mul_i64_bcast(const haflo_ctx* ctx, const void* d_c, int64_t k,
     src = (const u32*)d_out;
   }
   const HostSched plan = make_schedule(Big(mag), 4);
-  if (power_in_residues(ctx, count) && workspace_bytes >= ws_scalar_mul(ctx, count) && plan.nsquare >= kResiduePowerSquarings) {
+  const int squarings = residue_power_squarings(ctx, count);
+  if (squarings && plan.nsquare >= (uint64_t)squarings && workspace_bytes >= ws_scalar_mul(ctx, count)) {
     DevProg power;  // travels with the launch
     append_modexp(power.host, plan);
     power.table_entries = plan.table_len + 1;

@@ -155,6 +155,28 @@ def test_creating_a_public_context_is_quick(emu):  # noqa: F811
     assert best(lambda: emu.haflo_ctx_destroy(public_ctx(emu, n, 2048))) < 0.2 * best(lambda: pow(3, n, n * n))
 
 
+def test_scalar_powers_at_4096_bits(emu):  # noqa: F811
+    """Powers by one scalar on both sides of the line between limbs and residues (12 squarings for an array of any size), of either
+    sign, in place and not, in the workspace asked for and in the least."""
+    lib, bits, count = emu, 4096, 3
+    p, q = oracle_key(bits)
+    nsq, rng = (p * q) ** 2, random.Random(10)
+    ctx = public_ctx(lib, p * q, bits)
+    assert uses_residues(lib, ctx, _cabi.OP_SCALAR_MUL, count)
+    nlw = bits * 9 // 128
+    cs = [rng.randrange(2, nsq) for _ in range(count)]
+    for k in ((1 << 12) - 1, 1 << 12, -(1 << 13) - 77):
+        for size in (lib.haflo_workspace_bytes, lib.haflo_workspace_bytes_least):
+            d_c, d_o = zeros(lib, (count, nlw)), zeros(lib, (count, nlw))
+            assert lib.haflo_import_cipher(ctx, words(lib, cs, bits // 16).p, d_c.p, None, count, None) == 0
+            nb = size(ctx, _cabi.OP_SCALAR_MUL, count, 0)
+            w = Dev(lib, np.zeros(nb, np.uint8))  # ends at a guard page
+            for out in (d_o, d_c):
+                assert lib.haflo_scalar_mul_i64_bcast(ctx, d_c.p, k, out.p, count, w.p, nb, None) == 0
+                assert export_n(lib, ctx, bits, out, count) == [pow(c, k, nsq) for c in cs], (k, nb)
+    lib.haflo_ctx_destroy(ctx)
+
+
 def matvec(lib, ctx, bits, orientation, cs, x, room):
     rows, cols = x.shape
     op = _cabi.OP_MATVEC_XT_D if orientation == 0 else _cabi.OP_MATVEC_X_W

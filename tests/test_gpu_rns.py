@@ -151,6 +151,28 @@ def test_powers_by_one_scalar_match_small_batches(bits):
     pub.close()
 
 
+def test_powers_by_one_scalar_at_4096_bits(public_and_ciphertexts):
+    """Arrays of any size go through the residue form from 12 squarings on, from 2048 elements on from 8: the same bits as in the
+    least workspace, which is the limb arithmetic, next to the lines and on blocks of 8 and of 16 elements."""
+    api, ctx, c = public_and_ciphertexts(4096)
+    lib, n = api.lib(), (lambda p, q: p * q)(*oracle_key(4096))
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for count in (1, 17, 2047, 2048, 2049, 4100):
+        part = c[:count].contiguous()
+        for k in (255, 256, 4095, 4096, -(1 << 21) - 1, 2 ** 63 - 1):
+            print("scalar 4096", count, k, flush=True)
+            outs = []
+            for size in (lib.haflo_workspace_bytes, lib.haflo_workspace_bytes_least):
+                nbytes = size(ctx.handle, _cabi.OP_SCALAR_MUL, count, 0)
+                ws, out = torch.empty(nbytes, dtype=torch.uint8, device="cuda"), torch.empty_like(part)
+                assert lib.haflo_scalar_mul_i64_bcast(ctx.handle, C.c_void_p(part.data_ptr()), k, C.c_void_p(out.data_ptr()), count,
+                                                      C.c_void_p(ws.data_ptr()), nbytes, stream) == 0
+                outs.append(out)
+            assert torch.equal(*outs)
+        a, b = (dev_to_ints(api.haflo_export_cipher(ctx, t[count - 1:count].contiguous()))[0] for t in (part, outs[0]))
+        assert b == pow(a, k, n * n)
+
+
 @pytest.mark.parametrize("bits,count", [(1024, 24576), (1024, 24577), (1024, 45000), (1024, 80000)])
 def test_key_owner_is_not_slower_with_the_workspace_asked_for(bits, count):
     """The sizes around which single products modulo 512-bit primes are as quick on limbs as in residues: the same bits as
