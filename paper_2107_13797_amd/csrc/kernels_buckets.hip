@@ -892,17 +892,15 @@ constexpr size_t kResidueWords = (size_t)8 << 30;  // of 32 bits
 constexpr size_t kEnterRows = 1 << 17;  // 75 MB of pairs at 2048 bits; way in of so many 0.4 ms, against two launches
 // All products in the residue form. Those of the first round take a third of the time on a full chip (65536 by 32 entries at
 // 2048 bits 4.2 -> 1.35 ms), and the chains behind the rounds less than a quarter (0.55 -> 0.17), against a way in. Whole calls on
-// limbs / in residues, ms. 2048 bits: 4096 by 1 0.77 / 0.52, 30000 by 1 0.95 / 0.65, 4096 by 16 0.89 / 0.71, 4096 by 32 1.07 /
-// 0.80, 65536 by 4 1.44 / 0.93, 65536 by 32 5.27 / 2.40; so at every size. 4096 bits, where the matrices stream: 4096 by 8 1.74 /
-// 1.84, 4096 by 16 2.10 / 2.16; 8192 by 16 2.70 / 2.53, 4096 by 32 3.06 / 2.86, 16384 by 16 3.85 / 3.25, 16384 by 32 6.31 / 4.87. The
-// line was drawn when the way in took three times as long; tall narrow matrices have come to gain since (16384 by 4 2.11 / 2.05,
-// 65536 by 4 4.01 / 3.41). The shape does not say how many entries are zero: at 4096 bits a row of some one to five digits is
-// still quicker on limbs (5 % non-zero entries, 65536 by 16 2.63 / 2.84, by 64 4.58 / 4.88). At 1024 bits limbs are the quicker:
-// 65536 by 32 1.78 / 2.59 on blocks of 16 elements, 4096 by 32 0.59 / 0.65. An element takes twice the memory: limbs where the
-// plan would take more than 32 GiB (2048 bits: 131072 by 1024 is still below it, 2^24 by 8 and 2^25 by 1 are not).
+// limbs / in residues, ms. 2048 bits: 64 by 16 0.64 / 0.50, 4096 by 1 0.77 / 0.52, 30000 by 1 0.95 / 0.65, 4096 by 16 0.89 / 0.71,
+// 4096 by 32 1.07 / 0.80, 65536 by 4 1.44 / 0.93, 65536 by 32 5.27 / 2.40. 4096 bits: 64 by 2 1.18 / 1.03, 4096 by 1 1.52 / 1.22, 4096
+// by 8 1.75 / 1.39, 65536 by 1 2.63 / 2.14, 65536 by 4 4.16 / 2.69, 65536 by 16 10.4 / 5.3, 600 by 256 6.1 / 4.4. So at every size. The
+// shape does not say how many entries are zero: with 5 % of them non-zero, at 4096 bits, 65536 by 1 1.93 / 1.89, by 8 2.09 / 1.99.
+// Some hundreds of columns of a few rows are still quicker on limbs (16 by 1024 at 2048 bits 2.25 / 2.63). At 1024 bits limbs are the
+// quicker: 65536 by 32 1.78 / 2.59 on blocks of 16 elements, 4096 by 32 0.59 / 0.65. An element takes twice the memory: limbs where
+// the plan would take more than 32 GiB (2048 bits: 131072 by 1024 is still below it, 2^24 by 8 and 2^25 by 1 are not).
 bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  if (!ctx->Nh.d_rns) return false;
-  if (ctx->Nh.nl != 72 && !(ctx->Nh.nl == 144 && cols >= 16 && rows * cols >= (size_t)ctx->num_cu * 512)) return false;
+  if (!ctx->Nh.d_rns || ctx->Nh.nl < 72) return false;
   return xtd_bucket_plan(ctx, rows, cols, true).total <= kResidueWords;
 }
 

@@ -919,15 +919,15 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
 }
 // Tables and rows in the residue form. Whole calls on limbs / in residues, ms, 70 % zeros. 2048 bits: 65536 by 1 0.482 / 0.492, 16384
 // by 2 0.408 / 0.406; 40000 by 4 0.62 / 0.50, 4096 by 8 0.46 / 0.40, 1000 by 64 0.62 / 0.46, 64 by 256 1.11 / 0.62, 65536 by 32
-// 1.89 / 0.99, 16384 by 256 3.78 / 1.69. 4096 bits: 4096 by 8 0.99 / 1.16, 2000 by 32 1.26 / 1.28; 4096 by 32 1.51 / 1.40, 1000 by
-// 64 1.49 / 1.40, 64 by 256 3.05 / 2.39, 16384 by 64 4.15 / 3.13. At 1024 bits limbs are the quicker: 16384 by 64 0.54 / 0.69.
-// The shape does not say how many entries are zero: with less than one factor a row at 2048 bits, some five at 4096, limbs are
-// (300000 by 4 with 10 % of one digit 0.84 / 1.05 at 2048, 20000 by 64 with 5 % 1.13 / 1.28 at 4096).
+// 1.89 / 0.99, 16384 by 256 3.78 / 1.69. 4096 bits: 65536 by 1 1.19 / 1.30; 64 by 4 0.88 / 0.81, 65536 by 4 1.60 / 1.50, 1000 by 8 0.96
+// / 0.89, 4096 by 16 1.31 / 1.01, 2000 by 32 1.29 / 1.02, 300 by 48 1.34 / 1.01, 16384 by 64 4.15 / 2.05. At 1024 bits limbs are the
+// quicker: 16384 by 64 0.54 / 0.69. The shape does not say how many entries are zero: with less than one factor a row limbs are
+// (300000 by 4 with 10 % of one digit 0.84 / 1.05 at 2048, 65536 by 4 with 5 % of two 1.17 / 1.34 at 4096).
 // List places and table entries are 32-bit. An entry takes twice the memory of limbs: beyond 2048 columns (tables of 5 GB at 2048
 // bits, 10 at 4096) limbs. Rows take no more than on limbs but for one portion's columns (xw_portion) and 16 bytes each.
 bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
   if (!ctx->Nh.d_rns || rows >= (1u << 28) || cols > 2048 || rows > 0xFFFFFFFFull / kMaxPos / (cols ? cols : 1)) return false;
-  return (ctx->Nh.nl == 72 && cols >= 4) || (ctx->Nh.nl == 144 && (cols >= 64 || (cols >= 32 && rows >= 4096)));
+  return ctx->Nh.nl >= 72 && cols >= 4;
 }
 // Segments per row: doubled while the engine has no more than its fill of chains, and a list of 30 % a few factors a chain. A
 // compute unit has 192 chains in flight at 2048 bits and 16 at 4096, where a further segment's product weighs more: 20000 by 64 with

@@ -252,7 +252,8 @@ def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
 # Shapes of the residue form next to what bounds its memory (rows alone, columns alone, both), and some beyond it.
 @pytest.mark.parametrize("bits,rows,cols", [
     (2048, 4096, 1), (2048, 65536, 32), (2048, 4096, 1024), (2048, 1 << 20, 1), (2048, 1 << 22, 32), (2048, 1 << 24, 8),
-    (2048, 1 << 26, 2), (2048, 1 << 27, 1), (2048, 131072, 1024), (4096, 65536, 64), (4096, 1 << 22, 16), (4096, 131072, 1024)])
+    (2048, 1 << 26, 2), (2048, 1 << 27, 1), (2048, 131072, 1024), (4096, 65536, 64), (4096, 1 << 22, 16), (4096, 131072, 1024),
+    (4096, 4096, 1), (4096, 65536, 4), (4096, 1 << 24, 2)])
 def test_gradient_workspace_is_bounded(emu, bits, rows, cols):  # noqa: F811
     """What the call asks for is at most 2.2 times what it can do with (an element takes twice the memory, and there are
     some more for a column's last products), and more than the least only up to 32 GiB: the binding takes what is asked for
@@ -268,7 +269,7 @@ def test_gradient_workspace_is_bounded(emu, bits, rows, cols):  # noqa: F811
 
 @pytest.mark.parametrize("bits,rows,cols", [
     (2048, 64, 4), (2048, 65536, 32), (2048, 16384, 256), (2048, 100, 2048), (2048, 1 << 24, 4), (2048, 1 << 24, 8),
-    (2048, 40000000, 4), (4096, 1 << 20, 32), (4096, 300, 2048)])
+    (2048, 40000000, 4), (4096, 1 << 20, 32), (4096, 300, 2048), (4096, 64, 4), (4096, 65536, 8)])
 def test_forward_workspace_is_bounded(emu, bits, rows, cols):  # noqa: F811
     """The same for the forward product: its rows' lists are as long as on limbs, their products leave the form in portions
     of bounded size (0.6 GB at 2048 bits on 256 compute units; here there is one), and a row's place among them is 16 bytes."""

@@ -240,7 +240,7 @@ def random_ciphertexts(api, ctx, n, bits, count):
 # them); at 4096 bits shapes next to the rule
 @pytest.mark.parametrize("bits,rows,cols,top", [
     (2048, 4096, 1, 1 << 18), (2048, 4099, 32, 1 << 18), (2048, 5043, 26, 600), (2048, 65537, 2, 40), (2048, 140001, 1, 3),
-    (2048, 32768, 33, 1 << 17), (4096, 4096, 32, 1 << 18), (4096, 8201, 16, 40), (4096, 9001, 41, 1 << 17)])
+    (2048, 32768, 33, 1 << 17), (4096, 4096, 32, 1 << 18), (4096, 8201, 16, 40), (4096, 9001, 41, 1 << 17), (4096, 4097, 1, 1 << 18), (4096, 20001, 3, 600)])
 def test_gradient_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, top):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -256,7 +256,7 @@ def test_gradient_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, t
 # time; at 4096 bits shapes next to the rule
 @pytest.mark.parametrize("bits,rows,cols,top", [
     (2048, 81920, 4, 1 << 16), (2048, 10241, 32, 1 << 9), (2048, 641, 512, 200), (2048, 40001, 17, 1 << 28), (2048, 129, 5, 1 << 16),
-    (2048, 530001, 4, 1 << 16), (4096, 4096, 32, 1 << 16), (4096, 131, 64, 200), (4096, 6001, 65, 1 << 28)])
+    (2048, 530001, 4, 1 << 16), (4096, 4096, 32, 1 << 16), (4096, 131, 64, 200), (4096, 6001, 65, 1 << 28), (4096, 129, 5, 1 << 16), (4096, 20001, 4, 1 << 9)])
 def test_forward_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, top):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
