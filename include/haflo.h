@@ -124,12 +124,15 @@ int haflo_ctx_info(const haflo_ctx* ctx, uint32_t* n_bits, uint32_t* cipher_limb
 
 /* Row count from which X^T [[d]] (haflo_cipher_matvec, orientation 0) takes
  * the bucket method instead of per-base power tables; both give the same
- * ciphertext bits. The setting belongs to the context and is read by the
+ * ciphertext bits. By default it takes it from
+ * HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT rows on, and on fewer rows when it gets the
+ * workspace that it asks for (haflo_workspace_bytes), which is more than the
+ * tables' (haflo_workspace_bytes_least). The setting belongs to the context and is read by the
  * matvec itself and by every workspace query that contains one
  * (haflo_workspace_bytes for the matvec and the Taylor loss, the store's
  * calls), so change it only between a query and the call it sizes if both are
- * repeated. min_rows = 0 restores HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT; 1 forces
- * buckets wherever the shape allows them; SIZE_MAX forces tables. Not
+ * repeated. min_rows = 0 restores the default; 1 forces buckets wherever the
+ * shape allows them; SIZE_MAX forces tables. Not
  * synchronised: do not call it while another thread uses the context. */
 #define HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT 4096
 int haflo_ctx_set_xtd_bucket_min_rows(haflo_ctx* ctx, size_t min_rows);

@@ -696,7 +696,7 @@ int haflo_ctx_info(const haflo_ctx* ctx, uint32_t* n_bits, uint32_t* cipher_limb
 
 int haflo_ctx_set_xtd_bucket_min_rows(haflo_ctx* ctx, size_t min_rows) {
   if (!ctx) return HAFLO_EINVAL;
-  ctx->xtd_bucket_min_rows = min_rows ? min_rows : (size_t)HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT;
+  ctx->xtd_bucket_min_rows = min_rows;
   return HAFLO_OK;
 }
 

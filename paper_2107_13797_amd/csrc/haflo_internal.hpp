@@ -122,7 +122,7 @@ struct haflo_ctx {
   int lc = 0, lp = 0;  // canonical 32-bit limbs of a ciphertext / plaintext
   int num_cu = 0;
   int device = -1;  // the HIP device that was current when the context was created
-  size_t xtd_bucket_min_rows = HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT;  // X^T [[d]]: bucket method from this many rows on
+  size_t xtd_bucket_min_rows = 0;  // X^T [[d]]: the bucket method from this many rows on, 0: as the library chooses
   haflo::Big n, nsq, p, q;
   haflo::ModHost N;            // n^2
   haflo::ModHost Nw;           // n, at the limb count (and Montgomery radix) of n^2

@@ -867,11 +867,19 @@ XtdPlan xtd_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   return p;
 }
 
-// Tall matrices go through the bucket method (one product per exponent digit instead of four or
-// five, no tables); below the row threshold its fixed cost per column (1024 buckets per digit
-// position) outweighs that. The threshold is a setting of the context (haflo_ctx_set_xtd_bucket_min_rows).
-bool use_buckets(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  return rows >= ctx->xtd_bucket_min_rows && rows > 0 && xtd_buckets_fit(rows, cols);
+// The bucket method (one product per exponent digit instead of four or five, no tables) is the quicker at every size. us, tables /
+// buckets (those in residues at 2048 and 4096 bits): 1024 bits 1 by 1 349 / 260, 64 by 64 445 / 431, 600 by 16 443 / 389, 4000 by 16
+// 943 / 477, 64 by 1024 2518 / 1582; 2048 bits 64 by 1 619 / 443, 600 by 16 1222 / 559, 4000 by 64 2625 / 1045; 4096 bits 64 by 16
+// 1677 / 1188, 1200 by 4 5646 / 1162, 4000 by 64 8706 / 2697. But it takes more memory, and a call on few rows never asked for that:
+// below a number of rows, a setting of the context (haflo_ctx_set_xtd_bucket_min_rows), the tables' workspace is enough. Unless that
+// number was set, such a call asks for the buckets' as well, up to kShortWords of it, and takes them when it gets it.
+constexpr size_t kShortWords = (size_t)1 << 29;  // 2 GiB; the largest that came into question is 4000 by 64 at 4096 bits, 1.5
+bool needs_buckets(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  const size_t from = ctx->xtd_bucket_min_rows ? ctx->xtd_bucket_min_rows : (size_t)HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT;
+  return rows >= from && rows > 0 && xtd_buckets_fit(rows, cols);
+}
+bool may_use_buckets(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  return needs_buckets(ctx, rows, cols) || (!ctx->xtd_bucket_min_rows && rows > 0 && xtd_buckets_fit(rows, cols));
 }
 struct XtdBucketLayout {
   size_t off_P, off_ws, total;  // in u32 words; word 0 holds the largest |x|
@@ -981,14 +989,17 @@ size_t ws_xw_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
   return xw_in_residues(ctx, rows, cols) ? xw_residue_plan(ctx, rows, cols).total * 4 + 256 : 0;
 }
 
-// X^T [[d]]: what a call can do with, and what it asks for where the residue engine serves it (else 0)
+// X^T [[d]]: what a call can do with, and what it asks for where it takes the bucket method, on limbs or in residues (else 0)
 size_t ws_xtd_min(const haflo_ctx* ctx, size_t rows, size_t cols) {
   if (!cols) return 0;
-  return (use_buckets(ctx, rows, cols) ? xtd_bucket_layout(ctx, rows, cols, false).total : xtd_plan(ctx, rows, cols).total) * 4;
+  return (needs_buckets(ctx, rows, cols) ? xtd_bucket_layout(ctx, rows, cols, false).total : xtd_plan(ctx, rows, cols).total) * 4;
 }
-size_t ws_xtd_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
-  if (!cols || !use_buckets(ctx, rows, cols) || !xtd_buckets_in_residues(ctx, rows, cols)) return 0;
-  return xtd_bucket_layout(ctx, rows, cols, true).total * 4 + 256;  // its start is aligned to 256 bytes
+size_t ws_xtd_buckets(const haflo_ctx* ctx, size_t rows, size_t cols, bool residues) {
+  if (!cols || !may_use_buckets(ctx, rows, cols) || (residues && !xtd_buckets_in_residues(ctx, rows, cols))) return 0;
+  const size_t words = xtd_bucket_layout(ctx, rows, cols, residues).total;
+  const bool few = !needs_buckets(ctx, rows, cols);
+  if (words > kShortWords && few) return 0;
+  return words * 4 + (residues || few ? 256 : 0);  // their start is aligned to 256 bytes
 }
 
 // The tables of 256 entries per base and position, and `chains` as the rows' products need it
@@ -1121,7 +1132,7 @@ size_t haflo_workspace_bytes(const haflo_ctx* ctx, int op, size_t rows, size_t c
       return ((rows * (size_t)ctx->lp * 4 + 255) & ~(size_t)255) + ((rows * (size_t)ctx->N.nl * 4 + 255) & ~(size_t)255) +
              ws_encrypt(ctx, rows);
     case HAFLO_OP_MATVEC_XT_D:
-      return std::max(ws_xtd_min(ctx, rows, cols), ws_xtd_residues(ctx, rows, cols));
+      return std::max({ws_xtd_min(ctx, rows, cols), ws_xtd_buckets(ctx, rows, cols, false), ws_xtd_buckets(ctx, rows, cols, true)});
     case HAFLO_OP_MATVEC_X_W: return std::max(xw_plan(ctx, rows, cols).total * 4, ws_xw_residues(ctx, rows, cols));
     case HAFLO_OP_SUM_SEGMENTS:
       if (rows >= (1ull << 32) || cols >= (1ull << 24)) return (size_t)-1;
@@ -1157,10 +1168,11 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
   const size_t need = haflo_workspace_bytes_least(ctx, orientation == 0 ? HAFLO_OP_MATVEC_XT_D : HAFLO_OP_MATVEC_X_W, rows, cols);
   if (!d_workspace || workspace_bytes < need) return HAFLO_EINVAL;
   u32* ws = (u32*)d_workspace;
-  const size_t asked = orientation == 0 ? ws_xtd_residues(ctx, rows, cols) : ws_xw_residues(ctx, rows, cols);
+  const size_t asked = orientation == 0 ? ws_xtd_buckets(ctx, rows, cols, true) : ws_xw_residues(ctx, rows, cols);
   const bool residues = asked != 0 && workspace_bytes >= asked;
-  if (residues) ws = (u32*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
-  const bool buckets = orientation == 0 && use_buckets(ctx, rows, cols);
+  const size_t on_limbs = orientation == 0 ? ws_xtd_buckets(ctx, rows, cols, false) : 0;
+  const bool buckets = orientation == 0 && (residues || (on_limbs != 0 && workspace_bytes >= on_limbs));
+  if (residues || (buckets && !needs_buckets(ctx, rows, cols))) ws = (u32*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
   int rc = buckets ? HAFLO_OK
                    : launch_maxmag(ctx, d_X, rows * cols, ws, orientation == 0 ? 2 : (int)(kXwBinsAt + kLenBins), st);
   if (rc != HAFLO_OK) return rc;

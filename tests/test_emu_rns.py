@@ -249,6 +249,41 @@ def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     lib.haflo_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("bits,rows,cols", [(512, 1, 1), (512, 130, 2), (1024, 33, 3), (2048, 5, 2)])
+def test_gradient_matvec_on_few_rows(emu, bits, rows, cols):  # noqa: F811
+    """Fewer rows than the bucket method needs: it is taken with the workspace asked for, in residues where they serve the key and on
+    limbs (one byte less than that), and the tables with the least, which has no room for buckets: the same ciphertexts as the
+    oracle's. A threshold of the caller's own, and more columns than the bucket method takes, keep the tables."""
+    lib = emu
+    p, q = oracle_key(bits)
+    n, rng = p * q, random.Random(rows)
+    ctx = public_ctx(lib, n, bits)
+    sizes = lambda *shape: [f(ctx, _cabi.OP_MATVEC_XT_D, *shape) for f in (lib.haflo_workspace_bytes, lib.haflo_workspace_bytes_least)]  # noqa: E731
+    asked, least = sizes(rows, cols)
+    assert least < asked
+    npr = np.random.default_rng(rows)
+    x = npr.integers(-(1 << 18), 1 << 18, size=(rows, cols)).astype(np.int32)
+    x[npr.random(x.shape) < 0.2] = 0
+    x[0, 0] = -2 ** 31
+    cs = [rng.randrange(2, n * n) for _ in range(rows)]
+    want = O.matvec(O.PrivateKey(p, q).public, 0, cs, x.tolist())
+    nlw = bits * 9 // 128
+    d_c = zeros(lib, (rows, nlw))
+    assert lib.haflo_import_cipher(ctx, words(lib, cs, bits // 16).p, d_c.p, None, rows, None) == 0
+    for nb in (asked, asked - 1, least):
+        d_o, w = zeros(lib, (cols, nlw)), Dev(lib, np.zeros(nb, np.uint8))  # ends at a guard page
+        assert lib.haflo_cipher_matvec(ctx, 0, d_c.p, Dev(lib, x).p, rows, cols, d_o.p, w.p, nb, None) == 0
+        assert export_n(lib, ctx, bits, d_o, cols) == want, nb
+    assert lib.haflo_cipher_matvec(ctx, 0, d_c.p, Dev(lib, x).p, rows, cols, d_o.p, w.p, least - 1, None) == -1
+    for threshold in (4096, rows + 1, 2 ** 64 - 1):
+        assert lib.haflo_ctx_set_xtd_bucket_min_rows(ctx, threshold) == 0
+        assert sizes(rows, cols) == [least, least]
+    assert lib.haflo_ctx_set_xtd_bucket_min_rows(ctx, 0) == 0
+    assert sizes(rows, cols) == [asked, least] and max(sizes(4000, 64)) <= (2 << 30) + 256
+    assert sizes(4000, 1025) == [sizes(4000, 1025)[1]] * 2  # more columns than the bucket method takes
+    lib.haflo_ctx_destroy(ctx)
+
+
 # Shapes of the residue form next to what bounds its memory (rows alone, columns alone, both), and some beyond it.
 @pytest.mark.parametrize("bits,rows,cols", [
     (2048, 4096, 1), (2048, 65536, 32), (2048, 4096, 1024), (2048, 1 << 20, 1), (2048, 1 << 22, 32), (2048, 1 << 24, 8),

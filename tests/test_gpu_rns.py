@@ -252,6 +252,23 @@ def test_gradient_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, t
     assert torch.equal(api.haflo_cipher_matvec(ctx, 0, c, x), matvec_on_limbs(api, ctx, 0, c, x))
 
 
+# fewer rows than the bucket method needs: one, less and more than a chunk of 16 and of 32, next to the threshold; one column and many
+@pytest.mark.parametrize("bits", [512, 1024, 2048, 4096])
+@pytest.mark.parametrize("rows,cols,top", [(2, 1, 3), (15, 7, 1 << 18), (16, 40, 600), (33, 64, 1 << 17), (700, 3, 40), (4095, 5, 1 << 18)])
+def test_gradient_matvec_on_few_rows_matches_tables(bits, rows, cols, top):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_13797_amd import api
+    p, q = oracle_key(bits)
+    for ctx in (api.haflo_ctx_create_public(p * q, bits), api.haflo_ctx_create_private(p, q, bits)):
+        c = random_ciphertexts(api, ctx, p * q, bits, rows)
+        x = exponents(rows, cols, top, rows)
+        got = api.haflo_cipher_matvec(ctx, 0, c, x)
+        api.haflo_ctx_set_xtd_bucket_min_rows(ctx, 2 ** 64 - 1)
+        assert torch.equal(got, api.haflo_cipher_matvec(ctx, 0, c, x))
+        ctx.close()
+
+
 # rows in 1, 2 and up to 16 chains, lists of no to four digits an entry, all digit positions, more rows than leave the form at a
 # time; at 4096 bits shapes next to the rule
 @pytest.mark.parametrize("bits,rows,cols,top", [
