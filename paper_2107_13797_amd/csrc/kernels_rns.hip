@@ -2202,14 +2202,15 @@ struct RnsWide {
 
 // Instruction pc of the program `prog` of `len`, asked for one after the other. A wavefront keeps 64 of them at a time in the
 // lanes of `words`: read from memory between two products, one costs a wavefront that waits for little else 2 to 5 % of a
-// product. They are waited for where they are read, not where the ways join, which would wait for all loads at each instruction.
+// product. PIN: they are waited for where they are read, not where the ways join, which would wait for all loads at each instruction;
+// only k_rns_wide has loads on their way there (k_rns_group with it: 64 decryptions at a 4096-bit key 2.169 -> 2.184 ms).
 // A macro: as a function's argument the program's place in the launch's arguments would cost a copy of them.
-#define INSTRUCTION(ins, prog, len, pc, words)                                \
+#define INSTRUCTION(ins, prog, len, pc, words, PIN)                           \
   do {                                                                        \
     if ((pc & (WAVE - 1)) == 0) {                                             \
       const int at = pc + (int)(threadIdx.x & (WAVE - 1));                    \
       words = prog[at < len ? at : len - 1];                                  \
-      asm volatile("" : "+v"(words));                                         \
+      if constexpr (PIN) asm volatile("" : "+v"(words));                      \
     }                                                                         \
     ins = (u32)__builtin_amdgcn_readlane((int)words, pc & (WAVE - 1));        \
   } while (0)
@@ -2242,11 +2243,11 @@ __global__ __launch_bounds__((W + W1) * 64, NR == 10 && !PAIR ? 6 : (W + W1 + 3)
       u32 words = 0;                                                                                                \
       for (int pc = 0; pc < len;) {                                                                                 \
         u32 ins;                                                                                                    \
-        INSTRUCTION(ins, prog, len, pc, words);                                                                     \
+        INSTRUCTION(ins, prog, len, pc, words, false);                                                              \
         _Pragma("unroll 1") while (ins == ENG_SQ) {                                                                 \
           e.template multiply<true>(x, nullptr);                                                                    \
           ins = ~0u;                                                                                                \
-          if (++pc < len) INSTRUCTION(ins, prog, len, pc, words);                                                   \
+          if (++pc < len) INSTRUCTION(ins, prog, len, pc, words, false);                                            \
         }                                                                                                           \
         if (pc++ >= len) break;                                                                                     \
         const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;                                         \
@@ -2305,7 +2306,7 @@ __global__ __launch_bounds__(256, 1) void k_rns_wide(RnsJob j, size_t count) {
     u32 words = 0;
     for (int pc = 0; pc < len;) {
       u32 ins;
-      INSTRUCTION(ins, prog, len, pc, words);
+      INSTRUCTION(ins, prog, len, pc, words, true);
       ++pc;
       const u32 op = ins & 0xFFu, a = (ins >> 8) & 0xFFFu, b = ins >> 20;
       u32* entry = table + (size_t)a * G::kEntry;
@@ -2323,7 +2324,7 @@ __global__ __launch_bounds__(256, 1) void k_rns_wide(RnsJob j, size_t count) {
         for (;;) {
           e.template extend_to_b<true>(x, y);
           if (pc >= len) break;
-          INSTRUCTION(ins, prog, len, pc, words);
+          INSTRUCTION(ins, prog, len, pc, words, true);
           if (ins != ENG_SQ) break;
           ++pc;
           e.template extend_to_a<true>(x);
