@@ -39,7 +39,7 @@ PEAK_INT8_OPS_PER_S = 5.0e15  # dense
 TRAFFIC_PROFILE = "profiles/k_rns_encrypt_2048bit_b65536_pmc.md"
 TRAFFIC_BYTES_PROFILED = {(2048, 65536): (26846852 + 8591674) * 1024}
 # the kernel of the powers in a batch that fills the chip, by key size
-POWER_KERNEL = {1024: "k_rns", 2048: "k_rns_one", 4096: "k_rns_group"}
+POWER_KERNEL = {1024: "k_rns", 2048: "k_rns_one", 4096: "k_rns_wide"}
 
 
 def montmul_mul32(limbs):
