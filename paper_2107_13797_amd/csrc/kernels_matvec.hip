@@ -561,20 +561,24 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_places(u32 cols, u32* __re
 
 // Rows' products as chains: 2^seg_shift of near-equal length for a row, in the order `order`, and behind them (unless a row
 // is one chain) those that combine a row's. The chains that end in a row's product are launched `portion` at a time, each time
-// with kPortionWords of control words and counter of their own, and into places of their own where there are several.
+// with kPortionWords of control words and counter of their own. Where a row is one chain its product's place is that of the row in
+// the order, and the rows with empty lists, all behind the first *filled, take no part: of narrow sparse matrices they are most, and
+// their way out of the residue form took longer than everything did on limbs. us of whole calls, limbs / all rows / the filled ones,
+// 5 % of the entries non-zero: 4096 bits 65536 by 4 1203 / 1377 / 1003, by 16 1528 / 1520 / 1302, 262144 by 4 2364 / 3050 / 1439;
+// 2048 bits 65536 by 4 509 / 540 / 466, 262144 by 4 880 / 1014 / 600. With no empty rows 65536 by 32 at 2048 bits 2006 / 2011.
 enum { kPortionNext = kChainsControl, kPortionWords = 4 };
 __global__ __launch_bounds__(kBlockThreads) void k_xw_chains(size_t rows, size_t list_stride, int seg_shift, size_t portion,
                                                              const u32* __restrict__ counts, const u32* __restrict__ order,
-                                                             uint4* __restrict__ chains, u32* __restrict__ control,
-                                                             u32* __restrict__ portions) {
-  const size_t items = rows << seg_shift, at = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+                                                             const u32* __restrict__ filled, uint4* __restrict__ chains,
+                                                             u32* __restrict__ control, u32* __restrict__ portions) {
+  const size_t items = rows << seg_shift, leaving = seg_shift ? rows : (size_t)*filled, at = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
   if (at == 0) {
     control[kChainsTotal] = (u32)items;
     control[kChainsColumns] = 0;
   }
   for (size_t i = at; i * portion < rows; i += step) {
     u32* c = portions + i * kPortionWords;
-    c[kChainsTotal] = (u32)std::min(rows - i * portion, portion);
+    c[kChainsTotal] = (u32)(leaving > i * portion ? std::min(leaving - i * portion, portion) : 0);
     c[kChainsColumns] = 1;
     c[kPortionNext] = 0;
   }
@@ -582,7 +586,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_chains(size_t rows, size_t
     const u32 row = order[i >> seg_shift], seg = (u32)i & ((1u << seg_shift) - 1u);
     const u64 len = counts[row];
     const u32 e0 = (u32)((len * seg) >> seg_shift), e1 = (u32)((len * (seg + 1u)) >> seg_shift);
-    const u32 place = rows > portion ? (u32)(i % portion) : (row << seg_shift) + seg;
+    const u32 place = seg_shift ? (row << seg_shift) + seg : (u32)(i % portion);
     chains[i] = make_uint4(place, (u32)(row * list_stride) + e0, e1 - e0, 0u);
     if (seg == 0 && seg_shift) chains[items + row] = make_uint4(row, row << seg_shift, 1u << seg_shift, 0u);
   }
@@ -590,10 +594,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_xw_chains(size_t rows, size_t
 
 // Rows are handed to the wavefronts of k_xw_main in the order of their list lengths, longest
 // first, so that the rows a wavefront multiplies side by side finish together. The lengths are
-// sorted by counting in kLenBins classes.
+// sorted by counting in kLenBins classes, of which the empty lists are one.
 constexpr int kLenBins = 1024;
 __device__ __forceinline__ u32 length_bin(u32 len, size_t longest) {
-  return (u32)(((u64)len * (u64)(kLenBins - 1)) / (u64)(longest ? longest : 1));
+  return len == 0u ? 0u : 1u + (u32)(((u64)len * (u64)(kLenBins - 2)) / (u64)longest);
 }
 
 // Per row: the list of table entries its product consists of, one per non-zero 8-bit digit
@@ -717,26 +721,32 @@ __device__ __forceinline__ void xw_store_result(u32* dst, Elem<LPT, PAIR>& acc, 
   }
 }
 
-// The same from the residue engine's columns, those of row order[i], if there is an order, at place i
+// The same from the residue engine's columns, those of row order[at + i], if there is an order, at place i. From *filled on the rows
+// of the order are empty: one (r1, as it is stored), and no columns.
 template <int LPT, int T>
 __global__ __launch_bounds__(kBlockThreads, 4) void k_xw_leave(ModRef M, const u32* __restrict__ leave,
                                                                const long long* __restrict__ columns, int stride,
-                                                               size_t rows, const u32* __restrict__ order,
-                                                               u32* __restrict__ out) {
+                                                               size_t rows, const u32* __restrict__ order, size_t at,
+                                                               const u32* __restrict__ filled,
+                                                               const u32* __restrict__ r1, u32* __restrict__ out) {
   constexpr int EL = 2 * LPT * T;
+  const size_t products = !order ? rows : *filled > at ? *filled - at : 0;
   Grp<T> g;
   Batch<T> bt;
   ModRegs<LPT> mod;
   load_mod<LPT, T>(mod, M, g);
   for (size_t base = bt.first(); base < rows; base += bt.stride()) {
     const size_t row = base + bt.gib;
-    const bool active = row < rows;
-    const long long* src = columns + (active ? row : 0) * (size_t)(2 * stride);
+    const bool active = row < rows, product = active && row < products;
+    u32* to = out + (!active ? 0 : order ? order[at + row] : row) * (size_t)EL;
+    if (active && !product)
+      for (int i = g.k; i < EL; i += T) to[i] = r1[i];
+    if (!wave_any(product)) continue;
+    const long long* src = columns + (product ? row : 0) * (size_t)(2 * stride);
     Elem<LPT, true> acc;
     load_columns<LPT, T>(acc.x0, src, g);
     load_columns<LPT, T>(acc.x1, src + stride, g);
-    const size_t to = !active ? 0 : order ? order[row] : row;
-    xw_store_result<LPT, T, true>(out + to * (size_t)EL, acc, active, leave, mod, g);
+    xw_store_result<LPT, T, true>(to, acc, product, leave, mod, g);
   }
 }
 
@@ -927,10 +937,11 @@ XwPlan xw_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
 }
 // Tables and rows in the residue form. Whole calls on limbs / in residues, ms, 70 % zeros. 2048 bits: 65536 by 1 0.482 / 0.492, 16384
 // by 2 0.408 / 0.406; 40000 by 4 0.62 / 0.50, 4096 by 8 0.46 / 0.40, 1000 by 64 0.62 / 0.46, 64 by 256 1.11 / 0.62, 65536 by 32
-// 1.89 / 0.99, 16384 by 256 3.78 / 1.69. 4096 bits: 65536 by 1 1.19 / 1.30; 64 by 4 0.88 / 0.81, 65536 by 4 1.60 / 1.50, 1000 by 8 0.96
-// / 0.89, 4096 by 16 1.31 / 1.01, 2000 by 32 1.29 / 1.02, 300 by 48 1.34 / 1.01, 16384 by 64 4.15 / 2.05. At 1024 bits limbs are the
-// quicker: 16384 by 64 0.54 / 0.69. The shape does not say how many entries are zero: with less than one factor a row limbs are
-// (300000 by 4 with 10 % of one digit 0.84 / 1.05 at 2048, 65536 by 4 with 5 % of two 1.17 / 1.34 at 4096).
+// 1.89 / 0.99, 16384 by 256 3.78 / 1.69. 4096 bits: 65536 by 1 1.19 / 1.30; 64 by 4 0.79 / 0.80, 4096 by 4 0.84 / 0.87, 65536 by 4 1.45
+// / 1.36, 1000 by 8 0.87 / 0.87, 4096 by 16 1.16 / 0.97, 2000 by 32 1.29 / 1.02, 300 by 48 1.34 / 1.01, 16384 by 64 3.70 / 2.00. At
+// 1024 bits limbs are the quicker: 16384 by 64 0.54 / 0.69. The shape does not say how many entries are zero, nor how large they are.
+// At 4096 bits none zero, 64 by 4 0.93 / 0.86, 65536 by 4 3.3 / 2.1; 5 % of one digit, 64 by 4 0.68 / 0.72, 4096 by 4 0.72 / 0.74, 65536
+// by 4 0.98 / 0.85, by 16 1.06 / 1.07.
 // List places and table entries are 32-bit. An entry takes twice the memory of limbs: beyond 2048 columns (tables of 5 GB at 2048
 // bits, 10 at 4096) limbs. Rows take no more than on limbs but for one portion's columns (xw_portion) and 16 bytes each.
 bool xw_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
@@ -1280,8 +1291,9 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
     if (residues) {
       u32* control = ws + kXwControlAt + kChainsControl;
       u32* portions = ws + p.off_portions;
+      const u32* filled = bins + 1;  // the end of the shortest class that is not empty
       HAFLO_LAUNCH(k_xw_chains, launch_shape(ctx, rows << p.seg_shift, 1, 8), st, rows, cols * (size_t)kMaxPos, p.seg_shift,
-                   p.portion, (const u32*)cnt, (const u32*)order, (uint4*)(ws + p.off_chains), control, portions);
+                   p.portion, (const u32*)cnt, (const u32*)order, filled, (uint4*)(ws + p.off_chains), control, portions);
       chains.chains = ws + p.off_chains;
       chains.index = lists;
       chains.out = partial;
@@ -1302,11 +1314,11 @@ int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, 
         rc = rns_chains(ctx, mh, chains, count, count, st);
         if (rc != HAFLO_OK) return rc;
         chains.chains += count * 4;
-        const u32* places = rows > p.portion ? order + at : nullptr;
+        const u32* places = p.seg_shift ? nullptr : order;
         const LaunchShape sh = launch_shape(ctx, count, lanes, 8);
 #define CALL(LPT, T)                                                                                            \
   HAFLO_LAUNCH((k_xw_leave<LPT, T>), sh, st, M, (const u32*)(mh.d_pairs + (size_t)kConstMStored * 2 * mh.nl),  \
-               (const long long*)(ws + p.off_columns), rns_columns(mh), count, places, (u32*)d_out)
+               (const long long*)(ws + p.off_columns), rns_columns(mh), count, places, at, filled, ctx->N.ref().r1, (u32*)d_out)
         HAFLO_DISPATCH_PAIRS(mh, CALL);
 #undef CALL
       }

@@ -249,6 +249,28 @@ def test_forward_matvec_in_residues(emu, bits, kind, rows, cols):  # noqa: F811
     lib.haflo_ctx_destroy(ctx)
 
 
+# 2048 rows leave the form at a time on the one-unit emulated chip, by 8 or 16
+@pytest.mark.parametrize("rows,filled", [(40, 0), (40, 1), (40, 16), (40, 17), (40, 40), (2065, 2047), (2065, 2048), (2065, 2049)])
+def test_forward_matvec_with_empty_rows(emu, rows, filled):  # noqa: F811
+    """Rows without a non-zero entry are one, and take no part in the residue form: none, some, all, and as many others as
+    leave the form at a time."""
+    lib, bits, cols = emu, 2048, 4
+    p, q = oracle_key(bits)
+    nsq, rng = (p * q) ** 2, random.Random(filled)
+    ctx = public_ctx(lib, p * q, bits)
+    cs = [rng.randrange(2, nsq) for _ in range(cols)]
+    x = np.zeros((rows, cols), dtype=np.int32)
+    for row in rng.sample(range(rows), filled):
+        x[row, rng.randrange(cols)] = rng.choice([1, 3])
+    got = matvec(lib, ctx, bits, 1, cs, x, "asked")
+    lib.haflo_ctx_destroy(ctx)
+    power = {(j, k): pow(c, k, nsq) for j, c in enumerate(cs) for k in (1, 3)}
+    want = [1] * rows
+    for row, j in zip(*np.nonzero(x)):
+        want[row] = power[j, x[row, j]]
+    assert got == want
+
+
 @pytest.mark.parametrize("bits,rows,cols", [(512, 1, 1), (512, 130, 2), (1024, 33, 3), (2048, 5, 2)])
 def test_gradient_matvec_on_few_rows(emu, bits, rows, cols):  # noqa: F811
     """Fewer rows than the bucket method needs: it is taken with the workspace asked for, in residues where they serve the key and on
