@@ -877,13 +877,32 @@ XtdPlan xtd_plan(const haflo_ctx* ctx, size_t rows, size_t cols) {
   return p;
 }
 
-// The bucket method (one product per exponent digit instead of four or five, no tables) is the quicker at every size. us, tables /
-// buckets (those in residues at 2048 and 4096 bits): 1024 bits 1 by 1 349 / 260, 64 by 64 445 / 431, 600 by 16 443 / 389, 4000 by 16
-// 943 / 477, 64 by 1024 2518 / 1582; 2048 bits 64 by 1 619 / 443, 600 by 16 1222 / 559, 4000 by 64 2625 / 1045; 4096 bits 64 by 16
-// 1677 / 1188, 1200 by 4 5646 / 1162, 4000 by 64 8706 / 2697. But it takes more memory, and a call on few rows never asked for that:
-// below a number of rows, a setting of the context (haflo_ctx_set_xtd_bucket_min_rows), the tables' workspace is enough. Unless that
-// number was set, such a call asks for the buckets' as well, up to kShortWords of it, and takes them when it gets it.
-constexpr size_t kShortWords = (size_t)1 << 29;  // 2 GiB; the largest that came into question is 4000 by 64 at 4096 bits, 1.5
+// The bucket method forms one product per exponent digit instead of four or five, and no tables, but folds some thousand buckets per
+// column and digit position, and takes more memory, which a call on few rows never asked for: below a number of rows, a setting of
+// the context (haflo_ctx_set_xtd_bucket_min_rows), the tables' workspace is enough. Unless that number was set, such a call asks for
+// the buckets' as well, up to kShortWords of it, and takes them when it gets it. us, tables / buckets on limbs / in residues:
+//   1024 bits, two digits: 1 by 1 354 / 266, 64 by 64 450 / 437, 600 by 16 443 / 389, 1000 by 128 828 / 810, 4000 by 16 980 / 488, 1 by
+//   1024 2512 / 747, 64 by 1024 2537 / 1569; one digit, 5 % of the entries: 1000 by 16 338 / 375, 1000 by 256 1476 / 552.
+//   2048 bits, two digits: 1 by 1 620 / 483 / 435, 64 by 16 657 / 645 / 507, 64 by 64 805 / 914 / 641, 1000 by 16 1598 / 778 / 582, 1 by
+//   1024 4139 / 1730 / 2125; one digit, 5 %: 64 by 64 653 / 600 / 514, 1000 by 16 659 / 656 / 503.
+//   4096 bits, two digits: 1 by 1 1496 / 1050 / 994, 64 by 64 1954 / 1971 / 1544, 64 by 512 5373 / 5119 / 5407, 1000 by 4 4809 / 1415 /
+//   1142, 4000 by 64 8873 / 4443 / 2710; one digit, 5 %: 64 by 64 1444 / 1361 / 1084, 64 by 512 5003 / 2822 / 1815.
+// In residues they are the quicker everywhere, or within 2 % of it (4096 bits, some 64 by 512); on limbs where an entry has two digits, as
+// those of fixed-point features have, but for what few_rows_on_limbs() leaves out. With dense entries of one digit, which is one
+// position to the tables, limbs lose up to a third on up to 64 columns (1024 bits, 1000 by 16 345 / 462).
+// kShortWords is a line of memory and not of speed: from it on limbs where they are below it, then tables. 4096 bits, 4000 by 80 (942 MB on
+// limbs, 1987 in residues) 10.5 / 5.6 / 3.1 ms, by 96 (1129, 2385) 15.0 / 6.4 / 3.5, by 256 (2803, 5959) 45.5 / 14.0 / 7.7; tables take
+// 84 MB. What few rows cost by their columns: 1 by 64 at 4096 bits 176 MB in residues and 1.1 for tables.
+constexpr size_t kShortWords = (size_t)1 << 29;  // 2 GiB
+// Buckets on limbs at 2048 bits, which is where contexts with the private key have them: the middle, where the folds of that many columns
+// fill the chip, but not yet the tables' products. us, tables / buckets, two digits an entry: 16 by 64 775 / 769, 24 by 64 776 / 827, 64
+// by 16 657 / 645, 64 by 24 663 / 724, 128 by 96 995 / 1278, 192 by 96 1437 / 1291, 192 by 128 1160 / 1386, 512 by 160 1660 / 1833, 700
+// by 160 1844 / 1852, 96 by 192 1401 / 1577, 96 by 256 1687 / 1765, 96 by 512 2746 / 2496. At 1024 bits there is no such middle. At
+// 4096 tables gain up to 14 % in it with all entries of two digits and lose 8 to 29 % with three in ten.
+bool few_rows_on_limbs(const haflo_ctx* ctx, size_t rows, size_t cols) {
+  if (ctx->Nh.nl != 72 || rows <= 16 || cols >= 224) return true;
+  return rows < 160 ? cols < 24 : rows >= 640 || cols < 112;
+}
 bool needs_buckets(const haflo_ctx* ctx, size_t rows, size_t cols) {
   const size_t from = ctx->xtd_bucket_min_rows ? ctx->xtd_bucket_min_rows : (size_t)HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT;
   return rows >= from && rows > 0 && xtd_buckets_fit(rows, cols);
@@ -1009,7 +1028,7 @@ size_t ws_xtd_buckets(const haflo_ctx* ctx, size_t rows, size_t cols, bool resid
   if (!cols || !may_use_buckets(ctx, rows, cols) || (residues && !xtd_buckets_in_residues(ctx, rows, cols))) return 0;
   const size_t words = xtd_bucket_layout(ctx, rows, cols, residues).total;
   const bool few = !needs_buckets(ctx, rows, cols);
-  if (words > kShortWords && few) return 0;
+  if (few && (words > kShortWords || !(residues || few_rows_on_limbs(ctx, rows, cols)))) return 0;
   return words * 4 + (residues || few ? 256 : 0);  // their start is aligned to 256 bytes
 }
 

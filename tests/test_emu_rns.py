@@ -306,6 +306,24 @@ def test_gradient_matvec_on_few_rows(emu, bits, rows, cols):  # noqa: F811
     lib.haflo_ctx_destroy(ctx)
 
 
+# both sides of every line of the rule, which is one of limbs at 2048 bits: shape, and whether buckets are asked for
+@pytest.mark.parametrize("bits,shapes", [
+    (2048, {(16, 64): True, (17, 64): False, (159, 23): True, (159, 24): False, (160, 24): True, (160, 111): True, (160, 112): False,
+            (639, 112): False, (640, 112): True, (100, 223): False, (100, 224): True, (17, 1): True}),
+    (1024, {(100, 64): True, (17, 24): True}), (4096, {(100, 64): True, (200, 128): True})])
+def test_gradient_on_few_rows_by_private_contexts(emu, bits, shapes):  # noqa: F811
+    """Without the residue form (contexts with the private key) some shapes of few rows are quicker on tables than by buckets, and
+    those ask for no more than the tables."""
+    p, q = oracle_key(bits)
+    ctx = C.c_void_p()
+    le = [(C.c_uint8 * (bits // 16)).from_buffer_copy(v.to_bytes(bits // 16, "little")) for v in (p, q)]
+    assert emu.haflo_ctx_create_private(le[0], le[1], bits, C.byref(ctx)) == 0
+    got = {s: emu.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_XT_D, *s) > emu.haflo_workspace_bytes_least(ctx, _cabi.OP_MATVEC_XT_D, *s)
+           for s in shapes}
+    emu.haflo_ctx_destroy(ctx)
+    assert got == shapes
+
+
 # Shapes of the residue form next to what bounds its memory (rows alone, columns alone, both), and some beyond it.
 @pytest.mark.parametrize("bits,rows,cols", [
     (2048, 4096, 1), (2048, 65536, 32), (2048, 4096, 1024), (2048, 1 << 20, 1), (2048, 1 << 22, 32), (2048, 1 << 24, 8),
