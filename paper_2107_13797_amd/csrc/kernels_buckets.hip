@@ -894,13 +894,19 @@ constexpr size_t kEnterRows = 1 << 17;  // 75 MB of pairs at 2048 bits; way in o
 // 2048 bits 4.2 -> 1.35 ms), and the chains behind the rounds less than a quarter (0.55 -> 0.17), against a way in. Whole calls on
 // limbs / in residues, ms. 2048 bits: 64 by 16 0.64 / 0.50, 4096 by 1 0.77 / 0.52, 30000 by 1 0.95 / 0.65, 4096 by 16 0.89 / 0.71,
 // 4096 by 32 1.07 / 0.80, 65536 by 4 1.44 / 0.93, 65536 by 32 5.27 / 2.40. 4096 bits: 64 by 2 1.18 / 1.03, 4096 by 1 1.52 / 1.22, 4096
-// by 8 1.75 / 1.39, 65536 by 1 2.63 / 2.14, 65536 by 4 4.16 / 2.69, 65536 by 16 10.4 / 5.3, 600 by 256 6.1 / 4.4. So at every size. The
-// shape does not say how many entries are zero: with 5 % of them non-zero, at 4096 bits, 65536 by 1 1.93 / 1.89, by 8 2.09 / 1.99.
-// Some hundreds of columns of a few rows are still quicker on limbs (16 by 1024 at 2048 bits 2.25 / 2.63). At 1024 bits limbs are the
-// quicker: 65536 by 32 1.78 / 2.59 on blocks of 16 elements, 4096 by 32 0.59 / 0.65. An element takes twice the memory: limbs where
-// the plan would take more than 32 GiB (2048 bits: 131072 by 1024 is still below it, 2^24 by 8 and 2^25 by 1 are not).
+// by 8 1.75 / 1.39, 65536 by 1 2.63 / 2.14, 65536 by 4 4.16 / 2.69, 65536 by 16 10.4 / 5.3, 600 by 256 6.1 / 4.4. The shape does not say
+// how many entries are zero: with 5 % of them non-zero, at 4096 bits, 65536 by 1 1.98 / 1.93, by 8 2.13 / 2.02.
+// Hundreds of columns of a few rows are many short chains, which blocks of 8 elements do not shorten. At 2048 bits they are on limbs, in
+// less than a third of the memory. Both sides of the line, limbs / in residues, all entries of two digits | three in ten | 5 % of one
+// digit, which are the price: 16 by 448 1.41 / 1.43 | 1.19 / 1.31 | 1.03 / 0.80, 16 by 512 1.47 / 1.55 | 1.23 / 1.39 | 1.05 / 0.84, 16 by
+// 1024 2.25 / 2.66 | 1.89 / 2.35 | 1.63 / 1.29, 32 by 512 1.77 / 1.76 | 1.35 / 1.53 | 1.10 / 0.87, 48 by 512 1.99 / 1.88 | 1.46 / 1.61 | 1.13
+// / 0.88. At 4096 bits residues lose less than that and gain more: 16 by 512 3.61 / 3.79 (two digits) and 2.80 / 1.77 (one).
+// At 1024 bits limbs are the quicker: 65536 by 32 1.78 / 2.59 on blocks of 16 elements, 4096 by 32 0.59 / 0.65. An element takes
+// twice the memory: limbs where the plan would take more than 32 GiB (2048 bits: 131072 by 1024 is still below it, 2^24 by 8 and 2^25
+// by 1 are not).
 bool xtd_buckets_in_residues(const haflo_ctx* ctx, size_t rows, size_t cols) {
   if (!ctx->Nh.d_rns || ctx->Nh.nl < 72) return false;
+  if (ctx->Nh.nl == 72 && rows <= 32 && cols >= 512) return false;
   return xtd_bucket_plan(ctx, rows, cols, true).total <= kResidueWords;
 }
 

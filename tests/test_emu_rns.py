@@ -324,6 +324,19 @@ def test_gradient_on_few_rows_by_private_contexts(emu, bits, shapes):  # noqa: F
     assert got == shapes
 
 
+@pytest.mark.parametrize("rows,cols,residues", [(32, 512, False), (1, 1024, False), (33, 512, True), (32, 511, True)])
+def test_gradient_of_many_columns_on_few_rows(emu, rows, cols, residues):  # noqa: F811
+    """At 2048 bits those are quicker on limbs, which take less than half of the memory: the call asks for no more than that."""
+    bits = 2048
+    p, q = oracle_key(bits)
+    ctx = public_ctx(emu, p * q, bits)
+    asked = emu.haflo_workspace_bytes(ctx, _cabi.OP_MATVEC_XT_D, rows, cols)
+    assert emu.haflo_ctx_set_xtd_bucket_min_rows(ctx, 1) == 0
+    on_limbs = emu.haflo_workspace_bytes_least(ctx, _cabi.OP_MATVEC_XT_D, rows, cols)
+    emu.haflo_ctx_destroy(ctx)
+    assert asked > 2 * on_limbs if residues else asked == on_limbs + 256
+
+
 # Shapes of the residue form next to what bounds its memory (rows alone, columns alone, both), and some beyond it.
 @pytest.mark.parametrize("bits,rows,cols", [
     (2048, 4096, 1), (2048, 65536, 32), (2048, 4096, 1024), (2048, 1 << 20, 1), (2048, 1 << 22, 32), (2048, 1 << 24, 8),
