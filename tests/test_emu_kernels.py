@@ -228,6 +228,7 @@ def test_public_context_encrypts_identically(env):
 
 
 def test_matvec_sum(env):
+    """Both matvecs and a summation; the gradient by buckets (the workspace asked for) and on power tables (the least)."""
     lib, ctx, sk, nlw = env
     pk = sk.public
     n = pk.n
@@ -238,10 +239,12 @@ def test_matvec_sum(env):
     npr = np.random.default_rng(5)
     X = npr.integers(-(1 << 19), 1 << 19, size=(7, 3)).astype(np.int32)
     X[0, 0], X[1, 1], X[2, 2] = 0, -1, -2 ** 31
-    w, nb = ws(lib, ctx, _cabi.OP_MATVEC_XT_D, 7, 3)
-    d_o = zeros(lib, (3, nlw))
-    assert lib.haflo_cipher_matvec(ctx, 0, d_c.p, Dev(lib, X).p, 7, 3, d_o.p, w.p, nb, None) == 0
-    assert export(lib, ctx, d_o, 3) == O.matvec(pk, 0, cs, X.tolist())
+    want = O.matvec(pk, 0, cs, X.tolist())
+    for room in ("asked", "least"):
+        w, nb = ws(lib, ctx, _cabi.OP_MATVEC_XT_D, 7, 3, room)
+        d_o = zeros(lib, (3, nlw))
+        assert lib.haflo_cipher_matvec(ctx, 0, d_c.p, Dev(lib, X).p, 7, 3, d_o.p, w.p, nb, None) == 0
+        assert export(lib, ctx, d_o, 3) == want, room
     Y = npr.integers(-(1 << 16), 1 << 16, size=(5, 7)).astype(np.int32)
     Y[npr.random(Y.shape) < 0.5] = 0
     Y[3, :] = 0
@@ -256,17 +259,20 @@ def test_matvec_sum(env):
 
 
 @pytest.mark.parametrize("top", [15, 16, 17, 495, 496, 507375, 507376, 2 ** 31 - 1])
-def test_matvec_signed_digit_boundaries(env, top):
-    """Exponent magnitudes around the points where the signed base-32 recoding of
-    orientation 0 needs one more digit position."""
+@pytest.mark.parametrize("room", ["least", "asked"])
+def test_matvec_signed_digit_boundaries(env, top, room):
+    """Exponent magnitudes around the points where the signed base-32 recoding of orientation 0's power tables (the least
+    workspace) needs one more digit position; the same by buckets (the workspace asked for)."""
     lib, ctx, sk, nlw = env
+    sizes = [f(ctx, _cabi.OP_MATVEC_XT_D, 4, 2) for f in (lib.haflo_workspace_bytes, lib.haflo_workspace_bytes_least)]
+    assert sizes[0] > sizes[1]  # by buckets with the first and not with the second
     pk = sk.public
     rng = random.Random(top)
     cs = [O.encrypt(pk, rng.randrange(pk.n), rng.randrange(1, pk.n)) for _ in range(4)]
     d_c = zeros(lib, (4, nlw))
     assert lib.haflo_import_cipher(ctx, words(lib, cs, BITS // 16).p, d_c.p, None, 4, None) == 0
     X = np.array([[top, -top], [top - 1, 1], [-(top // 2), top // 3], [16, -17]], dtype=np.int64).astype(np.int32)
-    w, nb = ws(lib, ctx, _cabi.OP_MATVEC_XT_D, 4, 2)
+    w, nb = ws(lib, ctx, _cabi.OP_MATVEC_XT_D, 4, 2, room)
     d_o = zeros(lib, (2, nlw))
     assert lib.haflo_cipher_matvec(ctx, 0, d_c.p, Dev(lib, X).p, 4, 2, d_o.p, w.p, nb, None) == 0
     assert export(lib, ctx, d_o, 2) == O.matvec(pk, 0, cs, X.tolist())

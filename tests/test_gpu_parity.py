@@ -65,8 +65,8 @@ def room(request, api, monkeypatch):
     return request.param
 
 
-# X^T [[d]] has two implementations chosen by the row count (power tables below the threshold,
-# buckets above); the threshold is a setting of the context, so either can be forced.
+# X^T [[d]] has two implementations chosen by the row count and the workspace (power tables below the threshold in the least,
+# else buckets); the threshold is a setting of the context, so either can be forced.
 XTD_METHODS = {"tables": 2 ** 64 - 1, "buckets": 1}
 
 
@@ -537,9 +537,8 @@ def test_fore_gradient_chain(api):
 
 
 def test_taylor_loss_sequence(api):
-    """Encrypted Taylor loss: ciphertext parity with the oracle on a size the oracle finishes
-    (the single-column matvec runs through the table method), and the plaintext closed form at
-    a size that takes the bucket method."""
+    """Encrypted Taylor loss: ciphertext parity with the oracle on a size the oracle finishes, with the
+    single-column matvec on power tables and by buckets, and the plaintext closed form at a larger size."""
     bits, s = 1024, 20
     ctx, sk = context(api, bits)
     pk = sk.public
@@ -578,6 +577,9 @@ def test_taylor_loss_sequence(api):
             want, flag = O.taylor_loss(pk, cu_int, cu2_int, [float(v) for v in ug], [float(v) for v in y],
                                        synth.words_to_ints(r3)[0], s)
             assert flag == 1 and dev_to_ints(api.haflo_export_cipher(ctx, out)) == [want]
+            for method in XTD_METHODS:
+                with xtd_method(api, ctx, method):
+                    assert torch.equal(out, api.haflo_taylor_loss(ctx, c_u, c_u2, to_dev(ug), to_dev(y), to_dev(r3), s))
 
 
 @pytest.mark.parametrize("kind", ["int32_range", "one_hot", "sparse_small", "many_columns"])
