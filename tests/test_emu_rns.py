@@ -271,7 +271,7 @@ def test_forward_matvec_with_empty_rows(emu, rows, filled):  # noqa: F811
     assert got == want
 
 
-@pytest.mark.parametrize("bits,rows,cols", [(512, 1, 1), (512, 130, 2), (1024, 33, 3), (2048, 5, 2)])
+@pytest.mark.parametrize("bits,rows,cols", [(512, 1, 1), (512, 130, 2), (1024, 33, 3), (2048, 1, 1), (2048, 5, 2)])
 def test_gradient_matvec_on_few_rows(emu, bits, rows, cols):  # noqa: F811
     """Fewer rows than the bucket method needs: it is taken with the workspace asked for, in residues where they serve the key and on
     limbs (one byte less than that), and the tables with the least, which has no room for buckets: the same ciphertexts as the

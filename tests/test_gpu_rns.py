@@ -226,7 +226,9 @@ def exponents(rows, cols, top, seed):
     x = torch.randint(-top, top, (rows, cols), dtype=torch.int32, device="cuda", generator=gen)
     x[torch.rand(x.shape, device="cuda", generator=gen) < 0.3] = 0
     x[:, cols // 2] = 1024 * 3 + 5
-    x[0, 0], x[1, 0] = -2 ** 31, 2 ** 31 - 1
+    x[0, 0] = -2 ** 31
+    if rows > 1:
+        x[1, 0] = 2 ** 31 - 1
     return x
 
 
@@ -252,9 +254,11 @@ def test_gradient_matvec_in_residues_matches_limb_arithmetic(bits, rows, cols, t
     assert torch.equal(api.haflo_cipher_matvec(ctx, 0, c, x), matvec_on_limbs(api, ctx, 0, c, x))
 
 
-# fewer rows than the bucket method needs: one, less and more than a chunk of 16 and of 32, next to the threshold; one column and many
+# fewer rows than the bucket method needs: one, less and more than a chunk of 16 and of 32, next to the threshold; one column and many,
+# up to the most that buckets take and where those are on limbs at 2048 bits
 @pytest.mark.parametrize("bits", [512, 1024, 2048, 4096])
-@pytest.mark.parametrize("rows,cols,top", [(2, 1, 3), (15, 7, 1 << 18), (16, 40, 600), (33, 64, 1 << 17), (700, 3, 40), (4095, 5, 1 << 18)])
+@pytest.mark.parametrize("rows,cols,top", [(1, 1, 3), (2, 1, 3), (15, 7, 1 << 18), (16, 40, 600), (33, 64, 1 << 17), (700, 3, 40), (4095, 5, 1 << 18),
+                                           (1, 1024, 1 << 18), (3, 301, 1 << 18), (32, 513, 600), (35, 511, 1 << 17), (200, 113, 600)])
 def test_gradient_matvec_on_few_rows_matches_tables(bits, rows, cols, top):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
