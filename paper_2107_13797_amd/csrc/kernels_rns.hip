@@ -1172,6 +1172,7 @@ struct RnsGroup {
   static constexpr int kTileBytes = rns::tile_bytes(NR, 16);
   static constexpr bool kHeldCst = Shared::kHeldCst;
   static_assert(TILES >= kLimbTiles, "every tile has a wavefront");
+  static_assert(!LISTS || (PAIR && FOLD), "elements in memory by themselves are taken by halves");
   struct State {
     u32 a0[TW], a1[TW], b0[TW], b1[TW];
   };
@@ -1358,7 +1359,7 @@ struct RnsGroup {
     for (int i = 0; i < TW; ++i) v[i] = SQ ? own(x, i) : entry(y, i);
     multiply<SQ>(x, v, [] {});
   }
-  __device__ __forceinline__ void begin() {}
+  __device__ __forceinline__ void begin() {}  // for run_lists(): all matrices are held, none on its way
   // `meanwhile` asks for what the next product takes, behind this one's first barrier
   template <bool SQ, class F>
   __device__ __forceinline__ void multiply(State& x, const Quad (&v)[TW], const F& meanwhile) {
@@ -1457,27 +1458,22 @@ struct RnsGroup {
     const Twin v = *(const Twin*)entry_at(entry, i);
     return Quad{v[0], 0, v[1], 0};
   }
-  // The same of an element in memory by itself (see item_words): where the word of this lane's half (kBoth: of half x) is
-  __device__ __forceinline__ int item_at(int base, int x, int i) const {
-    const int t = tile(i), half = kBoth ? x : lane >> 3 & 1;
+  // LISTS: the same of an element in memory by itself (see item_words): where the word of this lane's half is
+  __device__ __forceinline__ int item_at(int base, int i) const {
+    const int t = tile(i), half = lane >> 3 & 1;
     const int quad = t < 4 * kFull ? 2 * (t / 4) + half : 2 * kFull, word = t < 4 * kFull ? t % 4 : 2 * half + t % 4;
     return base * (rns::item_words(NR) / 2) + (quad * 4 + g) * 4 + word;
   }
   __device__ __forceinline__ void load_item(Quad (&v)[TW], const u32* item) const {
 #pragma unroll
-    for (int i = 0; i < TW; ++i)
-      v[i] = Quad{item[item_at(0, 0, i)], kBoth ? item[item_at(0, 1, i)] : 0u, item[item_at(1, 0, i)], kBoth ? item[item_at(1, 1, i)] : 0u};
+    for (int i = 0; i < TW; ++i) v[i] = Quad{item[item_at(0, i)], 0u, item[item_at(1, i)], 0u};
   }
   __device__ __forceinline__ void store_item(const State& x, u32* item) const {
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
       if (!mine(i)) continue;
-      item[item_at(0, 0, i)] = x.a0[i];
-      item[item_at(1, 0, i)] = x.b0[i];
-      if constexpr (kBoth) {
-        item[item_at(0, 1, i)] = x.a1[i];
-        item[item_at(1, 1, i)] = x.b1[i];
-      }
+      item[item_at(0, i)] = x.a0[i];
+      item[item_at(1, i)] = x.b0[i];
     }
   }
   static __device__ __forceinline__ void set(State& x, const Quad (&v)[TW]) {
@@ -1485,10 +1481,6 @@ struct RnsGroup {
     for (int i = 0; i < TW; ++i) {
       x.a0[i] = v[i][0];
       x.b0[i] = v[i][2];
-      if constexpr (kBoth) {
-        x.a1[i] = v[i][1];
-        x.b1[i] = v[i][3];
-      }
     }
   }
   __device__ __forceinline__ void store_state(const State& x, u32* entry) const {
@@ -2430,10 +2422,10 @@ __device__ __forceinline__ void run_lists(G& e, const RnsLists& j, ListShared& s
     }
   }
 }
-template <int NR, int TW, int W, int TW1, int W1, bool FOLD>
+template <int NR, int TW, int W, int TW1, int W1>
 __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_lists(RnsLists j) {
-  using Main = RnsGroup<NR, TW, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
-  using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
+  using Main = RnsGroup<NR, TW, W + W1, W * TW + W1 * TW1, true, true, true>;
+  using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, true, true, true>;
   __shared__ __align__(16) typename Main::Shared shared;
   __shared__ ListShared lists;
   if (j.live && (size_t)blockIdx.x * Main::kElements >= *j.live) return;
@@ -2477,11 +2469,10 @@ __global__ __launch_bounds__(256, 1) void k_rns_wide_enter(const u32* __restrict
   }
 }
 
-// RnsChains on blocks of 8 or 16 elements, as k_rns_chains does on wavefronts of 16
+// RnsChains on blocks of 8 elements, as k_rns_chains does on wavefronts of 16
 template <class G>
 __device__ __forceinline__ void run_chains(G& e, const RnsChains& j, unsigned total) {
   const bool columns = __builtin_amdgcn_readfirstlane((int)j.control[kChainsColumns]) != 0;
-  e.begin();
   for (unsigned first = blockIdx.x * G::kElements; first < total; first += gridDim.x * G::kElements) {
     const unsigned own = first + (unsigned)(e.lane & (G::kElements - 1));
     const bool active = own < total;
@@ -2510,10 +2501,10 @@ __device__ __forceinline__ void run_chains(G& e, const RnsChains& j, unsigned to
     else if (active) e.store_item(x, j.out + (size_t)c[0] * rns::item_words(G::kRegs));
   }
 }
-template <int NR, int TW, int W, int TW1, int W1, bool FOLD>
+template <int NR, int TW, int W, int TW1, int W1>
 __global__ __launch_bounds__((W + W1) * 64, (W + W1 + 3) / 4) void k_rns_group_chains(RnsChains j) {
-  using Main = RnsGroup<NR, TW, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
-  using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, true, FOLD, true>;
+  using Main = RnsGroup<NR, TW, W + W1, W * TW + W1 * TW1, true, true, true>;
+  using Rest = RnsGroup<NR, TW1, W + W1, W * TW + W1 * TW1, true, true, true>;
   __shared__ __align__(16) typename Main::Shared shared;
   const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane((int)j.control[kChainsTotal]);
   if (blockIdx.x * Main::kElements >= total) return;
@@ -2681,14 +2672,11 @@ int rns_lists(const haflo_ctx* ctx, const ModHost& m, RnsLists j, size_t bound, 
   const unsigned blocks = (unsigned)std::max(group_blocks(ctx, nr, bound, 1, true), (size_t)1);
   j.tables = m.d_rns;
   j.nl = m.nl;
-#define GROUP(NR, TW, W, TW1, W1) \
-  hipLaunchKernelGGL((k_rns_lists<NR, TW, W, TW1, W1, true>), dim3(blocks), dim3((W + W1) * 64), 0, st, j)
   switch (nr) {
-    case 18: GROUP(18, 2, 8, 1, 2); break;
+    case 18: hipLaunchKernelGGL((k_rns_lists<18, 2, 8, 1, 2>), dim3(blocks), dim3(640), 0, st, j); break;
     case 36: hipLaunchKernelGGL(k_rns_wide_lists, dim3(blocks), dim3(256), 0, st, j); break;
     default: return HAFLO_EINVAL;
   }
-#undef GROUP
   return hip_status(hipGetLastError());
 }
 
@@ -2704,17 +2692,14 @@ int rns_chains(const haflo_ctx* ctx, const ModHost& m, RnsChains j, size_t bound
   }
   const bool fold = nr == 18 || expected <= (size_t)ctx->num_cu * 8 * group_blocks_per_cu(nr);
   const unsigned blocks = (unsigned)std::max(group_blocks(ctx, nr, bound, 1, fold), (size_t)1);
-#define GROUP(NR, TW, W, TW1, W1, FOLD) \
-  hipLaunchKernelGGL((k_rns_group_chains<NR, TW, W, TW1, W1, FOLD>), dim3(blocks), dim3((W + W1) * 64), 0, st, j)
   switch (nr) {
-    case 18: GROUP(18, 2, 8, 1, 2, true); break;
+    case 18: hipLaunchKernelGGL((k_rns_group_chains<18, 2, 8, 1, 2>), dim3(blocks), dim3(640), 0, st, j); break;
     case 36:
       if (fold) hipLaunchKernelGGL((k_rns_wide_chains<true>), dim3(blocks), dim3(256), 0, st, j);
       else hipLaunchKernelGGL((k_rns_wide_chains<false>), dim3(blocks), dim3(256), 0, st, j);
       break;
     default: return HAFLO_EINVAL;
   }
-#undef GROUP
   return hip_status(hipGetLastError());
 }
 
