@@ -59,16 +59,6 @@ def nonzero_digits_signed(X, torch, digit_bits, positions):
     return total
 
 
-def positions_needed(maxmag, digit_bits, max_positions):
-    base = 1 << digit_bits
-    offset = 0
-    for s in range(1, max_positions):
-        offset = offset * base + base // 2
-        if maxmag + offset < base ** s:
-            return s
-    return max_positions
-
-
 def run_configs(which=(1, 2, 3, 4, 5), reps=3, verbose=True):
     """-> {cfg: [ {op, units, unit, ms, rate, bound, frac, note}, ... ]}"""
     import numpy as np
@@ -163,15 +153,10 @@ def run_configs(which=(1, 2, 3, 4, 5), reps=3, verbose=True):
             assert torch.equal(c, c_own)
             del c_own
             X = api.haflo_encode_exponents_f32(Xf, cfg["scale_x"])
-            maxmag = int(X.to(torch.int64).abs().max().item())
-            buckets = R >= 4096
-            if buckets:
-                digits = nonzero_digits_signed(X, torch, 10, 4)
-            else:
-                digits = nonzero_digits_signed(X, torch, 5, positions_needed(maxmag, 5, 7))
+            digits = nonzero_digits_signed(X, torch, 10, 4)  # by buckets, with the workspace that the binding asks for
             ms, out = timed(lambda: api.haflo_cipher_matvec(pub, 0, c, X))
             alu("matvec X^T[[d]]", R * F, ms, "entries", digits / (R * F), lc,
-                "%s method, %.2f non-zero digits (one product each) per entry" % ("bucket" if buckets else "table", digits / (R * F)))
+                "bucket method, %.2f non-zero digits (one product each) per entry" % (digits / (R * F)))
             ms, pl = timed(lambda: api.haflo_decrypt(own, out))
             alu("decrypt", F, ms, "decryptions", dec_mm, dec_limbs)
             ms, _ = timed(lambda: api.haflo_decode(own, pl, cfg["scale_d"] + cfg["scale_x"]))

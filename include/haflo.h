@@ -125,9 +125,10 @@ int haflo_ctx_info(const haflo_ctx* ctx, uint32_t* n_bits, uint32_t* cipher_limb
 /* Row count from which X^T [[d]] (haflo_cipher_matvec, orientation 0) takes
  * the bucket method instead of per-base power tables; both give the same
  * ciphertext bits. By default it takes it from
- * HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT rows on, and on fewer rows when it gets the
- * workspace that it asks for (haflo_workspace_bytes), which is more than the
- * tables' (haflo_workspace_bytes_least). The setting belongs to the context and is read by the
+ * HAFLO_XTD_BUCKET_MIN_ROWS_DEFAULT rows on, and on fewer rows where it is the
+ * quicker, takes at most 2 GiB, and gets the workspace that the call then asks
+ * for (haflo_workspace_bytes); tables need less (haflo_workspace_bytes_least).
+ * The setting belongs to the context and is read by the
  * matvec itself and by every workspace query that contains one
  * (haflo_workspace_bytes for the matvec and the Taylor loss, the store's
  * calls), so change it only between a query and the call it sizes if both are
@@ -293,8 +294,9 @@ int haflo_scalar_mul_i64_bcast(const haflo_ctx* ctx, const void* d_c, int64_t k,
  * An empty or all-zero product is an encryption-free 1. d_out may not alias
  * d_c. Workspace: HAFLO_OP_MATVEC_XT_D / HAFLO_OP_MATVEC_X_W with the shape.
  * Orientation 0 has two implementations with identical results: the bucket
- * method, and per-base power tables for more than 1024 columns and for matrices
- * of fewer than 4096 rows in a workspace without room for the buckets; the row
+ * method, and per-base power tables for more than 1024 columns, and for matrices
+ * of fewer than 4096 rows in a workspace without room for the buckets, or where
+ * tables are the quicker (some shapes at 2048 bits, private contexts); the row
  * threshold is a setting of the context (haflo_ctx_set_xtd_bucket_min_rows).
  */
 int haflo_cipher_matvec(const haflo_ctx* ctx, int orientation, const void* d_c, const int32_t* d_X, size_t rows,

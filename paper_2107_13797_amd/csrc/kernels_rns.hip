@@ -1506,9 +1506,10 @@ struct RnsGroup {
 // The engine of 4096-bit moduli, whose matrices, 630 KB, fit neither a wavefront's registers nor the LDS: the slots of 16 (FOLD: 8)
 // elements spread over a block of four wavefronts, one to a SIMD, each with all 512 of its registers and nine tiles. Against twelve
 // wavefronts of three tiles, the form before:
-// - the operand of a matrix product is read from LDS once by each of four wavefronts, and not of twelve: 72 KB instead of 216;
+// - the operand of a matrix product is read from LDS once by each of four wavefronts, and not of twelve: 144 KB instead of 432 for the
+//   two matrix products of a modular one;
 // - of the 18 blocks of both matrices a tile has, 10 stay on the compute unit instead of 6: 7 in registers, in the half that only
-//   loads and the matrix unit reach, and three in LDS. 288 KB instead of 420 come from L2 for a product;
+//   loads and the matrix unit reach, and three in LDS. 288 KB instead of 420 come from L2 for a modular product;
 // - a matrix product goes tile by tile, with the vector unit's work on one tile between the matrix instructions of the next: the
 //   phases of the twelve wavefronts lay one after the other between their barriers.
 // ms before and now: encryption of 64 elements 17.8 / 12.6, 3001 21.7 / 18.8, 4096 25.5 / 21.4, 20000 125.6 / 105.1; gradient 20000 by
@@ -2455,7 +2456,8 @@ __global__ __launch_bounds__(256, 1) void k_rns_wide_lists(RnsLists j) {
 }
 
 // k_rns_enter for 4096-bit moduli, on blocks of 16 elements. What bounds it are the matrices of the way in and of the way back, which
-// stream from L2 for 16 elements at a time: 20000 elements 86 us.
+// stream from L2 for 16 elements at a time, those of the way in tile after tile: 20000 elements 86 us, 65536 233 to 243 (205 on blocks
+// of twelve wavefronts, the form before).
 __global__ __launch_bounds__(256, 1) void k_rns_wide_enter(const u32* __restrict__ tables, const u32* __restrict__ in,
                                                            size_t count, int nl, u32* __restrict__ items) {
   using G = Wide<false>::Chains;
